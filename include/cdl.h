@@ -22,7 +22,7 @@
  *   - Step size and sharpness are HOST scalars.
  *   - `ws` is caller-owned device scratch of at least the size the matching *_workspace_bytes()
  *     query returns (256-byte aligned); the library allocates and frees nothing and keeps no state
- *     between calls except the last HIP error code.  Two calls may share `ws` only if they are
+ *     between calls except the last HIP error code and a count of calls.  Two calls may share `ws` only if they are
  *     ordered on one stream.
  *   - `hip_stream` is a hipStream_t (NULL = the default stream).  Calls enqueue kernels and return
  *     without synchronising.  Outputs are overwritten, never accumulated into.

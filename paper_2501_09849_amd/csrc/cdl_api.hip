@@ -1,10 +1,12 @@
 // The C boundary of libcdl: argument validation (host only, before any GPU call) and dispatch.
 #include "cdl_internal.h"
+#include "cdl_finish.h"
 
 #include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <random>
 #include <vector>
 
 namespace cdl {
@@ -23,6 +25,17 @@ int check_launch()
 {
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? (int)CDL_OK : hip_failed(e);
+}
+
+unsigned long long next_finish_tag()
+{
+    // a counter from a random start, its bits mixed (the finalizer of the splitmix64 generator): distinct for 2^64 calls,
+    // and nothing that a workspace's old contents would hold by chance
+    static std::atomic<unsigned long long> count{((unsigned long long)std::random_device{}() << 32) | std::random_device{}()};
+    unsigned long long z = count.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
 }
 
 // ---- per-kernel timing ---------------------------------------------------------------------

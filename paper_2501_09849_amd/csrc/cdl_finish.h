@@ -1,0 +1,118 @@
+// Adding up per-block results inside the kernel that made them (not installed).
+//
+// A kernel whose blocks each leave a partial result is followed by a second, tiny launch that adds the partials up.  For
+// a small tensor that launch costs as much as the pass itself (a tensor of 32 K entries: 4.4 us, and 7.8 us for the
+// launch that adds up its sixteen histograms, and 3 - 4 us of host time), so where a grid has few blocks the block with
+// the highest number waits for the others and finishes the job itself (6.3 us in all).  Large grids keep the second
+// launch: there the waiting block reads a lot, from memory that is busy with the stores of the tensor.
+//
+// What bounds the hand-over is the number of trips to memory, one after the other, between blocks on different XCDs,
+// about 0.7 us each.  A flag behind the data would cost four (data out and acknowledged, flag out, flag in, data in).
+// So the data is its own flag: every record carries a check word, its contents combined with the launch's tag, and the
+// reader polls the record until the check word fits - one trip out, one in, no order needed between the stores of a
+// record.  Records are written and read with device-scope relaxed atomics, which bypass the caches that the XCDs do
+// not share.
+//
+// The records live in the caller's workspace, whose contents are arbitrary: the tag is a 64-bit number that no other
+// launch of the process uses, and the reader spoils the check word of every record it has taken, so that a captured
+// launch can be replayed with the tag it was captured with.  Every wait ends: a block only ever waits for blocks with
+// lower numbers, and those wait for nobody.
+#pragma once
+
+#include "cdl_internal.h"
+
+namespace cdl {
+
+// A tag no other launch of this process has (host).
+unsigned long long next_finish_tag();
+
+__device__ __forceinline__ void device_store(unsigned long long *p, unsigned long long v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long device_load(const unsigned long long *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+constexpr int kFinishMaxBlocks = 256;
+
+// What becomes of the per-block sums of the two scalar gradients.
+struct ScalarFinish {
+    double *partial;               // [gridDim.x][2]: left there for scalar_finalize_kernel; null: finished in the kernel
+    unsigned long long *records;   // [gridDim.x][4]
+    unsigned long long tag;
+    double mul_d, mul_a;
+    float *d_delta, *d_alpha;      // [1] or null
+};
+
+// d_delta = mul_d * sum over blocks of acc_d, d_alpha = mul_a * the same of acc_a; the sums run over threads and
+// blocks in a fixed order.  Called by all T threads of every block.
+template <int T>
+__device__ __forceinline__ void scalar_finish(double acc_d, double acc_a, const ScalarFinish &f)
+{
+    __shared__ double red_d[T / 64], red_a[T / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto block_sum = [&](double &d, double &a) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            d += __shfl_down(d, off, 64);
+            a += __shfl_down(a, off, 64);
+        }
+        if (lane == 0) { red_d[wave] = d; red_a[wave] = a; }
+        __syncthreads();
+        d = 0.0; a = 0.0;
+        if (threadIdx.x == 0)
+            for (int w = 0; w < T / 64; ++w) { d += red_d[w]; a += red_a[w]; }
+        __syncthreads();
+    };
+    block_sum(acc_d, acc_a);
+    if (f.partial) {
+        if (threadIdx.x == 0) {
+            f.partial[2 * (size_t)blockIdx.x] = acc_d;
+            f.partial[2 * (size_t)blockIdx.x + 1] = acc_a;
+        }
+        return;
+    }
+    const int last = (int)gridDim.x - 1;
+    // (the products keep the check word from fitting a record of which only one word has changed)
+    auto check = [&](unsigned long long x, unsigned long long y) {
+        return (x * 0x9E3779B97F4A7C15ull + y * 0xBF58476D1CE4E5B9ull) ^ f.tag;
+    };
+    if ((int)blockIdx.x != last) {
+        if (threadIdx.x == 0) {
+            unsigned long long *r = f.records + 4 * (size_t)blockIdx.x;
+            const unsigned long long x = (unsigned long long)__double_as_longlong(acc_d), y = (unsigned long long)__double_as_longlong(acc_a);
+            device_store(r, x);
+            device_store(r + 1, y);
+            device_store(r + 2, check(x, y));
+        }
+        return;
+    }
+    if (last > 0) {
+        static_assert(kFinishMaxBlocks <= T, "one record per thread");
+        double d = 0.0, a = 0.0;
+        if ((int)threadIdx.x < last) {
+            unsigned long long *r = f.records + 4 * (size_t)threadIdx.x;
+            unsigned long long x, y, z;
+            do {
+                x = device_load(r);
+                y = device_load(r + 1);
+                z = device_load(r + 2);
+            } while (z != check(x, y));
+            d = __longlong_as_double((long long)x);
+            a = __longlong_as_double((long long)y);
+            device_store(r + 2, 0ull);
+        }
+        const double own_d = acc_d, own_a = acc_a;
+        block_sum(d, a);
+        acc_d = d + own_d;
+        acc_a = a + own_a;
+    }
+    if (threadIdx.x == 0) {
+        if (f.d_delta) *f.d_delta = (float)(acc_d * f.mul_d);
+        if (f.d_alpha) *f.d_alpha = (float)(acc_a * f.mul_a);
+    }
+}
+
+}  // namespace cdl

@@ -25,6 +25,7 @@
 //          t^(j) exp(-kappa j^2), all multiplied by t^2 so that they are a polynomial in t;
 //   W = 3, 4: one exponential per level;  larger W: a loop over the band (soft regime).
 #include "cdl_internal.h"
+#include "cdl_finish.h"
 #include "cdl_quantizer_math.h"
 
 #include <math.h>
@@ -45,6 +46,127 @@ constexpr int kMaxHistTrips = 16;
 constexpr int kMargThreads = 512;   // threads of a block that builds a histogram
 constexpr int kHistScaleBits = 21;
 
+// What becomes of the per-block histograms: the marginal PMF and its entropy.
+struct MargFinish {
+    unsigned long long *rows;      // [gridDim.x][n_levels]: left there for marginal_finalize_kernel; null: finished in the kernel
+    unsigned long long *records;   // [blocks][n_levels][2]
+    unsigned long long tag;
+    double inv_n;                  // 1 / (n * 2^s)
+    float *marg;                   // [n_levels] or null
+    float *entropy_bits;           // [1] or null
+};
+
+// A record is a 64-bit sum and, as its check word, the sum combined with the tag.
+__device__ __forceinline__ void marginal_publish(unsigned long long v, size_t at, const MargFinish &f)
+{
+    device_store(f.records + 2 * at, v);
+    device_store(f.records + 2 * at + 1, v ^ f.tag);
+}
+
+// The last block's part, for all its T threads: adds the records of `rows` rows to `own` (thread i < n_levels: the
+// block's own sum for level i), normalises by n * 2^s and adds up the entropy terms in a fixed order.  The sums are
+// exact 64-bit integers, so their order does not matter.
+template <int T, int U>
+__device__ __forceinline__ void marginal_collect(unsigned long long own, int rows, int n_levels, const MargFinish &f)
+{
+    __shared__ unsigned long long red[T];
+    if (rows > 0) {
+        // threads: `lv` levels (a power of two) times T / lv rows at a time, U records in flight per thread
+        int lg = 1;
+        while ((1 << lg) < n_levels) ++lg;
+        const int lv = 1 << lg, level = (int)threadIdx.x & (lv - 1), sub = (int)threadIdx.x >> lg, subs = T >> lg;
+        unsigned long long s = 0ull;
+        if (level < n_levels) {
+            for (int r = sub; r < rows; r += U * subs) {
+                unsigned long long v[U];
+                bool waiting = true;
+                while (waiting) {
+                    unsigned long long c[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        // (past the end: the thread's first record once more)
+                        const int row = r + u * subs < rows ? r + u * subs : r;
+                        const unsigned long long *q = f.records + 2 * ((size_t)row * n_levels + level);
+                        v[u] = device_load(q);
+                        c[u] = device_load(q + 1);
+                    }
+                    waiting = false;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) waiting = waiting || (v[u] ^ c[u]) != f.tag;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (r + u * subs < rows) {
+                        s += v[u];
+                        device_store(f.records + 2 * ((size_t)(r + u * subs) * n_levels + level) + 1, v[u]);
+                    }
+            }
+        }
+        red[threadIdx.x] = s;
+        __syncthreads();
+        if ((int)threadIdx.x < lv)
+            for (int q = 0; q < subs; ++q) own += red[q * lv + threadIdx.x];
+    }
+    double h = 0.0;
+    if ((int)threadIdx.x < n_levels) {
+        const double m = (double)own * f.inv_n;
+        if (f.marg) f.marg[threadIdx.x] = (float)m;
+        h = m > 0.0 ? -m * log2(m) : 0.0;
+    }
+    __shared__ double hs[4];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) h += __shfl_down(h, off, 64);
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) hs[threadIdx.x >> 6] = h;
+    __syncthreads();
+    if (threadIdx.x == 0 && f.entropy_bits) *f.entropy_bits = (float)((hs[0] + hs[1]) + (hs[2] + hs[3]));
+}
+
+// The end of a kernel whose blocks have histograms.
+// Thread i < n_levels has the block's sum for level i.
+// FEW: the last block finishes (a template parameter: marginal_collect takes a kernel from 31 to 64
+// registers, the most with which eight waves of it fit a SIMD).
+template <int T, bool FEW>
+__device__ __forceinline__ void marginal_end(unsigned long long own, int n_levels, const MargFinish &f)
+{
+    if (FEW) {
+        if (blockIdx.x == gridDim.x - 1) marginal_collect<T, 8>(own, (int)blockIdx.x, n_levels, f);
+        else if ((int)threadIdx.x < n_levels) marginal_publish(own, (size_t)blockIdx.x * n_levels + threadIdx.x, f);
+    } else if ((int)threadIdx.x < n_levels) {
+        f.rows[(size_t)blockIdx.x * n_levels + threadIdx.x] = own;
+    }
+}
+
+// The rows of a large grid.  Grid: (ceil(levels / 8), chunks), about 64 blocks in all: a block adds its chunk of the
+// rows for eight levels (32 rows at a time, 64 contiguous bytes per row); the last block adds the chunks.  (A block for
+// all levels of every 32nd row instead: 5.4 us for 1024 rows of 31 levels, but 9.8 for 255, where the last block then
+// polls 8 K records.)
+constexpr int kFinChunks = 16;
+constexpr int kFinThreads = 256, kFinGroups = kFinThreads / 8;
+
+__global__ __launch_bounds__(kFinThreads)
+void marginal_finalize_kernel(const unsigned long long *__restrict__ rows, int n_rows, int n_levels, MargFinish fin)
+{
+    __shared__ unsigned long long red[kFinGroups][8];
+    const int b8 = threadIdx.x & 7, grp = threadIdx.x >> 3;
+    const int level = blockIdx.x * 8 + b8;
+    const int rows_per = (n_rows + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int r0 = blockIdx.y * rows_per, r1 = min(n_rows, r0 + rows_per);
+    unsigned long long s = 0ull;
+    if (level < n_levels) {
+#pragma unroll 8
+        for (int row = r0 + grp; row < r1; row += kFinGroups) s += rows[(size_t)row * n_levels + level];
+    }
+    red[grp][b8] = s;
+    __syncthreads();
+    if (threadIdx.x < 8 && level < n_levels) {
+        unsigned long long tot = 0ull;
+        for (int q = 0; q < kFinGroups; ++q) tot += red[q][threadIdx.x];
+        marginal_publish(tot, (size_t)blockIdx.y * n_levels + level, fin);
+    }
+    if (blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1)
+        marginal_collect<kFinThreads, 4>(0ull, (int)gridDim.y, n_levels, fin);
+}
+
 // ------------------------------------------------------------------------------------------
 // Forward kernel.  One thread handles four consecutive entries per trip of a grid-stride loop
 // (one 16-byte load, one 16-byte store of soft values, one 4-byte store of indices).
@@ -59,8 +181,7 @@ constexpr int kHistScaleBits = 21;
 // kernel at 255 levels, -22 % on the pass that only builds the histogram).  s comes from
 // kHistScaleBits: with at most kMaxHistTrips trips of the loop a cell never exceeds 2^31.
 // kPad spare bins on each side take the zero weights of levels that do not exist.  At the end
-// the block adds the copies into one 64-bit partial histogram row of `partial`; block 0
-// also clears the ticket that the finalize kernel uses.
+// the block adds the copies into 64-bit sums, and marginal_finish adds these over all blocks.
 // ------------------------------------------------------------------------------------------
 // Quantizes four entries: soft values, level indices, and (MARG) their CPMFs into the histogram.
 template <int W, bool IDX, bool MARG>
@@ -103,12 +224,11 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
     }
 }
 
-template <int W, bool IDX, bool SOFT, bool MARG>
+template <int W, bool IDX, bool SOFT, bool MARG, bool FEW>
 __global__ __launch_bounds__(MARG ? kMargThreads : kQuantThreads)
 void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
                          int8_t *__restrict__ idx, float *__restrict__ soft,
-                         unsigned long long *__restrict__ partial /* [gridDim.x][n_levels] */,
-                         unsigned int *__restrict__ ticket)
+                         MargFinish fin)
 {
     extern __shared__ unsigned int lds_hist[];  // [n_levels + 2 kPad][32] when MARG
     constexpr int R = 32;
@@ -117,7 +237,6 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
     unsigned int *my_hist = lds_hist + (threadIdx.x & (R - 1));
     if (MARG) {
         for (int i = threadIdx.x; i < bins * R; i += T) lds_hist[i] = 0u;
-        if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;
         __syncthreads();
     }
 
@@ -149,89 +268,25 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
 
     if (MARG) {
         __syncthreads();
-        for (int i = threadIdx.x; i < k.n_levels; i += T) {
-            unsigned long long s = 0ull;
-            const unsigned int *row = lds_hist + (i + kPad) * R;
+        unsigned long long own = 0ull;
+        if ((int)threadIdx.x < k.n_levels) {
+            const unsigned int *row = lds_hist + ((int)threadIdx.x + kPad) * R;
 #pragma unroll
-            for (int r = 0; r < R; ++r) s += row[(r + i) & (R - 1)];   // rotated start: no bank conflicts
-            partial[(size_t)blockIdx.x * k.n_levels + i] = s;
+            for (int r = 0; r < R; ++r) own += row[(r + (int)threadIdx.x) & (R - 1)];   // rotated start: no bank conflicts
         }
-    }
-}
-
-// Sums the per-block fixed-point histograms (exact 64-bit integers, so the order does not matter),
-// normalises by n * 2^s and adds up the entropy terms.  Grid: (ceil(levels / 8), chunks <= kFinChunks) with
-// about 64 blocks in all (every block ends with an atomic on one ticket word, and those serialize at
-// roughly 80 ns each); a block sums its share of the rows for eight levels (32 rows at a time, 64 contiguous bytes per row) into
-// second[chunk][level]; the block that finishes last (ticket) adds the chunk sums per level,
-// writes the marginal PMF and sums the entropy terms in level order.
-constexpr int kFinChunks = 16;
-constexpr int kFinThreads = 256, kFinGroups = kFinThreads / 8;
-
-__global__ __launch_bounds__(kFinThreads)
-void marginal_finalize_kernel(const unsigned long long *__restrict__ partial, int nblocks, int n_levels, double inv_n,
-                              float *__restrict__ marg, float *__restrict__ entropy_bits,
-                              unsigned long long *second /* [kFinChunks][256] */, unsigned int *ticket)
-{
-    __shared__ unsigned long long red[kFinGroups][8];
-    __shared__ double hsum[256];
-    __shared__ bool is_last;
-    const int b8 = threadIdx.x & 7, grp = threadIdx.x >> 3;
-    const int level = blockIdx.x * 8 + b8;
-    const int chunks = gridDim.y;
-    const int rows_per = (nblocks + chunks - 1) / chunks;
-    const int r0 = blockIdx.y * rows_per, r1 = min(nblocks, r0 + rows_per);
-    unsigned long long s = 0ull;
-    if (level < n_levels) {
-#pragma unroll 8
-        for (int row = r0 + grp; row < r1; row += kFinGroups) s += partial[(size_t)row * n_levels + level];
-    }
-    red[grp][b8] = s;
-    __syncthreads();
-    if (threadIdx.x < 8 && level < n_levels) {
-        unsigned long long tot = 0ull;
-        for (int q = 0; q < kFinGroups; ++q) tot += red[q][threadIdx.x];
-        __hip_atomic_store(&second[blockIdx.y * 256 + level], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // The chunk sums are device-scope atomic stores, which go through the L2 of this XCD; once the wave's
-    // store counter is zero they have arrived, and only then does the block take its ticket.  (A device-scope
-    // fence would do the same by writing back the whole L2: 4 us more on a kernel of 10.)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned int t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        is_last = (t == gridDim.x * gridDim.y - 1);
-    }
-    __syncthreads();
-    if (!is_last) return;
-    asm volatile("" ::: "memory");        // the loads below are device-scope atomic loads: they do not read a stale line
-    double h = 0.0;
-    if ((int)threadIdx.x < n_levels) {
-        unsigned long long tot = 0ull;
-        for (int c = 0; c < chunks; ++c)
-            tot += __hip_atomic_load(&second[c * 256 + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const double m = (double)tot * inv_n;
-        if (marg) marg[threadIdx.x] = (float)m;
-        h = m > 0.0 ? -m * log2(m) : 0.0;
-    }
-    if (threadIdx.x < 256) hsum[threadIdx.x] = h;
-    __syncthreads();
-    if (threadIdx.x == 0 && entropy_bits) {
-        double H = 0.0;
-        for (int i = 0; i < n_levels; ++i) H += hsum[i];
-        *entropy_bits = (float)H;
+        marginal_end<T, FEW>(own, k.n_levels, fin);
     }
 }
 
 // ------------------------------------------------------------------------------------------
 // Backward kernel: recomputes the band, forms the central moments and multiplies by the
-// upstream gradient.  The two scalar sums are accumulated per thread in double, reduced over the
-// block in a fixed order and written as one partial pair per block.
+// upstream gradient.  The two scalar sums are accumulated per thread in double and added up over
+// threads and blocks in a fixed order.
 // ------------------------------------------------------------------------------------------
 template <int W, bool DTHETA, bool SCALARS>
 __global__ __launch_bounds__(kQuantThreads)
 void quantize_bwd_kernel(const float *__restrict__ theta, const float *__restrict__ g, int64_t n, QConst k,
-                         float *__restrict__ dtheta, double *__restrict__ partial /* [gridDim.x][2] */)
+                         float *__restrict__ dtheta, ScalarFinish fin)
 {
     double acc_d = 0.0, acc_a = 0.0;
     const int64_t n4 = n >> 2;
@@ -271,22 +326,7 @@ void quantize_bwd_kernel(const float *__restrict__ theta, const float *__restric
             else for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
         }
     }
-    if (SCALARS) {
-        __shared__ double red_d[kQuantThreads / 64], red_a[kQuantThreads / 64];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            acc_d += __shfl_down(acc_d, off, 64);
-            acc_a += __shfl_down(acc_a, off, 64);
-        }
-        if ((threadIdx.x & 63) == 0) { red_d[threadIdx.x >> 6] = acc_d; red_a[threadIdx.x >> 6] = acc_a; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double sd = 0.0, sa = 0.0;
-            for (int w = 0; w < kQuantThreads / 64; ++w) { sd += red_d[w]; sa += red_a[w]; }
-            partial[2 * (size_t)blockIdx.x] = sd;
-            partial[2 * (size_t)blockIdx.x + 1] = sa;
-        }
-    }
+    if (SCALARS) scalar_finish<kQuantThreads>(acc_d, acc_a, fin);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -442,18 +482,16 @@ __device__ __forceinline__ void uni_sums_literal(float th, const UniConst &u, Un
     o.Z = Z; o.S1 = S1; o.S2 = S2; o.S3 = S3;
 }
 
-template <int JH, bool IDX, bool SOFT, bool MARG>
+template <int JH, bool IDX, bool SOFT, bool MARG, bool FEW>
 __global__ __launch_bounds__(kUniThreads)
 void quantize_fwd_uniform_kernel(const float *__restrict__ theta, int64_t n, QConst k, UniConst u,
                                  int8_t *__restrict__ idx, float *__restrict__ soft,
-                                 unsigned long long *__restrict__ partial /* [gridDim.x][n_levels] */,
-                                 unsigned int *__restrict__ ticket)
+                                 MargFinish fin)
 {
     extern __shared__ double uni_lds[];   // [kUniThreads][2 JH + 1] when MARG
     double acc_s[JH], acc_d[JH], acc_0 = 0.0;
 #pragma unroll
     for (int j = 0; j < JH; ++j) { acc_s[j] = 0.0; acc_d[j] = 0.0; }
-    if (MARG && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;
 
     const int64_t n4 = n >> 2;
     const int64_t stride = (int64_t)gridDim.x * kUniThreads;
@@ -521,19 +559,20 @@ void quantize_fwd_uniform_kernel(const float *__restrict__ theta, int64_t n, QCo
             }
         }
         __syncthreads();
+        unsigned long long own = 0ull;
         if ((int)threadIdx.x < k.n_levels) {
             double tot = 0.0;
             for (int t = 0; t < kUniThreads; ++t) tot += uni_lds[(size_t)t * LS + threadIdx.x];
-            partial[(size_t)blockIdx.x * k.n_levels + threadIdx.x] =
-                (unsigned long long)__double2ll_rn(tot * (double)(1u << kHistScaleBits));
+            own = (unsigned long long)__double2ll_rn(tot * (double)(1u << kHistScaleBits));
         }
+        marginal_end<kUniThreads, FEW>(own, k.n_levels, fin);
     }
 }
 
 template <int JH, bool ODD, bool DTHETA, bool SCALARS>
 __global__ __launch_bounds__(kUniThreads)
 void quantize_bwd_uniform_kernel(const float *__restrict__ theta, const float *__restrict__ g, int64_t n, QConst k, UniConst u,
-                                 float *__restrict__ dtheta, double *__restrict__ partial /* [gridDim.x][2] */)
+                                 float *__restrict__ dtheta, ScalarFinish fin)
 {
     double acc_d = 0.0, acc_a = 0.0;
     const int64_t n4 = n >> 2;
@@ -586,22 +625,7 @@ void quantize_bwd_uniform_kernel(const float *__restrict__ theta, const float *_
             else for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
         }
     }
-    if (SCALARS) {
-        __shared__ double red_d[kUniThreads / 64], red_a[kUniThreads / 64];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            acc_d += __shfl_down(acc_d, off, 64);
-            acc_a += __shfl_down(acc_a, off, 64);
-        }
-        if ((threadIdx.x & 63) == 0) { red_d[threadIdx.x >> 6] = acc_d; red_a[threadIdx.x >> 6] = acc_a; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double sd = 0.0, sa = 0.0;
-            for (int w = 0; w < kUniThreads / 64; ++w) { sd += red_d[w]; sa += red_a[w]; }
-            partial[2 * (size_t)blockIdx.x] = sd;
-            partial[2 * (size_t)blockIdx.x + 1] = sa;
-        }
-    }
+    if (SCALARS) scalar_finish<kUniThreads>(acc_d, acc_a, fin);
 }
 
 // d_delta = mul_d * sum of partials; d_alpha = mul_a * sum of partials.  Fixed summation order: thread t adds the
@@ -713,7 +737,7 @@ template <int W, bool DTHETA, bool SCALARS, bool ADD>
 __global__ __launch_bounds__(kQuantThreads)
 void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict__ marg, const float *__restrict__ g_in,
                         int64_t n, QConst k, float dtheta_mul /* scale * (-2 alpha delta / n) */,
-                        float *__restrict__ dtheta, double *__restrict__ partial /* [gridDim.x][2] */)
+                        float *__restrict__ dtheta, ScalarFinish fin)
 {
     // l_k as a sum of two floats: only differences of l enter, between levels a few apart, and the scalar
     // sums multiply them by the anchor index - with a level set around index 100 the 2^-24 of a single float
@@ -799,22 +823,7 @@ void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict
             else for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
         }
     }
-    if (SCALARS) {
-        __shared__ double red_d[kQuantThreads / 64], red_a[kQuantThreads / 64];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            acc_d += __shfl_down(acc_d, off, 64);
-            acc_a += __shfl_down(acc_a, off, 64);
-        }
-        if ((threadIdx.x & 63) == 0) { red_d[threadIdx.x >> 6] = acc_d; red_a[threadIdx.x >> 6] = acc_a; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double sd = 0.0, sa = 0.0;
-            for (int w = 0; w < kQuantThreads / 64; ++w) { sd += red_d[w]; sa += red_a[w]; }
-            partial[2 * (size_t)blockIdx.x] = sd;
-            partial[2 * (size_t)blockIdx.x + 1] = sa;
-        }
-    }
+    if (SCALARS) scalar_finish<kQuantThreads>(acc_d, acc_a, fin);
 }
 
 __global__ void zero_floats_kernel(float *a, int na, float *b, int nb, float *c, int nc)
@@ -889,38 +898,63 @@ int64_t hist_grid_for(int64_t n)
     return g;
 }
 
-// workspace layout: [per-block histograms][entropy terms + ticket][per-block scalar partials]
+// Whether the histogram kernel finishes the job itself: up to 256 blocks whose records one block can poll in a few
+// trips to memory (measured on quantizer forward + backward: 245 blocks of 15 levels 21.4 against 24.7 us, 49 blocks
+// of 255 levels 17.5 against 24.8, 98 of 255 even, 245 of 255 twice as slow as a second launch).
+bool hist_few(int64_t grid, int32_t n_levels) { return grid <= kFinishMaxBlocks && grid * n_levels <= 16384; }
+
+// workspace layout: [rows of the histogram kernel's blocks][records of the finishing blocks][scalar partials or records]
 size_t hist_bytes(int64_t n, int32_t n_levels)
 {
     return align_up((size_t)hist_grid_for(n) * (size_t)n_levels * sizeof(unsigned long long), 256);
 }
-size_t aux_bytes() { return align_up((size_t)kFinChunks * 256 * sizeof(unsigned long long) + sizeof(unsigned int), 256); }
-size_t scalar_bytes() { return align_up((size_t)kMaxQuantBlocks * 2 * sizeof(double), 256); }
+constexpr size_t kRecordBytes = 16384 * 2 * sizeof(unsigned long long);      // (marginal_finalize_kernel: at most 16 chunks of 256 levels)
+constexpr size_t kScalarBytes = (size_t)kMaxQuantBlocks * 2 * sizeof(double);
+
+ScalarFinish scalar_finish_args(void *ws, int64_t n, int32_t n_levels, int grid, double mul_d, double mul_a, float *d_delta, float *d_alpha)
+{
+    ScalarFinish f{};
+    double *area = reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + hist_bytes(n, n_levels) + kRecordBytes);
+    if (grid > kFinishMaxBlocks) f.partial = area;
+    else { f.records = reinterpret_cast<unsigned long long *>(area); f.tag = next_finish_tag(); }
+    f.mul_d = mul_d; f.mul_a = mul_a; f.d_delta = d_delta; f.d_alpha = d_alpha;
+    return f;
+}
+
+int launch_scalar_end(const ScalarFinish &f, int grid, hipStream_t stream)
+{
+    const int rc = check_launch();
+    return rc != CDL_OK || !f.partial ? rc : launch_scalar_finalize(f.partial, grid, f.mul_d, f.mul_a, f.d_delta, f.d_alpha, stream);
+}
 
 template <int W>
 void launch_fwd_w(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
                   const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
-                  unsigned long long *partial, unsigned int *ticket)
+                  const MargFinish &fin)
 {
     const size_t lds = (size_t)(k.n_levels + 2 * kPad) * sizeof(float) * 32;
 #define CDL_FWD(I, S, M)                                                                                  \
     CDL_LAUNCH((I) ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)", s,                     \
-               (quantize_fwd_kernel<W, I, S, M>), dim3(grid), dim3((M) ? kMargThreads : kQuantThreads), (M) ? lds : 0, \
-               theta, n, k, idx, soft, partial, ticket)
-    if (want_idx && want_soft && want_marg) CDL_FWD(true, true, true);
-    else if (want_idx && want_soft) CDL_FWD(true, true, false);
-    else if (want_idx && want_marg) CDL_FWD(true, false, true);
-    else if (want_idx) CDL_FWD(true, false, false);
-    else CDL_FWD(false, false, true);
+               (quantize_fwd_kernel<W, I, S, (M) != 0, (M) == 2>), dim3(grid), dim3((M) ? kMargThreads : kQuantThreads), (M) ? lds : 0, \
+               theta, n, k, idx, soft, fin)
+    const bool few = hist_few(grid, k.n_levels);
+    if (want_idx && want_soft && want_marg && few) CDL_FWD(true, true, 2);
+    else if (want_idx && want_soft && want_marg) CDL_FWD(true, true, 1);
+    else if (want_idx && want_soft) CDL_FWD(true, true, 0);
+    else if (want_idx && want_marg && few) CDL_FWD(true, false, 2);
+    else if (want_idx && want_marg) CDL_FWD(true, false, 1);
+    else if (want_idx) CDL_FWD(true, false, 0);
+    else if (few) CDL_FWD(false, false, 2);
+    else CDL_FWD(false, false, 1);
 #undef CDL_FWD
 }
 
 template <int W>
 void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
                 const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
-                unsigned long long *partial, unsigned int *ticket)
+                const MargFinish &fin)
 {
-    launch_fwd_w<W>(want_idx, want_soft, want_marg, grid, s, theta, n, k, idx, soft, partial, ticket);
+    launch_fwd_w<W>(want_idx, want_soft, want_marg, grid, s, theta, n, k, idx, soft, fin);
 }
 
 // The soft-regime kernels on a common centre serve: the full CPMF, 6 to 33 levels (smaller sets always fall to
@@ -965,38 +999,42 @@ UniConst make_uniform(const cdl_qparams &p, int jh)
 
 template <int JH>
 int launch_fwd_uniform(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s, const float *theta, int64_t n,
-                       const QConst &k, const UniConst &u, int8_t *idx, float *soft, unsigned long long *partial, unsigned int *ticket)
+                       const QConst &k, const UniConst &u, int8_t *idx, float *soft, const MargFinish &fin)
 {
     const size_t lds = want_marg ? (size_t)kUniThreads * (2 * JH + 1) * sizeof(double) : 0;
 #define CDL_UNI(I, S, M)                                                                                        \
     do {                                                                                                        \
         if (lds > 65536) {                                                                                      \
-            const hipError_t e_ = hipFuncSetAttribute((const void *)quantize_fwd_uniform_kernel<JH, I, S, M>,   \
+            const hipError_t e_ = hipFuncSetAttribute((const void *)quantize_fwd_uniform_kernel<JH, I, S, (M) != 0, (M) == 2>,   \
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);    \
             if (e_ != hipSuccess) return hip_failed(e_);                                                        \
         }                                                                                                       \
         CDL_LAUNCH((I) ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)", s,                       \
-                   (quantize_fwd_uniform_kernel<JH, I, S, M>), dim3(grid), dim3(kUniThreads), lds,              \
-                   theta, n, k, u, idx, soft, partial, ticket);                                                 \
+                   (quantize_fwd_uniform_kernel<JH, I, S, (M) != 0, (M) == 2>), dim3(grid), dim3(kUniThreads), lds,              \
+                   theta, n, k, u, idx, soft, fin);                                                 \
     } while (0)
-    if (want_idx && want_soft && want_marg) CDL_UNI(true, true, true);
-    else if (want_idx && want_soft) CDL_UNI(true, true, false);
-    else if (want_idx && want_marg) CDL_UNI(true, false, true);
-    else CDL_UNI(false, false, true);
+    const bool few = hist_few(grid, k.n_levels);
+    if (want_idx && want_soft && want_marg && few) CDL_UNI(true, true, 2);
+    else if (want_idx && want_soft && want_marg) CDL_UNI(true, true, 1);
+    else if (want_idx && want_soft) CDL_UNI(true, true, 0);
+    else if (want_idx && want_marg && few) CDL_UNI(true, false, 2);
+    else if (want_idx && want_marg) CDL_UNI(true, false, 1);
+    else if (few) CDL_UNI(false, false, 2);
+    else CDL_UNI(false, false, 1);
 #undef CDL_UNI
     return CDL_OK;
 }
 
 template <int JH>
 void launch_bwd_uniform(bool want_dtheta, bool want_scalars, int grid, hipStream_t s, const float *theta, const float *g,
-                        int64_t n, const QConst &k, const UniConst &u, float *dtheta, double *partial)
+                        int64_t n, const QConst &k, const UniConst &u, float *dtheta, const ScalarFinish &fin)
 {
 #define CDL_UNIB(D, S)                                                                                                          \
     do {                                                                                                                        \
         if (u.odd) CDL_LAUNCH("quantize_bwd_kernel", s, (quantize_bwd_uniform_kernel<JH, true, D, S>), dim3(grid), dim3(kUniThreads), 0, \
-                              theta, g, n, k, u, dtheta, partial);                                                              \
+                              theta, g, n, k, u, dtheta, fin);                                                              \
         else CDL_LAUNCH("quantize_bwd_kernel", s, (quantize_bwd_uniform_kernel<JH, false, D, S>), dim3(grid), dim3(kUniThreads), 0,      \
-                        theta, g, n, k, u, dtheta, partial);                                                                    \
+                        theta, g, n, k, u, dtheta, fin);                                                                    \
     } while (0)
     if (want_dtheta && want_scalars) CDL_UNIB(true, true);
     else if (want_dtheta) CDL_UNIB(true, false);
@@ -1006,11 +1044,11 @@ void launch_bwd_uniform(bool want_dtheta, bool want_scalars, int grid, hipStream
 
 template <int W>
 void launch_bwd_w(bool want_dtheta, bool want_scalars, int grid, hipStream_t s, const float *theta,
-                  const float *g, int64_t n, const QConst &k, float *dtheta, double *partial)
+                  const float *g, int64_t n, const QConst &k, float *dtheta, const ScalarFinish &fin)
 {
 #define CDL_BWD(D, S) \
     CDL_LAUNCH("quantize_bwd_kernel", s, (quantize_bwd_kernel<W, D, S>), dim3(grid), dim3(kQuantThreads), 0, \
-               theta, g, n, k, dtheta, partial)
+               theta, g, n, k, dtheta, fin)
     if (want_dtheta && want_scalars) CDL_BWD(true, true);
     else if (want_dtheta) CDL_BWD(true, false);
     else CDL_BWD(false, true);
@@ -1038,7 +1076,7 @@ int quantizer_window(double kappa, int n_levels)
 
 size_t quantize_workspace_bytes(int64_t n, int32_t n_levels)
 {
-    return hist_bytes(n, n_levels) + aux_bytes() + scalar_bytes();
+    return hist_bytes(n, n_levels) + kRecordBytes + kScalarBytes;
 }
 
 // ---- built-in scratch for callers that cannot allocate ---------------------------------------
@@ -1089,37 +1127,39 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
     const int64_t grid64 = want_marg ? hist_grid_for(n) : grid_for(n);
     if (grid64 > 2147483647LL) return CDL_ERR_PARAM;
     int grid = (int)grid64;
-    unsigned long long *partial = reinterpret_cast<unsigned long long *>(ws);
-    unsigned long long *second = want_marg
-        ? reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(ws) + hist_bytes(n, p.n_levels)) : nullptr;
-    unsigned int *ticket = want_marg ? reinterpret_cast<unsigned int *>(second + kFinChunks * 256) : nullptr;
+    MargFinish fin{};
+    if (want_marg) {
+        if (!hist_few(grid, p.n_levels)) fin.rows = reinterpret_cast<unsigned long long *>(ws);
+        fin.records = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(ws) + hist_bytes(n, p.n_levels));
+        fin.tag = next_finish_tag();
+        fin.inv_n = 1.0 / ((double)n * (double)(1u << kHistScaleBits));
+        fin.marg = marg;
+        fin.entropy_bits = entropy_bits;
+    }
     const bool want_idx = idx != nullptr, want_soft = soft != nullptr;
     const int jh = (want_soft || want_marg) ? uniform_half_width(p, k) : 0;
     if (jh) {
         const UniConst u = make_uniform(p, jh);
-        const int ugrid = grid < kMaxQuantBlocks ? grid : kMaxQuantBlocks;   // (any grid serves: the loop strides over the tensor)
+        if (grid > kMaxQuantBlocks) grid = kMaxQuantBlocks;      // (any grid serves: the loop strides over the tensor)
         int rcu = CDL_OK;
-        if (jh == 4) rcu = launch_fwd_uniform<4>(want_idx, want_soft, want_marg, ugrid, stream, theta, n, k, u, idx, soft, partial, ticket);
-        else if (jh == 8) rcu = launch_fwd_uniform<8>(want_idx, want_soft, want_marg, ugrid, stream, theta, n, k, u, idx, soft, partial, ticket);
-        else rcu = launch_fwd_uniform<16>(want_idx, want_soft, want_marg, ugrid, stream, theta, n, k, u, idx, soft, partial, ticket);
+        if (jh == 4) rcu = launch_fwd_uniform<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, u, idx, soft, fin);
+        else if (jh == 8) rcu = launch_fwd_uniform<8>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, u, idx, soft, fin);
+        else rcu = launch_fwd_uniform<16>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, u, idx, soft, fin);
         if (rcu != CDL_OK) return rcu;
-        grid = ugrid;
     } else
     switch (band_template(k)) {
-        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, partial, ticket); break;
-        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, partial, ticket); break;
-        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, partial, ticket); break;
-        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, partial, ticket); break;
-        default: launch_fwd<0>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, partial, ticket); break;
+        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        default: launch_fwd<0>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
     }
     int rc = check_launch();
-    if (rc != CDL_OK) return rc;
-    if (want_marg) {
+    if (rc == CDL_OK && fin.rows) {
         const int level_blocks = (p.n_levels + 7) / 8;
-        const int chunks = level_blocks >= 64 ? 1 : (64 / level_blocks < kFinChunks ? 64 / level_blocks : kFinChunks);
+        const int chunks = 64 / level_blocks < kFinChunks ? (64 / level_blocks > 1 ? 64 / level_blocks : 1) : kFinChunks;
         CDL_LAUNCH("marginal_finalize_kernel", stream, marginal_finalize_kernel, dim3(level_blocks, chunks), dim3(kFinThreads), 0,
-                   partial, grid, p.n_levels, 1.0 / ((double)n * (double)(1u << kHistScaleBits)), marg, entropy_bits,
-                   second, ticket);
+                   fin.rows, grid, p.n_levels, fin);
         rc = check_launch();
     }
     return rc;
@@ -1140,32 +1180,25 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
     const int grid = grid_for(n);
-    double *partial = want_scalars
-        ? reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + hist_bytes(n, p.n_levels) + aux_bytes()) : nullptr;
+    const double d = (double)p.delta;
+    ScalarFinish fin{};
+    if (want_scalars) fin = scalar_finish_args(ws, n, p.n_levels, grid, 1.0, d * d * d, d_delta, d_alpha);
     const bool want_dtheta = dtheta != nullptr;
     const int jh = uniform_half_width(p, k);
     if (jh) {
         const UniConst u = make_uniform(p, jh);
-        if (jh == 4) launch_bwd_uniform<4>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, u, dtheta, partial);
-        else if (jh == 8) launch_bwd_uniform<8>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, u, dtheta, partial);
-        else launch_bwd_uniform<16>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, u, dtheta, partial);
+        if (jh == 4) launch_bwd_uniform<4>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, u, dtheta, fin);
+        else if (jh == 8) launch_bwd_uniform<8>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, u, dtheta, fin);
+        else launch_bwd_uniform<16>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, u, dtheta, fin);
     } else
     switch (band_template(k)) {
-        case 1: launch_bwd_w<1>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, partial); break;
-        case 2: launch_bwd_w<2>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, partial); break;
-        case 3: launch_bwd_w<3>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, partial); break;
-        case 4: launch_bwd_w<4>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, partial); break;
-        default: launch_bwd_w<0>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, partial); break;
+        case 1: launch_bwd_w<1>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
+        case 2: launch_bwd_w<2>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
+        case 3: launch_bwd_w<3>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
+        case 4: launch_bwd_w<4>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
+        default: launch_bwd_w<0>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
     }
-    int rc = check_launch();
-    if (rc != CDL_OK) return rc;
-    if (want_scalars) {
-        const double d = (double)p.delta;
-        CDL_LAUNCH("scalar_finalize_kernel", stream, scalar_finalize_kernel, dim3(1), dim3(kScalarFinThreads), 0, partial, grid, 1.0, d * d * d,
-                   d_delta, d_alpha);
-        rc = check_launch();
-    }
-    return rc;
+    return launch_scalar_end(fin, grid, stream);
 }
 
 int launch_scalar_finalize(const double *partial, int n, double mul_d, double mul_a, float *d_delta, float *d_alpha, hipStream_t stream)
@@ -1196,11 +1229,11 @@ namespace {
 template <int W>
 void launch_entropy_bwd_w(bool want_dtheta, bool want_scalars, bool add, int grid, hipStream_t s, const float *theta,
                           const float *marg, const float *g_in, int64_t n, const QConst &k, float mul,
-                          float *dtheta, double *partial)
+                          float *dtheta, const ScalarFinish &fin)
 {
 #define CDL_EB(D, S, A) \
     CDL_LAUNCH("entropy_bwd_kernel", s, (entropy_bwd_kernel<W, D, S, A>), dim3(grid), dim3(kQuantThreads), 0, \
-               theta, marg, g_in, n, k, mul, dtheta, partial)
+               theta, marg, g_in, n, k, mul, dtheta, fin)
     if (want_dtheta && want_scalars && add) CDL_EB(true, true, true);
     else if (want_dtheta && want_scalars) CDL_EB(true, true, false);
     else if (want_dtheta && add) CDL_EB(true, false, true);
@@ -1225,26 +1258,19 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
     const int grid = grid_for(n);
-    double *partial = want_scalars
-        ? reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + hist_bytes(n, p.n_levels) + aux_bytes()) : nullptr;
     const bool want_dtheta = dtheta != nullptr;
     const double alpha = (double)p.alpha, delta = (double)p.delta;
     const double mul_theta = (double)scale * (-2.0 * alpha * delta / (double)n);
+    ScalarFinish fin{};
+    if (want_scalars) fin = scalar_finish_args(ws, n, p.n_levels, grid, mul_theta, (double)scale * delta * delta / (double)n, d_delta, d_alpha);
     switch (band_template(k)) {
-        case 1: launch_entropy_bwd_w<1>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, partial); break;
-        case 2: launch_entropy_bwd_w<2>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, partial); break;
-        case 3: launch_entropy_bwd_w<3>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, partial); break;
-        case 4: launch_entropy_bwd_w<4>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, partial); break;
-        default: launch_entropy_bwd_w<0>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, partial); break;
+        case 1: launch_entropy_bwd_w<1>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        case 2: launch_entropy_bwd_w<2>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        case 3: launch_entropy_bwd_w<3>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        case 4: launch_entropy_bwd_w<4>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        default: launch_entropy_bwd_w<0>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
     }
-    int rc = check_launch();
-    if (rc != CDL_OK) return rc;
-    if (want_scalars) {
-        CDL_LAUNCH("scalar_finalize_kernel", stream, scalar_finalize_kernel, dim3(1), dim3(kScalarFinThreads), 0, partial, grid,
-                   mul_theta, (double)scale * delta * delta / (double)n, d_delta, d_alpha);
-        rc = check_launch();
-    }
-    return rc;
+    return launch_scalar_end(fin, grid, stream);
 }
 
 }  // namespace cdl

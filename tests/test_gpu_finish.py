@@ -40,3 +40,20 @@ def test_block_sums(oracle, n, bits):
     assert abs(seen[0][2][0] - r["d_delta"]) <= 1e-6 + 1e-5 * abs(r["d_delta"]) + 2e-7 * scale
     assert abs(seen[0][3][0] - r["d_alpha"]) <= 1e-6 + 1e-5 * abs(r["d_alpha"])
 
+
+# one block, few, the last grid that finishes itself, the first that does not; skewed counts (many levels of the tree) and flat ones
+@pytest.mark.parametrize("n", [15, 40_001, 2_097_152, 2_129_937])
+@pytest.mark.parametrize("skewed", [False, True])
+def test_huffman_blocks(oracle, n, skewed):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    rng = np.random.default_rng(n)
+    idx = (np.minimum(rng.geometric(0.3, n), 255) - 128).astype(np.int8) if skewed else rng.integers(-127, 128, n).astype(np.int8)
+    ws = gu.workspace(cdl.huffman_workspace_bytes(n))
+    ws.fill_(255)
+    counts, total, rate = gu.empty((256,), torch.int64), gu.empty((1,), torch.int64), gu.empty((1,), torch.float32)
+    for _ in range(2):
+        cdl.cdl_huffman_bits(gu.dev(idx), n, -128, 256, counts, total, rate, ws)
+    r_counts, r_total, r_rate = oracle.huffman_bits(idx, -128, 256)
+    assert np.array_equal(counts.cpu().numpy(), np.asarray(r_counts).astype(np.int64)) and int(total.item()) == int(r_total)
+    assert float(rate.item()) == pytest.approx(float(r_rate), rel=1e-6)

@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libcdl.so: same names and arguments as include/cdl.h.
+"""Thin binding of libcdl.so: same names and arguments as include/cdl.h.  The library is loaded with ctypes; the calls of a
+layer step go through a small native module (csrc/marshal.c) that turns tensors into pointers.
 
 Tensors are torch CUDA (ROCm) tensors used only as device memory; every step
 of the computation runs in the library's kernels.  There is no fallback: if
@@ -13,6 +14,11 @@ from typing import Optional
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libcdl.so")
 _LIB = None
+_CALLS = None      # the native module, once the library is loaded
+
+_MARSHALLED = ("cdl_quantize_fwd", "cdl_quantize_bwd", "cdl_marginal_entropy", "cdl_quantize_draw", "cdl_entropy_bwd", "cdl_huffman_bits",
+               "cdl_qgemm_fwd_offset", "cdl_qgemm_bwd_offset", "cdl_qgemm_fwd_quantize", "cdl_qconv_fwd", "cdl_qconv_bwd_weights",
+               "cdl_qconv_bwd_activations", "cdl_qgemm_bwd_quantize_bwd")
 
 EXPORTS = (
     "cdl_quantize_workspace_bytes", "cdl_qgemm_fwd_workspace_bytes", "cdl_qgemm_bwd_workspace_bytes",
@@ -53,7 +59,7 @@ def lib_path() -> str:
 
 def load():
     """Load libcdl.so (built beforehand by paper_2501_09849_amd.build / __graft_entry__.build)."""
-    global _LIB
+    global _LIB, _CALLS
     if _LIB is None:
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError("libcdl.so is not built: run `python -m paper_2501_09849_amd.build` "
@@ -66,9 +72,11 @@ def load():
         # PyTorch-ROCm carries its own copy of the HIP runtime and loads it by path.  If libcdl.so came first,
         # the system's copy would be in the process as well, the two would not share a device context, and
         # every launch on torch's memory would fail with hipErrorNoDevice: let torch's be the first one.
+        stream_of, device = None, None
         try:
-            import torch  # noqa: F401
-        except ImportError:
+            import torch
+            stream_of, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        except (ImportError, AttributeError):
             pass
         L = ctypes.CDLL(_LIB_PATH)
         vp, i64, i32, f32, sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_size_t
@@ -135,6 +143,9 @@ def load():
         L.cdl_status_string.argtypes = [ctypes.c_int]
         L.cdl_last_hip_error.restype = ctypes.c_int
         L.cdl_version.restype = ctypes.c_int
+        from . import _marshal
+        _marshal.init({name: ctypes.cast(getattr(L, name), vp).value for name in _MARSHALLED}, stream_of, device)
+        _CALLS = _marshal
         _LIB = L
     return _LIB
 
@@ -148,12 +159,6 @@ def _ptr(t) -> Optional[int]:
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
     return t.data_ptr()
-
-
-def _ws(ws):
-    if ws is None:
-        return None, 0
-    return ws.data_ptr(), ws.numel() * ws.element_size()
 
 
 def _stream(stream) -> Optional[int]:
@@ -198,12 +203,16 @@ def _check(rc: int, where: str):
         raise CdlError(rc, where)
 
 
+def _calls():
+    if _CALLS is None:
+        load()
+    return _CALLS
+
+
 def cdl_quantize_fwd(theta, n, lo, n_levels, delta, alpha, idx, soft=None, marg=None, entropy_bits=None,
                      ws=None, stream=None, top_k=0):
-    wp, wb = _ws(ws)
-    q = _qp(lo, n_levels, delta, alpha, top_k)
-    _check(load().cdl_quantize_fwd(_ptr(theta), n, ctypes.byref(q), _ptr(idx), _ptr(soft), _ptr(marg),
-                                   _ptr(entropy_bits), wp, wb, _stream(stream)), "cdl_quantize_fwd")
+    _check((_CALLS or _calls()).cdl_quantize_fwd(theta, n, lo, n_levels, delta, alpha, top_k, idx, soft, marg, entropy_bits, ws, stream),
+           "cdl_quantize_fwd")
 
 
 def static_scratch_bytes() -> int:
@@ -219,33 +228,24 @@ def cdl_quantize_fwd_static(theta, n, lo, n_levels, delta, alpha, idx, soft=None
 
 def cdl_quantize_bwd(theta, g, n, lo, n_levels, delta, alpha, dtheta=None, d_delta=None, d_alpha=None,
                      ws=None, stream=None, top_k=0):
-    wp, wb = _ws(ws)
-    q = _qp(lo, n_levels, delta, alpha, top_k)
-    _check(load().cdl_quantize_bwd(_ptr(theta), _ptr(g), n, ctypes.byref(q), _ptr(dtheta), _ptr(d_delta),
-                                   _ptr(d_alpha), wp, wb, _stream(stream)), "cdl_quantize_bwd")
+    _check((_CALLS or _calls()).cdl_quantize_bwd(theta, g, n, lo, n_levels, delta, alpha, top_k, dtheta, d_delta, d_alpha, ws, stream),
+           "cdl_quantize_bwd")
 
 
 def cdl_marginal_entropy(theta, n, lo, n_levels, delta, alpha, marg=None, entropy_bits=None, ws=None, stream=None,
                          top_k=0):
-    wp, wb = _ws(ws)
-    q = _qp(lo, n_levels, delta, alpha, top_k)
-    _check(load().cdl_marginal_entropy(_ptr(theta), n, ctypes.byref(q), _ptr(marg), _ptr(entropy_bits),
-                                       wp, wb, _stream(stream)), "cdl_marginal_entropy")
+    _check((_CALLS or _calls()).cdl_marginal_entropy(theta, n, lo, n_levels, delta, alpha, top_k, marg, entropy_bits, ws, stream),
+           "cdl_marginal_entropy")
 
 
 def cdl_quantize_draw(theta, u, n, lo, n_levels, delta, alpha, idx, stream=None, top_k=0):
-    q = _qp(lo, n_levels, delta, alpha, top_k)
-    _check(load().cdl_quantize_draw(_ptr(theta), _ptr(u), n, ctypes.byref(q), _ptr(idx), _stream(stream)),
-           "cdl_quantize_draw")
+    _check((_CALLS or _calls()).cdl_quantize_draw(theta, u, n, lo, n_levels, delta, alpha, top_k, idx, stream), "cdl_quantize_draw")
 
 
 def cdl_entropy_bwd(theta, marg, n, lo, n_levels, delta, alpha, scale=1.0, g_in=None, dtheta=None, d_delta=None,
                     d_alpha=None, ws=None, stream=None, top_k=0):
-    wp, wb = _ws(ws)
-    q = _qp(lo, n_levels, delta, alpha, top_k)
-    _check(load().cdl_entropy_bwd(_ptr(theta), _ptr(marg), _ptr(g_in), n, ctypes.byref(q), float(scale),
-                                  _ptr(dtheta), _ptr(d_delta), _ptr(d_alpha), wp, wb, _stream(stream)),
-           "cdl_entropy_bwd")
+    _check((_CALLS or _calls()).cdl_entropy_bwd(theta, marg, g_in, n, lo, n_levels, delta, alpha, top_k, scale, dtheta, d_delta, d_alpha,
+                                                ws, stream), "cdl_entropy_bwd")
 
 
 def huffman_workspace_bytes(n: int) -> int:
@@ -253,41 +253,38 @@ def huffman_workspace_bytes(n: int) -> int:
 
 
 def cdl_huffman_bits(idx, n, lo, n_levels, counts=None, total_bits=None, bits_per_entry=None, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().cdl_huffman_bits(_ptr(idx), n, lo, n_levels, _ptr(counts), _ptr(total_bits), _ptr(bits_per_entry),
-                                   wp, wb, _stream(stream)), "cdl_huffman_bits")
+    _check((_CALLS or _calls()).cdl_huffman_bits(idx, n, lo, n_levels, counts, total_bits, bits_per_entry, ws, stream), "cdl_huffman_bits")
 
 
 def cdl_qgemm_fwd(a_idx, b_idx, M, N, K, delta_a, delta_b, acc=None, y=None, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().cdl_qgemm_fwd(_ptr(a_idx), _ptr(b_idx), M, N, K, delta_a, delta_b, _ptr(acc), _ptr(y),
-                                wp, wb, _stream(stream)), "cdl_qgemm_fwd")
+    _check((_CALLS or _calls()).cdl_qgemm_fwd_offset(a_idx, b_idx, M, N, K, delta_a, delta_b, 0, 0, acc, y, ws, stream), "cdl_qgemm_fwd")
 
 
 def cdl_qgemm_fwd_offset(a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, acc=None, y=None, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().cdl_qgemm_fwd_offset(_ptr(a_idx), _ptr(b_idx), M, N, K, delta_a, delta_b, int(a_offset), int(b_offset),
-                                       _ptr(acc), _ptr(y), wp, wb, _stream(stream)), "cdl_qgemm_fwd_offset")
+    _check((_CALLS or _calls()).cdl_qgemm_fwd_offset(a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, acc, y, ws, stream),
+           "cdl_qgemm_fwd_offset")
+
+
+def cdl_qgemm_bwd(g, a_idx, b_idx, M, N, K, delta_a, delta_b, d_a_hat=None, d_b_hat=None, ws=None, stream=None):
+    _check((_CALLS or _calls()).cdl_qgemm_bwd_offset(g, a_idx, b_idx, M, N, K, delta_a, delta_b, 0, 0, d_a_hat, d_b_hat, ws, stream),
+           "cdl_qgemm_bwd")
 
 
 def cdl_qgemm_bwd_offset(g, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat=None, d_b_hat=None,
                          ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().cdl_qgemm_bwd_offset(_ptr(g), _ptr(a_idx), _ptr(b_idx), M, N, K, delta_a, delta_b, int(a_offset), int(b_offset),
-                                       _ptr(d_a_hat), _ptr(d_b_hat), wp, wb, _stream(stream)), "cdl_qgemm_bwd_offset")
+    _check((_CALLS or _calls()).cdl_qgemm_bwd_offset(g, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, ws,
+                                                     stream), "cdl_qgemm_bwd_offset")
 
 
 def cdl_qgemm_bwd_quantize_bwd(g, a_idx, b_idx, M, N, K, theta_a, lo_a, n_levels_a, delta_a, alpha_a, delta_b, d_theta_a,
                                d_delta_a=None, d_alpha_a=None, d_b_hat=None, ws=None, stream=None, b_offset=0, top_k=0,
                                theta_b=None, qparams_b=None, d_theta_b=None, d_delta_b=None, d_alpha_b=None):
     """qparams_b: (lo, n_levels, delta, alpha[, top_k]) of the weight quantizer, with theta_b and d_theta_b."""
-    wp, wb = _ws(ws)
-    q = _qp(lo_a, n_levels_a, delta_a, alpha_a, top_k)
-    qb = _qp(*qparams_b) if qparams_b is not None else None
-    _check(load().cdl_qgemm_bwd_quantize_bwd(_ptr(g), _ptr(a_idx), _ptr(b_idx), M, N, K, _ptr(theta_a), ctypes.byref(q), delta_b,
-                                             int(b_offset), _ptr(d_theta_a), _ptr(d_delta_a), _ptr(d_alpha_a), _ptr(d_b_hat),
-                                             _ptr(theta_b), ctypes.byref(qb) if qb is not None else None, _ptr(d_theta_b),
-                                             _ptr(d_delta_b), _ptr(d_alpha_b), wp, wb, _stream(stream)), "cdl_qgemm_bwd_quantize_bwd")
+    qb = (0, 0, 0.0, 0.0, 0) if qparams_b is None else tuple(qparams_b) if len(qparams_b) == 5 else (*qparams_b, 0)
+    _check((_CALLS or _calls()).cdl_qgemm_bwd_quantize_bwd(g, a_idx, b_idx, M, N, K, theta_a, lo_a, n_levels_a, delta_a, alpha_a, top_k,
+                                                           delta_b, b_offset, d_theta_a, d_delta_a, d_alpha_a, d_b_hat, theta_b,
+                                                           qparams_b is not None, *qb, d_theta_b, d_delta_b, d_alpha_b, ws, stream),
+           "cdl_qgemm_bwd_quantize_bwd")
 
 
 def qconv_bwd_weights_workspace_bytes(B, H, W, C, N, R, S, stride, pad) -> int:
@@ -295,9 +292,8 @@ def qconv_bwd_weights_workspace_bytes(B, H, W, C, N, R, S, stride, pad) -> int:
 
 
 def cdl_qconv_bwd_weights(g, x_idx, B, H, W, C, N, R, S, stride, pad, delta_x, d_w_hat, ws, stream=None, x_offset=0):
-    wp, wb = _ws(ws)
-    _check(load().cdl_qconv_bwd_weights(_ptr(g), _ptr(x_idx), B, H, W, C, N, R, S, stride, pad, delta_x, int(x_offset),
-                                        _ptr(d_w_hat), wp, wb, _stream(stream)), "cdl_qconv_bwd_weights")
+    _check((_CALLS or _calls()).cdl_qconv_bwd_weights(g, x_idx, B, H, W, C, N, R, S, stride, pad, delta_x, x_offset, d_w_hat, ws, stream),
+           "cdl_qconv_bwd_weights")
 
 
 def qconv_bwd_activations_workspace_bytes(B, H, W, C, N, R, S, stride, pad) -> int:
@@ -305,14 +301,12 @@ def qconv_bwd_activations_workspace_bytes(B, H, W, C, N, R, S, stride, pad) -> i
 
 
 def cdl_qconv_bwd_activations(g, w_idx, B, H, W, C, N, R, S, stride, pad, delta_w, d_x_hat, ws, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().cdl_qconv_bwd_activations(_ptr(g), _ptr(w_idx), B, H, W, C, N, R, S, stride, pad, delta_w,
-                                            _ptr(d_x_hat), wp, wb, _stream(stream)), "cdl_qconv_bwd_activations")
+    _check((_CALLS or _calls()).cdl_qconv_bwd_activations(g, w_idx, B, H, W, C, N, R, S, stride, pad, delta_w, d_x_hat, ws, stream),
+           "cdl_qconv_bwd_activations")
 
 
 def cdl_qgemm_fwd_quantize(x, lo_a, n_levels_a, delta_a, alpha_a, b_idx, M, N, K, delta_b, y, stream=None):
-    q = _qp(lo_a, n_levels_a, delta_a, alpha_a, 0)
-    _check(load().cdl_qgemm_fwd_quantize(_ptr(x), ctypes.byref(q), _ptr(b_idx), M, N, K, delta_b, _ptr(y), _stream(stream)),
+    _check((_CALLS or _calls()).cdl_qgemm_fwd_quantize(x, lo_a, n_levels_a, delta_a, alpha_a, 0, b_idx, M, N, K, delta_b, y, stream),
            "cdl_qgemm_fwd_quantize")
 
 
@@ -322,15 +316,8 @@ def qconv_fwd_workspace_bytes(N: int, x_offset: int = 0) -> int:
 
 def cdl_qconv_fwd(x_idx, w_idx, B, H, W, C, N, R, S, stride, pad, delta_x, delta_w, acc=None, y=None, ws=None, stream=None,
                   x_offset=0):
-    wp, wb = _ws(ws)
-    _check(load().cdl_qconv_fwd(_ptr(x_idx), _ptr(w_idx), B, H, W, C, N, R, S, stride, pad, delta_x, delta_w, int(x_offset),
-                                _ptr(acc), _ptr(y), wp, wb, _stream(stream)), "cdl_qconv_fwd")
-
-
-def cdl_qgemm_bwd(g, a_idx, b_idx, M, N, K, delta_a, delta_b, d_a_hat=None, d_b_hat=None, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(load().cdl_qgemm_bwd(_ptr(g), _ptr(a_idx), _ptr(b_idx), M, N, K, delta_a, delta_b,
-                                _ptr(d_a_hat), _ptr(d_b_hat), wp, wb, _stream(stream)), "cdl_qgemm_bwd")
+    _check((_CALLS or _calls()).cdl_qconv_fwd(x_idx, w_idx, B, H, W, C, N, R, S, stride, pad, delta_x, delta_w, x_offset, acc, y, ws, stream),
+           "cdl_qconv_fwd")
 
 
 def cdl_probe_mfma_int8(iters: int, random_operands: bool, blocks: int, sink, stream=None) -> float:

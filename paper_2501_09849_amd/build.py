@@ -1,15 +1,18 @@
-"""Builds libcdl.so (the HIP kernels and the C boundary) for gfx950 with hipcc, in-tree."""
+"""Builds libcdl.so (the HIP kernels and the C boundary) for gfx950 with hipcc and the Python calls to it, in-tree."""
 from __future__ import annotations
 
 import glob
 import hashlib
 import os
 import subprocess
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libcdl.so")
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.c")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -30,7 +33,7 @@ HASH_PATH = LIB_PATH + ".srchash"
 
 
 def _deps():
-    return sources() + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + sorted(glob.glob(os.path.join(_ROOT, "include", "*.h")))
+    return sources() + [MARSHAL_SOURCE] + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + sorted(glob.glob(os.path.join(_ROOT, "include", "*.h")))
 
 
 def source_hash() -> str:
@@ -47,10 +50,22 @@ def source_hash() -> str:
 
 def is_stale() -> bool:
     """True when libcdl.so is missing or was not built from the sources now in the tree."""
-    if not (os.path.exists(LIB_PATH) and os.path.exists(HASH_PATH)):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(MARSHAL_PATH) and os.path.exists(HASH_PATH)):
         return True
     with open(HASH_PATH) as f:
         return f.read().strip() != source_hash()
+
+
+def build_marshal(path: str = MARSHAL_PATH) -> str:
+    """Compile the native module of the binding (host code only)."""
+    tmp = path + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(_ROOT, "include"), MARSHAL_SOURCE, "-o", tmp]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("compiling marshal.c failed:\n" + res.stdout)
+    os.replace(tmp, path)
+    return path
 
 
 def build_lib(verbose: bool = False) -> str:
@@ -65,6 +80,7 @@ def build_lib(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + res.stdout)
     if verbose and res.stdout.strip():
         print(res.stdout)
+    build_marshal()
     os.replace(tmp, LIB_PATH)
     if LIB_PATH.endswith(os.path.join(os.path.basename(_HERE), "libcdl.so")):
         with open(HASH_PATH, "w") as f:

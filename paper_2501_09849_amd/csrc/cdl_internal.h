@@ -106,6 +106,11 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
                      float delta_a, float delta_b, int32_t a_offset, int32_t b_offset, int32_t *acc, float *y,
                      void *ws, hipStream_t stream);
 
+// The same product for problems with few output tiles (cdl_qgemm_small.hip): any K >= 16, no workspace.
+bool qgemm_small_serves(int32_t M, int32_t N, int32_t K);
+int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset,
+                       int32_t b_offset, int32_t *acc, float *y, hipStream_t stream);
+
 // fq != null: d_a_hat receives dL/dtheta of the activations (the quantizer's backward pass applied in the epilogue
 // of the product) and the two scalar gradients go to fq->d_delta / fq->d_alpha.
 // fqb != null: the same for the weights, applied where the splits of the weight-gradient product are added up:

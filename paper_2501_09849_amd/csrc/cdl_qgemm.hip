@@ -2172,6 +2172,8 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
         if (y) CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)M * N, 256, 4096)), dim3(256), 0, y, (int64_t)M * N);
         return check_launch();
     }
+    if (qgemm_small_serves(M, N, K))
+        return launch_qgemm_small(a_idx, b_idx, M, N, K, delta_a * delta_b, a_offset, b_offset, acc, y, stream);
     GemmArgs g{};
     g.A = a_idx; g.B = b_idx; g.lda = K; g.ldb = K;
     g.rowsA = M; g.rowsB = N; g.Kc = K;

@@ -247,8 +247,9 @@ int cdl_qgemm_fwd_offset(const int8_t *a_idx, const int8_t *b_idx, int32_t M, in
  * d_b_hat is requested and M > 11 000 000 (32-bit offsets into the transposed copy of a_idx).
  * Diagnostics: once the call has run, the first two int32 of ws hold the limb counts the device
  * chose for d_a_hat and for d_b_hat, and the two doubles at byte offsets 32 and 40 of ws the bounds
- * above for the two products (meaningful for a product that was requested; d_a_hat with N <= 32 is
- * formed directly in double, without limbs).
+ * above for the two products (meaningful for a product that was requested).  Where the arithmetic is small both products are
+ * formed directly in double instead, each entry exact before its one rounding to fp32; the words then hold the counts and
+ * bounds that limbs would have had, and nothing for calls with N <= 32 or M*N*K <= 2^25.
  */
 int cdl_qgemm_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx,
                   int32_t M, int32_t N, int32_t K, float delta_a, float delta_b,
@@ -311,7 +312,7 @@ int cdl_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_t H
  *   d_w_hat[n,r,s,c] = delta_x * sum over (b,p,q) of g[b,p,q,n] * X[b, p*stride + r - pad, q*stride + s - pad, c]
  * with X as in cdl_qconv_fwd (level index x_idx + x_offset inside the image, 0 outside).  It is cdl_qgemm_bwd's
  * d_b_hat on the window matrix - same limbs, same exactness - whose transposed copy (which that product needs
- * anyway) is gathered straight from the activations.
+ * anyway) is gathered straight from the activations, or, where the arithmetic is small, the same sums in double.
  *   g DEVICE fp32[B,P,Q,N], x_idx DEVICE int8[B,H,W,C], d_w_hat DEVICE fp32[N,R,S,C]
  * Restrictions as for cdl_qconv_fwd, and B*P*Q <= 11 000 000.  Scratch: cdl_qconv_bwd_weights_workspace_bytes
  * (it holds the transposed window matrix: R*S*C * B*P*Q bytes).
@@ -326,8 +327,8 @@ int cdl_qconv_bwd_weights(const float *g, const int8_t *x_idx, int32_t B, int32_
  * The gradient with respect to the quantized activations of that convolutional layer (Algorithm 1, backward step):
  *   d_x_hat[b,h,w,c] = delta_w * sum over (p,q,r,s,n) with p*stride + r - pad = h, q*stride + s - pad = w of
  *                      g[b,p,q,n] * w_idx[n,r,s,c],
- * an exact real contraction over (r,s,n) rounded once, as cdl_qgemm_bwd's d_a_hat is: the same limb product, whose
- * fp32 operand is gathered from g tap by tap (a transposed convolution) instead of read row by row.
+ * an exact real contraction over (r,s,n) rounded once, as cdl_qgemm_bwd's d_a_hat is (in double where the arithmetic is
+ * small): the same limb product, whose fp32 operand is gathered from g tap by tap (a transposed convolution) instead of read row by row.
  *   g DEVICE fp32[B,P,Q,N], w_idx DEVICE int8[N,R,S,C] (level indices as they are), d_x_hat DEVICE fp32[B,H,W,C]
  * Restrictions: N and C multiples of 4, stride 1 or 2, pad < R and pad < S, R*S*N <= 131071
  * (CDL_ERR_PARAM / CDL_ERR_RANGE otherwise).  Pointers 16-byte aligned.  Scratch:
@@ -341,25 +342,21 @@ int cdl_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B, in
 
 /*
  * The backward step of Algorithm 1 for a layer in one call: cdl_qgemm_bwd followed by cdl_quantize_bwd on its
- * d_a_hat (and, optionally, on its d_b_hat), with the quantizer's backward pass (Lemma 1; eq. partialX3, Jgradqx,
- * Jgrad_alpha_q) applied to each tile of dL/dQ(x) in the epilogue of the product, while the tile is still on the
- * chip.  dL/dQ(x) itself is never written to memory or read back (on a transformer-sized layer that is a fifth of the
- * backward pass's traffic).  Arguments as for the two calls it replaces:
+ * d_a_hat (and, optionally, on its d_b_hat).  dL/dQ(x) needs no tensor of its own: it is formed in d_theta_a and turned
+ * into dL/dx in place (Lemma 1; eq. partialX3, Jgradqx, Jgrad_alpha_q).  Arguments as for the two calls it replaces:
  *   theta_a   fp32[M,K], the activations that were quantized into a_idx with the quantizer *p_a
  *   a_idx     int8[M,K] as cdl_quantize_fwd stored it (needed for d_b_hat only), b_idx int8[N,K] stored minus b_offset
  *   d_theta_a fp32[M,K]  = (delta_b * sum_n g[m,n] * level index of b[n,k]) * dQ_d/dtheta(theta_a[m,k])   (required)
  *   d_delta_a, d_alpha_a  the two scalar gradients of the activation quantizer       (DEVICE fp32[1], nullable)
  *   d_b_hat   fp32[N,K] as in cdl_qgemm_bwd(_offset), with a_offset = cdl_index_offset(p_a)              (nullable)
- * The weight operand likewise, if theta_b is given (all five of its arguments may be NULL instead): the quantizer's
- * backward pass on the weights (eq. partialW3, Jgradqw, Jgradq_alpha_w) is applied where the pieces of the
- * contraction over M are added up, so dL/dQ(w) is not read back either:
+ * The weight operand likewise, if theta_b is given (all five of its arguments may be NULL instead; eq. partialW3, Jgradqw,
+ * Jgradq_alpha_w):
  *   theta_b   fp32[N,K], the weights that were quantized into b_idx with *p_b; p_b->delta must equal delta_b and
  *             cdl_index_offset(p_b) must equal b_offset, else CDL_ERR_PARAM
  *   d_theta_b fp32[N,K]  = (delta_a * sum_m g[m,n] * level index of a[m,k]) * dQ_d/dtheta(theta_b[n,k])   (required then)
  *   d_delta_b, d_alpha_b  the two scalar gradients of the weight quantizer              (DEVICE fp32[1], nullable)
- *   d_b_hat   may still be requested and is written by the same kernel.
- * Results equal those of the separate calls (the same arithmetic on the same fp32 intermediate; the scalar
- * sums are added up in a different, fixed order).  Restrictions: M, N, K > 0, K a multiple of 4 and N > 32, else
+ *   d_b_hat   may still be requested.
+ * Results equal those of the separate calls bit for bit.  Restrictions: M, N, K > 0, K a multiple of 4 and N > 32, else
  * CDL_ERR_PARAM - use the separate calls there.  Scratch: cdl_qgemm_bwd_workspace_bytes(M, N, K).
  */
 int cdl_qgemm_bwd_quantize_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,

@@ -200,7 +200,8 @@ int cdl_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl_qp
         rc = check_ws(ws, ws_bytes, quantize_workspace_bytes(n, p->n_levels));
         if (rc != CDL_OK) return rc;
     }
-    return launch_quantize_bwd(theta, g, n, *p, dtheta, d_delta, d_alpha, ws, (hipStream_t)hip_stream);
+    return launch_quantize_bwd(theta, g, n, *p, dtheta, d_delta, d_alpha,
+                               d_delta || d_alpha ? quantize_scalar_area(ws, n, p->n_levels) : nullptr, (hipStream_t)hip_stream);
 }
 
 int cdl_marginal_entropy(const float *theta, int64_t n, const cdl_qparams *p,
@@ -387,7 +388,7 @@ int cdl_qconv_bwd_weights(const float *g, const int8_t *x_idx, int32_t B, int32_
     if (rc != CDL_OK) return rc;
     const ConvWindows cw{B, H, W, C, R, S, stride, pad, (int)P, (int)Q};
     return launch_qgemm_bwd(g, x_idx, nullptr, (int32_t)M, N, (int32_t)K, delta_x, 1.0f, x_offset, 0, nullptr, d_w_hat, ws,
-                            (hipStream_t)hip_stream, nullptr, nullptr, &cw);
+                            (hipStream_t)hip_stream, &cw);
 }
 
 namespace {
@@ -438,7 +439,6 @@ int cdl_qgemm_bwd_quantize_bwd(const float *g, const int8_t *a_idx, const int8_t
     if (rc != CDL_OK) return rc;
     if (M <= 0 || N <= 0 || K <= 0 || !offset_ok(b_offset)) return CDL_ERR_PARAM;
     if (!(std::isfinite(delta_b) && delta_b > 0.0f)) return CDL_ERR_PARAM;
-    // the fused epilogue walks the tile four columns at a time, and very short contractions take a kernel without it
     if (K % 4 != 0 || N <= 32) return CDL_ERR_PARAM;
     if (!d_theta_a) return CDL_ERR_NULL;
     const bool weights = theta_b || p_b || d_theta_b || d_delta_b || d_alpha_b;
@@ -459,10 +459,9 @@ int cdl_qgemm_bwd_quantize_bwd(const float *g, const int8_t *a_idx, const int8_t
         return CDL_ERR_ALIGN;
     rc = check_ws(ws, ws_bytes, qgemm_bwd_workspace_bytes(M, N, K));
     if (rc != CDL_OK) return rc;
-    const FusedQuantBwd fq{theta_a, p_a, d_delta_a, d_alpha_a, nullptr};
-    const FusedQuantBwd fqb{theta_b, p_b, d_delta_b, d_alpha_b, d_theta_b};
-    return launch_qgemm_bwd(g, a_idx, b_idx, M, N, K, p_a->delta, delta_b, index_offset(*p_a), b_offset, d_theta_a, d_b_hat, ws,
-                            (hipStream_t)hip_stream, &fq, weights ? &fqb : nullptr);
+    return launch_qgemm_bwd_quantize_bwd(g, a_idx, b_idx, M, N, K, index_offset(*p_a), b_offset, delta_b, theta_a, *p_a, d_theta_a, d_delta_a, d_alpha_a,
+                                         d_b_hat, weights ? theta_b : nullptr, weights ? p_b : nullptr, weights ? d_theta_b : nullptr, d_delta_b,
+                                         d_alpha_b, ws, (hipStream_t)hip_stream);
 }
 
 int cdl_qgemm_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx,

@@ -76,9 +76,13 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
                         int8_t *idx, float *soft, float *marg, float *entropy_bits,
                         void *ws, hipStream_t stream);
 
+// scalars: the part of a call's workspace that holds the blocks' sums of the two scalar gradients (kQuantScalarBytes).
+// g and dtheta may be the same tensor.
+constexpr size_t kQuantScalarBytes = (size_t)kMaxQuantBlocks * 2 * sizeof(double);
+void *quantize_scalar_area(void *ws, int64_t n, int32_t n_levels);
 int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams &p,
                         float *dtheta, float *d_delta, float *d_alpha,
-                        void *ws, hipStream_t stream);
+                        void *scalars, hipStream_t stream);
 
 int launch_quantize_draw(const float *theta, const float *u, int64_t n, const cdl_qparams &p, int8_t *idx, hipStream_t stream);
 
@@ -111,27 +115,40 @@ bool qgemm_small_serves(int32_t M, int32_t N, int32_t K);
 int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset,
                        int32_t b_offset, int32_t *acc, float *y, hipStream_t stream);
 
-// fq != null: d_a_hat receives dL/dtheta of the activations (the quantizer's backward pass applied in the epilogue
-// of the product) and the two scalar gradients go to fq->d_delta / fq->d_alpha.
-// fqb != null: the same for the weights, applied where the splits of the weight-gradient product are added up:
-// fqb->d_theta receives dL/dtheta of the weights; d_b_hat (nullable then) still receives dL/dQ(w) when given.
-struct FusedQuantBwd {
-    const float *theta;       // the tensor the operand was quantized from, in the operand's layout
-    const cdl_qparams *p;     // its quantizer
-    float *d_delta, *d_alpha; // DEVICE fp32[1], nullable
-    float *d_theta;           // weight side only: where dL/dtheta goes
-};
-
 // cw != null: a_idx is not an [M][K] matrix but the activations [B][H][W][C] of a convolutional layer, whose matrix of
 // input windows (M = B*P*Q rows, K = R*S*C columns) is the operand; only d_b_hat (the weight gradient) is served.
 struct ConvWindows {
     int B, H, W, C, R, S, stride, pad, P, Q;
 };
 
+// Both products of a small layer directly in double (cdl_bwd_direct.hip).
+struct BwdPlan;
+constexpr size_t kBwdDirectRecordBytes = 8192 * 2 * sizeof(unsigned long long);
+bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool want_a, bool want_b);
+int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float delta_a, float delta_b,
+                      int32_t a_offset, int32_t b_offset, float *d_a_hat, float *d_b_hat, BwdPlan *plan, void *records, double *partial, int max_splits,
+                      hipStream_t stream);
+
+// The same for the gradients of a convolution.  ConvDxGrid: a class of input pixels (2 i + oa, 2 j + oc) and the taps
+// (r0 + 2 r', s0 + 2 s'), r' < Rc, s' < Sc, that reach them (stride 1: one class, every pixel and tap, steps of 1).
+struct ConvDxGrid { int oa, oc, Hc, Wc, pad_h, pad_w, Rc, Sc, r0, s0; };
+bool conv_dw_direct_serves(int64_t M, int32_t N, int32_t K);
+int launch_conv_dw_direct(const float *g, const int8_t *x_idx, const ConvWindows &w, int32_t N, float delta_x, int32_t x_offset, float *d_w_hat,
+                          double *partial, int max_splits, hipStream_t stream);
+bool conv_dx_direct_serves(int64_t pixels, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride);
+int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
+                          int32_t R, int32_t S, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream);
+
 int launch_qgemm_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx,
                      int32_t M, int32_t N, int32_t K, float delta_a, float delta_b, int32_t a_offset, int32_t b_offset,
-                     float *d_a_hat, float *d_b_hat, void *ws, hipStream_t stream, const FusedQuantBwd *fq = nullptr,
-                     const FusedQuantBwd *fqb = nullptr, const ConvWindows *cw = nullptr);
+                     float *d_a_hat, float *d_b_hat, void *ws, hipStream_t stream, const ConvWindows *cw = nullptr);
+
+// The backward products followed by the quantizers' backward passes: dL/dQ(a) goes to d_theta_a (and dL/dQ(b) to d_theta_b
+// where d_b_hat is not asked for) and is turned into the gradient in place.
+int launch_qgemm_bwd_quantize_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,
+                                  int32_t a_offset, int32_t b_offset, float delta_b, const float *theta_a, const cdl_qparams &p_a,
+                                  float *d_theta_a, float *d_delta_a, float *d_alpha_a, float *d_b_hat, const float *theta_b,
+                                  const cdl_qparams *p_b, float *d_theta_b, float *d_delta_b, float *d_alpha_b, void *ws, hipStream_t stream);
 
 // Forward product with the quantizer of the activations in its prologue (K % 128 == 0, indices stored without an offset).
 int launch_qgemm_quantize_fwd(const float *x, const cdl_qparams &p, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,

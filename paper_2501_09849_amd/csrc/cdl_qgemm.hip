@@ -12,6 +12,8 @@
 // products are exact in int32 and are recombined in double in the epilogue.  L (3..6) is chosen on
 // the device so that the rounding of q stays well below the parity tolerance.
 #include "cdl_internal.h"
+#include "cdl_bwd_plan.h"
+#include "cdl_finish.h"
 
 #include <mutex>
 #include "cdl_quantizer_math.h"
@@ -31,14 +33,6 @@ typedef void __attribute__((address_space(3))) *lptr_t;
 
 constexpr int kGemmThreads = 256;
 constexpr int kKT = 64;          // forward: contraction bytes staged per pipeline step
-
-// Device-side plan of one backward call: scale of the gradient and limb counts.
-struct BwdPlan {
-    int limbs_da, limbs_db;          // limbs used for d_a_hat / d_b_hat
-    float gscale_da, gscale_db;      // 2^(8L-1) / sigma
-    double out_scale_da, out_scale_db;  // delta_b * sigma / 2^(8L-1), delta_a * sigma / 2^(8L-1)
-    double bound_da, bound_db;          // what the rounding of g can change in one entry of d_a_hat / d_b_hat, at most
-};
 
 struct GemmArgs {
     const int8_t *A;      // [rowsA][lda]
@@ -225,15 +219,10 @@ struct LimbArgs {
     const BwdPlan *plan;
     int which;            // 0 = d_a_hat, 1 = d_b_hat
     float *out;           // [rows][cols] (splits == 1)
-    double *partial;      // [splits][rows][cols] (splits > 1, or to_partial)
-    int to_partial;       // 1: the unscaled sums go to `partial` as doubles even with one split (a reduction kernel follows)
-    // d_a_hat only: the quantizer's backward pass applied to the tile before it leaves the chip (fq_theta != null):
-    // out receives dL/dtheta instead of dL/dQ(theta), fq_partial one pair of partial scalar gradients per block
-    const float *fq_theta;    // [rows][cols] the tensor that was quantized into the index operand of the forward product
-    double *fq_partial;       // [work items][2]
+    double *partial;      // [splits][rows][cols] (splits > 1)
+    // forward product with the quantizer in its prologue
     QConst fq_k;
-    int fq_wsel;              // band_template(fq_k)
-    float fq_scale;           // forward product with the quantizer in its prologue: delta_a * delta_b
+    float fq_scale;           // delta_a * delta_b
     // activation gradient of a convolution (CONVG): the rows of the fp32 operand are gathered.  Output row m is pixel
     // (b, i, j) of a grid of cg_H x cg_W pixels per image; contraction entry k = (tap (r, s) of cg_R' x cg_S taps, output
     // channel n) is read from G[b, p, q, n] with p = i + pad_h - r, q = j + pad_w - s where those are inside the output
@@ -255,7 +244,6 @@ constexpr int kLBK = 128;     // contraction bytes per K-tile
 constexpr int kLRows = 32;    // output rows per block
 constexpr int kLPlane = kLRows * kLBK;
 constexpr int kLThreads = 256;
-constexpr int kMinLimbs = 3, kMaxLimbs = 6;
 
 constexpr int limb_tn(int L) { return L <= 5 ? 3 : 2; }          // 32-column tiles per wave
 constexpr int limb_cols(int L) { return 4 * limb_tn(L) * 32; }   // output columns per block
@@ -843,8 +831,8 @@ __device__ __forceinline__ void limbs_of4(const float (&g)[4], float gscale, uin
 // lets the scheduler put the VALU and LDS work into the shadow of the MFMAs.
 // TRANS: G is read transposed (rows of the product are columns of G).  VEC: 16-byte loads of G
 // (N % 4 == 0).
-template <int L, int TN, bool TRANS, bool VEC, bool LONG_RUNS, bool FUSED = false, bool QUANT = false, bool CONVG = false>
-__device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, float gscale, double out_scale)
+template <int L, int TN, bool TRANS, bool VEC, bool LONG_RUNS, bool QUANT = false, bool CONVG = false>
+__device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, float gscale, double out_scale, int block)
 {
     constexpr int NB = 4 * TN * 32;
     constexpr int STAGE = L * kLPlane + NB * kLBK;
@@ -867,8 +855,8 @@ __device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, f
     // may hold more blocks than items (it is sized before the limb count is known).
     const int64_t items = (int64_t)runs * (tiles_c / c_per_block) * a.splits;
     const int64_t per_xcd = (items + 7) >> 3;
-    const int64_t slot = (int64_t)((int)blockIdx.x >> 3);
-    const int64_t logical = (int64_t)((int)blockIdx.x & 7) * per_xcd + slot;
+    const int64_t slot = (int64_t)(block >> 3);
+    const int64_t logical = (int64_t)(block & 7) * per_xcd + slot;
     if (slot >= per_xcd || logical >= items) return;
     const int c_begin = RUNS ? 0 : (int)(logical % tiles_c);
     const int64_t rest = RUNS ? logical : logical / tiles_c;
@@ -1087,7 +1075,7 @@ __device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, f
         // one address per row, the TN column tiles of a wave at fixed distances from it; tiles that do not reach
         // the edge of the matrix (FULL) store without a test
         const int64_t first = (int64_t)erow * a.cols + ecol;
-        const bool direct = a.splits == 1 && !a.to_partial;      // the block writes the finished fp32 output itself
+        const bool direct = a.splits == 1;                       // the block writes the finished fp32 output itself
         const bool corr = a.row_corr != nullptr && direct;
         // CORR: row corrections of an operand stored with an offset, in a copy of the write-out of their own.  A load
         // between the stores - even one that a branch skips - makes the compiler wait for every earlier store at each
@@ -1142,110 +1130,6 @@ __device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, f
             double *base = a.partial + (int64_t)split * a.rows * a.cols + first;
             if (full) emit(std::true_type{}, std::false_type{}, base);
             else emit(std::false_type{}, std::false_type{}, base);
-        }
-    };
-
-
-    // ---- the quantizer's backward pass in the epilogue (eq. partialX3, Jgradqx, Jgrad_alpha_q applied to the
-    // tile of dL/dQ(x) while it is still on the chip): the recombined tile goes to LDS as fp32 (the stages are free
-    // by now), then all threads walk it four entries at a time, load the matching entries of theta, evaluate the
-    // band of the CPMF as the stand-alone kernel does, and store dL/dtheta; dL/dQ(x) itself is never written. ----
-    auto fused_tile = [&]() {
-        constexpr int NBP = NB + 4;           // row pitch in floats: the two half-waves of a store land 16 banks apart
-        float *tile = reinterpret_cast<float *>(lds);
-        const int row0 = tile_r0 * kLRows, col0 = c_begin * NB;
-        constexpr int Q = NB / 4;             // groups of four columns per row
-        const QConst &k = a.fq_k;
-        // every thread takes T groups of four entries; all loads of theta are issued here, before the tile is
-        // recombined and written to LDS (with one wave per SIMD nothing else hides their latency)
-        constexpr int T = kLRows * Q / kLThreads;
-        static_assert(T * kLThreads == kLRows * Q, "whole trips");
-        // (row corrections of a weight operand stored with an offset: loaded first, in a branch of their own, so that the
-        // common path has no load whose wait would also be a wait for the theta loads below)
-        double rcs[16];
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) rcs[rr] = 0.0;
-        if (a.row_corr) {
-            const int lrow0 = tile_r0 * kLRows + 4 * (lane >> 5);
-#pragma unroll
-            for (int rr = 0; rr < 16; ++rr) {
-                const int dr = 8 * (rr >> 2) + (rr & 3);
-                rcs[rr] = lrow0 + dr < a.rows ? a.row_corr[lrow0 + dr] : 0.0;
-            }
-        }
-        float4 th4[T];
-        bool ok[T];
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int e4 = tid + t * kLThreads, row = e4 / Q, c4 = e4 - row * Q;
-            const int grow = row0 + row, gcol = col0 + 4 * c4;
-            ok[t] = grow < a.rows && gcol < a.cols;          // (cols % 4 == 0: a group is inside or outside)
-            const int64_t o = (int64_t)min(grow, a.rows - 1) * a.cols + min(gcol, a.cols - 4);
-            th4[t] = load_stream4(a.fq_theta + o, k.stream);
-        }
-        __builtin_amdgcn_s_waitcnt(kLgkmcnt0);
-        barrier();                            // every wave has read its last fragments
-        {
-            const int lrow = 4 * (lane >> 5), lcol = wave * TN * 32 + (lane & 31);
-#pragma unroll
-            for (int rr = 0; rr < 16; ++rr) {
-                const int dr = 8 * (rr >> 2) + (rr & 3);
-                const double rc = rcs[rr];
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    double run = (double)acc[L - 1][j][rr];
-#pragma unroll
-                    for (int l = L - 2; l >= 0; --l) run = __builtin_fma(run, 256.0, (double)acc[l][j][rr]);
-                    tile[(lrow + dr) * NBP + lcol + j * 32] = (float)__builtin_fma(run, out_scale, rc);
-                }
-            }
-        }
-        __syncthreads();
-        double acc_d = 0.0, acc_a = 0.0;
-        auto walk = [&](auto w_c) {
-            constexpr int W = decltype(w_c)::value;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int e4 = tid + t * kLThreads, row = e4 / Q, c4 = e4 - row * Q;
-                const int grow = row0 + row, gcol = col0 + 4 * c4;
-                const float4 v = *reinterpret_cast<const float4 *>(tile + row * NBP + 4 * c4);
-                const float ge[4] = {v.x, v.y, v.z, v.w}, th[4] = {th4[t].x, th4[t].y, th4[t].z, th4[t].w};
-                float dv[4], sum_d = 0.0f, sum_a = 0.0f;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float d_th, t_d, t_a;
-                    quantizer_bwd_terms<W, true>(th[e], k, d_th, t_d, t_a);
-                    dv[e] = ge[e] * d_th;
-                    sum_d = fmaf(ge[e], t_d, sum_d);
-                    sum_a = fmaf(ge[e], t_a, sum_a);
-                }
-                if (ok[t]) {
-                    acc_d += (double)sum_d;
-                    acc_a += (double)sum_a;
-                    store_stream4(a.out + ((int64_t)grow * a.cols + gcol), dv[0], dv[1], dv[2], dv[3], k.stream);
-                }
-            }
-        };
-        switch (a.fq_wsel) {
-            case 1: walk(std::integral_constant<int, 1>{}); break;
-            case 2: walk(std::integral_constant<int, 2>{}); break;
-            case 3: walk(std::integral_constant<int, 3>{}); break;
-            case 4: walk(std::integral_constant<int, 4>{}); break;
-            default: walk(std::integral_constant<int, 0>{}); break;
-        }
-        // partial sums of the block, in a fixed order
-        __syncthreads();
-        double *red = reinterpret_cast<double *>(lds);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            acc_d += __shfl_down(acc_d, off, 64);
-            acc_a += __shfl_down(acc_a, off, 64);
-        }
-        if (lane == 0) { red[2 * wave] = acc_d; red[2 * wave + 1] = acc_a; }
-        __syncthreads();
-        if (tid == 0) {
-            a.fq_partial[2 * logical] = (red[0] + red[2]) + (red[4] + red[6]);
-            a.fq_partial[2 * logical + 1] = (red[1] + red[3]) + (red[5] + red[7]);
         }
     };
 
@@ -1347,13 +1231,10 @@ __device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, f
     // the loads issued for steps past the end write LDS: they must be done before this wave ends
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 #undef CDL_INTERLEAVE
-    if (!RUNS) {
-        if (FUSED) fused_tile();
-        else write_tile(0, 0);
-    }
+    if (!RUNS) write_tile(0, 0);
 }
 
-template <bool TRANS, bool LONG_RUNS, bool FUSED = false>
+template <bool TRANS, bool LONG_RUNS>
 __global__ __launch_bounds__(kLThreads, 1)
 void limb_gemm_kernel(LimbArgs a)
 {
@@ -1363,11 +1244,36 @@ void limb_gemm_kernel(LimbArgs a)
     const float gscale = a.which == 0 ? a.plan->gscale_da : a.plan->gscale_db;
     const double out_scale = a.which == 0 ? a.plan->out_scale_da : a.plan->out_scale_db;
     switch (limbs) {
-        case 3: if (vec) limb_gemm_body<3, 3, TRANS, true, LONG_RUNS, FUSED>(a, limb_lds, gscale, out_scale); else limb_gemm_body<3, 3, TRANS, false, LONG_RUNS, FUSED>(a, limb_lds, gscale, out_scale); break;
-        case 4: if (vec) limb_gemm_body<4, 3, TRANS, true, LONG_RUNS, FUSED>(a, limb_lds, gscale, out_scale); else limb_gemm_body<4, 3, TRANS, false, LONG_RUNS, FUSED>(a, limb_lds, gscale, out_scale); break;
-        case 5: if (vec) limb_gemm_body<5, 3, TRANS, true, false, FUSED>(a, limb_lds, gscale, out_scale); else limb_gemm_body<5, 3, TRANS, false, false, FUSED>(a, limb_lds, gscale, out_scale); break;
-        default: if (vec) limb_gemm_body<6, 2, TRANS, true, false, FUSED>(a, limb_lds, gscale, out_scale); else limb_gemm_body<6, 2, TRANS, false, false, FUSED>(a, limb_lds, gscale, out_scale); break;
+        case 3: if (vec) limb_gemm_body<3, 3, TRANS, true, LONG_RUNS>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); else limb_gemm_body<3, 3, TRANS, false, LONG_RUNS>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
+        case 4: if (vec) limb_gemm_body<4, 3, TRANS, true, LONG_RUNS>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); else limb_gemm_body<4, 3, TRANS, false, LONG_RUNS>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
+        case 5: if (vec) limb_gemm_body<5, 3, TRANS, true, false>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); else limb_gemm_body<5, 3, TRANS, false, false>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
+        default: if (vec) limb_gemm_body<6, 2, TRANS, true, false>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); else limb_gemm_body<6, 2, TRANS, false, false>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
     }
+}
+
+// Both products of a small layer in one launch, one tile per block: neither fills the chip, and side by side they take the
+// time of the longer one.
+__global__ __launch_bounds__(kLThreads, 1)
+void limb_pair_kernel(LimbArgs a, LimbArgs b, int blocks_a)
+{
+    extern __shared__ __attribute__((aligned(16))) int8_t limb_lds[];
+    const bool vec = (a.N & 3) == 0, first = (int)blockIdx.x < blocks_a;
+    const BwdPlan *plan = a.plan;
+    const int limbs = first ? plan->limbs_da : plan->limbs_db, block = first ? (int)blockIdx.x : (int)blockIdx.x - blocks_a;
+    const float gscale = first ? plan->gscale_da : plan->gscale_db;
+    const double out_scale = first ? plan->out_scale_da : plan->out_scale_db;
+#define CDL_PAIR(L, TN)                                                                                                        \
+    if (first) { if (vec) limb_gemm_body<L, TN, false, true, false>(a, limb_lds, gscale, out_scale, block);                    \
+                 else limb_gemm_body<L, TN, false, false, false>(a, limb_lds, gscale, out_scale, block); }                     \
+    else { if (vec) limb_gemm_body<L, TN, true, true, false>(b, limb_lds, gscale, out_scale, block);                           \
+           else limb_gemm_body<L, TN, true, false, false>(b, limb_lds, gscale, out_scale, block); }
+    switch (limbs) {
+        case 3: CDL_PAIR(3, 3) break;
+        case 4: CDL_PAIR(4, 3) break;
+        case 5: CDL_PAIR(5, 3) break;
+        default: CDL_PAIR(6, 2) break;
+    }
+#undef CDL_PAIR
 }
 
 // dL/dQ(x) of a convolutional layer: the activation-gradient product with the rows of g gathered by taps (CONVG),
@@ -1389,7 +1295,7 @@ void limb_conv_dx_kernel(LimbArgs a)
     const int limbs = a.plan->limbs_da;
     const float gscale = a.plan->gscale_da;
     const double out_scale = a.plan->out_scale_da;
-#define CDL_CONV_DX(L, T) limb_gemm_body<L, T, false, true, false, false, false, true>(a, limb_lds, gscale, out_scale)
+#define CDL_CONV_DX(L, T) limb_gemm_body<L, T, false, true, false, false, true>(a, limb_lds, gscale, out_scale, (int)blockIdx.x)
     switch (limbs) {
         case 3: CDL_CONV_DX(3, TN); break;
         case 4: CDL_CONV_DX(4, TN); break;
@@ -1399,80 +1305,69 @@ void limb_conv_dx_kernel(LimbArgs a)
 #undef CDL_CONV_DX
 }
 
-// dL/dQ(x) of a convolutional layer with few channels on both sides (the first stages of a small CNN: 16 -> 16 channels,
-// 3 x 3: a contraction of 144 entries and 16 output columns, of which the limb kernel's 32 x 384 tiles would be nine
-// tenths padding): one thread per output entry (input pixel, channel c), the weights as doubles in LDS ([tap][n][c], so
-// that the lanes of a pixel read neighbouring words), every output a chain of at most R*S*N fused multiply-adds in
-// double - products of a float and an int8 are exact there, the additions round at 2^-53 relative.  CC: channels per
-// pixel padded to 16 or 32 lanes.
-template <int CC>
-__global__ __launch_bounds__(256)
-void conv_dx_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ w, int B, int H, int W, int C, int N,
-                           int R, int S, int stride, int pad, int P, int Q, double delta_w, float *__restrict__ out)
+// The plan of a backward call, made by the last block of the launch that forms the column sums (a launch of its own
+// took 5 us).  The flag of a block goes up when its sums have arrived; see cdl_finish.h.
+struct PlanArgs {
+    BwdPlan *plan;
+    const unsigned int *block_max;
+    int n_max;
+    const unsigned int *col_abs_a, *col_abs_b;
+    int n_abs_a, n_abs_b;
+    float delta_a, delta_b;
+    unsigned long long *flags;     // [blocks]
+    unsigned long long tag;
+};
+constexpr int kPlanMaxBlocks = 4096;
+
+// all 256 threads of block `self` of `blocks`
+__device__ __forceinline__ void plan_at_end(const PlanArgs &a, int self, int blocks)
 {
-    extern __shared__ double conv_wl[];      // [R*S*N][CC]
-    const int kc = R * S * N;
-    for (int i = threadIdx.x; i < kc * CC; i += 256) {
-        const int k = i / CC, c = i - k * CC, tap = k / N, n = k - tap * N;
-        conv_wl[i] = c < C ? (double)w[((int64_t)n * R * S + tap) * C + c] : 0.0;
-    }
+    if (!a.plan) return;      // (more blocks than flags: a launch of its own follows)
+    __shared__ unsigned int red[3][4];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    // a thread takes one channel of kPer consecutive pixels: every weight it reads from LDS serves kPer outputs
-    constexpr int kPer = 4;
-    constexpr int PIX = 256 / CC * kPer;
-    const int c = threadIdx.x % CC, pl = threadIdx.x / CC;
-    const int64_t pixels = (int64_t)B * H * W;
-    const int hw = H * W;
-    for (int64_t pix0 = (int64_t)blockIdx.x * PIX + pl * kPer; pix0 < pixels; pix0 += (int64_t)gridDim.x * PIX) {
-        int pb[kPer], ph[kPer], px[kPer];
+    if (self != blocks - 1) {
+        if (threadIdx.x == 0) device_store(a.flags + self, a.tag);
+        return;
+    }
+    for (int base = 0; base < blocks - 1; base += 8 * 256) {
+        bool waiting = true;
+        while (waiting) {
+            waiting = false;
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int64_t pix = min(pix0 + i, pixels - 1);
-            pb[i] = (int)(pix / hw);
-            const int rem = (int)(pix - (int64_t)pb[i] * hw);
-            ph[i] = rem / W;
-            px[i] = rem - ph[i] * W;
-        }
-        double acc[kPer] = {0.0, 0.0, 0.0, 0.0};
-        for (int r = 0; r < R; ++r) {
-            for (int t = 0; t < S; ++t) {
-                const float4 *gp[kPer];
-                bool ok[kPer];
-                bool any = false;
-#pragma unroll
-                for (int i = 0; i < kPer; ++i) {
-                    int hh = ph[i] + pad - r, ww = px[i] + pad - t;
-                    ok[i] = hh >= 0 && ww >= 0;
-                    if (stride == 2) { ok[i] = ok[i] && ((hh | ww) & 1) == 0; hh >>= 1; ww >>= 1; }
-                    ok[i] = ok[i] && hh < P && ww < Q;
-                    gp[i] = reinterpret_cast<const float4 *>(g + (ok[i] ? (((int64_t)pb[i] * P + hh) * Q + ww) * N : 0));
-                    any = any || ok[i];
-                }
-                if (!any) continue;
-                const double *wp = conv_wl + (int64_t)((r * S + t) * N) * CC + c;
-                for (int n4 = 0; n4 < N / 4; ++n4) {
-                    float4 v[kPer];
-#pragma unroll
-                    for (int i = 0; i < kPer; ++i) {
-                        v[i] = gp[i][n4];
-                        if (!ok[i]) v[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    }
-                    const double w0 = wp[(4 * n4) * CC], w1 = wp[(4 * n4 + 1) * CC], w2 = wp[(4 * n4 + 2) * CC], w3 = wp[(4 * n4 + 3) * CC];
-#pragma unroll
-                    for (int i = 0; i < kPer; ++i) {
-                        acc[i] = fma((double)v[i].x, w0, acc[i]);
-                        acc[i] = fma((double)v[i].y, w1, acc[i]);
-                        acc[i] = fma((double)v[i].z, w2, acc[i]);
-                        acc[i] = fma((double)v[i].w, w3, acc[i]);
-                    }
-                }
+            for (int u = 0; u < 8; ++u) {
+                const int i = base + u * 256 + (int)threadIdx.x;
+                if (i < blocks - 1 && device_load(a.flags + i) != a.tag) waiting = true;
             }
         }
-        if (c < C) {
 #pragma unroll
-            for (int i = 0; i < kPer; ++i)
-                if (pix0 + i < pixels) out[(pix0 + i) * C + c] = (float)(acc[i] * delta_w);
+        for (int u = 0; u < 8; ++u) {
+            const int i = base + u * 256 + (int)threadIdx.x;
+            if (i < blocks - 1) device_store(a.flags + i, 0ull);
         }
+    }
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    unsigned int v[3] = {0u, 0u, 0u};
+#pragma unroll 8
+    for (int i = threadIdx.x; i < a.n_max; i += 256) v[0] = max(v[0], a.block_max[i]);
+    auto sums = [&](const unsigned int *p, int n, unsigned int &m) {
+#pragma unroll 8
+        for (int i = threadIdx.x; i < n; i += 256) m = max(m, __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    sums(a.col_abs_a, a.n_abs_a, v[1]);
+    sums(a.col_abs_b, a.n_abs_b, v[2]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[q] = max(v[q], (unsigned int)__shfl_xor((int)v[q], off, 64));
+        if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[q] = max(max(red[q][0], red[q][1]), max(red[q][2], red[q][3]));
+        choose_limbs(a.plan, v[0], v[1], v[2], a.delta_a, a.delta_b);
     }
 }
 
@@ -1486,7 +1381,7 @@ struct ConvDxClasses { ConvDxClass c[4]; int tstep; };
 
 __global__ __launch_bounds__(256)
 void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int R, int S, int C, ConvDxClasses cls, int8_t *__restrict__ wr, int64_t ld,
-                         unsigned int *__restrict__ col_abs)
+                         unsigned int *col_abs, PlanArgs plan)
 {
     // one block per input channel c and class; four entries per thread and trip (one 4-byte store): the byte loads are a
     // stride of C apart and nothing but latency, so as many of them as possible are in flight
@@ -1515,7 +1410,9 @@ void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int R, int S, int 
     for (int o = 32; o > 0; o >>= 1) s_abs += (unsigned int)__shfl_down((int)s_abs, o, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s_abs;
     __syncthreads();
-    if (threadIdx.x == 0) col_abs[blockIdx.y * C + c] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&col_abs[blockIdx.y * C + c], (red[0] + red[1]) + (red[2] + red[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    plan_at_end(plan, (int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
 }
 
 // The forward product with the quantizer of the activations in its prologue: y = delta_a delta_b (Q_idx(X) . Wi^T)
@@ -1529,7 +1426,7 @@ __global__ __launch_bounds__(kLThreads, 1)
 void qgemm_quantize_fwd_kernel(LimbArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) int8_t limb_lds[];
-    limb_gemm_body<1, kQuantFwdTN, false, true, true, false, true>(a, limb_lds, 0.0f, 0.0);
+    limb_gemm_body<1, kQuantFwdTN, false, true, true, true>(a, limb_lds, 0.0f, 0.0, (int)blockIdx.x);
 }
 
 // out = out_scale * sum over the contraction splits.  Four partial sums per lane, combined in a fixed order,
@@ -1564,52 +1461,6 @@ void limb_reduce_kernel(const double *__restrict__ partial, int splits, int64_t 
     }
 }
 
-// limb_reduce_kernel<1> followed by the quantizer's backward pass on its output (Lemma 1; eq. partialW3, Jgradqw,
-// Jgradq_alpha_w): an entry of dL/dQ(w) is formed exactly as above, rounded to fp32 as above, optionally stored, and
-// multiplied by the partials of the quantizer at the matching entry of theta - the arithmetic of the stand-alone
-// backward kernel, on the same fp32 value it would have read back.  Partial scalar gradients: one pair per block.
-template <int W>
-__global__ __launch_bounds__(256)
-void limb_reduce_quantize_bwd_kernel(const double *__restrict__ partial, int splits, int64_t n, const BwdPlan *plan,
-                                     float *__restrict__ d_hat /* nullable */, const double *__restrict__ row_corr, int cols,
-                                     const float *__restrict__ theta, QConst k, float *__restrict__ d_theta,
-                                     double *__restrict__ fq_partial /* [gridDim.x][2] */)
-{
-    const double out_scale = plan->out_scale_db;
-    double acc_d = 0.0, acc_a = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        int p = 0;
-        for (; p + 3 < splits; p += 4) {
-            s0 += partial[(int64_t)p * n + i];
-            s1 += partial[(int64_t)(p + 1) * n + i];
-            s2 += partial[(int64_t)(p + 2) * n + i];
-            s3 += partial[(int64_t)(p + 3) * n + i];
-        }
-        for (; p < splits; ++p) s0 += partial[(int64_t)p * n + i];
-        const double s = (s0 + s1) + (s2 + s3);
-        const float ge = (float)__builtin_fma(s, out_scale, row_corr ? row_corr[i / cols] : 0.0);
-        if (d_hat) d_hat[i] = ge;
-        float d_th, t_d, t_a;
-        quantizer_bwd_terms<W, true>(theta[i], k, d_th, t_d, t_a);
-        d_theta[i] = ge * d_th;
-        acc_d += (double)(ge * t_d);
-        acc_a += (double)(ge * t_a);
-    }
-    __shared__ double red[8];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        acc_d += __shfl_down(acc_d, off, 64);
-        acc_a += __shfl_down(acc_a, off, 64);
-    }
-    if ((threadIdx.x & 63) == 0) { red[2 * (threadIdx.x >> 6)] = acc_d; red[2 * (threadIdx.x >> 6) + 1] = acc_a; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        fq_partial[2 * (size_t)blockIdx.x] = (red[0] + red[2]) + (red[4] + red[6]);
-        fq_partial[2 * (size_t)blockIdx.x + 1] = (red[1] + red[3]) + (red[5] + red[7]);
-    }
-}
-
 // dL/dQ(a) for a very short contraction (N <= 32: the first stages of a small CNN have 16 or 32 output
 // channels): d_a_hat[m][k] = delta_b * sum_n g[m][n] * b_idx[n][k].  One K-tile of the limb kernel would be
 // at least three quarters padding there; here a block takes 128 or 64 rows of g (kept in LDS as doubles), a thread
@@ -1620,6 +1471,7 @@ void limb_reduce_quantize_bwd_kernel(const double *__restrict__ partial, int spl
 // block idle (35 us; 28 us now); C columns per thread use each value read from LDS C times and load the C index
 // bytes of a row of b_idx as one word.
 constexpr int kDirectMaxN = 32;
+constexpr int64_t kDirectMinOutputs = 1 << 22;
 constexpr int direct_rows(int nn) { return 2048 / nn; }     // rows of g per block: 16 KiB of LDS as doubles
 
 template <int NN, int C>
@@ -1735,11 +1587,22 @@ __global__ __launch_bounds__(256) void g_colsum_kernel(const float *__restrict__
 
 __global__ __launch_bounds__(256) void g_colsum_finish_kernel(const double *__restrict__ partial, int blocks, int N, double mult, double *__restrict__ out)
 {
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
+    // 32 columns per block, eight threads to a column, eight loads in flight each (one thread per column is one chain of
+    // memory latencies: 60 us for 512 blocks' sums of 1000 columns)
+    __shared__ double part[8][33];
+    const int e = threadIdx.x & 31, sub = threadIdx.x >> 5, n = blockIdx.x * 32 + e;
     double s = 0.0;
-    for (int b = 0; b < blocks; ++b) s += partial[(int64_t)b * N + n];
-    out[n] = mult * s;
+    if (n < N) {
+#pragma unroll 8
+        for (int b = sub; b < blocks; b += 8) s += partial[(int64_t)b * N + n];
+    }
+    part[sub][e] = s;
+    __syncthreads();
+    if (sub == 0 && n < N) {
+#pragma unroll
+        for (int q = 1; q < 8; ++q) s += part[q][e];
+        out[n] = mult * s;
+    }
 }
 
 // ---- helpers -------------------------------------------------------------------------------
@@ -1801,7 +1664,7 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ g
 // zero-filled from `rows` up to the next multiple of 128.  Also adds, for every column c of src, the sum of
 // |src[r][c]| over the block's rows to col_abs[c] (one atomic per column and block; the array is cleared by the
 // max|g| kernel that runs first): the largest of these sums bounds what the rounding of g can do to one output of
-// the product that contracts over r, see plan_kernel.  One block moves a tile of 128 rows x
+// the product that contracts over r, see choose_limbs.  One block moves a tile of 128 rows x
 // 64 columns: 4-byte loads along the rows into LDS (row stride 17 words), then every thread takes a
 // 4 x 4 byte block, transposes it in registers and stores 4 bytes of four output rows, so that 32
 // lanes write 128 contiguous bytes.  VEC: cols % 4 == 0 (aligned 4-byte loads).
@@ -1814,15 +1677,29 @@ struct ConvGeom {
     int pad_word;
 };
 
-template <bool VEC, bool CONV = false>
-__global__ __launch_bounds__(256) void transpose_i8_kernel(const int8_t *__restrict__ src, int rows, int cols,
-                                                           int8_t *__restrict__ dst, int64_t ldd,
-                                                           unsigned int *__restrict__ col_abs, int tiles_per_block, ConvGeom geom)
+struct TransposeJob {
+    const int8_t *src;
+    int rows, cols;
+    int8_t *dst;
+    int64_t ldd;
+    unsigned int *col_abs;
+    int tiles_per_block;
+    int blocks_r, blocks;      // blocks along the rows, and in all
+};
+
+template <bool VEC, bool CONV>
+__device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int block, const ConvGeom &geom)
 {
+    const int8_t *__restrict__ src = job.src;
+    int8_t *__restrict__ dst = job.dst;
+    const int rows = job.rows, cols = job.cols, tiles_per_block = job.tiles_per_block;
+    const int64_t ldd = job.ldd;
+    unsigned int *__restrict__ col_abs = job.col_abs;
+    const int block_x = block % job.blocks_r, block_y = block / job.blocks_r;   // neighbouring blocks write neighbouring 128-byte pieces
     __shared__ uint32_t tile[128 * 17];
     __shared__ unsigned int abs_s[64];
     __shared__ int row_h0[128], row_w0[128], row_off[128];     // CONV: window origin of the tile's rows
-    const int c0 = blockIdx.y * 64;   // neighbouring blocks write neighbouring 128-byte pieces
+    const int c0 = block_y * 64;
     const int tid = threadIdx.x;
     if (tid < 64) abs_s[tid] = 0u;
     // A block takes `tiles_per_block` consecutive row tiles of its 64 columns and keeps the column sums of |x| in
@@ -1830,7 +1707,7 @@ __global__ __launch_bounds__(256) void transpose_i8_kernel(const int8_t *__restr
     // workload 5's activations queued 512 atomics on every address and doubled the kernel's time).
     unsigned int part[2][4] = {};
     const int row_tiles = (rows + 127) / 128;
-    const int t_end = min(row_tiles, ((int)blockIdx.x + 1) * tiles_per_block);
+    const int t_end = min(row_tiles, (block_x + 1) * tiles_per_block);
     // CONV: the thread's column (the same in all its loads) as a tap and an offset from the window's origin
     int tap_r = 0, tap_s = 0, tap_off = 0;
     if (CONV) {
@@ -1840,7 +1717,7 @@ __global__ __launch_bounds__(256) void transpose_i8_kernel(const int8_t *__restr
         tap_s = tap - tap_r * geom.S;
         tap_off = (tap_r * geom.W + tap_s) * geom.C + (c - tap * geom.C);
     }
-    for (int rt = (int)blockIdx.x * tiles_per_block; rt < t_end; ++rt) {
+    for (int rt = block_x * tiles_per_block; rt < t_end; ++rt) {
         const int r0 = rt * 128;
         if (CONV) {
             if (tid < 128) {
@@ -1910,17 +1787,16 @@ __global__ __launch_bounds__(256) void transpose_i8_kernel(const int8_t *__restr
     if (tid < 64 && c0 + tid < cols && abs_s[tid] != 0u) atomicAdd(&col_abs[c0 + tid], abs_s[tid]);
 }
 
-// Chooses the power-of-two scale of g and, for each backward product, the number of limbs.  With
-// sigma = 2^e > 1.01 max|g| and L limbs, q = rint(g 2^(8L-1)/sigma) is off by at most half a unit, i.e. every
-// entry of g is represented to within sigma 2^-8L, so one output of a product, delta * sum_c g_c idx_c, is off by
-// at most delta sigma 2^-8L sum_c |idx_c| whatever the signs and values of g: a bound, not an estimate.  The
-// largest sum of |idx| over the contraction (one per output column: col_abs, from the transposition kernels)
-// goes in, and L is the smallest count (3..6) that brings the bound under 9e-7 - the absolute part of the
-// parity tolerance, less a margin for the roundings of the recombination and of the fp32 result, which are
-// relative (1e-7) and covered by its relative part.  If six limbs do not reach it (contractions of many
-// millions of large indices) six are used and the bound, stored in the plan, says what was reached.
-constexpr double kLimbBoundTarget = 9e-7;
+// Blocks 0 .. a.blocks - 1 do job a, the rest job b; the last of all makes the plan.
+template <bool VEC, bool CONV>
+__global__ __launch_bounds__(256) void transpose_i8_kernel(TransposeJob a, TransposeJob b, ConvGeom geom, PlanArgs plan)
+{
+    if ((int)blockIdx.x < a.blocks) transpose_tiles<VEC, CONV>(a, blockIdx.x, geom);
+    else transpose_tiles<VEC, false>(b, (int)blockIdx.x - a.blocks, geom);
+    plan_at_end(plan, blockIdx.x, gridDim.x);
+}
 
+// The plan as a launch of its own (more blocks than plan_at_end has flags for).
 __global__ __launch_bounds__(1024)
 void plan_kernel(BwdPlan *plan, const unsigned int *__restrict__ block_max, int n_max,
                  const unsigned int *__restrict__ col_abs_a, int n_abs_a, const unsigned int *__restrict__ col_abs_b, int n_abs_b,
@@ -1949,23 +1825,7 @@ void plan_kernel(BwdPlan *plan, const unsigned int *__restrict__ block_max, int 
         __syncthreads();
     }
     if (threadIdx.x != 0) return;
-    const float amax = __uint_as_float(red_m[0]);
-    int e = 0;
-    if (amax > 0.0f) frexpf(amax * 1.01f, &e);   // amax * 1.01 = f 2^e with f in [0.5, 1)
-    e = max(min(e, 127), -80);                   // keeps 2^(8L-1-e) a normal float for every L
-    // d_a_hat contracts g with b_idx (step delta_b), d_b_hat with a_idx (step delta_a)
-    const double unit_da = (double)delta_b * (double)red_b[0], unit_db = (double)delta_a * (double)red_a[0];
-    int la = kMinLimbs, lb = kMinLimbs;
-    while (la < kMaxLimbs && unit_da * ldexp(1.0, e - 8 * la) > kLimbBoundTarget) ++la;
-    while (lb < kMaxLimbs && unit_db * ldexp(1.0, e - 8 * lb) > kLimbBoundTarget) ++lb;
-    plan->bound_da = unit_da * ldexp(1.0, e - 8 * la);
-    plan->bound_db = unit_db * ldexp(1.0, e - 8 * lb);
-    plan->limbs_da = la;
-    plan->limbs_db = lb;
-    plan->gscale_da = ldexpf(1.0f, 8 * la - 1 - e);
-    plan->gscale_db = ldexpf(1.0f, 8 * lb - 1 - e);
-    plan->out_scale_da = (double)delta_b * ldexp(1.0, e + 1 - 8 * la);
-    plan->out_scale_db = (double)delta_a * ldexp(1.0, e + 1 - 8 * lb);
+    choose_limbs(plan, red_m[0], red_a[0], red_b[0], delta_a, delta_b);
 }
 
 __global__ void zero_f32_kernel(float *p, int64_t n)
@@ -2024,11 +1884,9 @@ inline unsigned blocks_for(int64_t n, int per_block, int cap = 65536)
 }
 
 // workspace layout of a backward call
-constexpr int kFusedReduceBlocks = 2048;   // most blocks of limb_reduce_quantize_bwd_kernel
 
 struct BwdLayout {
-    size_t plan, block_max, ss_a, ss_b, fq_partial, fqb_partial, bt, at, partial, corr_da, corr_db, colsum_partial, total;
-    int fq_items;                 // most work items the fused activation-gradient product can have
+    size_t plan, records, block_max, ss_a, ss_b, scalars, bt, at, partial, corr_da, corr_db, colsum_partial, total;
     int n_max;                    // per-block partial results of the absmax launch
     int64_t ldn, ldm;             // row strides of the transposed index copies (odd multiples of kLBK)
     int nk_n, nk_m;               // K-tiles of the two contractions
@@ -2058,13 +1916,11 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
     L.n_max = (int)blocks_for(((int64_t)M * N) >> 2, 2048, 2048);
     size_t off = 0;
     L.plan = off;    off += align_up(sizeof(BwdPlan), 256);
+    L.records = off; off += kBwdDirectRecordBytes;
     L.block_max = off; off += align_up((size_t)L.n_max * sizeof(unsigned int), 256);
     L.ss_a = off;    off += align_up((size_t)K * sizeof(unsigned int), 256);   // sums of |a_idx| per column, directly followed by
     L.ss_b = off;    off += align_up((size_t)K * sizeof(unsigned int), 256);   // sums of |b_idx| per column (cleared together)
-    // fused quantizer backward: one pair of partial scalar gradients per work item of the narrowest column tile (cleared with the above)
-    L.fq_items = (int)((((int64_t)M + kLRows - 1) / kLRows) * ((K + limb_cols(6) - 1) / limb_cols(6)));
-    L.fq_partial = off; off += align_up((size_t)L.fq_items * 2 * sizeof(double), 256);
-    L.fqb_partial = off; off += align_up((size_t)kFusedReduceBlocks * 2 * sizeof(double), 256);   // same for the weight-gradient side: one pair per block
+    L.scalars = off; off += kQuantScalarBytes;     // the quantizers' backward passes that follow in the same call
     L.bt = off;      off += align_up((size_t)K * (size_t)L.ldn, 256);           // b_idx^T: [K][ldn]
     L.at = off;      off += align_up((size_t)K * (size_t)L.ldm, 256);           // a_idx^T: [K][ldm]
     // (one split: used only when a reduction kernel with the quantizer's backward pass follows)
@@ -2097,43 +1953,66 @@ int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
     // Runs pay off for short contractions (measured against one tile per block: -12 % at two K-tiles, -20 % at
     // one, +10 % at 24, where the start-up they save is small and the blocks, all in the same phase for the
     // whole launch, ask L2 for the same lines at the same moments).
-    const bool fused = a.fq_theta != nullptr;      // (one tile per block: the epilogue needs the LDS of the stages)
-    const bool long_runs = a.kt_per_split <= 4 && !fused;
-    const void *fn = fused ? (const void *)limb_gemm_kernel<false, false, true>
-                   : trans ? (long_runs ? (const void *)limb_gemm_kernel<true, true> : (const void *)limb_gemm_kernel<true, false>)
+    const bool long_runs = a.kt_per_split <= 4;
+    const void *fn = trans ? (long_runs ? (const void *)limb_gemm_kernel<true, true> : (const void *)limb_gemm_kernel<true, false>)
                            : (long_runs ? (const void *)limb_gemm_kernel<false, true> : (const void *)limb_gemm_kernel<false, false>);
     // more than 64 KiB of dynamic LDS has to be allowed per function (and per device: set it every time)
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLimbLdsBytes);
     if (e != hipSuccess) return hip_failed(e);
     const char *name = trans ? "limb_gemm_kernel(d_b_hat)" : "limb_gemm_kernel(d_a_hat)";
-    if (fused) CDL_LAUNCH("limb_gemm_kernel(d_a_hat + quantize_bwd)", stream, (limb_gemm_kernel<false, false, true>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
-    else if (trans && long_runs) CDL_LAUNCH(name, stream, (limb_gemm_kernel<true, true>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
+    if (trans && long_runs) CDL_LAUNCH(name, stream, (limb_gemm_kernel<true, true>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
     else if (trans) CDL_LAUNCH(name, stream, (limb_gemm_kernel<true, false>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
     else if (long_runs) CDL_LAUNCH(name, stream, (limb_gemm_kernel<false, true>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
     else CDL_LAUNCH(name, stream, (limb_gemm_kernel<false, false>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
     return check_launch();
 }
 
-void launch_transpose(const int8_t *src, int rows, int cols, int8_t *dst, int64_t ldd, unsigned int *col_abs, hipStream_t stream)
+// Whether the two products go into one launch: their blocks (in tiles of 384 columns) are at most four for every compute
+// unit, and those of the first product too few for runs of tiles to pay.
+bool limb_pair_serves(const LimbArgs &a, const LimbArgs &b)
 {
-    // about a thousand blocks where the matrix has that many tiles, each with up to 16 row tiles of its columns
-    const int row_tiles = (rows + 127) / 128, col_tiles = (cols + 63) / 64;
-    int per = (int)(((int64_t)row_tiles * col_tiles + 1023) / 1024);
-    per = per < 1 ? 1 : (per > 16 ? 16 : per);
-    const dim3 grid((row_tiles + per - 1) / per, col_tiles);
-    if (cols % 4 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, transpose_i8_kernel<true>, grid, dim3(256), 0, src, rows, cols, dst, ldd, col_abs, per, ConvGeom{});
-    else CDL_LAUNCH("transpose_i8_kernel", stream, transpose_i8_kernel<false>, grid, dim3(256), 0, src, rows, cols, dst, ldd, col_abs, per, ConvGeom{});
+    const int64_t tiles_c = (a.cols + limb_cols(5) - 1) / limb_cols(5);
+    const int64_t na = a.tiles_r * tiles_c, nb = b.tiles_r * tiles_c * b.splits;
+    return na <= 512 && na + nb <= 1024;
 }
 
-// the transposed matrix of input windows of a convolution, straight from the activations (rows = B*P*Q, cols = R*S*C)
-void launch_transpose_windows(const int8_t *x, const ConvGeom &g, int8_t *dst, int64_t ldd, unsigned int *col_abs, hipStream_t stream)
+int launch_limb_pair(LimbArgs a, LimbArgs b, hipStream_t stream)
 {
-    const int rows = g.B * g.P * g.Q, cols = g.R * g.S * g.C;
+    const int64_t tiles_c = (a.cols + limb_cols(6) - 1) / limb_cols(6);
+    if ((int64_t)limb_cols(3) * a.ldb > 0xffffffffLL || (int64_t)limb_cols(3) * b.ldb > 0xffffffffLL) return CDL_ERR_RANGE;
+    a.units_per_block = b.units_per_block = 1;
+    const unsigned ga = (unsigned)((a.tiles_r * tiles_c + 7) / 8 * 8), gb = (unsigned)((b.tiles_r * tiles_c * b.splits + 7) / 8 * 8);
+    const hipError_t e = hipFuncSetAttribute((const void *)limb_pair_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLimbLdsBytes);
+    if (e != hipSuccess) return hip_failed(e);
+    CDL_LAUNCH("limb_pair_kernel(d_a_hat, d_b_hat)", stream, limb_pair_kernel, dim3(ga + gb), dim3(kLThreads), kLimbLdsBytes, a, b, (int)ga);
+    return check_launch();
+}
+
+// about a thousand blocks where the matrix has that many tiles, each with up to 16 row tiles of its columns
+TransposeJob transpose_job(const int8_t *src, int rows, int cols, int8_t *dst, int64_t ldd, unsigned int *col_abs)
+{
     const int row_tiles = (rows + 127) / 128, col_tiles = (cols + 63) / 64;
     int per = (int)(((int64_t)row_tiles * col_tiles + 1023) / 1024);
     per = per < 1 ? 1 : (per > 16 ? 16 : per);
-    const dim3 grid((row_tiles + per - 1) / per, col_tiles);
-    CDL_LAUNCH("transpose_i8_kernel(windows)", stream, (transpose_i8_kernel<true, true>), grid, dim3(256), 0, x, rows, cols, dst, ldd, col_abs, per, g);
+    const int blocks_r = (row_tiles + per - 1) / per;
+    return TransposeJob{src, rows, cols, dst, ldd, col_abs, per, blocks_r, blocks_r * col_tiles};
+}
+
+// Column sums and transposed copies of the operands, and from them the plan (whatever `p` asks for).
+int launch_transposes(const TransposeJob &a, const TransposeJob &b, const ConvGeom *windows, PlanArgs p, void *flags, hipStream_t stream)
+{
+    const int blocks = a.blocks + b.blocks;
+    const PlanArgs here = p;
+    p.flags = reinterpret_cast<unsigned long long *>(flags);
+    p.tag = next_finish_tag();
+    if (blocks > kPlanMaxBlocks) p.plan = nullptr;
+    if (windows) CDL_LAUNCH("transpose_i8_kernel(windows)", stream, (transpose_i8_kernel<true, true>), dim3((unsigned)blocks), dim3(256), 0, a, b, *windows, p);
+    else if (a.cols % 4 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<true, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
+    else CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<false, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
+    if (!p.plan)
+        CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, here.plan, here.block_max, here.n_max, here.col_abs_a, here.n_abs_a,
+                   here.col_abs_b, here.n_abs_b, here.delta_a, here.delta_b);
+    return check_launch();
 }
 
 }  // namespace
@@ -2243,15 +2122,9 @@ int launch_qgemm_quantize_fwd(const float *x, const cdl_qparams &p, const int8_t
     return check_launch();
 }
 
-// few channels on both sides: the direct kernel (its weights in at most 48 KiB of LDS)
-bool conv_dx_is_direct(int32_t N, int32_t C, int32_t R, int32_t S)
-{
-    return C <= 32 && (int64_t)R * S * N <= 288 && (int64_t)R * S * N * (C <= 16 ? 16 : 32) * 8 <= 49152;
-}
-
 // workspace of the activation gradient of a convolution: [plan][per-block max|g|][col sums][Wr]
 struct ConvDxLayout {
-    size_t plan, block_max, ss_b, wr, total;
+    size_t plan, flags, block_max, ss_b, wr, total;
     int n_max, nk, classes;
     int64_t ld;
 };
@@ -2267,6 +2140,7 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     L.n_max = (int)blocks_for((M_out * N) >> 2, 2048, 2048);
     size_t off = 0;
     L.plan = off;      off += align_up(sizeof(BwdPlan), 256);
+    L.flags = off;     off += kPlanMaxBlocks * sizeof(unsigned long long);
     L.block_max = off; off += align_up((size_t)L.n_max * sizeof(unsigned int), 256);
     L.ss_b = off;      off += align_up((size_t)L.classes * C * sizeof(unsigned int), 256);
     L.wr = off;        off += align_up((size_t)L.classes * C * (size_t)L.ld, 256);
@@ -2285,14 +2159,6 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
 {
     const int P = (H + 2 * pad - R) / stride + 1, Q = (W + 2 * pad - S) / stride + 1;
     const int64_t M_out = (int64_t)B * P * Q;
-    if (conv_dx_is_direct(N, C, R, S)) {
-        const int cc = C <= 16 ? 16 : 32;
-        const size_t lds = (size_t)R * S * N * cc * sizeof(double);
-        const unsigned grid = blocks_for((int64_t)B * H * W, 256 / cc * 4, 16384);
-        if (cc == 16) CDL_LAUNCH("conv_dx_direct_kernel", stream, conv_dx_direct_kernel<16>, dim3(grid), dim3(256), lds, g, w_idx, B, H, W, C, N, R, S, stride, pad, P, Q, (double)delta_w, d_x_hat);
-        else CDL_LAUNCH("conv_dx_direct_kernel", stream, conv_dx_direct_kernel<32>, dim3(grid), dim3(256), lds, g, w_idx, B, H, W, C, N, R, S, stride, pad, P, Q, (double)delta_w, d_x_hat);
-        return check_launch();
-    }
     const ConvDxLayout L = conv_dx_layout(M_out, N, C, R, S, stride);
     char *base = reinterpret_cast<char *>(ws);
     BwdPlan *plan = reinterpret_cast<BwdPlan *>(base + L.plan);
@@ -2328,12 +2194,22 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
     if (zero_first)
         CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)B * H * W * C, 256, 4096)), dim3(256), 0, d_x_hat, (int64_t)B * H * W * C);
     if (n_cls == 0) return check_launch();
+    if (conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride)) {
+        ConvDxGrid grids[4];
+        for (int c = 0; c < n_cls; ++c)
+            grids[c] = ConvDxGrid{cl[c].oa, cl[c].oc, cl[c].Hc, cl[c].Wc, cl[c].pad_h, cl[c].pad_w, cl[c].Rc, cl[c].Sc, taps.c[c].r0, taps.c[c].s0};
+        return launch_conv_dx_direct(g, w_idx, grids, n_cls, B, H, W, C, N, R, S, P, Q, stride, delta_w, d_x_hat, stream);
+    }
     CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, 0);
-    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, dim3((unsigned)C, (unsigned)n_cls), dim3(256), 0,
-               w_idx, N, R, S, C, taps, wr, L.ld, ss_b);
     // (one limb count for all classes: the largest column sum of any of them)
-    CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
-               (const unsigned int *)nullptr, 0, ss_b, n_cls * C, 1.0f, delta_w);
+    PlanArgs pa{plan, block_max, L.n_max, nullptr, ss_b, 0, n_cls * C, 1.0f, delta_w, reinterpret_cast<unsigned long long *>(base + L.flags), next_finish_tag()};
+    const bool plan_apart = n_cls * C > kPlanMaxBlocks;
+    if (plan_apart) pa.plan = nullptr;
+    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, dim3((unsigned)C, (unsigned)n_cls), dim3(256), 0,
+               w_idx, N, R, S, C, taps, wr, L.ld, ss_b, pa);
+    if (plan_apart)
+        CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
+                   (const unsigned int *)nullptr, 0, ss_b, n_cls * C, 1.0f, delta_w);
     int rc = check_launch();
     if (rc != CDL_OK) return rc;
     LimbArgs a{};
@@ -2468,10 +2344,9 @@ int qconv_max_chunks() { return kConvMaxChunks; }
 
 int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
                      int32_t M, int32_t N, int32_t K, float delta_a, float delta_b, int32_t a_offset, int32_t b_offset,
-                     float *d_a_hat, float *d_b_hat, void *ws, hipStream_t stream, const FusedQuantBwd *fq, const FusedQuantBwd *fqb,
-                     const ConvWindows *cw)
+                     float *d_a_hat, float *d_b_hat, void *ws, hipStream_t stream, const ConvWindows *cw)
 {
-    const bool want_db = d_b_hat != nullptr || fqb != nullptr;     // the weight-gradient product runs
+    const bool want_db = d_b_hat != nullptr;
     if (cw && d_a_hat) return CDL_ERR_PARAM;                       // (windows: a_idx is not a matrix; only the product over its rows is served)
     if (d_a_hat && ((int64_t)M * K > 0) && N == 0)
         CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)M * K, 256, 4096)), dim3(256), 0, d_a_hat, (int64_t)M * K);
@@ -2479,7 +2354,13 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)N * K, 256, 4096)), dim3(256), 0, d_b_hat, (int64_t)N * K);
     if ((int64_t)M * N * K == 0) return check_launch();
 
-    if (d_a_hat && N <= kDirectMaxN) {
+    const BwdLayout L = bwd_layout(M, N, K);
+    char *base = reinterpret_cast<char *>(ws);
+    BwdPlan *plan = reinterpret_cast<BwdPlan *>(base + L.plan);
+    double *partial = reinterpret_cast<double *>(base + L.partial);
+    if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.splits, stream);
+    // (many outputs of few multiplications each: one thread per four outputs, see da_direct_kernel)
+    if (d_a_hat && N <= kDirectMaxN && ((int64_t)M * K >= kDirectMinOutputs || !bwd_direct_serves(M, N, K, true, want_db))) {
         // four columns per thread (two where 32 index values per column would not leave registers for four)
         const int c_per = N <= 16 ? 4 : 2;
         const int col_groups = (K + c_per - 1) / c_per;
@@ -2492,28 +2373,32 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         if (!want_db) return check_launch();
     }
 
-    const BwdLayout L = bwd_layout(M, N, K);
-    char *base = reinterpret_cast<char *>(ws);
-    BwdPlan *plan = reinterpret_cast<BwdPlan *>(base + L.plan);
+    if (!cw && bwd_direct_serves(M, N, K, d_a_hat != nullptr, d_b_hat != nullptr))
+        return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.splits, stream);
+
     int8_t *bt = reinterpret_cast<int8_t *>(base + L.bt);
     int8_t *at = reinterpret_cast<int8_t *>(base + L.at);
-    double *partial = reinterpret_cast<double *>(base + L.partial);
 
     unsigned int *block_max = reinterpret_cast<unsigned int *>(base + L.block_max);
     unsigned int *ss_a = reinterpret_cast<unsigned int *>(base + L.ss_a);
     unsigned int *ss_b = reinterpret_cast<unsigned int *>(base + L.ss_b);
     CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, gr, (int64_t)M * N, block_max,
-               ss_a, fq ? (int)((L.fq_partial - L.ss_a) / sizeof(unsigned int)) + L.fq_items * 4
-                        : (int)((L.ss_b - L.ss_a) / sizeof(unsigned int)) + K);
-    if (d_a_hat) launch_transpose(b_idx, N, K, bt, L.ldn, ss_b, stream);
-    if (want_db && cw) {
-        ConvGeom g{cw->B, cw->H, cw->W, cw->C, cw->R, cw->S, cw->stride, cw->pad, cw->P, cw->Q, 0};
-        const uint32_t pb = (uint32_t)(uint8_t)(int8_t)(-a_offset);
-        g.pad_word = (int)(pb | (pb << 8) | (pb << 16) | (pb << 24));
-        launch_transpose_windows(a_idx, g, at, L.ldm, ss_a, stream);
-    } else if (want_db) launch_transpose(a_idx, M, K, at, L.ldm, ss_a, stream);
-    CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
-               ss_a, want_db ? K : 0, ss_b, d_a_hat ? K : 0, delta_a, delta_b);
+               ss_a, (int)((L.ss_b - L.ss_a) / sizeof(unsigned int)) + K);
+    {
+        // the larger operand first: what is left when its blocks run out is the smaller one's
+        TransposeJob ja{}, jb{};
+        if (want_db) ja = transpose_job(a_idx, M, K, at, L.ldm, ss_a);
+        if (d_a_hat) (want_db ? jb : ja) = transpose_job(b_idx, N, K, bt, L.ldn, ss_b);
+        const PlanArgs pa{plan, block_max, L.n_max, ss_a, ss_b, want_db ? K : 0, d_a_hat ? K : 0, delta_a, delta_b, nullptr, 0ull};
+        ConvGeom g{};
+        if (cw) {
+            g = ConvGeom{cw->B, cw->H, cw->W, cw->C, cw->R, cw->S, cw->stride, cw->pad, cw->P, cw->Q, 0};
+            const uint32_t pb = (uint32_t)(uint8_t)(int8_t)(-a_offset);
+            g.pad_word = (int)(pb | (pb << 8) | (pb << 16) | (pb << 24));
+        }
+        const int rc = launch_transposes(ja, jb, cw ? &g : nullptr, pa, base + L.records, stream);
+        if (rc != CDL_OK) return rc;
+    }
     // operands stored as index - offset: d_a_hat lacks delta_b * ob * sum_n g[m][n] in row m, d_b_hat lacks
     // delta_a * oa * sum_m g[m][n] in row n; both sums are taken of the unrounded g, in double
     double *corr_da = nullptr, *corr_db = nullptr;
@@ -2528,73 +2413,41 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         const int rows_per = (M + kColsumBlocks - 1) / kColsumBlocks;
         const int blocks = (M + rows_per - 1) / rows_per;
         CDL_LAUNCH("g_colsum_kernel", stream, g_colsum_kernel, dim3(blocks), dim3(256), 0, gr, M, N, rows_per, cp);
-        CDL_LAUNCH("g_colsum_finish_kernel", stream, g_colsum_finish_kernel, dim3((N + 255) / 256), dim3(256), 0, cp, blocks, N,
+        CDL_LAUNCH("g_colsum_finish_kernel", stream, g_colsum_finish_kernel, dim3((N + 31) / 32), dim3(256), 0, cp, blocks, N,
                    (double)delta_a * (double)a_offset, corr_db);
     }
     int rc = check_launch();
     if (rc != CDL_OK) return rc;
 
-    if (d_a_hat) {
-        LimbArgs a{};
-        a.G = gr; a.M = M; a.N = N;
-        a.Bt = bt; a.ldb = L.ldn;
-        a.rows = M; a.cols = K; a.kc = N;
-        a.nk = L.nk_n;
-        a.tiles_r = (M + kLRows - 1) / kLRows; a.splits = 1; a.kt_per_split = L.nk_n;
-        a.plan = plan; a.which = 0;
-        a.out = d_a_hat; a.partial = nullptr;
-        a.row_corr = corr_da;
-        if (fq) {
-            a.fq_theta = fq->theta;
-            a.fq_partial = reinterpret_cast<double *>(base + L.fq_partial);
-            a.fq_k = make_const(*fq->p);
-            a.fq_k.stream = (int64_t)M * K >= kStreamFrom;
-            a.fq_wsel = band_template(a.fq_k);
-        }
-        rc = launch_limb_gemm(a, false, stream);
-        if (rc != CDL_OK) return rc;
-        if (fq && (fq->d_delta || fq->d_alpha)) {
-            const double d = (double)fq->p->delta;
-            rc = launch_scalar_finalize(a.fq_partial, L.fq_items, 1.0, d * d * d, fq->d_delta, fq->d_alpha, stream);
-            if (rc != CDL_OK) return rc;
-        }
+    LimbArgs pa{}, pb{};
+    pa.G = pb.G = gr;
+    pa.M = pb.M = M;
+    pa.N = pb.N = N;
+    pa.cols = pb.cols = K;
+    pa.plan = pb.plan = plan;
+    pa.Bt = bt; pa.ldb = L.ldn;
+    pa.rows = M; pa.kc = N;
+    pa.nk = L.nk_n;
+    pa.tiles_r = (M + kLRows - 1) / kLRows; pa.splits = 1; pa.kt_per_split = L.nk_n;
+    pa.which = 0;
+    pa.out = d_a_hat;
+    pa.row_corr = corr_da;
+    pb.Bt = at; pb.ldb = L.ldm;
+    pb.rows = N; pb.kc = M;
+    pb.nk = L.nk_m;
+    pb.tiles_r = (N + kLRows - 1) / kLRows; pb.splits = L.splits; pb.kt_per_split = L.kt_per_split;
+    pb.which = 1;
+    pb.out = d_b_hat; pb.partial = partial;
+    pb.row_corr = corr_db;
+    if (d_a_hat && want_db && limb_pair_serves(pa, pb)) {
+        rc = launch_limb_pair(pa, pb, stream);
+    } else {
+        if (d_a_hat) rc = launch_limb_gemm(pa, false, stream);
+        if (rc == CDL_OK && want_db) rc = launch_limb_gemm(pb, true, stream);
     }
+    if (rc != CDL_OK) return rc;
     if (want_db) {
-        LimbArgs a{};
-        a.G = gr; a.M = M; a.N = N;
-        a.Bt = at; a.ldb = L.ldm;
-        a.rows = N; a.cols = K; a.kc = M;
-        a.nk = L.nk_m;
-        a.tiles_r = (N + kLRows - 1) / kLRows; a.splits = L.splits; a.kt_per_split = L.kt_per_split;
-        a.plan = plan; a.which = 1;
-        a.out = d_b_hat; a.partial = partial;
-        a.to_partial = fqb ? 1 : 0;
-        a.row_corr = corr_db;
-        rc = launch_limb_gemm(a, true, stream);
-        if (rc != CDL_OK) return rc;
-        if (fqb) {
-            // the sum over the splits (one or more) and the quantizer's backward pass on the weights in one kernel
-            QConst k = make_const(*fqb->p);
-            k.stream = 0;
-            double *fp = reinterpret_cast<double *>(base + L.fqb_partial);
-            const int blocks = (int)blocks_for((int64_t)N * K, 256, kFusedReduceBlocks);
-#define CDL_RQ(WW) CDL_LAUNCH("limb_reduce_kernel(+ quantize_bwd)", stream, (limb_reduce_quantize_bwd_kernel<WW>), dim3(blocks), dim3(256), 0, \
-                              partial, L.splits, (int64_t)N * K, plan, d_b_hat, corr_db, K, fqb->theta, k, fqb->d_theta, fp)
-            switch (band_template(k)) {
-                case 1: CDL_RQ(1); break;
-                case 2: CDL_RQ(2); break;
-                case 3: CDL_RQ(3); break;
-                case 4: CDL_RQ(4); break;
-                default: CDL_RQ(0); break;
-            }
-#undef CDL_RQ
-            rc = check_launch();
-            if (rc != CDL_OK) return rc;
-            if (fqb->d_delta || fqb->d_alpha) {
-                const double d = (double)fqb->p->delta;
-                rc = launch_scalar_finalize(fp, blocks, 1.0, d * d * d, fqb->d_delta, fqb->d_alpha, stream);
-            }
-        } else if (L.splits > 1) {
+        if (L.splits > 1) {
             if ((int64_t)N * K <= 65536 && L.splits >= 32)
                 CDL_LAUNCH("limb_reduce_kernel", stream, limb_reduce_kernel<16>, dim3(blocks_for((int64_t)N * K * 16, 256, 4096)), dim3(256), 0,
                            partial, L.splits, (int64_t)N * K, plan, d_b_hat, corr_db, K);
@@ -2604,6 +2457,21 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
             rc = check_launch();
         }
     }
+    return rc;
+}
+
+int launch_qgemm_bwd_quantize_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,
+                                  int32_t a_offset, int32_t b_offset, float delta_b, const float *theta_a, const cdl_qparams &p_a,
+                                  float *d_theta_a, float *d_delta_a, float *d_alpha_a, float *d_b_hat, const float *theta_b,
+                                  const cdl_qparams *p_b, float *d_theta_b, float *d_delta_b, float *d_alpha_b, void *ws, hipStream_t stream)
+{
+    float *b_hat = d_b_hat ? d_b_hat : d_theta_b;      // (null: the weight gradient is not asked for)
+    int rc = launch_qgemm_bwd(g, a_idx, b_idx, M, N, K, p_a.delta, delta_b, a_offset, b_offset, d_theta_a, b_hat, ws, stream);
+    if (rc != CDL_OK) return rc;
+    void *scalars = reinterpret_cast<char *>(ws) + bwd_layout(M, N, K).scalars;
+    rc = launch_quantize_bwd(theta_a, d_theta_a, (int64_t)M * K, p_a, d_theta_a, d_delta_a, d_alpha_a, scalars, stream);
+    if (rc == CDL_OK && d_theta_b)
+        rc = launch_quantize_bwd(theta_b, b_hat, (int64_t)N * K, *p_b, d_theta_b, d_delta_b, d_alpha_b, scalars, stream);
     return rc;
 }
 

@@ -285,8 +285,8 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
 // ------------------------------------------------------------------------------------------
 template <int W, bool DTHETA, bool SCALARS>
 __global__ __launch_bounds__(kQuantThreads)
-void quantize_bwd_kernel(const float *__restrict__ theta, const float *__restrict__ g, int64_t n, QConst k,
-                         float *__restrict__ dtheta, ScalarFinish fin)
+void quantize_bwd_kernel(const float *__restrict__ theta, const float *g, int64_t n, QConst k,
+                         float *dtheta /* may be g */, ScalarFinish fin)
 {
     double acc_d = 0.0, acc_a = 0.0;
     const int64_t n4 = n >> 2;
@@ -571,8 +571,8 @@ void quantize_fwd_uniform_kernel(const float *__restrict__ theta, int64_t n, QCo
 
 template <int JH, bool ODD, bool DTHETA, bool SCALARS>
 __global__ __launch_bounds__(kUniThreads)
-void quantize_bwd_uniform_kernel(const float *__restrict__ theta, const float *__restrict__ g, int64_t n, QConst k, UniConst u,
-                                 float *__restrict__ dtheta, ScalarFinish fin)
+void quantize_bwd_uniform_kernel(const float *__restrict__ theta, const float *g, int64_t n, QConst k, UniConst u,
+                                 float *dtheta /* may be g */, ScalarFinish fin)
 {
     double acc_d = 0.0, acc_a = 0.0;
     const int64_t n4 = n >> 2;
@@ -909,12 +909,11 @@ size_t hist_bytes(int64_t n, int32_t n_levels)
     return align_up((size_t)hist_grid_for(n) * (size_t)n_levels * sizeof(unsigned long long), 256);
 }
 constexpr size_t kRecordBytes = 16384 * 2 * sizeof(unsigned long long);      // (marginal_finalize_kernel: at most 16 chunks of 256 levels)
-constexpr size_t kScalarBytes = (size_t)kMaxQuantBlocks * 2 * sizeof(double);
 
-ScalarFinish scalar_finish_args(void *ws, int64_t n, int32_t n_levels, int grid, double mul_d, double mul_a, float *d_delta, float *d_alpha)
+ScalarFinish scalar_finish_args(void *scalars, int grid, double mul_d, double mul_a, float *d_delta, float *d_alpha)
 {
     ScalarFinish f{};
-    double *area = reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + hist_bytes(n, n_levels) + kRecordBytes);
+    double *area = reinterpret_cast<double *>(scalars);
     if (grid > kFinishMaxBlocks) f.partial = area;
     else { f.records = reinterpret_cast<unsigned long long *>(area); f.tag = next_finish_tag(); }
     f.mul_d = mul_d; f.mul_a = mul_a; f.d_delta = d_delta; f.d_alpha = d_alpha;
@@ -1074,9 +1073,11 @@ int quantizer_window(double kappa, int n_levels)
     return W;
 }
 
+void *quantize_scalar_area(void *ws, int64_t n, int32_t n_levels) { return reinterpret_cast<char *>(ws) + hist_bytes(n, n_levels) + kRecordBytes; }
+
 size_t quantize_workspace_bytes(int64_t n, int32_t n_levels)
 {
-    return hist_bytes(n, n_levels) + kRecordBytes + kScalarBytes;
+    return hist_bytes(n, n_levels) + kRecordBytes + kQuantScalarBytes;
 }
 
 // ---- built-in scratch for callers that cannot allocate ---------------------------------------
@@ -1166,7 +1167,7 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
 }
 
 int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams &p,
-                        float *dtheta, float *d_delta, float *d_alpha, void *ws, hipStream_t stream)
+                        float *dtheta, float *d_delta, float *d_alpha, void *scalars, hipStream_t stream)
 {
     const bool want_scalars = (d_delta != nullptr) || (d_alpha != nullptr);
     if (n == 0) {
@@ -1182,7 +1183,7 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
     const int grid = grid_for(n);
     const double d = (double)p.delta;
     ScalarFinish fin{};
-    if (want_scalars) fin = scalar_finish_args(ws, n, p.n_levels, grid, 1.0, d * d * d, d_delta, d_alpha);
+    if (want_scalars) fin = scalar_finish_args(scalars, grid, 1.0, d * d * d, d_delta, d_alpha);
     const bool want_dtheta = dtheta != nullptr;
     const int jh = uniform_half_width(p, k);
     if (jh) {
@@ -1262,7 +1263,7 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     const double alpha = (double)p.alpha, delta = (double)p.delta;
     const double mul_theta = (double)scale * (-2.0 * alpha * delta / (double)n);
     ScalarFinish fin{};
-    if (want_scalars) fin = scalar_finish_args(ws, n, p.n_levels, grid, mul_theta, (double)scale * delta * delta / (double)n, d_delta, d_alpha);
+    if (want_scalars) fin = scalar_finish_args(quantize_scalar_area(ws, n, p.n_levels), grid, mul_theta, (double)scale * delta * delta / (double)n, d_delta, d_alpha);
     switch (band_template(k)) {
         case 1: launch_entropy_bwd_w<1>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
         case 2: launch_entropy_bwd_w<2>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;

@@ -22,3 +22,52 @@ def test_forward(M, N, K, oa, ob):
     ref = (a.astype(np.int64) + oa) @ (b.astype(np.int64) + ob).T
     assert np.array_equal(acc.cpu().numpy(), ref)
     assert np.array_equal(y.cpu().numpy(), ref.astype(np.float32) * np.float32(0.125))
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 4), (17, 5, 7), (16, 16, 64), (15, 33, 65), (33, 40, 6), (130, 1, 68), (260, 34, 129), (5000, 20, 70), (5121, 31, 64),
+                                   (700, 250, 300), (300, 700, 77), (5003, 61, 131),      # with the diagnostic words
+                                   (6001, 130, 333), (9001, 301, 333)])                   # limbs: the two products side by side, one after the other
+@pytest.mark.parametrize("oa,ob", [(0, 0), (128, 128)])
+def test_backward(oracle, M, N, K, oa, ob):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    rng = np.random.default_rng(M + N + K)
+    g = rng.standard_normal((M, N)).astype(np.float32)
+    a, b = cdl_inputs.draw_indices((M, K), -128, 127, seed=M), cdl_inputs.draw_indices((N, K), -128, 127, seed=N)
+    d_a, d_b = gu.empty((M, K), torch.float32), gu.empty((N, K), torch.float32)
+    ws = gu.workspace(cdl.qgemm_bwd_workspace_bytes(M, N, K))
+    ws.fill_(255)
+    for _ in range(2):
+        d_a.fill_(float("nan"))
+        d_b.fill_(float("nan"))
+        cdl.cdl_qgemm_bwd_offset(gu.dev(g), gu.dev(a), gu.dev(b), M, N, K, 0.015625, 0.0078125, oa, ob, d_a, d_b, ws)
+    g64 = g.astype(np.float64)
+    gu.assert_close(d_a.cpu().numpy(), 0.0078125 * (g64 @ (b.astype(np.float64) + ob)), "d_a_hat")
+    gu.assert_close(d_b.cpu().numpy(), 0.015625 * (g64.T @ (a.astype(np.float64) + oa)), "d_b_hat")
+    only = gu.empty((N, K), torch.float32)
+    cdl.cdl_qgemm_bwd_offset(gu.dev(g), gu.dev(a), gu.dev(b), M, N, K, 0.015625, 0.0078125, oa, ob, None, only, ws)
+    gu.assert_close(only.cpu().numpy(), 0.015625 * (g64.T @ (a.astype(np.float64) + oa)), "d_b_hat alone")
+
+
+# few and many channels, one and four classes of pixels, and just too large for the direct kernels
+@pytest.mark.parametrize("B,H,W,C,N,R,S,stride,pad", [(2, 9, 7, 16, 4, 3, 3, 1, 1), (3, 8, 11, 48, 20, 5, 3, 2, 2), (1, 13, 13, 80, 12, 1, 1, 2, 0),
+                                                      (40, 17, 19, 112, 36, 3, 3, 1, 1), (12, 57, 57, 48, 100, 3, 3, 1, 1)])
+@pytest.mark.parametrize("x_offset", [0, 128])
+def test_convolution_gradients(oracle, B, H, W, C, N, R, S, stride, pad, x_offset):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    rng = np.random.default_rng(C + N)
+    x = cdl_inputs.draw_indices((B, H, W, C), -128, 127, seed=C)
+    w = cdl_inputs.draw_indices((N, R, S, C), -127, 127, seed=N)
+    g = rng.standard_normal((B, P, Q, N)).astype(np.float32)
+    dX, dW = gu.empty((B, H, W, C), torch.float32), gu.empty((N, R, S, C), torch.float32)
+    geom = (B, H, W, C, N, R, S, stride, pad)
+    ws = gu.workspace(max(cdl.qconv_bwd_weights_workspace_bytes(*geom), cdl.qconv_bwd_activations_workspace_bytes(*geom)))
+    ws.fill_(255)
+    for _ in range(2):
+        cdl.cdl_qconv_bwd_weights(gu.dev(g), gu.dev(x), *geom, 0.015625, dW, ws, x_offset=x_offset)
+        cdl.cdl_qconv_bwd_activations(gu.dev(g), gu.dev(w), *geom, 0.0078125, dX, ws)
+    r_x, r_w = oracle.qconv_bwd(g, x.astype(np.int16) + x_offset, w, stride, pad, 0.015625, 0.0078125)
+    gu.assert_close(dX.cpu().numpy(), r_x, "d_x_hat")
+    gu.assert_close(dW.cpu().numpy(), r_w, "d_w_hat")

@@ -78,7 +78,12 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
 
 // scalars: the part of a call's workspace that holds the blocks' sums of the two scalar gradients (kQuantScalarBytes).
 // g and dtheta may be the same tensor.
-constexpr size_t kQuantScalarBytes = (size_t)kMaxQuantBlocks * 2 * sizeof(double);
+// Behind them, the table of the soft regime (cdl_soft.hip): made where the call has a workspace and kSoftFrom entries or more.
+constexpr int64_t kSoftFrom = 1 << 16;
+constexpr int kSoftMaxBins = 512;
+constexpr size_t kSoftTableBytes = (size_t)kSoftMaxBins * 48;
+constexpr size_t kQuantSumBytes = (size_t)kMaxQuantBlocks * 2 * sizeof(double);
+constexpr size_t kQuantScalarBytes = kQuantSumBytes + kSoftTableBytes;
 void *quantize_scalar_area(void *ws, int64_t n, int32_t n_levels);
 int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams &p,
                         float *dtheta, float *d_delta, float *d_alpha,

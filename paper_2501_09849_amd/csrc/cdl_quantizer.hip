@@ -23,10 +23,13 @@
 //   W = 1 (kappa > 10.9): two exponentials whose arguments are formed without rounding error;
 //   W = 2 (3.8 < kappa <= 10.9): one exponential t = exp(2 alpha delta u); the five weights are
 //          t^(j) exp(-kappa j^2), all multiplied by t^2 so that they are a polynomial in t;
-//   W = 3, 4: one exponential per level;  larger W: a loop over the band (soft regime).
+//   W = 3, 4: one exponential per level;  larger W (soft regime): a table (cdl_soft.hip), kernels on a common centre or a
+//          loop over the band.
 #include "cdl_internal.h"
 #include "cdl_finish.h"
+#include "cdl_marginal.h"
 #include "cdl_quantizer_math.h"
+#include "cdl_soft.h"
 
 #include <math.h>
 
@@ -44,97 +47,6 @@ constexpr int kPad = 4;   // spare histogram bins on each side, so that band off
 // every cell at or below 2^31.
 constexpr int kMaxHistTrips = 16;
 constexpr int kMargThreads = 512;   // threads of a block that builds a histogram
-constexpr int kHistScaleBits = 21;
-
-// What becomes of the per-block histograms: the marginal PMF and its entropy.
-struct MargFinish {
-    unsigned long long *rows;      // [gridDim.x][n_levels]: left there for marginal_finalize_kernel; null: finished in the kernel
-    unsigned long long *records;   // [blocks][n_levels][2]
-    unsigned long long tag;
-    double inv_n;                  // 1 / (n * 2^s)
-    float *marg;                   // [n_levels] or null
-    float *entropy_bits;           // [1] or null
-};
-
-// A record is a 64-bit sum and, as its check word, the sum combined with the tag.
-__device__ __forceinline__ void marginal_publish(unsigned long long v, size_t at, const MargFinish &f)
-{
-    device_store(f.records + 2 * at, v);
-    device_store(f.records + 2 * at + 1, v ^ f.tag);
-}
-
-// The last block's part, for all its T threads: adds the records of `rows` rows to `own` (thread i < n_levels: the
-// block's own sum for level i), normalises by n * 2^s and adds up the entropy terms in a fixed order.  The sums are
-// exact 64-bit integers, so their order does not matter.
-template <int T, int U>
-__device__ __forceinline__ void marginal_collect(unsigned long long own, int rows, int n_levels, const MargFinish &f)
-{
-    __shared__ unsigned long long red[T];
-    if (rows > 0) {
-        // threads: `lv` levels (a power of two) times T / lv rows at a time, U records in flight per thread
-        int lg = 1;
-        while ((1 << lg) < n_levels) ++lg;
-        const int lv = 1 << lg, level = (int)threadIdx.x & (lv - 1), sub = (int)threadIdx.x >> lg, subs = T >> lg;
-        unsigned long long s = 0ull;
-        if (level < n_levels) {
-            for (int r = sub; r < rows; r += U * subs) {
-                unsigned long long v[U];
-                bool waiting = true;
-                while (waiting) {
-                    unsigned long long c[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        // (past the end: the thread's first record once more)
-                        const int row = r + u * subs < rows ? r + u * subs : r;
-                        const unsigned long long *q = f.records + 2 * ((size_t)row * n_levels + level);
-                        v[u] = device_load(q);
-                        c[u] = device_load(q + 1);
-                    }
-                    waiting = false;
-#pragma unroll
-                    for (int u = 0; u < U; ++u) waiting = waiting || (v[u] ^ c[u]) != f.tag;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (r + u * subs < rows) {
-                        s += v[u];
-                        device_store(f.records + 2 * ((size_t)(r + u * subs) * n_levels + level) + 1, v[u]);
-                    }
-            }
-        }
-        red[threadIdx.x] = s;
-        __syncthreads();
-        if ((int)threadIdx.x < lv)
-            for (int q = 0; q < subs; ++q) own += red[q * lv + threadIdx.x];
-    }
-    double h = 0.0;
-    if ((int)threadIdx.x < n_levels) {
-        const double m = (double)own * f.inv_n;
-        if (f.marg) f.marg[threadIdx.x] = (float)m;
-        h = m > 0.0 ? -m * log2(m) : 0.0;
-    }
-    __shared__ double hs[4];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) h += __shfl_down(h, off, 64);
-    if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) hs[threadIdx.x >> 6] = h;
-    __syncthreads();
-    if (threadIdx.x == 0 && f.entropy_bits) *f.entropy_bits = (float)((hs[0] + hs[1]) + (hs[2] + hs[3]));
-}
-
-// The end of a kernel whose blocks have histograms.
-// Thread i < n_levels has the block's sum for level i.
-// FEW: the last block finishes (a template parameter: marginal_collect takes a kernel from 31 to 64
-// registers, the most with which eight waves of it fit a SIMD).
-template <int T, bool FEW>
-__device__ __forceinline__ void marginal_end(unsigned long long own, int n_levels, const MargFinish &f)
-{
-    if (FEW) {
-        if (blockIdx.x == gridDim.x - 1) marginal_collect<T, 8>(own, (int)blockIdx.x, n_levels, f);
-        else if ((int)threadIdx.x < n_levels) marginal_publish(own, (size_t)blockIdx.x * n_levels + threadIdx.x, f);
-    } else if ((int)threadIdx.x < n_levels) {
-        f.rows[(size_t)blockIdx.x * n_levels + threadIdx.x] = own;
-    }
-}
 
 // The rows of a large grid.  Grid: (ceil(levels / 8), chunks), about 64 blocks in all: a block adds its chunk of the
 // rows for eight levels (32 rows at a time, 64 contiguous bytes per row); the last block adds the chunks.  (A block for
@@ -904,9 +816,12 @@ int64_t hist_grid_for(int64_t n)
 bool hist_few(int64_t grid, int32_t n_levels) { return grid <= kFinishMaxBlocks && grid * n_levels <= 16384; }
 
 // workspace layout: [rows of the histogram kernel's blocks][records of the finishing blocks][scalar partials or records]
+// (or the table and the rows of moments of the soft regime)
 size_t hist_bytes(int64_t n, int32_t n_levels)
 {
-    return align_up((size_t)hist_grid_for(n) * (size_t)n_levels * sizeof(unsigned long long), 256);
+    const size_t rows = align_up((size_t)hist_grid_for(n) * (size_t)n_levels * sizeof(unsigned long long), 256);
+    const size_t soft = n >= kSoftFrom ? align_up(soft_fwd_bytes(n, n_levels), 256) : 0;
+    return rows > soft ? rows : soft;
 }
 constexpr size_t kRecordBytes = 16384 * 2 * sizeof(unsigned long long);      // (marginal_finalize_kernel: at most 16 chunks of 256 levels)
 
@@ -971,6 +886,14 @@ int uniform_half_width(const cdl_qparams &p, const QConst &k)
     if (kappa * jh * jh > 72.0) return 0;
     return jh;
 }
+
+// Where the table of cdl_soft.hip is faster than these kernels although it takes two small launches more (forward + backward,
+// 31 levels: 0.5 M entries 29 against 26 us, 1 M 33.8 against 36.7, 2 M 43 against 52, 25.6 M 162 against 403; 15 levels: 2 M 43
+// against 41 us, 4 M 51 against 62).  The loop over the levels, forward only for sets that it serves, is left for the
+// table from kSoftFrom on (63 levels, 65 K entries: 36 against 50 us; 255 levels: 73 against 156, 1 M entries 124 against 245).
+// The backward pass of those larger sets stays with the loop: in the soft regime the scalar gradients' sums cancel
+// almost completely, and what is left there are the roundings of the loop's own arithmetic.
+bool soft_from_uniform(const cdl_qparams &p, int64_t n) { return n * (p.n_levels / 2) >= (1ll << 24); }
 
 UniConst make_uniform(const cdl_qparams &p, int jh)
 {
@@ -1137,6 +1060,8 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
         fin.marg = marg;
         fin.entropy_bits = entropy_bits;
     }
+    const SoftPlan plan = want_marg && (soft_from_uniform(p, n) || !uniform_half_width(p, k)) ? soft_plan(p, k, n) : SoftPlan{};
+    if (plan.bins) return launch_soft_fwd(theta, n, p, k, plan, idx, soft, fin, ws, stream);
     const bool want_idx = idx != nullptr, want_soft = soft != nullptr;
     const int jh = (want_soft || want_marg) ? uniform_half_width(p, k) : 0;
     if (jh) {
@@ -1184,6 +1109,11 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
     const double d = (double)p.delta;
     ScalarFinish fin{};
     if (want_scalars) fin = scalar_finish_args(scalars, grid, 1.0, d * d * d, d_delta, d_alpha);
+    const SoftPlan plan = want_scalars && uniform_half_width(p, k) && soft_from_uniform(p, n) ? soft_plan(p, k, n) : SoftPlan{};
+    if (plan.bins) {
+        const int rc = launch_soft_bwd(theta, g, n, p, k, plan, dtheta, fin, reinterpret_cast<char *>(scalars) + kQuantSumBytes, grid, stream);
+        return rc != CDL_OK ? rc : launch_scalar_end(fin, grid, stream);
+    }
     const bool want_dtheta = dtheta != nullptr;
     const int jh = uniform_half_width(p, k);
     if (jh) {

@@ -1,0 +1,577 @@
+// Soft regime (few or many levels, most of them live: the paper starts training at alpha = 500, Sec. V-B).
+//
+// Once the quantizer's parameters are fixed every quantity of an entry is a function of theta alone.  With
+// r = theta / delta - c0 (c0 the centre of the level set) and mu(r) the mean of the level offset under the CPMF,
+//     Q_d = delta (c0 + mu),   Var = mu' / (2 kappa),   third central moment = mu'' / (4 kappa^2)
+// (in steps; kappa = alpha delta^2), because a derivative with respect to r brings down a cumulant of the CPMF and a factor
+// 2 kappa.  mu is analytic with features no finer than the CPMF's own width sigma = 1 / sqrt(2 kappa): on intervals of a quarter
+// of sigma a polynomial of degree 7 through the Chebyshev nodes gives mu to 1e-12, Var to 1e-10 and the third moment to
+// 3e-8 of their size (all against sums in double over the levels), so one table of eight coefficients per interval replaces the loop over
+// the levels: a gather from LDS and 21 fused multiply-adds in double per entry where 31 levels took 250 instructions.
+// The table is made by a kernel of its own (the levels' exponentials in double, at 8 nodes per interval).  Forward and
+// backward of 25.6 M entries and 31 levels: 403 -> 162 us, 3.3 TB/s of the traffic (copies reach 5).
+//
+// Marginal PMF: the sum of P_k(r) over the entries is wanted for every level k.  An entry adds the Chebyshev polynomials
+// T_0 .. T_5 of its place in its interval to six cells of a histogram (fixed point, LDS integer atomics); since on an
+// interval P_k = sum_m c_km T_m up to 4e-9 of its peak, the sums over the entries follow from the cells - at the end, once
+// per interval and level.
+//
+// Entries beyond the table's range (theta more than twice as far out as the last level) are evaluated one by one as the
+// other kernels do, and add their probabilities to a histogram of levels.
+#include "cdl_internal.h"
+#include "cdl_soft.h"
+
+#include <math.h>
+
+namespace cdl {
+
+namespace {
+
+constexpr int kSoftBwdThreads = 256;
+constexpr int kSoftScaleBits = 18;         // an entry adds rint(T_m * 2^18) to a cell: at most 2^12 entries between two flushes
+constexpr int kSoftFinBlocks = 32;
+constexpr int kM = kSoftMoments;
+constexpr int kSoftOwn = (kM * kSoftMaxBins + kSoftThreads - 1) / kSoftThreads;      // cells that a thread adds up
+
+struct SoftConst {
+    int bins, copies, lg_copies, n_levels, small_set;
+    int hist_copies, lg_hist_copies;
+    double half_range, inv_h, c0, inv_delta, delta, kappa;
+    double r_safe;
+    double lo_off;         // offset of the lowest level from the centre
+};
+
+// ---- the table: coefficients 0..3 as doubles, 4..7 as floats, of t^q, t in [-1, 1] along the interval ----
+
+// rows of the inverse of the Vandermonde matrix of the eight Chebyshev nodes x_i = cos((2 i + 1) pi / 16): coefficient q of the
+// interpolating polynomial is sum_i inv[q][i] f(x_i)
+struct NodeMatrix { double node[8], inv[8][8]; };
+
+__global__ __launch_bounds__(64)
+void soft_table_kernel(SoftConst s, NodeMatrix m, double *__restrict__ table /* [bins][4] doubles, then [bins][4] floats */)
+{
+    __shared__ double mu[8];
+    const int bin = blockIdx.x, node = threadIdx.x >> 3, part = threadIdx.x & 7;
+    const double r = -s.half_range + (bin + 0.5 * (1.0 + m.node[node])) / s.inv_h;
+    // relative to the nearest level, so that the largest weight is about one
+    const double near = fmin(fmax(rint(r - s.lo_off), 0.0), (double)(s.n_levels - 1)) + s.lo_off, d0 = r - near;
+    double Z = 0.0, S = 0.0;
+    for (int k = part; k < s.n_levels; k += 8) {
+        const double o = s.lo_off + k, d = r - o, w = exp(s.kappa * (d0 * d0 - d * d));
+        Z += w;
+        S = fma(o - near, w, S);
+    }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) {
+        Z += __shfl_xor(Z, off, 64);
+        S += __shfl_xor(S, off, 64);
+    }
+    if (part == 0) mu[node] = near + S / Z;
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        double c = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c = fma(m.inv[threadIdx.x][i], mu[i], c);
+        if (threadIdx.x < 4) table[(size_t)bin * 4 + threadIdx.x] = c;
+        else reinterpret_cast<float *>(table + (size_t)s.bins * 4)[(size_t)bin * 4 + threadIdx.x - 4] = (float)c;
+    }
+}
+
+// The table in LDS as three arrays of 16 bytes per interval ({c0, c1}, {c2, c3}, {c4 .. c7}), each in `copies` copies side by
+// side: the copy is the group of banks, so that the lanes of a gather, each in its own interval, do not meet.
+template <int T>
+__device__ __forceinline__ void load_table(const SoftConst &s, const double *__restrict__ table, uint4 *lds)
+{
+    const uint4 *d = reinterpret_cast<const uint4 *>(table), *f = reinterpret_cast<const uint4 *>(table + (size_t)s.bins * 4);
+    for (int i = threadIdx.x; i < s.bins << s.lg_copies; i += T) {
+        const int b = i >> s.lg_copies;
+        lds[i] = d[2 * b];
+        lds[(s.bins << s.lg_copies) + i] = d[2 * b + 1];
+        lds[2 * (s.bins << s.lg_copies) + i] = f[b];
+    }
+}
+
+struct SoftPlace { int bin; double t; bool in; };
+__device__ __forceinline__ SoftPlace soft_place(double r, const SoftConst &s)
+{
+    SoftPlace p;
+    p.in = fabs(r) <= s.half_range;
+    const double x = fmin(fmax((r + s.half_range) * s.inv_h, 0.0), (double)s.bins);
+    p.bin = min((int)x, s.bins - 1);
+    p.t = fma(2.0, x - (double)p.bin, -1.0);
+    return p;
+}
+
+struct SoftCoef { double c[8]; };
+__device__ __forceinline__ SoftCoef soft_coef(int bin, const SoftConst &s, const uint4 *lds)
+{
+    const int at = (bin << s.lg_copies) + ((int)threadIdx.x & (s.copies - 1)), plane = s.bins << s.lg_copies;
+    const double2 a = *reinterpret_cast<const double2 *>(lds + at), b = *reinterpret_cast<const double2 *>(lds + plane + at);
+    const float4 f = *reinterpret_cast<const float4 *>(lds + 2 * plane + at);
+    return SoftCoef{{a.x, a.y, b.x, b.y, (double)f.x, (double)f.y, (double)f.z, (double)f.w}};
+}
+
+// Sums over all levels in double, for entries outside the table (at most 33 levels), with offsets from the nearest level.
+// r is held at +-r_safe, where the CPMF is one level to 1e-13 (theta may be infinite).
+struct SoftSums { double near, d0, Z, S1, S2, S3; };
+__device__ __forceinline__ double soft_clamp(double r, const SoftConst &s) { return fmin(fmax(r, -s.r_safe), s.r_safe); }
+__device__ __forceinline__ SoftSums soft_direct(double r, const SoftConst &s)
+{
+    const double near = fmin(fmax(rint(r - s.lo_off), 0.0), (double)(s.n_levels - 1)) + s.lo_off;
+    SoftSums q{near, r - near, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int k = 0; k < s.n_levels; ++k) {
+        const double j = s.lo_off + k - near, w = exp(s.kappa * j * (2.0 * q.d0 - j));
+        q.Z += w;
+        q.S1 = fma(j, w, q.S1);
+        q.S2 = fma(j * j, w, q.S2);
+        q.S3 = fma(j * j * j, w, q.S3);
+    }
+    return q;
+}
+
+// ---- forward ----
+// One block of 1024 threads per compute unit.  LDS: [table][levels, 64 bits][cells: (6 bins) x hist_copies].  A cell lies in
+// the bank group of its copy, as in the other histogram kernels.  After hist_copies trips of the loop (2^12 entries for a
+// cell) every thread moves its cells to 64-bit registers.
+template <bool IDX, bool SOFT>
+__global__ __launch_bounds__(kSoftThreads)
+void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftConst s, const double *__restrict__ table,
+                     int8_t *__restrict__ idx, float *__restrict__ soft, long long *__restrict__ rows /* [gridDim.x][6 bins + levels] */)
+{
+    extern __shared__ __attribute__((aligned(16))) uint4 soft_lds[];
+    unsigned long long *levels = reinterpret_cast<unsigned long long *>(soft_lds + 3 * (s.bins << s.lg_copies));
+    int *cells = reinterpret_cast<int *>(levels + s.n_levels);
+    const int n_cells = kM * s.bins;
+    load_table<kSoftThreads>(s, table, soft_lds);
+    for (int i = threadIdx.x; i < n_cells << s.lg_hist_copies; i += kSoftThreads) cells[i] = 0;
+    if ((int)threadIdx.x < s.n_levels) levels[threadIdx.x] = 0ull;
+    __syncthreads();
+    int *mine = cells + ((int)threadIdx.x & (s.hist_copies - 1));
+    long long own[kSoftOwn] = {};
+
+    auto flush = [&](bool again) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kSoftOwn; ++q) {
+            const int i = q * kSoftThreads + threadIdx.x;
+            if (i < n_cells) {
+                int *c = cells + (i << s.lg_hist_copies);
+                long long v = 0;
+                for (int j = 0; j < s.hist_copies; ++j) {
+                    const int at = (j + (i >> (5 - s.lg_hist_copies))) & (s.hist_copies - 1);
+                    v += c[at];
+                    c[at] = 0;
+                }
+                own[q] += v;
+            }
+        }
+        if (again) __syncthreads();
+    };
+
+    // true: done; false: an entry beyond the table
+    auto inside = [&](float th, float &sv) -> bool {
+        const double r = fma((double)th, s.inv_delta, -s.c0);
+        const SoftPlace p = soft_place(r, s);
+        if (p.in) {
+            if (SOFT) {
+                const SoftCoef q = soft_coef(p.bin, s, soft_lds);
+                double mu = q.c[7];
+#pragma unroll
+                for (int i = 6; i >= 0; --i) mu = fma(mu, p.t, q.c[i]);
+                sv = (float)(s.delta * (s.c0 + mu));
+            }
+            constexpr float kOne = (float)(1 << kSoftScaleBits);
+            const float t = (float)p.t;
+            int *c = mine + ((kM * p.bin) << s.lg_hist_copies);
+            atomicAdd(c, 1 << kSoftScaleBits);
+            float before = 1.0f, now = t;
+#pragma unroll
+            for (int m = 1; m < kM; ++m) {
+                c += s.hist_copies;
+                atomicAdd(c, (int)rintf(now * kOne));
+                const float next = fmaf(2.0f * t, now, -before);
+                before = now;
+                now = next;
+            }
+        }
+        return p.in;
+    };
+    auto outside = [&](float th) -> float {
+        if (s.small_set) {
+            const double r = soft_clamp(fma((double)th, s.inv_delta, -s.c0), s);
+            const SoftSums q = soft_direct(r, s);
+            const double scale = (double)(1u << kHistScaleBits) / q.Z;
+#pragma unroll 1
+            for (int l = 0; l < s.n_levels; ++l) {
+                const double j = s.lo_off + l - q.near;
+                atomicAdd(levels + l, (unsigned long long)rint(exp(s.kappa * j * (2.0 * q.d0 - j)) * scale));
+            }
+            return (float)(s.delta * (s.c0 + q.near + q.S1 / q.Z));
+        }
+        GenericSums q;
+        generic_sums<IDX>(th, k, q);
+        const float inv = fast_rcp(q.Z), two_u = 2.0f * q.u, scale = inv * (float)(1u << kHistScaleBits);
+#pragma unroll 1
+        for (int j = q.jlo; j <= q.jhi; ++j)
+            atomicAdd(levels + ((int)q.cf - k.lo + j), (unsigned long long)rintf(generic_weight(j, two_u, k) * scale));
+        return fmaf(q.S1 * inv, k.delta, q.cf * k.delta);
+    };
+
+    const int64_t n4 = n >> 2, stride = (int64_t)gridDim.x * kSoftThreads;
+    int trips = 0;
+    int64_t v = (int64_t)blockIdx.x * kSoftThreads + threadIdx.x;
+    float4 ahead = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (v < n4) ahead = load_stream4(theta + 4 * v, k.stream);
+    for (int64_t base = (int64_t)blockIdx.x * kSoftThreads; base < n4; base += stride, v += stride) {
+        const float th[4] = {ahead.x, ahead.y, ahead.z, ahead.w};
+        if (v + stride < n4) ahead = load_stream4(theta + 4 * (v + stride), k.stream);
+        if (v < n4) {
+            float sv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            bool in[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) in[e] = inside(th[e], sv[e]);
+            if (!(in[0] && in[1] && in[2] && in[3])) {
+#pragma unroll 1
+                for (int e = 0; e < 4; ++e) {
+                    if (e == 0 ? in[0] : (e == 1 ? in[1] : (e == 2 ? in[2] : in[3]))) continue;
+                    const float sv_e = outside(e == 0 ? th[0] : (e == 1 ? th[1] : (e == 2 ? th[2] : th[3])));
+                    sv[0] = e == 0 ? sv_e : sv[0]; sv[1] = e == 1 ? sv_e : sv[1];
+                    sv[2] = e == 2 ? sv_e : sv[2]; sv[3] = e == 3 ? sv_e : sv[3];
+                }
+            }
+            if (SOFT) store_stream4(soft + 4 * v, sv[0], sv[1], sv[2], sv[3], k.stream);
+            if (IDX) {
+                int ci[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ci[e] = (int)anchor_level<true>(th[e], k);
+                reinterpret_cast<uint32_t *>(idx)[v] = pack_indices(ci[0], ci[1], ci[2], ci[3], k.idx_off);
+            }
+        }
+        if (++trips == s.hist_copies) {
+            flush(true);
+            trips = 0;
+        }
+    }
+    flush(true);
+    // ragged tail: the last 1..3 entries
+    if (blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x == 0)
+            for (int64_t e = n4 << 2; e < n; ++e) {
+                float sv = 0.0f;
+                if (!inside(theta[e], sv)) sv = outside(theta[e]);
+                if (SOFT) soft[e] = sv;
+                if (IDX) idx[e] = (int8_t)((int)anchor_level<true>(theta[e], k) - k.idx_off);
+            }
+        flush(true);
+    }
+    long long *row = rows + (size_t)blockIdx.x * (n_cells + s.n_levels);
+#pragma unroll
+    for (int q = 0; q < kSoftOwn; ++q) {
+        const int i = q * kSoftThreads + threadIdx.x;
+        if (i < n_cells) row[i] = own[q];
+    }
+    if ((int)threadIdx.x < s.n_levels) row[n_cells + threadIdx.x] = (long long)levels[threadIdx.x];
+}
+
+// From the moments to the marginal PMF.  Block b takes the intervals [b bins / B, (b + 1) bins / B): adds the rows' cells,
+// turns the six moments S_m of an interval into weights of its six Chebyshev nodes x_q (the discrete orthogonality of the T_m:
+// w_q = (S_0 + 2 sum_m S_m T_m(x_q)) / 6 gives sum_q w_q f(x_q) = the sum of f over the entries for every polynomial f of
+// degree 5), and adds w_q P_k(x_q) for all levels k.
+constexpr int kSoftFinThreads = 1024;
+constexpr int kFinCells = 128;                               // at least kM * kSoftMaxBins / kSoftFinBlocks
+static_assert(kM * ((kSoftMaxBins + kSoftFinBlocks - 1) / kSoftFinBlocks) <= kFinCells, "cells of a block");
+struct NodePlace { double x[kM]; };
+
+__global__ __launch_bounds__(kSoftFinThreads)
+void soft_marginal_kernel(const long long *__restrict__ rows, int n_rows, SoftConst s, NodePlace nodes, MargFinish fin)
+{
+    __shared__ long long part[kSoftFinThreads];
+    __shared__ double red[kSoftFinThreads];
+    __shared__ long long sums[kFinCells];
+    __shared__ double weight[kFinCells], place[kFinCells], from[kFinCells];
+    const int tid = threadIdx.x, n_cells = kM * s.bins, row = n_cells + s.n_levels;
+    const int b0 = (int)((int64_t)blockIdx.x * s.bins / gridDim.x), b1 = (int)((int64_t)(blockIdx.x + 1) * s.bins / gridDim.x);
+    const int cells = kM * (b1 - b0);
+    {
+        constexpr int kSubs = kSoftFinThreads / kFinCells;
+        const int c = tid & (kFinCells - 1), sub = tid / kFinCells;
+        long long v = 0;
+        if (c < cells) {
+#pragma unroll 16
+            for (int r = sub; r < n_rows; r += kSubs) v += rows[(size_t)r * row + kM * b0 + c];
+        }
+        part[tid] = v;
+        __syncthreads();
+        if (tid < kFinCells) {
+            long long t = 0;
+#pragma unroll
+            for (int q = 0; q < kSubs; ++q) t += part[q * kFinCells + tid];
+            sums[tid] = t;
+        }
+        __syncthreads();
+    }
+    // eight threads to a node for the normaliser
+    {
+        const int node = tid >> 3, lane8 = tid & 7;
+        const int i = node / kM, q = node % kM;
+        const double x = nodes.x[q];
+        const double r = -s.half_range + (b0 + i + 0.5 * (1.0 + x)) / s.inv_h;
+        const double near = fmin(fmax(rint(r - s.lo_off), 0.0), (double)(s.n_levels - 1)) + s.lo_off, d0 = r - near;
+        double Z = 0.0;
+        if (node < cells)
+            for (int l = lane8; l < s.n_levels; l += 8) {
+                const double d = r - (s.lo_off + l);
+                Z += exp(s.kappa * (d0 * d0 - d * d));
+            }
+#pragma unroll
+        for (int off = 4; off > 0; off >>= 1) Z += __shfl_xor(Z, off, 64);
+        if (node < cells && lane8 == 0) {
+            double w = 0.5 * (double)sums[kM * i], before = 1.0, now = x;
+#pragma unroll
+            for (int m = 1; m < kM; ++m) {
+                w = fma((double)sums[kM * i + m], now, w);
+                const double next = fma(2.0 * x, now, -before);
+                before = now;
+                now = next;
+            }
+            weight[node] = w * (2.0 / kM) / Z;
+            place[node] = r;
+            from[node] = d0 * d0;
+        }
+    }
+    __syncthreads();
+    // level x part of the nodes
+    int lg = 3;
+    while ((1 << lg) < s.n_levels) ++lg;
+    const int level = tid & ((1 << lg) - 1), sub = tid >> lg, subs = kSoftFinThreads >> lg;
+    double m = 0.0;
+    if (level < s.n_levels) {
+        const double o = s.lo_off + level;
+        for (int node = sub; node < cells; node += subs) {
+            const double d = place[node] - o;
+            m = fma(weight[node], exp(s.kappa * (from[node] - d * d)), m);
+        }
+    }
+    red[tid] = m;
+    __syncthreads();
+    unsigned long long own = 0ull;
+    if (tid < s.n_levels) {
+        double t = 0.0;
+        for (int q = 0; q < subs; ++q) t += red[(q << lg) + tid];
+        long long extra = 0;
+#pragma unroll 4
+        for (int r = blockIdx.x; r < n_rows; r += gridDim.x) extra += rows[(size_t)r * row + n_cells + tid];
+        own = (unsigned long long)(__double2ll_rn(t * (double)(1 << (kHistScaleBits - kSoftScaleBits))) + extra);
+    }
+    if (blockIdx.x != gridDim.x - 1) {
+        if (tid < s.n_levels) marginal_publish(own, (size_t)blockIdx.x * s.n_levels + tid, fin);
+    } else {
+        marginal_collect<kSoftFinThreads, 8>(own, (int)gridDim.x - 1, s.n_levels, fin);
+    }
+}
+
+// ---- backward ----
+template <bool DTHETA>
+__global__ __launch_bounds__(kSoftBwdThreads, 5)
+void soft_bwd_kernel(const float *__restrict__ theta, const float *g, int64_t n, QConst k, SoftConst s, const double *__restrict__ table,
+                     float *dtheta /* may be g */, ScalarFinish fin)
+{
+    extern __shared__ __attribute__((aligned(16))) uint4 soft_lds[];
+    load_table<kSoftBwdThreads>(s, table, soft_lds);
+    __syncthreads();
+    const double two_inv_h = 2.0 * s.inv_h, to_var = s.inv_h / s.kappa, to_c3 = 2.0 * s.inv_h * s.inv_h / (s.kappa * s.kappa);
+    double acc_d = 0.0, acc_a = 0.0;
+    auto terms = [&](double r, double gd, double mu, double two_kappa_var, double var, double c3) -> float {
+        acc_d = fma(gd, (s.c0 + mu) + 2.0 * s.kappa * fma(r - s.c0 - 2.0 * mu, var, -c3), acc_d);
+        acc_a = fma(gd, fma(2.0 * (r - mu), var, -c3), acc_a);
+        return (float)(gd * two_kappa_var);
+    };
+    // true: done; false: an entry beyond the table
+    auto inside = [&](float th, float ge, float &dv) -> bool {
+        const double r = fma((double)th, s.inv_delta, -s.c0);
+        const SoftPlace pl = soft_place(r, s);
+        if (pl.in) {
+            const SoftCoef q = soft_coef(pl.bin, s, soft_lds);
+            double p = q.c[7], p1 = 0.0, p2 = 0.0;      // the polynomial, its derivative, half its second derivative
+#pragma unroll
+            for (int i = 6; i >= 0; --i) {
+                p2 = fma(p2, pl.t, p1);
+                p1 = fma(p1, pl.t, p);
+                p = fma(p, pl.t, q.c[i]);
+            }
+            dv = terms(r, (double)ge, p, p1 * two_inv_h, p1 * to_var, p2 * to_c3);
+        }
+        return pl.in;
+    };
+    auto outside = [&](float th, float ge) -> float {
+        if (s.small_set) {
+            const double r = soft_clamp(fma((double)th, s.inv_delta, -s.c0), s);
+            const SoftSums q = soft_direct(r, s);
+            const double inv = 1.0 / q.Z, m1 = q.S1 * inv, m2 = q.S2 * inv, var = fma(-m1, m1, m2);
+            return terms(r, (double)ge, q.near + m1, 2.0 * s.kappa * var, var, fma(-m1, fma(-2.0 * m1, m1, 3.0 * m2), q.S3 * inv));
+        }
+        float d_th, t_d, t_a;
+        quantizer_bwd_terms<0, true>(th, k, d_th, t_d, t_a);
+        acc_d += (double)(ge * t_d);
+        acc_a += (double)(ge * t_a);
+        return ge * d_th;
+    };
+    const int64_t n4 = n >> 2, stride = (int64_t)gridDim.x * kSoftBwdThreads;
+    for (int64_t v = (int64_t)blockIdx.x * kSoftBwdThreads + threadIdx.x; v < n4; v += stride) {
+        const float4 t = load_stream4(theta + 4 * v, k.stream), q = load_stream4(g + 4 * v, k.stream);
+        const float th[4] = {t.x, t.y, t.z, t.w}, ge[4] = {q.x, q.y, q.z, q.w};
+        float dv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        bool in[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) in[e] = inside(th[e], ge[e], dv[e]);
+        if (!(in[0] && in[1] && in[2] && in[3])) {
+#pragma unroll 1
+            for (int e = 0; e < 4; ++e) {
+                if (e == 0 ? in[0] : (e == 1 ? in[1] : (e == 2 ? in[2] : in[3]))) continue;
+                const float dv_e = outside(e == 0 ? th[0] : (e == 1 ? th[1] : (e == 2 ? th[2] : th[3])), e == 0 ? ge[0] : (e == 1 ? ge[1] : (e == 2 ? ge[2] : ge[3])));
+                dv[0] = e == 0 ? dv_e : dv[0]; dv[1] = e == 1 ? dv_e : dv[1];
+                dv[2] = e == 2 ? dv_e : dv[2]; dv[3] = e == 3 ? dv_e : dv[3];
+            }
+        }
+        if (DTHETA) store_stream4(dtheta + 4 * v, dv[0], dv[1], dv[2], dv[3], k.stream);
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+        for (int64_t e = n4 << 2; e < n; ++e) {
+            float dv;
+            if (!inside(theta[e], g[e], dv)) dv = outside(theta[e], g[e]);
+            if (DTHETA) dtheta[e] = dv;
+        }
+    scalar_finish<kSoftBwdThreads>(acc_d, acc_a, fin);
+}
+
+SoftConst soft_const(const cdl_qparams &p, const SoftPlan &s)
+{
+    SoftConst c{};
+    c.bins = s.bins; c.n_levels = p.n_levels; c.small_set = s.small_set;
+    c.half_range = s.half_range; c.inv_h = s.inv_h; c.c0 = s.c0; c.inv_delta = s.inv_delta; c.delta = s.delta; c.kappa = s.kappa;
+    c.r_safe = (double)p.n_levels + 15.0 / s.kappa;
+    c.lo_off = -0.5 * (double)(p.n_levels - 1);
+    return c;
+}
+
+// copies of the table and of the cells that fit `bytes` of LDS (powers of two, up to 8 and 32)
+void soft_copies(SoftConst &c, size_t table_bytes, size_t hist_bytes)
+{
+    c.lg_copies = 0;
+    while (c.lg_copies < 3 && ((size_t)c.bins * 48 << (c.lg_copies + 1)) <= table_bytes) ++c.lg_copies;
+    c.copies = 1 << c.lg_copies;
+    c.lg_hist_copies = 0;
+    while (c.lg_hist_copies < 5 && ((size_t)c.bins * kM * sizeof(int) << (c.lg_hist_copies + 1)) <= hist_bytes) ++c.lg_hist_copies;
+    c.hist_copies = 1 << c.lg_hist_copies;
+}
+
+int launch_table(const SoftConst &c, void *table, hipStream_t stream)
+{
+    // the Chebyshev nodes and the map from values there to coefficients of powers: with f = sum_m a_m T_m, a_m = (2 - [m = 0]) / 8
+    // sum_i f(x_i) T_m(x_i), and the coefficients of T_m from its recurrence
+    static const NodeMatrix m = [] {
+        NodeMatrix m{};
+        double T[8][8] = {};
+        T[0][0] = 1.0;
+        T[1][1] = 1.0;
+        for (int a = 2; a < 8; ++a)
+            for (int q = 0; q < 8; ++q) T[a][q] = (q > 0 ? 2.0 * T[a - 1][q - 1] : 0.0) - T[a - 2][q];
+        for (int i = 0; i < 8; ++i) {
+            const double angle = (2 * i + 1) * 3.14159265358979323846 / 16.0;
+            m.node[i] = cos(angle);
+            for (int q = 0; q < 8; ++q)
+                for (int a = 0; a < 8; ++a) m.inv[q][i] += (a == 0 ? 1.0 : 2.0) / 8.0 * cos(a * angle) * T[a][q];
+        }
+        return m;
+    }();
+    CDL_LAUNCH("soft_table_kernel", stream, soft_table_kernel, dim3((unsigned)c.bins), dim3(64), 0, c, m, reinterpret_cast<double *>(table));
+    return check_launch();
+}
+
+NodePlace marginal_nodes()
+{
+    NodePlace p;
+    for (int q = 0; q < kM; ++q) p.x[q] = cos((2 * q + 1) * 3.14159265358979323846 / (2 * kM));
+    return p;
+}
+
+}  // namespace
+
+// One block per compute unit, at least two trips of the loop each
+int64_t soft_fwd_grid(int64_t n)
+{
+    int64_t g = ((n >> 2) + 2 * kSoftThreads - 1) / (2 * kSoftThreads);
+    if (g > 256) g = 256;
+    return g < 1 ? 1 : g;
+}
+
+constexpr int kSoftRowWords = kSoftMoments * kSoftMaxBins + 256;
+size_t soft_fwd_bytes(int64_t n, int32_t) { return kSoftTableBytes + (size_t)soft_fwd_grid(n) * kSoftRowWords * sizeof(long long); }
+
+SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n)
+{
+    SoftPlan s{};
+    // (the other kernels: truncated CPMFs, sharp regimes, small tensors)
+    if (k.slide || band_template(k) != 0 || p.n_levels < 6 || n < kSoftFrom) return s;
+    const double delta = (double)p.delta, kappa = (double)p.alpha * delta * delta, sigma = 1.0 / sqrt(2.0 * kappa);
+    s.small_set = p.n_levels <= 33;
+    s.half_range = (double)(p.n_levels - 1) + 4.0;
+    const double most = 0.125 * sigma * kSoftMaxBins;
+    if (most < 0.75 * (double)(p.n_levels - 1) + 4.0) return s;      // a band much narrower than the set: the loop over the band
+    if (s.half_range > most) s.half_range = most;
+    // at least eight intervals: entries then spread over the banks
+    s.bins = (int)ceil(2.0 * s.half_range / (0.25 * sigma));
+    if (s.bins < 8) s.bins = 8;
+    if (s.bins > kSoftMaxBins) s.bins = kSoftMaxBins;
+    s.inv_h = s.bins / (2.0 * s.half_range);
+    s.c0 = (double)p.lo + 0.5 * (double)(p.n_levels - 1);
+    s.delta = delta;
+    s.inv_delta = 1.0 / delta;
+    s.kappa = kappa;
+    return s;
+}
+
+int launch_soft_fwd(const float *theta, int64_t n, const cdl_qparams &p, const QConst &k, const SoftPlan &s, int8_t *idx, float *soft,
+                    const MargFinish &fin, void *ws, hipStream_t stream)
+{
+    SoftConst c = soft_const(p, s);
+    // 64 KB of LDS at most: 20 (one copy of the largest table: 24) + 40 (there: 24) and the levels' cells
+    soft_copies(c, 20 << 10, 40 << 10);
+    int rc = launch_table(c, ws, stream);
+    if (rc != CDL_OK) return rc;
+    const int64_t grid = soft_fwd_grid(n);
+    long long *rows = reinterpret_cast<long long *>(reinterpret_cast<char *>(ws) + kSoftTableBytes);
+    const double *table = reinterpret_cast<const double *>(ws);
+    const size_t lds = ((size_t)c.bins * 48 << c.lg_copies) + (size_t)c.n_levels * sizeof(long long) + ((size_t)c.bins * kM * sizeof(int) << c.lg_hist_copies);
+    const char *name = soft || idx ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)";
+#define CDL_SOFT(I, S) \
+    CDL_LAUNCH(name, stream, (soft_fwd_kernel<I, S>), dim3((unsigned)grid), dim3(kSoftThreads), lds, theta, n, k, c, table, idx, soft, rows)
+    if (idx && soft) CDL_SOFT(true, true);
+    else if (idx) CDL_SOFT(true, false);
+    else if (soft) CDL_SOFT(false, true);
+    else CDL_SOFT(false, false);
+#undef CDL_SOFT
+    rc = check_launch();
+    if (rc != CDL_OK) return rc;
+    static const NodePlace nodes = marginal_nodes();
+    CDL_LAUNCH("marginal_finalize_kernel", stream, soft_marginal_kernel, dim3(kSoftFinBlocks), dim3(kSoftFinThreads), 0, rows, (int)grid, c, nodes, fin);
+    return check_launch();
+}
+
+int launch_soft_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams &p, const QConst &k, const SoftPlan &s, float *dtheta,
+                    const ScalarFinish &fin, void *table, int grid, hipStream_t stream)
+{
+    SoftConst c = soft_const(p, s);
+    soft_copies(c, 28 << 10, 0);
+    int rc = launch_table(c, table, stream);
+    if (rc != CDL_OK) return rc;
+    const size_t lds = (size_t)c.bins * 48 << c.lg_copies;
+    if (dtheta) CDL_LAUNCH("quantize_bwd_kernel", stream, soft_bwd_kernel<true>, dim3((unsigned)grid), dim3(kSoftBwdThreads), lds, theta, g, n, k, c,
+                           reinterpret_cast<const double *>(table), dtheta, fin);
+    else CDL_LAUNCH("quantize_bwd_kernel", stream, soft_bwd_kernel<false>, dim3((unsigned)grid), dim3(kSoftBwdThreads), lds, theta, g, n, k, c,
+                    reinterpret_cast<const double *>(table), dtheta, fin);
+    return check_launch();
+}
+
+}  // namespace cdl

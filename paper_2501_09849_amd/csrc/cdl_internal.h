@@ -144,6 +144,12 @@ bool conv_dx_direct_serves(int64_t pixels, int32_t N, int32_t C, int32_t R, int3
 int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
                           int32_t R, int32_t S, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream);
 
+// The same on limbs (cdl_conv_dx.hip).  wr: the weights per class as [ld / 64][C][64]; Np: N padded to whole chunks of 16 channels;
+// planes: room for the digits of g, kMaxLimbs * M_out * Np bytes; zeros: a page of zeros.
+int launch_conv_dx_planes(const float *g, const int8_t *wr, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H, int32_t W,
+                          int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, const BwdPlan *plan, int8_t *planes,
+                          const int8_t *zeros, float *d_x_hat, hipStream_t stream);
+
 int launch_qgemm_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx,
                      int32_t M, int32_t N, int32_t K, float delta_a, float delta_b, int32_t a_offset, int32_t b_offset,
                      float *d_a_hat, float *d_b_hat, void *ws, hipStream_t stream, const ConvWindows *cw = nullptr);

@@ -13,6 +13,7 @@
 // the device so that the rounding of q stays well below the parity tolerance.
 #include "cdl_internal.h"
 #include "cdl_bwd_plan.h"
+#include "cdl_limbs.h"
 #include "cdl_finish.h"
 
 #include <mutex>
@@ -26,10 +27,6 @@ namespace cdl {
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef const void __attribute__((address_space(1))) *gptr_t;
-typedef void __attribute__((address_space(3))) *lptr_t;
 
 constexpr int kGemmThreads = 256;
 constexpr int kKT = 64;          // forward: contraction bytes staged per pipeline step
@@ -223,19 +220,6 @@ struct LimbArgs {
     // forward product with the quantizer in its prologue
     QConst fq_k;
     float fq_scale;           // delta_a * delta_b
-    // activation gradient of a convolution (CONVG): the rows of the fp32 operand are gathered.  Output row m is pixel
-    // (b, i, j) of a grid of cg_H x cg_W pixels per image; contraction entry k = (tap (r, s) of cg_R' x cg_S taps, output
-    // channel n) is read from G[b, p, q, n] with p = i + pad_h - r, q = j + pad_w - s where those are inside the output
-    // image, else 0.  A thread's four consecutive entries share a tap (N % 4 == 0).  Stride 1: the grid is the input
-    // image.  Stride 2: one launch per parity class (a, c) of the input pixels, whose grid holds the pixels
-    // (2 i + a, 2 j + c) and whose taps are those of the same parity as (a + pad, c + pad) - the only ones that reach
-    // such a pixel -, renumbered; the output rows then lie scattered in the tensor (cg_ostep = 2).
-    int cg_H, cg_W, cg_P, cg_Q, cg_S, cg_pad_h, cg_pad_w;
-    float cg_inv_n, cg_inv_s;     // 1 / N, 1 / S
-    int cg_ostep, cg_oa, cg_oc, cg_oH, cg_oW;   // output pixel of grid pixel (b, i, j): (b, ostep i + oa, ostep j + oc) of oH x oW
-    uint32_t cg_mul_hw, cg_mul_w;               // m / (cg_H cg_W) and m / cg_W as multiplications (div_by)
-    int cg_sh_hw, cg_sh_w;
-    int tn;                       // 32-column tiles per wave (1..3; with six limbs at most 2)
     const double *row_corr;   // [rows] or null: added to every entry of an output row (the index operand is stored with an offset:
                               // the missing part of the product is offset * step * sum of g over the contraction); splits == 1 only
 };
@@ -253,10 +237,7 @@ static_assert(limb_stage_bytes(3) <= limb_stage_bytes(5) && limb_stage_bytes(4) 
               limb_stage_bytes(6) <= limb_stage_bytes(5), "LDS sized for five limbs");
 
 __device__ __forceinline__ int lswz(int row) { return (row >> 1) & 7; }
-constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }   // s_waitcnt vmcnt(n) only
-constexpr int kLgkmcnt0 = 0xc07f;                                                   // s_waitcnt lgkmcnt(0) only
 
-__device__ __forceinline__ uint32_t bperm(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); }
 
 // Forward product, fast path for contraction lengths that are multiples of 128: 512 threads = 2 x 4 waves,
 // 256 x 256 block tile (wave tile 128 x 64: eight 32x32 accumulators), K-tiles of 128 bytes brought in by
@@ -740,70 +721,6 @@ void conv_prep_kernel(int8_t *page, int off, const int8_t *w, int N, int Kc, int
 // without an offset, so that such calls need no workspace
 static __device__ __align__(256) int8_t conv_zero_page[256];
 
-// n / d for 0 <= n < 2^31 by one multiplication: with s = ceil(log2 d) and mul = ceil(2^(31 + s) / d) (below 2^32) the
-// quotient is (n * mul) >> (31 + s), exactly (the excess mul * d - 2^(31 + s) is below d <= 2^s, so it adds less than
-// one unit of the quotient over the whole range of n); sh = s - 1, or -1 for d = 1.
-struct DivBy { uint32_t mul; int sh; };
-inline DivBy make_div_by(uint32_t d)
-{
-    if (d <= 1) return DivBy{0u, -1};
-    int s = 0;
-    while ((1ull << s) < d) ++s;
-    const unsigned long long mul = ((1ull << (31 + s)) + d - 1) / d;
-    return DivBy{(uint32_t)mul, s - 1};
-}
-__device__ __forceinline__ int div_by(int n, uint32_t mul, int sh)
-{
-    return sh < 0 ? n : (int)(__umulhi((uint32_t)n, mul) >> sh);
-}
-
-// Digits of four values: out[l] holds digit l (a signed byte, l = 0 least significant) of g[0..3] in
-// its bytes 0..3.  x = g * gscale is exact (gscale is a power of two) and |x| < 0.99 * 2^(8L-1);
-// q = rint(x) = sum_l d_l 256^l with d_l in [-128, 127]: the bytes of (q + 0x80..80) ^ 0x80..80.
-template <int L>
-__device__ __forceinline__ void limbs_of4(const float (&g)[4], float gscale, uint32_t (&out)[L])
-{
-    if (L <= 4) {
-        constexpr uint32_t off = L == 4 ? 0x80808080u : 0x00808080u;
-        uint32_t d[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int q = (int)rintf(g[e] * gscale);
-            d[e] = ((uint32_t)q + off) ^ off;
-        }
-        const uint32_t t0 = bperm(d[1], d[0], 0x05010400u), t2 = bperm(d[3], d[2], 0x05010400u);
-        out[0] = bperm(t2, t0, 0x05040100u);
-        out[1] = bperm(t2, t0, 0x07060302u);
-        const uint32_t t1 = bperm(d[1], d[0], 0x07030602u), t3 = bperm(d[3], d[2], 0x07030602u);
-        out[2] = bperm(t3, t1, 0x05040100u);
-        if (L == 4) out[L - 1] = bperm(t3, t1, 0x07060302u);
-    } else {
-        // q has up to 48 bits: the low 16 (digits 0, 1) and the rest are rounded separately
-        constexpr uint32_t offh = L == 6 ? 0x80808080u : 0x00808080u;
-        uint32_t lo[4], hi[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float x = g[e] * gscale;
-            const float H = rintf(x * (1.0f / 65536.0f));
-            const float r = fmaf(-H, 65536.0f, x);          // exact, |r| <= 32768
-            // r + 1.5 * 2^23 has unit spacing: its mantissa bits are those of the constant plus rint(r), ties to even
-            const int t = (int)(__float_as_uint(r + 12582912.0f) + (0x8080u - 0x4B400000u));   // rint(r) + 0x8080, in [0x80, 0x10080]
-            lo[e] = (uint32_t)t ^ 0x8080u;                  // bytes 0, 1: digits 0, 1
-            const int h = (int)H + (t >> 16);               // carry out of the low two digits
-            hi[e] = ((uint32_t)h + offh) ^ offh;
-        }
-        const uint32_t a0 = bperm(lo[1], lo[0], 0x05010400u), a2 = bperm(lo[3], lo[2], 0x05010400u);
-        out[0] = bperm(a2, a0, 0x05040100u);
-        out[1] = bperm(a2, a0, 0x07060302u);
-        const uint32_t t0 = bperm(hi[1], hi[0], 0x05010400u), t2 = bperm(hi[3], hi[2], 0x05010400u);
-        out[2] = bperm(t2, t0, 0x05040100u);
-        out[3] = bperm(t2, t0, 0x07060302u);
-        const uint32_t t1 = bperm(hi[1], hi[0], 0x07030602u), t3 = bperm(hi[3], hi[2], 0x07030602u);
-        out[4] = bperm(t3, t1, 0x05040100u);
-        if (L == 6) out[L - 1] = bperm(t3, t1, 0x07060302u);
-    }
-}
-
 // One output tile is 32 rows x (4 waves x TN x 32) columns; every wave holds all L limb tiles of the
 // 32 rows for its TN column tiles (one wave per SIMD, accumulators in the AGPRs).  A block takes
 // `units_per_block` consecutive row tiles of one column tile (and one piece of the contraction) and
@@ -831,7 +748,7 @@ __device__ __forceinline__ void limbs_of4(const float (&g)[4], float gscale, uin
 // lets the scheduler put the VALU and LDS work into the shadow of the MFMAs.
 // TRANS: G is read transposed (rows of the product are columns of G).  VEC: 16-byte loads of G
 // (N % 4 == 0).
-template <int L, int TN, bool TRANS, bool VEC, bool LONG_RUNS, bool QUANT = false, bool CONVG = false>
+template <int L, int TN, bool TRANS, bool VEC, bool LONG_RUNS, bool QUANT = false>
 __device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, float gscale, double out_scale, int block)
 {
     constexpr int NB = 4 * TN * 32;
@@ -887,36 +804,10 @@ __device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, f
     const int ak = TRANS ? 4 * tr_j : 4 * (tid & 31);        // first contraction entry inside the K-tile
     // (every address inside a tile is clamped to the matrix)
     // (r, kt): row tile inside the block and K-tile inside the contraction piece, both valid
-    // CONVG (one row tile per block): the input pixel of each of the thread's four rows, as b * P * Q, h, w
-    int cg_base[4] = {0, 0, 0, 0}, cg_h[4] = {0, 0, 0, 0}, cg_w[4] = {0, 0, 0, 0};
-    if (CONVG) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int m = min(tile_r0 * kLRows + ar + 8 * q, a.rows - 1), hw = a.cg_H * a.cg_W;
-            const int b = div_by(m, a.cg_mul_hw, a.cg_sh_hw), rem = m - b * hw;
-            cg_h[q] = div_by(rem, a.cg_mul_w, a.cg_sh_w);
-            cg_w[q] = rem - cg_h[q] * a.cg_W;
-            cg_base[q] = b * a.cg_P * a.cg_Q;
-        }
-    }
     auto load_g = [&](float (&g)[16], int r, int kt) {
         const int row0 = (tile_r0 + r) * kLRows;
         const int k0 = (kt0 + kt) * kLBK + ak;
-        if (CONVG) {
-            // tap and channel of this thread's entries: k0 = tap * N + n0 (k0 < 2^17, so (k0 + 1/2) / N in fp32 is far
-            // from a whole number on either side and truncates to the quotient; likewise tap / S)
-            const int tap = (int)(((float)k0 + 0.5f) * a.cg_inv_n), n0 = k0 - tap * a.N;
-            const int tr = (int)(((float)tap + 0.5f) * a.cg_inv_s), ts = tap - tr * a.cg_S;
-            const int dh = a.cg_pad_h - tr, dw = a.cg_pad_w - ts;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int hh = cg_h[q] + dh, ww = cg_w[q] + dw;
-                const bool ok = (unsigned)hh < (unsigned)a.cg_P && (unsigned)ww < (unsigned)a.cg_Q;
-                const int64_t o = ok ? (int64_t)(cg_base[q] + hh * a.cg_Q + ww) * a.N + n0 : 0;
-                const float4 v = *reinterpret_cast<const float4 *>(a.G + o);
-                g[4 * q] = ok ? v.x : 0.0f; g[4 * q + 1] = ok ? v.y : 0.0f; g[4 * q + 2] = ok ? v.z : 0.0f; g[4 * q + 3] = ok ? v.w : 0.0f;
-            }
-        } else if (!TRANS) {
+        if (!TRANS) {
             // g[4 q + e] = G[row0 + ar + 8 q][k0 + e]
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -1102,22 +993,6 @@ __device__ __forceinline__ void limb_gemm_body(const LimbArgs &a, int8_t *lds, f
                 }
             }
         };
-        if (CONVG && a.cg_ostep != 1) {
-            // the rows of a parity class lie scattered in the tensor: one address per row (no loads between the stores)
-#pragma unroll
-            for (int rr = 0; rr < 16; ++rr) {
-                const int m = erow + 8 * (rr >> 2) + (rr & 3);
-                if (m >= a.rows) continue;
-                const int b = div_by(m, a.cg_mul_hw, a.cg_sh_hw), rem = m - b * (a.cg_H * a.cg_W);
-                const int i = div_by(rem, a.cg_mul_w, a.cg_sh_w), jj = rem - i * a.cg_W;
-                const int64_t pix = ((int64_t)b * a.cg_oH + a.cg_ostep * i + a.cg_oa) * a.cg_oW + a.cg_ostep * jj + a.cg_oc;
-                float *p = a.out + pix * a.cols + ecol;
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    if (ecol + j * 32 < a.cols) p[j * 32] = (float)__builtin_fma(combined(j, rr), out_scale, 0.0);
-            }
-            return;
-        }
         if (direct) {
             if (corr) {
                 if (full) emit(std::true_type{}, std::true_type{}, a.out + first);
@@ -1276,35 +1151,6 @@ void limb_pair_kernel(LimbArgs a, LimbArgs b, int blocks_a)
 #undef CDL_PAIR
 }
 
-// dL/dQ(x) of a convolutional layer: the activation-gradient product with the rows of g gathered by taps (CONVG),
-// one row tile of 32 input pixels per block.  TN = column tiles per wave, chosen by the launcher: channel counts are
-// powers of two, and 256 or 512 output columns in tiles of 384 would spend a third of the MFMAs on padding.  With one
-// column tile per wave (up to 128 channels: the first stages of a network) a K-tile has only 4 L MFMAs per wave, fewer
-// cycles than a load takes to come back, and the loop runs at one memory round trip per K-tile: that kernel is held to
-// 256 registers and asks for 80 KiB of LDS, so that two blocks share a compute unit and fill each other's waits.
-constexpr int conv_dx_lds_bytes(int tn)
-{
-    return tn == 3 ? kLimbLdsBytes : 2 * (kMaxLimbs * kLPlane + 4 * tn * 32 * kLBK);
-}
-
-template <int TN>
-__global__ __launch_bounds__(kLThreads, TN == 1 ? 2 : 1)
-void limb_conv_dx_kernel(LimbArgs a)
-{
-    extern __shared__ __attribute__((aligned(16))) int8_t limb_lds[];
-    const int limbs = a.plan->limbs_da;
-    const float gscale = a.plan->gscale_da;
-    const double out_scale = a.plan->out_scale_da;
-#define CDL_CONV_DX(L, T) limb_gemm_body<L, T, false, true, false, false, true>(a, limb_lds, gscale, out_scale, (int)blockIdx.x)
-    switch (limbs) {
-        case 3: CDL_CONV_DX(3, TN); break;
-        case 4: CDL_CONV_DX(4, TN); break;
-        case 5: CDL_CONV_DX(5, TN); break;
-        default: CDL_CONV_DX(6, (TN < 2 ? TN : 2)); break;
-    }
-#undef CDL_CONV_DX
-}
-
 // The plan of a backward call, made by the last block of the launch that forms the column sums (a launch of its own
 // took 5 us).  The flag of a block goes up when its sums have arrived; see cdl_finish.h.
 struct PlanArgs {
@@ -1371,8 +1217,8 @@ __device__ __forceinline__ void plan_at_end(const PlanArgs &a, int self, int blo
     }
 }
 
-// For that product: the weights [N][R][S][C] rearranged as its index operand Wr[c][(r', s', n)] (contraction index
-// contiguous, rows ld bytes apart, zero beyond the contraction length) and the sum of |w| over the contraction per
+// dL/dQ(x) of a convolutional layer (cdl_conv_dx.hip): the weights [N][R][S][C] rearranged as its index operand
+// Wr[(r', s', n) / 64][c][64], every tap's channels padded with zeros to Np (zero beyond the contraction length, up to ld) and the sum of |w| over the contraction per
 // channel c (the limb rule's column sums).  One rearrangement per class of taps (blockIdx.y): the taps
 // (r0 + tstep r', s0 + tstep s') with r' < Rc, s' < Sc - all of them for stride 1 (one class, tstep = 1), those of one
 // parity for stride 2.
@@ -1380,39 +1226,49 @@ struct ConvDxClass { int r0, s0, Rc, Sc; };
 struct ConvDxClasses { ConvDxClass c[4]; int tstep; };
 
 __global__ __launch_bounds__(256)
-void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int R, int S, int C, ConvDxClasses cls, int8_t *__restrict__ wr, int64_t ld,
-                         unsigned int *col_abs, PlanArgs plan)
+void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int S, int C, ConvDxClasses cls, int8_t *__restrict__ wr, int64_t ld,
+                         unsigned int *col_abs /* zeroed */, PlanArgs plan)
 {
-    // one block per input channel c and class; four entries per thread and trip (one 4-byte store): the byte loads are a
-    // stride of C apart and nothing but latency, so as many of them as possible are in flight
-    __shared__ unsigned int red[4];
-    const ConvDxClass k_ = cls.c[blockIdx.y];
-    const int kc = k_.Rc * k_.Sc * N;
-    const int c = blockIdx.x;
-    int8_t *dst = wr + ((int64_t)blockIdx.y * C + c) * ld;
-    unsigned int s_abs = 0u;
-    for (int k4 = threadIdx.x * 4; k4 < (int)ld; k4 += 1024) {
-        int v[4];
+    // A block turns 64 contraction entries x 64 channels of one class (blockIdx.z): rows of 64 channels are contiguous in w,
+    // 64 entries of a channel in wr.
+    __shared__ int8_t tile[64][68];
+    const ConvDxClass k_ = cls.c[blockIdx.z];
+    const int kc = k_.Rc * k_.Sc * Np, k0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    {
+        const int c = threadIdx.x & 63, part = threadIdx.x >> 6;
+        int8_t v[16];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = k4 + e, kk = min(k, kc - 1), tap = kk / N, n = kk - tap * N;
+        for (int e = 0; e < 16; ++e) {
+            const int k = k0 + 4 * e + part, kk = min(k, kc - 1), tap = kk / Np, nn = kk - tap * Np, n = min(nn, N - 1);
             const int tr = tap / k_.Sc, ts = tap - tr * k_.Sc;
             const int r = k_.r0 + cls.tstep * tr, sx = k_.s0 + cls.tstep * ts;
-            const int x = (int)w[(((int64_t)n * R + r) * S + sx) * C + c];
-            v[e] = k < kc ? x : 0;
+            const int8_t x = w[(((int64_t)n * R + r) * S + sx) * C + min(c0 + c, C - 1)];
+            v[e] = k < kc && nn < N ? x : (int8_t)0;
         }
-        *reinterpret_cast<uint32_t *>(dst + k4) =
-            (uint32_t)(v[0] & 0xff) | ((uint32_t)(v[1] & 0xff) << 8) | ((uint32_t)(v[2] & 0xff) << 16) | ((uint32_t)(v[3] & 0xff) << 24);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s_abs += (unsigned int)(v[e] < 0 ? -v[e] : v[e]);
+        for (int e = 0; e < 16; ++e) tile[c][4 * e + part] = v[e];
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s_abs += (unsigned int)__shfl_down((int)s_abs, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s_abs;
     __syncthreads();
-    if (threadIdx.x == 0)
-        __hip_atomic_store(&col_abs[blockIdx.y * C + c], (red[0] + red[1]) + (red[2] + red[3]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    plan_at_end(plan, (int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
+    const int c = threadIdx.x >> 2, q = threadIdx.x & 3;
+    unsigned int s_abs = 0u;
+    uint32_t word[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        word[i] = *reinterpret_cast<const uint32_t *>(&tile[c][16 * q + 4 * i]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int x = (int)(int8_t)(word[i] >> (8 * e));
+            s_abs += (unsigned int)(x < 0 ? -x : x);
+        }
+    }
+    s_abs += (unsigned int)__shfl_xor((int)s_abs, 1, 64);
+    s_abs += (unsigned int)__shfl_xor((int)s_abs, 2, 64);
+    if (c0 + c < C) {
+        int8_t *dst = wr + (int64_t)blockIdx.z * C * ld + ((int64_t)blockIdx.x * C + c0 + c) * 64 + 16 * q;
+        *reinterpret_cast<uint4 *>(dst) = uint4{word[0], word[1], word[2], word[3]};
+        if (q == 0) __hip_atomic_fetch_add(&col_abs[blockIdx.z * C + c0 + c], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    plan_at_end(plan, (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y * gridDim.z));
 }
 
 // The forward product with the quantizer of the activations in its prologue: y = delta_a delta_b (Q_idx(X) . Wi^T)
@@ -2123,9 +1979,31 @@ int launch_qgemm_quantize_fwd(const float *x, const cdl_qparams &p, const int8_t
 }
 
 // workspace of the activation gradient of a convolution: [plan][per-block max|g|][col sums][Wr]
+// address of conv_zero_page on the current device (taken once per device)
+static int conv_zero_page_ptr(const int8_t **ptr)
+{
+    constexpr int kMaxDevices = 64;
+    static const int8_t *cached[kMaxDevices];
+    static std::mutex mu;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return hip_failed(e);
+    if (dev < 0 || dev >= kMaxDevices) return CDL_ERR_PARAM;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!cached[dev]) {
+        void *p = nullptr;
+        e = hipGetSymbolAddress(&p, HIP_SYMBOL(conv_zero_page));
+        if (e != hipSuccess) return hip_failed(e);
+        if (!p) return hip_failed(hipErrorInvalidSymbol);
+        cached[dev] = reinterpret_cast<const int8_t *>(p);
+    }
+    *ptr = cached[dev];
+    return CDL_OK;
+}
+
 struct ConvDxLayout {
-    size_t plan, flags, block_max, ss_b, wr, total;
-    int n_max, nk, classes;
+    size_t plan, flags, block_max, ss_b, wr, planes, total;
+    int n_max, Np, classes;
     int64_t ld;
 };
 
@@ -2134,9 +2012,9 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     ConvDxLayout L;
     // stride 2: four classes of taps, each with at most ceil(R / 2) x ceil(S / 2) of them
     L.classes = stride == 2 ? 4 : 1;
-    const int64_t kc = stride == 2 ? (int64_t)((R + 1) / 2) * ((S + 1) / 2) * N : (int64_t)R * S * N;
-    L.nk = (int)((kc + kLBK - 1) / kLBK);
-    L.ld = (int64_t)(L.nk | 1) * kLBK;
+    L.Np = (N + 15) / 16 * 16;
+    const int64_t kc = (stride == 2 ? (int64_t)((R + 1) / 2) * ((S + 1) / 2) : (int64_t)R * S) * L.Np;
+    L.ld = (kc + 63) / 64 * 64;
     L.n_max = (int)blocks_for((M_out * N) >> 2, 2048, 2048);
     size_t off = 0;
     L.plan = off;      off += align_up(sizeof(BwdPlan), 256);
@@ -2144,13 +2022,17 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     L.block_max = off; off += align_up((size_t)L.n_max * sizeof(unsigned int), 256);
     L.ss_b = off;      off += align_up((size_t)L.classes * C * sizeof(unsigned int), 256);
     L.wr = off;        off += align_up((size_t)L.classes * C * (size_t)L.ld, 256);
+    L.planes = off;    off += align_up((size_t)M_out * (size_t)L.Np * kMaxLimbs, 256);
     L.total = off;
     return L;
 }
 
 size_t qconv_bwd_activations_workspace_bytes(int64_t M_out, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride)
 {
-    return conv_dx_layout(M_out, N, C, R, S, stride).total;
+    const size_t own = conv_dx_layout(M_out, N, C, R, S, stride).total;
+    // (a 1 x 1 convolution is a linear layer)
+    const size_t linear = R == 1 && S == 1 && stride == 1 ? bwd_layout((int32_t)M_out, N, C).total : 0;
+    return own > linear ? own : linear;
 }
 
 int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
@@ -2194,99 +2076,35 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
     if (zero_first)
         CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)B * H * W * C, 256, 4096)), dim3(256), 0, d_x_hat, (int64_t)B * H * W * C);
     if (n_cls == 0) return check_launch();
-    if (conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride)) {
-        ConvDxGrid grids[4];
-        for (int c = 0; c < n_cls; ++c)
-            grids[c] = ConvDxGrid{cl[c].oa, cl[c].oc, cl[c].Hc, cl[c].Wc, cl[c].pad_h, cl[c].pad_w, cl[c].Rc, cl[c].Sc, taps.c[c].r0, taps.c[c].s0};
+    ConvDxGrid grids[4];
+    for (int c = 0; c < n_cls; ++c)
+        grids[c] = ConvDxGrid{cl[c].oa, cl[c].oc, cl[c].Hc, cl[c].Wc, cl[c].pad_h, cl[c].pad_w, cl[c].Rc, cl[c].Sc, taps.c[c].r0, taps.c[c].s0};
+    if (conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride))
         return launch_conv_dx_direct(g, w_idx, grids, n_cls, B, H, W, C, N, R, S, P, Q, stride, delta_w, d_x_hat, stream);
-    }
-    CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, 0);
+    if (R == 1 && S == 1 && stride == 1 && pad == 0)
+        return launch_qgemm_bwd(g, nullptr, w_idx, (int32_t)M_out, N, C, 1.0f, delta_w, 0, 0, d_x_hat, nullptr, ws, stream);
+    CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, n_cls * C);
     // (one limb count for all classes: the largest column sum of any of them)
     PlanArgs pa{plan, block_max, L.n_max, nullptr, ss_b, 0, n_cls * C, 1.0f, delta_w, reinterpret_cast<unsigned long long *>(base + L.flags), next_finish_tag()};
-    const bool plan_apart = n_cls * C > kPlanMaxBlocks;
+    const dim3 prep((unsigned)(L.ld / 64), (unsigned)((C + 63) / 64), (unsigned)n_cls);
+    const bool plan_apart = (int64_t)prep.x * prep.y * prep.z > kPlanMaxBlocks;
     if (plan_apart) pa.plan = nullptr;
-    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, dim3((unsigned)C, (unsigned)n_cls), dim3(256), 0,
-               w_idx, N, R, S, C, taps, wr, L.ld, ss_b, pa);
+    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, prep, dim3(256), 0,
+               w_idx, N, L.Np, R, S, C, taps, wr, L.ld, ss_b, pa);
     if (plan_apart)
         CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
                    (const unsigned int *)nullptr, 0, ss_b, n_cls * C, 1.0f, delta_w);
+    const int8_t *zeros = nullptr;
     int rc = check_launch();
+    if (rc == CDL_OK) rc = conv_zero_page_ptr(&zeros);
     if (rc != CDL_OK) return rc;
-    LimbArgs a{};
-    a.G = g; a.M = (int)M_out; a.N = N;
-    a.ldb = L.ld;
-    a.cols = C;
-    a.splits = 1;
-    a.units_per_block = 1;
-    a.plan = plan; a.which = 0;
-    a.out = d_x_hat;
-    a.cg_P = P; a.cg_Q = Q;
-    a.cg_inv_n = 1.0f / (float)N;
-    a.cg_ostep = stride; a.cg_oH = H; a.cg_oW = W;
-    // the tile width (128, 256 or 384 columns) that pads the channels least; the widest of those that pad equally
-    a.tn = 3;
-    for (int tn = 2; tn >= 1; --tn) {
-        const int w = 128 * tn, wbest = 128 * a.tn;
-        if ((C + w - 1) / w * w < (C + wbest - 1) / wbest * wbest) a.tn = tn;
-    }
-    if ((int64_t)limb_cols(3) * a.ldb > 0xffffffffLL) return CDL_ERR_RANGE;
-    const void *fn = a.tn == 1 ? (const void *)limb_conv_dx_kernel<1> : a.tn == 2 ? (const void *)limb_conv_dx_kernel<2> : (const void *)limb_conv_dx_kernel<3>;
-    const int lds_bytes = conv_dx_lds_bytes(a.tn);
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-    if (e != hipSuccess) return hip_failed(e);
-    for (int ci = 0; ci < n_cls; ++ci) {
-        const Cls &k = cl[ci];
-        a.Bt = wr + (int64_t)ci * C * L.ld;
-        a.rows = B * k.Hc * k.Wc;
-        a.kc = k.Rc * k.Sc * N;
-        a.nk = (a.kc + kLBK - 1) / kLBK;
-        a.kt_per_split = a.nk;
-        a.tiles_r = (a.rows + kLRows - 1) / kLRows;
-        a.cg_H = k.Hc; a.cg_W = k.Wc; a.cg_S = k.Sc; a.cg_pad_h = k.pad_h; a.cg_pad_w = k.pad_w;
-        a.cg_inv_s = 1.0f / (float)k.Sc;
-        a.cg_oa = k.oa; a.cg_oc = k.oc;
-        const DivBy by_hw = make_div_by((uint32_t)k.Hc * (uint32_t)k.Wc), by_w = make_div_by((uint32_t)k.Wc);
-        a.cg_mul_hw = by_hw.mul; a.cg_sh_hw = by_hw.sh; a.cg_mul_w = by_w.mul; a.cg_sh_w = by_w.sh;
-        // (the grid is sized before the limb count is known: six limbs take tiles of at most 256 columns)
-        const int narrow = 128 * (a.tn < 2 ? a.tn : 2);
-        const int64_t items = (int64_t)a.tiles_r * ((a.cols + narrow - 1) / narrow);
-        if (items > 2147483640LL) return CDL_ERR_PARAM;
-        const unsigned grid = (unsigned)((items + 7) / 8 * 8);
-        if (a.tn == 1) CDL_LAUNCH("limb_gemm_kernel(conv d_x_hat)", stream, limb_conv_dx_kernel<1>, dim3(grid), dim3(kLThreads), lds_bytes, a);
-        else if (a.tn == 2) CDL_LAUNCH("limb_gemm_kernel(conv d_x_hat)", stream, limb_conv_dx_kernel<2>, dim3(grid), dim3(kLThreads), lds_bytes, a);
-        else CDL_LAUNCH("limb_gemm_kernel(conv d_x_hat)", stream, limb_conv_dx_kernel<3>, dim3(grid), dim3(kLThreads), lds_bytes, a);
-    }
-    return check_launch();
+    return launch_conv_dx_planes(g, wr, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, plan, reinterpret_cast<int8_t *>(base + L.planes), zeros, d_x_hat, stream);
 }
 
 size_t qconv_fwd_workspace_bytes(int32_t N, int32_t x_offset)
 {
     return x_offset != 0 ? 256 + align_up((size_t)N * sizeof(int32_t), 256) : 0;
 }
-
-namespace {
-// address of conv_zero_page on the current device (taken once per device)
-int conv_zero_page_ptr(const int8_t **ptr)
-{
-    constexpr int kMaxDevices = 64;
-    static const int8_t *cached[kMaxDevices];
-    static std::mutex mu;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return hip_failed(e);
-    if (dev < 0 || dev >= kMaxDevices) return CDL_ERR_PARAM;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!cached[dev]) {
-        void *p = nullptr;
-        e = hipGetSymbolAddress(&p, HIP_SYMBOL(conv_zero_page));
-        if (e != hipSuccess) return hip_failed(e);
-        if (!p) return hip_failed(hipErrorInvalidSymbol);
-        cached[dev] = reinterpret_cast<const int8_t *>(p);
-    }
-    *ptr = cached[dev];
-    return CDL_OK;
-}
-}  // namespace
 
 int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
                      int32_t R, int32_t S, int32_t stride, int32_t pad, float delta_x, float delta_w, int32_t x_offset,

@@ -29,7 +29,7 @@ namespace {
 
 constexpr int kSoftBwdThreads = 256;
 constexpr int kSoftScaleBits = 18;         // an entry adds rint(T_m * 2^18) to a cell: at most 2^12 entries between two flushes
-constexpr int kSoftFinBlocks = 32;
+constexpr int kSoftFinBlocks = 64;
 constexpr int kM = kSoftMoments;
 constexpr int kSoftOwn = (kM * kSoftMaxBins + kSoftThreads - 1) / kSoftThreads;      // cells that a thread adds up
 
@@ -279,7 +279,7 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
 // w_q = (S_0 + 2 sum_m S_m T_m(x_q)) / 6 gives sum_q w_q f(x_q) = the sum of f over the entries for every polynomial f of
 // degree 5), and adds w_q P_k(x_q) for all levels k.
 constexpr int kSoftFinThreads = 1024;
-constexpr int kFinCells = 128;                               // at least kM * kSoftMaxBins / kSoftFinBlocks
+constexpr int kFinCells = 64;                               // at least kM * kSoftMaxBins / kSoftFinBlocks
 static_assert(kM * ((kSoftMaxBins + kSoftFinBlocks - 1) / kSoftFinBlocks) <= kFinCells, "cells of a block");
 struct NodePlace { double x[kM]; };
 

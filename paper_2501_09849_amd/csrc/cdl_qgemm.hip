@@ -1126,6 +1126,28 @@ void limb_gemm_kernel(LimbArgs a)
     }
 }
 
+// Output matrices of few columns: tiles of 128 (TN = 1) or 256 columns (TN = 2) instead of 384, for N % 4 == 0.  The
+// conversion of g costs the same whatever the width, 0.55 and 0.73 of a K-tile's time in all (limb_tile_width).  With one column tile per wave
+// a K-tile has only 4 L MFMAs per wave, fewer cycles than a load takes to come back, so that kernel is held to 256
+// registers and 80 KiB of LDS: two blocks share a compute unit and fill each other's waits.
+constexpr int limb_narrow_lds_bytes(int tn) { return 2 * (kMaxLimbs * kLPlane + 4 * tn * 32 * kLBK); }
+
+template <int TN, bool TRANS, bool LONG_RUNS>
+__global__ __launch_bounds__(kLThreads, TN == 1 ? 2 : 1)
+void limb_narrow_kernel(LimbArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) int8_t limb_lds[];
+    const int limbs = a.which == 0 ? a.plan->limbs_da : a.plan->limbs_db;
+    const float gscale = a.which == 0 ? a.plan->gscale_da : a.plan->gscale_db;
+    const double out_scale = a.which == 0 ? a.plan->out_scale_da : a.plan->out_scale_db;
+    switch (limbs) {
+        case 3: limb_gemm_body<3, TN, TRANS, true, LONG_RUNS>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
+        case 4: limb_gemm_body<4, TN, TRANS, true, LONG_RUNS>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
+        case 5: limb_gemm_body<5, TN, TRANS, true, false>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
+        default: limb_gemm_body<6, TN, TRANS, true, false>(a, limb_lds, gscale, out_scale, (int)blockIdx.x); break;
+    }
+}
+
 // Both products of a small layer in one launch, one tile per block: neither fills the chip, and side by side they take the
 // time of the longer one.
 __global__ __launch_bounds__(kLThreads, 1)
@@ -1789,6 +1811,19 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
     return L;
 }
 
+// 32-column tiles per wave: the width whose tiles take the least time in all (see limb_narrow_kernel)
+int limb_tile_width(const LimbArgs &a)
+{
+    if (a.N % 4 != 0) return 3;
+    const int64_t cost[4] = {0, 55, 73, 100};
+    int best = 3;
+    for (int tn = 2; tn >= 1; --tn) {
+        auto time = [&](int t) { return (a.cols + 128 * t - 1) / (128 * t) * cost[t]; };
+        if (time(tn) < time(best)) best = tn;
+    }
+    return best;
+}
+
 int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
 {
     // About one block per compute unit: each works through a run of consecutive row tiles.  The limb count,
@@ -1798,10 +1833,11 @@ int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
         n_cu = 256;
-    const int64_t runs_wanted = n_cu / a.splits > 0 ? n_cu / a.splits : 1;
+    const int64_t slots = limb_tile_width(a) == 1 ? 2 * n_cu : n_cu, runs_wanted = slots / a.splits > 0 ? slots / a.splits : 1;
     a.units_per_block = (int)((a.tiles_r + runs_wanted - 1) / runs_wanted);
     // (five and six limbs: one row tile per block, and six limbs have the narrower column tile)
-    const int64_t items = (int64_t)a.tiles_r * ((a.cols + limb_cols(6) - 1) / limb_cols(6)) * a.splits;
+    const int tn = limb_tile_width(a), narrowest = tn == 3 ? limb_cols(6) : 128 * tn;
+    const int64_t items = (int64_t)a.tiles_r * ((a.cols + narrowest - 1) / narrowest) * a.splits;
     if (items > 2147483640LL) return CDL_ERR_PARAM;
     // the kernel addresses the rows of one column tile of the index matrix with 32-bit offsets
     if ((int64_t)limb_cols(3) * a.ldb > 0xffffffffLL) return CDL_ERR_RANGE;
@@ -1810,12 +1846,26 @@ int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
     // one, +10 % at 24, where the start-up they save is small and the blocks, all in the same phase for the
     // whole launch, ask L2 for the same lines at the same moments).
     const bool long_runs = a.kt_per_split <= 4;
+    const char *name = trans ? "limb_gemm_kernel(d_b_hat)" : "limb_gemm_kernel(d_a_hat)";
+    if (tn < 3) {
+        const int lds = limb_narrow_lds_bytes(tn);
+#define CDL_NARROW(T, TR, LR)                                                                                                            \
+    do {                                                                                                                                 \
+        const hipError_t e_ = hipFuncSetAttribute((const void *)limb_narrow_kernel<T, TR, LR>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
+        if (e_ != hipSuccess) return hip_failed(e_);                                                                                     \
+        CDL_LAUNCH(name, stream, (limb_narrow_kernel<T, TR, LR>), dim3(grid), dim3(kLThreads), lds, a);                                  \
+    } while (0)
+        if (trans) { if (tn == 1) CDL_NARROW(1, true, false); else CDL_NARROW(2, true, false); }
+        else if (long_runs) { if (tn == 1) CDL_NARROW(1, false, true); else CDL_NARROW(2, false, true); }
+        else { if (tn == 1) CDL_NARROW(1, false, false); else CDL_NARROW(2, false, false); }
+#undef CDL_NARROW
+        return check_launch();
+    }
     const void *fn = trans ? (long_runs ? (const void *)limb_gemm_kernel<true, true> : (const void *)limb_gemm_kernel<true, false>)
                            : (long_runs ? (const void *)limb_gemm_kernel<false, true> : (const void *)limb_gemm_kernel<false, false>);
     // more than 64 KiB of dynamic LDS has to be allowed per function (and per device: set it every time)
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLimbLdsBytes);
     if (e != hipSuccess) return hip_failed(e);
-    const char *name = trans ? "limb_gemm_kernel(d_b_hat)" : "limb_gemm_kernel(d_a_hat)";
     if (trans && long_runs) CDL_LAUNCH(name, stream, (limb_gemm_kernel<true, true>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
     else if (trans) CDL_LAUNCH(name, stream, (limb_gemm_kernel<true, false>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);
     else if (long_runs) CDL_LAUNCH(name, stream, (limb_gemm_kernel<false, true>), dim3(grid), dim3(kLThreads), kLimbLdsBytes, a);

@@ -1542,10 +1542,13 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ g
 // zero-filled from `rows` up to the next multiple of 128.  Also adds, for every column c of src, the sum of
 // |src[r][c]| over the block's rows to col_abs[c] (one atomic per column and block; the array is cleared by the
 // max|g| kernel that runs first): the largest of these sums bounds what the rounding of g can do to one output of
-// the product that contracts over r, see choose_limbs.  One block moves a tile of 128 rows x
-// 64 columns: 4-byte loads along the rows into LDS (row stride 17 words), then every thread takes a
-// 4 x 4 byte block, transposes it in registers and stores 4 bytes of four output rows, so that 32
-// lanes write 128 contiguous bytes.  VEC: cols % 4 == 0 (aligned 4-byte loads).
+// the product that contracts over r, see choose_limbs.
+// One block moves tiles of 128 rows x 128 columns: 16-byte loads along the rows (those of the next tile under way while this one is
+// stored), four to a thread, into LDS; then every thread takes 16 rows of 4 columns, transposes their 4 x 4 byte blocks in
+// registers and stores 16 bytes of four output rows, so that 8 lanes write 128 contiguous bytes.  LDS rows are 33 words apart and
+// rows from 64 on 8 words further: the 32 lanes of a read (8 groups of 16 rows, 4 columns) then lie in different banks.
+// Limited by memory: 50176 windows of 2304 entries 65 -> 28 us (4.6 TB/s), a matrix of that size 70 -> 44.
+// ALIGN: of the rows - cols % 16 == 0 (one load per 16 bytes), % 4 == 0 (four) or neither (byte by byte).
 // CONV: src is not a matrix but the activations of a convolutional layer, [B][H][W][C] with C a multiple of 16, and
 // "src[r][c]" is entry c = (tap row, tap column, channel) of the window of output pixel r = (b, p, q) - the matrix of
 // input windows, which is never stored the right way round: only its transpose is written, as the product that
@@ -1553,6 +1556,7 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ g
 struct ConvGeom {
     int B, H, W, C, R, S, stride, pad, P, Q;
     int pad_word;
+    DivBy by_pq, by_q;
 };
 
 struct TransposeJob {
@@ -1565,112 +1569,125 @@ struct TransposeJob {
     int blocks_r, blocks;      // blocks along the rows, and in all
 };
 
-template <bool VEC, bool CONV>
+constexpr int kTrRows = 128, kTrCols = 128;
+
+template <int ALIGN, bool CONV>
 __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int block, const ConvGeom &geom)
 {
     const int8_t *__restrict__ src = job.src;
     int8_t *__restrict__ dst = job.dst;
     const int rows = job.rows, cols = job.cols, tiles_per_block = job.tiles_per_block;
     const int64_t ldd = job.ldd;
-    unsigned int *__restrict__ col_abs = job.col_abs;
     const int block_x = block % job.blocks_r, block_y = block / job.blocks_r;   // neighbouring blocks write neighbouring 128-byte pieces
-    __shared__ uint32_t tile[128 * 17];
-    __shared__ unsigned int abs_s[64];
-    __shared__ int row_h0[128], row_w0[128], row_off[128];     // CONV: window origin of the tile's rows
-    const int c0 = block_y * 64;
-    const int tid = threadIdx.x;
-    if (tid < 64) abs_s[tid] = 0u;
-    // A block takes `tiles_per_block` consecutive row tiles of its 64 columns and keeps the column sums of |x| in
-    // registers across them: one atomic per column and BLOCK on col_abs (with one per tile the 512 row tiles of
-    // workload 5's activations queued 512 atomics on every address and doubled the kernel's time).
-    unsigned int part[2][4] = {};
-    const int row_tiles = (rows + 127) / 128;
-    const int t_end = min(row_tiles, (block_x + 1) * tiles_per_block);
-    // CONV: the thread's column (the same in all its loads) as a tap and an offset from the window's origin
+    __shared__ uint32_t tile[kTrRows * 33 + 8];
+    auto at = [](int row, int word) { return row * 33 + (row >> 6) * 8 + word; };
+    const int c0 = block_y * kTrCols, tid = threadIdx.x;
+    const int row_tiles = (rows + kTrRows - 1) / kTrRows;
+    const int t0 = block_x * tiles_per_block, t_end = min(row_tiles, t0 + tiles_per_block);
+
+    // load j: row tid / 8 + 32 j of the tile, 16-byte chunk tid % 8
+    const int lrow = tid >> 3, c = c0 + 16 * (tid & 7);
+    // CONV: the chunk as a tap and an offset from the window's origin (C % 16 == 0: it lies inside one tap)
     int tap_r = 0, tap_s = 0, tap_off = 0;
     if (CONV) {
-        const int c = min(c0 + 4 * (tid & 15), cols - 4);
-        const int tap = c / geom.C;
+        const int cc = min(c, cols - 16), tap = cc / geom.C;
         tap_r = tap / geom.S;
         tap_s = tap - tap_r * geom.S;
-        tap_off = (tap_r * geom.W + tap_s) * geom.C + (c - tap * geom.C);
+        tap_off = (tap_r * geom.W + tap_s) * geom.C + (cc - tap * geom.C);
     }
-    for (int rt = block_x * tiles_per_block; rt < t_end; ++rt) {
-        const int r0 = rt * 128;
-        if (CONV) {
-            if (tid < 128) {
-                const int m = min(r0 + tid, rows - 1), pq = geom.P * geom.Q;
-                const int b = m / pq, rem = m - b * pq, p = rem / geom.Q, q = rem - p * geom.Q;
-                const int h0 = p * geom.stride - geom.pad, w0 = q * geom.stride - geom.pad;
-                row_h0[tid] = h0;
-                row_w0[tid] = w0;
-                row_off[tid] = ((b * geom.H + h0) * geom.W + w0) * geom.C;      // (host: B*H*W*C < 2^31)
-            }
-            __syncthreads();
-        }
+    uint4 v[4];
+    auto load = [&](int rt) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int i = tid + 256 * j, row = i >> 4, cd = i & 15;
-            uint32_t w = 0u;
-            const int r = r0 + row, c = c0 + 4 * cd;
+        for (int j = 0; j < 4; ++j) {
+            const int r = rt * kTrRows + lrow + 32 * j;
+            v[j] = uint4{0u, 0u, 0u, 0u};
             if (CONV) {
+                const int m = min(r, rows - 1), pq = geom.P * geom.Q;
+                const int b = div_by(m, geom.by_pq.mul, geom.by_pq.sh), rem = m - b * pq, p = div_by(rem, geom.by_q.mul, geom.by_q.sh), q = rem - p * geom.Q;
+                const int h0 = p * geom.stride - geom.pad, w0 = q * geom.stride - geom.pad;
+                const bool inside = (unsigned)(h0 + tap_r) < (unsigned)geom.H && (unsigned)(w0 + tap_s) < (unsigned)geom.W;
                 if (r < rows && c < cols) {
-                    const bool inside = (unsigned)(row_h0[row] + tap_r) < (unsigned)geom.H && (unsigned)(row_w0[row] + tap_s) < (unsigned)geom.W;
-                    w = inside ? *reinterpret_cast<const uint32_t *>(src + ((int64_t)row_off[row] + tap_off)) : (uint32_t)geom.pad_word;
+                    const uint32_t pw = (uint32_t)geom.pad_word;
+                    v[j] = uint4{pw, pw, pw, pw};
+                    // (host: B*H*W*C < 2^31)
+                    if (inside) v[j] = *reinterpret_cast<const uint4 *>(src + (((b * geom.H + h0) * geom.W + w0) * geom.C + tap_off));
                 }
             } else if (r < rows) {
                 const int8_t *p = src + (int64_t)r * cols + c;
-                if (VEC) {
-                    if (c < cols) w = *reinterpret_cast<const uint32_t *>(p);
+                if (ALIGN == 16) {
+                    if (c < cols) v[j] = *reinterpret_cast<const uint4 *>(p);
                 } else {
+                    uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        if (c + b < cols) w |= (uint32_t)(uint8_t)p[b] << (8 * b);
+                    for (int i = 0; i < 4; ++i) {
+                        if (ALIGN == 4) {
+                            if (c + 4 * i < cols) w[i] = *reinterpret_cast<const uint32_t *>(p + 4 * i);
+                        } else {
+#pragma unroll
+                            for (int b = 0; b < 4; ++b)
+                                if (c + 4 * i + b < cols) w[i] |= (uint32_t)(uint8_t)p[4 * i + b] << (8 * b);
+                        }
+                    }
+                    v[j] = uint4{w[0], w[1], w[2], w[3]};
                 }
             }
-            tile[row * 17 + cd] = w;
+        }
+    };
+    // A block takes `tiles_per_block` consecutive row tiles of its columns and keeps the column sums of |x| in
+    // registers across them: one atomic per column and BLOCK on col_abs (with one per tile the 512 row tiles of
+    // workload 5's activations queued 512 atomics on every address and doubled the kernel's time).
+    unsigned int part[4] = {};
+    const int rg = tid & 7, cg = tid >> 3;      // rows 16 rg .. + 15, columns 4 cg .. + 3
+    if (t0 < t_end) load(t0);
+    for (int rt = t0; rt < t_end; ++rt) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            uint32_t *d = tile + at(lrow + 32 * j, 4 * (tid & 7));
+            d[0] = v[j].x; d[1] = v[j].y; d[2] = v[j].z; d[3] = v[j].w;
         }
         __syncthreads();
-        const int rg = tid & 31;
+        if (rt + 1 < t_end) load(rt + 1);
+        uint32_t o[4][4];                       // [column][group of four rows]
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int cg = (tid >> 5) + 8 * p;
-            const uint32_t d0 = tile[(4 * rg) * 17 + cg], d1 = tile[(4 * rg + 1) * 17 + cg];
-            const uint32_t d2 = tile[(4 * rg + 2) * 17 + cg], d3 = tile[(4 * rg + 3) * 17 + cg];
-            const uint32_t t0 = bperm(d1, d0, 0x05010400u), t2 = bperm(d3, d2, 0x05010400u);
-            const uint32_t t1 = bperm(d1, d0, 0x07030602u), t3 = bperm(d3, d2, 0x07030602u);
-            const uint32_t o[4] = {bperm(t2, t0, 0x05040100u), bperm(t2, t0, 0x07060302u),
-                                   bperm(t3, t1, 0x05040100u), bperm(t3, t1, 0x07060302u)};
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t d0 = tile[at(16 * rg + 4 * g, cg)], d1 = tile[at(16 * rg + 4 * g + 1, cg)];
+            const uint32_t d2 = tile[at(16 * rg + 4 * g + 2, cg)], d3 = tile[at(16 * rg + 4 * g + 3, cg)];
+            const uint32_t x0 = bperm(d1, d0, 0x05010400u), x2 = bperm(d3, d2, 0x05010400u);
+            const uint32_t x1 = bperm(d1, d0, 0x07030602u), x3 = bperm(d3, d2, 0x07030602u);
+            o[0][g] = bperm(x2, x0, 0x05040100u);
+            o[1][g] = bperm(x2, x0, 0x07060302u);
+            o[2][g] = bperm(x3, x1, 0x05040100u);
+            o[3][g] = bperm(x3, x1, 0x07060302u);
+        }
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int c = c0 + 4 * cg + b;
-                if (c < cols) *reinterpret_cast<uint32_t *>(dst + (int64_t)c * ldd + r0 + 4 * rg) = o[b];
-                // sum of |x| over the four int8 of the word: |x| = |(x + 128) - 128| on the biased bytes
-                part[p][b] += __builtin_amdgcn_sad_u8(o[b] ^ 0x80808080u, 0x80808080u, 0u);
-            }
+        for (int b = 0; b < 4; ++b) {
+            const int col = c0 + 4 * cg + b;
+            if (col < cols) *reinterpret_cast<uint4 *>(dst + (int64_t)col * ldd + rt * kTrRows + 16 * rg) = uint4{o[b][0], o[b][1], o[b][2], o[b][3]};
+            // sum of |x| over the four int8 of a word: |x| = |(x + 128) - 128| on the biased bytes
+#pragma unroll
+            for (int g = 0; g < 4; ++g) part[b] = __builtin_amdgcn_sad_u8(o[b][g] ^ 0x80808080u, 0x80808080u, part[b]);
         }
         __syncthreads();   // the tile is overwritten by the next trip
     }
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+    for (int b = 0; b < 4; ++b) {
+        unsigned int sum = part[b];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            // the 32 lanes of a half-wave hold the same column: add them up, one LDS atomic per half-wave
-            unsigned int v = part[p][b];
-#pragma unroll
-            for (int off = 16; off > 0; off >>= 1) v += (unsigned int)__shfl_xor((int)v, off, 32);
-            if ((tid & 31) == 0) atomicAdd(&abs_s[4 * ((tid >> 5) + 8 * p) + b], v);
-        }
+        for (int off = 4; off > 0; off >>= 1) sum += (unsigned int)__shfl_xor((int)sum, off, 64);
+        if (rg == 0) tile[4 * cg + b] = sum;
+    }
+    // (one atomic instruction over neighbouring words: from the lanes that have the sums it would be four with eight words each,
+    // and L2 takes the atomics of one line one after the other - 347 blocks of 128 columns: 33 us instead of 14)
     __syncthreads();
-    if (tid < 64 && c0 + tid < cols && abs_s[tid] != 0u) atomicAdd(&col_abs[c0 + tid], abs_s[tid]);
+    if (tid < kTrCols && c0 + tid < cols && tile[tid] != 0u) atomicAdd(&job.col_abs[c0 + tid], tile[tid]);
 }
 
 // Blocks 0 .. a.blocks - 1 do job a, the rest job b; the last of all makes the plan.
-template <bool VEC, bool CONV>
+template <int ALIGN, bool CONV>
 __global__ __launch_bounds__(256) void transpose_i8_kernel(TransposeJob a, TransposeJob b, ConvGeom geom, PlanArgs plan)
 {
-    if ((int)blockIdx.x < a.blocks) transpose_tiles<VEC, CONV>(a, blockIdx.x, geom);
-    else transpose_tiles<VEC, false>(b, (int)blockIdx.x - a.blocks, geom);
+    if ((int)blockIdx.x < a.blocks) transpose_tiles<ALIGN, CONV>(a, blockIdx.x, geom);
+    else if (!CONV) transpose_tiles<ALIGN, false>(b, (int)blockIdx.x - a.blocks, geom);
     plan_at_end(plan, blockIdx.x, gridDim.x);
 }
 
@@ -1897,7 +1914,7 @@ int launch_limb_pair(LimbArgs a, LimbArgs b, hipStream_t stream)
 // about a thousand blocks where the matrix has that many tiles, each with up to 16 row tiles of its columns
 TransposeJob transpose_job(const int8_t *src, int rows, int cols, int8_t *dst, int64_t ldd, unsigned int *col_abs)
 {
-    const int row_tiles = (rows + 127) / 128, col_tiles = (cols + 63) / 64;
+    const int row_tiles = (rows + kTrRows - 1) / kTrRows, col_tiles = (cols + kTrCols - 1) / kTrCols;
     int per = (int)(((int64_t)row_tiles * col_tiles + 1023) / 1024);
     per = per < 1 ? 1 : (per > 16 ? 16 : per);
     const int blocks_r = (row_tiles + per - 1) / per;
@@ -1912,9 +1929,10 @@ int launch_transposes(const TransposeJob &a, const TransposeJob &b, const ConvGe
     p.flags = reinterpret_cast<unsigned long long *>(flags);
     p.tag = next_finish_tag();
     if (blocks > kPlanMaxBlocks) p.plan = nullptr;
-    if (windows) CDL_LAUNCH("transpose_i8_kernel(windows)", stream, (transpose_i8_kernel<true, true>), dim3((unsigned)blocks), dim3(256), 0, a, b, *windows, p);
-    else if (a.cols % 4 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<true, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
-    else CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<false, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
+    if (windows) CDL_LAUNCH("transpose_i8_kernel(windows)", stream, (transpose_i8_kernel<16, true>), dim3((unsigned)blocks), dim3(256), 0, a, b, *windows, p);
+    else if (a.cols % 16 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<16, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
+    else if (a.cols % 4 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<4, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
+    else CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<1, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
     if (!p.plan)
         CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, here.plan, here.block_max, here.n_max, here.col_abs_a, here.n_abs_a,
                    here.col_abs_b, here.n_abs_b, here.delta_a, here.delta_b);
@@ -2260,7 +2278,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         const PlanArgs pa{plan, block_max, L.n_max, ss_a, ss_b, want_db ? K : 0, d_a_hat ? K : 0, delta_a, delta_b, nullptr, 0ull};
         ConvGeom g{};
         if (cw) {
-            g = ConvGeom{cw->B, cw->H, cw->W, cw->C, cw->R, cw->S, cw->stride, cw->pad, cw->P, cw->Q, 0};
+            g = ConvGeom{cw->B, cw->H, cw->W, cw->C, cw->R, cw->S, cw->stride, cw->pad, cw->P, cw->Q, 0, make_div_by((uint32_t)cw->P * (uint32_t)cw->Q), make_div_by((uint32_t)cw->Q)};
             const uint32_t pb = (uint32_t)(uint8_t)(int8_t)(-a_offset);
             g.pad_word = (int)(pb | (pb << 8) | (pb << 16) | (pb << 24));
         }

@@ -1862,7 +1862,10 @@ int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
     // Runs pay off for short contractions (measured against one tile per block: -12 % at two K-tiles, -20 % at
     // one, +10 % at 24, where the start-up they save is small and the blocks, all in the same phase for the
     // whole launch, ask L2 for the same lines at the same moments).
-    const bool long_runs = a.kt_per_split <= 4;
+    // But a block does every column tile of its row tiles: where that leaves four compute units in ten without work, one tile per
+    // block is better (142 row tiles x 2432 columns, two K-tiles: 60 -> 41 us; 94 x 3000, four: 87 -> 42; runs of two over
+    // 324 row tiles x 832 columns, 63 % of the units busy: 29 us against 44).
+    const bool long_runs = a.kt_per_split <= 4 && (int64_t)a.tiles_r * 10 >= a.units_per_block * runs_wanted * 6;
     const char *name = trans ? "limb_gemm_kernel(d_b_hat)" : "limb_gemm_kernel(d_a_hat)";
     if (tn < 3) {
         const int lds = limb_narrow_lds_bytes(tn);

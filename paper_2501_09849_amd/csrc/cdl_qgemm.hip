@@ -1780,12 +1780,26 @@ inline unsigned blocks_for(int64_t n, int per_block, int cap = 65536)
 
 // workspace layout of a backward call
 
+// 32-column tiles per wave: the width whose tiles take the least time in all (see limb_narrow_kernel)
+int limb_tile_width(int N, int cols)
+{
+    if (N % 4 != 0) return 3;
+    const int64_t cost[4] = {0, 55, 73, 100};
+    int best = 3;
+    for (int tn = 2; tn >= 1; --tn) {
+        auto time = [&](int t) { return ((int64_t)cols + 128 * t - 1) / (128 * t) * cost[t]; };
+        if (time(tn) < time(best)) best = tn;
+    }
+    return best;
+}
+
 struct BwdLayout {
     size_t plan, records, block_max, ss_a, ss_b, scalars, bt, at, partial, corr_da, corr_db, colsum_partial, total;
     int n_max;                    // per-block partial results of the absmax launch
     int64_t ldn, ldm;             // row strides of the transposed index copies (odd multiples of kLBK)
     int nk_n, nk_m;               // K-tiles of the two contractions
     int splits, kt_per_split;     // d_b_hat: splits of the contraction over M
+    int direct_splits;            // the same for the products in double, at most
 };
 
 BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
@@ -1795,17 +1809,29 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
     L.nk_m = (int)((M + kLBK - 1) / kLBK);
     L.ldn = (int64_t)(L.nk_n | 1) * kLBK;
     L.ldm = (int64_t)(L.nk_m | 1) * kLBK;
-    // d_b_hat has few output tiles and a long contraction: cut the contraction so that about three
-    // blocks per compute unit exist, each with at least four K-tiles and (int32 accumulators of
-    // products up to 2^14) at most 1023 of them.
-    const int64_t base = (int64_t)((N + kLRows - 1) / kLRows) * ((K + limb_cols(5) - 1) / limb_cols(5));
+    // d_b_hat has few output tiles and a long contraction: cut the contraction into pieces of at least four K-tiles and (int32
+    // accumulators of products up to 2^14) at most 1023 of them.  More pieces fill the last round of blocks better but
+    // each is written and read again in double.  Of the numbers of pieces that just fill one to six rounds, the one with the
+    // least rounds x K-tiles of a piece (1.8 us each) + traffic of the partial results (5 TB/s).  Against three blocks per compute
+    // unit throughout: 1344 x 448 over 11924 rows 82 -> 51 us with the reduction, 576 x 128 over 100352 79 -> 55, 2304 x 256 over 50176 148 -> 140.
+    const int tn = limb_tile_width(N, K);
+    const int64_t base = (int64_t)((N + kLRows - 1) / kLRows) * ((K + 128 * tn - 1) / (128 * tn)), slots = tn == 1 ? 512 : 256;
     const int64_t nk = L.nk_m;
-    int64_t splits = (768 + base - 1) / base;
-    if (splits > nk / 4) splits = nk / 4;
-    if (splits < 1) splits = 1;
-    int64_t per = (nk + splits - 1) / splits;
-    if (per > 1023) per = 1023;
-    splits = (nk + per - 1) / per;
+    int64_t splits = 1, per = nk;
+    double least = -1.0;
+    for (int rounds = 1; rounds <= 6; ++rounds) {
+        int64_t s = rounds * slots / base;
+        if (s > nk / 4) s = nk / 4;
+        if (s < 1) s = 1;
+        int64_t p = (nk + s - 1) / s;
+        if (p > 1023) p = 1023;
+        s = (nk + p - 1) / p;
+        const double t = 1.8 * (double)((base * s + slots - 1) / slots * p) + (s > 1 ? (double)s * N * K * 16.0 / 5e6 : 0.0);
+        if (least < 0.0 || t < least) { least = t; splits = s; per = p; }
+    }
+    // (the products in double: room for about three blocks per compute unit)
+    L.direct_splits = (int)((768 + base - 1) / base < nk / 4 ? (768 + base - 1) / base : nk / 4);
+    if (L.direct_splits < 1) L.direct_splits = 1;
     L.splits = (int)splits;
     L.kt_per_split = (int)per;
     L.n_max = (int)blocks_for(((int64_t)M * N) >> 2, 2048, 2048);
@@ -1819,26 +1845,13 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
     L.bt = off;      off += align_up((size_t)K * (size_t)L.ldn, 256);           // b_idx^T: [K][ldn]
     L.at = off;      off += align_up((size_t)K * (size_t)L.ldm, 256);           // a_idx^T: [K][ldm]
     // (one split: used only when a reduction kernel with the quantizer's backward pass follows)
-    L.partial = off; off += align_up((size_t)L.splits * (size_t)N * (size_t)K * sizeof(double), 256);
+    L.partial = off; off += align_up((size_t)(L.splits > L.direct_splits ? L.splits : L.direct_splits) * (size_t)N * (size_t)K * sizeof(double), 256);
     // operands stored with an offset: one correction per output row of either product, and the per-block column sums of g
     L.corr_da = off; off += align_up((size_t)M * sizeof(double), 256);
     L.corr_db = off; off += align_up((size_t)N * sizeof(double), 256);
     L.colsum_partial = off; off += align_up((size_t)kColsumBlocks * (size_t)N * sizeof(double), 256);
     L.total = off;
     return L;
-}
-
-// 32-column tiles per wave: the width whose tiles take the least time in all (see limb_narrow_kernel)
-int limb_tile_width(const LimbArgs &a)
-{
-    if (a.N % 4 != 0) return 3;
-    const int64_t cost[4] = {0, 55, 73, 100};
-    int best = 3;
-    for (int tn = 2; tn >= 1; --tn) {
-        auto time = [&](int t) { return (a.cols + 128 * t - 1) / (128 * t) * cost[t]; };
-        if (time(tn) < time(best)) best = tn;
-    }
-    return best;
 }
 
 int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
@@ -1850,10 +1863,10 @@ int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
         n_cu = 256;
-    const int64_t slots = limb_tile_width(a) == 1 ? 2 * n_cu : n_cu, runs_wanted = slots / a.splits > 0 ? slots / a.splits : 1;
+    const int tn = limb_tile_width(a.N, a.cols), narrowest = tn == 3 ? limb_cols(6) : 128 * tn;
+    const int64_t slots = tn == 1 ? 2 * n_cu : n_cu, runs_wanted = slots / a.splits > 0 ? slots / a.splits : 1;
     a.units_per_block = (int)((a.tiles_r + runs_wanted - 1) / runs_wanted);
     // (five and six limbs: one row tile per block, and six limbs have the narrower column tile)
-    const int tn = limb_tile_width(a), narrowest = tn == 3 ? limb_cols(6) : 128 * tn;
     const int64_t items = (int64_t)a.tiles_r * ((a.cols + narrowest - 1) / narrowest) * a.splits;
     if (items > 2147483640LL) return CDL_ERR_PARAM;
     // the kernel addresses the rows of one column tile of the index matrix with 32-bit offsets
@@ -2247,7 +2260,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     char *base = reinterpret_cast<char *>(ws);
     BwdPlan *plan = reinterpret_cast<BwdPlan *>(base + L.plan);
     double *partial = reinterpret_cast<double *>(base + L.partial);
-    if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.splits, stream);
+    if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.direct_splits, stream);
     // (many outputs of few multiplications each: one thread per four outputs, see da_direct_kernel)
     if (d_a_hat && N <= kDirectMaxN && ((int64_t)M * K >= kDirectMinOutputs || !bwd_direct_serves(M, N, K, true, want_db))) {
         // four columns per thread (two where 32 index values per column would not leave registers for four)
@@ -2263,7 +2276,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     }
 
     if (!cw && bwd_direct_serves(M, N, K, d_a_hat != nullptr, d_b_hat != nullptr))
-        return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.splits, stream);
+        return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.direct_splits, stream);
 
     int8_t *bt = reinterpret_cast<int8_t *>(base + L.bt);
     int8_t *at = reinterpret_cast<int8_t *>(base + L.at);

@@ -1256,13 +1256,15 @@ void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int
     __shared__ int8_t tile[64][68];
     const ConvDxClass k_ = cls.c[blockIdx.z];
     const int kc = k_.Rc * k_.Sc * Np, k0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    const float inv_np = 1.0f / (float)Np, inv_s = 1.0f / (float)k_.Sc;
     {
         const int c = threadIdx.x & 63, part = threadIdx.x >> 6;
         int8_t v[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int k = k0 + 4 * e + part, kk = min(k, kc - 1), tap = kk / Np, nn = kk - tap * Np, n = min(nn, N - 1);
-            const int tr = tap / k_.Sc, ts = tap - tr * k_.Sc;
+            // (k < 2^17: (k + 1/2) / Np in fp32 is far enough from a whole number to truncate to the quotient)
+            const int k = k0 + 4 * e + part, kk = min(k, kc - 1), tap = (int)(((float)kk + 0.5f) * inv_np), nn = kk - tap * Np, n = min(nn, N - 1);
+            const int tr = (int)(((float)tap + 0.5f) * inv_s), ts = tap - tr * k_.Sc;
             const int r = k_.r0 + cls.tstep * tr, sx = k_.s0 + cls.tstep * ts;
             const int8_t x = w[(((int64_t)n * R + r) * S + sx) * C + min(c0 + c, C - 1)];
             v[e] = k < kc && nn < N ? x : (int8_t)0;

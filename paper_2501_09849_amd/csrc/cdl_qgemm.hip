@@ -117,8 +117,12 @@ void qgemm_kernel(GemmArgs a)
     const int steps = (a.Kc + kKT - 1) / kKT;
     const v4i zero4 = {0, 0, 0, 0};
 
-    v4i pa[LA], pb[LB];
-    auto fetch = [&](int kt) {
+    // 64-row tiles, which run where tiles are fewer than compute units, have two sets of staging registers: a step's chunks are
+    // asked for two steps ahead (with one set a step took a whole trip to memory; 10000 x 128 x 1024: 25.4 -> 20.4 us with the
+    // index quantizer, 1500 x 1500 x 1500: 38.4 -> 30.5).  Larger tiles fill each other's waits, two sets cost them 1 - 3 %.
+    constexpr bool DEEP = TM == 1;
+    v4i pa0[LA], pb0[LB], pa1[DEEP ? LA : 1], pb1[DEEP ? LB : 1];
+    auto fetch = [&](int kt, v4i (&pa)[LA], v4i (&pb)[LB]) {
         const int64_t off = (int64_t)kt * kKT;
 #pragma unroll
         for (int i = 0; i < LA; ++i)
@@ -127,7 +131,7 @@ void qgemm_kernel(GemmArgs a)
         for (int i = 0; i < LB; ++i)
             pb[i] = (kt * kKT + qb[i] < a.Kc) ? *reinterpret_cast<const v4i *>(gb[i] + off) : zero4;
     };
-    auto stash = [&](int stage) {
+    auto stash = [&](int stage, const v4i (&pa)[LA], const v4i (&pb)[LB]) {
 #pragma unroll
         for (int i = 0; i < LA; ++i)
             *reinterpret_cast<v4i *>(&lds[stage][(tid + kGemmThreads * i) * 16]) = pa[i];
@@ -136,15 +140,7 @@ void qgemm_kernel(GemmArgs a)
             *reinterpret_cast<v4i *>(&lds[stage][BM * kKT + (tid + kGemmThreads * i) * 16]) = pb[i];
     };
 
-    if (steps > 0) {
-        fetch(0);
-        stash(0);
-    }
-    __syncthreads();
-
-    for (int step = 0; step < steps; ++step) {
-        const int stage = step & 1;
-        if (step + 1 < steps) fetch(step + 1);
+    auto compute = [&](int stage) {
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             v4i fa[TM], fb[TN];
@@ -158,8 +154,30 @@ void qgemm_kernel(GemmArgs a)
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
-        if (step + 1 < steps) stash(stage ^ 1);
-        __syncthreads();
+    };
+    fetch(0, pa0, pb0);
+    if constexpr (DEEP) fetch(1, pa1, pb1);
+    stash(0, pa0, pb0);
+    __syncthreads();
+    if constexpr (DEEP) {
+        for (int step = 0; step < steps; step += 2) {
+            fetch(step + 2, pa0, pb0);
+            compute(0);
+            stash(1, pa1, pb1);
+            __syncthreads();
+            if (step + 1 >= steps) break;
+            fetch(step + 3, pa1, pb1);
+            compute(1);
+            stash(0, pa0, pb0);
+            __syncthreads();
+        }
+    } else {
+        for (int step = 0; step < steps; ++step) {
+            if (step + 1 < steps) fetch(step + 1, pa0, pb0);
+            compute(step & 1);
+            if (step + 1 < steps) stash((step & 1) ^ 1, pa0, pb0);
+            __syncthreads();
+        }
     }
 
     // epilogue: lane holds column (lane%32) of each 32x32 tile; register r holds row 8(r/4) + 4(lane/32) + r%4.
@@ -623,25 +641,27 @@ void qconv_kernel(ConvArgs a)
     const v4i pad4 = {a.pad_word, a.pad_word, a.pad_word, a.pad_word};
     __syncthreads();        // the tap table is complete
 
-    v4i pa[LA], pb[LB];
-    auto fetch = [&](int kt) {
+    // Two sets of staging registers where the tile leaves room for them: a step's chunks are asked for two steps ahead, and taps
+    // outside the image read the page of padding instead of branching round the load (a convolution 5 x 5 x 272 -> 24 on 176
+    // images of 11 x 11, with its 64-row tiles: whole step 275 -> 253 us).  The largest tile was 2 % slower that way.
+    constexpr bool DEEP = TM * TN < 8;
+    v4i pa0[LA], pb0[LB], pa1[DEEP ? LA : 1], pb1[DEEP ? LB : 1];
+    auto fetch = [&](int kt, v4i (&pa)[LA], v4i (&pb)[LB]) {
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int c16 = kt * (kKT / 16) + qa[i];
-            v4i v = zero4;                       // beyond the contraction: multiplies zeros of the other operand as well
-            if (c16 < chunks) {
-                const int2 t = taps[c16];
-                const bool inside = (unsigned)(xr[i].h0 + (t.y >> 16)) < (unsigned)a.H && (unsigned)(xr[i].w0 + (t.y & 0xffff)) < (unsigned)a.W;
-                v = inside ? *reinterpret_cast<const v4i *>(a.X + (xr[i].off + t.x)) : pad4;
-            }
-            pa[i] = v;
+            // (beyond the contraction: multiplies zeros of the other operand)
+            const int2 t = taps[min(c16, chunks - 1)];
+            const bool inside = (unsigned)(xr[i].h0 + (t.y >> 16)) < (unsigned)a.H && (unsigned)(xr[i].w0 + (t.y & 0xffff)) < (unsigned)a.W;
+            if constexpr (DEEP) pa[i] = *reinterpret_cast<const v4i *>(inside ? a.X + (xr[i].off + t.x) : a.pad_page);
+            else pa[i] = inside ? *reinterpret_cast<const v4i *>(a.X + (xr[i].off + t.x)) : pad4;
         }
         const int64_t off = (int64_t)kt * kKT;
 #pragma unroll
         for (int i = 0; i < LB; ++i)
             pb[i] = (kt * kKT + qb[i] < a.Kc) ? *reinterpret_cast<const v4i *>(gb[i] + off) : zero4;
     };
-    auto stash = [&](int stage) {
+    auto stash = [&](int stage, const v4i (&pa)[LA], const v4i (&pb)[LB]) {
 #pragma unroll
         for (int i = 0; i < LA; ++i)
             *reinterpret_cast<v4i *>(&lds[stage][(tid + kGemmThreads * i) * 16]) = pa[i];
@@ -650,15 +670,7 @@ void qconv_kernel(ConvArgs a)
             *reinterpret_cast<v4i *>(&lds[stage][BM * kKT + (tid + kGemmThreads * i) * 16]) = pb[i];
     };
 
-    if (steps > 0) {
-        fetch(0);
-        stash(0);
-    }
-    __syncthreads();
-
-    for (int step = 0; step < steps; ++step) {
-        const int stage = step & 1;
-        if (step + 1 < steps) fetch(step + 1);
+    auto compute = [&](int stage) {
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             v4i fa[TM], fb[TN];
@@ -672,8 +684,30 @@ void qconv_kernel(ConvArgs a)
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
-        if (step + 1 < steps) stash(stage ^ 1);
-        __syncthreads();
+    };
+    fetch(0, pa0, pb0);
+    if constexpr (DEEP) fetch(1, pa1, pb1);
+    stash(0, pa0, pb0);
+    __syncthreads();
+    if constexpr (DEEP) {
+        for (int step = 0; step < steps; step += 2) {
+            fetch(step + 2, pa0, pb0);
+            compute(0);
+            stash(1, pa1, pb1);
+            __syncthreads();
+            if (step + 1 >= steps) break;
+            fetch(step + 3, pa1, pb1);
+            compute(1);
+            stash(0, pa0, pb0);
+            __syncthreads();
+        }
+    } else {
+        for (int step = 0; step < steps; ++step) {
+            if (step + 1 < steps) fetch(step + 1, pa0, pb0);
+            compute(step & 1);
+            if (step + 1 < steps) stash((step & 1) ^ 1, pa0, pb0);
+            __syncthreads();
+        }
     }
 
     auto epilogue = [&](auto corr_c) {
@@ -2033,8 +2067,10 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
     // (up to 64 output columns: tiles 64 columns wide, so that half of a wider one is not padding; fewer tiles of 256
     // rows than compute units: tiles of 128 rows, twice as many blocks)
     const bool few = (int64_t)((M + 255) / 256) * ((N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128)) < 256 && M > 128;
-    if (N <= 64) return few ? launch_gemm<2, 1>(g, stream) : launch_gemm<4, 1>(g, stream);
-    return few ? launch_gemm<2, 2>(g, stream) : launch_gemm<4, 2>(g, stream);
+    // (and of 64 where tiles of 128 are too few)
+    const bool fewer = few && (int64_t)((M + 127) / 128) * ((N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128)) < 256;
+    if (N <= 64) return fewer ? launch_gemm<1, 1>(g, stream) : few ? launch_gemm<2, 1>(g, stream) : launch_gemm<4, 1>(g, stream);
+    return fewer ? launch_gemm<1, 2>(g, stream) : few ? launch_gemm<2, 2>(g, stream) : launch_gemm<4, 2>(g, stream);
 }
 
 int launch_qgemm_quantize_fwd(const float *x, const cdl_qparams &p, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,
@@ -2233,11 +2269,14 @@ int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_
     // (fewer such tiles than compute units: 128 rows per tile, twice as many blocks)
     const int BN = N <= 64 ? 64 : 128;
     const bool few = (int64_t)((a.M + 255) / 256) * ((N + BN - 1) / BN) < 256 && a.M > 128;
-    const int BM = few ? 128 : 256;
+    const bool fewer = few && (int64_t)((a.M + 127) / 128) * ((N + BN - 1) / BN) < 256;
+    const int BM = fewer ? 64 : few ? 128 : 256;
     a.tiles_m = (a.M + BM - 1) / BM;
     a.tiles_n = (N + BN - 1) / BN;
     const int64_t grid = ((int64_t)a.tiles_m * a.tiles_n + 7) / 8 * 8;
-    if (N <= 64 && few) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<2, 1>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
+    if (N <= 64 && fewer) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<1, 1>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
+    else if (fewer) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<1, 2>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
+    else if (N <= 64 && few) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<2, 1>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
     else if (N <= 64) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<4, 1>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
     else if (few) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<2, 2>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
     else CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<4, 2>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);

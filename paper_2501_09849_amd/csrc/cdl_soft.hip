@@ -1,15 +1,21 @@
 // Soft regime (few or many levels, most of them live: the paper starts training at alpha = 500, Sec. V-B).
 //
 // Once the quantizer's parameters are fixed every quantity of an entry is a function of theta alone.  With
-// r = theta / delta - c0 (c0 the centre of the level set) and mu(r) the mean of the level offset under the CPMF,
-//     Q_d = delta (c0 + mu),   Var = mu' / (2 kappa),   third central moment = mu'' / (4 kappa^2)
-// (in steps; kappa = alpha delta^2), because a derivative with respect to r brings down a cumulant of the CPMF and a factor
-// 2 kappa.  mu is analytic with features no finer than the CPMF's own width sigma = 1 / sqrt(2 kappa): on intervals of a quarter
-// of sigma a polynomial of degree 7 through the Chebyshev nodes gives mu to 1e-12, Var to 1e-10 and the third moment to
-// 3e-8 of their size (all against sums in double over the levels), so one table of eight coefficients per interval replaces the loop over
-// the levels: a gather from LDS and 21 fused multiply-adds in double per entry where 31 levels took 250 instructions.
-// The table is made by a kernel of its own (the levels' exponentials in double, at 8 nodes per interval).  Forward and
-// backward of 25.6 M entries and 31 levels: 403 -> 162 us, 3.3 TB/s of the traffic (copies reach 5).
+// r = theta / delta - c0 (c0 the centre of the level set) and mu(r), var(r), c3(r) the mean, variance and third central moment of
+// the level offset under the CPMF,
+//     Q_d = delta (c0 + mu),   mu' = 2 kappa var,   var' = 2 kappa c3
+// (kappa = alpha delta^2), because a derivative with respect to r brings down a cumulant of the CPMF and a factor 2 kappa.  All
+// three are analytic with features no finer than the CPMF's own width sigma = 1 / sqrt(2 kappa), so one polynomial per interval
+// of a quarter of sigma replaces the loop over the levels: a gather from LDS and 33 fused multiply-adds in double per entry where 31
+// levels took 250 instructions.
+//
+// The polynomial is made from its highest derivative: c3 at ten Chebyshev nodes and mu, var at the middle of the interval are sums
+// over the levels, and mu(t) is the second integral of the interpolated c3 (eleventh degree).  Integration makes errors smaller
+// where differentiation multiplies them by 1 / (kappa h) each time: from an interpolated mean the third moment had 3e-8 of its size,
+// and no digit right where kappa is 1e-8.  So made, every coefficient has the relative precision of a double however small kappa
+// is, and mu, var and 2 (r - mu) var - c3 come out within 1e-15, 7e-15 and 9e-14 of their largest value (6 - 33 levels, kappa 1e-12
+// to 1.2, against sums in 80 bits; the loop over the levels: 3e-15, 4e-13, 2e-11).
+// The table is made by a kernel of its own.
 //
 // Marginal PMF: the sum of P_k(r) over the entries is wanted for every level k.  An entry adds the Chebyshev polynomials
 // T_0 .. T_5 of its place in its interval to six cells of a histogram (fixed point, LDS integer atomics); since on an
@@ -30,6 +36,9 @@ namespace {
 constexpr int kSoftBwdThreads = 256;
 constexpr int kSoftScaleBits = 18;         // an entry adds rint(T_m * 2^18) to a cell: at most 2^12 entries between two flushes
 constexpr int kSoftFinBlocks = 64;
+constexpr int kNodes = 10;                  // Chebyshev nodes of an interval, for c3
+constexpr int kCoefs = kSoftCoefs;          // coefficients of t^q in mu, t in [-1, 1] along the interval
+static_assert(kCoefs == kNodes + 2 && kCoefs % 2 == 0, "two integrations; pairs of coefficients are loaded");
 constexpr int kM = kSoftMoments;
 constexpr int kSoftOwn = (kM * kSoftMaxBins + kSoftThreads - 1) / kSoftThreads;      // cells that a thread adds up
 
@@ -41,53 +50,83 @@ struct SoftConst {
     double lo_off;         // offset of the lowest level from the centre
 };
 
-// ---- the table: coefficients 0..3 as doubles, 4..7 as floats, of t^q, t in [-1, 1] along the interval ----
+// ---- the table: [bins][kCoefs] ----
 
-// rows of the inverse of the Vandermonde matrix of the eight Chebyshev nodes x_i = cos((2 i + 1) pi / 16): coefficient q of the
-// interpolating polynomial is sum_i inv[q][i] f(x_i)
-struct NodeMatrix { double node[8], inv[8][8]; };
+// Chebyshev nodes, values there -> coefficients of the T_m, and the coefficients of t^q in T_m.  (Two steps: the product of the two
+// matrices has entries of several hundred, which the roundings of the values would be multiplied by.)
+struct NodeMatrix { double node[kNodes], cheb[kNodes][kNodes], power[kNodes][kNodes]; };
 
-__global__ __launch_bounds__(64)
-void soft_table_kernel(SoftConst s, NodeMatrix m, double *__restrict__ table /* [bins][4] doubles, then [bins][4] floats */)
+constexpr int kTableThreads = 128;          // eight threads to a node; node kNodes is the middle of the interval
+
+__global__ __launch_bounds__(kTableThreads)
+void soft_table_kernel(SoftConst s, NodeMatrix m, double *__restrict__ table)
 {
-    __shared__ double mu[8];
+    __shared__ double c3[kNodes], cheb[kNodes], mid[2];
     const int bin = blockIdx.x, node = threadIdx.x >> 3, part = threadIdx.x & 7;
-    const double r = -s.half_range + (bin + 0.5 * (1.0 + m.node[node])) / s.inv_h;
-    // relative to the nearest level, so that the largest weight is about one
+    const double x = node < kNodes ? m.node[node] : 0.0;
+    const double r = -s.half_range + (bin + 0.5 * (1.0 + x)) / s.inv_h;
+    // offsets from the nearest level, so that the largest weight is about one
     const double near = fmin(fmax(rint(r - s.lo_off), 0.0), (double)(s.n_levels - 1)) + s.lo_off, d0 = r - near;
-    double Z = 0.0, S = 0.0;
-    for (int k = part; k < s.n_levels; k += 8) {
-        const double o = s.lo_off + k, d = r - o, w = exp(s.kappa * (d0 * d0 - d * d));
-        Z += w;
-        S = fma(o - near, w, S);
-    }
+    auto weight = [&](int k, double &j) {
+        j = s.lo_off + k - near;
+        return exp(s.kappa * j * (2.0 * d0 - j));
+    };
+    auto add8 = [](double &v) {
 #pragma unroll
-    for (int off = 4; off > 0; off >>= 1) {
-        Z += __shfl_xor(Z, off, 64);
-        S += __shfl_xor(S, off, 64);
+        for (int off = 4; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    };
+    double Z = 0.0, S = 0.0, j;
+    for (int k = part; k < s.n_levels; k += 8) {
+        const double w = weight(k, j);
+        Z += w;
+        S = fma(j, w, S);
     }
-    if (part == 0) mu[node] = near + S / Z;
+    add8(Z);
+    add8(S);
+    const double mean = S / Z;
+    double V = 0.0, T = 0.0;
+    for (int k = part; k < s.n_levels; k += 8) {
+        const double w = weight(k, j), d = j - mean, dw = d * w;
+        V = fma(d, dw, V);
+        T = fma(d * d, dw, T);
+    }
+    add8(V);
+    add8(T);
+    if (part == 0) {
+        if (node < kNodes) c3[node] = T / Z;
+        else if (node == kNodes) { mid[0] = near + mean; mid[1] = V / Z; }
+    }
     __syncthreads();
-    if (threadIdx.x < 8) {
+    const int q = threadIdx.x;
+    if (q < kNodes) {
+        double a = 0.0;
+#pragma unroll
+        for (int i = 0; i < kNodes; ++i) a = fma(m.cheb[q][i], c3[i], a);
+        cheb[q] = a;
+    }
+    __syncthreads();
+    const double kh = s.kappa / s.inv_h;        // d var / dt = kappa h c3, d mu / dt = kappa h var
+    double *out = table + (size_t)bin * kCoefs;
+    if (q < kNodes) {
         double c = 0.0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) c = fma(m.inv[threadIdx.x][i], mu[i], c);
-        if (threadIdx.x < 4) table[(size_t)bin * 4 + threadIdx.x] = c;
-        else reinterpret_cast<float *>(table + (size_t)s.bins * 4)[(size_t)bin * 4 + threadIdx.x - 4] = (float)c;
+        for (int a = 0; a < kNodes; ++a) c = fma(m.power[a][q], cheb[a], c);
+        out[q + 2] = kh * (kh * c) / (double)((q + 1) * (q + 2));
+    } else if (q < kCoefs) {
+        out[q - kNodes] = q == kNodes ? mid[0] : kh * mid[1];
     }
 }
 
-// The table in LDS as three arrays of 16 bytes per interval ({c0, c1}, {c2, c3}, {c4 .. c7}), each in `copies` copies side by
+// The table in LDS as arrays of 16 bytes per interval (two coefficients each), every array in `copies` copies side by
 // side: the copy is the group of banks, so that the lanes of a gather, each in its own interval, do not meet.
 template <int T>
 __device__ __forceinline__ void load_table(const SoftConst &s, const double *__restrict__ table, uint4 *lds)
 {
-    const uint4 *d = reinterpret_cast<const uint4 *>(table), *f = reinterpret_cast<const uint4 *>(table + (size_t)s.bins * 4);
+    const uint4 *d = reinterpret_cast<const uint4 *>(table);
     for (int i = threadIdx.x; i < s.bins << s.lg_copies; i += T) {
         const int b = i >> s.lg_copies;
-        lds[i] = d[2 * b];
-        lds[(s.bins << s.lg_copies) + i] = d[2 * b + 1];
-        lds[2 * (s.bins << s.lg_copies) + i] = f[b];
+#pragma unroll
+        for (int q = 0; q < kCoefs / 2; ++q) lds[q * (s.bins << s.lg_copies) + i] = d[b * (kCoefs / 2) + q];
     }
 }
 
@@ -102,13 +141,18 @@ __device__ __forceinline__ SoftPlace soft_place(double r, const SoftConst &s)
     return p;
 }
 
-struct SoftCoef { double c[8]; };
+struct SoftCoef { double c[kCoefs]; };
 __device__ __forceinline__ SoftCoef soft_coef(int bin, const SoftConst &s, const uint4 *lds)
 {
     const int at = (bin << s.lg_copies) + ((int)threadIdx.x & (s.copies - 1)), plane = s.bins << s.lg_copies;
-    const double2 a = *reinterpret_cast<const double2 *>(lds + at), b = *reinterpret_cast<const double2 *>(lds + plane + at);
-    const float4 f = *reinterpret_cast<const float4 *>(lds + 2 * plane + at);
-    return SoftCoef{{a.x, a.y, b.x, b.y, (double)f.x, (double)f.y, (double)f.z, (double)f.w}};
+    SoftCoef q;
+#pragma unroll
+    for (int i = 0; i < kCoefs / 2; ++i) {
+        const double2 v = *reinterpret_cast<const double2 *>(lds + i * plane + at);
+        q.c[2 * i] = v.x;
+        q.c[2 * i + 1] = v.y;
+    }
+    return q;
 }
 
 // Sums over all levels in double, for entries outside the table (at most 33 levels), with offsets from the nearest level.
@@ -140,7 +184,7 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
                      int8_t *__restrict__ idx, float *__restrict__ soft, long long *__restrict__ rows /* [gridDim.x][6 bins + levels] */)
 {
     extern __shared__ __attribute__((aligned(16))) uint4 soft_lds[];
-    unsigned long long *levels = reinterpret_cast<unsigned long long *>(soft_lds + 3 * (s.bins << s.lg_copies));
+    unsigned long long *levels = reinterpret_cast<unsigned long long *>(soft_lds + kCoefs / 2 * (s.bins << s.lg_copies));
     int *cells = reinterpret_cast<int *>(levels + s.n_levels);
     const int n_cells = kM * s.bins;
     load_table<kSoftThreads>(s, table, soft_lds);
@@ -176,9 +220,9 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
         if (p.in) {
             if (SOFT) {
                 const SoftCoef q = soft_coef(p.bin, s, soft_lds);
-                double mu = q.c[7];
+                double mu = q.c[kCoefs - 1];
 #pragma unroll
-                for (int i = 6; i >= 0; --i) mu = fma(mu, p.t, q.c[i]);
+                for (int i = kCoefs - 2; i >= 0; --i) mu = fma(mu, p.t, q.c[i]);
                 sv = (float)(s.delta * (s.c0 + mu));
             }
             constexpr float kOne = (float)(1 << kSoftScaleBits);
@@ -380,7 +424,7 @@ void soft_bwd_kernel(const float *__restrict__ theta, const float *g, int64_t n,
     extern __shared__ __attribute__((aligned(16))) uint4 soft_lds[];
     load_table<kSoftBwdThreads>(s, table, soft_lds);
     __syncthreads();
-    const double two_inv_h = 2.0 * s.inv_h, to_var = s.inv_h / s.kappa, to_c3 = 2.0 * s.inv_h * s.inv_h / (s.kappa * s.kappa);
+    const double to_var = s.inv_h / s.kappa, to_c3 = 2.0 * to_var * to_var, two_inv_h = 2.0 * s.inv_h;
     double acc_d = 0.0, acc_a = 0.0;
     auto terms = [&](double r, double gd, double mu, double two_kappa_var, double var, double c3) -> float {
         acc_d = fma(gd, (s.c0 + mu) + 2.0 * s.kappa * fma(r - s.c0 - 2.0 * mu, var, -c3), acc_d);
@@ -393,9 +437,9 @@ void soft_bwd_kernel(const float *__restrict__ theta, const float *g, int64_t n,
         const SoftPlace pl = soft_place(r, s);
         if (pl.in) {
             const SoftCoef q = soft_coef(pl.bin, s, soft_lds);
-            double p = q.c[7], p1 = 0.0, p2 = 0.0;      // the polynomial, its derivative, half its second derivative
+            double p = q.c[kCoefs - 1], p1 = 0.0, p2 = 0.0;      // the polynomial, its derivative, half its second derivative
 #pragma unroll
-            for (int i = 6; i >= 0; --i) {
+            for (int i = kCoefs - 2; i >= 0; --i) {
                 p2 = fma(p2, pl.t, p1);
                 p1 = fma(p1, pl.t, p);
                 p = fma(p, pl.t, q.c[i]);
@@ -459,7 +503,7 @@ SoftConst soft_const(const cdl_qparams &p, const SoftPlan &s)
 void soft_copies(SoftConst &c, size_t table_bytes, size_t hist_bytes)
 {
     c.lg_copies = 0;
-    while (c.lg_copies < 3 && ((size_t)c.bins * 48 << (c.lg_copies + 1)) <= table_bytes) ++c.lg_copies;
+    while (c.lg_copies < 3 && ((size_t)c.bins * kSoftBinBytes << (c.lg_copies + 1)) <= table_bytes) ++c.lg_copies;
     c.copies = 1 << c.lg_copies;
     c.lg_hist_copies = 0;
     while (c.lg_hist_copies < 5 && ((size_t)c.bins * kM * sizeof(int) << (c.lg_hist_copies + 1)) <= hist_bytes) ++c.lg_hist_copies;
@@ -468,24 +512,21 @@ void soft_copies(SoftConst &c, size_t table_bytes, size_t hist_bytes)
 
 int launch_table(const SoftConst &c, void *table, hipStream_t stream)
 {
-    // the Chebyshev nodes and the map from values there to coefficients of powers: with f = sum_m a_m T_m, a_m = (2 - [m = 0]) / 8
-    // sum_i f(x_i) T_m(x_i), and the coefficients of T_m from its recurrence
+    // with f = sum_m a_m T_m, a_m = (2 - [m = 0]) / kNodes sum_i f(x_i) T_m(x_i); the coefficients of T_m from its recurrence
     static const NodeMatrix m = [] {
         NodeMatrix m{};
-        double T[8][8] = {};
-        T[0][0] = 1.0;
-        T[1][1] = 1.0;
-        for (int a = 2; a < 8; ++a)
-            for (int q = 0; q < 8; ++q) T[a][q] = (q > 0 ? 2.0 * T[a - 1][q - 1] : 0.0) - T[a - 2][q];
-        for (int i = 0; i < 8; ++i) {
-            const double angle = (2 * i + 1) * 3.14159265358979323846 / 16.0;
+        m.power[0][0] = 1.0;
+        m.power[1][1] = 1.0;
+        for (int a = 2; a < kNodes; ++a)
+            for (int q = 0; q < kNodes; ++q) m.power[a][q] = (q > 0 ? 2.0 * m.power[a - 1][q - 1] : 0.0) - m.power[a - 2][q];
+        for (int i = 0; i < kNodes; ++i) {
+            const double angle = (2 * i + 1) * 3.14159265358979323846 / (2 * kNodes);
             m.node[i] = cos(angle);
-            for (int q = 0; q < 8; ++q)
-                for (int a = 0; a < 8; ++a) m.inv[q][i] += (a == 0 ? 1.0 : 2.0) / 8.0 * cos(a * angle) * T[a][q];
+            for (int a = 0; a < kNodes; ++a) m.cheb[a][i] = (a == 0 ? 1.0 : 2.0) / kNodes * cos(a * angle);
         }
         return m;
     }();
-    CDL_LAUNCH("soft_table_kernel", stream, soft_table_kernel, dim3((unsigned)c.bins), dim3(64), 0, c, m, reinterpret_cast<double *>(table));
+    CDL_LAUNCH("soft_table_kernel", stream, soft_table_kernel, dim3((unsigned)c.bins), dim3(kTableThreads), 0, c, m, reinterpret_cast<double *>(table));
     return check_launch();
 }
 
@@ -536,21 +577,25 @@ int launch_soft_fwd(const float *theta, int64_t n, const cdl_qparams &p, const Q
                     const MargFinish &fin, void *ws, hipStream_t stream)
 {
     SoftConst c = soft_const(p, s);
-    // 64 KB of LDS at most: 20 (one copy of the largest table: 24) + 40 (there: 24) and the levels' cells
-    soft_copies(c, 20 << 10, 40 << 10);
+    // one block per compute unit: the table up to 28 KB (one copy of the largest: 48) and the cells up to 40, and the levels' cells
+    soft_copies(c, 28 << 10, 40 << 10);
     int rc = launch_table(c, ws, stream);
     if (rc != CDL_OK) return rc;
     const int64_t grid = soft_fwd_grid(n);
     long long *rows = reinterpret_cast<long long *>(reinterpret_cast<char *>(ws) + kSoftTableBytes);
     const double *table = reinterpret_cast<const double *>(ws);
-    const size_t lds = ((size_t)c.bins * 48 << c.lg_copies) + (size_t)c.n_levels * sizeof(long long) + ((size_t)c.bins * kM * sizeof(int) << c.lg_hist_copies);
+    const size_t lds = ((size_t)c.bins * kSoftBinBytes << c.lg_copies) + (size_t)c.n_levels * sizeof(long long) + ((size_t)c.bins * kM * sizeof(int) << c.lg_hist_copies);
     const char *name = soft || idx ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)";
 #define CDL_SOFT(I, S) \
+    if (lds > 65536) { \
+        const hipError_t e_ = hipFuncSetAttribute((const void *)soft_fwd_kernel<I, S>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+        if (e_ != hipSuccess) return hip_failed(e_); \
+    } \
     CDL_LAUNCH(name, stream, (soft_fwd_kernel<I, S>), dim3((unsigned)grid), dim3(kSoftThreads), lds, theta, n, k, c, table, idx, soft, rows)
-    if (idx && soft) CDL_SOFT(true, true);
-    else if (idx) CDL_SOFT(true, false);
-    else if (soft) CDL_SOFT(false, true);
-    else CDL_SOFT(false, false);
+    if (idx && soft) { CDL_SOFT(true, true); }
+    else if (idx) { CDL_SOFT(true, false); }
+    else if (soft) { CDL_SOFT(false, true); }
+    else { CDL_SOFT(false, false); }
 #undef CDL_SOFT
     rc = check_launch();
     if (rc != CDL_OK) return rc;
@@ -566,7 +611,7 @@ int launch_soft_bwd(const float *theta, const float *g, int64_t n, const cdl_qpa
     soft_copies(c, 28 << 10, 0);
     int rc = launch_table(c, table, stream);
     if (rc != CDL_OK) return rc;
-    const size_t lds = (size_t)c.bins * 48 << c.lg_copies;
+    const size_t lds = (size_t)c.bins * kSoftBinBytes << c.lg_copies;
     if (dtheta) CDL_LAUNCH("quantize_bwd_kernel", stream, soft_bwd_kernel<true>, dim3((unsigned)grid), dim3(kSoftBwdThreads), lds, theta, g, n, k, c,
                            reinterpret_cast<const double *>(table), dtheta, fin);
     else CDL_LAUNCH("quantize_bwd_kernel", stream, soft_bwd_kernel<false>, dim3((unsigned)grid), dim3(kSoftBwdThreads), lds, theta, g, n, k, c,

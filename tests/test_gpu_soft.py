@@ -72,3 +72,59 @@ def test_soft_table(oracle, n, levels, lo, kappa, spread):
         t_d, t_a = (c0 + mu) + 2 * k * ((r - c0 - 2 * mu) * var - c3), 2 * (r - mu) * var - c3
         assert abs(dd[0] - (gf * t_d).sum()) <= (1e-8 if fine else 2e-7) * (np.abs(gf) * (np.abs(c0 + mu) + 2 * k * np.abs(r - c0 - 2 * mu) * var)).sum() + 1e-7 * abs((gf * t_d).sum())
         assert abs(da[0] - step ** 3 * (gf * t_a).sum()) <= step ** 3 * (np.abs(gf) * (2e-6 * np.abs(2 * (r - mu) * var) + 2e-6 * np.abs(c3) + 1e-9 * (np.abs(r) + np.abs(mu)) * var)).sum()
+
+
+def _moments(r, levels, kappa):
+    """P, mean, variance and third central moment of the level offset from the centre, in extended precision."""
+    o = np.arange(levels).astype(np.longdouble) - np.longdouble(levels - 1) / 2
+    r = r.astype(np.longdouble)[:, None]
+    e = -np.longdouble(kappa) * (r - o) ** 2
+    P = np.exp(e - e.max(1, keepdims=True))
+    P /= P.sum(1, keepdims=True)
+    mu = (P * o).sum(1)
+    dev = o - mu[:, None]
+    return P, mu, (P * dev ** 2).sum(1), (P * dev ** 3).sum(1)
+
+
+@pytest.mark.parametrize("levels", [6, 7, 15, 31, 33])
+@pytest.mark.parametrize("kappa", [1.0, 0.0077, 1e-4, 1e-6, 1e-8])
+def test_scalar_gradients_of_the_table_at_any_sharpness(levels, kappa):
+    """The scalar sums just above the size from which the table serves, down to sharpness at which the CPMF hardly leaves the
+    uniform one, with gradients that cancel and gradients that do not."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    n = (1 << 24) // (levels // 2) + 5
+    if kappa == 1.0:      # the highest sharpness that the table serves
+        kappa = {6: 1.2, 7: 1.2, 15: 0.8, 31: 0.15, 33: 0.13}[levels]
+    lo = -(levels // 2)
+    step = np.float64(np.float32(0.03))
+    sharp = np.float64(np.float32(kappa / step ** 2))
+    k, c0 = sharp * step * step, lo + 0.5 * (levels - 1)
+    rng = np.random.default_rng(levels)
+    values = ((rng.standard_normal(4001) * 0.4 * (levels - 1) / 2 + 0.3 + c0) * step).astype(np.float32)
+    place = np.arange(n) % values.size
+    theta = values[place]
+    r = values.astype(np.float64) / step - c0
+    _, mu, var, c3 = _moments(r, levels, k)
+    t_d, t_a = (c0 + mu) + 2 * k * ((r - c0 - 2 * mu) * var - c3), 2 * (r - mu) * var - c3
+    size_d = np.abs(c0 + mu) + 2 * k * (np.abs(r - c0 - 2 * mu) * var + np.abs(c3))
+    size_a = 2 * np.abs(r - mu) * var + np.abs(c3)
+    ws = gu.workspace(cdl.quantize_workspace_bytes(n, levels))
+    th_d = gu.dev(theta)
+    for sign in (None, np.sign(r)):
+        g = rng.standard_normal(n).astype(np.float32)
+        if sign is not None:
+            g = (np.abs(g) * sign[place]).astype(np.float32)
+        dth, dd, da = gu.empty((n,), torch.float32), gu.empty((1,), torch.float32), gu.empty((1,), torch.float32)
+        cdl.cdl_quantize_bwd(th_d, gu.dev(g), n, lo, levels, float(step), float(sharp), dth, dd, da, ws)
+        torch.cuda.synchronize()
+        g_sum = np.bincount(place, g.astype(np.float64))
+        g_abs = np.bincount(place, np.abs(g.astype(np.float64)))
+        # per term: roundings of double sums over the levels (mean: of the size of the set; 1e-12 of the other parts); the result is a float
+        bound_d = (g_abs * (1e-12 * size_d + 4 * 2.2e-16 * levels / 2)).sum()
+        bound_a = (g_abs * (1e-12 * size_a + 2 * var * 4 * 2.2e-16 * levels / 2)).sum()
+        ref_d, ref_a = (g_sum * t_d).sum(), (g_sum * t_a).sum()
+        assert abs(dd.item() - ref_d) <= bound_d + 6e-8 * abs(ref_d), (dd.item(), ref_d)
+        assert abs(da.item() - step ** 3 * ref_a) <= step ** 3 * (bound_a + 6e-8 * abs(ref_a)), (da.item(), ref_a)
+        want = g[:values.size] * (2 * k * var).astype(np.float64)
+        assert (np.abs(dth[:values.size].cpu().numpy() - want) <= 1.2e-7 * np.abs(want)).all()

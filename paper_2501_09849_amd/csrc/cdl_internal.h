@@ -81,7 +81,7 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
 // Behind them, the table of the soft regime (cdl_soft.hip): made where the call has a workspace and kSoftFrom entries or more.
 constexpr int64_t kSoftFrom = 1 << 16;
 constexpr int kSoftMaxBins = 512;
-constexpr int kSoftCoefs = 12;
+constexpr int kSoftCoefs = 10;
 constexpr size_t kSoftBinBytes = kSoftCoefs * sizeof(double), kSoftTableBytes = kSoftMaxBins * kSoftBinBytes;
 constexpr size_t kQuantSumBytes = (size_t)kMaxQuantBlocks * 2 * sizeof(double);
 constexpr size_t kQuantScalarBytes = kQuantSumBytes + kSoftTableBytes;

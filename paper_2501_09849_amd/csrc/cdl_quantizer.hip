@@ -897,13 +897,16 @@ int uniform_half_width(const cdl_qparams &p, const QConst &k)
     return jh;
 }
 
-// Where the table of cdl_soft.hip is faster than these kernels although it takes two small launches more (forward + backward,
-// 31 levels: 0.5 M entries 29 against 26 us, 1 M 33.8 against 36.7, 2 M 43 against 52, 25.6 M 162 against 403; 15 levels: 2 M 43
-// against 41 us, 4 M 51 against 62).  The loop over the levels, forward only for sets that it serves, is left for the
-// table from kSoftFrom on (63 levels, 65 K entries: 36 against 50 us; 255 levels: 73 against 156, 1 M entries 124 against 245).
+// Where the table of cdl_soft.hip is faster than these kernels although it takes two small launches more (us, table against
+// loop over the levels, at n * (n_levels / 2) = 1, 2, 3 times 2^24):
+//   forward   31 levels  27.0/23.5  30.3/29.9  33.4/36.6     15 levels  30.1/22.6  37.0/34.3  42.2/45.6     7 levels  38.5/31.7  53.4/53.4  69.0/77.1 (4)
+//   backward             16.0/14.6  19.8/21.9  22.4/28.5                19.1/18.3  26.8/30.3  32.7/40.2               28.1/28.5  43.1/48.2  58.8/71.6
+// The loop over the levels, forward only for sets that it serves, is left for the
+// table from kSoftFrom on (63 levels, 65 K entries: 24 against 50 us; 255 levels: 36 against 156, 1 M entries 39 against 245).
 // The backward pass of those larger sets stays with the loop: in the soft regime the scalar gradients' sums cancel
 // almost completely, and what is left there are the roundings of the loop's own arithmetic.
-bool soft_from_uniform(const cdl_qparams &p, int64_t n) { return n * (p.n_levels / 2) >= (1ll << 24); }
+bool soft_fwd_from_uniform(const cdl_qparams &p, int64_t n) { return n * (p.n_levels / 2) >= (5ll << 23); }
+bool soft_bwd_from_uniform(const cdl_qparams &p, int64_t n) { return n * (p.n_levels / 2) >= (3ll << 23); }
 
 UniConst make_uniform(const cdl_qparams &p, int jh)
 {
@@ -1071,7 +1074,8 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
         fin.marg = marg;
         fin.entropy_bits = entropy_bits;
     }
-    const SoftPlan plan = want_marg && (soft_from_uniform(p, n) || !uniform_half_width(p, k)) ? soft_plan(p, k, n) : SoftPlan{};
+    const bool uniform = uniform_half_width(p, k) != 0;
+    const SoftPlan plan = want_marg && (soft_fwd_from_uniform(p, n) || !uniform) ? soft_plan(p, k, n, uniform) : SoftPlan{};
     if (plan.bins) return launch_soft_fwd(theta, n, p, k, plan, idx, soft, fin, ws, stream);
     const bool want_idx = idx != nullptr, want_soft = soft != nullptr;
     const int jh = (want_soft || want_marg) ? uniform_half_width(p, k) : 0;
@@ -1120,7 +1124,7 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
     const double d = (double)p.delta;
     ScalarFinish fin{};
     if (want_scalars) fin = scalar_finish_args(scalars, grid, 1.0, d * d * d, d_delta, d_alpha);
-    const SoftPlan plan = want_scalars && uniform_half_width(p, k) && soft_from_uniform(p, n) ? soft_plan(p, k, n) : SoftPlan{};
+    const SoftPlan plan = want_scalars && uniform_half_width(p, k) && soft_bwd_from_uniform(p, n) ? soft_plan(p, k, n, true) : SoftPlan{};
     if (plan.bins) {
         const int rc = launch_soft_bwd(theta, g, n, p, k, plan, dtheta, fin, reinterpret_cast<char *>(scalars) + kQuantSumBytes, grid, stream);
         return rc != CDL_OK ? rc : launch_scalar_end(fin, grid, stream);

@@ -8,7 +8,9 @@
 namespace cdl {
 
 // (kSoftMaxBins, kSoftTableBytes, kSoftFrom: cdl_internal.h)
-constexpr int kSoftMoments = 6;
+// moments of an interval; one more where the intervals are fine, and their number so that the rows of the blocks hold them
+constexpr int kSoftMoments = 6, kSoftMoreMoments = 7;
+constexpr int kSoftMoreBins = kSoftMoments * kSoftMaxBins / kSoftMoreMoments;
 constexpr int kSoftThreads = 1024;
 
 // Workspace of the forward pass: the table, then the rows of the blocks' moments.
@@ -17,6 +19,7 @@ size_t soft_fwd_bytes(int64_t n, int32_t n_levels);
 
 struct SoftPlan {
     int bins;              // 0: another kernel serves
+    int fine;              // sets that the kernels in double serve otherwise: intervals of sigma / 8, else sigma / 4
     int small_set;         // at most 33 levels: entries outside the table's range in double, as the kernels for them do
     double half_range;     // the table covers |r| <= half_range, r = theta / delta - c0
     double inv_h;          // bins per unit of r
@@ -24,8 +27,8 @@ struct SoftPlan {
     double kappa;
 };
 
-// Whether the table serves (soft regime, full CPMF, a tensor large enough); bwd: for the backward pass.
-SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n);
+// Whether the table serves (soft regime, full CPMF, a tensor large enough).
+SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n, bool fine);
 
 int launch_soft_fwd(const float *theta, int64_t n, const cdl_qparams &p, const QConst &k, const SoftPlan &s, int8_t *idx, float *soft,
                     const MargFinish &fin, void *ws, hipStream_t stream);

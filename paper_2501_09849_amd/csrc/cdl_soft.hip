@@ -6,21 +6,30 @@
 //     Q_d = delta (c0 + mu),   mu' = 2 kappa var,   var' = 2 kappa c3
 // (kappa = alpha delta^2), because a derivative with respect to r brings down a cumulant of the CPMF and a factor 2 kappa.  All
 // three are analytic with features no finer than the CPMF's own width sigma = 1 / sqrt(2 kappa), so one polynomial per interval
-// of a quarter of sigma replaces the loop over the levels: a gather from LDS and 33 fused multiply-adds in double per entry where 31
+// of an eighth of sigma replaces the loop over the levels: a gather from LDS and 27 fused multiply-adds in double per entry where 31
 // levels took 250 instructions.
 //
-// The polynomial is made from its highest derivative: c3 at ten Chebyshev nodes and mu, var at the middle of the interval are sums
-// over the levels, and mu(t) is the second integral of the interpolated c3 (eleventh degree).  Integration makes errors smaller
+// The polynomial is made from its highest derivative: c3 at eight Chebyshev nodes and mu, var at the middle of the interval are sums
+// over the levels, and mu(t) is the second integral of the interpolated c3 (ninth degree).  Integration makes errors smaller
 // where differentiation multiplies them by 1 / (kappa h) each time: from an interpolated mean the third moment had 3e-8 of its size,
 // and no digit right where kappa is 1e-8.  So made, every coefficient has the relative precision of a double however small kappa
-// is, and mu, var and 2 (r - mu) var - c3 come out within 1e-15, 7e-15 and 9e-14 of their largest value (6 - 33 levels, kappa 1e-12
+// is, and mu, var and 2 (r - mu) var - c3 come out within 1e-15, 7e-15 and 2e-13 of their largest value (6 - 33 levels, kappa 1e-12
 // to 1.2, against sums in 80 bits; the loop over the levels: 3e-15, 4e-13, 2e-11).
 // The table is made by a kernel of its own.
 //
 // Marginal PMF: the sum of P_k(r) over the entries is wanted for every level k.  An entry adds the Chebyshev polynomials
-// T_0 .. T_5 of its place in its interval to six cells of a histogram (fixed point, LDS integer atomics); since on an
-// interval P_k = sum_m c_km T_m up to 4e-9 of its peak, the sums over the entries follow from the cells - at the end, once
-// per interval and level.
+// T_0 .. T_6 of its place in its interval to seven cells of a histogram; since on an interval P_k = sum_m c_km T_m up to 6e-13 of
+// its peak, the sums over the entries follow from the cells - at the end, once per interval and level.  The terms are doubles in
+// fixed point (LDS integer atomics, 2^-44, cells of 64 bits: 8.4 lane updates per clock and CU against 12.4 of 32 bits), so that
+// their rounding stays below the interpolation's error also where every entry is the same and nothing averages out.  (Six terms
+// in fp32, rounded to 2^-18, on intervals twice as long: 7e-8 of a probability there.)
+//
+// That is for the sets that the kernels on a common centre serve otherwise, whose arithmetic is double too.  The forward pass of
+// the sets that only the loop in fp32 would serve takes intervals twice as long and six moments (mu 5e-15, marginal PMF 3e-9).
+//
+// 25.6 M entries, 31 levels at the initial sharpness: forward 98 us, backward 88 (2.3 and 3.5 TB/s; LDS atomics 35 us and gathers of
+// 80 bytes an entry 26 us on the LDS pipe, 61 us of memory traffic at the copy rate), both together 187 where the loop over the
+// levels takes 403.
 //
 // Entries beyond the table's range (theta more than twice as far out as the last level) are evaluated one by one as the
 // other kernels do, and add their probabilities to a histogram of levels.
@@ -34,13 +43,14 @@ namespace cdl {
 namespace {
 
 constexpr int kSoftBwdThreads = 256;
-constexpr int kSoftScaleBits = 18;         // an entry adds rint(T_m * 2^18) to a cell: at most 2^12 entries between two flushes
+// An entry adds rint(T_m * 2^b) to a cell, with b as large as keeps a block's sums below 2^62 (44 up to 2^26 entries, then one less for
+// every doubling).  magic = 1.5 * 2^(52 - b): T_m + magic has a spacing of 2^-b, so its bits are those of magic plus that integer;
+// what the constant adds is taken off at the end, with the count T_0.
+constexpr int kSoftMostBits = 44;
 constexpr int kSoftFinBlocks = 64;
-constexpr int kNodes = 10;                  // Chebyshev nodes of an interval, for c3
+constexpr int kNodes = 8;                   // Chebyshev nodes of an interval, for c3
 constexpr int kCoefs = kSoftCoefs;          // coefficients of t^q in mu, t in [-1, 1] along the interval
 static_assert(kCoefs == kNodes + 2 && kCoefs % 2 == 0, "two integrations; pairs of coefficients are loaded");
-constexpr int kM = kSoftMoments;
-constexpr int kSoftOwn = (kM * kSoftMaxBins + kSoftThreads - 1) / kSoftThreads;      // cells that a thread adds up
 
 struct SoftConst {
     int bins, copies, lg_copies, n_levels, small_set;
@@ -48,6 +58,7 @@ struct SoftConst {
     double half_range, inv_h, c0, inv_delta, delta, kappa;
     double r_safe;
     double lo_off;         // offset of the lowest level from the centre
+    double scale, magic;   // 2^b, 1.5 * 2^(52 - b) (forward)
 };
 
 // ---- the table: [bins][kCoefs] ----
@@ -75,8 +86,11 @@ void soft_table_kernel(SoftConst s, NodeMatrix m, double *__restrict__ table)
 #pragma unroll
         for (int off = 4; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     };
+    // (a level j away from the nearest one weighs at most exp(-kappa j^2): the others are below 3e-20 of it)
+    const double band = ceil(sqrt(45.0 / s.kappa)), at = near - s.lo_off;
+    const int first = (int)fmax(0.0, at - band), last = (int)fmin((double)(s.n_levels - 1), at + band);
     double Z = 0.0, S = 0.0, j;
-    for (int k = part; k < s.n_levels; k += 8) {
+    for (int k = first + part; k <= last; k += 8) {
         const double w = weight(k, j);
         Z += w;
         S = fma(j, w, S);
@@ -85,7 +99,7 @@ void soft_table_kernel(SoftConst s, NodeMatrix m, double *__restrict__ table)
     add8(S);
     const double mean = S / Z;
     double V = 0.0, T = 0.0;
-    for (int k = part; k < s.n_levels; k += 8) {
+    for (int k = first + part; k <= last; k += 8) {
         const double w = weight(k, j), d = j - mean, dw = d * w;
         V = fma(d, dw, V);
         T = fma(d * d, dw, T);
@@ -175,43 +189,22 @@ __device__ __forceinline__ SoftSums soft_direct(double r, const SoftConst &s)
 }
 
 // ---- forward ----
-// One block of 1024 threads per compute unit.  LDS: [table][levels, 64 bits][cells: (6 bins) x hist_copies].  A cell lies in
-// the bank group of its copy, as in the other histogram kernels.  After hist_copies trips of the loop (2^12 entries for a
-// cell) every thread moves its cells to 64-bit registers.
-template <bool IDX, bool SOFT>
+// One block of 1024 threads per compute unit.  LDS: [table][levels][cells: (M bins) x hist_copies].  A cell lies in the bank
+// group of its copy, as in the other histogram kernels.
+template <int M, bool IDX, bool SOFT>
 __global__ __launch_bounds__(kSoftThreads)
 void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftConst s, const double *__restrict__ table,
-                     int8_t *__restrict__ idx, float *__restrict__ soft, long long *__restrict__ rows /* [gridDim.x][6 bins + levels] */)
+                     int8_t *__restrict__ idx, float *__restrict__ soft, long long *__restrict__ rows /* [gridDim.x][M bins + levels] */)
 {
     extern __shared__ __attribute__((aligned(16))) uint4 soft_lds[];
     unsigned long long *levels = reinterpret_cast<unsigned long long *>(soft_lds + kCoefs / 2 * (s.bins << s.lg_copies));
-    int *cells = reinterpret_cast<int *>(levels + s.n_levels);
-    const int n_cells = kM * s.bins;
+    unsigned long long *cells = levels + s.n_levels;
+    const int n_cells = M * s.bins;
     load_table<kSoftThreads>(s, table, soft_lds);
-    for (int i = threadIdx.x; i < n_cells << s.lg_hist_copies; i += kSoftThreads) cells[i] = 0;
+    for (int i = threadIdx.x; i < n_cells << s.lg_hist_copies; i += kSoftThreads) cells[i] = 0ull;
     if ((int)threadIdx.x < s.n_levels) levels[threadIdx.x] = 0ull;
     __syncthreads();
-    int *mine = cells + ((int)threadIdx.x & (s.hist_copies - 1));
-    long long own[kSoftOwn] = {};
-
-    auto flush = [&](bool again) {
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kSoftOwn; ++q) {
-            const int i = q * kSoftThreads + threadIdx.x;
-            if (i < n_cells) {
-                int *c = cells + (i << s.lg_hist_copies);
-                long long v = 0;
-                for (int j = 0; j < s.hist_copies; ++j) {
-                    const int at = (j + (i >> (5 - s.lg_hist_copies))) & (s.hist_copies - 1);
-                    v += c[at];
-                    c[at] = 0;
-                }
-                own[q] += v;
-            }
-        }
-        if (again) __syncthreads();
-    };
+    unsigned long long *mine = cells + ((int)threadIdx.x & (s.hist_copies - 1));
 
     // true: done; false: an entry beyond the table
     auto inside = [&](float th, float &sv) -> bool {
@@ -225,16 +218,14 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
                 for (int i = kCoefs - 2; i >= 0; --i) mu = fma(mu, p.t, q.c[i]);
                 sv = (float)(s.delta * (s.c0 + mu));
             }
-            constexpr float kOne = (float)(1 << kSoftScaleBits);
-            const float t = (float)p.t;
-            int *c = mine + ((kM * p.bin) << s.lg_hist_copies);
-            atomicAdd(c, 1 << kSoftScaleBits);
-            float before = 1.0f, now = t;
+            unsigned long long *c = mine + ((M * p.bin) << s.lg_hist_copies);
+            atomicAdd(c, 1ull);
+            double before = 1.0, now = p.t;
 #pragma unroll
-            for (int m = 1; m < kM; ++m) {
+            for (int m = 1; m < M; ++m) {
                 c += s.hist_copies;
-                atomicAdd(c, (int)rintf(now * kOne));
-                const float next = fmaf(2.0f * t, now, -before);
+                atomicAdd(c, (unsigned long long)__double_as_longlong(now + s.magic));
+                const double next = fma(2.0 * p.t, now, -before);
                 before = now;
                 now = next;
             }
@@ -245,7 +236,7 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
         if (s.small_set) {
             const double r = soft_clamp(fma((double)th, s.inv_delta, -s.c0), s);
             const SoftSums q = soft_direct(r, s);
-            const double scale = (double)(1u << kHistScaleBits) / q.Z;
+            const double scale = s.scale / q.Z;
 #pragma unroll 1
             for (int l = 0; l < s.n_levels; ++l) {
                 const double j = s.lo_off + l - q.near;
@@ -255,7 +246,7 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
         }
         GenericSums q;
         generic_sums<IDX>(th, k, q);
-        const float inv = fast_rcp(q.Z), two_u = 2.0f * q.u, scale = inv * (float)(1u << kHistScaleBits);
+        const float inv = fast_rcp(q.Z), two_u = 2.0f * q.u, scale = inv * (float)s.scale;
 #pragma unroll 1
         for (int j = q.jlo; j <= q.jhi; ++j)
             atomicAdd(levels + ((int)q.cf - k.lo + j), (unsigned long long)rintf(generic_weight(j, two_u, k) * scale));
@@ -263,7 +254,6 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
     };
 
     const int64_t n4 = n >> 2, stride = (int64_t)gridDim.x * kSoftThreads;
-    int trips = 0;
     int64_t v = (int64_t)blockIdx.x * kSoftThreads + threadIdx.x;
     float4 ahead = {0.0f, 0.0f, 0.0f, 0.0f};
     if (v < n4) ahead = load_stream4(theta + 4 * v, k.stream);
@@ -292,73 +282,74 @@ void soft_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k, SoftC
                 reinterpret_cast<uint32_t *>(idx)[v] = pack_indices(ci[0], ci[1], ci[2], ci[3], k.idx_off);
             }
         }
-        if (++trips == s.hist_copies) {
-            flush(true);
-            trips = 0;
-        }
     }
-    flush(true);
     // ragged tail: the last 1..3 entries
-    if (blockIdx.x == gridDim.x - 1) {
-        if (threadIdx.x == 0)
-            for (int64_t e = n4 << 2; e < n; ++e) {
-                float sv = 0.0f;
-                if (!inside(theta[e], sv)) sv = outside(theta[e]);
-                if (SOFT) soft[e] = sv;
-                if (IDX) idx[e] = (int8_t)((int)anchor_level<true>(theta[e], k) - k.idx_off);
-            }
-        flush(true);
-    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+        for (int64_t e = n4 << 2; e < n; ++e) {
+            float sv = 0.0f;
+            if (!inside(theta[e], sv)) sv = outside(theta[e]);
+            if (SOFT) soft[e] = sv;
+            if (IDX) idx[e] = (int8_t)((int)anchor_level<true>(theta[e], k) - k.idx_off);
+        }
+    __syncthreads();
     long long *row = rows + (size_t)blockIdx.x * (n_cells + s.n_levels);
-#pragma unroll
-    for (int q = 0; q < kSoftOwn; ++q) {
-        const int i = q * kSoftThreads + threadIdx.x;
-        if (i < n_cells) row[i] = own[q];
+    auto cell_sum = [&](int i) {
+        unsigned long long v = 0ull;
+        for (int j = 0; j < s.hist_copies; ++j) v += cells[(i << s.lg_hist_copies) + ((j + i) & (s.hist_copies - 1))];
+        return v;
+    };
+    for (int i = threadIdx.x; i < n_cells; i += kSoftThreads) {
+        const int m = i % M;
+        unsigned long long v = cell_sum(i);
+        if (m) v -= cell_sum(i - m) * (unsigned long long)__double_as_longlong(s.magic);
+        row[i] = (long long)v;
     }
     if ((int)threadIdx.x < s.n_levels) row[n_cells + threadIdx.x] = (long long)levels[threadIdx.x];
 }
 
 // From the moments to the marginal PMF.  Block b takes the intervals [b bins / B, (b + 1) bins / B): adds the rows' cells,
-// turns the six moments S_m of an interval into weights of its six Chebyshev nodes x_q (the discrete orthogonality of the T_m:
-// w_q = (S_0 + 2 sum_m S_m T_m(x_q)) / 6 gives sum_q w_q f(x_q) = the sum of f over the entries for every polynomial f of
-// degree 5), and adds w_q P_k(x_q) for all levels k.
+// turns the M moments S_m of an interval into weights of its M Chebyshev nodes x_q (the discrete orthogonality of the T_m:
+// w_q = (S_0 + 2 sum_m S_m T_m(x_q)) / M gives sum_q w_q f(x_q) = the sum of f over the entries for every polynomial f of
+// degree M - 1), and adds w_q P_k(x_q) for all levels k.  The rows' integers are added up as doubles, in a fixed order.
 constexpr int kSoftFinThreads = 1024;
-constexpr int kFinCells = 64;                               // at least kM * kSoftMaxBins / kSoftFinBlocks
-static_assert(kM * ((kSoftMaxBins + kSoftFinBlocks - 1) / kSoftFinBlocks) <= kFinCells, "cells of a block");
-struct NodePlace { double x[kM]; };
+constexpr int kFinCells = 64;                               // at least the cells of a block
+static_assert(kSoftMoments * ((kSoftMaxBins + kSoftFinBlocks - 1) / kSoftFinBlocks) <= kFinCells &&
+              kSoftMoreMoments * ((kSoftMoreBins + kSoftFinBlocks - 1) / kSoftFinBlocks) <= kFinCells, "cells of a block");
+struct NodePlace { double x[kSoftMoreMoments]; };
 
+template <int M>
 __global__ __launch_bounds__(kSoftFinThreads)
 void soft_marginal_kernel(const long long *__restrict__ rows, int n_rows, SoftConst s, NodePlace nodes, MargFinish fin)
 {
-    __shared__ long long part[kSoftFinThreads];
+    __shared__ double part[kSoftFinThreads];
     __shared__ double red[kSoftFinThreads];
-    __shared__ long long sums[kFinCells];
+    __shared__ double sums[kFinCells];
     __shared__ double weight[kFinCells], place[kFinCells], from[kFinCells];
-    const int tid = threadIdx.x, n_cells = kM * s.bins, row = n_cells + s.n_levels;
+    const int tid = threadIdx.x, n_cells = M * s.bins, row = n_cells + s.n_levels;
     const int b0 = (int)((int64_t)blockIdx.x * s.bins / gridDim.x), b1 = (int)((int64_t)(blockIdx.x + 1) * s.bins / gridDim.x);
-    const int cells = kM * (b1 - b0);
+    const int cells = M * (b1 - b0);
     {
         constexpr int kSubs = kSoftFinThreads / kFinCells;
         const int c = tid & (kFinCells - 1), sub = tid / kFinCells;
-        long long v = 0;
+        double v = 0.0;
         if (c < cells) {
 #pragma unroll 16
-            for (int r = sub; r < n_rows; r += kSubs) v += rows[(size_t)r * row + kM * b0 + c];
+            for (int r = sub; r < n_rows; r += kSubs) v += (double)rows[(size_t)r * row + M * b0 + c];
         }
         part[tid] = v;
         __syncthreads();
         if (tid < kFinCells) {
-            long long t = 0;
+            double t = 0.0;
 #pragma unroll
             for (int q = 0; q < kSubs; ++q) t += part[q * kFinCells + tid];
-            sums[tid] = t;
+            sums[tid] = tid % M ? t : t * s.scale;      // (T_0 is counted in ones)
         }
         __syncthreads();
     }
     // eight threads to a node for the normaliser
     {
         const int node = tid >> 3, lane8 = tid & 7;
-        const int i = node / kM, q = node % kM;
+        const int i = node / M, q = node % M;
         const double x = nodes.x[q];
         const double r = -s.half_range + (b0 + i + 0.5 * (1.0 + x)) / s.inv_h;
         const double near = fmin(fmax(rint(r - s.lo_off), 0.0), (double)(s.n_levels - 1)) + s.lo_off, d0 = r - near;
@@ -371,15 +362,15 @@ void soft_marginal_kernel(const long long *__restrict__ rows, int n_rows, SoftCo
 #pragma unroll
         for (int off = 4; off > 0; off >>= 1) Z += __shfl_xor(Z, off, 64);
         if (node < cells && lane8 == 0) {
-            double w = 0.5 * (double)sums[kM * i], before = 1.0, now = x;
+            double w = 0.5 * sums[M * i], before = 1.0, now = x;
 #pragma unroll
-            for (int m = 1; m < kM; ++m) {
-                w = fma((double)sums[kM * i + m], now, w);
+            for (int m = 1; m < M; ++m) {
+                w = fma(sums[M * i + m], now, w);
                 const double next = fma(2.0 * x, now, -before);
                 before = now;
                 now = next;
             }
-            weight[node] = w * (2.0 / kM) / Z;
+            weight[node] = w * (2.0 / M) / Z;
             place[node] = r;
             from[node] = d0 * d0;
         }
@@ -403,10 +394,9 @@ void soft_marginal_kernel(const long long *__restrict__ rows, int n_rows, SoftCo
     if (tid < s.n_levels) {
         double t = 0.0;
         for (int q = 0; q < subs; ++q) t += red[(q << lg) + tid];
-        long long extra = 0;
 #pragma unroll 4
-        for (int r = blockIdx.x; r < n_rows; r += gridDim.x) extra += rows[(size_t)r * row + n_cells + tid];
-        own = (unsigned long long)(__double2ll_rn(t * (double)(1 << (kHistScaleBits - kSoftScaleBits))) + extra);
+        for (int r = blockIdx.x; r < n_rows; r += gridDim.x) t += (double)rows[(size_t)r * row + n_cells + tid];
+        own = (unsigned long long)__double2ll_rn(t * ((double)(1 << kHistScaleBits) / s.scale));
     }
     if (blockIdx.x != gridDim.x - 1) {
         if (tid < s.n_levels) marginal_publish(own, (size_t)blockIdx.x * s.n_levels + tid, fin);
@@ -500,13 +490,13 @@ SoftConst soft_const(const cdl_qparams &p, const SoftPlan &s)
 }
 
 // copies of the table and of the cells that fit `bytes` of LDS (powers of two, up to 8 and 32)
-void soft_copies(SoftConst &c, size_t table_bytes, size_t hist_bytes)
+void soft_copies(SoftConst &c, size_t table_bytes, int moments, size_t hist_bytes)
 {
     c.lg_copies = 0;
     while (c.lg_copies < 3 && ((size_t)c.bins * kSoftBinBytes << (c.lg_copies + 1)) <= table_bytes) ++c.lg_copies;
     c.copies = 1 << c.lg_copies;
     c.lg_hist_copies = 0;
-    while (c.lg_hist_copies < 5 && ((size_t)c.bins * kM * sizeof(int) << (c.lg_hist_copies + 1)) <= hist_bytes) ++c.lg_hist_copies;
+    while (c.lg_hist_copies < 5 && ((size_t)c.bins * moments * sizeof(long long) << (c.lg_hist_copies + 1)) <= hist_bytes) ++c.lg_hist_copies;
     c.hist_copies = 1 << c.lg_hist_copies;
 }
 
@@ -530,11 +520,47 @@ int launch_table(const SoftConst &c, void *table, hipStream_t stream)
     return check_launch();
 }
 
-NodePlace marginal_nodes()
+NodePlace marginal_nodes(int moments)
 {
-    NodePlace p;
-    for (int q = 0; q < kM; ++q) p.x[q] = cos((2 * q + 1) * 3.14159265358979323846 / (2 * kM));
+    NodePlace p{};
+    for (int q = 0; q < moments; ++q) p.x[q] = cos((2 * q + 1) * 3.14159265358979323846 / (2 * moments));
     return p;
+}
+
+template <int M>
+int launch_soft_fwd_m(const float *theta, int64_t n, const QConst &k, SoftConst c, int8_t *idx, float *soft, const MargFinish &fin, void *ws,
+                      hipStream_t stream)
+{
+    // one block per compute unit: the table up to 28 KB (one copy of the largest: 48), the levels' cells, and the cells in what is left
+    soft_copies(c, 28 << 10, M, (160 << 10) - 2048 - (c.bins * kSoftBinBytes > (28 << 10) ? c.bins * kSoftBinBytes : 28 << 10));
+    const int64_t grid = soft_fwd_grid(n);
+    const int64_t per_block = ((n >> 2) + grid * kSoftThreads) / (grid * kSoftThreads) * (4 * kSoftThreads) + 3;
+    int bits = kSoftMostBits;
+    while (bits > 20 && per_block > 1ll << (62 - bits)) --bits;
+    c.scale = (double)(1ll << bits);
+    c.magic = 1.5 * (double)(1ll << (52 - bits));
+    long long *rows = reinterpret_cast<long long *>(reinterpret_cast<char *>(ws) + kSoftTableBytes);
+    const double *table = reinterpret_cast<const double *>(ws);
+    const size_t lds = ((size_t)c.bins * kSoftBinBytes << c.lg_copies) + (size_t)c.n_levels * sizeof(long long) + ((size_t)c.bins * M * sizeof(long long) << c.lg_hist_copies);
+    const char *name = soft || idx ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)";
+#define CDL_SOFT(I, S) \
+    do { \
+        if (lds > 65536) { \
+            const hipError_t e_ = hipFuncSetAttribute((const void *)soft_fwd_kernel<M, I, S>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+            if (e_ != hipSuccess) return hip_failed(e_); \
+        } \
+        CDL_LAUNCH(name, stream, (soft_fwd_kernel<M, I, S>), dim3((unsigned)grid), dim3(kSoftThreads), lds, theta, n, k, c, table, idx, soft, rows); \
+    } while (0)
+    if (idx && soft) CDL_SOFT(true, true);
+    else if (idx) CDL_SOFT(true, false);
+    else if (soft) CDL_SOFT(false, true);
+    else CDL_SOFT(false, false);
+#undef CDL_SOFT
+    const int rc = check_launch();
+    if (rc != CDL_OK) return rc;
+    static const NodePlace nodes = marginal_nodes(M);
+    CDL_LAUNCH("marginal_finalize_kernel", stream, soft_marginal_kernel<M>, dim3(kSoftFinBlocks), dim3(kSoftFinThreads), 0, rows, (int)grid, c, nodes, fin);
+    return check_launch();
 }
 
 }  // namespace
@@ -550,7 +576,7 @@ int64_t soft_fwd_grid(int64_t n)
 constexpr int kSoftRowWords = kSoftMoments * kSoftMaxBins + 256;
 size_t soft_fwd_bytes(int64_t n, int32_t) { return kSoftTableBytes + (size_t)soft_fwd_grid(n) * kSoftRowWords * sizeof(long long); }
 
-SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n)
+SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n, bool fine)
 {
     SoftPlan s{};
     // (the other kernels: truncated CPMFs, sharp regimes, small tensors)
@@ -558,13 +584,14 @@ SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n)
     const double delta = (double)p.delta, kappa = (double)p.alpha * delta * delta, sigma = 1.0 / sqrt(2.0 * kappa);
     s.small_set = p.n_levels <= 33;
     s.half_range = (double)(p.n_levels - 1) + 4.0;
-    const double most = 0.125 * sigma * kSoftMaxBins;
+    s.fine = fine;
+    const double width = (fine ? 0.125 : 0.25) * sigma, most = 0.5 * width * (fine ? kSoftMoreBins : kSoftMaxBins);
     if (most < 0.75 * (double)(p.n_levels - 1) + 4.0) return s;      // a band much narrower than the set: the loop over the band
     if (s.half_range > most) s.half_range = most;
     // at least eight intervals: entries then spread over the banks
-    s.bins = (int)ceil(2.0 * s.half_range / (0.25 * sigma));
+    s.bins = (int)ceil(2.0 * s.half_range / width);
     if (s.bins < 8) s.bins = 8;
-    if (s.bins > kSoftMaxBins) s.bins = kSoftMaxBins;
+    if (s.bins > (fine ? kSoftMoreBins : kSoftMaxBins)) s.bins = fine ? kSoftMoreBins : kSoftMaxBins;
     s.inv_h = s.bins / (2.0 * s.half_range);
     s.c0 = (double)p.lo + 0.5 * (double)(p.n_levels - 1);
     s.delta = delta;
@@ -576,39 +603,18 @@ SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n)
 int launch_soft_fwd(const float *theta, int64_t n, const cdl_qparams &p, const QConst &k, const SoftPlan &s, int8_t *idx, float *soft,
                     const MargFinish &fin, void *ws, hipStream_t stream)
 {
-    SoftConst c = soft_const(p, s);
-    // one block per compute unit: the table up to 28 KB (one copy of the largest: 48) and the cells up to 40, and the levels' cells
-    soft_copies(c, 28 << 10, 40 << 10);
-    int rc = launch_table(c, ws, stream);
+    const SoftConst c = soft_const(p, s);
+    const int rc = launch_table(c, ws, stream);
     if (rc != CDL_OK) return rc;
-    const int64_t grid = soft_fwd_grid(n);
-    long long *rows = reinterpret_cast<long long *>(reinterpret_cast<char *>(ws) + kSoftTableBytes);
-    const double *table = reinterpret_cast<const double *>(ws);
-    const size_t lds = ((size_t)c.bins * kSoftBinBytes << c.lg_copies) + (size_t)c.n_levels * sizeof(long long) + ((size_t)c.bins * kM * sizeof(int) << c.lg_hist_copies);
-    const char *name = soft || idx ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)";
-#define CDL_SOFT(I, S) \
-    if (lds > 65536) { \
-        const hipError_t e_ = hipFuncSetAttribute((const void *)soft_fwd_kernel<I, S>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
-        if (e_ != hipSuccess) return hip_failed(e_); \
-    } \
-    CDL_LAUNCH(name, stream, (soft_fwd_kernel<I, S>), dim3((unsigned)grid), dim3(kSoftThreads), lds, theta, n, k, c, table, idx, soft, rows)
-    if (idx && soft) { CDL_SOFT(true, true); }
-    else if (idx) { CDL_SOFT(true, false); }
-    else if (soft) { CDL_SOFT(false, true); }
-    else { CDL_SOFT(false, false); }
-#undef CDL_SOFT
-    rc = check_launch();
-    if (rc != CDL_OK) return rc;
-    static const NodePlace nodes = marginal_nodes();
-    CDL_LAUNCH("marginal_finalize_kernel", stream, soft_marginal_kernel, dim3(kSoftFinBlocks), dim3(kSoftFinThreads), 0, rows, (int)grid, c, nodes, fin);
-    return check_launch();
+    return s.fine ? launch_soft_fwd_m<kSoftMoreMoments>(theta, n, k, c, idx, soft, fin, ws, stream)
+                                   : launch_soft_fwd_m<kSoftMoments>(theta, n, k, c, idx, soft, fin, ws, stream);
 }
 
 int launch_soft_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams &p, const QConst &k, const SoftPlan &s, float *dtheta,
                     const ScalarFinish &fin, void *table, int grid, hipStream_t stream)
 {
     SoftConst c = soft_const(p, s);
-    soft_copies(c, 28 << 10, 0);
+    soft_copies(c, 28 << 10, 1, 0);
     int rc = launch_table(c, table, stream);
     if (rc != CDL_OK) return rc;
     const size_t lds = (size_t)c.bins * kSoftBinBytes << c.lg_copies;

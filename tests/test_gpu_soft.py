@@ -93,7 +93,7 @@ def test_scalar_gradients_of_the_table_at_any_sharpness(levels, kappa):
     uniform one, with gradients that cancel and gradients that do not."""
     import paper_2501_09849_amd as cdl
     torch = gu.torch_mod()
-    n = (1 << 24) // (levels // 2) + 5
+    n = (3 << 23) // (levels // 2) + 5
     if kappa == 1.0:      # the highest sharpness that the table serves
         kappa = {6: 1.2, 7: 1.2, 15: 0.8, 31: 0.15, 33: 0.13}[levels]
     lo = -(levels // 2)
@@ -128,3 +128,29 @@ def test_scalar_gradients_of_the_table_at_any_sharpness(levels, kappa):
         assert abs(da.item() - step ** 3 * ref_a) <= step ** 3 * (bound_a + 6e-8 * abs(ref_a)), (da.item(), ref_a)
         want = g[:values.size] * (2 * k * var).astype(np.float64)
         assert (np.abs(dth[:values.size].cpu().numpy() - want) <= 1.2e-7 * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("levels,kappa", [(6, 1.2), (7, 0.05), (15, 0.8), (15, 0.0077), (31, 0.15), (31, 0.0077), (33, 0.13), (31, 1e-6)])
+def test_marginal_pmf_of_equal_entries(levels, kappa):
+    """Where every entry is the same nothing averages out: the marginal PMF is the entry's CPMF rounded to fp32, inside the table's range
+    (next to a node, at an interval's edge, anywhere) and beyond it."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    n = (5 << 23) // (levels // 2) + 3
+    lo = -(levels // 2)
+    step = np.float64(np.float32(0.03))
+    sharp = np.float64(np.float32(kappa / step ** 2))
+    k, c0 = sharp * step * step, lo + 0.5 * (levels - 1)
+    ws = gu.workspace(cdl.quantize_workspace_bytes(n, levels))
+    idx, marg, H = gu.empty((n,), torch.int8), gu.empty((levels,), torch.float32), gu.empty((1,), torch.float32)
+    values = np.float32([0.0, 0.013, -0.4 * (levels - 1) * step, 0.31 * step * levels, (levels + 4.0) * step, (-levels - 9.3) * step])
+    P = _moments(values.astype(np.float64) / step - c0, levels, k)[0]
+    for v, want in zip(values, P):
+        theta = torch.full((n,), float(v), device="cuda")
+        cdl.cdl_quantize_fwd(theta, n, lo, levels, float(step), float(sharp), idx, None, marg, H, ws)
+        torch.cuda.synchronize()
+        m = marg.cpu().numpy().astype(np.longdouble)
+        # half a unit of the fp32 result; interpolation: 1e-12 of the largest probability; 64 partial sums rounded to 2^-21
+        assert (np.abs(m - want) <= 6e-8 * want + 1e-12 * want.max() + 64 * 2.0 ** -22 / n).all(), (float(v), np.abs(m - want).max())
+        w = want[want > 0]
+        assert abs(H.item() + float((w * np.log2(w)).sum())) <= 1.2e-7 * abs(H.item()) + 1e-9

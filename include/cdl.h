@@ -116,12 +116,13 @@ int cdl_quantize_fwd(const float *theta, int64_t n, const cdl_qparams *p,
 /*
  * cdl_quantize_fwd for callers that cannot allocate device memory or have no workspace to hand over: code
  * running under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * outputs and kernels as cdl_quantize_fwd, minus `ws`: the per-block histograms, the second-level sums and the
- * ticket word of the marginal PMF live in a buffer that is part of the library's device code
- * (cdl_static_scratch_bytes() = 8 MiB on every GPU the library runs on, held until the process ends).  The call
+ * outputs and kernels as cdl_quantize_fwd, minus `ws`: the per-block histograms and sums of the marginal PMF live in a
+ * buffer that is part of the library's device code (cdl_static_scratch_bytes() = 8 MiB for the histograms, and 256 KiB
+ * beside them, on every GPU the library runs on, held until the process ends).  The call
  * allocates and frees nothing, on the host or on the device, as long as cdl_profile_enable is off.
- * CDL_ERR_TOO_LARGE when marg or entropy_bits is requested and cdl_quantize_workspace_bytes(n, n_levels)
- * exceeds cdl_static_scratch_bytes() (with 255 levels: beyond about 10^8 entries); nothing is launched then.
+ * CDL_ERR_TOO_LARGE when marg or entropy_bits is requested and the histograms - 8 n_levels bytes for each of at
+ * most 1024 blocks, or beyond 2^25 entries for every 32768 of them, in whole multiples of 1024 - and 65792 bytes more
+ * exceed cdl_static_scratch_bytes() (with 255 levels: beyond about 10^8 entries); nothing is launched then.
  * Without marg and entropy_bits no scratch is used and any n is accepted.
  * All calls on one GPU share that GPU's buffer, which keeps the last call's contents (every call overwrites
  * what it reads): two calls that overlap in time on one GPU - different streams, different host threads -

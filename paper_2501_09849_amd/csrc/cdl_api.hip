@@ -178,7 +178,7 @@ int cdl_quantize_fwd_static(const float *theta, int64_t n, const cdl_qparams *p,
         return CDL_ERR_ALIGN;
     void *ws = nullptr;
     if (marg || entropy_bits) {
-        if (quantize_workspace_bytes(n, p->n_levels) > kStaticScratchBytes) return CDL_ERR_TOO_LARGE;
+        if (!quantizer_static_fits(n, p->n_levels)) return CDL_ERR_TOO_LARGE;
         rc = quantizer_static_scratch(&ws);
         if (rc != CDL_OK) return rc;
     }

@@ -96,8 +96,9 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
                        float scale, float *dtheta, float *d_delta, float *d_alpha, void *ws, hipStream_t stream);
 
 // Scratch that lives inside the library (one file-scope device array per GPU) for the entry point that takes
-// no workspace: its size, and its device address on the current device (looked up on first use).
+// no workspace: whether it holds what a forward call needs, and its device address on the current device (looked up on first use).
 constexpr size_t kStaticScratchBytes = 8u << 20;
+bool quantizer_static_fits(int64_t n, int32_t n_levels);
 int quantizer_static_scratch(void **ptr);
 
 // 0, or 128 for level sets that reach beyond 127: what the kernels subtract from a level index before storing it.

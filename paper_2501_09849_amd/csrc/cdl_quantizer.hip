@@ -827,9 +827,10 @@ bool hist_few(int64_t grid, int32_t n_levels) { return grid <= kFinishMaxBlocks 
 
 // workspace layout: [rows of the histogram kernel's blocks][records of the finishing blocks][scalar partials or records]
 // (or the table and the rows of moments of the soft regime)
+size_t hist_row_bytes(int64_t n, int32_t n_levels) { return align_up((size_t)hist_grid_for(n) * (size_t)n_levels * sizeof(unsigned long long), 256); }
 size_t hist_bytes(int64_t n, int32_t n_levels)
 {
-    const size_t rows = align_up((size_t)hist_grid_for(n) * (size_t)n_levels * sizeof(unsigned long long), 256);
+    const size_t rows = hist_row_bytes(n, n_levels);
     const size_t soft = n >= kSoftFrom ? align_up(soft_fwd_bytes(n, n_levels), 256) : 0;
     return rows > soft ? rows : soft;
 }
@@ -1020,13 +1021,19 @@ size_t quantize_workspace_bytes(int64_t n, int32_t n_levels)
 // One array per GPU the library runs on, held until the process ends.  In host code the array's name is only a
 // stand-in: the device address comes from hipGetSymbolAddress, looked up once per device (with that device
 // current) and kept; kernels and copies are always handed that address.
+// kStaticScratchBytes are for the blocks' histograms and 65792 bytes that the documented limit counts with them; the records of the
+// blocks that finish a marginal PMF lie behind.  The soft regime's table and rows, which take the place of the histograms, are smaller.
 namespace {
-__device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+constexpr size_t kStaticBesideRows = 65792;
+__device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kRecordBytes];
+static_assert(kStaticScratchBytes - kStaticBesideRows >= kSoftTableBytes + 256 * (size_t)kSoftRowWords * sizeof(long long) + 256, "soft regime");
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void *g_scratch_ptr[kMaxDevices] = {};
 }  // namespace
+
+bool quantizer_static_fits(int64_t n, int32_t n_levels) { return hist_row_bytes(n, n_levels) + kStaticBesideRows <= kStaticScratchBytes; }
 
 int quantizer_static_scratch(void **ptr)
 {

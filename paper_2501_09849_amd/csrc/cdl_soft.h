@@ -12,6 +12,7 @@ namespace cdl {
 constexpr int kSoftMoments = 6, kSoftMoreMoments = 7;
 constexpr int kSoftMoreBins = kSoftMoments * kSoftMaxBins / kSoftMoreMoments;
 constexpr int kSoftThreads = 1024;
+constexpr int kSoftRowWords = kSoftMoments * kSoftMaxBins + 256;
 
 // Workspace of the forward pass: the table, then the rows of the blocks' moments.
 int64_t soft_fwd_grid(int64_t n);

@@ -573,7 +573,6 @@ int64_t soft_fwd_grid(int64_t n)
     return g < 1 ? 1 : g;
 }
 
-constexpr int kSoftRowWords = kSoftMoments * kSoftMaxBins + 256;
 size_t soft_fwd_bytes(int64_t n, int32_t) { return kSoftTableBytes + (size_t)soft_fwd_grid(n) * kSoftRowWords * sizeof(long long); }
 
 SoftPlan soft_plan(const cdl_qparams &p, const QConst &k, int64_t n, bool fine)

@@ -82,3 +82,23 @@ def test_static_scratch_entry_point_matches_the_workspace_one(oracle):
     assert rc == -7
     msg = _raw(lib, "cdl_status_string", ctypes.c_char_p, [ctypes.c_int])(rc).decode()
     assert "scratch" in msg
+
+
+@pytest.mark.parametrize("n,levels", [(200_000_000, 169), (300_000_000, 112)])
+def test_static_scratch_at_the_largest_size_it_takes(n, levels):
+    """The last level count whose histograms fit the built-in buffer is served and gives what the call with a workspace gives; one
+    level more is refused.  (The records behind the histograms must not count against the limit.)"""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(levels)
+    theta = torch.randn(n, device="cuda", generator=gen)
+    spec = (-(levels // 2), levels, 0.05, 4.0 / 0.05 ** 2)
+    idx, m0, m1, h0, h1 = gu.empty((n,), torch.int8), *(gu.empty((k,), torch.float32) for k in (levels, levels, 1, 1))
+    cdl.cdl_quantize_fwd(theta, n, *spec, idx, None, m0, h0, gu.workspace(cdl.quantize_workspace_bytes(n, levels)))
+    cdl.cdl_quantize_fwd_static(theta, n, *spec, idx, None, m1, h1)
+    torch.cuda.synchronize()
+    assert torch.equal(m0, m1) and torch.equal(h0, h1) and abs(float(m0.double().sum()) - 1.0) < 1e-5
+    with pytest.raises(cdl.CdlError) as e:
+        cdl.cdl_quantize_fwd_static(theta, n, spec[0], levels + 1, *spec[2:], idx, None, gu.empty((levels + 1,), torch.float32), h1)
+    assert e.value.status == -7

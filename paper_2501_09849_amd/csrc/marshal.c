@@ -70,20 +70,37 @@ static int get_stream(PyObject *o, void **p)
     return PyErr_Occurred() ? -1 : 0;
 }
 
-static int get_int(PyObject *o, int64_t *v)
+/*
+ * An integer.  Sizes are integers or what Python takes as an index (a float or a text would be a wrong length without a word);
+ * the numbers of a quantizer and offsets are converted as int() does.
+ */
+static int get_int_by(PyObject *o, int64_t *v, PyObject *(*convert)(PyObject *))
 {
     if (PyLong_Check(o)) { *v = (int64_t)PyLong_AsUnsignedLongLongMask(o); return PyErr_Occurred() ? -1 : 0; }
-    PyObject *n = PyNumber_Long(o);
+    PyObject *n = convert(o);
     if (!n) return -1;
     *v = (int64_t)PyLong_AsUnsignedLongLongMask(n);
     Py_DECREF(n);
     return PyErr_Occurred() ? -1 : 0;
 }
+static int get_index(PyObject *o, int64_t *v) { return get_int_by(o, v, PyNumber_Index); }
+static int get_int(PyObject *o, int64_t *v) { return get_int_by(o, v, PyNumber_Long); }
+
+/* a real number of a quantizer, or a scale: as float() converts it */
+static int get_real(PyObject *o, float *v)
+{
+    if (PyFloat_Check(o)) { *v = (float)PyFloat_AS_DOUBLE(o); return 0; }
+    PyObject *f = PyNumber_Float(o);
+    if (!f) return -1;
+    *v = (float)PyFloat_AsDouble(f);
+    Py_DECREF(f);
+    return PyErr_Occurred() ? -1 : 0;
+}
 
 /*
- * One call's arguments by the letters of a format: p pointer, n 64-bit size, i 32-bit integer, f float, q quantizer (lo,
- * n_levels, delta, alpha, top_k: five arguments), w workspace (pointer and size), s stream.  They are filled in order
- * into the arrays of their kind.
+ * One call's arguments by the letters of a format: p pointer, n 64-bit size, i 32-bit size, o offset (among the 32-bit
+ * integers), f float, r real number by float() (among the floats), q quantizer (lo, n_levels, delta, alpha, top_k: five
+ * arguments), w workspace (pointer and size), s stream.  They are filled in order into the arrays of their kind.
  */
 struct args {
     void *p[12];
@@ -105,8 +122,10 @@ static int parse(const char *name, const char *format, PyObject *const *o, Py_ss
         if (at + (*c == 'q' ? 5 : 1) > count) goto wrong;
         switch (*c) {
             case 'p': if (get_ptr(o[at++], &a->p[np++])) return -1; break;
-            case 'n': if (get_int(o[at++], &a->n)) return -1; break;
-            case 'i': if (get_int(o[at++], &v)) return -1; a->i[ni++] = (int32_t)v; break;
+            case 'n': if (get_index(o[at++], &a->n)) return -1; break;
+            case 'i': if (get_index(o[at++], &v)) return -1; a->i[ni++] = (int32_t)v; break;
+            case 'o': if (get_int(o[at++], &v)) return -1; a->i[ni++] = (int32_t)v; break;
+            case 'r': if (get_real(o[at++], &a->f[nf++])) return -1; break;
             case 'f': a->f[nf] = (float)PyFloat_AsDouble(o[at++]); ++nf; if (PyErr_Occurred()) return -1; break;
             case 'q': {
                 cdl_qparams *q = &a->q[nq++];
@@ -114,9 +133,7 @@ static int parse(const char *name, const char *format, PyObject *const *o, Py_ss
                 q->lo = (int32_t)v;
                 if (get_int(o[at + 1], &v)) return -1;
                 q->n_levels = (int32_t)v;
-                q->delta = (float)PyFloat_AsDouble(o[at + 2]);
-                q->alpha = (float)PyFloat_AsDouble(o[at + 3]);
-                if (PyErr_Occurred() || get_int(o[at + 4], &v)) return -1;
+                if (get_real(o[at + 2], &q->delta) || get_real(o[at + 3], &q->alpha) || get_int(o[at + 4], &v)) return -1;
                 q->top_k = (int32_t)v;
                 at += 5;
                 break;
@@ -137,24 +154,24 @@ wrong:
     X(cdl_quantize_bwd, "ppnqpppws", (a.p[0], a.p[1], a.n, &a.q[0], a.p[2], a.p[3], a.p[4], a.ws, a.ws_bytes, a.stream))                \
     X(cdl_marginal_entropy, "pnqppws", (a.p[0], a.n, &a.q[0], a.p[1], a.p[2], a.ws, a.ws_bytes, a.stream))                              \
     X(cdl_quantize_draw, "ppnqps", (a.p[0], a.p[1], a.n, &a.q[0], a.p[2], a.stream))                                                    \
-    X(cdl_entropy_bwd, "pppnqfpppws", (a.p[0], a.p[1], a.p[2], a.n, &a.q[0], a.f[0], a.p[3], a.p[4], a.p[5], a.ws, a.ws_bytes, a.stream)) \
+    X(cdl_entropy_bwd, "pppnqrpppws", (a.p[0], a.p[1], a.p[2], a.n, &a.q[0], a.f[0], a.p[3], a.p[4], a.p[5], a.ws, a.ws_bytes, a.stream)) \
     X(cdl_huffman_bits, "pniipppws", (a.p[0], a.n, a.i[0], a.i[1], a.p[1], a.p[2], a.p[3], a.ws, a.ws_bytes, a.stream))                 \
-    X(cdl_qgemm_fwd_offset, "ppiiiffiippws",                                                                                            \
+    X(cdl_qgemm_fwd_offset, "ppiiiffooppws",                                                                                            \
       (a.p[0], a.p[1], a.i[0], a.i[1], a.i[2], a.f[0], a.f[1], a.i[3], a.i[4], a.p[2], a.p[3], a.ws, a.ws_bytes, a.stream))             \
-    X(cdl_qgemm_bwd_offset, "pppiiiffiippws",                                                                                           \
+    X(cdl_qgemm_bwd_offset, "pppiiiffooppws",                                                                                           \
       (a.p[0], a.p[1], a.p[2], a.i[0], a.i[1], a.i[2], a.f[0], a.f[1], a.i[3], a.i[4], a.p[3], a.p[4], a.ws, a.ws_bytes, a.stream))     \
     X(cdl_qgemm_fwd_quantize, "pqpiiifps", (a.p[0], &a.q[0], a.p[1], a.i[0], a.i[1], a.i[2], a.f[0], a.p[2], a.stream))                 \
-    X(cdl_qconv_fwd, "ppiiiiiiiiiffippws",                                                                                              \
+    X(cdl_qconv_fwd, "ppiiiiiiiiiffoppws",                                                                                              \
       (a.p[0], a.p[1], a.i[0], a.i[1], a.i[2], a.i[3], a.i[4], a.i[5], a.i[6], a.i[7], a.i[8], a.f[0], a.f[1], a.i[9], a.p[2], a.p[3],  \
        a.ws, a.ws_bytes, a.stream))                                                                                                     \
-    X(cdl_qconv_bwd_weights, "ppiiiiiiiiifipws",                                                                                        \
+    X(cdl_qconv_bwd_weights, "ppiiiiiiiiifopws",                                                                                        \
       (a.p[0], a.p[1], a.i[0], a.i[1], a.i[2], a.i[3], a.i[4], a.i[5], a.i[6], a.i[7], a.i[8], a.f[0], a.i[9], a.p[2], a.ws,            \
        a.ws_bytes, a.stream))                                                                                                           \
     X(cdl_qconv_bwd_activations, "ppiiiiiiiiifpws",                                                                                     \
       (a.p[0], a.p[1], a.i[0], a.i[1], a.i[2], a.i[3], a.i[4], a.i[5], a.i[6], a.i[7], a.i[8], a.f[0], a.p[2], a.ws, a.ws_bytes,        \
        a.stream))                                                                                                                       \
     /* the last integer: whether the weight quantizer is given */                                                                       \
-    X(cdl_qgemm_bwd_quantize_bwd, "pppiiipqfipppppiqpppws",                                                                             \
+    X(cdl_qgemm_bwd_quantize_bwd, "pppiiipqfopppppiqpppws",                                                                             \
       (a.p[0], a.p[1], a.p[2], a.i[0], a.i[1], a.i[2], a.p[3], &a.q[0], a.f[0], a.i[3], a.p[4], a.p[5], a.p[6], a.p[7], a.p[8],         \
        a.i[4] ? &a.q[1] : NULL, a.p[9], a.p[10], a.p[11], a.ws, a.ws_bytes, a.stream))
 

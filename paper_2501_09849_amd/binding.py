@@ -57,6 +57,21 @@ def lib_path() -> str:
     return _LIB_PATH
 
 
+def _stream_queries():
+    """Functions for the current device and for the address of a device's current stream.  torch's own internal ones where it has
+    them, else the public ones (which make a Stream object per call)."""
+    try:
+        import torch
+    except ImportError:       # addresses and streams are given as integers then
+        def missing(*_):
+            raise RuntimeError("torch is not importable: pass the stream explicitly")
+        return missing, missing
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return (lambda d: torch.cuda.current_stream(d).cuda_stream), torch.cuda.current_device
+    return raw, device
+
+
 def load():
     """Load libcdl.so (built beforehand by paper_2501_09849_amd.build / __graft_entry__.build)."""
     global _LIB, _CALLS
@@ -72,12 +87,7 @@ def load():
         # PyTorch-ROCm carries its own copy of the HIP runtime and loads it by path.  If libcdl.so came first,
         # the system's copy would be in the process as well, the two would not share a device context, and
         # every launch on torch's memory would fail with hipErrorNoDevice: let torch's be the first one.
-        stream_of, device = None, None
-        try:
-            import torch
-            stream_of, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-        except (ImportError, AttributeError):
-            pass
+        stream_of, device = _stream_queries()      # (imports torch)
         L = ctypes.CDLL(_LIB_PATH)
         vp, i64, i32, f32, sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_size_t
         qp = ctypes.POINTER(QParams)

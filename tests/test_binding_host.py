@@ -50,3 +50,26 @@ def test_quantizers_and_offsets_are_converted_as_int_and_float_do(cdl):
     assert _status(cdl, cdl.cdl_entropy_bwd, FAKE, FAKE, -1, -7, 15, 0.02, 1e4, scale="0.5", dtheta=FAKE) == -2
     with pytest.raises(TypeError):       # a step of a product is a number
         cdl.cdl_qgemm_fwd(FAKE, FAKE, -1, 16, 16, "1.0", 1.0, None, FAKE, stream=0)
+
+
+def test_current_stream_without_the_internal_queries_of_torch(cdl, monkeypatch):
+    """The address of the current stream comes from torch's public functions where the internal ones are missing."""
+    import types
+    from paper_2501_09849_amd import _marshal, binding
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d=None: types.SimpleNamespace(cuda_stream=0x1000 + d))
+    stream_of, device = binding._stream_queries()
+    assert device() == 3 and stream_of(device()) == 0x1003
+    lib = cdl.load()
+    import ctypes
+    table = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in binding._MARSHALLED}
+    _marshal.init(table, stream_of, device)
+    try:
+        with pytest.raises(cdl.CdlError) as e:      # (reaches the library: no stream given)
+            cdl.cdl_quantize_draw(FAKE, FAKE, -1, -7, 15, 0.02, 1e4, FAKE)
+        assert e.value.status == -2
+    finally:
+        monkeypatch.undo()
+        _marshal.init(table, *binding._stream_queries())

@@ -12,7 +12,9 @@ _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libcdl.so")
 MARSHAL_SOURCE = os.path.join(CSRC, "marshal.c")
-MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
+# (with the interpreter's tag, e.g. _marshal.cpython-310-x86_64-linux-gnu.so: another Python does not load it)
+MARSHAL_SUFFIX = sysconfig.get_config_var("EXT_SUFFIX")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal" + MARSHAL_SUFFIX)
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -37,10 +39,11 @@ def _deps():
 
 
 def source_hash() -> str:
-    """sha256 over the compiler flags and every source and header the library is built from (contents, not
-    time stamps: a copy of the tree to another machine keeps it)."""
+    """sha256 over the compiler flags, the interpreter's tag and every source and header the library is built from (contents,
+    not time stamps: a copy of the tree to another machine keeps it)."""
     h = hashlib.sha256()
     h.update(" ".join(HIPCC_FLAGS).encode())
+    h.update(MARSHAL_SUFFIX.encode())
     for path in _deps():
         h.update(os.path.basename(path).encode())
         with open(path, "rb") as f:
@@ -65,6 +68,9 @@ def build_marshal(path: str = MARSHAL_PATH) -> str:
     if res.returncode != 0:
         raise RuntimeError("compiling marshal.c failed:\n" + res.stdout)
     os.replace(tmp, path)
+    untagged = os.path.join(_HERE, "_marshal.so")       # of a tree built before the tag: any Python would load it
+    if os.path.exists(untagged):
+        os.remove(untagged)
     return path
 
 

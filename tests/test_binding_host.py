@@ -73,3 +73,14 @@ def test_current_stream_without_the_internal_queries_of_torch(cdl, monkeypatch):
     finally:
         monkeypatch.undo()
         _marshal.init(table, *binding._stream_queries())
+
+
+def test_native_module_belongs_to_one_interpreter(cdl, monkeypatch):
+    import sysconfig
+    import paper_2501_09849_amd.build as b
+    from paper_2501_09849_amd import _marshal
+    assert os.path.basename(b.MARSHAL_PATH) == "_marshal" + sysconfig.get_config_var("EXT_SUFFIX") != "_marshal.so"
+    assert os.path.samefile(_marshal.__file__, b.MARSHAL_PATH)
+    assert not b.is_stale()
+    monkeypatch.setattr(b, "MARSHAL_SUFFIX", ".cpython-399-x86_64-linux-gnu.so")
+    assert b.is_stale()

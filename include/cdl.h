@@ -329,11 +329,14 @@ int cdl_qconv_bwd_weights(const float *g, const int8_t *x_idx, int32_t B, int32_
  *   d_x_hat[b,h,w,c] = delta_w * sum over (p,q,r,s,n) with p*stride + r - pad = h, q*stride + s - pad = w of
  *                      g[b,p,q,n] * w_idx[n,r,s,c],
  * an exact real contraction over (r,s,n) rounded once, as cdl_qgemm_bwd's d_a_hat is (in double where the arithmetic is
- * small): the same limb product, whose fp32 operand is gathered from g tap by tap (a transposed convolution) instead of read row by row.
+ * small): the same limb product, whose operand - the digits of g, made once in the workspace - is gathered tap by tap (a transposed
+ * convolution) instead of read row by row.
  *   g DEVICE fp32[B,P,Q,N], w_idx DEVICE int8[N,R,S,C] (level indices as they are), d_x_hat DEVICE fp32[B,H,W,C]
  * Restrictions: N and C multiples of 4, stride 1 or 2, pad < R and pad < S, R*S*N <= 131071
  * (CDL_ERR_PARAM / CDL_ERR_RANGE otherwise).  Pointers 16-byte aligned.  Scratch:
- * cdl_qconv_bwd_activations_workspace_bytes (a rearranged copy of the weights and small tables).
+ * cdl_qconv_bwd_activations_workspace_bytes: a rearranged copy of the weights and small tables, and, where the limb product serves,
+ * six bytes for every entry of g (N rounded up to a multiple of 16): 308 MB for 256 x 56 x 56 x 64.  Not for 1 x 1 kernels of
+ * stride 1 (as cdl_qgemm_bwd) nor where the arithmetic is small.
  */
 size_t cdl_qconv_bwd_activations_workspace_bytes(int32_t B, int32_t H, int32_t W, int32_t C, int32_t N, int32_t R, int32_t S,
                                                  int32_t stride, int32_t pad);

@@ -2149,11 +2149,16 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     return L;
 }
 
-size_t qconv_bwd_activations_workspace_bytes(int64_t M_out, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride)
+// (a 1 x 1 convolution of stride 1 is a linear layer)
+bool conv_dx_is_linear(int32_t R, int32_t S, int32_t stride) { return R == 1 && S == 1 && stride == 1; }
+
+size_t qconv_bwd_activations_workspace_bytes(int64_t pixels, int64_t M_out, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride)
 {
-    const size_t own = conv_dx_layout(M_out, N, C, R, S, stride).total;
-    // (a 1 x 1 convolution is a linear layer)
-    const size_t linear = R == 1 && S == 1 && stride == 1 ? bwd_layout((int32_t)M_out, N, C).total : 0;
+    const ConvDxLayout L = conv_dx_layout(M_out, N, C, R, S, stride);
+    // the digit planes of g only where they are made: neither the direct product nor a linear layer has them
+    const bool direct = conv_dx_direct_serves(pixels, N, C, R, S, stride), is_linear = conv_dx_is_linear(R, S, stride);
+    const size_t own = direct || is_linear ? L.planes : L.total;
+    const size_t linear = is_linear ? bwd_layout((int32_t)M_out, N, C).total : 0;
     return own > linear ? own : linear;
 }
 
@@ -2203,7 +2208,7 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
         grids[c] = ConvDxGrid{cl[c].oa, cl[c].oc, cl[c].Hc, cl[c].Wc, cl[c].pad_h, cl[c].pad_w, cl[c].Rc, cl[c].Sc, taps.c[c].r0, taps.c[c].s0};
     if (conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride))
         return launch_conv_dx_direct(g, w_idx, grids, n_cls, B, H, W, C, N, R, S, P, Q, stride, delta_w, d_x_hat, stream);
-    if (R == 1 && S == 1 && stride == 1 && pad == 0)
+    if (conv_dx_is_linear(R, S, stride))      // (the padding is smaller than the kernel: none)
         return launch_qgemm_bwd(g, nullptr, w_idx, (int32_t)M_out, N, C, 1.0f, delta_w, 0, 0, d_x_hat, nullptr, ws, stream);
     CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, n_cls * C);
     // (one limb count for all classes: the largest column sum of any of them)

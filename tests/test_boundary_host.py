@@ -230,3 +230,15 @@ def test_a_stale_binary_is_detected_by_content(monkeypatch):
     assert h == b.source_hash()
     monkeypatch.setattr(b, "HIPCC_FLAGS", b.HIPCC_FLAGS + ["-DSOMETHING_ELSE"])
     assert b.source_hash() != h and b.is_stale()
+
+
+def test_activation_gradient_asks_for_digit_planes_only_where_they_are_made(cdl):
+    """Six bytes per entry of g for the limb product; small layers (in double) and 1 x 1 kernels (a linear layer) have no planes."""
+    f = cdl.qconv_bwd_activations_workspace_bytes
+    planes = 6 * 256 * 14 * 14 * 256
+    assert planes < f(256, 14, 14, 256, 256, 3, 3, 1, 1) < planes + 2 * 9 * 256 * 256 + (1 << 20)
+    assert f(128, 32, 32, 16, 16, 3, 3, 1, 1) < 1 << 20        # 131072 x 16 outputs: six bytes each would be 12.6 MB
+    assert f(4096, 32, 32, 16, 16, 3, 3, 1, 1) < 1 << 20       # any number of pixels where a limb tile would be padding
+    assert f(128, 32, 32, 16, 16, 3, 3, 2, 1) < 1 << 20
+    assert f(64, 56, 56, 64, 256, 1, 1, 1, 0) == cdl.qgemm_bwd_workspace_bytes(64 * 56 * 56, 256, 64)
+    assert f(64, 56, 56, 64, 256, 1, 1, 2, 0) > 6 * 64 * 28 * 28 * 256      # stride 2: the limb product

@@ -360,8 +360,9 @@ int cdl_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B, in
  *   d_theta_b fp32[N,K]  = (delta_a * sum_m g[m,n] * level index of a[m,k]) * dQ_d/dtheta(theta_b[n,k])   (required then)
  *   d_delta_b, d_alpha_b  the two scalar gradients of the weight quantizer              (DEVICE fp32[1], nullable)
  *   d_b_hat   may still be requested.
- * Results equal those of the separate calls bit for bit.  Restrictions: M, N, K > 0, K a multiple of 4 and N > 32, else
- * CDL_ERR_PARAM - use the separate calls there.  Scratch: cdl_qgemm_bwd_workspace_bytes(M, N, K).
+ * Results equal those of the separate calls bit for bit.  No output may share memory with theta_a or theta_b, which are read
+ * after the products have been written (CDL_ERR_PARAM); cdl_quantize_bwd itself works in place.  Restrictions: M, N, K > 0, K a
+ * multiple of 4 and N > 32, else CDL_ERR_PARAM - use the separate calls there.  Scratch: cdl_qgemm_bwd_workspace_bytes(M, N, K).
  */
 int cdl_qgemm_bwd_quantize_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,
                                const float *theta_a, const cdl_qparams *p_a, float delta_b, int32_t b_offset,

@@ -103,6 +103,13 @@ int check_qparams(const cdl_qparams *p)
     return CDL_OK;
 }
 
+// whether two tensors of fp32 share memory (null: not there)
+bool overlap(const float *a, int64_t na, const float *b, int64_t nb)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + (uintptr_t)nb * 4 && y < x + (uintptr_t)na * 4;
+}
+
 int check_ws(const void *ws, size_t have, size_t need)
 {
     if (need == 0) return CDL_OK;
@@ -459,6 +466,11 @@ int cdl_qgemm_bwd_quantize_bwd(const float *g, const int8_t *a_idx, const int8_t
         return CDL_ERR_ALIGN;
     rc = check_ws(ws, ws_bytes, qgemm_bwd_workspace_bytes(M, N, K));
     if (rc != CDL_OK) return rc;
+    // the products are written, to d_theta_a and to d_b_hat or d_theta_b, before the quantizers' passes read theta
+    const int64_t na = (int64_t)M * K, nb = (int64_t)N * K;
+    for (const float *out : {d_b_hat, d_theta_b})
+        if (overlap(out, nb, theta_a, na) || overlap(out, nb, theta_b, nb)) return CDL_ERR_PARAM;
+    if (overlap(d_theta_a, na, theta_a, na) || overlap(d_theta_a, na, theta_b, nb)) return CDL_ERR_PARAM;
     return launch_qgemm_bwd_quantize_bwd(g, a_idx, b_idx, M, N, K, index_offset(*p_a), b_offset, delta_b, theta_a, *p_a, d_theta_a, d_delta_a, d_alpha_a,
                                          d_b_hat, weights ? theta_b : nullptr, weights ? p_b : nullptr, weights ? d_theta_b : nullptr, d_delta_b,
                                          d_alpha_b, ws, (hipStream_t)hip_stream);

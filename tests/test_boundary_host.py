@@ -242,3 +242,23 @@ def test_activation_gradient_asks_for_digit_planes_only_where_they_are_made(cdl)
     assert f(128, 32, 32, 16, 16, 3, 3, 2, 1) < 1 << 20
     assert f(64, 56, 56, 64, 256, 1, 1, 1, 0) == cdl.qgemm_bwd_workspace_bytes(64 * 56 * 56, 256, 64)
     assert f(64, 56, 56, 64, 256, 1, 1, 2, 0) > 6 * 64 * 28 * 28 * 256      # stride 2: the limb product
+
+
+def test_combined_backward_call_refuses_outputs_over_its_inputs(cdl):
+    """d_theta_a holds dL/dQ(a) before theta_a is read: in place it would be wrong without a word.  (What is allowed is called
+    without a workspace and ends at that check, so nothing is ever launched.)"""
+    f = cdl.load().cdl_qgemm_bwd_quantize_bwd
+    M, N, K = 128, 64, 256
+    qa, qb = _q(0, 16, 0.25, 64.0), _q(-7, 15, 0.02, 1e4)
+    G, XI, WI, X, W, DX, DW, DWH = (FAKE + (i << 20) for i in range(8))
+
+    def call(x=X, w=W, dx=DX, dw=DW, dwh=DWH):
+        return f(G, XI, WI, M, N, K, x, qa, 0.02, 0, dx, None, None, dwh, w, qb, dw, None, None, *ws, None)
+
+    ws = (None, 0)
+    assert call() == WS and call(dwh=None) == WS and call(dwh=DW) == WS
+    assert call(dx=X + 4 * M * K) == WS and call(dx=X - 4 * M * K) == WS
+    ws = (FAKE + (8 << 20), 1 << 40)
+    assert call(dx=X) == PARAM and call(dx=X + 64) == PARAM and call(dx=X - 4 * M * K + 64) == PARAM
+    assert call(dw=W) == PARAM and call(dw=W, dwh=None) == PARAM and call(dwh=W) == PARAM
+    assert call(dx=W) == PARAM and call(dw=X) == PARAM and call(dwh=X) == PARAM

@@ -367,8 +367,8 @@ __device__ __forceinline__ void direct_store(const DirectProduct &p, const doubl
 struct DirectArgs {
     DirectProduct a, b;            // dL/dQ(a), dL/dQ(b); rows = 0: not asked for
     int blocks_a, blocks_b;
-    // DIAG: the limb rule's inputs, for the diagnostic words
-    BwdPlan *plan;
+    BwdPlan *plan;                 // for the diagnostic words
+    // DIAG: the limb rule's inputs
     unsigned long long *records;   // [gridDim.x][2]
     unsigned long long tag;
     float delta_a, delta_b;
@@ -376,7 +376,7 @@ struct DirectArgs {
 
 // DIAG: leaves in the workspace the limb counts and bounds that the limb products would have had (the documented
 // diagnostic words): every block publishes the largest |g| and the largest column sum of |index| it has seen, the last
-// block takes the maxima.
+// block takes the maxima.  Otherwise: that there are none.
 template <bool DIAG>
 __global__ __launch_bounds__(kDirThreads)
 void bwd_direct_kernel(DirectArgs a)
@@ -392,6 +392,7 @@ void bwd_direct_kernel(DirectArgs a)
     const int row0 = (tr * (kDirWaves / p.ksp) + wave / p.ksp) * 16, col0 = tc * (p.narrow ? 16 : 64);
     const int s0 = split * p.steps_per_split, s1 = min(s0 + p.steps_per_split, (p.kc + 15) / 16);
     Diag dg = {0.0f, {0, 0, 0, 0}};
+    if (!DIAG && blockIdx.x == 0 && threadIdx.x == 0) no_limbs(a.plan);
     auto product = [&](auto &&src, auto tn_c) {
         constexpr int TN = decltype(tn_c)::value;
         const auto same = [](int row) { return (int64_t)row; };
@@ -571,7 +572,7 @@ static double padded_macs(int64_t rows, int64_t kc, int64_t cols) { return (doub
 //   256 x 1000 x 512        45 -> 18      2000 x 300 x 1000 (0.6 G)                      70 ->  67
 //   131072 x 16 x 144, dL/dQ(b) 43 -> 26  1000 x 1000 x 1000 (1 G)                       65 ->  88
 // so up to 0.7 G multiply-adds in whole tiles, both products together.
-// Up to kBwdDirectNoDiag neither product has limbs and the diagnostic words of the workspace stay as they are.
+// Up to kBwdDirectNoDiag the diagnostic words say that neither product has limbs.
 constexpr int64_t kBwdDirectNoDiag = 1ll << 25;
 constexpr double kBwdDirectMaxMacs = 7e8, kConvDwDirectMaxMacs = 5e8, kConvDxDirectMaxMacs = 5e8;
 

@@ -27,6 +27,13 @@ struct BwdPlan {
 // millions of large indices) six are used and the bound, stored in the plan, says what was reached.
 constexpr double kLimbBoundTarget = 9e-7;
 
+// The diagnostic words of a call whose products were formed directly in double (one thread): no limbs, nothing rounded.
+__device__ __forceinline__ void no_limbs(BwdPlan *plan)
+{
+    plan->limbs_da = plan->limbs_db = 0;
+    plan->bound_da = plan->bound_db = 0.0;
+}
+
 // (one thread; amax_bits: the largest |g| as the bits of a float)
 __device__ __forceinline__ void choose_limbs(BwdPlan *plan, unsigned int amax_bits, unsigned int col_abs_a, unsigned int col_abs_b,
                                              float delta_a, float delta_b)

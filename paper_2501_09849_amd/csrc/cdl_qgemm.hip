@@ -1391,10 +1391,11 @@ constexpr int direct_rows(int nn) { return 2048 / nn; }     // rows of g per blo
 template <int NN, int C>
 __global__ __launch_bounds__(256)
 void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_idx, int M, int N, int K,
-                      double delta_b, double b_offset, float *__restrict__ out, int vec_store)
+                      double delta_b, double b_offset, float *__restrict__ out, int vec_store, BwdPlan *plan /* null: another product follows */)
 {
     constexpr int kRows = direct_rows(NN);
     __shared__ double gs[kRows][NN];
+    if (plan && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) no_limbs(plan);
     const int row0 = blockIdx.x * kRows;
     const int rows = min(kRows, M - row0);
     const int groups_total = (K + C - 1) / C;              // groups of C columns
@@ -2315,8 +2316,9 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         const int rows_per = direct_rows(N <= 16 ? 16 : 32);
         const dim3 grid((M + rows_per - 1) / rows_per, (col_groups + 255) / 256);
         const int vec_store = K % 4 == 0 && (reinterpret_cast<uintptr_t>(d_a_hat) & 15) == 0 && (reinterpret_cast<uintptr_t>(b_idx) & 3) == 0;
-        if (N <= 16) CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<16, 4>), grid, dim3(256), 0, gr, b_idx, M, N, K, (double)delta_b, (double)b_offset, d_a_hat, vec_store);
-        else CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<32, 2>), grid, dim3(256), 0, gr, b_idx, M, N, K, (double)delta_b, (double)b_offset, d_a_hat, vec_store);
+        BwdPlan *words = want_db ? nullptr : plan;
+        if (N <= 16) CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<16, 4>), grid, dim3(256), 0, gr, b_idx, M, N, K, (double)delta_b, (double)b_offset, d_a_hat, vec_store, words);
+        else CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<32, 2>), grid, dim3(256), 0, gr, b_idx, M, N, K, (double)delta_b, (double)b_offset, d_a_hat, vec_store, words);
         d_a_hat = nullptr;           // done; what follows is for the other product only
         if (!want_db) return check_launch();
     }

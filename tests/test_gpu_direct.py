@@ -71,3 +71,20 @@ def test_convolution_gradients(oracle, B, H, W, C, N, R, S, stride, pad, x_offse
     r_x, r_w = oracle.qconv_bwd(g, x.astype(np.int16) + x_offset, w, stride, pad, 0.015625, 0.0078125)
     gu.assert_close(dX.cpu().numpy(), r_x, "d_x_hat")
     gu.assert_close(dW.cpu().numpy(), r_w, "d_w_hat")
+
+
+@pytest.mark.parametrize("M,N,K", [(32, 128, 256), (512, 256, 256), (5000, 16, 144), (131072, 16, 144), (20000, 32, 100)])
+@pytest.mark.parametrize("want", ["both", "a", "b"])
+def test_diagnostic_words_of_products_without_limbs(M, N, K, want):
+    """A call that forms its products directly says so in the workspace - no limbs, bounds of zero - whatever lay there before."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    ws = gu.workspace(cdl.qgemm_bwd_workspace_bytes(M, N, K))
+    ws.fill_(0x5a)
+    g = torch.randn((M, N), device="cuda")
+    a, b = torch.randint(0, 16, (M, K), dtype=torch.int8, device="cuda"), torch.randint(-7, 8, (N, K), dtype=torch.int8, device="cuda")
+    da, db = gu.empty((M, K), torch.float32), gu.empty((N, K), torch.float32)
+    cdl.cdl_qgemm_bwd(g, a, b, M, N, K, 0.5, 0.02, da if want != "b" else None, db if want != "a" else None, ws)
+    torch.cuda.synchronize()
+    limbs, bounds = ws[:8].view(torch.int32).tolist(), ws[32:48].view(torch.float64).tolist()
+    assert limbs == [0, 0] and bounds == [0.0, 0.0]

@@ -154,3 +154,62 @@ def test_marginal_pmf_of_equal_entries(levels, kappa):
         assert (np.abs(m - want) <= 6e-8 * want + 1e-12 * want.max() + 64 * 2.0 ** -22 / n).all(), (float(v), np.abs(m - want).max())
         w = want[want > 0]
         assert abs(H.item() + float((w * np.log2(w)).sum())) <= 1.2e-7 * abs(H.item()) + 1e-9
+
+
+@pytest.mark.parametrize("levels,lo,kappa", [(34, -17, 0.3), (63, -31, 0.05), (127, -63, 0.9), (255, -127, 0.01), (256, 0, 0.05)])
+def test_gradient_of_wide_sets_entry_by_entry(levels, lo, kappa):
+    """dtheta of sets above 33 levels against the variance of each entry, not the largest one; inside the set and a little beyond it.
+    The weights are fp32: base-2 exponents down to -28 and their factors carry 2^-24 each, 3 x 28 x 2^-24 = 5e-6 of a weight, and the
+    weights that far down do not count; a beyond entry's variance is one neighbour's weight, whose exponent grows with its distance."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    n = FROM + 5
+    step = np.float64(np.float32(0.03))
+    sharp = np.float64(np.float32(kappa / step ** 2))
+    k, c0, half = sharp * step * step, lo + 0.5 * (levels - 1), 0.5 * (levels - 1)
+    rng = np.random.default_rng(levels)
+    values = ((np.linspace(-half - 1.5, half + 1.5, 3001) + c0) * step).astype(np.float32)
+    theta = values[np.arange(n) % values.size]
+    g = rng.standard_normal(n).astype(np.float32)
+    dth, sc = gu.empty((n,), torch.float32), gu.empty((2,), torch.float32)
+    cdl.cdl_quantize_bwd(gu.dev(theta), gu.dev(g), n, lo, levels, float(step), float(sharp), dth, sc[0:1], sc[1:2],
+                         gu.workspace(cdl.quantize_workspace_bytes(n, levels)))
+    var = _moments(values.astype(np.float64) / step - c0, levels, k)[2]
+    want = g.astype(np.float64) * (2 * k * var).astype(np.float64)[np.arange(n) % values.size]
+    got = dth.cpu().numpy()
+    worst = (np.abs(got - want) / np.abs(want)).max()
+    assert worst <= 1e-5, worst
+
+
+@pytest.mark.parametrize("n,levels,kappa", [((3 << 23) // 15 + 1, 31, 0.0077), ((3 << 23) // 3 + 2, 7, 0.8), (5000, 31, 0.0077), (300_003, 15, 0.3)])
+def test_scalar_sums_with_infinite_entries(n, levels, kappa):
+    """An infinite entry sits on the outermost level: it adds g times that level to the step's sum, nothing to the sharpness's sum, and
+    nothing of it is NaN - with the table and with the loop over the levels."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    lo = -(levels // 2)
+    step = np.float64(np.float32(0.03))
+    sharp = np.float64(np.float32(kappa / step ** 2))
+    k, c0, half = sharp * step * step, lo + 0.5 * (levels - 1), 0.5 * (levels - 1)
+    rng = np.random.default_rng(n)
+    values = ((rng.standard_normal(997) * 0.4 * half + c0) * step).astype(np.float32)
+    values[[3, 500, 996]] = np.inf
+    values[[7, 501]] = -np.inf
+    place = np.arange(n) % values.size
+    g = rng.standard_normal(n).astype(np.float32)
+    g_sum, g_abs = np.bincount(place, g.astype(np.float64)), np.bincount(place, np.abs(g.astype(np.float64)))
+    dth, sc = gu.empty((n,), torch.float32), gu.empty((2,), torch.float32)
+    cdl.cdl_quantize_bwd(gu.dev(values[place]), gu.dev(g), n, lo, levels, float(step), float(sharp), dth, sc[0:1], sc[1:2],
+                         gu.workspace(cdl.quantize_workspace_bytes(n, levels)))
+    fin = np.isfinite(values)
+    r = np.where(fin, values, 0.0).astype(np.float64) / step - c0
+    _, mu, var, c3 = _moments(r, levels, k)
+    t_d = np.where(fin, (c0 + mu) + 2 * k * ((r - c0 - 2 * mu) * var - c3), c0 + np.sign(values) * half)
+    t_a = np.where(fin, 2 * (r - mu) * var - c3, 0.0)
+    size_d = np.where(fin, np.abs(c0 + mu) + 2 * k * (np.abs(r - c0 - 2 * mu) * var + np.abs(c3)), half)
+    size_a = np.where(fin, 2 * np.abs(r - mu) * var + np.abs(c3), half ** 3)
+    dd, da = sc.cpu().numpy().astype(np.float64)
+    # the entry is held where its CPMF is one level to e^-30 / kappa
+    assert abs(dd - (g_sum * t_d).sum()) <= 6e-8 * abs(dd) + 1e-11 * (g_abs * size_d).sum()
+    assert abs(da - step ** 3 * (g_sum * t_a).sum()) <= 6e-8 * abs(da) + step ** 3 * 1e-10 * (g_abs * size_a).sum()
+    assert np.array_equal(np.abs(dth.cpu().numpy()[:values.size][~fin]) <= 1e-9 * np.abs(g[:values.size][~fin]), np.ones((~fin).sum(), bool))

@@ -112,3 +112,133 @@ def test_step_replayed_from_a_graph_matches_eager_every_time():
         torch.cuda.synchronize()
         graph.replay()
         same(layer.results(), want)
+
+
+def _replayed(run, outputs, refresh, replays=4):
+    """Captures run(), and for each replay - fresh inputs, junk in the outputs, eager work in between - compares every output with what
+    the eager call gives."""
+    torch = gu.torch_mod()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        run()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+
+    def junk():
+        for t in outputs:
+            t.fill_(float("nan") if t.dtype.is_floating_point else 77)
+    for rep in range(replays):
+        if rep != 1:
+            refresh(rep)
+        junk()
+        run()
+        torch.cuda.synchronize()
+        want = [t.clone() for t in outputs]
+        junk()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for i, (t, w) in enumerate(zip(outputs, want)):
+            assert torch.equal(t, w), (rep, i)
+
+
+@pytest.mark.parametrize("n,levels,kappa", [((5 << 23) // 15 + 3, 31, 0.008), ((5 << 23) // 7 + 1, 15, 0.5), (70_001, 63, 0.05), (300_000, 255, 0.02),
+                                            (40_001, 31, 0.008), (900_000, 31, 0.008)])
+def test_soft_regime_replayed_from_a_graph(n, levels, kappa):
+    """The table, its moments and the sums of the scalar gradients: kernels of cdl_soft.hip on both sides of the sizes that they serve."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    spec = (-(levels // 2), levels, 0.01, kappa / 0.01 ** 2)
+    theta, g = gu.empty(n, torch.float32), gu.empty(n, torch.float32)
+    idx, soft, dth = gu.empty(n, torch.int8), gu.empty(n, torch.float32), gu.empty(n, torch.float32)
+    marg, only, sc = gu.empty(levels, torch.float32), gu.empty(levels, torch.float32), gu.empty(8, torch.float32)
+    ws = gu.workspace(cdl.quantize_workspace_bytes(n, levels))
+
+    def run():
+        cdl.cdl_quantize_fwd(theta, n, *spec, idx, soft, marg, sc[0:1], ws)
+        cdl.cdl_quantize_bwd(theta, g, n, *spec, dth, sc[1:2], sc[2:3], ws)
+        cdl.cdl_marginal_entropy(theta, n, *spec, only, sc[3:4], ws)
+        sc[4:].zero_()
+
+    def refresh(rep):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(rep)
+        theta.copy_(torch.randn(n, device="cuda", generator=gen) * (0.002 * levels * (1 + rep)))
+        g.copy_(torch.randn(n, device="cuda", generator=gen))
+    refresh(9)
+    _replayed(run, [idx, soft, marg, dth, only, sc], refresh)
+
+
+@pytest.mark.parametrize("n,levels", [(3000, 15), (200_000, 255), (2_359_296, 255)])
+def test_huffman_size_replayed_from_a_graph(n, levels):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    idx = gu.empty(n, torch.int8)
+    counts, bits, rate = gu.empty(levels, torch.int64), gu.empty(1, torch.int64), gu.empty(1, torch.float32)
+    ws = gu.workspace(cdl.huffman_workspace_bytes(n))
+
+    def refresh(rep):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(rep)
+        half = levels // 2
+        idx.copy_((torch.randn(n, device="cuda", generator=gen) * half / (2 + rep)).clamp(-half, half).to(torch.int8))
+    refresh(9)
+    _replayed(lambda: cdl.cdl_huffman_bits(idx, n, -(levels // 2), levels, counts, bits, rate, ws), [counts, bits, rate], refresh)
+
+
+# limb products with the plan made at the end of the transpositions, one and several pieces of the contraction; direct products whose
+# last block fills the diagnostic words; direct products of a few outputs each
+@pytest.mark.parametrize("M,N,K", [(2048, 640, 1024), (60000, 96, 144), (256, 1000, 512), (32, 128, 256), (131072, 16, 144)])
+@pytest.mark.parametrize("offset", [0, 128])
+def test_backward_products_replayed_from_a_graph(M, N, K, offset):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    g = gu.empty((M, N), torch.float32)
+    a, b = gu.empty((M, K), torch.int8), gu.empty((N, K), torch.int8)
+    da, db = gu.empty((M, K), torch.float32), gu.empty((N, K), torch.float32)
+    ws = gu.workspace(cdl.qgemm_bwd_workspace_bytes(M, N, K))
+    words = gu.empty(2, torch.int32)
+
+    def run():
+        cdl.cdl_qgemm_bwd_offset(g, a, b, M, N, K, 0.25, 0.02, offset, 0, da, db, ws)
+        words.copy_(ws[:8].view(torch.int32))
+
+    def refresh(rep):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(rep)
+        g.copy_(torch.randn((M, N), device="cuda", generator=gen) * 10.0 ** (rep % 5))
+        a.copy_(torch.randint(-128, 128, (M, K), device="cuda", generator=gen))
+        b.copy_(torch.randint(-7, 8, (N, K), device="cuda", generator=gen))
+    refresh(9)
+    _replayed(run, [da, db, words], refresh)
+
+
+# digit planes at stride 1 and 2, the direct product, a linear layer
+@pytest.mark.parametrize("B,H,W,C,N,R,stride", [(16, 14, 14, 256, 256, 3, 1), (16, 28, 29, 64, 128, 3, 2), (32, 32, 32, 16, 16, 3, 1), (16, 28, 28, 128, 64, 1, 1)])
+def test_convolution_gradients_replayed_from_a_graph(B, H, W, C, N, R, stride):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    pad = R // 2
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    geom = (B, H, W, C, N, R, R, stride, pad)
+    g, x, w = gu.empty((B, P, Q, N), torch.float32), gu.empty((B, H, W, C), torch.int8), gu.empty((N, R, R, C), torch.int8)
+    y, dx, dw = gu.empty((B, P, Q, N), torch.float32), gu.empty((B, H, W, C), torch.float32), gu.empty((N, R, R, C), torch.float32)
+    ws = gu.workspace(max(cdl.qconv_fwd_workspace_bytes(N, 0), cdl.qconv_bwd_weights_workspace_bytes(*geom), cdl.qconv_bwd_activations_workspace_bytes(*geom)))
+
+    def run():
+        cdl.cdl_qconv_fwd(x, w, *geom, 0.25, 0.02, None, y, ws)
+        cdl.cdl_qconv_bwd_weights(g, x, *geom, 0.25, dw, ws)
+        cdl.cdl_qconv_bwd_activations(g, w, *geom, 0.02, dx, ws)
+
+    def refresh(rep):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(rep)
+        g.copy_(torch.randn(g.shape, device="cuda", generator=gen) * 10.0 ** (rep % 5))
+        x.copy_(torch.randint(0, 16, x.shape, device="cuda", generator=gen))
+        w.copy_(torch.randint(-7, 8, w.shape, device="cuda", generator=gen))
+    refresh(9)
+    _replayed(run, [y, dx, dw], refresh)

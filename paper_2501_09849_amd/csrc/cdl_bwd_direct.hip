@@ -12,6 +12,7 @@
 #include "cdl_internal.h"
 #include "cdl_finish.h"
 #include "cdl_bwd_plan.h"
+#include "cdl_div.h"
 
 #include <type_traits>
 
@@ -23,18 +24,6 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 typedef uint32_t u32_any __attribute__((aligned(1)));
 
 constexpr int kDirThreads = 512, kDirWaves = 8;
-
-// n / d for 0 <= n < 2^31 by one multiplication: mul = ceil(2^(31 + s) / d) with s = ceil(log2 d), sh = s - 1 (-1 for d = 1);
-// the excess mul * d - 2^(31 + s) is below 2^s, so it adds less than one unit of the quotient
-struct DivBy { uint32_t mul; int sh; };
-DivBy div_by(uint32_t d)
-{
-    if (d <= 1) return DivBy{0u, -1};
-    int s = 0;
-    while ((1ull << s) < d) ++s;
-    return DivBy{(uint32_t)(((1ull << (31 + s)) + d - 1) / d), s - 1};
-}
-__device__ __forceinline__ int quotient(int n, DivBy d) { return d.sh < 0 ? n : (int)(__umulhi((uint32_t)n, d.mul) >> d.sh); }
 
 // A convolution's part of a product.
 //   windows (weight gradient): contraction entry m is output pixel (b, p, q), column k entry (tap row, tap column, channel) of
@@ -183,7 +172,7 @@ struct ColumnsOfGWindows : ColumnsOfG {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int m = WHOLE ? e + j : min(e + j, p.kc - 1);
-            const int bb = quotient(m, cv->by_pq), rem = m - bb * (cv->P * cv->Q), pp = quotient(rem, cv->by_q), qq = rem - pp * cv->Q;
+            const int bb = div_by(m, cv->by_pq), rem = m - bb * (cv->P * cv->Q), pp = div_by(rem, cv->by_q), qq = rem - pp * cv->Q;
             const int h = pp * cv->stride, w = qq * cv->stride;
             const bool in = (unsigned)(h + tr) < (unsigned)cv->H && (unsigned)(w + ts) < (unsigned)cv->W;
             ok |= in ? 1 << j : 0;
@@ -206,8 +195,8 @@ struct GatheredG {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = min(row0 + 16 * i + (lane & 15), p.rows - 1);
-            const int bb = quotient(m, cv->by_ghw), rem = m - bb * (cv->gh * cv->gw);
-            gi[i] = quotient(rem, cv->by_gw);
+            const int bb = div_by(m, cv->by_ghw), rem = m - bb * (cv->gh * cv->gw);
+            gi[i] = div_by(rem, cv->by_gw);
             gj[i] = rem - gi[i] * cv->gw;
             base[i] = bb * cv->P * cv->Q;
         }
@@ -218,7 +207,7 @@ struct GatheredG {
     __device__ __forceinline__ void load(const DirectProduct &p, int e, float (&a)[TM][4], uint32_t (&b)[4], int &ok) const
     {
         const int k = WHOLE ? e : min(e, p.kc - 4);                     // (gn a multiple of 4: four entries share a tap)
-        const int t = quotient(k, cv->by_gn), n = k - t * cv->gn, r = quotient(t, cv->by_st), s = t - r * cv->st;
+        const int t = div_by(k, cv->by_gn), n = k - t * cv->gn, r = div_by(t, cv->by_st), s = t - r * cv->st;
         const int dh = cv->ph - r, dw = cv->pw - s;
         ok = 0;
 #pragma unroll
@@ -508,7 +497,7 @@ void conv_dx_direct_kernel(ConvDxArgs a)
     const int row0 = (tr * (kDirWaves / p.ksp) + wave / p.ksp) * 16 * TM, col0 = tc * 16 * TN;
     Diag dg = {0.0f, {0, 0, 0, 0}};
     const auto scattered = [&](int m) {
-        const int bb = quotient(m, cv.by_ghw), rem = m - bb * (cv.gh * cv.gw), i = quotient(rem, cv.by_gw), j = rem - i * cv.gw;
+        const int bb = div_by(m, cv.by_ghw), rem = m - bb * (cv.gh * cv.gw), i = div_by(rem, cv.by_gw), j = rem - i * cv.gw;
         return ((int64_t)bb * cv.H + cv.step * i + cv.oa) * cv.W + cv.step * j + cv.oc;
     };
     GatheredG src;
@@ -638,8 +627,8 @@ int launch_conv_dw_direct(const float *g, const int8_t *x_idx, const ConvWindows
     ConvPart cv{};
     cv.H = w.H; cv.W = w.W; cv.C = w.C; cv.S = w.S; cv.stride = w.stride; cv.pad = w.pad; cv.P = w.P; cv.Q = w.Q;
     cv.pad_byte = (int)(uint8_t)(int8_t)(-x_offset);
-    cv.by_pq = div_by((uint32_t)(w.P * w.Q));
-    cv.by_q = div_by((uint32_t)w.Q);
+    cv.by_pq = make_div_by((uint32_t)(w.P * w.Q));
+    cv.by_q = make_div_by((uint32_t)w.Q);
     CDL_LAUNCH("conv_dw_direct_kernel", stream, conv_dw_direct_kernel, dim3((unsigned)(p.tiles_r * p.tiles_c * p.splits)), dim3(kDirThreads), 0, p, cv);
     int rc = check_launch();
     if (rc == CDL_OK && p.splits > 1) {
@@ -679,8 +668,8 @@ int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid 
         cv.H = H; cv.W = W; cv.C = C; cv.S = S; cv.P = P; cv.Q = Q;
         cv.gh = k.Hc; cv.gw = k.Wc; cv.gn = N; cv.st = k.Sc; cv.ph = k.pad_h; cv.pw = k.pad_w;
         cv.step = stride; cv.oa = k.oa; cv.oc = k.oc; cv.r0 = k.r0; cv.s0 = k.s0;
-        cv.by_ghw = div_by((uint32_t)(k.Hc * k.Wc)); cv.by_gw = div_by((uint32_t)k.Wc);
-        cv.by_gn = div_by((uint32_t)N); cv.by_st = div_by((uint32_t)k.Sc);
+        cv.by_ghw = make_div_by((uint32_t)(k.Hc * k.Wc)); cv.by_gw = make_div_by((uint32_t)k.Wc);
+        cv.by_gn = make_div_by((uint32_t)N); cv.by_st = make_div_by((uint32_t)k.Sc);
         cv.taps_c = R * S * C;
         a.first[c] = blocks;
         blocks += p.tiles_r * p.tiles_c;

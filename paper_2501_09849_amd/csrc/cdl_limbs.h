@@ -1,6 +1,7 @@
-// What the kernels on limbs of the gradient share: digits, direct loads, waits, divisions (not installed).
+// What the kernels on limbs of the gradient share: digits, direct loads, waits (not installed).
 #pragma once
 
+#include "cdl_div.h"
 #include "cdl_internal.h"
 
 namespace cdl {
@@ -14,23 +15,6 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; } 
 constexpr int kLgkmcnt0 = 0xc07f;                                                   // s_waitcnt lgkmcnt(0) only
 
 __device__ __forceinline__ uint32_t bperm(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); }
-
-// n / d for 0 <= n < 2^31 by one multiplication: with s = ceil(log2 d) and mul = ceil(2^(31 + s) / d) (below 2^32) the
-// quotient is (n * mul) >> (31 + s), exactly (the excess mul * d - 2^(31 + s) is below d <= 2^s, so it adds less than
-// one unit of the quotient over the whole range of n); sh = s - 1, or -1 for d = 1.
-struct DivBy { uint32_t mul; int sh; };
-inline DivBy make_div_by(uint32_t d)
-{
-    if (d <= 1) return DivBy{0u, -1};
-    int s = 0;
-    while ((1ull << s) < d) ++s;
-    const unsigned long long mul = ((1ull << (31 + s)) + d - 1) / d;
-    return DivBy{(uint32_t)mul, s - 1};
-}
-__device__ __forceinline__ int div_by(int n, uint32_t mul, int sh)
-{
-    return sh < 0 ? n : (int)(__umulhi((uint32_t)n, mul) >> sh);
-}
 
 // Digits of four values: out[l] holds digit l (a signed byte, l = 0 least significant) of g[0..3] in
 // its bytes 0..3.  x = g * gscale is exact (gscale is a power of two) and |x| < 0.99 * 2^(8L-1);

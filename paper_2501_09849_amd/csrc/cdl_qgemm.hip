@@ -1881,7 +1881,6 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
     L.scalars = off; off += kQuantScalarBytes;     // the quantizers' backward passes that follow in the same call
     L.bt = off;      off += align_up((size_t)K * (size_t)L.ldn, 256);           // b_idx^T: [K][ldn]
     L.at = off;      off += align_up((size_t)K * (size_t)L.ldm, 256);           // a_idx^T: [K][ldm]
-    // (one split: used only when a reduction kernel with the quantizer's backward pass follows)
     L.partial = off; off += align_up((size_t)(L.splits > L.direct_splits ? L.splits : L.direct_splits) * (size_t)N * (size_t)K * sizeof(double), 256);
     // operands stored with an offset: one correction per output row of either product, and the per-block column sums of g
     L.corr_da = off; off += align_up((size_t)M * sizeof(double), 256);
@@ -2101,7 +2100,6 @@ int launch_qgemm_quantize_fwd(const float *x, const cdl_qparams &p, const int8_t
     return check_launch();
 }
 
-// workspace of the activation gradient of a convolution: [plan][per-block max|g|][col sums][Wr]
 // address of conv_zero_page on the current device (taken once per device)
 static int conv_zero_page_ptr(const int8_t **ptr)
 {

@@ -46,8 +46,11 @@ __device__ __forceinline__ v4i tail_chunk(const int8_t *row, int k0, int K)
     return u.v;
 }
 
-// TM x TN: 32 x 32 MFMA tiles of a block, KS: waves of a block, OFF: operands stored with an offset.
-template <int TM, int TN, int KS, bool OFF>
+// 32 x 32 MFMA tiles of a block, and its waves
+constexpr int TM = 1, TN = 1, KS = 4;
+
+// OFF: operands stored with an offset.
+template <bool OFF>
 __global__ __launch_bounds__(64 * KS)
 void qgemm_small_kernel(SmallArgs a)
 {
@@ -163,14 +166,13 @@ void qgemm_small_kernel(SmallArgs a)
     }
 }
 
-template <int TM, int TN, int KS>
 int launch_tiles(SmallArgs a, hipStream_t stream)
 {
     a.tiles_m = (a.M + 32 * TM - 1) / (32 * TM);
     a.tiles_n = (a.N + 32 * TN - 1) / (32 * TN);
     const int64_t grid = ((int64_t)a.tiles_m * a.tiles_n + 7) / 8 * 8;
-    if (a.oa || a.ob) CDL_LAUNCH("qgemm_kernel(fwd)", stream, (qgemm_small_kernel<TM, TN, KS, true>), dim3((unsigned)grid), dim3(64 * KS), 0, a);
-    else CDL_LAUNCH("qgemm_kernel(fwd)", stream, (qgemm_small_kernel<TM, TN, KS, false>), dim3((unsigned)grid), dim3(64 * KS), 0, a);
+    if (a.oa || a.ob) CDL_LAUNCH("qgemm_kernel(fwd)", stream, qgemm_small_kernel<true>, dim3((unsigned)grid), dim3(64 * KS), 0, a);
+    else CDL_LAUNCH("qgemm_kernel(fwd)", stream, qgemm_small_kernel<false>, dim3((unsigned)grid), dim3(64 * KS), 0, a);
     return check_launch();
 }
 
@@ -197,7 +199,7 @@ int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int3
     a.acc_out = acc; a.y_out = y;
     a.scale = scale;
     a.oa = a_offset; a.ob = b_offset;
-    return launch_tiles<1, 1, 4>(a, stream);
+    return launch_tiles(a, stream);
 }
 
 }  // namespace cdl

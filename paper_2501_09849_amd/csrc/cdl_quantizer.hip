@@ -853,7 +853,7 @@ int launch_scalar_end(const ScalarFinish &f, int grid, hipStream_t stream)
 }
 
 template <int W>
-void launch_fwd_w(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
+void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
                   const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
                   const MargFinish &fin)
 {
@@ -872,14 +872,6 @@ void launch_fwd_w(bool want_idx, bool want_soft, bool want_marg, int grid, hipSt
     else if (few) CDL_FWD(false, false, 2);
     else CDL_FWD(false, false, 1);
 #undef CDL_FWD
-}
-
-template <int W>
-void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
-                const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
-                const MargFinish &fin)
-{
-    launch_fwd_w<W>(want_idx, want_soft, want_marg, grid, s, theta, n, k, idx, soft, fin);
 }
 
 // The soft-regime kernels on a common centre serve: the full CPMF, 6 to 33 levels (smaller sets always fall to

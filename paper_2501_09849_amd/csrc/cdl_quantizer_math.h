@@ -1,5 +1,4 @@
-// Device-side arithmetic of the probabilistic quantizer shared by the quantizer kernels and by the backward
-// product that applies the quantizer's backward pass in its epilogue (not installed).
+// Device-side arithmetic of the probabilistic quantizer (not installed).
 //
 // The conditional PMF of one entry theta over the levels i*delta is softmax_i(-alpha (theta - i delta)^2)
 // (eq. CPMF, Sec. III-A).  With c a level next to theta, u = theta - c*delta and kappa = alpha*delta^2, the weight

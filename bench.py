@@ -115,13 +115,13 @@ class Step:
         cdl.cdl_quantize_fwd(self.X, self.nX, *xa, self.Xi, self.Xsoft, self.margX, s[1:2], self.ws)
         cdl.cdl_qgemm_fwd(self.Xi, self.Wi, M, N, K, x.delta, w.delta, None, self.Y, self.ws)
         if self.fused == "both":
-            # the whole backward step in one call: neither dL/dQ(X) nor dL/dQ(W) is written
+            # the whole backward step in one call: dL/dQ(X) and dL/dQ(W) need no tensors of their own
             cdl.cdl_qgemm_bwd_quantize_bwd(self.G, self.Xi, self.Wi, M, N, K, self.X, *xa, w.delta, self.dX, s[4:5], s[5:6],
                                            None, self.ws, theta_b=self.W, qparams_b=wa, d_theta_b=self.dW, d_delta_b=s[2:3],
                                            d_alpha_b=s[3:4])
             return
         if self.fused:
-            # the activation-gradient product applies the quantizer's backward pass in its epilogue: dL/dQ(X) is never written
+            # the products and the activations' quantizer in one call: dL/dQ(X) is turned into dL/dX in place
             cdl.cdl_qgemm_bwd_quantize_bwd(self.G, self.Xi, self.Wi, M, N, K, self.X, *xa, w.delta, self.dX, s[4:5], s[5:6],
                                            self.dWh, self.ws)
         else:
@@ -147,8 +147,6 @@ def kernel_model(wl, name, occurrence):
     if name == "quantize_bwd_kernel":
         n = (nX if occurrence == 0 else nW) if wl.has_gemm else nW
         return "hbm", 12.0 * n, n
-    if name == "limb_gemm_kernel(d_a_hat + quantize_bwd)":
-        return "mfma", 2.0 * wl.M * wl.N * wl.K, 0
     if name.startswith("qgemm_kernel") or name.startswith("limb_gemm_kernel"):
         return "mfma", 2.0 * wl.M * wl.N * wl.K, 0
     if name == "absmax_kernel":
@@ -156,8 +154,7 @@ def kernel_model(wl, name, occurrence):
     if name == "da_direct_kernel":
         return "hbm", 4.0 * wl.M * wl.N + 1.0 * wl.N * wl.K + 4.0 * wl.M * wl.K, 0   # reads g and b_idx, writes d_a_hat
     if name == "transpose_i8_kernel":
-        n = wl.N * wl.K if occurrence == 0 else wl.M * wl.K
-        return "hbm", 2.0 * n, 0                    # reads and writes an index matrix
+        return "hbm", 2.0 * (nW + nX), 0            # reads and writes both index matrices
     return None, 0.0, 0
 
 
@@ -729,9 +726,9 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extra", action="store_true")
     ap.add_argument("--fused", nargs="?", const="both", default=None, choices=["activations", "both"],
-                    help="backward step through cdl_qgemm_bwd_quantize_bwd (the quantizer's backward pass applied where the products "
-                         "finish: dL/dQ(X), and with 'both' also dL/dQ(W), never written) instead of cdl_qgemm_bwd followed by "
-                         "cdl_quantize_bwd; measured slower by about 1 %% on workload 5, so the separate calls are the default")
+                    help="backward step through cdl_qgemm_bwd_quantize_bwd (products and quantizers in one call: dL/dQ(X), and with 'both' "
+                         "also dL/dQ(W), turned into the gradients in place) instead of cdl_qgemm_bwd followed by "
+                         "cdl_quantize_bwd; the same time within 1 %% on workload 5, the separate calls are the default")
     ap.add_argument("--step-only", action="store_true",
                     help="time the step and nothing else (for profiler runs): no quantizer-only legs, so `value` is null")
     ap.add_argument("--copy-probe", action="store_true",
@@ -873,7 +870,7 @@ def main():
         torch.cuda.synchronize()
         limbs = st.ws[:8].view(torch.int32).cpu().tolist()
         for r in kernels:
-            which = {"limb_gemm_kernel(d_a_hat)": 0, "limb_gemm_kernel(d_a_hat + quantize_bwd)": 0, "limb_gemm_kernel(d_b_hat)": 1}.get(r["kernel"])
+            which = {"limb_gemm_kernel(d_a_hat)": 0, "limb_gemm_kernel(d_b_hat)": 1}.get(r["kernel"])
             if which is not None and "algorithmic_TOPS" in r:
                 r["limbs"] = limbs[which]
                 r["issued_TOPS"] = r["algorithmic_TOPS"] * limbs[which]
@@ -917,7 +914,7 @@ def main():
                 return (time.perf_counter() - t0) * 1e3 / args.steps
             ms_s, ms_f = eager(None), eager("both")
             # the same step at the paper's initial sharpness alpha = beta = 500 (Sec. V-B) instead of kappa = 4: with
-            # this workload's steps that is the weights of this workload are deep in the soft regime (kappa_w in the line: every level live, the generic loop)
+            # this workload's steps that is the weights of this workload are deep in the soft regime (kappa_w in the line: every level live, the table forward, the generic loop backward)
             import dataclasses
             wl_k4 = st.wl
             st.wl = dataclasses.replace(wl_k4, w_spec=wl_k4.w_spec.with_alpha(cdl_inputs.ALPHA_PAPER),

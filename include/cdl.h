@@ -77,7 +77,11 @@ typedef enum cdl_status {
     CDL_ERR_TOO_LARGE = -7    /* cdl_quantize_fwd_static: the tensor needs more scratch than the built-in buffer holds */
 } cdl_status;
 
-/* Scratch needed by cdl_quantize_fwd / cdl_quantize_bwd / cdl_marginal_entropy for n elements. */
+/*
+ * Scratch needed by cdl_quantize_fwd / cdl_quantize_bwd / cdl_marginal_entropy for n elements: 0.3 - 0.4 MB, from 65536
+ * elements on 0.6 MB growing to 7.2 MB at 2 million (rows of the soft regime's moments, whether or not the parameters of
+ * the call lie in it), more only for the histograms of very large tensors of many levels.
+ */
 size_t cdl_quantize_workspace_bytes(int64_t n, int32_t n_levels);
 
 /* Scratch needed by cdl_qgemm_fwd (staging copies when K is not a multiple of 16). */
@@ -142,7 +146,9 @@ int cdl_quantize_fwd_static(const float *theta, int64_t n, const cdl_qparams *p,
  *   d_alpha   = sum_e g[e] * (2 theta Var - Skew_u)                           (fp32[1], nullable)
  * The last formula is not printed in the paper (Sec. IV-B only notes that it has an analytic form):
  * dQ_d/dalpha = -Cov(Q_p, (theta - Q_p)^2).  At least one output must be non-NULL.
- * The two sums are reproducible: same inputs, same bits.
+ * The two sums are reproducible: same inputs, same bits.  dtheta is too, for calls that ask for the same outputs: in the soft regime
+ * of large tensors a call with a sum evaluates a table in ws and one without sums over the levels, both in double, and one
+ * entry in some ten million rounds to the neighbouring float.  The soft values of cdl_quantize_fwd likewise, with marg or entropy_bits.
  */
 int cdl_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams *p,
                      float *dtheta, float *d_delta, float *d_alpha,

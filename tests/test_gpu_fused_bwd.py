@@ -1,4 +1,4 @@
-"""cdl_qgemm_bwd_quantize_bwd: the activation-gradient product with the quantizer's backward pass in its epilogue.
+"""cdl_qgemm_bwd_quantize_bwd: the backward products and the quantizers' backward passes in one call, in place.
 Its outputs must be those of the two calls it replaces: dL/dtheta entry by entry (the arithmetic is the same, on the same
 fp32 intermediate, so the two GPU paths agree bit for bit), and against the oracle's backward pass fed with that
 intermediate; the scalar gradients at the stated tolerance; d_b_hat unchanged."""

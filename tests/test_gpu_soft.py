@@ -213,3 +213,32 @@ def test_scalar_sums_with_infinite_entries(n, levels, kappa):
     assert abs(dd - (g_sum * t_d).sum()) <= 6e-8 * abs(dd) + 1e-11 * (g_abs * size_d).sum()
     assert abs(da - step ** 3 * (g_sum * t_a).sum()) <= 6e-8 * abs(da) + step ** 3 * 1e-10 * (g_abs * size_a).sum()
     assert np.array_equal(np.abs(dth.cpu().numpy()[:values.size][~fin]) <= 1e-9 * np.abs(g[:values.size][~fin]), np.ones((~fin).sum(), bool))
+
+
+@pytest.mark.parametrize("n,levels,kappa", [((1 << 28) + 6, 31, 0.0077), ((1 << 26) + 4096 * 256 + 1, 255, 0.02)])
+def test_marginal_pmf_of_a_large_tensor(n, levels, kappa):
+    """Beyond 2^26 entries the moments are rounded to fewer bits, so that a block's sums stay inside 64; also the index and the ragged tail."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    lo = -(levels // 2)
+    step = np.float64(np.float32(0.03))
+    sharp = np.float64(np.float32(kappa / step ** 2))
+    k, c0 = sharp * step * step, lo + 0.5 * (levels - 1)
+    rng = np.random.default_rng(levels)
+    values = ((rng.standard_normal(1009) * 0.35 * (levels - 1) / 2 + c0) * step).astype(np.float32)
+    theta = gu.dev(values).repeat(n // values.size + 1)[:n].contiguous()
+    idx, marg, H = gu.empty((n,), torch.int8), gu.empty((levels,), torch.float32), gu.empty((1,), torch.float32)
+    cdl.cdl_quantize_fwd(theta, n, lo, levels, float(step), float(sharp), idx, None, marg, H, gu.workspace(cdl.quantize_workspace_bytes(n, levels)))
+    torch.cuda.synchronize()
+    count = np.full(values.size, n // values.size, np.longdouble)
+    count[: n % values.size] += 1
+    P = _moments(values.astype(np.float64) / step - c0, levels, k)[0]
+    want = (P * count[:, None]).sum(0) / n
+    # (wide sets: interpolation of sixth order)
+    assert (np.abs(marg.cpu().numpy() - want) <= 6e-8 * want + (1e-12 if levels <= 33 else 3e-9) * P.max()).all()
+    w = want[want > 0]
+    assert abs(H.item() + float((w * np.log2(w)).sum())) <= 1.2e-7 * H.item() + (1e-9 if levels <= 33 else 1e-7)
+    r = values.astype(np.float64) / step
+    near = np.clip(np.ceil(r - 0.5), lo, lo + levels - 1).astype(np.int8)
+    last = np.arange(n - 5000, n) % values.size
+    assert np.array_equal(idx[-5000:].cpu().numpy(), near[last])

@@ -4,8 +4,8 @@
 // A histogram of the int8 indices (16 bytes per thread and trip; per-wave LDS histograms with eight interleaved
 // copies of every bin, so that lanes collide only when they share copy and bin), whose rows - one of 256 counts per
 // block - are added up by its last block (few blocks: cdl_finish.h) or by a second kernel of one block.  Either then
-// sorts the counts and runs the two-queue form of Huffman's algorithm: the total code length is the sum of the weights
-// of all merged nodes, which no choice among equal weights can change.
+// sorts the counts and runs the two-queue form of Huffman's algorithm, many nodes at a time: the total code length is
+// the sum of the weights of all merged nodes, which no choice among equal weights can change.
 #include "cdl_internal.h"
 #include "cdl_finish.h"
 
@@ -16,6 +16,7 @@ namespace {
 constexpr int kHistThreads = 256;
 constexpr int kHistCopies = 8;
 constexpr int kHistMaxBlocks = 1024;
+constexpr int kHuffThreads = 1024;
 
 struct HuffmanOut {
     int64_t n;
@@ -25,73 +26,119 @@ struct HuffmanOut {
     float *bits_per_entry;            // [1] or null
 };
 
-constexpr int kQueue = 256 + 4;      // weights of a queue and the empty places that may be looked at behind them
+constexpr int kWave = 64;
+constexpr int kQueue = 256 + kWave;      // weights of a queue and the empty places that a window of 64 may reach behind them
 
-// Sum of the weights of the merged nodes.  leaf: the sorted counts, node: empty; places that hold no weight hold kNone.
-// One step takes the two smallest of the heads L0, L1 of the leaves and M0, M1 of the nodes and appends their sum to
-// the nodes.  What bounds it is one chain of a few dozen instructions per step on one wave (256 levels: 255 steps), so
-// nothing in it branches or waits: the places behind the heads, L2, L3 and M2, M3, are asked for at the end of a step
-// and needed at the end of the next, which hides the latency of LDS (two pops per step, each with reads that the next
-// compare waits for and branches: 54 us for the kernel at 255 levels, this way 28).
+// The value of lane (this lane xor S).
+template <int S>
+__device__ __forceinline__ unsigned int lane_xor(unsigned int v)
+{
+    if (S == 1) return (unsigned int)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true);      // quad_perm(1, 0, 3, 2)
+    if (S == 2) return (unsigned int)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xf, 0xf, true);      // quad_perm(2, 3, 0, 1)
+    if (S == 4) {                                                                                  // 3 (quad_perm), then 7 (half row mirrored)
+        const int q = __builtin_amdgcn_mov_dpp((int)v, 0x1B, 0xf, 0xf, true);
+        return (unsigned int)__builtin_amdgcn_mov_dpp(q, 0x141, 0xf, 0xf, true);
+    }
+    if (S == 8) return (unsigned int)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);     // row rotated by 8 of 16
+    return (unsigned int)__shfl_xor((int)v, S, kWave);
+}
+template <int S>
+__device__ __forceinline__ unsigned long long lane_xor(unsigned long long v)
+{
+    return ((unsigned long long)lane_xor<S>((unsigned int)(v >> 32)) << 32) | lane_xor<S>((unsigned int)v);
+}
+template <int S, typename T>
+__device__ __forceinline__ T compare_exchange(T v, int lane)
+{
+    const T o = lane_xor<S>(v);
+    const T lo = v < o ? v : o, hi = v < o ? o : v;
+    return (lane & S) ? hi : lo;
+}
+__device__ __forceinline__ unsigned int lane_value(unsigned int v, int lane) { return (unsigned int)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ __forceinline__ unsigned long long lane_value(unsigned long long v, int lane)
+{
+    return ((unsigned long long)lane_value((unsigned int)(v >> 32), lane) << 32) | lane_value((unsigned int)v, lane);
+}
+
+// Sum of the weights of the merged nodes.  leaf[first .. 255]: the sorted counts, behind them and all of node: kNone.  One wave.
+// With t the sum of the two smallest weights, no node that is still to be made weighs less than t, so the weights <= t are
+// taken two by two in their order whatever is made meanwhile (equal weights may be exchanged): all these pairs are merged
+// at once, and the new nodes, in order, go behind the old ones, none of which weighs more.  A round takes the smallest 64 of
+// the leaves and nodes that are left: the minimum of the leaves' next 64 with the nodes' next 64 in reverse is that set as a
+// bitonic sequence, six compare-exchange steps sort it.  The smallest weight at least doubles in two rounds, so there are few of them
+// (2.4 M entries on 255 levels, normal: 14 rounds instead of 254 dependent steps; 43 for Fibonacci's numbers, the worst of 32 bits).
+// What bounds it is the chain of a round, about a hundred dependent instructions and a trip through LDS.  The kernel that
+// merges 255 levels: 28 us with a step per node, 8 us so.
 template <typename T>
 __device__ __forceinline__ unsigned long long merge_weights(const T *leaf, T *node, int first)
 {
-    constexpr T kNone = ~(T)0;             // above every weight
-    int zero = 0;
-    asm volatile("" : "+v"(zero));         // (every lane does the same; told so, the compiler would branch on the scalar unit)
-    const T *lp = leaf + first + zero;
-    const T *mp = node + zero;
-    T *tail = node + zero;
-    T L0 = lp[0], L1 = lp[1], L2 = lp[2], L3 = lp[3], M0 = kNone, M1 = kNone, M2 = kNone, M3 = kNone;
-    unsigned long long total = 0ull;
-    for (int step = 255 - first; step > 0; --step) {
-        const bool two_leaves = L1 <= M0, two_nodes = M1 < L0;
-        const T w = (two_nodes ? M1 : L0) + (two_leaves ? L1 : M0);       // (never both)
-        total += (unsigned long long)w;
-        *tail = w;
-        const T l0 = two_nodes ? L0 : L1, l1 = two_nodes ? L1 : L2, m0 = two_leaves ? M0 : M1, m1 = two_leaves ? M1 : M2;
-        L0 = two_leaves ? L2 : l0;
-        L1 = two_leaves ? L3 : l1;
-        M0 = two_nodes ? M2 : m0;
-        M1 = two_nodes ? M3 : m1;
-        lp += two_leaves ? 2 : (two_nodes ? 0 : 1);
-        mp += two_leaves ? 0 : (two_nodes ? 2 : 1);
-        M0 = mp == tail ? w : M0;
-        M1 = mp + 1 == tail ? w : M1;
-        ++tail;
-        L2 = lp[2]; L3 = lp[3];
-        M2 = mp[2]; M3 = mp[3];
+    const int lane = threadIdx.x & (kWave - 1);
+    int left = 256 - first, head = first, node_head = 0, tail = 0;
+    unsigned long long total = 0ull;       // this lane's share
+    while (left > 1) {
+        const T l = leaf[head + lane], m = node[node_head + (kWave - 1 - lane)];
+        T v = l < m ? l : m;
+        v = compare_exchange<32>(v, lane);
+        v = compare_exchange<16>(v, lane);
+        v = compare_exchange<8>(v, lane);
+        v = compare_exchange<4>(v, lane);
+        v = compare_exchange<2>(v, lane);
+        v = compare_exchange<1>(v, lane);
+        const T t = lane_value(v, 0) + lane_value(v, 1);
+        const int pairs = __popcll(__ballot(v <= t)) >> 1;
+        const T sum = v + lane_xor<1>(v);
+        if (lane < 2 * pairs) {
+            total += (unsigned long long)v;
+            if (!(lane & 1)) node[tail + (lane >> 1)] = sum;
+        }
+        // how many of the taken weights were leaves: those below the largest taken one, and of those that equal it the first
+        const T top = lane_value(v, 2 * pairs - 1);
+        const int below = __popcll(__ballot(l < top)), equal = __popcll(__ballot(l == top)), nodes_below = __popcll(__ballot(m < top));
+        const int rest = 2 * pairs - below - nodes_below, leaves = below + (rest < equal ? rest : equal);
+        head += leaves;
+        node_head += 2 * pairs - leaves;
+        tail += pairs;
+        left -= pairs;
+        asm volatile("" ::: "memory");     // the nodes are in LDS before the next windows are read (one wave: in order)
     }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) total += __shfl_xor(total, off, kWave);
     return total;
 }
 
-// All threads of the block (the first 256 of them work): from the count of every byte value, in `key`, to the outputs.
-// Thread t has byte value t, i.e. level (int8)t.  `key` is overwritten.
+// All T threads of the block: from the count of every byte value, in `key`, to the outputs.
+// Thread t < 256 has byte value t, i.e. level (int8)t.  `key` is overwritten.
+template <int T>
 __device__ __forceinline__ void huffman_finish(unsigned long long *key /* [kQueue] */, unsigned long long *sorted /* [kQueue] */, const HuffmanOut &o)
 {
-    const int t = threadIdx.x;
-    unsigned long long c = 0ull;
+    constexpr int kParts = T / 256;      // threads that share a byte value, each compares it with a part of the others
+    __shared__ int ranks[kParts > 1 ? 256 : 1];
+    const int t = threadIdx.x, value = t & 255;
+    const int level = (int)(int8_t)(uint8_t)value;
+    const bool in_set = level >= o.lo && level < o.lo + o.n_levels;
+    const unsigned long long c = in_set ? key[value] : 0ull;
+    if (t < 256 && o.counts && in_set) o.counts[level - o.lo] = c;
+    __syncthreads();
+    const unsigned long long mine = (c << 8) | (unsigned int)value;      // counts made different by their bins
     if (t < 256) {
-        const int level = (int)(int8_t)(uint8_t)t;
-        const bool in_set = level >= o.lo && level < o.lo + o.n_levels;
-        c = in_set ? key[t] : 0ull;
-        if (o.counts && in_set) o.counts[level - o.lo] = c;
+        key[t] = mine;
+        if (kParts > 1) ranks[t] = 0;
     }
     __syncthreads();
-    const unsigned long long mine = (c << 8) | (unsigned int)t;      // counts made different by their bins
-    if (t < 256) key[t] = mine;
-    __syncthreads();
-    // rank of every count among the 256: two counts per 16-byte LDS read that all lanes share, no barriers
-    if (t < 256) {
-        int rank = 0;
-        const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(key);
+    // rank of every count among the 256: two counts per 16-byte LDS read that all lanes share
+    int rank = 0;
+    const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(key) + (t >> 8) * (128 / kParts);
 #pragma unroll 8
-        for (int q = 0; q < 128; ++q) {
-            const ulonglong2 v = pairs[q];
-            rank += (v.x < mine ? 1 : 0) + (v.y < mine ? 1 : 0);
-        }
-        sorted[rank] = c;
+    for (int q = 0; q < 128 / kParts; ++q) {
+        const ulonglong2 v = pairs[q];
+        rank += (v.x < mine ? 1 : 0) + (v.y < mine ? 1 : 0);
     }
+    if (kParts > 1) {
+        atomicAdd(&ranks[value], rank);
+        __syncthreads();
+        rank = ranks[value];
+    }
+    if (t < 256) sorted[rank] = c;
     __syncthreads();
     if (t >= 64) return;
     // the zeros sort to the front
@@ -103,20 +150,22 @@ __device__ __forceinline__ void huffman_finish(unsigned long long *key /* [kQueu
     if (first == 255) {
         total = sorted[255];          // a single level that occurs: one bit per entry
     } else if (first < 255) {
+        constexpr int kTrips = kQueue / kWave;
         if (o.n < (1ll << 31)) {
             unsigned int *leaf32 = reinterpret_cast<unsigned int *>(key), *node32 = leaf32 + kQueue;
 #pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                const int i = 64 * q + t;
-                if (i < kQueue) { leaf32[i] = i < 256 ? (unsigned int)sorted[i] : ~0u; node32[i] = ~0u; }
+            for (int q = 0; q < kTrips; ++q) {
+                const int i = kWave * q + t;
+                leaf32[i] = i < 256 ? (unsigned int)sorted[i] : ~0u;
+                node32[i] = ~0u;
             }
             total = merge_weights<unsigned int>(leaf32, node32, first);
         } else {
 #pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                const int i = 64 * q + t;
-                if (i >= 256 && i < kQueue) sorted[i] = ~0ull;
-                if (i < kQueue) key[i] = ~0ull;
+            for (int q = 0; q < kTrips; ++q) {
+                const int i = kWave * q + t;
+                if (i >= 256) sorted[i] = ~0ull;
+                key[i] = ~0ull;
             }
             total = merge_weights<unsigned long long>(sorted, key, first);
         }
@@ -194,10 +243,10 @@ void index_hist_kernel(const int8_t *__restrict__ idx, int64_t n, unsigned int *
     unsigned long long *key = reinterpret_cast<unsigned long long *>(&hist[0][0]);
     key[threadIdx.x] = total;
     __syncthreads();
-    huffman_finish(key, key + kQueue, out);
+    huffman_finish<kHistThreads>(key, key + kQueue, out);
 }
 
-__global__ __launch_bounds__(1024)
+__global__ __launch_bounds__(kHuffThreads)
 void huffman_kernel(const unsigned int *__restrict__ rows, int nrows, HuffmanOut out)
 {
     __shared__ __attribute__((aligned(16))) unsigned long long key[kQueue];
@@ -233,7 +282,7 @@ void huffman_kernel(const unsigned int *__restrict__ rows, int nrows, HuffmanOut
         key[threadIdx.x] = c;
     }
     __syncthreads();
-    huffman_finish(key, sorted, out);
+    huffman_finish<kHuffThreads>(key, sorted, out);
 }
 
 // Up to this many blocks the histogram's last block finishes the job (all of them: 2 M entries).
@@ -270,7 +319,7 @@ int launch_huffman_bits(const int8_t *idx, int64_t n, int lo, int n_levels, unsi
     unsigned int *rows = reinterpret_cast<unsigned int *>(ws);
     CDL_LAUNCH("index_hist_kernel", stream, index_hist_kernel<false>, dim3(blocks), dim3(kHistThreads), 0, idx, n, rows,
                (unsigned long long *)nullptr, 0ull, out);
-    CDL_LAUNCH("huffman_kernel", stream, huffman_kernel, dim3(1), dim3(1024), 0, rows, blocks, out);
+    CDL_LAUNCH("huffman_kernel", stream, huffman_kernel, dim3(1), dim3(kHuffThreads), 0, rows, blocks, out);
     return check_launch();
 }
 

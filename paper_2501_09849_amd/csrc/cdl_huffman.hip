@@ -106,39 +106,43 @@ __device__ __forceinline__ unsigned long long merge_weights(const T *leaf, T *no
     return total;
 }
 
-// All T threads of the block: from the count of every byte value, in `key`, to the outputs.
-// Thread t < 256 has byte value t, i.e. level (int8)t.  `key` is overwritten.
+// All T threads of the block: from the count of every byte value, in `key`, to the outputs.  `key` is overwritten.
+// Thread t < 256 has level lo + t.  Only the levels of the set are ranked: with all 256 places compared, the sizes of three
+// levels took 1 us longer.
 template <int T>
 __device__ __forceinline__ void huffman_finish(unsigned long long *key /* [kQueue] */, unsigned long long *sorted /* [kQueue] */, const HuffmanOut &o)
 {
-    constexpr int kParts = T / 256;      // threads that share a byte value, each compares it with a part of the others
+    constexpr int kParts = T / 256;      // threads that share a level, each compares it with a part of the others
     __shared__ int ranks[kParts > 1 ? 256 : 1];
-    const int t = threadIdx.x, value = t & 255;
-    const int level = (int)(int8_t)(uint8_t)value;
-    const bool in_set = level >= o.lo && level < o.lo + o.n_levels;
-    const unsigned long long c = in_set ? key[value] : 0ull;
-    if (t < 256 && o.counts && in_set) o.counts[level - o.lo] = c;
+    const int t = threadIdx.x, at = t & 255;
+    const bool in_set = at < o.n_levels;
+    const unsigned long long c = in_set ? key[(uint8_t)(o.lo + at)] : 0ull;
+    if (t < 256 && o.counts && in_set) o.counts[at] = c;
     __syncthreads();
-    const unsigned long long mine = (c << 8) | (unsigned int)value;      // counts made different by their bins
+    const unsigned long long mine = (c << 8) | (unsigned int)at;         // counts made different by their levels
     if (t < 256) {
-        key[t] = mine;
+        key[t] = in_set ? mine : ~0ull;
         if (kParts > 1) ranks[t] = 0;
     }
     __syncthreads();
-    // rank of every count among the 256: two counts per 16-byte LDS read that all lanes share
+    // rank of every count: two counts per 16-byte LDS read that all lanes share
     int rank = 0;
-    const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(key) + (t >> 8) * (128 / kParts);
+    const ulonglong2 *pairs = reinterpret_cast<const ulonglong2 *>(key);
+    const int n_pairs = (o.n_levels + 1) >> 1;
 #pragma unroll 8
-    for (int q = 0; q < 128 / kParts; ++q) {
+    for (int q = t >> 8; q < n_pairs; q += kParts) {
         const ulonglong2 v = pairs[q];
         rank += (v.x < mine ? 1 : 0) + (v.y < mine ? 1 : 0);
     }
     if (kParts > 1) {
-        atomicAdd(&ranks[value], rank);
+        atomicAdd(&ranks[at], rank);
         __syncthreads();
-        rank = ranks[value];
+        rank = ranks[at];
     }
-    if (t < 256) sorted[rank] = c;
+    if (t < 256) {
+        if (in_set) sorted[256 - o.n_levels + rank] = c;
+        else sorted[at - o.n_levels] = 0ull;
+    }
     __syncthreads();
     if (t >= 64) return;
     // the zeros sort to the front

@@ -255,8 +255,9 @@ int cdl_qgemm_fwd_offset(const int8_t *a_idx, const int8_t *b_idx, int32_t M, in
  * Diagnostics: once the call has run, the first two int32 of ws hold the limb counts the device
  * chose for d_a_hat and for d_b_hat, and the two doubles at byte offsets 32 and 40 of ws the bounds
  * above for the two products (meaningful for a product that was requested).  Where the arithmetic is small both products are
- * formed directly in double instead, each entry exact before its one rounding to fp32; the words then hold the counts and
- * bounds that limbs would have had, or, for calls with N <= 32 or M*N*K <= 2^25, zeros: no limbs, nothing rounded.  (d_a_hat
+ * formed directly instead, in double or on digits that give every entry of g to within 2^-44 of the largest of its row (d_a_hat;
+ * column for d_b_hat), summed in double before the one rounding to fp32; the words then hold the counts and
+ * bounds that limbs would have had, or, for calls with N <= 32 or M*N*K <= 2^25, zeros: no limbs.  (d_a_hat
  * with N <= 32 never has limbs, also where d_b_hat has.)
  */
 int cdl_qgemm_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx,

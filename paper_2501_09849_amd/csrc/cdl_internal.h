@@ -128,13 +128,14 @@ struct ConvWindows {
     int B, H, W, C, R, S, stride, pad, P, Q;
 };
 
-// Both products of a small layer directly in double (cdl_bwd_direct.hip).
+// Both products of a small layer directly (cdl_bwd_direct.hip).  only_b: for a layer whose dL/dQ(a) is formed
+// elsewhere (the plan is the same whichever of the others are asked for).  words: the diagnostic words may have to tell limb counts.
 struct BwdPlan;
 constexpr size_t kBwdDirectRecordBytes = 8192 * 2 * sizeof(unsigned long long);
-bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool want_a, bool want_b);
+bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool only_b, double *partial, int max_splits, bool words);
 int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float delta_a, float delta_b,
                       int32_t a_offset, int32_t b_offset, float *d_a_hat, float *d_b_hat, BwdPlan *plan, void *records, double *partial, int max_splits,
-                      hipStream_t stream);
+                      bool only_b, bool words, hipStream_t stream);
 
 // The same for the gradients of a convolution.  ConvDxGrid: a class of input pixels (2 i + oa, 2 j + oc) and the taps
 // (r0 + 2 r', s0 + 2 s'), r' < Rc, s' < Sc, that reach them (stride 1: one class, every pixel and tap, steps of 1).

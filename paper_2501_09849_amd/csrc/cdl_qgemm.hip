@@ -2305,9 +2305,13 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     char *base = reinterpret_cast<char *>(ws);
     BwdPlan *plan = reinterpret_cast<BwdPlan *>(base + L.plan);
     double *partial = reinterpret_cast<double *>(base + L.partial);
+    // (the windows of a 1 x 1 kernel of stride 1 are the activations as they lie)
+    const bool is_conv_weights = cw != nullptr;
+    if (cw && cw->R == 1 && cw->S == 1 && cw->stride == 1 && cw->pad == 0) cw = nullptr;
     if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.direct_splits, stream);
     // (many outputs of few multiplications each: one thread per four outputs, see da_direct_kernel)
-    if (d_a_hat && N <= kDirectMaxN && ((int64_t)M * K >= kDirectMinOutputs || !bwd_direct_serves(M, N, K, true, want_db))) {
+    const bool only_b = is_conv_weights || (N <= kDirectMaxN && ((int64_t)M * K >= kDirectMinOutputs || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true)));
+    if (d_a_hat && only_b) {
         // four columns per thread (two where 32 index values per column would not leave registers for four)
         const int c_per = N <= 16 ? 4 : 2;
         const int col_groups = (K + c_per - 1) / c_per;
@@ -2321,8 +2325,8 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         if (!want_db) return check_launch();
     }
 
-    if (!cw && bwd_direct_serves(M, N, K, d_a_hat != nullptr, d_b_hat != nullptr))
-        return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.direct_splits, stream);
+    if (!cw && bwd_direct_serves(M, N, K, only_b, partial, L.direct_splits, !is_conv_weights))
+        return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.direct_splits, only_b, !is_conv_weights, stream);
 
     int8_t *bt = reinterpret_cast<int8_t *>(base + L.bt);
     int8_t *at = reinterpret_cast<int8_t *>(base + L.at);

@@ -284,17 +284,6 @@ __device__ __forceinline__ void store_outputs(const DirectProduct &p, int64_t ro
     }
 }
 
-// out[t]: byte t of w[0..3]
-__device__ __forceinline__ void transpose4(const uint32_t (&w)[4], uint32_t *out)
-{
-    const uint32_t t0 = bperm(w[1], w[0], 0x05010400u), t2 = bperm(w[3], w[2], 0x05010400u);
-    out[0] = bperm(t2, t0, 0x05040100u);
-    out[1] = bperm(t2, t0, 0x07060302u);
-    const uint32_t t1 = bperm(w[1], w[0], 0x07030602u), t3 = bperm(w[3], w[2], 0x07030602u);
-    out[2] = bperm(t3, t1, 0x05040100u);
-    out[3] = bperm(t3, t1, 0x07060302u);
-}
-
 // The products of a tile over steps [s0, s1) of 16 contraction entries, wave ks of p.ksp, into the wave's part of LDS
 // (`mine`), or to memory where there is nothing to add (null).
 // TM x TN: 16 x 16 MFMA tiles; TN = 4: the tiles' columns are the four bytes of a word, 64 columns in all.
@@ -384,27 +373,6 @@ __device__ __forceinline__ void direct_tile(const DirectProduct &p, Src &src, in
 #pragma unroll
             for (int t = 0; t < TN; ++t) d[t] = acc[i][t][r];
         }
-}
-
-// Digits of four values, six limbs: q = rint(g unit) = sum_l d_l 256^l, d_l in [-128, 127]; unit a power of two, |g unit| < 2^46.
-// Added to 1.5 2^52 in double, q is rounded (to even) into the last bits of the sum, in two's complement; with 0x80..80 added to it
-// as well, its bytes are the digits plus 128.
-__device__ __forceinline__ void digits_of4(const float (&g)[4], double unit, uint32_t (&out)[6])
-{
-    constexpr double kMagic = 6755399441055744.0 + 141289400074368.0;      // 1.5 2^52 + 0x808080808080
-    uint32_t lo[4], hi[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const unsigned long long v = (unsigned long long)__double_as_longlong(__builtin_fma((double)g[e], unit, kMagic));
-        lo[e] = (uint32_t)v;
-        hi[e] = (uint32_t)(v >> 32);
-    }
-    transpose4(lo, &out[0]);
-    const uint32_t h0 = bperm(hi[1], hi[0], 0x05010400u), h2 = bperm(hi[3], hi[2], 0x05010400u);
-    out[4] = bperm(h2, h0, 0x05040100u);
-    out[5] = bperm(h2, h0, 0x07060302u);
-#pragma unroll
-    for (int l = 0; l < 6; ++l) out[l] ^= 0x80808080u;
 }
 
 // the largest of three; a NaN if there is one
@@ -601,7 +569,7 @@ __device__ __forceinline__ void digit_tile(const DirectProduct &p, Src &src, int
                 continue;
             }
             uint32_t d[kDigits], w[4], c[4];
-            digits_of4(g[u][0], scale, d);
+            limbs_of4_wide<kDigits>(g[u][0], scale, d);
 #pragma unroll
             for (int l = 0; l < kDigits; ++l) fa[l][u] = (int)d[l];
 #pragma unroll

@@ -1,0 +1,460 @@
+// dL/dQ(x) of a convolutional layer on limbs, from patches of g that stay in LDS: d_x_hat[b,h,w,c] = delta_w sum_{r,s,n}
+// g[b,p,q,n] w[n,r,s,c] over the taps that reach pixel (h, w), without a matrix of windows.
+//
+// The pixels of g that a run of output pixels needs are one contiguous range of g, [lo, lo + count) x N, of about the run's length
+// and R - 1 image rows.  A block takes such a range, finds its largest entry, chooses the limb count and the scale of its digits
+// by the rule of the other limb products (the bound of cdl_bwd_plan.h, over its own columns), and writes the digits into LDS once,
+// one byte per limb and entry; every tap then reads its fragments there, row by row at an offset that depends on the tap.  So nothing
+// runs before this kernel but the rearrangement of the weights, and g is read from memory about once per 256 channels.
+// The weights' fragments go from L2 straight to registers: a wave's columns are its own, LDS would be written and read for one use.
+//
+// What bounds it: the matrix cores while both blocks of a compute unit are in their k-steps (96 % busy; LDS and the vector cache at half
+// their rates); the rest of a block - largest entry 6 us, digits 5, outputs 3 of 35 - hides only behind the other block.  Before, a pass
+// for max |g| and one that made the digits ran first and the product read them tap by tap through L2 into LDS, where
+// reads and writes together took longer than the matrix instructions.  The whole call, us, with uniform indices: 256 images of
+// 14 x 14 x 256 -> 256, 3 x 3  216 -> 144;  128 x 28 x 28 x 128 -> 128  123 -> 87;  128 x 7 x 7 x 512 -> 512  139 -> 85;
+// 128 x 56 x 56 x 64 -> 128, stride 2  119 -> 97.
+#include "cdl_bwd_plan.h"
+#include "cdl_limbs.h"
+
+namespace cdl {
+
+namespace {
+
+constexpr int kPatchThreads = 256;
+constexpr int kPatchLds = 80 << 10;          // two blocks share a compute unit
+constexpr int kPatchFixed = 64;              // bytes for the reductions
+// At least four limbs.  Where every entry of g has the scale of the largest one of all, three may keep the bound for small ones; here they
+// would be chosen block by block, and a block of small entries next to large ones would be less exact than with the count that the
+// largest asks for (2.5e-8 -> 9e-8 of the norm of the outputs).  Relative to a block's largest entry four leave 2^-32, below the rounding of the fp32 result.
+constexpr int kPatchMinLimbs = 4;
+
+struct PatchClass {
+    int oa, oc, Hc, Wc, pad_h, pad_w, Rc, Sc;
+    const int8_t *wr;
+    const unsigned int *col_abs;             // [ld / 64][C]
+    DivBy by_s;
+};
+
+// The classes of output pixels (one; stride 2: up to four) share a grid of Hm x Wm pixels an image, the smaller ones with pixels that
+// are not there; grid pixel (i, j) reads g at rows i + lo_h .. i + hi_h and columns j + lo_w .. j + hi_w, over all classes.
+struct PatchArgs {
+    PatchClass c[4];
+    int n_classes;
+    const float *g;
+    float *out;
+    int N, Np, C, C32, P, Q, oH, oW, step, tiles_c, share, pixels;      // C32: C padded to 32; share: row tiles of an XCD; pixels: of g
+    int Hm, Wm, rows, row_tiles, lo_h, hi_h, lo_w, hi_w;
+    DivBy by_hw, by_w;
+    int px_max;                              // pixels of a patch, at most
+    int nc[kMaxLimbs + 1];                   // channels of a patch that fit, by limbs
+    int taps;                                // of a class, at most
+    double delta_w;
+};
+// (read where the launch put them: indexing a by-value argument by the class would copy it to scratch memory)
+typedef const PatchArgs __attribute__((address_space(4))) *patch_args_t;
+
+__device__ __forceinline__ float patch_largest(float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); }
+
+struct PatchTile { int row0, col0, lo, count; };
+
+// Four waves: WN = 1, 2, 4 as (4 / WN) x WN, 32 pixels by 64 channels each, of the one class; WN = 0: a wave for each class, 32 grid
+// pixels by 64 channels (four classes read the same patch, and no wave has to load weights behind stores: a wave's loads wait for
+// its older stores, which take microseconds).
+constexpr int patch_rows(int wn) { return wn == 0 ? 32 : 32 * (4 / wn); }
+constexpr int patch_cols(int wn) { return wn == 0 ? 64 : 64 * wn; }
+
+template <int L, int WN>
+__device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t, int8_t *lds, double out_scale, float gscale)
+{
+    constexpr int TN = 2, ROWS = patch_rows(WN);
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));      // (what the limb counts' code has in common is not moved in front of all of it, where registers are short)
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = WN == 0 ? 0 : wave / (WN ? WN : 1), wn = WN == 0 ? 0 : wave % (WN ? WN : 1), cls = WN == 0 ? wave : 0;
+    const bool idle = WN == 0 && cls >= args->n_classes;
+    const auto &k = args->c[idle ? 0 : cls];
+    const int P = args->P, Q = args->Q, Np = args->Np, N = args->N, C = args->C, Wm = args->Wm, hw = args->Hm * Wm, rows = args->rows, Sc = k.Sc, taps = k.Rc * Sc;
+    const DivBy by_hw{args->by_hw.mul, args->by_hw.sh}, by_w{args->by_w.mul, args->by_w.sh};
+    const int nc = args->nc[L], stride = nc + 16, px_max = args->px_max;      // (rows an odd multiple of 16 bytes apart: no bank conflicts)
+    const int plane = (px_max + 1) * stride;                                  // (row px_max of a plane: zeros)
+    // [class][taps + 1][ROWS]: the row of a plane where a tap's pixel lies
+    uint16_t *table = reinterpret_cast<uint16_t *>(lds + kPatchFixed) + (idle ? 0 : cls) * (args->taps + 1) * ROWS;
+    int8_t *planes = lds + kPatchFixed + 2 * (WN == 0 ? args->n_classes : 1) * (args->taps + 1) * ROWS;
+
+    for (int i = tid; i < L * (stride / 4); i += kPatchThreads) {
+        const int l = i / (stride / 4), w = i - l * (stride / 4);
+        reinterpret_cast<uint32_t *>(planes + l * plane + px_max * stride)[w] = 0u;
+    }
+    // digits of channels n0 .. n0 + nc of the patch: a thread keeps its four channels and goes through the pixels
+    const int words = nc >> 2, px_step = kPatchThreads / words;      // (words <= 256: what fits LDS)
+    const int px0 = tid / words, n_own = 4 * (tid - px0 * words);
+    auto make_digits = [&](int n0) {
+        if (px0 >= px_step) return;
+        const bool there = n0 + n_own < N;
+        const float *src = args->g + (int64_t)t.lo * N + (there ? n0 + n_own : 0);
+        constexpr int U = 8;
+        // (behind the last pixel: the last one again, with what its own thread writes; count N and count stride < 2^22)
+        const int src_step = px_step * N, src_last = (t.count - 1) * N, dst_step = px_step * stride, dst_last = (t.count - 1) * stride;
+        int from = px0 * N, to = px0 * stride;
+        for (int px = px0; px < t.count; px += U * px_step) {
+            float4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4 *>(src + min(from + u * src_step, src_last));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float g4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                uint32_t w[L];
+                limbs_of4<L>(g4, gscale, w);
+                if (!there)
+#pragma unroll
+                    for (int l = 0; l < L; ++l) w[l] = 0u;
+                int8_t *d = planes + min(to + u * dst_step, dst_last) + n_own;
+#pragma unroll
+                for (int l = 0; l < L; ++l) *reinterpret_cast<uint32_t *>(d + l * plane) = w[l];
+            }
+            from += U * src_step;
+            to += U * dst_step;
+        }
+    };
+    if (nc == Np) make_digits(0);      // all channels at once, for all classes
+
+    // weights: 1 KB a k-step of 32 entries and tile of 32 columns, in the order of the lanes
+    uint32_t bo[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bo[j] = (uint32_t)min((t.col0 >> 5) + wn * TN + j, (args->C32 >> 5) - 1) * 1024u + (uint32_t)lane * 16u;
+    const int64_t step_bytes = (int64_t)args->C32 * 32;
+    const int half = (lane >> 5) * 16;
+
+    // (WN = 0: a wave makes its own table)
+    for (int i = WN == 0 ? lane : tid; i < (idle ? 0 : taps + 1) * ROWS; i += WN == 0 ? 64 : kPatchThreads) {
+        const int tap = i / ROWS, row = i - tap * ROWS, m = t.row0 + row;
+        const int b = div_by(m, by_hw), rem = m - b * hw, ii = div_by(rem, by_w), jj = rem - ii * Wm;
+        const int tr = div_by(tap, k.by_s.mul, k.by_s.sh), ts = tap - tr * Sc;
+        const int p = ii + k.pad_h - tr, q = jj + k.pad_w - ts;
+        const bool inside = tap < taps && m < rows && (unsigned)p < (unsigned)P && (unsigned)q < (unsigned)Q;
+        const int px = (b * P + p) * Q + q - t.lo;
+        table[i] = (uint16_t)(inside ? min(max(px, 0), px_max - 1) : px_max);
+    }
+    v16i acc[L][TN];
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[l][j][r] = 0;
+    const int arow = wm * 32 + (lane & 31), nk = idle ? 0 : taps * (nc / 32);
+
+    for (int n0 = 0; n0 < Np; n0 += nc) {
+        if (n0 > 0) __syncthreads();
+        if (nc < Np) make_digits(n0);
+        __syncthreads();
+
+        // k-steps of 32 entries, tap after tap.  The weights of a step are asked for four steps ahead, the row of LDS two, the digits
+        // one (more than four limbs leave registers for less).
+        constexpr int NA = L <= 5 ? 2 : 1, NB = L <= 4 ? 4 : (L == 5 ? 2 : 1);
+        v4i fa[NA][L], fb[NB][TN];
+        int row[2], at[2];      // a lane's row of a plane, and the step's first channel (put together where they are used: no wait for the table before)
+        const int8_t *next_b = k.wr + (int64_t)(n0 >> 5) * step_bytes;
+        const int64_t skip = (int64_t)((Np - nc) >> 5) * step_bytes;      // to the next tap's part
+        int in_tap = nc >> 5;
+        auto load_b = [&](int buf) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[buf][j] = *reinterpret_cast<const v4i *>(next_b + bo[j]);
+            // (up to four steps behind the last one are read too: the host leaves room for them)
+            --in_tap;
+            next_b += step_bytes + (in_tap == 0 ? skip : 0);
+            in_tap = in_tap == 0 ? nc >> 5 : in_tap;
+        };
+        int rt = 0, rn = 0;
+        auto load_row = [&](int buf) {
+            row[buf] = table[rt * ROWS + arow];
+            at[buf] = rn;
+            rn += 32;
+            rt = min(rn == nc ? rt + 1 : rt, taps);
+            rn = rn == nc ? 0 : rn;
+        };
+        auto load_a = [&](int buf, int rbuf) {
+            const int8_t *p = planes + (row[rbuf] * stride + (at[rbuf] + half));
+#pragma unroll
+            for (int l = 0; l < L; ++l) fa[buf][l] = *reinterpret_cast<const v4i *>(p + l * plane);
+        };
+        auto mfma_all = [&](int abuf, int bbuf) {
+#pragma unroll
+            for (int l = 0; l < L; ++l)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[l][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[abuf][l], fb[bbuf][j], acc[l][j], 0, 0, 0);
+        };
+#pragma unroll
+        for (int u = 0; u < NB; ++u) load_b(u);
+        load_row(0);
+        load_row(1);
+        if (NA == 2) load_a(0, 0);
+        // (a step behind the last one multiplies rows of zeros)
+        for (int it = 0; it < nk; it += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (u == 2 && it + 2 >= nk) break;
+                if (NA == 2) load_a((u + 1) & 1, (u + 1) & 1);
+                else load_a(0, u & 1);
+                load_row(u & 1);
+                mfma_all(NA == 2 ? u & 1 : 0, u % NB);
+                load_b(u % NB);
+#pragma unroll
+                for (int i = 0; i < L * TN; ++i) {      // behind each matrix instruction a part of the rest
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x006, 5, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+
+    if (idle) return;
+    // the limbs of an output: the integers are exact, the Horner steps round at 2^-53 relative
+    int elane = lane;
+    asm volatile("" : "+v"(elane));      // (addresses formed here, not kept in registers through the loop)
+    const int m = t.row0 + wm * 32 + (elane & 31);
+    const int b = div_by(m, by_hw), rem = m - b * hw, i = div_by(rem, by_w), jj = rem - i * Wm;
+    const int pixel = m < rows && i < k.Hc && jj < k.Wc ? (b * args->oH + args->step * i + k.oa) * args->oW + args->step * jj + k.oc : -1;
+    float *out = args->out;
+    const int ecol = t.col0 + wn * TN * 32 + (elane & 31);
+#pragma unroll
+    for (int rr = 0; rr < 16; ++rr) {
+        const int pix = __shfl(pixel, 4 * (elane >> 5) + 8 * (rr >> 2) + (rr & 3), 64);      // (layout of an accumulator)
+        float *p = out + (int64_t)pix * C + ecol;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            double run = (double)acc[L - 1][j][rr];
+#pragma unroll
+            for (int l = L - 2; l >= 0; --l) run = __builtin_fma(run, 256.0, (double)acc[l][j][rr]);
+            if (pix >= 0 && ecol + j * 32 < C) p[j * 32] = (float)(run * out_scale);
+        }
+    }
+}
+
+template <int WN>
+__global__ __launch_bounds__(kPatchThreads, 2)
+void limb_conv_patch_kernel(PatchArgs a)
+{
+    constexpr int ROWS = patch_rows(WN), COLS = patch_cols(WN);
+    extern __shared__ __attribute__((aligned(16))) int8_t patch_lds[];
+    const patch_args_t args = (patch_args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    // Blocks go to the eight XCDs round-robin; XCD x takes the x-th eighth of the row tiles, all columns of one after the
+    // other (they read the same g through one L2).
+    const int xcd = (int)blockIdx.x & 7, q = (int)blockIdx.x >> 3, r = q / args->tiles_c;
+    PatchTile t;
+    t.col0 = (q - r * args->tiles_c) * COLS;
+    const int tile = xcd * args->share + r;
+    if (r >= args->share || tile >= args->row_tiles) return;
+    t.row0 = tile * ROWS;
+    // the range of g
+    {
+        const int m1 = min(t.row0 + ROWS, args->rows) - 1, Wm = args->Wm, hw = args->Hm * Wm, P = args->P, Q = args->Q;
+        const DivBy by_hw{args->by_hw.mul, args->by_hw.sh}, by_w{args->by_w.mul, args->by_w.sh};
+        const int b0 = div_by(t.row0, by_hw), rem0 = t.row0 - b0 * hw, i0 = div_by(rem0, by_w), j0 = rem0 - i0 * Wm;
+        const int b1 = div_by(m1, by_hw), rem1 = m1 - b1 * hw, i1 = div_by(rem1, by_w), j1 = rem1 - i1 * Wm;
+        const int p0 = i0 + args->lo_h, q0 = j0 + args->lo_w, p1 = i1 + args->hi_h, q1 = j1 + args->hi_w;
+        // (above the image: from its first pixel on; below it: to its last one)
+        const int lo = (b0 * P + min(max(p0, 0), P - 1)) * Q + (p0 < 0 ? 0 : min(max(q0, 0), Q - 1));
+        const int hi = (b1 * P + min(max(p1, 0), P - 1)) * Q + (p1 > P - 1 ? Q - 1 : min(max(q1, 0), Q - 1));
+        t.lo = __builtin_amdgcn_readfirstlane(lo);
+        t.count = __builtin_amdgcn_readfirstlane(min(max(hi - lo + 1, 1), min(args->px_max, args->pixels - lo)));
+    }
+    // largest |g| of the range, largest sum of |w| of the columns
+    float *red = reinterpret_cast<float *>(patch_lds);
+    unsigned int *redc = reinterpret_cast<unsigned int *>(patch_lds) + 4;
+    {
+        // (the sums of the columns are asked for first, forty pieces of a class at a time: one trip to memory together with g)
+        unsigned int cs = 0u;
+        const bool column = (int)threadIdx.x < COLS * args->n_classes && t.col0 + (int)threadIdx.x % COLS < args->C;
+        const auto &k = args->c[column ? (int)threadIdx.x / COLS : 0];
+        const unsigned int *col = k.col_abs + min(t.col0 + (int)threadIdx.x % COLS, args->C - 1);
+        const int kb = (k.Rc * k.Sc * args->Np + 63) / 64;
+        constexpr int kPieces = 40;
+        unsigned int v[kPieces];
+#pragma unroll
+        for (int u = 0; u < kPieces; ++u) v[u] = col[(int64_t)min(u, kb - 1) * args->C];
+        float mx = 0.0f;
+        const float4 *g4 = reinterpret_cast<const float4 *>(args->g + (int64_t)t.lo * args->N);
+        const int quads = t.count * (args->N >> 2);
+#pragma unroll 8
+        for (int i = threadIdx.x; i < quads; i += kPatchThreads) {
+            const float4 f = g4[i];
+            mx = patch_largest(mx, fabsf(f.x), fabsf(f.y));
+            mx = patch_largest(mx, fabsf(f.z), fabsf(f.w));
+        }
+#pragma unroll
+        for (int u = 0; u < kPieces; ++u) cs += u < kb ? v[u] : 0u;
+        for (int i = kPieces; i < kb; ++i) cs += col[(int64_t)i * args->C];
+        if (!column) cs = 0u;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, off, 64));
+            cs = max(cs, (unsigned int)__shfl_xor((int)cs, off, 64));
+        }
+        if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = mx; redc[threadIdx.x >> 6] = cs; }
+    }
+    __syncthreads();
+    const float amax = patch_largest(patch_largest(red[0], red[1], red[2]), red[3], 0.0f);
+    const unsigned int sums = max(max(redc[0], redc[1]), max(redc[2], redc[3]));
+    // sigma = 2^e > 1.01 max|g|, and the fewest limbs (four to six) whose bound delta_w sigma 2^-8L sum|w| is under the target (choose_limbs)
+    int e = 0;
+    if (amax > 0.0f) frexpf(amax * 1.01f, &e);
+    e = __builtin_amdgcn_readfirstlane(max(min(e, 127), -80));
+    const double unit = args->delta_w * (double)sums;
+    int L = kPatchMinLimbs;
+    while (L < kMaxLimbs && unit * ldexp(1.0, e - 8 * L) > kLimbBoundTarget) ++L;
+    L = __builtin_amdgcn_readfirstlane(L);
+    // (an infinity or a NaN in the range: NaN for the tile)
+    const bool finite = (__float_as_uint(amax) & 0x7f800000u) != 0x7f800000u;
+    // (in scalar registers: kept in memory, their loads among the stores of the outputs would wait for every store before them)
+    const long long scale_bits = finite ? __double_as_longlong(args->delta_w * ldexp(1.0, e + 1 - 8 * L)) : 0x7ff8000000000000ll;
+    const double out_scale = __hiloint2double(__builtin_amdgcn_readfirstlane((int)(scale_bits >> 32)), __builtin_amdgcn_readfirstlane((int)scale_bits));
+    const float gscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, 8 * L - 1 - e))));
+    switch (L) {
+        case 4: patch_body<4, WN>(args, t, patch_lds, out_scale, gscale); break;
+        case 5: patch_body<5, WN>(args, t, patch_lds, out_scale, gscale); break;
+        default: patch_body<6, WN>(args, t, patch_lds, out_scale, gscale); break;
+    }
+}
+
+// The grid that the classes share, and what a pixel of it reads.
+struct PatchGrid { int Hm, Wm, lo_h, hi_h, lo_w, hi_w; };
+
+PatchGrid patch_grid(const ConvDxGrid *grids, int n)
+{
+    PatchGrid p{0, 0, 1 << 30, -(1 << 30), 1 << 30, -(1 << 30)};
+    auto least = [](int &a, int b) { if (b < a) a = b; };
+    auto most = [](int &a, int b) { if (b > a) a = b; };
+    for (int i = 0; i < n; ++i) {
+        const ConvDxGrid &s = grids[i];
+        most(p.Hm, s.Hc);
+        most(p.Wm, s.Wc);
+        least(p.lo_h, s.pad_h - s.Rc + 1);
+        most(p.hi_h, s.pad_h);
+        least(p.lo_w, s.pad_w - s.Sc + 1);
+        most(p.hi_w, s.pad_w);
+    }
+    return p;
+}
+
+// Pixels of g that a run of `rows` pixels of the grid needs, at most: from what the first one reads first to what the last one reads
+// last, with what g's rows and images have more than the grid's at every end of a row and an image.
+int64_t patch_pixels(const PatchGrid &s, int rows, int P, int Q, int64_t all)
+{
+    const int64_t hw = (int64_t)s.Hm * s.Wm, row_ends = (rows - 2 + s.Wm) / s.Wm, image_ends = (rows - 2 + hw) / hw;
+    int64_t n = rows + (int64_t)(s.hi_h - s.lo_h) * Q + s.hi_w - s.lo_w;
+    if (Q > s.Wm) n += row_ends * (Q - s.Wm);
+    if (P > s.Hm) n += image_ends * (int64_t)(P - s.Hm) * Q;
+    // (pixels beyond the last window: their range begins at the image's last row or pixel instead)
+    if (s.Hm - 1 + s.lo_h > P - 1) n += (int64_t)(s.Hm + s.lo_h - P) * Q;
+    if (s.Wm - 1 + s.lo_w > Q - 1) n += s.Wm + s.lo_w - Q;
+    return n < all ? n : all;
+}
+
+struct PatchPlan {
+    bool served;
+    int wn, px_max, taps;
+    int nc[kMaxLimbs + 1];
+};
+
+// The tile of 32 x 256, 64 x 128 or 128 x 64 outputs that pads the channels least (of equals the widest, which needs the smallest
+// patch; several classes: 32 x 64 of each), and the channels of a patch that fit LDS: all of them or an equal part, a multiple of 32.
+PatchPlan plan_patch(const ConvDxGrid *grids, int n_grids, int64_t B, int P, int Q, int C, int Np)
+{
+    PatchPlan best{};
+    int64_t least = 0;
+    const PatchGrid grid = patch_grid(grids, n_grids);
+    if (n_grids < 1 || B * grid.Hm * grid.Wm > 2147483647LL) return best;
+    for (int wn = n_grids > 1 ? 0 : 4; wn >= 0; wn = wn > 1 ? wn / 2 : -1) {
+        const int rows = patch_rows(wn), cols = patch_cols(wn);
+        const int64_t padded = (int64_t)((C + cols - 1) / cols) * cols;
+        if (best.served && padded >= least) continue;
+        PatchPlan p{};
+        p.served = true;
+        p.wn = wn;
+        for (int i = 0; i < n_grids; ++i)
+            if (grids[i].Rc * grids[i].Sc > p.taps) p.taps = grids[i].Rc * grids[i].Sc;
+        const int64_t px = patch_pixels(grid, rows, P, Q, B * P * Q);
+        if (px > 4096) continue;
+        p.px_max = (int)px;
+        for (int l = kPatchMinLimbs; l <= kMaxLimbs; ++l) {
+            p.nc[l] = 0;
+            for (int parts = 1; parts <= Np / 32 && !p.nc[l]; ++parts)
+                if (Np / 32 % parts == 0 && kPatchFixed + 2ll * n_grids * (p.taps + 1) * rows + l * (px + 1) * (Np / parts + 16) <= kPatchLds) p.nc[l] = Np / parts;
+            p.served = p.served && p.nc[l] != 0;
+        }
+        if (!p.served) continue;
+        best = p;
+        least = padded;
+    }
+    // A block takes about 12 us beside its k-steps (0.28 us each), which short contractions do not pay for once there are enough blocks for
+    // the passes that this kernel does without (20 - 30 us) not to count.  Digits made beforehand / patches, us: 59 x 52 x 52 x 240 -> 48, 3 x 3
+    // (18 steps, 5 K blocks)  129 / 150;  195 x 38 x 38 x 96 -> 24 (9, 4.4 K)  101 / 108;  19 x 45 x 45 x 208 -> 36 (18, 1.2 K)  49 / 45;
+    // 27 x 56 x 56 x 64 -> 24 (9, 0.7 K)  44 / 29.
+    int taps = 0;
+    for (int i = 0; i < n_grids; ++i) taps += grids[i].Rc * grids[i].Sc;
+    if (best.served && taps * (Np / 32) < 20) {
+        const int rows = patch_rows(best.wn), cols = patch_cols(best.wn);
+        if ((B * grid.Hm * grid.Wm + rows - 1) / rows * ((C + cols - 1) / cols) > 2000) best.served = false;
+    }
+    return best;
+}
+
+template <int WN>
+int launch_patch(PatchArgs a, hipStream_t stream)
+{
+    constexpr int ROWS = patch_rows(WN), COLS = patch_cols(WN);
+    a.tiles_c = (a.C + COLS - 1) / COLS;
+    a.row_tiles = (a.rows + ROWS - 1) / ROWS;
+    a.share = (a.row_tiles + 7) / 8;
+    const int64_t blocks = 8ll * a.share * a.tiles_c;
+    if (blocks > 2147483647LL) return CDL_ERR_PARAM;
+    const hipError_t e = hipFuncSetAttribute((const void *)limb_conv_patch_kernel<WN>, hipFuncAttributeMaxDynamicSharedMemorySize, kPatchLds);
+    if (e != hipSuccess) return hip_failed(e);
+    CDL_LAUNCH("limb_conv_patch_kernel", stream, (limb_conv_patch_kernel<WN>), dim3((unsigned)blocks), dim3(kPatchThreads), kPatchLds, a);
+    return check_launch();
+}
+
+}  // namespace
+
+bool conv_dx_patch_serves(const ConvDxGrid *grids, int n_grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q)
+{
+    return plan_patch(grids, n_grids, B, P, Q, C, (N + 31) / 32 * 32).served;
+}
+
+int launch_conv_dx_patch(const float *g, const int8_t *wr, const unsigned int *col_abs, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
+                         int32_t W, int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream)
+{
+    const PatchPlan p = plan_patch(grids, n_grids, B, P, Q, C, Np);
+    const PatchGrid grid = patch_grid(grids, n_grids);
+    PatchArgs a{};
+    a.n_classes = n_grids;
+    a.g = g; a.out = d_x_hat;
+    a.N = N; a.Np = Np; a.C = C; a.C32 = (C + 31) / 32 * 32; a.P = P; a.Q = Q; a.oH = H; a.oW = W; a.step = stride;
+    a.pixels = B * P * Q;
+    a.Hm = grid.Hm; a.Wm = grid.Wm; a.rows = B * grid.Hm * grid.Wm;
+    a.lo_h = grid.lo_h; a.hi_h = grid.hi_h; a.lo_w = grid.lo_w; a.hi_w = grid.hi_w;
+    a.by_hw = make_div_by((uint32_t)grid.Hm * (uint32_t)grid.Wm);
+    a.by_w = make_div_by((uint32_t)grid.Wm);
+    a.px_max = p.px_max; a.taps = p.taps;
+    for (int l = kPatchMinLimbs; l <= kMaxLimbs; ++l) a.nc[l] = p.nc[l];
+    a.delta_w = (double)delta_w;
+    for (int i = 0; i < n_grids; ++i) {
+        const ConvDxGrid &s = grids[i];
+        PatchClass &d = a.c[i];
+        d.oa = s.oa; d.oc = s.oc; d.Hc = s.Hc; d.Wc = s.Wc; d.pad_h = s.pad_h; d.pad_w = s.pad_w; d.Rc = s.Rc; d.Sc = s.Sc;
+        d.wr = wr + (int64_t)i * a.C32 * ld;
+        d.col_abs = col_abs + (int64_t)i * (ld / 64) * C;
+        d.by_s = make_div_by((uint32_t)s.Sc);
+    }
+    if (p.wn == 0) return launch_patch<0>(a, stream);
+    if (p.wn == 4) return launch_patch<4>(a, stream);
+    if (p.wn == 2) return launch_patch<2>(a, stream);
+    return launch_patch<1>(a, stream);
+}
+
+}  // namespace cdl

@@ -147,7 +147,13 @@ bool conv_dx_direct_serves(int64_t pixels, int32_t N, int32_t C, int32_t R, int3
 int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
                           int32_t R, int32_t S, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream);
 
-// The same on limbs (cdl_conv_dx.hip).  wr: the weights per class as [ld / 64][C][64]; Np: N padded to whole chunks of 16 channels;
+// The same on limbs, from patches of g in LDS (cdl_conv_patch.hip).  wr: the weights per class as [ld / 32][C / 32][2][32][16] (halves of 32
+// contraction entries, channels, entries), a tap's channels padded with zeros to Np, a multiple of 32; col_abs: sums of |w| per class as [ld / 64][C].
+bool conv_dx_patch_serves(const ConvDxGrid *grids, int n_grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q);
+int launch_conv_dx_patch(const float *g, const int8_t *wr, const unsigned int *col_abs, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
+                         int32_t W, int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream);
+
+// The same on limbs, from digits made beforehand (cdl_conv_dx.hip).  wr: the weights per class as [ld / 64][C][64]; Np: N padded to whole chunks of 16 channels;
 // planes: room for the digits of g, kMaxLimbs * M_out * Np bytes; zeros: a page of zeros.
 int launch_conv_dx_planes(const float *g, const int8_t *wr, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H, int32_t W,
                           int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, const BwdPlan *plan, int8_t *planes,
@@ -176,8 +182,7 @@ int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_
                      int32_t *acc, float *y, void *ws, hipStream_t stream);
 
 // Activation gradient of a convolutional layer (N % 128 == 0, stride 1 or 2): d_x_hat [B][H][W][C].
-// pixels: of the input, B H W; M_out: of the output, B P Q
-size_t qconv_bwd_activations_workspace_bytes(int64_t pixels, int64_t M_out, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride);
+size_t qconv_bwd_activations_workspace_bytes(int32_t B, int32_t H, int32_t W, int32_t C, int32_t N, int32_t R, int32_t S, int32_t stride, int32_t pad);
 int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
                                  int32_t R, int32_t S, int32_t stride, int32_t pad, float delta_w, float *d_x_hat, void *ws,
                                  hipStream_t stream);

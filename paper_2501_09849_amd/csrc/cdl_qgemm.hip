@@ -1283,7 +1283,7 @@ struct ConvDxClasses { ConvDxClass c[4]; int tstep; };
 
 __global__ __launch_bounds__(256)
 void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int S, int C, ConvDxClasses cls, int8_t *__restrict__ wr, int64_t ld,
-                         unsigned int *col_abs /* zeroed */, PlanArgs plan)
+                         unsigned int *col_abs /* zeroed, or null */, unsigned int *part /* [class][ld / 64][C], or null */, PlanArgs plan)
 {
     // A block turns 64 contraction entries x 64 channels of one class (blockIdx.z): rows of 64 channels are contiguous in w,
     // 64 entries of a channel in wr.
@@ -1322,10 +1322,15 @@ void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int
     s_abs += (unsigned int)__shfl_xor((int)s_abs, 1, 64);
     s_abs += (unsigned int)__shfl_xor((int)s_abs, 2, 64);
     if (c0 + c < C) {
-        int8_t *dst = wr + (int64_t)blockIdx.z * C * ld + ((int64_t)blockIdx.x * C + c0 + c) * 64 + 16 * q;
+        // (patches: 1 KB for 32 contraction entries of 32 channels, [half of the entries][channel][16])
+        const int C32 = (C + 31) & ~31, ch = c0 + c;
+        int8_t *dst = part ? wr + (int64_t)blockIdx.z * C32 * ld + (((int64_t)(2 * blockIdx.x + (q >> 1)) * (C32 >> 5) + (ch >> 5)) * 64 + (q & 1) * 32 + (ch & 31)) * 16
+                           : wr + (int64_t)blockIdx.z * C * ld + ((int64_t)blockIdx.x * C + ch) * 64 + 16 * q;
         *reinterpret_cast<uint4 *>(dst) = uint4{word[0], word[1], word[2], word[3]};
-        if (q == 0) __hip_atomic_fetch_add(&col_abs[blockIdx.z * C + c0 + c], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (q == 0 && part) part[((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * C + c0 + c] = s_abs;
+        if (q == 0 && col_abs) __hip_atomic_fetch_add(&col_abs[blockIdx.z * C + c0 + c], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (!col_abs) return;
     plan_at_end(plan, (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y * gridDim.z));
 }
 
@@ -2123,17 +2128,17 @@ static int conv_zero_page_ptr(const int8_t **ptr)
 }
 
 struct ConvDxLayout {
-    size_t plan, flags, block_max, ss_b, wr, planes, total;
+    size_t plan, flags, block_max, ss_b, wr, planes, total;      // (patches: sums of |w| in the place of the planes)
     int n_max, Np, classes;
     int64_t ld;
 };
 
-ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride)
+ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride, int32_t pad_n)
 {
     ConvDxLayout L;
     // stride 2: four classes of taps, each with at most ceil(R / 2) x ceil(S / 2) of them
     L.classes = stride == 2 ? 4 : 1;
-    L.Np = (N + 15) / 16 * 16;
+    L.Np = (N + pad_n - 1) / pad_n * pad_n;
     const int64_t kc = (stride == 2 ? (int64_t)((R + 1) / 2) * ((S + 1) / 2) : (int64_t)R * S) * L.Np;
     L.ld = (kc + 63) / 64 * 64;
     L.n_max = (int)blocks_for((M_out * N) >> 2, 2048, 2048);
@@ -2142,7 +2147,8 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     L.flags = off;     off += kPlanMaxBlocks * sizeof(unsigned long long);
     L.block_max = off; off += align_up((size_t)L.n_max * sizeof(unsigned int), 256);
     L.ss_b = off;      off += align_up((size_t)L.classes * C * sizeof(unsigned int), 256);
-    L.wr = off;        off += align_up((size_t)L.classes * C * (size_t)L.ld, 256);
+    // (and the four k-steps behind a class that are read in vain, of as much as a part of a tap's channels leaves out)
+    L.wr = off;        off += align_up((size_t)((C + 31) / 32 * 32) * ((size_t)L.classes * (size_t)L.ld + 4 * (32 + (size_t)L.Np)), 256);
     L.planes = off;    off += align_up((size_t)M_out * (size_t)L.Np * kMaxLimbs, 256);
     L.total = off;
     return L;
@@ -2151,12 +2157,51 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
 // (a 1 x 1 convolution of stride 1 is a linear layer)
 bool conv_dx_is_linear(int32_t R, int32_t S, int32_t stride) { return R == 1 && S == 1 && stride == 1; }
 
-size_t qconv_bwd_activations_workspace_bytes(int64_t pixels, int64_t M_out, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride)
+// The classes of input pixels.  Stride 1: all of them, every tap.  Stride 2: input pixel (h, w) is reached only by the
+// taps r = h + pad, s = w + pad (mod 2) - with all R x S taps three products in four would multiply zeros -, so the
+// pixels (2 i + a, 2 j + c) of each parity (a, c) form a product of their own over the taps r = r0 + 2 r',
+// s = s0 + 2 s' (r0 = (a + pad) mod 2, likewise s0), in which g is read at p = i + (a + pad - r0) / 2 - r'.
+// Returns their number; unreached: there are pixels that no tap reaches.
+static int conv_dx_classes(int32_t H, int32_t W, int32_t R, int32_t S, int32_t stride, int32_t pad, ConvDxGrid (&grids)[4], bool &unreached)
 {
-    const ConvDxLayout L = conv_dx_layout(M_out, N, C, R, S, stride);
-    // the digit planes of g only where they are made: neither the direct product nor a linear layer has them
-    const bool direct = conv_dx_direct_serves(pixels, N, C, R, S, stride), is_linear = conv_dx_is_linear(R, S, stride);
-    const size_t own = direct || is_linear ? L.planes : L.total;
+    int n = 0;
+    unreached = false;
+    if (stride == 1) {
+        grids[n++] = ConvDxGrid{0, 0, H, W, pad, pad, R, S, 0, 0};
+        return n;
+    }
+    for (int pa = 0; pa < 2; ++pa)
+        for (int pc = 0; pc < 2; ++pc) {
+            const int Hc = (H - pa + 1) / 2, Wc = (W - pc + 1) / 2;
+            if (Hc <= 0 || Wc <= 0) continue;
+            const int r0 = (pa + pad) & 1, s0 = (pc + pad) & 1;
+            const int Rc = r0 < R ? (R - r0 + 1) / 2 : 0, Sc = s0 < S ? (S - s0 + 1) / 2 : 0;
+            if (Rc == 0 || Sc == 0) { unreached = true; continue; }
+            grids[n++] = ConvDxGrid{pa, pc, Hc, Wc, (pa + pad - r0) / 2, (pc + pad - s0) / 2, Rc, Sc, r0, s0};
+        }
+    return n;
+}
+
+size_t qconv_bwd_activations_workspace_bytes(int32_t B, int32_t H, int32_t W, int32_t C, int32_t N, int32_t R, int32_t S, int32_t stride, int32_t pad)
+{
+    const int P = (H + 2 * pad - R) / stride + 1, Q = (W + 2 * pad - S) / stride + 1;
+    const int64_t M_out = (int64_t)B * P * Q;
+    ConvDxGrid grids[4];
+    bool unreached;
+    const int n_cls = conv_dx_classes(H, W, R, S, stride, pad, grids, unreached);
+    const bool patch = conv_dx_patch_serves(grids, n_cls, B, C, N, P, Q);
+    const ConvDxLayout L = conv_dx_layout(M_out, N, C, R, S, stride, patch ? 32 : 16);
+    // Room for digit planes from half a G multiply-adds on: the digits of a patch lie in LDS, but what a size asks for does not depend on
+    // which of the kernels serves it.  None for a linear layer, nor for few channels on both sides (the direct product at any size).
+    const bool is_linear = conv_dx_is_linear(R, S, stride), few = C <= 32 && (int64_t)R * S * N <= 288;
+    const double cols = C <= 48 ? (C + 15) / 16 * 16 : (C + 63) / 64 * 64;
+    const double work = (double)B * H * W * cols * (double)(((int64_t)R * S * N + 15) / 16 * 16) / (stride * stride);
+    size_t own = is_linear || few || work <= 5e8 ? L.planes : L.total;
+    const size_t sums = L.planes + align_up((size_t)L.classes * (size_t)(L.ld / 64) * C * sizeof(unsigned int), 256);
+    if (!conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride) && !is_linear) {
+        const size_t least = patch ? sums : L.total;
+        if (least > own) own = least;
+    }
     const size_t linear = is_linear ? bwd_layout((int32_t)M_out, N, C).total : 0;
     return own > linear ? own : linear;
 }
@@ -2167,48 +2212,35 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
 {
     const int P = (H + 2 * pad - R) / stride + 1, Q = (W + 2 * pad - S) / stride + 1;
     const int64_t M_out = (int64_t)B * P * Q;
-    const ConvDxLayout L = conv_dx_layout(M_out, N, C, R, S, stride);
+    ConvDxGrid grids[4];
+    bool zero_first;
+    const int n_cls = conv_dx_classes(H, W, R, S, stride, pad, grids, zero_first);
+    if (zero_first)
+        CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)B * H * W * C, 256, 4096)), dim3(256), 0, d_x_hat, (int64_t)B * H * W * C);
+    if (n_cls == 0) return check_launch();
+    if (conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride))
+        return launch_conv_dx_direct(g, w_idx, grids, n_cls, B, H, W, C, N, R, S, P, Q, stride, delta_w, d_x_hat, stream);
+    if (conv_dx_is_linear(R, S, stride))      // (the padding is smaller than the kernel: none)
+        return launch_qgemm_bwd(g, nullptr, w_idx, (int32_t)M_out, N, C, 1.0f, delta_w, 0, 0, d_x_hat, nullptr, ws, stream);
+
+    const bool patch = conv_dx_patch_serves(grids, n_cls, B, C, N, P, Q);
+    const ConvDxLayout L = conv_dx_layout(M_out, N, C, R, S, stride, patch ? 32 : 16);
     char *base = reinterpret_cast<char *>(ws);
     BwdPlan *plan = reinterpret_cast<BwdPlan *>(base + L.plan);
     unsigned int *block_max = reinterpret_cast<unsigned int *>(base + L.block_max);
     unsigned int *ss_b = reinterpret_cast<unsigned int *>(base + L.ss_b);
     int8_t *wr = reinterpret_cast<int8_t *>(base + L.wr);
-
-    // The classes of input pixels.  Stride 1: all of them, every tap.  Stride 2: input pixel (h, w) is reached only by the
-    // taps r = h + pad, s = w + pad (mod 2) - with all R x S taps three products in four would multiply zeros -, so the
-    // pixels (2 i + a, 2 j + c) of each parity (a, c) form a product of their own over the taps r = r0 + 2 r',
-    // s = s0 + 2 s' (r0 = (a + pad) mod 2, likewise s0), in which g is read at p = i + (a + pad - r0) / 2 - r'.
-    struct Cls { int oa, oc, Hc, Wc, pad_h, pad_w, Rc, Sc; };
-    Cls cl[4];
     ConvDxClasses taps{};
     taps.tstep = stride;
-    int n_cls = 0;
-    bool zero_first = false;
-    if (stride == 1) {
-        cl[n_cls] = Cls{0, 0, H, W, pad, pad, R, S};
-        taps.c[n_cls++] = ConvDxClass{0, 0, R, S};
-    } else {
-        for (int pa = 0; pa < 2; ++pa)
-            for (int pc = 0; pc < 2; ++pc) {
-                const int Hc = (H - pa + 1) / 2, Wc = (W - pc + 1) / 2;
-                if (Hc <= 0 || Wc <= 0) continue;
-                const int r0 = (pa + pad) & 1, s0 = (pc + pad) & 1;
-                const int Rc = r0 < R ? (R - r0 + 1) / 2 : 0, Sc = s0 < S ? (S - s0 + 1) / 2 : 0;
-                if (Rc == 0 || Sc == 0) { zero_first = true; continue; }     // no tap reaches these pixels
-                cl[n_cls] = Cls{pa, pc, Hc, Wc, (pa + pad - r0) / 2, (pc + pad - s0) / 2, Rc, Sc};
-                taps.c[n_cls++] = ConvDxClass{r0, s0, Rc, Sc};
-            }
+    for (int c = 0; c < n_cls; ++c) taps.c[c] = ConvDxClass{grids[c].r0, grids[c].s0, grids[c].Rc, grids[c].Sc};
+    if (patch) {
+        unsigned int *part = reinterpret_cast<unsigned int *>(base + L.planes);
+        const dim3 grid((unsigned)(L.ld / 64), (unsigned)((C + 63) / 64), (unsigned)n_cls);
+        CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, grid, dim3(256), 0, w_idx, N, L.Np, R, S, C, taps, wr, L.ld, (unsigned int *)nullptr, part, PlanArgs{});
+        const int rc = check_launch();
+        if (rc != CDL_OK) return rc;
+        return launch_conv_dx_patch(g, wr, part, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, delta_w, d_x_hat, stream);
     }
-    if (zero_first)
-        CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)B * H * W * C, 256, 4096)), dim3(256), 0, d_x_hat, (int64_t)B * H * W * C);
-    if (n_cls == 0) return check_launch();
-    ConvDxGrid grids[4];
-    for (int c = 0; c < n_cls; ++c)
-        grids[c] = ConvDxGrid{cl[c].oa, cl[c].oc, cl[c].Hc, cl[c].Wc, cl[c].pad_h, cl[c].pad_w, cl[c].Rc, cl[c].Sc, taps.c[c].r0, taps.c[c].s0};
-    if (conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride))
-        return launch_conv_dx_direct(g, w_idx, grids, n_cls, B, H, W, C, N, R, S, P, Q, stride, delta_w, d_x_hat, stream);
-    if (conv_dx_is_linear(R, S, stride))      // (the padding is smaller than the kernel: none)
-        return launch_qgemm_bwd(g, nullptr, w_idx, (int32_t)M_out, N, C, 1.0f, delta_w, 0, 0, d_x_hat, nullptr, ws, stream);
     CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, n_cls * C);
     // (one limb count for all classes: the largest column sum of any of them)
     PlanArgs pa{plan, block_max, L.n_max, nullptr, ss_b, 0, n_cls * C, 1.0f, delta_w, reinterpret_cast<unsigned long long *>(base + L.flags), next_finish_tag()};
@@ -2216,7 +2248,7 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
     const bool plan_apart = (int64_t)prep.x * prep.y * prep.z > kPlanMaxBlocks;
     if (plan_apart) pa.plan = nullptr;
     CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, prep, dim3(256), 0,
-               w_idx, N, L.Np, R, S, C, taps, wr, L.ld, ss_b, pa);
+               w_idx, N, L.Np, R, S, C, taps, wr, L.ld, ss_b, (unsigned int *)nullptr, pa);
     if (plan_apart)
         CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
                    (const unsigned int *)nullptr, 0, ss_b, n_cls * C, 1.0f, delta_w);

@@ -147,6 +147,11 @@ bool conv_dx_direct_serves(int64_t pixels, int32_t N, int32_t C, int32_t R, int3
 int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
                           int32_t R, int32_t S, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream);
 
+// cdl_limb_rows.hip: dL/dQ(a) over short contractions; frag: b_idx in the fragments of the matrix instructions, tile_bytes for 32 columns
+bool limb_rows_serves(int64_t M, int32_t N, int32_t K);
+int launch_limb_rows(const float *g, const int8_t *frag, int64_t tile_bytes, int32_t M, int32_t N, int32_t K, const BwdPlan *plan, const double *row_corr, float *out,
+                     hipStream_t stream);
+
 // The same on limbs, from patches of g in LDS (cdl_conv_patch.hip).  wr: the weights per class as [ld / 32][C / 32][2][32][16] (halves of 32
 // contraction entries, channels, entries), a tap's channels padded with zeros to Np, a multiple of 32; col_abs: sums of |w| per class as [ld / 64][C].
 bool conv_dx_patch_serves(const ConvDxGrid *grids, int n_grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q);

@@ -1609,6 +1609,7 @@ struct TransposeJob {
     unsigned int *col_abs;
     int tiles_per_block;
     int blocks_r, blocks;      // blocks along the rows, and in all
+    bool fragments;            // 1 KB for 32 rows of 32 columns, [half of the rows][column][16], those of 32 columns one after the other (ldd * 32 bytes)
 };
 
 constexpr int kTrRows = 128, kTrCols = 128;
@@ -1704,7 +1705,9 @@ __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int blo
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int col = c0 + 4 * cg + b;
-            if (col < cols) *reinterpret_cast<uint4 *>(dst + (int64_t)col * ldd + rt * kTrRows + 16 * rg) = uint4{o[b][0], o[b][1], o[b][2], o[b][3]};
+            const int64_t at_col = job.fragments ? (int64_t)(col >> 5) * 32 * ldd + (rt * kTrRows + 16 * (rg & 6)) * 32 + (rg & 1) * 512 + (col & 31) * 16
+                                                 : (int64_t)col * ldd + rt * kTrRows + 16 * rg;
+            if (col < cols) *reinterpret_cast<uint4 *>(dst + at_col) = uint4{o[b][0], o[b][1], o[b][2], o[b][3]};
             // sum of |x| over the four int8 of a word: |x| = |(x + 128) - 128| on the biased bytes
 #pragma unroll
             for (int g = 0; g < 4; ++g) part[b] = __builtin_amdgcn_sad_u8(o[b][g] ^ 0x80808080u, 0x80808080u, part[b]);
@@ -1884,7 +1887,7 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
     L.ss_a = off;    off += align_up((size_t)K * sizeof(unsigned int), 256);   // sums of |a_idx| per column, directly followed by
     L.ss_b = off;    off += align_up((size_t)K * sizeof(unsigned int), 256);   // sums of |b_idx| per column (cleared together)
     L.scalars = off; off += kQuantScalarBytes;     // the quantizers' backward passes that follow in the same call
-    L.bt = off;      off += align_up((size_t)K * (size_t)L.ldn, 256);           // b_idx^T: [K][ldn]
+    L.bt = off;      off += align_up((size_t)pad_to(K, 32) * (size_t)L.ldn, 256);           // b_idx^T: [K][ldn], or in fragments (limb_by_rows)
     L.at = off;      off += align_up((size_t)K * (size_t)L.ldm, 256);           // a_idx^T: [K][ldm]
     L.partial = off; off += align_up((size_t)(L.splits > L.direct_splits ? L.splits : L.direct_splits) * (size_t)N * (size_t)K * sizeof(double), 256);
     // operands stored with an offset: one correction per output row of either product, and the per-block column sums of g
@@ -1949,11 +1952,20 @@ int launch_limb_gemm(LimbArgs a, bool trans, hipStream_t stream)
 
 // Whether the two products go into one launch: their blocks (in tiles of 384 columns) are at most four for every compute
 // unit, and those of the first product too few for runs of tiles to pay.
-bool limb_pair_serves(const LimbArgs &a, const LimbArgs &b)
+bool limb_pair_serves(int64_t M, int32_t N, int32_t K, int splits)
 {
-    const int64_t tiles_c = (a.cols + limb_cols(5) - 1) / limb_cols(5);
-    const int64_t na = a.tiles_r * tiles_c, nb = b.tiles_r * tiles_c * b.splits;
+    const int64_t tiles_c = (K + limb_cols(5) - 1) / limb_cols(5);
+    const int64_t na = (M + kLRows - 1) / kLRows * tiles_c, nb = (int64_t)((N + kLRows - 1) / kLRows) * tiles_c * splits;
     return na <= 512 && na + nb <= 1024;
+}
+
+// Whether dL/dQ(a) goes through limb_rows_kernel where that serves (by sizes alone, whatever is asked for): not where both products fit
+// one launch in one or two tiles of 384 columns with little padding, us a call: 9000 x 384 x 384 51.1 / 46.1, 4000 x 320 x 768 45.5 / 42.8,
+// 8000 x 128 x 384 38.4 / 36.2; but 9000 x 384 x 512 51.0 / 54.3, 3000 x 384 x 1500 57.1 / 64.5, 3000 x 256 x 2304 51.9 / 62.2.
+bool limb_by_rows(int64_t M, int32_t N, int32_t K, int splits)
+{
+    const int padded = (K + limb_cols(5) - 1) / limb_cols(5) * limb_cols(5);
+    return limb_rows_serves(M, N, K) && !(padded <= 2 * limb_cols(5) && padded * 10 <= K * 11 && limb_pair_serves(M, N, K, splits));
 }
 
 int launch_limb_pair(LimbArgs a, LimbArgs b, hipStream_t stream)
@@ -1969,13 +1981,13 @@ int launch_limb_pair(LimbArgs a, LimbArgs b, hipStream_t stream)
 }
 
 // about a thousand blocks where the matrix has that many tiles, each with up to 16 row tiles of its columns
-TransposeJob transpose_job(const int8_t *src, int rows, int cols, int8_t *dst, int64_t ldd, unsigned int *col_abs)
+TransposeJob transpose_job(const int8_t *src, int rows, int cols, int8_t *dst, int64_t ldd, unsigned int *col_abs, bool fragments = false)
 {
     const int row_tiles = (rows + kTrRows - 1) / kTrRows, col_tiles = (cols + kTrCols - 1) / kTrCols;
     int per = (int)(((int64_t)row_tiles * col_tiles + 1023) / 1024);
     per = per < 1 ? 1 : (per > 16 ? 16 : per);
     const int blocks_r = (row_tiles + per - 1) / per;
-    return TransposeJob{src, rows, cols, dst, ldd, col_abs, per, blocks_r, blocks_r * col_tiles};
+    return TransposeJob{src, rows, cols, dst, ldd, col_abs, per, blocks_r, blocks_r * col_tiles, fragments};
 }
 
 // Column sums and transposed copies of the operands, and from them the plan (whatever `p` asks for).
@@ -2360,6 +2372,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     if (!cw && bwd_direct_serves(M, N, K, only_b, partial, L.direct_splits, !is_conv_weights))
         return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.direct_splits, only_b, !is_conv_weights, stream);
 
+    const bool by_rows = d_a_hat && limb_by_rows(M, N, K, L.splits);
     int8_t *bt = reinterpret_cast<int8_t *>(base + L.bt);
     int8_t *at = reinterpret_cast<int8_t *>(base + L.at);
 
@@ -2372,7 +2385,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         // the larger operand first: what is left when its blocks run out is the smaller one's
         TransposeJob ja{}, jb{};
         if (want_db) ja = transpose_job(a_idx, M, K, at, L.ldm, ss_a);
-        if (d_a_hat) (want_db ? jb : ja) = transpose_job(b_idx, N, K, bt, L.ldn, ss_b);
+        if (d_a_hat) (want_db ? jb : ja) = transpose_job(b_idx, N, K, bt, L.ldn, ss_b, by_rows);
         const PlanArgs pa{plan, block_max, L.n_max, ss_a, ss_b, want_db ? K : 0, d_a_hat ? K : 0, delta_a, delta_b, nullptr, 0ull};
         ConvGeom g{};
         if (cw) {
@@ -2423,7 +2436,10 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     pb.which = 1;
     pb.out = d_b_hat; pb.partial = partial;
     pb.row_corr = corr_db;
-    if (d_a_hat && want_db && limb_pair_serves(pa, pb)) {
+    if (by_rows) {
+        rc = launch_limb_rows(gr, bt, 32 * L.ldn, M, N, K, plan, corr_da, d_a_hat, stream);
+        if (rc == CDL_OK && want_db) rc = launch_limb_gemm(pb, true, stream);
+    } else if (d_a_hat && want_db && limb_pair_serves(M, N, K, L.splits)) {
         rc = launch_limb_pair(pa, pb, stream);
     } else {
         if (d_a_hat) rc = launch_limb_gemm(pa, false, stream);

@@ -35,10 +35,6 @@ struct RowsArgs {
     float *out;
 };
 
-// Outputs beyond the memory-side cache (256 MiB) are stored past the caches: 50176 x 256 x 2304 160 -> 150 us; below it the pass that
-// follows finds them there (a step on 100000 x 64 x 288: 229 us against 233).
-constexpr int64_t kRowsStreamFrom = 64ll << 20;
-
 // rows of g whose digits fit: 64, or 32
 constexpr int rows_row_bytes(int nk) { return 32 * nk + 16; }      // (an odd multiple of 16: no bank conflicts)
 constexpr bool rows_fit(int rows, int nk, int limbs) { return kRowsFixed + rows * rows_row_bytes(nk) * limbs <= kRowsLds; }
@@ -265,7 +261,7 @@ int launch_limb_rows(const float *g, const int8_t *frag, int64_t tile_bytes, int
     a.frag = frag; a.tile_bytes = tile_bytes;
     a.nk = (N + 63) / 64 * 2;
     a.plan = plan; a.row_corr = row_corr; a.out = out;
-    const bool stream_out = (int64_t)M * K > kRowsStreamFrom;
+    const bool stream_out = stream_output((int64_t)M * K, K, out);      // (50176 x 256 x 2304 160 -> 150 us)
 #define CDL_PICK(NB) (stream_out ? limb_rows_kernel<NB, true> : limb_rows_kernel<NB, false>)
     const auto kernel = a.nk % 8 == 0 ? CDL_PICK(8) : a.nk % 6 == 0 ? CDL_PICK(6) : a.nk % 4 == 0 ? CDL_PICK(4) : CDL_PICK(2);
 #undef CDL_PICK

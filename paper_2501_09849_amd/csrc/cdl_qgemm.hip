@@ -257,126 +257,176 @@ static_assert(limb_stage_bytes(3) <= limb_stage_bytes(5) && limb_stage_bytes(4) 
 __device__ __forceinline__ int lswz(int row) { return (row >> 1) & 7; }
 
 
-// Forward product, fast path for contraction lengths that are multiples of 128: 512 threads = 2 x 4 waves,
-// 256 x 256 block tile (wave tile 128 x 64: eight 32x32 accumulators), K-tiles of 128 bytes brought in by
-// direct global->LDS loads (no staging registers) into two LDS stages of 64 KiB, 16-byte chunks XOR-swizzled
-// over the eight chunks of a row so that the fragment reads are free of bank conflicts.  The barrier is a
-// bare s_barrier with the one wait it needs written out: the loads of the next tile are issued right after
-// it and have the whole K-tile of MFMAs to land.
-constexpr int kFBK = 128;
+// Forward product, fast path for contraction lengths that are multiples of 64: 512 threads = 2 x 4 waves, 256 x 256 tiles
+// (wave tile 128 x 64: eight 32x32 accumulators).  One block per compute unit takes tile after tile as ONE sequence of K-tiles of 64
+// bytes, brought in by direct global->LDS loads (no staging registers) through a ring of five stages of 32 KiB, four of them under way;
+// 16-byte chunks XOR-swizzled over the four chunks of a row so that the fragment reads are free of bank conflicts.  The
+// barrier is a bare s_barrier with the one wait it needs written out.
+// What bounds it: for large outputs the stores (65536 x 3072 x 768: 805 MB in 219 us, the matrix cores 28 % busy), otherwise the trips of a
+// K-tile's loads.  With a block for each tile and one K-tile under way every tile began with an empty pipeline and a K-tile
+// took a trip to memory (that size 286 us, without its stores still 252; 100000 x 512 x 128 51 -> 37, 60000 x 1500 x 1024 about 200 -> 160,
+// 65536 x 1024 x 256 63 -> 54).
+constexpr int kFBK = 128;                 // (K-tile of the convolution)
 constexpr int kFThreads = 512;
 constexpr int kFTile = 256;
 constexpr int kFStage = 2 * kFTile * kFBK;
 constexpr int kFLdsBytes = 2 * kFStage;
+constexpr int kRing = 5, kRingBK = 64, kRingStage = 2 * kFTile * kRingBK, kRingLdsBytes = kRing * kRingStage;
 
+template <bool STREAM>
 __global__ __launch_bounds__(kFThreads, 1)
 void qgemm_dma_kernel(GemmArgs a)
 {
-    constexpr int WN = 4, TM = 4, TN = 2, CH = kFBK / 16, KS = kFBK / 32;
-    constexpr int WL = kFTile * CH / 64 / 8;      // wave-level loads per wave, per operand and K-tile: 4
+    constexpr int WN = 4, TM = 4, TN = 2, KS = kRingBK / 32, AHEAD = kRing - 1;
+    constexpr int WL = kFTile / 16 / 8;      // loads per wave, per operand and K-tile: 2, each of 16 rows
     extern __shared__ __attribute__((aligned(16))) int8_t flds[];
-
-    const int total = a.tiles_m * a.tiles_n;
-    const int per_xcd = (int)gridDim.x >> 3;
-    const int logical = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
-    if (logical >= total) return;
-    const int tile_m = logical / a.tiles_n, tile_n = logical % a.tiles_n;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
 
-    // wave-level load i of this wave fills LDS slots (wave * WL + i) * 64 + lane: row slot / 8, chunk slot % 8
-    const int8_t *ga[WL];
-    const int8_t *gb[WL];
+    // Workgroups go to the eight XCDs round-robin; XCD x takes the x-th eighth of the tiles, its blocks side by side through them
+    // (tiles of one A row-block meet in one L2).
+    const int total = a.tiles_m * a.tiles_n, share = (total + 7) >> 3, xcd = (int)blockIdx.x & 7, each = (int)gridDim.x >> 3;
+    const int first = xcd * share + ((int)blockIdx.x >> 3), end = min(total, (xcd + 1) * share);
+    if (first >= end) return;
+    const int tiles = (end - 1 - first) / each + 1, nk = a.Kc / kRingBK, steps = tiles * nk;
+
+    // load i of this wave fills LDS slots (wave * WL + i) * 64 + lane: row slot / 4, chunk slot % 4
+    const int lrow = wave * WL * 16 + (lane >> 2), chunk = swz(lane >> 2, lane & 3) * 16;      // (rows 16 apart swizzle alike)
+    const int8_t *src_a, *src_b;             // of the next K-tile to load (uniform)
+    uint32_t off_a[WL], off_b[WL];
+    int load_tile = first, load_kt = 0;
+    auto tile_sources = [&]() {
+        const int m = load_tile / a.tiles_n, n = load_tile - m * a.tiles_n;
+        src_a = a.A + (int64_t)m * kFTile * a.lda;
+        src_b = a.B + (int64_t)n * kFTile * a.ldb;
 #pragma unroll
-    for (int i = 0; i < WL; ++i) {
-        const int sidx = (wave * WL + i) * 64 + lane, row = sidx / CH;
-        const int q = (sidx % CH) ^ lswz(row);
-        ga[i] = a.A + (int64_t)min(tile_m * kFTile + row, a.rowsA - 1) * a.lda + q * 16;
-        gb[i] = a.B + (int64_t)min(tile_n * kFTile + row, a.rowsB - 1) * a.ldb + q * 16;
-    }
-    int ra[TM], rb[TN], sa[TM], sb[TN];
+        for (int i = 0; i < WL; ++i) {
+            off_a[i] = (uint32_t)min(lrow + 16 * i, a.rowsA - 1 - m * kFTile) * (uint32_t)a.lda + (uint32_t)chunk;
+            off_b[i] = (uint32_t)min(lrow + 16 * i, a.rowsB - 1 - n * kFTile) * (uint32_t)a.ldb + (uint32_t)chunk;
+        }
+    };
+    auto issue = [&](int stage) {
+        int8_t *base = flds + stage * kRingStage + wave * WL * 1024;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int row = (wm * TM + i) * 32 + (lane & 31);
-        ra[i] = row * kFBK;
-        sa[i] = lswz(row);
-    }
+        for (int i = 0; i < WL; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_a + off_a[i]), (lptr_t)(base + i * 1024), 16, 0, 0);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int row = (wn * TN + j) * 32 + (lane & 31);
-        rb[j] = kFTile * kFBK + row * kFBK;
-        sb[j] = lswz(row);
-    }
+        for (int i = 0; i < WL; ++i)
+            __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(base + kFTile * kRingBK + i * 1024), 16, 0, 0);
+        src_a += kRingBK;
+        src_b += kRingBK;
+        if (++load_kt == nk) {
+            load_kt = 0;
+            load_tile = min(load_tile + each, total - 1);
+            tile_sources();
+        }
+    };
+    const int frow = lane & 31;
+    int fr[KS];                               // (rows 32 apart swizzle alike)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fr[ks] = frow * kRingBK + swz(frow, 2 * ks + (lane >> 5)) * 16;
+    const int fa_at = wm * TM * 32 * kRingBK, fb_at = (kFTile + wn * TN * 32) * kRingBK;
 
     v16i acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-
-    const int nk = a.Kc / kFBK;
-    auto issue = [&](int kt) {
-        int8_t *base = flds + (kt & 1) * kFStage;
-        const int64_t off = (int64_t)kt * kFBK;
-#pragma unroll
-        for (int i = 0; i < WL; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(ga[i] + off), (lptr_t)(base + (wave * WL + i) * 1024), 16, 0, 0);
-#pragma unroll
-        for (int i = 0; i < WL; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(gb[i] + off), (lptr_t)(base + kFTile * kFBK + (wave * WL + i) * 1024), 16, 0, 0);
-    };
-
-    issue(0);
-    for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // tile kt has landed (nothing younger is in flight)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();               // ... for every wave, and every wave has left the other stage
-        asm volatile("" ::: "memory");
-        if (kt + 1 < nk) issue(kt + 1);
-        const int8_t *base = flds + (kt & 1) * kFStage;
+    auto multiply = [&](int stage, auto first_c) {
+        constexpr bool FIRST = decltype(first_c)::value;
+        const int8_t *base = flds + stage * kRingStage;
+        const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             v4i fa[TM], fb[TN];
-            const int q = 2 * ks + (lane >> 5);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const v4i *>(base + ra[i] + ((q ^ sa[i]) << 4));
+            for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const v4i *>(base + fa_at + i * 32 * kRingBK + fr[ks]);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const v4i *>(base + rb[j] + ((q ^ sb[j]) << 4));
+            for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const v4i *>(base + fb_at + j * 32 * kRingBK + fr[ks]);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], FIRST && ks == 0 ? zero : acc[i][j], 0, 0, 0);
         }
-    }
-
-    const bool full = (tile_m + 1) * kFTile <= a.rowsA && (tile_n + 1) * kFTile <= a.rowsB;
-    // (CORR: operands stored with an offset; kept out of the common path, see qgemm_kernel)
-    auto epilogue = [&](auto corr_c) {
-        constexpr bool CORR = decltype(corr_c)::value;
+    };
+    // CORR: operands stored with an offset, corrections per column and row (a copy of its own: a load between the stores makes
+    // every store wait for the one before it)
+    auto emit = [&](auto full_c, auto corr_c, auto *out, int row0, int col0) {
+        constexpr bool FULL = decltype(full_c)::value, CORR = decltype(corr_c)::value;
+        using T = std::remove_pointer_t<decltype(out)>;
+        typedef T __attribute__((address_space(1))) *out_t;
+        typedef char __attribute__((address_space(1))) *byte_t;
+        int elane = lane;
+        asm volatile("" : "+v"(elane));      // (addresses formed here, not kept in registers through the loop)
+        const int half4 = 4 * (elane >> 5), ecol = elane & 31;
+        const uint32_t off = 4u * (uint32_t)(half4 * (int)a.ldc + ecol);
+        const out_t base = (out_t)out + (int64_t)row0 * a.ldc + col0;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int col = tile_n * kFTile + (wn * TN + j) * 32 + (lane & 31);
-                const int cc = (CORR && a.corr_col && col < a.rowsB) ? a.corr_col[col] : 0;
+            for (int r = 0; r < 16; ++r) {
+                const int dr = i * 32 + 8 * (r >> 2) + (r & 3);
+                out_t at = base + (int64_t)dr * a.ldc;
+                asm("" : "+s"(at));          // (a base in scalar registers and the lane's offset)
+                const out_t p = (out_t)((byte_t)at + off);
+                const bool row_ok = FULL || row0 + dr + half4 < a.rowsA;
+                const int rc = CORR && a.corr_row && row_ok ? a.corr_row[row0 + dr + half4] : 0;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = tile_m * kFTile + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    if (full || (row < a.rowsA && col < a.rowsB)) {
-                        const int64_t o = (int64_t)row * a.ldc + col;
-                        const int v = CORR ? acc[i][j][r] + cc + (a.corr_row ? a.corr_row[row] : 0) : acc[i][j][r];
-                        if (a.acc_out) a.acc_out[o] = v;
-                        if (a.y_out) a.y_out[o] = a.scale * (float)v;
-                    }
+                for (int j = 0; j < TN; ++j) {
+                    const bool ok = FULL || (row_ok && col0 + ecol + 32 * j < a.rowsB);
+                    if (!ok) continue;
+                    const int v = CORR ? acc[i][j][r] + rc + (a.corr_col ? a.corr_col[col0 + ecol + 32 * j] : 0) : acc[i][j][r];
+                    const T x = std::is_same<T, float>::value ? (T)(a.scale * (float)v) : (T)v;
+                    if (FULL && STREAM) __builtin_nontemporal_store(x, p + 32 * j);
+                    else p[32 * j] = x;
                 }
             }
     };
-    if (a.corr_col || a.corr_row) epilogue(std::true_type{});
-    else epilogue(std::false_type{});
+    auto epilogue = [&](int tile) {
+        const int m = tile / a.tiles_n, n = tile - m * a.tiles_n, row0 = m * kFTile + wm * TM * 32, col0 = n * kFTile + wn * TN * 32;
+        const bool full = row0 + TM * 32 <= a.rowsA && col0 + TN * 32 <= a.rowsB, corr = a.corr_col || a.corr_row;
+        auto all = [&](auto full_c, auto corr_c) {
+            if (a.acc_out) emit(full_c, corr_c, a.acc_out, row0, col0);
+            if (a.y_out) emit(full_c, corr_c, a.y_out, row0, col0);
+        };
+        if (full && !corr) {
+            all(std::true_type{}, std::false_type{});
+        } else {
+            if (corr) all(std::false_type{}, std::true_type{});
+            else all(std::false_type{}, std::false_type{});
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // (fewer than 128 stores, see below)
+        }
+    };
+
+    tile_sources();
+    for (int s = 0; s < AHEAD; ++s) issue(s);              // (past the last step: the last tile again, which nobody reads)
+    int stage = 0, kt = 0, tile = first;
+    for (int s = 0; s < steps; ++s) {
+        // This step's loads have landed; younger are those of three steps, and where a tile ended since they were asked for its
+        // 128 stores or more: loads and stores are counted together, up to 63, in order.
+        if (s >= nk && kt < AHEAD) __builtin_amdgcn_s_waitcnt(vmcnt_imm(63));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 1) * 2 * WL));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();                      // ... for every wave, and every wave has left the stage before
+        asm volatile("" ::: "memory");
+        issue(stage == 0 ? kRing - 1 : stage - 1);
+        if (kt == 0) multiply(stage, std::true_type{});
+        else multiply(stage, std::false_type{});
+        stage = stage + 1 == kRing ? 0 : stage + 1;
+        if (++kt == nk) {
+            epilogue(tile);
+            kt = 0;
+            tile += each;
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));              // the loads behind the last step write LDS: done before this wave ends
+}
+
+// Contraction lengths that are whole K-tiles, and enough rows: where the rounds of 256 x 256 tiles, one a compute unit, take no longer
+// than those of 256 x 128 tiles, two a compute unit - a round 1.25 times as long, 0.85 with one.  us, this kernel / that one, K = 1024: 24000 rows x
+// 640 columns 41.5 / 30.6, x 512 24.3 / 29.4, x 256 21.0 / 19.4; 9000 x 640 23.2 / 19.5, x 1000 25.0 / 28.6; 60000 x 1000 104 / 133.
+bool dma_serves(int64_t M, int64_t N, int64_t K)
+{
+    // (32-bit offsets inside a tile)
+    if (K % kRingBK != 0 || M * N < (int64_t)kFTile * kFTile * 64 || N <= 128 || K >= 1 << 23 || N >= 1 << 27) return false;
+    const int64_t rows = (M + 255) / 256, here = (rows * ((N + 255) / 256) + 255) / 256, other = rows * ((N + 127) / 128), rest = other % 512;
+    return here * 100 <= other / 512 * 125 + (rest == 0 ? 0 : rest <= 256 ? 85 : 125);
 }
 
 int launch_gemm_dma(GemmArgs a, hipStream_t stream)
@@ -385,10 +435,14 @@ int launch_gemm_dma(GemmArgs a, hipStream_t stream)
     a.tiles_n = (a.rowsB + kFTile - 1) / kFTile;
     const int64_t total = (int64_t)a.tiles_m * a.tiles_n;
     if (total == 0) return CDL_OK;
-    const int64_t grid = (total + 7) / 8 * 8;
-    const hipError_t e = hipFuncSetAttribute((const void *)qgemm_dma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFLdsBytes);
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
+        n_cu = 256;
+    const int64_t grid = total < n_cu ? (total + 7) / 8 * 8 : n_cu / 8 * 8;
+    const auto kernel = stream_output((int64_t)a.rowsA * a.rowsB, a.rowsB, a.y_out) && !a.acc_out ? qgemm_dma_kernel<true> : qgemm_dma_kernel<false>;
+    const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsBytes);
     if (e != hipSuccess) return hip_failed(e);
-    CDL_LAUNCH("qgemm_kernel(fwd)", stream, qgemm_dma_kernel, dim3((unsigned)grid), dim3(kFThreads), kFLdsBytes, a);
+    CDL_LAUNCH("qgemm_kernel(fwd)", stream, kernel, dim3((unsigned)grid), dim3(kFThreads), kRingLdsBytes, a);
     return check_launch();
 }
 
@@ -2077,10 +2131,7 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
     }
     g.acc_out = acc; g.y_out = y; g.ldc = N;
     g.scale = delta_a * delta_b;
-    // contraction lengths that are whole 128-byte K-tiles take the direct-load kernel (a tile grid of 256 x 256
-    // needs enough rows to be worth it)
-    // (up to 128 output columns would leave half of its 256-column tile empty)
-    if (g.Kc % kFBK == 0 && (int64_t)M * N >= (int64_t)kFTile * kFTile * 64 && N > 128) return launch_gemm_dma(g, stream);
+    if (dma_serves(M, N, g.Kc)) return launch_gemm_dma(g, stream);
     // (up to 64 output columns: tiles 64 columns wide, so that half of a wider one is not padding; fewer tiles of 256
     // rows than compute units: tiles of 128 rows, twice as many blocks)
     const bool few = (int64_t)((M + 255) / 256) * ((N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128)) < 256 && M > 128;

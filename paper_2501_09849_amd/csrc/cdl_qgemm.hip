@@ -265,20 +265,23 @@ __device__ __forceinline__ int lswz(int row) { return (row >> 1) & 7; }
 // What bounds it: for large outputs the stores (65536 x 3072 x 768: 805 MB in 219 us, the matrix cores 28 % busy), otherwise the trips of a
 // K-tile's loads.  With a block for each tile and one K-tile under way every tile began with an empty pipeline and a K-tile
 // took a trip to memory (that size 286 us, without its stores still 252; 100000 x 512 x 128 51 -> 37, 60000 x 1500 x 1024 about 200 -> 160,
-// 65536 x 1024 x 256 63 -> 54).
-constexpr int kFBK = 128;                 // (K-tile of the convolution)
+// 65536 x 1024 x 256 63 -> 54).  A step's first fragments are read behind the products of the step before (8192 x 3072 x 3072
+// 101 -> 93).
 constexpr int kFThreads = 512;
 constexpr int kFTile = 256;
-constexpr int kFStage = 2 * kFTile * kFBK;
-constexpr int kFLdsBytes = 2 * kFStage;
 constexpr int kRing = 5, kRingBK = 64, kRingStage = 2 * kFTile * kRingBK, kRingLdsBytes = kRing * kRingStage;
 
-template <bool STREAM>
-__global__ __launch_bounds__(kFThreads, 1)
-void qgemm_dma_kernel(GemmArgs a)
+// load i of a wave and operand fills LDS slots (wave * kRingLoads + i) * 64 + lane: row slot / 4, chunk slot % 4
+constexpr int kRingLoads = kFTile / 16 / 8;
+__device__ __forceinline__ int ring_row(int wave, int lane, int i) { return (wave * kRingLoads + i) * 16 + (lane >> 2); }
+__device__ __forceinline__ int ring_chunk(int lane) { return swz(lane >> 2, lane & 3) * 16; }      // (rows 16 apart swizzle alike)
+
+// SOURCE: where a wave's loads come from - tile(m, n, ...) the first K-tile of a tile, issue() the loads of a K-tile and on to the next
+template <bool STREAM, class SOURCE>
+__device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, int nk)
 {
     constexpr int WN = 4, TM = 4, TN = 2, KS = kRingBK / 32, AHEAD = kRing - 1;
-    constexpr int WL = kFTile / 16 / 8;      // loads per wave, per operand and K-tile: 2, each of 16 rows
+    constexpr int WL = kRingLoads;
     extern __shared__ __attribute__((aligned(16))) int8_t flds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -288,32 +291,15 @@ void qgemm_dma_kernel(GemmArgs a)
     const int total = a.tiles_m * a.tiles_n, share = (total + 7) >> 3, xcd = (int)blockIdx.x & 7, each = (int)gridDim.x >> 3;
     const int first = xcd * share + ((int)blockIdx.x >> 3), end = min(total, (xcd + 1) * share);
     if (first >= end) return;
-    const int tiles = (end - 1 - first) / each + 1, nk = a.Kc / kRingBK, steps = tiles * nk;
+    const int tiles = (end - 1 - first) / each + 1, steps = tiles * nk;
 
-    // load i of this wave fills LDS slots (wave * WL + i) * 64 + lane: row slot / 4, chunk slot % 4
-    const int lrow = wave * WL * 16 + (lane >> 2), chunk = swz(lane >> 2, lane & 3) * 16;      // (rows 16 apart swizzle alike)
-    const int8_t *src_a, *src_b;             // of the next K-tile to load (uniform)
-    uint32_t off_a[WL], off_b[WL];
     int load_tile = first, load_kt = 0;
     auto tile_sources = [&]() {
         const int m = load_tile / a.tiles_n, n = load_tile - m * a.tiles_n;
-        src_a = a.A + (int64_t)m * kFTile * a.lda;
-        src_b = a.B + (int64_t)n * kFTile * a.ldb;
-#pragma unroll
-        for (int i = 0; i < WL; ++i) {
-            off_a[i] = (uint32_t)min(lrow + 16 * i, a.rowsA - 1 - m * kFTile) * (uint32_t)a.lda + (uint32_t)chunk;
-            off_b[i] = (uint32_t)min(lrow + 16 * i, a.rowsB - 1 - n * kFTile) * (uint32_t)a.ldb + (uint32_t)chunk;
-        }
+        source.tile(m, n, wave, lane);
     };
     auto issue = [&](int stage) {
-        int8_t *base = flds + stage * kRingStage + wave * WL * 1024;
-#pragma unroll
-        for (int i = 0; i < WL; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_a + off_a[i]), (lptr_t)(base + i * 1024), 16, 0, 0);
-#pragma unroll
-        for (int i = 0; i < WL; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(base + kFTile * kRingBK + i * 1024), 16, 0, 0);
-        src_a += kRingBK;
-        src_b += kRingBK;
+        source.issue(flds + stage * kRingStage + wave * WL * 1024);
         if (++load_kt == nk) {
             load_kt = 0;
             load_tile = min(load_tile + each, total - 1);
@@ -326,24 +312,23 @@ void qgemm_dma_kernel(GemmArgs a)
     for (int ks = 0; ks < KS; ++ks) fr[ks] = frow * kRingBK + swz(frow, 2 * ks + (lane >> 5)) * 16;
     const int fa_at = wm * TM * 32 * kRingBK, fb_at = (kFTile + wn * TN * 32) * kRingBK;
 
+    static_assert(KS == 2, "fragments of two k-steps");
     v16i acc[TM][TN];
-    auto multiply = [&](int stage, auto first_c) {
-        constexpr bool FIRST = decltype(first_c)::value;
+    v4i fa[2][TM], fb[2][TN];
+    auto read = [&](int stage, int ks) {
         const int8_t *base = flds + stage * kRingStage;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[ks][i] = *reinterpret_cast<const v4i *>(base + fa_at + i * 32 * kRingBK + fr[ks]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[ks][j] = *reinterpret_cast<const v4i *>(base + fb_at + j * 32 * kRingBK + fr[ks]);
+    };
+    auto multiply = [&](int ks, auto first_c) {
+        constexpr bool FIRST = decltype(first_c)::value;
         const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            v4i fa[TM], fb[TN];
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const v4i *>(base + fa_at + i * 32 * kRingBK + fr[ks]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const v4i *>(base + fb_at + j * 32 * kRingBK + fr[ks]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], FIRST && ks == 0 ? zero : acc[i][j], 0, 0, 0);
-        }
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks][i], fb[ks][j], FIRST ? zero : acc[i][j], 0, 0, 0);
     };
     // CORR: operands stored with an offset, corrections per column and row (a copy of its own: a load between the stores makes
     // every store wait for the one before it)
@@ -396,19 +381,29 @@ void qgemm_dma_kernel(GemmArgs a)
 
     tile_sources();
     for (int s = 0; s < AHEAD; ++s) issue(s);              // (past the last step: the last tile again, which nobody reads)
+    auto barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 1) * 2 * WL));
+    barrier();
+    read(0, 0);
     int stage = 0, kt = 0, tile = first;
     for (int s = 0; s < steps; ++s) {
-        // This step's loads have landed; younger are those of three steps, and where a tile ended since they were asked for its
-        // 128 stores or more: loads and stores are counted together, up to 63, in order.
-        if (s >= nk && kt < AHEAD) __builtin_amdgcn_s_waitcnt(vmcnt_imm(63));
-        else __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 1) * 2 * WL));
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();                      // ... for every wave, and every wave has left the stage before
-        asm volatile("" ::: "memory");
+        // The next step's loads have landed, so that its first fragments are read behind this one's products; younger are those of two
+        // steps, and where a tile ended since they were asked for its 128 stores or more: loads and stores are counted together, up to 63, in order.
+        if (s >= nk && kt < AHEAD - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(63));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 2) * 2 * WL));
+        barrier();                                         // ... for every wave, and every wave has left the stage before
+        const int next = stage + 1 == kRing ? 0 : stage + 1;
         issue(stage == 0 ? kRing - 1 : stage - 1);
-        if (kt == 0) multiply(stage, std::true_type{});
-        else multiply(stage, std::false_type{});
-        stage = stage + 1 == kRing ? 0 : stage + 1;
+        read(stage, 1);
+        if (kt == 0) multiply(0, std::true_type{});
+        else multiply(0, std::false_type{});
+        read(next, 0);
+        multiply(1, std::false_type{});
+        stage = next;
         if (++kt == nk) {
             epilogue(tile);
             kt = 0;
@@ -416,6 +411,40 @@ void qgemm_dma_kernel(GemmArgs a)
         }
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));              // the loads behind the last step write LDS: done before this wave ends
+}
+
+struct MatrixSource {
+    const GemmArgs &a;
+    const int8_t *src_a, *src_b;             // of the next K-tile (uniform)
+    uint32_t off_a[kRingLoads], off_b[kRingLoads];
+    __device__ __forceinline__ void tile(int m, int n, int wave, int lane)
+    {
+        src_a = a.A + (int64_t)m * kFTile * a.lda;
+        src_b = a.B + (int64_t)n * kFTile * a.ldb;
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i) {
+            off_a[i] = (uint32_t)min(ring_row(wave, lane, i), a.rowsA - 1 - m * kFTile) * (uint32_t)a.lda + (uint32_t)ring_chunk(lane);
+            off_b[i] = (uint32_t)min(ring_row(wave, lane, i), a.rowsB - 1 - n * kFTile) * (uint32_t)a.ldb + (uint32_t)ring_chunk(lane);
+        }
+    }
+    __device__ __forceinline__ void issue(int8_t *to)
+    {
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_a + off_a[i]), (lptr_t)(to + i * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i)
+            __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(to + kFTile * kRingBK + i * 1024), 16, 0, 0);
+        src_a += kRingBK;
+        src_b += kRingBK;
+    }
+};
+
+template <bool STREAM>
+__global__ __launch_bounds__(kFThreads, 1)
+void qgemm_dma_kernel(GemmArgs a)
+{
+    MatrixSource source{a};
+    ring_tiles<STREAM>(a, source, a.Kc / kRingBK);
 }
 
 // Contraction lengths that are whole K-tiles, and enough rows: where the rounds of 256 x 256 tiles, one a compute unit, take no longer
@@ -429,16 +458,21 @@ bool dma_serves(int64_t M, int64_t N, int64_t K)
     return here * 100 <= other / 512 * 125 + (rest == 0 ? 0 : rest <= 256 ? 85 : 125);
 }
 
+int64_t ring_grid(int64_t tiles)
+{
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
+        n_cu = 256;
+    return tiles < n_cu ? (tiles + 7) / 8 * 8 : n_cu / 8 * 8;
+}
+
 int launch_gemm_dma(GemmArgs a, hipStream_t stream)
 {
     a.tiles_m = (a.rowsA + kFTile - 1) / kFTile;
     a.tiles_n = (a.rowsB + kFTile - 1) / kFTile;
     const int64_t total = (int64_t)a.tiles_m * a.tiles_n;
     if (total == 0) return CDL_OK;
-    int dev = 0, n_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
-        n_cu = 256;
-    const int64_t grid = total < n_cu ? (total + 7) / 8 * 8 : n_cu / 8 * 8;
+    const int64_t grid = ring_grid(total);
     const auto kernel = stream_output((int64_t)a.rowsA * a.rowsB, a.rowsB, a.y_out) && !a.acc_out ? qgemm_dma_kernel<true> : qgemm_dma_kernel<false>;
     const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsBytes);
     if (e != hipSuccess) return hip_failed(e);
@@ -488,136 +522,70 @@ __device__ __forceinline__ void conv_store(const ConvArgs &a, int row, int col, 
     if (a.y_out) a.y_out[o] = a.scale * (float)v;
 }
 
-// C a multiple of 128: the structure of qgemm_dma_kernel (256 x 256 tile, K-tiles of 128 bytes by direct
-// global->LDS loads, two stages), a K-tile being 128 channels of one tap.
+// C a multiple of 64: the tiles of qgemm_dma_kernel, a K-tile being 64 channels of one tap.  Where a row's chunk lies is worked out when the tap
+// changes; inside a tap it moves on by 64 channels, or stays on the padding.  us, against a block for every tile with K-tiles of 128 channels: 256 images of
+// 14 x 14 x 320 -> 320, 3 x 3  102 -> 81;  128 x 28 x 28 x 192 -> 192  76 -> 59;  256 x 14 x 14 x 256 -> 256  44.6 -> 43.0.
+struct WindowSource {
+    const ConvArgs &a;
+    const int8_t *src_b;                     // of the next K-tile (uniform)
+    uint32_t off_b[kRingLoads];
+    int h0[kRingLoads], w0[kRingLoads];      // first input row and column of a row's window, and its first chunk
+    int64_t off[kRingLoads];
+    int tr, ts, left;                        // tap of the next K-tile, and K-tiles left in it
+    const int8_t *at[kRingLoads];            // a row's chunk of the next K-tile, or the padding
+    uint32_t on[kRingLoads];
+    __device__ __forceinline__ void tap()
+    {
+        const int64_t tap_off = ((int64_t)tr * a.W + ts) * a.C;
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i) {
+            const bool inside = (unsigned)(h0[i] + tr) < (unsigned)a.H && (unsigned)(w0[i] + ts) < (unsigned)a.W;
+            at[i] = inside ? a.X + (off[i] + tap_off) : a.pad_page;
+            on[i] = inside ? kRingBK : 0;
+        }
+        left = a.C / kRingBK;
+    }
+    __device__ __forceinline__ void tile(int m, int n, int wave, int lane)
+    {
+        src_b = a.Wt + (int64_t)n * kFTile * a.Kc;
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i) {
+            const ConvRow r = conv_row(a, min(m * kFTile + ring_row(wave, lane, i), a.M - 1));
+            h0[i] = r.h0;
+            w0[i] = r.w0;
+            off[i] = r.off + ring_chunk(lane);
+            off_b[i] = (uint32_t)min(ring_row(wave, lane, i), a.N - 1 - n * kFTile) * (uint32_t)a.Kc + (uint32_t)ring_chunk(lane);
+        }
+        tr = ts = 0;
+        tap();
+    }
+    __device__ __forceinline__ void issue(int8_t *to)
+    {
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i) __builtin_amdgcn_global_load_lds((gptr_t)at[i], (lptr_t)(to + i * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i)
+            __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(to + kFTile * kRingBK + i * 1024), 16, 0, 0);
+        src_b += kRingBK;
+#pragma unroll
+        for (int i = 0; i < kRingLoads; ++i) at[i] += on[i];
+        if (--left == 0) {
+            if (++ts == a.S) { ts = 0; ++tr; }
+            tap();                           // (behind the last tap: the next tile follows, or nobody loads from there)
+        }
+    }
+};
+
+template <bool STREAM>
 __global__ __launch_bounds__(kFThreads, 1)
 void qconv_dma_kernel(ConvArgs a)
 {
-    constexpr int WN = 4, TM = 4, TN = 2, CH = kFBK / 16, KS = kFBK / 32;
-    constexpr int WL = kFTile * CH / 64 / 8;
-    extern __shared__ __attribute__((aligned(16))) int8_t flds[];
-
-    const int total = a.tiles_m * a.tiles_n;
-    const int per_xcd = (int)gridDim.x >> 3;
-    const int logical = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
-    if (logical >= total) return;
-    const int tile_m = logical / a.tiles_n, tile_n = logical % a.tiles_n;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-
-    ConvRow xr[WL];
-    const int8_t *gb[WL];
-#pragma unroll
-    for (int i = 0; i < WL; ++i) {
-        const int sidx = (wave * WL + i) * 64 + lane, row = sidx / CH;
-        const int q = (sidx % CH) ^ lswz(row);
-        xr[i] = conv_row(a, min(tile_m * kFTile + row, a.M - 1));
-        xr[i].off += q * 16;
-        gb[i] = a.Wt + (int64_t)min(tile_n * kFTile + row, a.N - 1) * a.Kc + q * 16;
-    }
-    int ra[TM], rb[TN], sa[TM], sb[TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int row = (wm * TM + i) * 32 + (lane & 31);
-        ra[i] = row * kFBK;
-        sa[i] = lswz(row);
-    }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int row = (wn * TN + j) * 32 + (lane & 31);
-        rb[j] = kFTile * kFBK + row * kFBK;
-        sb[j] = lswz(row);
-    }
-
-    v16i acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-
-    const int nk = a.Kc / kFBK;
-    // tap (tr, ts) and first channel tc of the K-tile that `issue` is called with next (called with 0, 1, 2, ...)
-    int tr = 0, ts = 0, tc = 0;
-    // where the rows of the next K-tile are read from: worked out while the MFMAs of the current one run, so that the
-    // loads go out right behind the barrier
-    const int8_t *srcA[WL];
-    auto prepare = [&]() {
-        const int64_t tap_off = ((int64_t)tr * a.W + ts) * a.C + tc;
-#pragma unroll
-        for (int i = 0; i < WL; ++i) {
-            const bool inside = (unsigned)(xr[i].h0 + tr) < (unsigned)a.H && (unsigned)(xr[i].w0 + ts) < (unsigned)a.W;
-            srcA[i] = inside ? a.X + (xr[i].off + tap_off) : a.pad_page;
-        }
-        tc += kFBK;
-        if (tc == a.C) { tc = 0; if (++ts == a.S) { ts = 0; ++tr; } }
-    };
-    auto issue = [&](int kt) {
-        int8_t *base = flds + (kt & 1) * kFStage;
-#pragma unroll
-        for (int i = 0; i < WL; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)srcA[i], (lptr_t)(base + (wave * WL + i) * 1024), 16, 0, 0);
-        const int64_t off = (int64_t)kt * kFBK;
-#pragma unroll
-        for (int i = 0; i < WL; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(gb[i] + off), (lptr_t)(base + kFTile * kFBK + (wave * WL + i) * 1024), 16, 0, 0);
-    };
-
-    prepare();
-    issue(0);
-    if (nk > 1) prepare();
-    for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (kt + 1 < nk) issue(kt + 1);
-        if (kt + 2 < nk) prepare();
-        const int8_t *base = flds + (kt & 1) * kFStage;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            v4i fa[TM], fb[TN];
-            const int q = 2 * ks + (lane >> 5);
-#pragma unroll
-            for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const v4i *>(base + ra[i] + ((q ^ sa[i]) << 4));
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const v4i *>(base + rb[j] + ((q ^ sb[j]) << 4));
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-    }
-
-    const bool full = (tile_m + 1) * kFTile <= a.M && (tile_n + 1) * kFTile <= a.N;
-    // (the corrections of an operand stored with an offset are loaded before the first store and live in a copy of the
-    // epilogue of their own: a load between the stores makes every store wait for the one before it - loads and stores
-    // share one counter - which cost 10 us per round of blocks)
-    auto epilogue = [&](auto corr_c) {
-        constexpr bool CORR = decltype(corr_c)::value;
-        int cc[TN];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = tile_n * kFTile + (wn * TN + j) * 32 + (lane & 31);
-            cc[j] = (CORR && col < a.N) ? a.corr_col[col] : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int col = tile_n * kFTile + (wn * TN + j) * 32 + (lane & 31);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = tile_m * kFTile + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    if (full || (row < a.M && col < a.N)) conv_store(a, row, col, CORR ? acc[i][j][r] + cc[j] : acc[i][j][r]);
-                }
-            }
-    };
-    if (a.corr_col) epilogue(std::true_type{});
-    else epilogue(std::false_type{});
+    GemmArgs out{};
+    out.rowsA = a.M; out.rowsB = a.N; out.ldc = a.N;
+    out.tiles_m = a.tiles_m; out.tiles_n = a.tiles_n;
+    out.acc_out = a.acc_out; out.y_out = a.y_out; out.scale = a.scale; out.corr_col = a.corr_col;
+    WindowSource source{a};
+    ring_tiles<STREAM>(out, source, a.Kc / kRingBK);
 }
 
 // Any C that is a multiple of 16: the structure of qgemm_kernel (256 x 128 tile, 64-byte K steps staged through
@@ -2355,13 +2323,14 @@ int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_
     }
     const uint32_t pb = (uint32_t)(uint8_t)(int8_t)(-x_offset);
     a.pad_word = (int)(pb | (pb << 8) | (pb << 16) | (pb << 24));
-    if (C % kFBK == 0 && (int64_t)a.M * N >= (int64_t)kFTile * kFTile * 64 && N > 128) {
+    if (C % kRingBK == 0 && dma_serves(a.M, N, a.Kc)) {
         a.tiles_m = (a.M + kFTile - 1) / kFTile;
         a.tiles_n = (N + kFTile - 1) / kFTile;
-        const int64_t grid = ((int64_t)a.tiles_m * a.tiles_n + 7) / 8 * 8;
-        const hipError_t e = hipFuncSetAttribute((const void *)qconv_dma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFLdsBytes);
+        const int64_t grid = ring_grid((int64_t)a.tiles_m * a.tiles_n);
+        const auto kernel = stream_output((int64_t)a.M * N, N, y) && !acc ? qconv_dma_kernel<true> : qconv_dma_kernel<false>;
+        const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsBytes);
         if (e != hipSuccess) return hip_failed(e);
-        CDL_LAUNCH("qconv_kernel(fwd)", stream, qconv_dma_kernel, dim3((unsigned)grid), dim3(kFThreads), kFLdsBytes, a);
+        CDL_LAUNCH("qconv_kernel(fwd)", stream, kernel, dim3((unsigned)grid), dim3(kFThreads), kRingLdsBytes, a);
         return check_launch();
     }
     // (tiles of 256 x 128, or 256 x 64 for up to 64 output channels)

@@ -46,3 +46,31 @@ def test_output_beyond_the_caches():
 @pytest.mark.parametrize("oa,ob", [(128, 0), (128, 128), (0, 128)])
 def test_offsets(oa, ob):
     _check(30_001, 700, 192, want_acc=True, oa=oa, ob=ob)
+
+
+@pytest.mark.parametrize("B,H,W,C,N,R,S,stride,pad,off", [
+    (41, 28, 27, 64, 256, 3, 3, 1, 1, 0), (90, 29, 31, 192, 260, 3, 3, 2, 1, 128), (33, 30, 30, 128, 700, 1, 1, 1, 0, 0), (70, 19, 23, 320, 192, 5, 3, 1, 2, 0),
+    (64, 56, 55, 64, 200, 3, 5, 2, 2, 128), (130, 14, 14, 256, 256, 3, 3, 1, 1, 0)])
+def test_windows(B, H, W, C, N, R, S, stride, pad, off):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    gen = torch.Generator(device="cuda").manual_seed(H * W + C)
+    x = torch.randint(-128, 28, (B, H, W, C), device="cuda", generator=gen, dtype=torch.int32).to(torch.int8)
+    w = torch.randint(-128, 128, (N, R, S, C), device="cuda", generator=gen, dtype=torch.int32).to(torch.int8)
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    y, acc = gu.empty((B, P, Q, N), torch.float32), gu.empty((B, P, Q, N), torch.int32)
+    y.fill_(7e7)
+    ws = gu.workspace(cdl.qconv_fwd_workspace_bytes(N, off))
+    for _ in range(2):
+        cdl.cdl_qconv_fwd(x, w, B, H, W, C, N, R, S, stride, pad, 0.3, 0.07, acc, y, ws, x_offset=off)
+    torch.cuda.synchronize()
+    padded = torch.zeros((B, H + 2 * pad, W + 2 * pad, C), dtype=torch.float64, device="cuda")      # (level index 0 outside the image)
+    padded[:, pad:pad + H, pad:pad + W] = x.double() + off
+    want = torch.zeros((B * P * Q, N), dtype=torch.float64, device="cuda")
+    for r in range(R):
+        for s in range(S):
+            tap = padded[:, r:r + stride * (P - 1) + 1:stride, s:s + stride * (Q - 1) + 1:stride].reshape(-1, C)
+            want += tap @ w[:, r, s].double().t().contiguous()
+    want = want.to(torch.int32).reshape(B, P, Q, N)
+    assert torch.equal(acc, want)
+    assert torch.equal(y, want.float() * (torch.tensor(0.3, device="cuda") * torch.tensor(0.07, device="cuda")))

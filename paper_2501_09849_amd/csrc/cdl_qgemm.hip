@@ -274,7 +274,10 @@ constexpr int kRing = 5, kRingBK = 64, kRingStage = 2 * kFTile * kRingBK, kRingL
 // load i of a wave and operand fills LDS slots (wave * kRingLoads + i) * 64 + lane: row slot / 4, chunk slot % 4
 constexpr int kRingLoads = kFTile / 16 / 8;
 __device__ __forceinline__ int ring_row(int wave, int lane, int i) { return (wave * kRingLoads + i) * 16 + (lane >> 2); }
-__device__ __forceinline__ int ring_chunk(int lane) { return swz(lane >> 2, lane & 3) * 16; }      // (rows 16 apart swizzle alike)
+// (sixteen rows read at the same chunk q lie in all sixteen chunks of the 64 banks; with (row >> 1) half the cycles of the reads
+// were conflicts; up to 1 % of the kernel's time)
+__device__ __forceinline__ int ring_swz(int row, int q) { return q ^ ((row >> 2) & 3); }
+__device__ __forceinline__ int ring_chunk(int lane) { return ring_swz(lane >> 2, lane & 3) * 16; }      // (rows 16 apart swizzle alike)
 
 // SOURCE: where a wave's loads come from - tile(m, n, ...) the first K-tile of a tile, issue() the loads of a K-tile and on to the next
 template <bool STREAM, class SOURCE>
@@ -309,7 +312,7 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
     const int frow = lane & 31;
     int fr[KS];                               // (rows 32 apart swizzle alike)
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) fr[ks] = frow * kRingBK + swz(frow, 2 * ks + (lane >> 5)) * 16;
+    for (int ks = 0; ks < KS; ++ks) fr[ks] = frow * kRingBK + ring_swz(frow, 2 * ks + (lane >> 5)) * 16;
     const int fa_at = wm * TM * 32 * kRingBK, fb_at = (kFTile + wn * TN * 32) * kRingBK;
 
     static_assert(KS == 2, "fragments of two k-steps");
@@ -1866,7 +1869,7 @@ struct BwdLayout {
     int64_t ldn, ldm;             // row strides of the transposed index copies (odd multiples of kLBK)
     int nk_n, nk_m;               // K-tiles of the two contractions
     int splits, kt_per_split;     // d_b_hat: splits of the contraction over M
-    int direct_splits;            // the same for the products in double, at most
+    int direct_splits;            // the same for the direct products, at most
 };
 
 BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
@@ -1896,7 +1899,7 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
         const double t = 1.8 * (double)((base * s + slots - 1) / slots * p) + (s > 1 ? (double)s * N * K * 16.0 / 5e6 : 0.0);
         if (least < 0.0 || t < least) { least = t; splits = s; per = p; }
     }
-    // (the products in double: room for about three blocks per compute unit)
+    // (the direct products: room for about three blocks per compute unit)
     L.direct_splits = (int)((768 + base - 1) / base < nk / 4 ? (768 + base - 1) / base : nk / 4);
     if (L.direct_splits < 1) L.direct_splits = 1;
     L.splits = (int)splits;

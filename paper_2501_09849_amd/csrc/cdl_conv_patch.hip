@@ -22,12 +22,6 @@ namespace cdl {
 namespace {
 
 constexpr int kPatchThreads = 256;
-constexpr int kPatchLds = 80 << 10;          // two blocks share a compute unit
-constexpr int kPatchFixed = 64;              // bytes for the reductions
-// At least four limbs.  Where every entry of g has the scale of the largest one of all, three may keep the bound for small ones; here they
-// would be chosen block by block, and a block of small entries next to large ones would be less exact than with the count that the
-// largest asks for (2.5e-8 -> 9e-8 of the norm of the outputs).  Relative to a block's largest entry four leave 2^-32, below the rounding of the fp32 result.
-constexpr int kPatchMinLimbs = 4;
 
 struct PatchClass {
     int oa, oc, Hc, Wc, pad_h, pad_w, Rc, Sc;
@@ -57,12 +51,6 @@ typedef const PatchArgs __attribute__((address_space(4))) *patch_args_t;
 __device__ __forceinline__ float patch_largest(float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); }
 
 struct PatchTile { int row0, col0, lo, count; };
-
-// Four waves: WN = 1, 2, 4 as (4 / WN) x WN, 32 pixels by 64 channels each, of the one class; WN = 0: a wave for each class, 32 grid
-// pixels by 64 channels (four classes read the same patch, and no wave has to load weights behind stores: a wave's loads wait for
-// its older stores, which take microseconds).
-constexpr int patch_rows(int wn) { return wn == 0 ? 32 : 32 * (4 / wn); }
-constexpr int patch_cols(int wn) { return wn == 0 ? 64 : 64 * wn; }
 
 template <int L, int WN>
 __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t, int8_t *lds, double out_scale, float gscale)
@@ -123,7 +111,6 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
     uint32_t bo[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) bo[j] = (uint32_t)min((t.col0 >> 5) + wn * TN + j, (args->C32 >> 5) - 1) * 1024u + (uint32_t)lane * 16u;
-    const int64_t step_bytes = (int64_t)args->C32 * 32;
     const int half = (lane >> 5) * 16;
 
     // (WN = 0: a wave makes its own table)
@@ -152,19 +139,14 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
 
         // k-steps of 32 entries, tap after tap.  The weights of a step are asked for four steps ahead, the row of LDS two, the digits
         // one (more than four limbs leave registers for less).
-        constexpr int NA = L <= 5 ? 2 : 1, NB = L <= 4 ? 4 : (L == 5 ? 2 : 1);
+        constexpr int NA = L <= 5 ? 2 : 1, NB = patch_ahead(L);
         v4i fa[NA][L], fb[NB][TN];
         int row[2], at[2];      // a lane's row of a plane, and the step's first channel (put together where they are used: no wait for the table before)
-        const int8_t *next_b = k.wr + (int64_t)(n0 >> 5) * step_bytes;
-        const int64_t skip = (int64_t)((Np - nc) >> 5) * step_bytes;      // to the next tap's part
-        int in_tap = nc >> 5;
+        PatchWeights weights(n0, nc, Np, args->C32, nk);
         auto load_b = [&](int buf) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j) fb[buf][j] = *reinterpret_cast<const v4i *>(next_b + bo[j]);
-            // (up to four steps behind the last one are read too: the host leaves room for them)
-            --in_tap;
-            next_b += step_bytes + (in_tap == 0 ? skip : 0);
-            in_tap = in_tap == 0 ? nc >> 5 : in_tap;
+            for (int j = 0; j < TN; ++j) fb[buf][j] = *reinterpret_cast<const v4i *>(k.wr + weights.at + bo[j]);
+            weights.next();
         };
         int rt = 0, rn = 0;
         auto load_row = [&](int buf) {
@@ -319,89 +301,6 @@ void limb_conv_patch_kernel(PatchArgs a)
         case 5: patch_body<5, WN>(args, t, patch_lds, out_scale, gscale); break;
         default: patch_body<6, WN>(args, t, patch_lds, out_scale, gscale); break;
     }
-}
-
-// The grid that the classes share, and what a pixel of it reads.
-struct PatchGrid { int Hm, Wm, lo_h, hi_h, lo_w, hi_w; };
-
-PatchGrid patch_grid(const ConvDxGrid *grids, int n)
-{
-    PatchGrid p{0, 0, 1 << 30, -(1 << 30), 1 << 30, -(1 << 30)};
-    auto least = [](int &a, int b) { if (b < a) a = b; };
-    auto most = [](int &a, int b) { if (b > a) a = b; };
-    for (int i = 0; i < n; ++i) {
-        const ConvDxGrid &s = grids[i];
-        most(p.Hm, s.Hc);
-        most(p.Wm, s.Wc);
-        least(p.lo_h, s.pad_h - s.Rc + 1);
-        most(p.hi_h, s.pad_h);
-        least(p.lo_w, s.pad_w - s.Sc + 1);
-        most(p.hi_w, s.pad_w);
-    }
-    return p;
-}
-
-// Pixels of g that a run of `rows` pixels of the grid needs, at most: from what the first one reads first to what the last one reads
-// last, with what g's rows and images have more than the grid's at every end of a row and an image.
-int64_t patch_pixels(const PatchGrid &s, int rows, int P, int Q, int64_t all)
-{
-    const int64_t hw = (int64_t)s.Hm * s.Wm, row_ends = (rows - 2 + s.Wm) / s.Wm, image_ends = (rows - 2 + hw) / hw;
-    int64_t n = rows + (int64_t)(s.hi_h - s.lo_h) * Q + s.hi_w - s.lo_w;
-    if (Q > s.Wm) n += row_ends * (Q - s.Wm);
-    if (P > s.Hm) n += image_ends * (int64_t)(P - s.Hm) * Q;
-    // (pixels beyond the last window: their range begins at the image's last row or pixel instead)
-    if (s.Hm - 1 + s.lo_h > P - 1) n += (int64_t)(s.Hm + s.lo_h - P) * Q;
-    if (s.Wm - 1 + s.lo_w > Q - 1) n += s.Wm + s.lo_w - Q;
-    return n < all ? n : all;
-}
-
-struct PatchPlan {
-    bool served;
-    int wn, px_max, taps;
-    int nc[kMaxLimbs + 1];
-};
-
-// The tile of 32 x 256, 64 x 128 or 128 x 64 outputs that pads the channels least (of equals the widest, which needs the smallest
-// patch; several classes: 32 x 64 of each), and the channels of a patch that fit LDS: all of them or an equal part, a multiple of 32.
-PatchPlan plan_patch(const ConvDxGrid *grids, int n_grids, int64_t B, int P, int Q, int C, int Np)
-{
-    PatchPlan best{};
-    int64_t least = 0;
-    const PatchGrid grid = patch_grid(grids, n_grids);
-    if (n_grids < 1 || B * grid.Hm * grid.Wm > 2147483647LL) return best;
-    for (int wn = n_grids > 1 ? 0 : 4; wn >= 0; wn = wn > 1 ? wn / 2 : -1) {
-        const int rows = patch_rows(wn), cols = patch_cols(wn);
-        const int64_t padded = (int64_t)((C + cols - 1) / cols) * cols;
-        if (best.served && padded >= least) continue;
-        PatchPlan p{};
-        p.served = true;
-        p.wn = wn;
-        for (int i = 0; i < n_grids; ++i)
-            if (grids[i].Rc * grids[i].Sc > p.taps) p.taps = grids[i].Rc * grids[i].Sc;
-        const int64_t px = patch_pixels(grid, rows, P, Q, B * P * Q);
-        if (px > 4096) continue;
-        p.px_max = (int)px;
-        for (int l = kPatchMinLimbs; l <= kMaxLimbs; ++l) {
-            p.nc[l] = 0;
-            for (int parts = 1; parts <= Np / 32 && !p.nc[l]; ++parts)
-                if (Np / 32 % parts == 0 && kPatchFixed + 2ll * n_grids * (p.taps + 1) * rows + l * (px + 1) * (Np / parts + 16) <= kPatchLds) p.nc[l] = Np / parts;
-            p.served = p.served && p.nc[l] != 0;
-        }
-        if (!p.served) continue;
-        best = p;
-        least = padded;
-    }
-    // A block takes about 12 us beside its k-steps (0.28 us each), which short contractions do not pay for once there are enough blocks for
-    // the passes that this kernel does without (20 - 30 us) not to count.  Digits made beforehand / patches, us: 59 x 52 x 52 x 240 -> 48, 3 x 3
-    // (18 steps, 5 K blocks)  129 / 150;  195 x 38 x 38 x 96 -> 24 (9, 4.4 K)  101 / 108;  19 x 45 x 45 x 208 -> 36 (18, 1.2 K)  49 / 45;
-    // 27 x 56 x 56 x 64 -> 24 (9, 0.7 K)  44 / 29.
-    int taps = 0;
-    for (int i = 0; i < n_grids; ++i) taps += grids[i].Rc * grids[i].Sc;
-    if (best.served && taps * (Np / 32) < 20) {
-        const int rows = patch_rows(best.wn), cols = patch_cols(best.wn);
-        if ((B * grid.Hm * grid.Wm + rows - 1) / rows * ((C + cols - 1) / cols) > 2000) best.served = false;
-    }
-    return best;
 }
 
 template <int WN>

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "cdl.h"
+#include "cdl_conv_patch.h"
 
 namespace cdl {
 
@@ -144,9 +145,7 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
                       int32_t a_offset, int32_t b_offset, float *d_a_hat, float *d_b_hat, BwdPlan *plan, void *records, double *partial, int max_splits,
                       bool only_b, bool words, hipStream_t stream);
 
-// The same for the gradients of a convolution.  ConvDxGrid: a class of input pixels (2 i + oa, 2 j + oc) and the taps
-// (r0 + 2 r', s0 + 2 s'), r' < Rc, s' < Sc, that reach them (stride 1: one class, every pixel and tap, steps of 1).
-struct ConvDxGrid { int oa, oc, Hc, Wc, pad_h, pad_w, Rc, Sc, r0, s0; };
+// The same for the gradients of a convolution, by classes of input pixels (cdl_conv_patch.h).
 bool conv_dw_direct_serves(int64_t M, int32_t N, int32_t K);
 int launch_conv_dw_direct(const float *g, const int8_t *x_idx, const ConvWindows &w, int32_t N, float delta_x, int32_t x_offset, float *d_w_hat,
                           double *partial, int max_splits, hipStream_t stream);

@@ -2181,8 +2181,7 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     L.flags = off;     off += kPlanMaxBlocks * sizeof(unsigned long long);
     L.block_max = off; off += align_up((size_t)L.n_max * sizeof(unsigned int), 256);
     L.ss_b = off;      off += align_up((size_t)L.classes * C * sizeof(unsigned int), 256);
-    // (and the four k-steps behind a class that are read in vain, of as much as a part of a tap's channels leaves out)
-    L.wr = off;        off += align_up((size_t)((C + 31) / 32 * 32) * ((size_t)L.classes * (size_t)L.ld + 4 * (32 + (size_t)L.Np)), 256);
+    L.wr = off;        off += align_up((size_t)((C + 31) / 32 * 32) * (size_t)L.classes * (size_t)L.ld, 256);
     L.planes = off;    off += align_up((size_t)M_out * (size_t)L.Np * kMaxLimbs, 256);
     L.total = off;
     return L;
@@ -2190,31 +2189,6 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
 
 // (a 1 x 1 convolution of stride 1 is a linear layer)
 bool conv_dx_is_linear(int32_t R, int32_t S, int32_t stride) { return R == 1 && S == 1 && stride == 1; }
-
-// The classes of input pixels.  Stride 1: all of them, every tap.  Stride 2: input pixel (h, w) is reached only by the
-// taps r = h + pad, s = w + pad (mod 2) - with all R x S taps three products in four would multiply zeros -, so the
-// pixels (2 i + a, 2 j + c) of each parity (a, c) form a product of their own over the taps r = r0 + 2 r',
-// s = s0 + 2 s' (r0 = (a + pad) mod 2, likewise s0), in which g is read at p = i + (a + pad - r0) / 2 - r'.
-// Returns their number; unreached: there are pixels that no tap reaches.
-static int conv_dx_classes(int32_t H, int32_t W, int32_t R, int32_t S, int32_t stride, int32_t pad, ConvDxGrid (&grids)[4], bool &unreached)
-{
-    int n = 0;
-    unreached = false;
-    if (stride == 1) {
-        grids[n++] = ConvDxGrid{0, 0, H, W, pad, pad, R, S, 0, 0};
-        return n;
-    }
-    for (int pa = 0; pa < 2; ++pa)
-        for (int pc = 0; pc < 2; ++pc) {
-            const int Hc = (H - pa + 1) / 2, Wc = (W - pc + 1) / 2;
-            if (Hc <= 0 || Wc <= 0) continue;
-            const int r0 = (pa + pad) & 1, s0 = (pc + pad) & 1;
-            const int Rc = r0 < R ? (R - r0 + 1) / 2 : 0, Sc = s0 < S ? (S - s0 + 1) / 2 : 0;
-            if (Rc == 0 || Sc == 0) { unreached = true; continue; }
-            grids[n++] = ConvDxGrid{pa, pc, Hc, Wc, (pa + pad - r0) / 2, (pc + pad - s0) / 2, Rc, Sc, r0, s0};
-        }
-    return n;
-}
 
 size_t qconv_bwd_activations_workspace_bytes(int32_t B, int32_t H, int32_t W, int32_t C, int32_t N, int32_t R, int32_t S, int32_t stride, int32_t pad)
 {

@@ -78,3 +78,11 @@ def test_non_finite_entries_show(geom, value):
     assert bool(torch.isnan(got[~torch.isfinite(ref)]).all())
     rest = [b for b in range(geom[0]) if abs(b - 3) > 1 + 128 // (geom[1] * geom[2])]      # images that share no tile with it
     assert bool(torch.isfinite(got[rest]).all())
+
+
+# a prime number of 32 channels that do not fit together: parts of one k-step a tap, an odd number of steps, the weights at the end of a workspace of
+# just the size asked for
+@pytest.mark.parametrize("geom", [(1, 11, 11, 1280, 992, 3, 3, 1, 1), (4, 7, 7, 1408, 544, 3, 3, 1, 0), (12, 15, 14, 64, 224, 5, 5, 1, 2), (60, 13, 13, 96, 352, 3, 3, 2, 1)])
+@pytest.mark.parametrize("scale", [1.0, 3.0e4])
+def test_parts_of_one_step(geom, scale):
+    test_activation_gradient(geom, scale)

@@ -41,6 +41,7 @@ inline int conv_dx_classes(int32_t H, int32_t W, int32_t R, int32_t S, int32_t s
     return n;
 }
 
+constexpr int kPatchThreads = 256;
 constexpr int kPatchLds = 80 << 10;          // two blocks share a compute unit
 constexpr int kPatchFixed = 64;              // bytes for the reductions
 // At least four limbs.  Where every entry of g has the scale of the largest one of all, three may keep the bound for small ones; here they
@@ -95,7 +96,8 @@ struct PatchPlan {
 };
 
 // The tile of 32 x 256, 64 x 128 or 128 x 64 outputs that pads the channels least (of equals the widest, which needs the smallest
-// patch; several classes: 32 x 64 of each), and the channels of a patch that fit LDS: all of them or an equal part, a multiple of 32.
+// patch; several classes: 32 x 64 of each), and the channels of a patch that fit LDS: all of them or an equal part, a multiple of 32, of at most
+// four a thread (a thread makes the digits of one word of a pixel's row; more fit LDS where g has up to some eighteen pixels).
 inline PatchPlan plan_patch(const ConvDxGrid *grids, int n_grids, int64_t B, int P, int Q, int C, int Np)
 {
     PatchPlan best{};
@@ -117,7 +119,7 @@ inline PatchPlan plan_patch(const ConvDxGrid *grids, int n_grids, int64_t B, int
         for (int l = kPatchMinLimbs; l <= kPatchMaxLimbs; ++l) {
             p.nc[l] = 0;
             for (int parts = 1; parts <= Np / 32 && !p.nc[l]; ++parts)
-                if (Np / 32 % parts == 0 && kPatchFixed + 2ll * n_grids * (p.taps + 1) * rows + l * (px + 1) * (Np / parts + 16) <= kPatchLds) p.nc[l] = Np / parts;
+                if (Np / 32 % parts == 0 && Np / parts <= 4 * kPatchThreads && kPatchFixed + 2ll * n_grids * (p.taps + 1) * rows + l * (px + 1) * (Np / parts + 16) <= kPatchLds) p.nc[l] = Np / parts;
             p.served = p.served && p.nc[l] != 0;
         }
         if (!p.served) continue;

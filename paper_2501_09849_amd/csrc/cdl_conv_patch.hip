@@ -21,8 +21,6 @@ namespace cdl {
 
 namespace {
 
-constexpr int kPatchThreads = 256;
-
 struct PatchClass {
     int oa, oc, Hc, Wc, pad_h, pad_w, Rc, Sc;
     const int8_t *wr;
@@ -75,7 +73,7 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
         reinterpret_cast<uint32_t *>(planes + l * plane + px_max * stride)[w] = 0u;
     }
     // digits of channels n0 .. n0 + nc of the patch: a thread keeps its four channels and goes through the pixels
-    const int words = nc >> 2, px_step = kPatchThreads / words;      // (words <= 256: what fits LDS)
+    const int words = nc >> 2, px_step = kPatchThreads / words;      // (plan_patch: words <= kPatchThreads)
     const int px0 = tid / words, n_own = 4 * (tid - px0 * words);
     auto make_digits = [&](int n0) {
         if (px0 >= px_step) return;

@@ -86,3 +86,10 @@ def test_non_finite_entries_show(geom, value):
 @pytest.mark.parametrize("scale", [1.0, 3.0e4])
 def test_parts_of_one_step(geom, scale):
     test_activation_gradient(geom, scale)
+
+
+# few pixels of g, more output channels than a block has words for: a fully connected head as a convolution
+@pytest.mark.parametrize("geom", [(1, 7, 7, 512, 2048, 7, 7, 1, 0), (4, 7, 7, 512, 1280, 7, 7, 1, 0), (8, 7, 7, 512, 2048, 7, 7, 1, 0), (16, 7, 7, 512, 1056, 7, 7, 1, 0)])
+@pytest.mark.parametrize("scale", [1.0, 3.0e4])
+def test_few_pixels_many_channels(geom, scale):
+    test_activation_gradient(geom, scale)

@@ -255,10 +255,11 @@ int cdl_qgemm_fwd_offset(const int8_t *a_idx, const int8_t *b_idx, int32_t M, in
  * Diagnostics: once the call has run, the first two int32 of ws hold the limb counts the device
  * chose for d_a_hat and for d_b_hat, and the two doubles at byte offsets 32 and 40 of ws the bounds
  * above for the two products (meaningful for a product that was requested).  Where the arithmetic is small both products are
- * formed directly instead, in double or on digits that give every entry of g to within 2^-44 of the largest of its row (d_a_hat;
- * column for d_b_hat), summed in double before the one rounding to fp32; the words then hold the counts and
- * bounds that limbs would have had, or, for calls with N <= 32 or M*N*K <= 2^25, zeros: no limbs.  (d_a_hat
- * with N <= 32 never has limbs, also where d_b_hat has.)
+ * formed directly instead, each product of an entry of g and an index exact and summed in double before the one rounding to
+ * fp32 (beyond 0.7 * 10^9 multiply-adds of the requested products, in whole tiles, what entries below 2^-20 of the largest of
+ * their row of g - column for d_b_hat - have beyond 2^-44 of it may be left out, if that changes no output by more than 2e-9); the words
+ * then hold the counts and bounds that limbs would have had and say nothing about these products, or, for calls with N <= 32
+ * or M*N*K <= 2^25, zeros: no limbs, nothing rounded.  (d_a_hat with N <= 32 never has limbs, also where d_b_hat has.)
  */
 int cdl_qgemm_bwd(const float *g, const int8_t *a_idx, const int8_t *b_idx,
                   int32_t M, int32_t N, int32_t K, float delta_a, float delta_b,
@@ -321,7 +322,8 @@ int cdl_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_t H
  *   d_w_hat[n,r,s,c] = delta_x * sum over (b,p,q) of g[b,p,q,n] * X[b, p*stride + r - pad, q*stride + s - pad, c]
  * with X as in cdl_qconv_fwd (level index x_idx + x_offset inside the image, 0 outside).  It is cdl_qgemm_bwd's
  * d_b_hat on the window matrix - same limbs, same exactness - whose transposed copy (which that product needs
- * anyway) is gathered straight from the activations, or, where the arithmetic is small, the same sums in double.
+ * anyway) is gathered straight from the activations, or, where the arithmetic is small, the same sums formed directly (exact
+ * products up to 0.5 * 10^9 multiply-adds, see cdl_qgemm_bwd).
  *   g DEVICE fp32[B,P,Q,N], x_idx DEVICE int8[B,H,W,C], d_w_hat DEVICE fp32[N,R,S,C]
  * Restrictions as for cdl_qconv_fwd, and B*P*Q <= 11 000 000.  Scratch: cdl_qconv_bwd_weights_workspace_bytes
  * (it holds the transposed window matrix: R*S*C * B*P*Q bytes).

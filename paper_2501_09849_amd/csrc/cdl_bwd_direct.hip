@@ -15,6 +15,7 @@
 #include "cdl_div.h"
 #include "cdl_limbs.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace cdl {
@@ -53,6 +54,7 @@ struct DirectProduct {
     int ksp;               // waves that split a contraction piece (1, 2, 4 or 8)
     int narrow;            // tiles of 16 x 16 outputs per wave instead of 16 x 64
     int tiles_r, tiles_c, splits, steps, steps_per_split;      // steps: of 64 contraction entries, narrow and thin tiles: 16
+    int rounds_to;         // on digits: biased exponent up to which a row's scale may round entries far below it (-1: never)
     double delta;
     float *out;            // [rows][cols]
     double *partial;       // [splits][rows][cols], unscaled, when splits > 1
@@ -381,6 +383,11 @@ __device__ __forceinline__ float largest(float a, float b, float c)
     return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
 }
 
+__device__ __forceinline__ float smallest(float a, float b, float c)
+{
+    return __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, b), c);
+}
+
 __device__ __forceinline__ unsigned int max_over_groups(unsigned int v)      // over lanes that agree mod 16
 {
     const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
@@ -392,17 +399,19 @@ __device__ __forceinline__ unsigned int max_over_groups(unsigned int v)      // 
 // The products of a 16 x 64 tile as direct_tile forms them, on the int8 matrix cores: steps of 64 contraction entries, the
 // lane's 16 entries of a row of g as six balanced base-256 digits of g 2^s, s from the largest exponent in the row.
 //
-// What is rounded.  A row's scale leaves the entry that set it at 2^43 .. 2^44 and holds entries up to 2^46, so an entry is off by
-// at most 2^-44 of the largest of its row, and by nothing if it is within 2^-20 of it (24 bits of mantissa); digit sums are exact
-// in int32 and are added up in double.  The distance of all outputs from the products in double is that of their fp32 rounding
-// (2.5e-8 of their norm) to seven digits, as it is with every product formed in double (eight shapes up to 131072 x 16 x 144;
-// normal, heavy-tailed, sparse and subnormal g).  A row whose entries grow beyond its scale has its sums moved to double and
-// gets a new scale; a step with an infinity or a NaN is formed in double, where it shows in the same outputs as before.
+// What is exact.  A row's scale leaves the entry that set it at 2^43 .. 2^44 and holds entries up to 2^46, so digits give an entry within 2^-20 of the
+// row's largest in full (24 bits of mantissa) and smaller ones to 2^-44 of it; digit sums are exact in int32 and are added up in
+// double.  What they leave of the smaller ones is multiplied in double, the 4 contraction entries of an instruction at a time
+// where there is something left: with entries N(0, 1) one step in 600 has such an entry, so that every product is exact, as it is in
+// double, at 0.2 - 0.6 us of 9 - 20.  A step with many of them is formed in double as a whole, as one with an infinity or a NaN, which shows in
+// the same outputs as before (256 x 1000 x 512  N(0, 1) 12.4 us; times e^2N 17; spread over 2^60 25, in double 29).  Beyond the sizes where double is
+// the alternative what is left is left out where that is harmless (rounds_to).  A row whose entries grow beyond its scale has its sums
+// moved to double and gets a new scale.
 //
-// Why.  In double a step of 64 entries is 64 matrix instructions of 64 cycles; here 24 of 16 and about 235 others, of which 104
+// Why.  In double a step of 64 entries is 64 matrix instructions of 64 cycles; here 24 of 16 and about 245 others, of which 104
 // make the digits.  What bounds it is that wave's chain of instructions, two waves to a SIMD: 1 us a step, of 4 us + 2 us a step for a
 // block (load 1.5, the last sums and their addition over waves 2.5).  Both products, in double / so: 256 x 1000 x 512  29 / 12 us,
-// 512 x 512 x 256  20 / 9, 700 x 700 x 700 (limbs before)  48 / 20, dL/dQ(w) of 16 images of 28 x 28 x 64 -> 64, 3 x 3  32 / 16.
+// 512 x 512 x 256  20 / 10, 700 x 700 x 700 (limbs before)  48 / 21, dL/dQ(w) of 16 images of 28 x 28 x 64 -> 64, 3 x 3  32 / 18.
 // (Tiles of 16 columns would need as long for the digits as double takes in all: those stay with direct_tile.)
 // SHORT: the contraction may have fewer than 64 entries (whose loads, one by one with their bounds, would cost the others registers).
 constexpr int kDigits = 6, kDigitStep = 64;
@@ -513,14 +522,20 @@ __device__ __forceinline__ void digit_tile(const DirectProduct &p, Src &src, int
                     g[u][0][j] = e >= kDigitStep * s && e < p.kc ? g[u][0][j] : 0.0f;
                 }
         }
+        // smallest magnitude (of what lies inside the image), largest, a NaN stays one, and the biased exponent of the row's largest
+        float m = 0.0f, least = INFINITY;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float two = __builtin_elementwise_minimum(fabsf(g[u][0][0]), fabsf(g[u][0][1]));
+            const float four = smallest(two, fabsf(g[u][0][2]), fabsf(g[u][0][3]));
+            least = __builtin_elementwise_minimum(least, Src::kMask == 2 && !(ok[buf][u] & 1) ? INFINITY : four);
+        }
         if (Src::kMask == 2) {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) g[u][0][j] = (ok[buf][u] & 1) ? g[u][0][j] : 0.0f;
         }
-        // largest magnitude (a NaN stays one), and its biased exponent
-        float m = 0.0f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             m = largest(m, fabsf(g[u][0][0]), fabsf(g[u][0][1]));
@@ -532,10 +547,32 @@ __device__ __forceinline__ void digit_tile(const DirectProduct &p, Src &src, int
         auto word = [&](int u, int j) {
             return Src::kMask == 1 && !(ok[buf][u] >> j & 1) ? pad_word : b[buf][u][j] >> sh;
         };
-        if (__ballot(E > cap) != 0 || since == 1024) {      // (an int32 holds 2048 steps of 64 products of 128 and 128)
-            const bool special = __ballot(E == 255) != 0;
-            if (since > 0 || (special && !folded)) fold();
-            if (special) {
+        // what the row's scale holds with this step, and the exponent from which on its unit divides an entry (0: rounding is allowed)
+        const int to = E > cap ? min(E + 2, 254) : cap, whole_from = to <= p.rounds_to ? 0 : max(to - 22, 0);
+        if (__ballot(E > cap || !(least >= __int_as_float(whole_from << 23))) != 0 || since == 1024) {      // (an int32 holds 2048 steps of 64 products of 128 and 128)
+            // bits without the sign, one less, so that zeros are the largest
+            auto ordered = [&](int k) { return 2u * __float_as_uint(g[k >> 2][0][k & 3]) - 1u; };
+            const uint32_t limit = whole_from > 0 ? ((uint32_t)whole_from << 24) - 1u : 0u;
+            uint32_t small = ~0u;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) small = min(small, ordered(k));
+            // the contraction entries (quarter u, place j: bit 4 u + j) where the digits would round one
+            uint32_t groups = 0u;
+            if (__ballot(small < limit) != 0)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) groups |= __ballot(ordered(k) < limit) != 0 ? 1u << k : 0u;
+            // Where most are, or with an infinity or a NaN, the step is formed in double without digits; otherwise what the digits leave is.
+            const bool all = __ballot(E == 255) != 0 || __popc(groups) > 12;
+            if (all) groups = 0xffffu;
+            if (since == 1024 || (since > 0 && !all && __ballot(E > cap) != 0)) fold();
+            if (!all) cap = to;
+            if (groups && !folded) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mine[i * 64 + lane] = 0.0;
+                folded = true;
+            }
+            if (groups) {
+                const double unit_of = __hiloint2double((1023 - 172 + cap) << 20, 0), per_unit = __hiloint2double((1023 + 172 - cap) << 20, 0);
                 v4d sum[4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) sum[t] = v4d{0.0, 0.0, 0.0, 0.0};
@@ -543,19 +580,27 @@ __device__ __forceinline__ void digit_tile(const DirectProduct &p, Src &src, int
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const float gv = u == 0 ? g[0][0][j] : u == 1 ? g[1][0][j] : u == 2 ? g[2][0][j] : g[3][0][j];
+                        if (!(groups >> (4 * u + j) & 1)) continue;
+                        double v = (double)(u == 0 ? g[0][0][j] : u == 1 ? g[1][0][j] : u == 2 ? g[2][0][j] : g[3][0][j]);
+                        if (!all) {
+                            v *= per_unit;
+                            v = (v - __builtin_rint(v)) * unit_of;
+                        }
                         const uint32_t w = u == 0 ? word(0, j) : u == 1 ? word(1, j) : u == 2 ? word(2, j) : word(3, j);
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) sum[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)gv, (double)(((int)(w << (24 - 8 * t)) >> 24) + p.offset), sum[t], 0, 0, 0);
+                        for (int t = 0; t < 4; ++t) sum[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, (double)(((int)(w << (24 - 8 * t)) >> 24) + p.offset), sum[t], 0, 0, 0);
                     }
                 // (element (row q + 4 r, ...) of that tile)
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) mine[(4 * t + q) * 64 + 16 * r + (lane & 15)] += sum[t][r];
-                return;
             }
-            cap = E > cap ? min(E + 2, 254) : cap;
+            if (all) {
+                if (!DIAG) return;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) g[k >> 2][0][k & 3] = 0.0f;      // (on for the sums of |index|)
+            }
         }
         const double scale = __hiloint2double((1023 + 172 - cap) << 20, 0);
         v4i fa[kDigits], fb[4];
@@ -1110,10 +1155,25 @@ double plan_digits(DirectProduct **ps, int n, int max_splits)
 
 static int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
+// multiply-adds of one product, counted in whole tiles
+static double padded_macs(int64_t rows, int64_t kc, int64_t cols) { return (double)round_up(rows, 16) * (double)round_up(kc, 16) * (double)round_up(cols, 64); }
+
 // Up to kBwdDirectNoDiag the diagnostic words say that neither product has limbs.
 constexpr int64_t kBwdDirectNoDiag = 1ll << 25;
 
 static bool bwd_direct_diag(int32_t M, int32_t N, int32_t K) { return N > 32 && (int64_t)M * N * K > kBwdDirectNoDiag; }
+
+// DirectProduct::rounds_to.  Where sums in double are the alternative (`exact`) nothing is rounded.  Beyond, the alternative are limbs, whose
+// rounding may change an output by kLimbBoundTarget, and digits may round (entries 2^-20 of their row's largest and smaller, by half a unit,
+// 2^(cap - 173)) where that changes an output by a 512th of it at most, whatever the indices.  That is never more than limbs round an entry: up to five
+// leave 2^-40 of the largest |g| of all at least, digits 2^-44 of the row's; six leave 2^-48 of it, but serve only where five miss the target,
+// hence for a |g| beyond 2^(cap - 125).
+static int digits_round_to(const DirectProduct &p, bool exact)
+{
+    if (exact) return -1;
+    const int e = 173 + std::ilogb(kLimbBoundTarget / 512.0 / (p.delta * (128.0 + std::abs(p.offset)) * (double)p.kc));
+    return e < -1 ? -1 : (e > 254 ? 254 : e);
+}
 
 // The products of a call as a launch: in double or on digits, and the plan.
 struct BwdDirectPlan {
@@ -1124,7 +1184,7 @@ struct BwdDirectPlan {
     double us;             // on digits: what it takes
 };
 
-// (by the layer's sizes alone: an output has the same bits whether or not the other one is asked for too)
+// (by the layer's sizes alone: an output is formed in the same order whether or not the other one is asked for too)
 static void plan_bwd_direct(BwdDirectPlan &d, int32_t M, int32_t N, int32_t K, bool only_b, bool diag, double *partial, int max_splits)
 {
     d.a = d.b = DirectProduct{};
@@ -1179,6 +1239,12 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
     plan_bwd_direct(d, M, N, K, only_b, diag, partial, max_splits);
     d.a.g = g; d.a.idx = b_idx; d.a.ldg = N; d.a.ldi = K; d.a.offset = b_offset; d.a.vec = N % 4 == 0; d.a.delta = (double)delta_b; d.a.out = d_a_hat;
     d.b.g = g; d.b.idx = a_idx; d.b.ldg = N; d.b.ldi = K; d.b.offset = a_offset; d.b.delta = (double)delta_a; d.b.out = d_b_hat;
+    // (as far as sums in double are as fast as limbs, both products, us: 2000 x 300 x 1000 67 / 70;  1000 x 1000 x 1000 88 / 65.  By what is asked for: only
+    // outputs next to entries of g more than 2^20 times as large can show it.)
+    const double asked = (d.a.out && !only_b ? padded_macs(M, N, K) : 0.0) + (d.b.out ? padded_macs(N, M, K) : 0.0);
+    const bool exact = asked <= 7e8 && (!bwd_direct_diag(M, N, K) || (M <= 5120 && N <= 5120));
+    d.a.rounds_to = digits_round_to(d.a, exact);
+    d.b.rounds_to = digits_round_to(d.b, exact);
     DirectArgs a{};
     a.plan = plan;
     a.records = reinterpret_cast<unsigned long long *>(records);
@@ -1220,13 +1286,12 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
     return rc;
 }
 
-// multiply-adds of one product, counted in whole tiles
-static double padded_macs(int64_t rows, int64_t kc, int64_t cols) { return (double)round_up(rows, 16) * (double)round_up(kc, 16) * (double)round_up(cols, 64); }
 // The gradients of a convolution, directly / on limbs, us: weights, 16 x 28 x 28 x 64 -> 64, 3 x 3 (0.5 G in whole tiles)  16 / 32;
 // 24 x 32 x 32 x 48 -> 84 (1.0 G)  28 / 39;  31 x 30 x 30 x 80 -> 56 (1.3 G)  36 / 41;  25 x 33 x 33 x 288 -> 112, stride 2 (1.7 G)  51 / 40;
 // activations, on digits  58 x 19 x 19 x 80 -> 32 (0.8 G)  28 / 29;  72 x 17 x 17 x 272 -> 64, stride 2 (1.0 G)  35 / 37;
 // 17 x 9 x 9 x 368 -> 204 (1.0 G)  40 / 39;  31 x 30 x 30 x 80 -> 56 (1.8 G)  45 / 40.
 constexpr double kConvDwDirectMaxMacs = 1.2e9, kConvDxDirectMaxMacs = 1e9, kConvDxDoubleMaxMacs = 5e8;
+constexpr double kConvExactMacs = 5e8;      // (digits_round_to: as far as sums in double are as fast as limbs)
 
 bool conv_dw_direct_serves(int64_t M, int32_t N, int32_t K) { return padded_macs(N, M, K) <= kConvDwDirectMaxMacs; }
 
@@ -1236,6 +1301,7 @@ int launch_conv_dw_direct(const float *g, const int8_t *x_idx, const ConvWindows
     DirectProduct p{};
     p.g = g; p.idx = x_idx; p.rows = N; p.cols = w.R * w.S * w.C; p.kc = w.B * w.P * w.Q; p.ldg = N;
     p.offset = x_offset; p.delta = (double)delta_x; p.out = d_w_hat; p.partial = partial;
+    p.rounds_to = digits_round_to(p, padded_macs(p.rows, p.kc, p.cols) <= kConvExactMacs);
     DirectProduct *one = &p;
     const bool digits = p.kc >= kDigitStep && double_cycles(p) >= kDigitsFrom / 2;
     if (digits) plan_digits(&one, 1, max_splits);
@@ -1290,6 +1356,7 @@ int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid 
         DirectProduct &p = a.p[c];
         p.g = g; p.idx = w_idx; p.rows = B * k.Hc * k.Wc; p.cols = C; p.kc = k.Rc * k.Sc * N;
         p.delta = (double)delta_w; p.out = d_x_hat; p.splits = 1;
+        p.rounds_to = digits_round_to(p, (double)B * H * W * (double)round_up(C, C <= 48 ? 16 : 64) * (double)round_up((int64_t)R * S * N, 16) / (stride * stride) <= kConvExactMacs);
         const int64_t steps = ceil_div(p.kc, form == kWideDigits ? kDigitStep : 16), rows = ceil_div(p.rows, thin ? 64 : 16);
         p.steps = (int)steps;
         p.tiles_c = (int)ceil_div(C, thin ? 16 : 64);

@@ -27,7 +27,7 @@ struct BwdPlan {
 // millions of large indices) six are used and the bound, stored in the plan, says what was reached.
 constexpr double kLimbBoundTarget = 9e-7;
 
-// The diagnostic words of a call whose products were formed directly in double (one thread): no limbs, nothing rounded.
+// The diagnostic words of a call whose products were formed directly (one thread): no limbs, nothing rounded.
 __device__ __forceinline__ void no_limbs(BwdPlan *plan)
 {
     plan->limbs_da = plan->limbs_db = 0;

@@ -1,9 +1,9 @@
-"""GPU backward products on digits scaled by row: ends of the contraction, scales that grow inside a row, far apart rows, non-finite entries,
-and the products that are cut into pieces together with the diagnostic words.
+"""GPU backward products on digits scaled by row: ends of the contraction, scales that grow inside a row, far apart rows, small entries next to
+far larger ones, non-finite entries, and the products that are cut into pieces together with the diagnostic words.
 
-Tolerance.  An entry of g is off by at most 2^-44 of the largest of its row of the product, so an output by at most that times the sum of
-|index|; rounding to fp32 adds 2^-24 of the output, the sum of a few partial results in double nothing that shows.  Checked entry by
-entry with the bound twice as large (the reference is summed in double, in another order)."""
+Tolerance.  Every product of an entry of g and an index is exact, so an output is off by what its sum of n products in double is, at most
+n 2^-53 of the sum of their magnitudes, and by 2^-24 of the output for fp32.  Checked entry by entry with bounds twice as large (the reference
+is summed in double, in another order)."""
 import numpy as np
 import pytest
 
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 def _check(got, g64, idx64, step, what):
     ref = g64 @ idx64
-    bound = step * (2.0 ** -43 * np.max(np.abs(g64), axis=1, keepdims=True) * np.sum(np.abs(idx64), axis=0, keepdims=True) + 2.0 ** -23 * np.abs(ref))
+    bound = step * (g64.shape[1] * 2.0 ** -52 * (np.abs(g64) @ np.abs(idx64)) + 2.0 ** -23 * np.abs(ref))
     off = np.abs(got.astype(np.float64) - step * ref)
     assert np.all(off <= bound + 1.5e-45), "%s: %.3g of the bound" % (what, np.max(off / (bound + 1e-300)))
 
@@ -80,6 +80,67 @@ def test_scales(kind, M, N, K):
         _check(d_b, np.ascontiguousarray(g64.T), a.astype(np.float64), 0.5, "d_b_hat")
 
 
+# One row and one column of g far larger than the rest, with zeros among the indices that they meet: what the others contribute to those outputs
+# keeps all its bits.  "mixed": entries of every size in every step, zeros among them.
+@pytest.mark.parametrize("kind", [2.0 ** 18, 2.0 ** 24, 2.0 ** 30, 2.0 ** 60, "mixed"])
+@pytest.mark.parametrize("M,N,K", [(2048, 64, 256), (256, 1000, 512), (600, 650, 300), (700, 63, 400), (5120, 64, 192)])
+@pytest.mark.parametrize("oa,ob", [(0, 0), (128, 128)])
+def test_small_entries_next_to_large_ones(kind, M, N, K, oa, ob):
+    rng = np.random.default_rng(K)
+    g = rng.standard_normal((M, N))
+    a, b = _indices(M, N, K)
+    if kind == "mixed":
+        g *= np.exp2(rng.uniform(-60, 0, (M, N))) * (rng.random((M, N)) < 0.7)
+    else:
+        g[:, 5] *= kind
+        g[70 % M, :5] *= kind
+        g[70 % M, 6:] *= kind
+    b[5, ::2] = -ob
+    a[70 % M, ::2] = -oa
+    g = g.astype(np.float32)
+    d_a, d_b, _ = _run(g, a, b, oa, ob)
+    g64 = g.astype(np.float64)
+    _check(d_a, g64, b.astype(np.float64) + ob, 0.25, "d_a_hat")
+    _check(d_b, np.ascontiguousarray(g64.T), a.astype(np.float64) + oa, 0.5, "d_b_hat")
+
+
+# the same for the gradients of a convolution, 16 x 28 x 28 x 64 -> 64 and with stride 2
+@pytest.mark.parametrize("geom", [(16, 28, 28, 64, 64, 3, 3, 1, 1), (24, 33, 31, 96, 64, 3, 3, 2, 1)])
+@pytest.mark.parametrize("size", [1.0, 2.0 ** 30])
+def test_small_entries_next_to_large_ones_conv(geom, size):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    B, H, W, C, N, R, S, stride, pad = geom
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    gen = torch.Generator().manual_seed(H)
+    g = torch.randn((B, P, Q, N), generator=gen)
+    g[..., 5] *= size                       # a channel (activations' gradient) and a pixel (weights')
+    g[1, 2, 3, :5] *= size
+    x = torch.randint(-128, 128, (B, H, W, C), generator=gen, dtype=torch.int32)
+    w = torch.randint(-128, 128, (N, R, S, C), generator=gen, dtype=torch.int32)
+    w[5, :, :, ::2] = 0
+    x[1, 2 * stride - pad:2 * stride - pad + R, 3 * stride - pad:3 * stride - pad + S, ::2] = 0
+    G, X, Wi = g.cuda(), x.to(torch.int8).cuda(), w.to(torch.int8).cuda()
+    dx, dw = gu.empty((B, H, W, C), torch.float32), gu.empty((N, R, S, C), torch.float32)
+    ws = gu.workspace(max(cdl.qconv_bwd_weights_workspace_bytes(*geom), cdl.qconv_bwd_activations_workspace_bytes(*geom)))
+    cdl.cdl_qconv_bwd_activations(G, Wi, *geom, 0.25, dx, ws)
+    cdl.cdl_qconv_bwd_weights(G, X, *geom, 0.5, dw, ws)
+    torch.cuda.synchronize()
+    g2, xp = g.double().reshape(-1, N), torch.zeros((B, H + 2 * pad + R, W + 2 * pad + S, C), dtype=torch.float64)
+    xp[:, pad:pad + H, pad:pad + W] = x.double()
+    sums = []
+    for f in (lambda t: t, torch.abs):      # the products, and the sums of their magnitudes
+        out, dw_ref = torch.zeros_like(xp), torch.zeros((N, R, S, C), dtype=torch.float64)
+        for r in range(R):
+            for s in range(S):
+                out[:, r:r + stride * P:stride, s:s + stride * Q:stride] += (f(g2) @ f(w.double())[:, r, s].contiguous()).reshape(B, P, Q, C)
+                dw_ref[:, r, s] = f(g2).t().contiguous() @ f(xp)[:, r:r + stride * P:stride, s:s + stride * Q:stride].reshape(-1, C)
+        sums.append((out[:, pad:pad + H, pad:pad + W], dw_ref))
+    for got, ref, mag, step, n in ((dx, sums[0][0], sums[1][0], 0.25, R * S * N), (dw, sums[0][1], sums[1][1], 0.5, B * P * Q)):
+        off, bound = (got.cpu().double() - step * ref).abs(), step * (n * 2.0 ** -52 * mag + 2.0 ** -23 * ref.abs())
+        assert bool((off <= bound).all()), float((off / (bound + 1e-300)).max())
+
+
 # an infinity or a NaN shows in the outputs it enters, as a sum in double has it, and in no other
 @pytest.mark.parametrize("M,N,K", [(600, 650, 300), (4000, 200, 256)])
 @pytest.mark.parametrize("offset", [0, 128])
@@ -103,11 +164,12 @@ def test_non_finite_entries(M, N, K, offset):
     _check(d_b[good_c], np.ascontiguousarray(finite.T)[good_c], a.astype(np.float64) + offset, 0.5, "d_b_hat")
 
 
-# long contractions over few output tiles, cut into pieces: the diagnostic words come from the kernel that adds them up
+# long contractions over few output tiles, cut into pieces: the diagnostic words come from the kernel that adds them up; spread: entries of many sizes
 @pytest.mark.parametrize("M,N,K", [(6001, 40, 333), (12000, 64, 192), (20000, 64, 100), (9000, 48, 79)])      # (more than 2^25 multiply-adds: fewer have no such words)
-def test_pieces_and_diagnostic_words(M, N, K):
+@pytest.mark.parametrize("spread", [0, 16])
+def test_pieces_and_diagnostic_words(M, N, K, spread):
     rng = np.random.default_rng(M)
-    g = rng.standard_normal((M, N)).astype(np.float32)
+    g = (rng.standard_normal((M, N)) * np.exp2(rng.uniform(-spread, 0, (M, N)))).astype(np.float32)
     a, b = _indices(M, N, K)
     d_a, d_b, ws = _run(g, a, b)
     g64 = g.astype(np.float64)

@@ -339,7 +339,7 @@ int cdl_qconv_bwd_weights(const float *g, const int8_t *x_idx, int32_t B, int32_
  *   d_x_hat[b,h,w,c] = delta_w * sum over (p,q,r,s,n) with p*stride + r - pad = h, q*stride + s - pad = w of
  *                      g[b,p,q,n] * w_idx[n,r,s,c],
  * an exact real contraction over (r,s,n) rounded once, as cdl_qgemm_bwd's d_a_hat is (directly where the arithmetic is
- * small): the same limb product (at least four limbs where they are chosen block by block), whose operand - the digits of g, made in
+ * small): the same limb product (where the digits are made in LDS at least four limbs, scaled block by block), whose operand - the digits of g, made in
  * LDS or once in the workspace - is gathered tap by tap (a transposed convolution) instead of read row by row.
  *   g DEVICE fp32[B,P,Q,N], w_idx DEVICE int8[N,R,S,C] (level indices as they are), d_x_hat DEVICE fp32[B,H,W,C]
  * Restrictions: N and C multiples of 4, stride 1 or 2, pad < R and pad < S, R*S*N <= 131071

@@ -44,9 +44,8 @@ inline int conv_dx_classes(int32_t H, int32_t W, int32_t R, int32_t S, int32_t s
 constexpr int kPatchThreads = 256;
 constexpr int kPatchLds = 80 << 10;          // two blocks share a compute unit
 constexpr int kPatchFixed = 64;              // bytes for the reductions
-// At least four limbs.  Where every entry of g has the scale of the largest one of all, three may keep the bound for small ones; here they
-// would be chosen block by block, and a block of small entries next to large ones would be less exact than with the count that the
-// largest asks for (2.5e-8 -> 9e-8 of the norm of the outputs).  Relative to a block's largest entry four leave 2^-32, below the rounding of the fp32 result.
+// At least four limbs: relative to a block's largest entry they leave 2^-32, below the rounding of the fp32 result.  (Three keep the bound where the
+// steps and indices are small; outputs 2.5e-8 -> 9e-8 of their norm.)
 constexpr int kPatchMinLimbs = 4, kPatchMaxLimbs = 6;
 
 // Four waves: WN = 1, 2, 4 as (4 / WN) x WN, 32 pixels by 64 channels each, of the one class; WN = 0: a wave for each class, 32 grid

@@ -2,15 +2,17 @@
 // g[b,p,q,n] w[n,r,s,c] over the taps that reach pixel (h, w), without a matrix of windows.
 //
 // The pixels of g that a run of output pixels needs are one contiguous range of g, [lo, lo + count) x N, of about the run's length
-// and R - 1 image rows.  A block takes such a range, finds its largest entry, chooses the limb count and the scale of its digits
-// by the rule of the other limb products (the bound of cdl_bwd_plan.h, over its own columns), and writes the digits into LDS once,
-// one byte per limb and entry; every tap then reads its fragments there, row by row at an offset that depends on the tap.  So nothing
-// runs before this kernel but the rearrangement of the weights, and g is read from memory about once per 256 channels.
+// and R - 1 image rows.  A block takes such a range, scales its digits by the range's largest entry, and writes them into LDS once,
+// one byte per limb and entry; every tap then reads its fragments there, row by row at an offset that depends on the tap.  The limb
+// count is that of the whole tensor, so no output is further from the exact sum than with one scale for all of g: a pass over g takes the
+// largest entry of every pixel and of all, and the launch that rearranges the weights makes the plan.  g is read from memory once more, or found
+// in the last-level cache, about once per 256 channels.
 // The weights' fragments go from L2 straight to registers: a wave's columns are its own, LDS would be written and read for one use.
 //
 // What bounds it: the matrix cores while both blocks of a compute unit are in their k-steps (96 % busy; LDS and the vector cache at half
-// their rates); the rest of a block - largest entry 6 us, digits 5, outputs 3 of 35 - hides only behind the other block.  Before, a pass
-// for max |g| and one that made the digits ran first and the product read them tap by tap through L2 into LDS, where
+// their rates); the rest of a block - digits 5 us, outputs 3 of 30 - hides only behind the other block.  (With the largest entry taken by every block
+// from g itself, 6 us more a block, and a limb count of its own: the same for 14 x 14 x 256, 8 us more for stride 2.)  Before, a pass
+// that made the digits ran first and the product read them tap by tap through L2 into LDS, where
 // reads and writes together took longer than the matrix instructions.  The whole call, us, with uniform indices: 256 images of
 // 14 x 14 x 256 -> 256, 3 x 3  216 -> 144;  128 x 28 x 28 x 128 -> 128  123 -> 87;  128 x 7 x 7 x 512 -> 512  139 -> 85;
 // 128 x 56 x 56 x 64 -> 128, stride 2  119 -> 97.
@@ -24,7 +26,6 @@ namespace {
 struct PatchClass {
     int oa, oc, Hc, Wc, pad_h, pad_w, Rc, Sc;
     const int8_t *wr;
-    const unsigned int *col_abs;             // [ld / 64][C]
     DivBy by_s;
 };
 
@@ -41,12 +42,12 @@ struct PatchArgs {
     int px_max;                              // pixels of a patch, at most
     int nc[kMaxLimbs + 1];                   // channels of a patch that fit, by limbs
     int taps;                                // of a class, at most
+    const BwdPlan *plan;
+    const unsigned int *pixel_max;           // [pixels]
     double delta_w;
 };
 // (read where the launch put them: indexing a by-value argument by the class would copy it to scratch memory)
 typedef const PatchArgs __attribute__((address_space(4))) *patch_args_t;
-
-__device__ __forceinline__ float patch_largest(float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); }
 
 struct PatchTile { int row0, col0, lo, count; };
 
@@ -243,53 +244,27 @@ void limb_conv_patch_kernel(PatchArgs a)
         t.lo = __builtin_amdgcn_readfirstlane(lo);
         t.count = __builtin_amdgcn_readfirstlane(min(max(hi - lo + 1, 1), min(args->px_max, args->pixels - lo)));
     }
-    // largest |g| of the range, largest sum of |w| of the columns
-    float *red = reinterpret_cast<float *>(patch_lds);
-    unsigned int *redc = reinterpret_cast<unsigned int *>(patch_lds) + 4;
+    // largest |g| of the range (an infinity or a NaN is larger than any number)
+    unsigned int *red = reinterpret_cast<unsigned int *>(patch_lds);
     {
-        // (the sums of the columns are asked for first, forty pieces of a class at a time: one trip to memory together with g)
-        unsigned int cs = 0u;
-        const bool column = (int)threadIdx.x < COLS * args->n_classes && t.col0 + (int)threadIdx.x % COLS < args->C;
-        const auto &k = args->c[column ? (int)threadIdx.x / COLS : 0];
-        const unsigned int *col = k.col_abs + min(t.col0 + (int)threadIdx.x % COLS, args->C - 1);
-        const int kb = (k.Rc * k.Sc * args->Np + 63) / 64;
-        constexpr int kPieces = 40;
-        unsigned int v[kPieces];
+        unsigned int mx = 0u;
+        for (int i = threadIdx.x; i < t.count; i += kPatchThreads) mx = max(mx, args->pixel_max[t.lo + i]);
 #pragma unroll
-        for (int u = 0; u < kPieces; ++u) v[u] = col[(int64_t)min(u, kb - 1) * args->C];
-        float mx = 0.0f;
-        const float4 *g4 = reinterpret_cast<const float4 *>(args->g + (int64_t)t.lo * args->N);
-        const int quads = t.count * (args->N >> 2);
-#pragma unroll 8
-        for (int i = threadIdx.x; i < quads; i += kPatchThreads) {
-            const float4 f = g4[i];
-            mx = patch_largest(mx, fabsf(f.x), fabsf(f.y));
-            mx = patch_largest(mx, fabsf(f.z), fabsf(f.w));
-        }
-#pragma unroll
-        for (int u = 0; u < kPieces; ++u) cs += u < kb ? v[u] : 0u;
-        for (int i = kPieces; i < kb; ++i) cs += col[(int64_t)i * args->C];
-        if (!column) cs = 0u;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            mx = __builtin_elementwise_maximum(mx, __shfl_xor(mx, off, 64));
-            cs = max(cs, (unsigned int)__shfl_xor((int)cs, off, 64));
-        }
-        if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = mx; redc[threadIdx.x >> 6] = cs; }
+        for (int off = 32; off > 0; off >>= 1) mx = max(mx, (unsigned int)__shfl_xor((int)mx, off, 64));
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
     }
+    const unsigned int all_bits = args->plan->amax_bits;
+    const int all_limbs = args->plan->limbs_da;
     __syncthreads();
-    const float amax = patch_largest(patch_largest(red[0], red[1], red[2]), red[3], 0.0f);
-    const unsigned int sums = max(max(redc[0], redc[1]), max(redc[2], redc[3]));
-    // sigma = 2^e > 1.01 max|g|, and the fewest limbs (four to six) whose bound delta_w sigma 2^-8L sum|w| is under the target (choose_limbs)
+    const unsigned int amax_bits = max(max(red[0], red[1]), max(red[2], red[3])), inf_bits = 0x7f800000u;
+    const float amax = __uint_as_float(amax_bits);
+    // The limb count of the whole tensor (choose_limbs; six if it has an infinity or a NaN), the scale of the range: sigma = 2^e > 1.01 max|g|
+    const int L = __builtin_amdgcn_readfirstlane(all_bits < inf_bits ? max(all_limbs, kPatchMinLimbs) : kMaxLimbs);
     int e = 0;
     if (amax > 0.0f) frexpf(amax * 1.01f, &e);
     e = __builtin_amdgcn_readfirstlane(max(min(e, 127), -80));
-    const double unit = args->delta_w * (double)sums;
-    int L = kPatchMinLimbs;
-    while (L < kMaxLimbs && unit * ldexp(1.0, e - 8 * L) > kLimbBoundTarget) ++L;
-    L = __builtin_amdgcn_readfirstlane(L);
     // (an infinity or a NaN in the range: NaN for the tile)
-    const bool finite = (__float_as_uint(amax) & 0x7f800000u) != 0x7f800000u;
+    const bool finite = amax_bits < inf_bits;
     // (in scalar registers: kept in memory, their loads among the stores of the outputs would wait for every store before them)
     const long long scale_bits = finite ? __double_as_longlong(args->delta_w * ldexp(1.0, e + 1 - 8 * L)) : 0x7ff8000000000000ll;
     const double out_scale = __hiloint2double(__builtin_amdgcn_readfirstlane((int)(scale_bits >> 32)), __builtin_amdgcn_readfirstlane((int)scale_bits));
@@ -323,7 +298,7 @@ bool conv_dx_patch_serves(const ConvDxGrid *grids, int n_grids, int32_t B, int32
     return plan_patch(grids, n_grids, B, P, Q, C, (N + 31) / 32 * 32).served;
 }
 
-int launch_conv_dx_patch(const float *g, const int8_t *wr, const unsigned int *col_abs, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
+int launch_conv_dx_patch(const float *g, const int8_t *wr, const BwdPlan *plan, const unsigned int *pixel_max, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
                          int32_t W, int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream)
 {
     const PatchPlan p = plan_patch(grids, n_grids, B, P, Q, C, Np);
@@ -339,13 +314,13 @@ int launch_conv_dx_patch(const float *g, const int8_t *wr, const unsigned int *c
     a.by_w = make_div_by((uint32_t)grid.Wm);
     a.px_max = p.px_max; a.taps = p.taps;
     for (int l = kPatchMinLimbs; l <= kMaxLimbs; ++l) a.nc[l] = p.nc[l];
+    a.plan = plan; a.pixel_max = pixel_max;
     a.delta_w = (double)delta_w;
     for (int i = 0; i < n_grids; ++i) {
         const ConvDxGrid &s = grids[i];
         PatchClass &d = a.c[i];
         d.oa = s.oa; d.oc = s.oc; d.Hc = s.Hc; d.Wc = s.Wc; d.pad_h = s.pad_h; d.pad_w = s.pad_w; d.Rc = s.Rc; d.Sc = s.Sc;
         d.wr = wr + (int64_t)i * a.C32 * ld;
-        d.col_abs = col_abs + (int64_t)i * (ld / 64) * C;
         d.by_s = make_div_by((uint32_t)s.Sc);
     }
     if (p.wn == 0) return launch_patch<0>(a, stream);

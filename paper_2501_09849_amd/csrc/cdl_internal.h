@@ -159,9 +159,10 @@ int launch_limb_rows(const float *g, const int8_t *frag, int64_t tile_bytes, int
                      hipStream_t stream);
 
 // The same on limbs, from patches of g in LDS (cdl_conv_patch.hip).  wr: the weights per class as [ld / 32][C / 32][2][32][16] (halves of 32
-// contraction entries, channels, entries), a tap's channels padded with zeros to Np, a multiple of 32; col_abs: sums of |w| per class as [ld / 64][C].
+// contraction entries, channels, entries), a tap's channels padded with zeros to Np, a multiple of 32; plan: of the whole tensor;
+// pixel_max: the largest |g| of every pixel, as the bits of a float.
 bool conv_dx_patch_serves(const ConvDxGrid *grids, int n_grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q);
-int launch_conv_dx_patch(const float *g, const int8_t *wr, const unsigned int *col_abs, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
+int launch_conv_dx_patch(const float *g, const int8_t *wr, const BwdPlan *plan, const unsigned int *pixel_max, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
                          int32_t W, int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream);
 
 // The same on limbs, from digits made beforehand (cdl_conv_dx.hip).  wr: the weights per class as [ld / 64][C][64]; Np: N padded to whole chunks of 16 channels;

@@ -1308,7 +1308,7 @@ struct ConvDxClasses { ConvDxClass c[4]; int tstep; };
 
 __global__ __launch_bounds__(256)
 void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int S, int C, ConvDxClasses cls, int8_t *__restrict__ wr, int64_t ld,
-                         unsigned int *col_abs /* zeroed, or null */, unsigned int *part /* [class][ld / 64][C], or null */, PlanArgs plan)
+                         unsigned int *col_abs /* zeroed */, bool fragments, PlanArgs plan)
 {
     // A block turns 64 contraction entries x 64 channels of one class (blockIdx.z): rows of 64 channels are contiguous in w,
     // 64 entries of a channel in wr.
@@ -1349,13 +1349,11 @@ void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int
     if (c0 + c < C) {
         // (patches: 1 KB for 32 contraction entries of 32 channels, [half of the entries][channel][16])
         const int C32 = (C + 31) & ~31, ch = c0 + c;
-        int8_t *dst = part ? wr + (int64_t)blockIdx.z * C32 * ld + (((int64_t)(2 * blockIdx.x + (q >> 1)) * (C32 >> 5) + (ch >> 5)) * 64 + (q & 1) * 32 + (ch & 31)) * 16
-                           : wr + (int64_t)blockIdx.z * C * ld + ((int64_t)blockIdx.x * C + ch) * 64 + 16 * q;
+        int8_t *dst = fragments ? wr + (int64_t)blockIdx.z * C32 * ld + (((int64_t)(2 * blockIdx.x + (q >> 1)) * (C32 >> 5) + (ch >> 5)) * 64 + (q & 1) * 32 + (ch & 31)) * 16
+                                : wr + (int64_t)blockIdx.z * C * ld + ((int64_t)blockIdx.x * C + ch) * 64 + 16 * q;
         *reinterpret_cast<uint4 *>(dst) = uint4{word[0], word[1], word[2], word[3]};
-        if (q == 0 && part) part[((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * C + c0 + c] = s_abs;
-        if (q == 0 && col_abs) __hip_atomic_fetch_add(&col_abs[blockIdx.z * C + c0 + c], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (q == 0) __hip_atomic_fetch_add(&col_abs[blockIdx.z * C + c0 + c], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (!col_abs) return;
     plan_at_end(plan, (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y * gridDim.z));
 }
 
@@ -1601,6 +1599,52 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ g
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned int)__shfl_down((int)m, off, 64));
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) block_max[blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
+}
+
+// The same for g as [pixels][N], N a multiple of 4, with the largest |g| of every pixel besides (as the bits of a float).  2^log_t lanes to a pixel, four
+// pixels at a time, two trips of loads under way.
+__global__ __launch_bounds__(256) void pixel_max_kernel(const float *__restrict__ g, int pixels, int N, int log_t, unsigned int *__restrict__ pixel_max,
+                                                        unsigned int *__restrict__ block_max, unsigned int *__restrict__ clear, int n_clear)
+{
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0u;
+    constexpr int U = 4;
+    __shared__ unsigned int wave_max[4];
+    const int quads = N >> 2, own = threadIdx.x & ((1 << log_t) - 1), group = threadIdx.x >> log_t, per = 256 >> log_t;
+    unsigned int all = 0u;
+    for (int p0 = blockIdx.x * per * U + group; p0 < pixels; p0 += gridDim.x * per * U) {
+        const float4 *src[U];
+        unsigned int m[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            src[u] = reinterpret_cast<const float4 *>(g + (int64_t)min(p0 + u * per, pixels - 1) * N);
+            m[u] = 0u;
+        }
+#pragma unroll 2
+        for (int q = own; q < quads; q += 1 << log_t) {
+            float4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = src[u][q];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                m[u] = max(m[u], max(__float_as_uint(fabsf(v[u].x)), __float_as_uint(fabsf(v[u].y))));
+                m[u] = max(m[u], max(__float_as_uint(fabsf(v[u].z)), __float_as_uint(fabsf(v[u].w))));
+            }
+        }
+        for (int off = 1 << log_t >> 1; off > 0; off >>= 1)
+#pragma unroll
+            for (int u = 0; u < U; ++u) m[u] = max(m[u], (unsigned int)__shfl_xor((int)m[u], off, 64));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (own == 0 && p0 + u * per < pixels) pixel_max[p0 + u * per] = m[u];
+            all = max(all, m[u]);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) all = max(all, (unsigned int)__shfl_xor((int)all, off, 64));
+    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = all;
     __syncthreads();
     if (threadIdx.x == 0) block_max[blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
@@ -2162,7 +2206,7 @@ static int conv_zero_page_ptr(const int8_t **ptr)
 }
 
 struct ConvDxLayout {
-    size_t plan, flags, block_max, ss_b, wr, planes, total;      // (patches: sums of |w| in the place of the planes)
+    size_t plan, flags, block_max, ss_b, wr, planes, total;      // (patches: the pixels' largest |g| in the place of the planes)
     int n_max, Np, classes;
     int64_t ld;
 };
@@ -2205,9 +2249,9 @@ size_t qconv_bwd_activations_workspace_bytes(int32_t B, int32_t H, int32_t W, in
     const double cols = C <= 48 ? (C + 15) / 16 * 16 : (C + 63) / 64 * 64;
     const double work = (double)B * H * W * cols * (double)(((int64_t)R * S * N + 15) / 16 * 16) / (stride * stride);
     size_t own = is_linear || few || work <= 5e8 ? L.planes : L.total;
-    const size_t sums = L.planes + align_up((size_t)L.classes * (size_t)(L.ld / 64) * C * sizeof(unsigned int), 256);
+    const size_t maxima = L.planes + align_up((size_t)M_out * sizeof(unsigned int), 256);
     if (!conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride) && !is_linear) {
-        const size_t least = patch ? sums : L.total;
+        const size_t least = patch ? maxima : L.total;
         if (least > own) own = least;
     }
     const size_t linear = is_linear ? bwd_layout((int32_t)M_out, N, C).total : 0;
@@ -2241,27 +2285,27 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
     ConvDxClasses taps{};
     taps.tstep = stride;
     for (int c = 0; c < n_cls; ++c) taps.c[c] = ConvDxClass{grids[c].r0, grids[c].s0, grids[c].Rc, grids[c].Sc};
+    unsigned int *pixel_max = reinterpret_cast<unsigned int *>(base + L.planes);
     if (patch) {
-        unsigned int *part = reinterpret_cast<unsigned int *>(base + L.planes);
-        const dim3 grid((unsigned)(L.ld / 64), (unsigned)((C + 63) / 64), (unsigned)n_cls);
-        CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, grid, dim3(256), 0, w_idx, N, L.Np, R, S, C, taps, wr, L.ld, (unsigned int *)nullptr, part, PlanArgs{});
-        const int rc = check_launch();
-        if (rc != CDL_OK) return rc;
-        return launch_conv_dx_patch(g, wr, part, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, delta_w, d_x_hat, stream);
+        int log_t = 0;
+        while (log_t < 6 && 2 << log_t <= N / 4) ++log_t;
+        CDL_LAUNCH("pixel_max_kernel", stream, pixel_max_kernel, dim3(L.n_max), dim3(256), 0, g, (int)M_out, N, log_t, pixel_max, block_max, ss_b, n_cls * C);
+    } else {
+        CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, n_cls * C);
     }
-    CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, n_cls * C);
     // (one limb count for all classes: the largest column sum of any of them)
     PlanArgs pa{plan, block_max, L.n_max, nullptr, ss_b, 0, n_cls * C, 1.0f, delta_w, reinterpret_cast<unsigned long long *>(base + L.flags), next_finish_tag()};
     const dim3 prep((unsigned)(L.ld / 64), (unsigned)((C + 63) / 64), (unsigned)n_cls);
     const bool plan_apart = (int64_t)prep.x * prep.y * prep.z > kPlanMaxBlocks;
     if (plan_apart) pa.plan = nullptr;
-    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, prep, dim3(256), 0,
-               w_idx, N, L.Np, R, S, C, taps, wr, L.ld, ss_b, (unsigned int *)nullptr, pa);
+    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, prep, dim3(256), 0, w_idx, N, L.Np, R, S, C, taps, wr, L.ld, ss_b, patch, pa);
     if (plan_apart)
         CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
                    (const unsigned int *)nullptr, 0, ss_b, n_cls * C, 1.0f, delta_w);
     const int8_t *zeros = nullptr;
     int rc = check_launch();
+    if (rc == CDL_OK && patch)
+        return launch_conv_dx_patch(g, wr, plan, pixel_max, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, delta_w, d_x_hat, stream);
     if (rc == CDL_OK) rc = conv_zero_page_ptr(&zeros);
     if (rc != CDL_OK) return rc;
     return launch_conv_dx_planes(g, wr, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, plan, reinterpret_cast<int8_t *>(base + L.planes), zeros, d_x_hat, stream);

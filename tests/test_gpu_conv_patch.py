@@ -80,6 +80,25 @@ def test_non_finite_entries_show(geom, value):
     assert bool(torch.isfinite(got[rest]).all())
 
 
+# The limb count is that of the whole tensor: one entry per image that sets the scale, meeting zeros in half of the channels, whose other contributions are
+# 2^-12 of it; in the first image it is twice as large, and there the bound asks for a limb more.  Tolerance: the bound with that limb, for all images.
+@pytest.mark.parametrize("geom", [CASES[0], CASES[3], CASES[9]])
+def test_limb_count_of_the_whole_tensor(geom):
+    torch = gu.torch_mod()
+    step = 0.0625
+    g, w = _inputs(geom, 1.0)
+    w[5, :, :, ::2] = 0
+    sums = float(w.abs().double().sum(dim=(0, 1, 2)).max()) if geom[7] == 1 else max(
+        float(w[:, r::2, s::2].abs().double().sum(dim=(0, 1, 2)).max()) for r in range(2) for s in range(2))
+    e = int(np.floor(np.log2(9e-7 * 2.0 ** 32 / (step * sums))))      # the largest sigma = 2^e that four limbs serve
+    g = torch.randn_like(g) * 2.0 ** (e - 14)
+    g[:, 1, 1, 5] = 0.9 * 2.0 ** e
+    g[0, 1, 1, 5] *= 2.0
+    got, ref = _call(g, w, geom, step).double()[..., ::2], _reference(g, w, geom, step)[..., ::2]
+    off = (got - ref).abs()
+    assert bool((off <= step * sums * 2.0 ** (e + 1 - 40) + 2.0 ** -23 * ref.abs()).all()), float(off.max())
+
+
 # a prime number of 32 channels that do not fit together: parts of one k-step a tap, an odd number of steps, the weights at the end of a workspace of
 # just the size asked for
 @pytest.mark.parametrize("geom", [(1, 11, 11, 1280, 992, 3, 3, 1, 1), (4, 7, 7, 1408, 544, 3, 3, 1, 0), (12, 15, 14, 64, 224, 5, 5, 1, 2), (60, 13, 13, 96, 352, 3, 3, 2, 1)])

@@ -731,14 +731,7 @@ __device__ __forceinline__ void direct_store(const DirectProduct &p, const doubl
             for (int c = 0; c < 4; ++c)
                 if (col + c < p.cols) o[c] = v[c];
         } else {
-            float *o = p.out + out_row(row) * p.cols + col;
-            if ((p.cols & 3) == 0) {
-                if (col < p.cols) *reinterpret_cast<float4 *>(o) = make_float4((float)(v[0] * p.delta), (float)(v[1] * p.delta), (float)(v[2] * p.delta), (float)(v[3] * p.delta));
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (col + c < p.cols) o[c] = (float)(v[c] * p.delta);
-            }
+            store_outputs(p, out_row(row), col, v);
         }
     }
 }

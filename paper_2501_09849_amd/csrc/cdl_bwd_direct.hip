@@ -573,28 +573,30 @@ __device__ __forceinline__ void digit_tile(const DirectProduct &p, Src &src, int
             }
             if (groups) {
                 const double unit_of = __hiloint2double((1023 - 172 + cap) << 20, 0), per_unit = __hiloint2double((1023 + 172 - cap) << 20, 0);
-                v4d sum[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) sum[t] = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
-                for (int u = 0; u < 4; ++u)
+                for (int t0 = 0; t0 < 4; t0 += 2) {      // (two columns of a word at a time: registers)
+                    v4d sum[2] = {v4d{0.0, 0.0, 0.0, 0.0}, v4d{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll 1
+                    for (int u = 0; u < 4; ++u)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        if (!(groups >> (4 * u + j) & 1)) continue;
-                        double v = (double)(u == 0 ? g[0][0][j] : u == 1 ? g[1][0][j] : u == 2 ? g[2][0][j] : g[3][0][j]);
-                        if (!all) {
-                            v *= per_unit;
-                            v = (v - __builtin_rint(v)) * unit_of;
+                        for (int j = 0; j < 4; ++j) {
+                            if (!(groups >> (4 * u + j) & 1)) continue;
+                            double v = (double)(u == 0 ? g[0][0][j] : u == 1 ? g[1][0][j] : u == 2 ? g[2][0][j] : g[3][0][j]);
+                            if (!all) {
+                                v *= per_unit;
+                                v = (v - __builtin_rint(v)) * unit_of;
+                            }
+                            const uint32_t w = (u == 0 ? word(0, j) : u == 1 ? word(1, j) : u == 2 ? word(2, j) : word(3, j)) >> (8 * t0);
+#pragma unroll
+                            for (int t = 0; t < 2; ++t)
+                                sum[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, (double)(((int)(w << (24 - 8 * t)) >> 24) + p.offset), sum[t], 0, 0, 0);
                         }
-                        const uint32_t w = u == 0 ? word(0, j) : u == 1 ? word(1, j) : u == 2 ? word(2, j) : word(3, j);
+                    // (element (row q + 4 r, ...) of that tile)
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) sum[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, (double)(((int)(w << (24 - 8 * t)) >> 24) + p.offset), sum[t], 0, 0, 0);
-                    }
-                // (element (row q + 4 r, ...) of that tile)
+                    for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) mine[(4 * t + q) * 64 + 16 * r + (lane & 15)] += sum[t][r];
+                        for (int r = 0; r < 4; ++r) mine[(4 * (t0 + t) + q) * 64 + 16 * r + (lane & 15)] += sum[t][r];
+                }
             }
             if (all) {
                 if (!DIAG) return;

@@ -14,7 +14,6 @@ struct BwdPlan {
     float gscale_da, gscale_db;      // 2^(8L-1) / sigma
     double out_scale_da, out_scale_db;  // delta_b * sigma / 2^(8L-1), delta_a * sigma / 2^(8L-1)
     double bound_da, bound_db;          // what the rounding of g can change in one entry of d_a_hat / d_b_hat, at most
-    unsigned int amax_bits;             // the largest |g|, as the bits of a float
 };
 
 // Chooses the power-of-two scale of g and, for each backward product, the number of limbs.  With
@@ -50,7 +49,6 @@ __device__ __forceinline__ void choose_limbs(BwdPlan *plan, unsigned int amax_bi
     while (lb < kMaxLimbs && unit_db * ldexp(1.0, e - 8 * lb) > kLimbBoundTarget) ++lb;
     plan->bound_da = unit_da * ldexp(1.0, e - 8 * la);
     plan->bound_db = unit_db * ldexp(1.0, e - 8 * lb);
-    plan->amax_bits = amax_bits;
     plan->limbs_da = la;
     plan->limbs_db = lb;
     plan->gscale_da = ldexpf(1.0f, 8 * la - 1 - e);

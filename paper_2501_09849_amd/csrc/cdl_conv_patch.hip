@@ -5,7 +5,7 @@
 // and R - 1 image rows.  A block takes such a range, scales its digits by the range's largest entry, and writes them into LDS once,
 // one byte per limb and entry; every tap then reads its fragments there, row by row at an offset that depends on the tap.  The limb
 // count is that of the whole tensor, so no output is further from the exact sum than with one scale for all of g: a pass over g takes the
-// largest entry of every pixel and of all, and the launch that rearranges the weights makes the plan.  g is read from memory once more, or found
+// largest entry of every pixel and of every block of that pass, the launch that rearranges the weights their sums by column.  g is read from memory once more, or found
 // in the last-level cache, about once per 256 channels.
 // The weights' fragments go from L2 straight to registers: a wave's columns are its own, LDS would be written and read for one use.
 //
@@ -42,8 +42,7 @@ struct PatchArgs {
     int px_max;                              // pixels of a patch, at most
     int nc[kMaxLimbs + 1];                   // channels of a patch that fit, by limbs
     int taps;                                // of a class, at most
-    const BwdPlan *plan;
-    const unsigned int *pixel_max;           // [pixels]
+    PatchMaxima maxima;
     double delta_w;
 };
 // (read where the launch put them: indexing a by-value argument by the class would copy it to scratch memory)
@@ -244,22 +243,37 @@ void limb_conv_patch_kernel(PatchArgs a)
         t.lo = __builtin_amdgcn_readfirstlane(lo);
         t.count = __builtin_amdgcn_readfirstlane(min(max(hi - lo + 1, 1), min(args->px_max, args->pixels - lo)));
     }
-    // largest |g| of the range (an infinity or a NaN is larger than any number)
+    // largest |g| of the range and of all (an infinity or a NaN is larger than any number), largest sum of |w| of a column.  Every block takes the
+    // maxima by itself, in the trip to memory for its pixels' (by the last block of the launch before: 4 us).
     unsigned int *red = reinterpret_cast<unsigned int *>(patch_lds);
     {
-        unsigned int mx = 0u;
-        for (int i = threadIdx.x; i < t.count; i += kPatchThreads) mx = max(mx, args->pixel_max[t.lo + i]);
+        const unsigned int *block_max = args->maxima.block_max;
+        const int n_max = args->maxima.n_max, n_abs = args->maxima.n_abs;
+        unsigned int v[3] = {0u, 0u, 0u};
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = max(mx, (unsigned int)__shfl_xor((int)mx, off, 64));
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+        for (int u = 0; u < kPatchMaxima / kPatchThreads; ++u) v[1] = max(v[1], block_max[min(u * kPatchThreads + (int)threadIdx.x, n_max - 1)]);
+        for (int i = threadIdx.x; i < n_abs; i += kPatchThreads) v[2] = max(v[2], args->maxima.col_abs[i]);
+        for (int i = threadIdx.x; i < t.count; i += kPatchThreads) v[0] = max(v[0], args->maxima.pixel_max[t.lo + i]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v[k] = max(v[k], (unsigned int)__shfl_xor((int)v[k], off, 64));
+            if ((threadIdx.x & 63) == 0) red[4 * k + (threadIdx.x >> 6)] = v[k];
+        }
     }
-    const unsigned int all_bits = args->plan->amax_bits;
-    const int all_limbs = args->plan->limbs_da;
     __syncthreads();
-    const unsigned int amax_bits = max(max(red[0], red[1]), max(red[2], red[3])), inf_bits = 0x7f800000u;
-    const float amax = __uint_as_float(amax_bits);
-    // The limb count of the whole tensor (choose_limbs; six if it has an infinity or a NaN), the scale of the range: sigma = 2^e > 1.01 max|g|
-    const int L = __builtin_amdgcn_readfirstlane(all_bits < inf_bits ? max(all_limbs, kPatchMinLimbs) : kMaxLimbs);
+    auto maximum = [&](int k) { return max(max(red[4 * k], red[4 * k + 1]), max(red[4 * k + 2], red[4 * k + 3])); };
+    const unsigned int amax_bits = maximum(0), all_bits = maximum(1), inf_bits = 0x7f800000u;
+    const float amax = __uint_as_float(amax_bits), all = __uint_as_float(all_bits);
+    // The fewest limbs, four to six, whose bound for the whole tensor, delta_w sigma 2^-8L sum|w| with sigma = 2^e > 1.01 max|g|, is under the
+    // target (choose_limbs; six with an infinity or a NaN), and the scale of the range
+    int e_all = 0;
+    if (all > 0.0f) frexpf(all * 1.01f, &e_all);
+    e_all = max(min(e_all, 127), -80);
+    const double unit = args->delta_w * (double)maximum(2);
+    int L = all_bits < inf_bits ? kPatchMinLimbs : kMaxLimbs;
+    while (L < kMaxLimbs && unit * ldexp(1.0, e_all - 8 * L) > kLimbBoundTarget) ++L;
+    L = __builtin_amdgcn_readfirstlane(L);
     int e = 0;
     if (amax > 0.0f) frexpf(amax * 1.01f, &e);
     e = __builtin_amdgcn_readfirstlane(max(min(e, 127), -80));
@@ -298,7 +312,7 @@ bool conv_dx_patch_serves(const ConvDxGrid *grids, int n_grids, int32_t B, int32
     return plan_patch(grids, n_grids, B, P, Q, C, (N + 31) / 32 * 32).served;
 }
 
-int launch_conv_dx_patch(const float *g, const int8_t *wr, const BwdPlan *plan, const unsigned int *pixel_max, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
+int launch_conv_dx_patch(const float *g, const int8_t *wr, const PatchMaxima &maxima, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
                          int32_t W, int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream)
 {
     const PatchPlan p = plan_patch(grids, n_grids, B, P, Q, C, Np);
@@ -314,7 +328,7 @@ int launch_conv_dx_patch(const float *g, const int8_t *wr, const BwdPlan *plan, 
     a.by_w = make_div_by((uint32_t)grid.Wm);
     a.px_max = p.px_max; a.taps = p.taps;
     for (int l = kPatchMinLimbs; l <= kMaxLimbs; ++l) a.nc[l] = p.nc[l];
-    a.plan = plan; a.pixel_max = pixel_max;
+    a.maxima = maxima;
     a.delta_w = (double)delta_w;
     for (int i = 0; i < n_grids; ++i) {
         const ConvDxGrid &s = grids[i];

@@ -159,10 +159,13 @@ int launch_limb_rows(const float *g, const int8_t *frag, int64_t tile_bytes, int
                      hipStream_t stream);
 
 // The same on limbs, from patches of g in LDS (cdl_conv_patch.hip).  wr: the weights per class as [ld / 32][C / 32][2][32][16] (halves of 32
-// contraction entries, channels, entries), a tap's channels padded with zeros to Np, a multiple of 32; plan: of the whole tensor;
-// pixel_max: the largest |g| of every pixel, as the bits of a float.
+// contraction entries, channels, entries), a tap's channels padded with zeros to Np, a multiple of 32; pixel_max: the largest |g| of
+// every pixel, as the bits of a float; block_max [n_max <= kPatchMaxima], col_abs [n_abs]: their maxima are the largest |g| of all and the
+// largest sum of |w| of a column of any class.
 bool conv_dx_patch_serves(const ConvDxGrid *grids, int n_grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q);
-int launch_conv_dx_patch(const float *g, const int8_t *wr, const BwdPlan *plan, const unsigned int *pixel_max, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
+struct PatchMaxima { const unsigned int *pixel_max, *block_max, *col_abs; int n_max, n_abs; };
+constexpr int kPatchMaxima = 2048;
+int launch_conv_dx_patch(const float *g, const int8_t *wr, const PatchMaxima &maxima, int64_t ld, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H,
                          int32_t W, int32_t C, int32_t N, int32_t Np, int32_t P, int32_t Q, int32_t stride, float delta_w, float *d_x_hat, hipStream_t stream);
 
 // The same on limbs, from digits made beforehand (cdl_conv_dx.hip).  wr: the weights per class as [ld / 64][C][64]; Np: N padded to whole chunks of 16 channels;

@@ -2205,6 +2205,7 @@ static int conv_zero_page_ptr(const int8_t **ptr)
     return CDL_OK;
 }
 
+constexpr int kConvDxMaxBlocks = 2048;      // of the pass for max |g|
 struct ConvDxLayout {
     size_t plan, flags, block_max, ss_b, wr, planes, total;      // (patches: the pixels' largest |g| in the place of the planes)
     int n_max, Np, classes;
@@ -2219,7 +2220,7 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     L.Np = (N + pad_n - 1) / pad_n * pad_n;
     const int64_t kc = (stride == 2 ? (int64_t)((R + 1) / 2) * ((S + 1) / 2) : (int64_t)R * S) * L.Np;
     L.ld = (kc + 63) / 64 * 64;
-    L.n_max = (int)blocks_for((M_out * N) >> 2, 2048, 2048);
+    L.n_max = (int)blocks_for((M_out * N) >> 2, 2048, kConvDxMaxBlocks);
     size_t off = 0;
     L.plan = off;      off += align_up(sizeof(BwdPlan), 256);
     L.flags = off;     off += kPlanMaxBlocks * sizeof(unsigned long long);
@@ -2297,15 +2298,19 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
     PlanArgs pa{plan, block_max, L.n_max, nullptr, ss_b, 0, n_cls * C, 1.0f, delta_w, reinterpret_cast<unsigned long long *>(base + L.flags), next_finish_tag()};
     const dim3 prep((unsigned)(L.ld / 64), (unsigned)((C + 63) / 64), (unsigned)n_cls);
     const bool plan_apart = (int64_t)prep.x * prep.y * prep.z > kPlanMaxBlocks;
-    if (plan_apart) pa.plan = nullptr;
+    if (plan_apart || patch) pa.plan = nullptr;
     CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, prep, dim3(256), 0, w_idx, N, L.Np, R, S, C, taps, wr, L.ld, ss_b, patch, pa);
+    if (patch) {
+        static_assert(kPatchMaxima >= kConvDxMaxBlocks, "maxima that a block of the patch kernel reads");
+        const int rc = check_launch();
+        if (rc != CDL_OK) return rc;
+        return launch_conv_dx_patch(g, wr, PatchMaxima{pixel_max, block_max, ss_b, L.n_max, n_cls * C}, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, delta_w, d_x_hat, stream);
+    }
     if (plan_apart)
         CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
                    (const unsigned int *)nullptr, 0, ss_b, n_cls * C, 1.0f, delta_w);
     const int8_t *zeros = nullptr;
     int rc = check_launch();
-    if (rc == CDL_OK && patch)
-        return launch_conv_dx_patch(g, wr, plan, pixel_max, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, delta_w, d_x_hat, stream);
     if (rc == CDL_OK) rc = conv_zero_page_ptr(&zeros);
     if (rc != CDL_OK) return rc;
     return launch_conv_dx_planes(g, wr, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, plan, reinterpret_cast<int8_t *>(base + L.planes), zeros, d_x_hat, stream);

@@ -9,13 +9,14 @@
 // in the last-level cache, about once per 256 channels.
 // The weights' fragments go from L2 straight to registers: a wave's columns are its own, LDS would be written and read for one use.
 //
-// What bounds it: the matrix cores while both blocks of a compute unit are in their k-steps (96 % busy; LDS and the vector cache at half
-// their rates); the rest of a block - digits 5 us, outputs 3 of 30 - hides only behind the other block.  (With the largest entry taken by every block
-// from g itself, 6 us more a block, and a limb count of its own: the same for 14 x 14 x 256, 8 us more for stride 2.)  Before, a pass
+// What bounds it: the matrix cores while both blocks of a compute unit are in their k-steps (pipes 55 % busy over the whole kernel at 14 x 14 x 256; LDS
+// and the vector cache at half their rates); the rest of a block - digits 5 us, outputs 3 of 30 - hides only behind the other block.
+// Stride 2: 18 %, digits of 62 pixels for 32 of the grid, and waves of one to four taps.  (With the largest entry taken by every block
+// from g itself, 6 us more a block and no pass before, and a limb count of its own, the whole call was as long within 5 %.)  Before, a pass
 // that made the digits ran first and the product read them tap by tap through L2 into LDS, where
 // reads and writes together took longer than the matrix instructions.  The whole call, us, with uniform indices: 256 images of
-// 14 x 14 x 256 -> 256, 3 x 3  216 -> 144;  128 x 28 x 28 x 128 -> 128  123 -> 87;  128 x 7 x 7 x 512 -> 512  139 -> 85;
-// 128 x 56 x 56 x 64 -> 128, stride 2  119 -> 97.
+// 14 x 14 x 256 -> 256, 3 x 3  216 -> 154;  128 x 28 x 28 x 128 -> 128  123 -> 101;  128 x 7 x 7 x 512 -> 512  139 -> 85;
+// 128 x 56 x 56 x 64 -> 128, stride 2  119 -> 96.
 #include "cdl_bwd_plan.h"
 #include "cdl_limbs.h"
 
@@ -62,7 +63,9 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
     const auto &k = args->c[idle ? 0 : cls];
     const int P = args->P, Q = args->Q, Np = args->Np, N = args->N, C = args->C, Wm = args->Wm, hw = args->Hm * Wm, rows = args->rows, Sc = k.Sc, taps = k.Rc * Sc;
     const DivBy by_hw{args->by_hw.mul, args->by_hw.sh}, by_w{args->by_w.mul, args->by_w.sh};
-    const int nc = args->nc[L], stride = nc + 16, px_max = args->px_max;      // (rows an odd multiple of 16 bytes apart: no bank conflicts)
+    // (rows an odd multiple of 16 bytes apart: conflicts only where lanes read the row of zeros or pixels that do not follow each other, 0.28 of the
+    // LDS cycles at 14 x 14 x 256, 0.07 at stride 2)
+    const int nc = args->nc[L], stride = nc + 16, px_max = args->px_max;
     const int plane = (px_max + 1) * stride;                                  // (row px_max of a plane: zeros)
     // [class][taps + 1][ROWS]: the row of a plane where a tap's pixel lies
     uint16_t *table = reinterpret_cast<uint16_t *>(lds + kPatchFixed) + (idle ? 0 : cls) * (args->taps + 1) * ROWS;

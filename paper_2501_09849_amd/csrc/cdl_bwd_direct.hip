@@ -404,7 +404,7 @@ __device__ __forceinline__ unsigned int max_over_groups(unsigned int v)      // 
 // double.  What they leave of the smaller ones is multiplied in double, the 4 contraction entries of an instruction at a time
 // where there is something left: with entries N(0, 1) one step in 600 has such an entry, so that every product is exact, as it is in
 // double, at 0.2 - 0.6 us of 9 - 20.  A step with many of them is formed in double as a whole, as one with an infinity or a NaN, which shows in
-// the same outputs as before (256 x 1000 x 512  N(0, 1) 12.4 us; times e^2N 17; spread over 2^60 25, in double 29).  Beyond the sizes where double is
+// the same outputs as before (256 x 1000 x 512  N(0, 1) 12.4 us; times e^2N 18; spread over 2^60 28, in double 29).  Beyond the sizes where double is
 // the alternative what is left is left out where that is harmless (rounds_to).  A row whose entries grow beyond its scale has its sums
 // moved to double and gets a new scale.
 //

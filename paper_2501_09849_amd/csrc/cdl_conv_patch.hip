@@ -4,9 +4,9 @@
 // The pixels of g that a run of output pixels needs are one contiguous range of g, [lo, lo + count) x N, of about the run's length
 // and R - 1 image rows.  A block takes such a range, scales its digits by the range's largest entry, and writes them into LDS once,
 // one byte per limb and entry; every tap then reads its fragments there, row by row at an offset that depends on the tap.  The limb
-// count is that of the whole tensor, so no output is further from the exact sum than with one scale for all of g: a pass over g takes the
-// largest entry of every pixel and of every block of that pass, the launch that rearranges the weights their sums by column.  g is read from memory once more, or found
-// in the last-level cache, about once per 256 channels.
+// count is that of the whole tensor, so no output is further from the exact sum than with one scale for all of g: the launch that rearranges the weights
+// also takes, in a pass over g beside that, the largest entry of every pixel and of every block of the pass, and the columns' sums of |w|.
+// g is read from memory once more, or found in the last-level cache, about once per 256 channels.
 // The weights' fragments go from L2 straight to registers: a wave's columns are its own, LDS would be written and read for one use.
 //
 // What bounds it: the matrix cores while both blocks of a compute unit are in their k-steps (pipes 55 % busy over the whole kernel at 14 x 14 x 256; LDS

@@ -1306,15 +1306,25 @@ __device__ __forceinline__ void plan_at_end(const PlanArgs &a, int self, int blo
 struct ConvDxClass { int r0, s0, Rc, Sc; };
 struct ConvDxClasses { ConvDxClass c[4]; int tstep; };
 
-__global__ __launch_bounds__(256)
-void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int S, int C, ConvDxClasses cls, int8_t *__restrict__ wr, int64_t ld,
-                         unsigned int *col_abs /* zeroed */, bool fragments, PlanArgs plan)
+struct ConvDxWeights {
+    const int8_t *w;
+    int N, Np, R, S, C;
+    ConvDxClasses cls;
+    int8_t *wr;
+    int64_t ld;
+};
+
+// A block turns 64 contraction entries (bx) x 64 channels (by) of one class (bz): rows of 64 channels are contiguous in w, 64 entries of a channel in
+// wr (PATCH: 1 KB for 32 contraction entries of 32 channels, [half of the entries][channel][16]).  Returns, to four threads each, the sum of |w| over the entries of
+// channel 64 by + threadIdx.x / 4.
+template <bool PATCH>
+__device__ __forceinline__ unsigned int rearrange_weights(const ConvDxWeights &a, int bx, int by, int bz)
 {
-    // A block turns 64 contraction entries x 64 channels of one class (blockIdx.z): rows of 64 channels are contiguous in w,
-    // 64 entries of a channel in wr.
     __shared__ int8_t tile[64][68];
-    const ConvDxClass k_ = cls.c[blockIdx.z];
-    const int kc = k_.Rc * k_.Sc * Np, k0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    const int N = a.N, Np = a.Np, R = a.R, S = a.S, C = a.C;
+    const int8_t *w = a.w;
+    const ConvDxClass k_ = a.cls.c[bz];
+    const int kc = k_.Rc * k_.Sc * Np, k0 = bx * 64, c0 = by * 64;
     const float inv_np = 1.0f / (float)Np, inv_s = 1.0f / (float)k_.Sc;
     {
         const int c = threadIdx.x & 63, part = threadIdx.x >> 6;
@@ -1324,7 +1334,7 @@ void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int
             // (k < 2^17: (k + 1/2) / Np in fp32 is far enough from a whole number to truncate to the quotient)
             const int k = k0 + 4 * e + part, kk = min(k, kc - 1), tap = (int)(((float)kk + 0.5f) * inv_np), nn = kk - tap * Np, n = min(nn, N - 1);
             const int tr = (int)(((float)tap + 0.5f) * inv_s), ts = tap - tr * k_.Sc;
-            const int r = k_.r0 + cls.tstep * tr, sx = k_.s0 + cls.tstep * ts;
+            const int r = k_.r0 + a.cls.tstep * tr, sx = k_.s0 + a.cls.tstep * ts;
             const int8_t x = w[(((int64_t)n * R + r) * S + sx) * C + min(c0 + c, C - 1)];
             v[e] = k < kc && nn < N ? x : (int8_t)0;
         }
@@ -1347,14 +1357,114 @@ void conv_dx_prep_kernel(const int8_t *__restrict__ w, int N, int Np, int R, int
     s_abs += (unsigned int)__shfl_xor((int)s_abs, 1, 64);
     s_abs += (unsigned int)__shfl_xor((int)s_abs, 2, 64);
     if (c0 + c < C) {
-        // (patches: 1 KB for 32 contraction entries of 32 channels, [half of the entries][channel][16])
         const int C32 = (C + 31) & ~31, ch = c0 + c;
-        int8_t *dst = fragments ? wr + (int64_t)blockIdx.z * C32 * ld + (((int64_t)(2 * blockIdx.x + (q >> 1)) * (C32 >> 5) + (ch >> 5)) * 64 + (q & 1) * 32 + (ch & 31)) * 16
-                                : wr + (int64_t)blockIdx.z * C * ld + ((int64_t)blockIdx.x * C + ch) * 64 + 16 * q;
+        int8_t *dst = PATCH ? a.wr + (int64_t)bz * C32 * a.ld + (((int64_t)(2 * bx + (q >> 1)) * (C32 >> 5) + (ch >> 5)) * 64 + (q & 1) * 32 + (ch & 31)) * 16
+                            : a.wr + (int64_t)bz * C * a.ld + ((int64_t)bx * C + ch) * 64 + 16 * q;
         *reinterpret_cast<uint4 *>(dst) = uint4{word[0], word[1], word[2], word[3]};
-        if (q == 0) __hip_atomic_fetch_add(&col_abs[blockIdx.z * C + c0 + c], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    return s_abs;
+}
+
+__global__ __launch_bounds__(256)
+void conv_dx_prep_kernel(ConvDxWeights a, unsigned int *col_abs /* zeroed */, PlanArgs plan)
+{
+    const unsigned int s_abs = rearrange_weights<false>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    const int ch = blockIdx.y * 64 + (threadIdx.x >> 2);
+    if ((threadIdx.x & 3) == 0 && ch < a.C) __hip_atomic_fetch_add(&col_abs[blockIdx.z * a.C + ch], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     plan_at_end(plan, (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y * gridDim.z));
+}
+
+// What the kernel on patches needs (cdl_conv_patch.hip), in one launch: blocks 0 .. nx ny nz - 1 rearrange the weights, and the last block of every 64
+// channels of a class adds up the column sums of |w| of its blocks and leaves the largest; the others take the largest |g| of every
+// pixel (as the bits of a float), and of all their pixels.  Waiting is for lower blocks only (cdl_finish.h); the weights' 8 us pass beside the pass over g.
+struct PatchPrep {
+    ConvDxWeights weights;
+    int nx, ny, nz;
+    unsigned int *part;                // [nz][nx][C]
+    unsigned long long *flags;         // [nz][ny][nx]
+    unsigned long long tag;
+    unsigned int *col_max;             // [nz][ny]
+    const float *g;
+    int pixels, N, log_t;              // N a multiple of 4; 2^log_t lanes to a pixel
+    unsigned int *pixel_max, *block_max;
+};
+
+__global__ __launch_bounds__(256)
+void conv_patch_prep_kernel(PatchPrep a)
+{
+    __shared__ unsigned int red[4];
+    const int prep = a.nx * a.ny * a.nz;
+    auto block_largest = [&](unsigned int v) {      // thread 0 has it
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v = max(v, (unsigned int)__shfl_xor((int)v, off, 64));
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+        __syncthreads();
+        return max(max(red[0], red[1]), max(red[2], red[3]));
+    };
+    if ((int)blockIdx.x < prep) {
+        const int bx = blockIdx.x % a.nx, bg = blockIdx.x / a.nx, by = bg % a.ny, bz = bg / a.ny, C = a.weights.C;
+        const unsigned int s_abs = rearrange_weights<true>(a.weights, bx, by, bz);
+        const int ch = by * 64 + (threadIdx.x >> 2);
+        if ((threadIdx.x & 3) == 0 && ch < C) __hip_atomic_store(&a.part[((int64_t)bz * a.nx + bx) * C + ch], s_abs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        unsigned long long *flags = a.flags + (int64_t)bg * a.nx;
+        if (bx != a.nx - 1) {
+            if (threadIdx.x == 0) device_store(flags + bx, a.tag);
+            return;
+        }
+        for (int i = threadIdx.x; i < a.nx - 1; i += 256) {
+            while (device_load(flags + i) != a.tag) {}
+            device_store(flags + i, 0ull);
+        }
+        asm volatile("" ::: "memory");
+        __syncthreads();
+        // four threads to a channel
+        unsigned int sum = 0u;
+        if (ch < C)
+#pragma unroll 8
+            for (int i = threadIdx.x & 3; i < a.nx; i += 4) sum += __hip_atomic_load(&a.part[((int64_t)bz * a.nx + i) * C + ch], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sum += (unsigned int)__shfl_xor((int)sum, 1, 64);
+        sum += (unsigned int)__shfl_xor((int)sum, 2, 64);
+        const unsigned int most = block_largest(sum);
+        if (threadIdx.x == 0) a.col_max[bg] = most;
+        return;
+    }
+    // four pixels at a time, two trips of loads under way
+    constexpr int U = 4;
+    const int self = blockIdx.x - prep, blocks = gridDim.x - prep, log_t = a.log_t;
+    const int quads = a.N >> 2, own = threadIdx.x & ((1 << log_t) - 1), group = threadIdx.x >> log_t, per = 256 >> log_t;
+    unsigned int all = 0u;
+    for (int p0 = self * per * U + group; p0 < a.pixels; p0 += blocks * per * U) {
+        const float4 *src[U];
+        unsigned int m[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            src[u] = reinterpret_cast<const float4 *>(a.g + (int64_t)min(p0 + u * per, a.pixels - 1) * a.N);
+            m[u] = 0u;
+        }
+#pragma unroll 2
+        for (int q = own; q < quads; q += 1 << log_t) {
+            float4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = src[u][q];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                m[u] = max(m[u], max(__float_as_uint(fabsf(v[u].x)), __float_as_uint(fabsf(v[u].y))));
+                m[u] = max(m[u], max(__float_as_uint(fabsf(v[u].z)), __float_as_uint(fabsf(v[u].w))));
+            }
+        }
+        for (int off = 1 << log_t >> 1; off > 0; off >>= 1)
+#pragma unroll
+            for (int u = 0; u < U; ++u) m[u] = max(m[u], (unsigned int)__shfl_xor((int)m[u], off, 64));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (own == 0 && p0 + u * per < a.pixels) a.pixel_max[p0 + u * per] = m[u];
+            all = max(all, m[u]);
+        }
+    }
+    const unsigned int most = block_largest(all);
+    if (threadIdx.x == 0) a.block_max[self] = most;
 }
 
 // The forward product with the quantizer of the activations in its prologue: y = delta_a delta_b (Q_idx(X) . Wi^T)
@@ -1599,52 +1709,6 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ g
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned int)__shfl_down((int)m, off, 64));
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) block_max[blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
-}
-
-// The same for g as [pixels][N], N a multiple of 4, with the largest |g| of every pixel besides (as the bits of a float).  2^log_t lanes to a pixel, four
-// pixels at a time, two trips of loads under way.
-__global__ __launch_bounds__(256) void pixel_max_kernel(const float *__restrict__ g, int pixels, int N, int log_t, unsigned int *__restrict__ pixel_max,
-                                                        unsigned int *__restrict__ block_max, unsigned int *__restrict__ clear, int n_clear)
-{
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0u;
-    constexpr int U = 4;
-    __shared__ unsigned int wave_max[4];
-    const int quads = N >> 2, own = threadIdx.x & ((1 << log_t) - 1), group = threadIdx.x >> log_t, per = 256 >> log_t;
-    unsigned int all = 0u;
-    for (int p0 = blockIdx.x * per * U + group; p0 < pixels; p0 += gridDim.x * per * U) {
-        const float4 *src[U];
-        unsigned int m[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            src[u] = reinterpret_cast<const float4 *>(g + (int64_t)min(p0 + u * per, pixels - 1) * N);
-            m[u] = 0u;
-        }
-#pragma unroll 2
-        for (int q = own; q < quads; q += 1 << log_t) {
-            float4 v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = src[u][q];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                m[u] = max(m[u], max(__float_as_uint(fabsf(v[u].x)), __float_as_uint(fabsf(v[u].y))));
-                m[u] = max(m[u], max(__float_as_uint(fabsf(v[u].z)), __float_as_uint(fabsf(v[u].w))));
-            }
-        }
-        for (int off = 1 << log_t >> 1; off > 0; off >>= 1)
-#pragma unroll
-            for (int u = 0; u < U; ++u) m[u] = max(m[u], (unsigned int)__shfl_xor((int)m[u], off, 64));
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (own == 0 && p0 + u * per < pixels) pixel_max[p0 + u * per] = m[u];
-            all = max(all, m[u]);
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) all = max(all, (unsigned int)__shfl_xor((int)all, off, 64));
-    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = all;
     __syncthreads();
     if (threadIdx.x == 0) block_max[blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
@@ -2207,7 +2271,7 @@ static int conv_zero_page_ptr(const int8_t **ptr)
 
 constexpr int kConvDxMaxBlocks = 2048;      // of the pass for max |g|
 struct ConvDxLayout {
-    size_t plan, flags, block_max, ss_b, wr, planes, total;      // (patches: the pixels' largest |g| in the place of the planes)
+    size_t plan, flags, block_max, ss_b, wr, planes, total;      // (patches: see patch_scratch)
     int n_max, Np, classes;
     int64_t ld;
 };
@@ -2232,6 +2296,21 @@ ConvDxLayout conv_dx_layout(int64_t M_out, int32_t N, int32_t C, int32_t R, int3
     return L;
 }
 
+// What the kernel on patches has in the place of the planes.
+struct PatchScratch { size_t pixel_max, part, flags, total; int nx, ny; };
+PatchScratch patch_scratch(const ConvDxLayout &L, int64_t M_out, int32_t C)
+{
+    PatchScratch p;
+    p.nx = (int)(L.ld / 64);
+    p.ny = (C + 63) / 64;
+    size_t off = L.planes;
+    p.pixel_max = off; off += align_up((size_t)M_out * sizeof(unsigned int), 256);
+    p.part = off;      off += align_up((size_t)L.classes * (size_t)p.nx * (size_t)C * sizeof(unsigned int), 256);
+    p.flags = off;     off += align_up((size_t)L.classes * (size_t)p.nx * (size_t)p.ny * sizeof(unsigned long long), 256);
+    p.total = off;
+    return p;
+}
+
 // (a 1 x 1 convolution of stride 1 is a linear layer)
 bool conv_dx_is_linear(int32_t R, int32_t S, int32_t stride) { return R == 1 && S == 1 && stride == 1; }
 
@@ -2250,9 +2329,8 @@ size_t qconv_bwd_activations_workspace_bytes(int32_t B, int32_t H, int32_t W, in
     const double cols = C <= 48 ? (C + 15) / 16 * 16 : (C + 63) / 64 * 64;
     const double work = (double)B * H * W * cols * (double)(((int64_t)R * S * N + 15) / 16 * 16) / (stride * stride);
     size_t own = is_linear || few || work <= 5e8 ? L.planes : L.total;
-    const size_t maxima = L.planes + align_up((size_t)M_out * sizeof(unsigned int), 256);
     if (!conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride) && !is_linear) {
-        const size_t least = patch ? maxima : L.total;
+        const size_t least = patch ? patch_scratch(L, M_out, C).total : L.total;
         if (least > own) own = least;
     }
     const size_t linear = is_linear ? bwd_layout((int32_t)M_out, N, C).total : 0;
@@ -2286,26 +2364,35 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
     ConvDxClasses taps{};
     taps.tstep = stride;
     for (int c = 0; c < n_cls; ++c) taps.c[c] = ConvDxClass{grids[c].r0, grids[c].s0, grids[c].Rc, grids[c].Sc};
-    unsigned int *pixel_max = reinterpret_cast<unsigned int *>(base + L.planes);
+    const ConvDxWeights weights{w_idx, N, L.Np, R, S, C, taps, wr, L.ld};
     if (patch) {
-        int log_t = 0;
-        while (log_t < 6 && 2 << log_t <= N / 4) ++log_t;
-        CDL_LAUNCH("pixel_max_kernel", stream, pixel_max_kernel, dim3(L.n_max), dim3(256), 0, g, (int)M_out, N, log_t, pixel_max, block_max, ss_b, n_cls * C);
-    } else {
-        CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, n_cls * C);
+        static_assert(kPatchMaxima >= kConvDxMaxBlocks, "maxima that a block of the patch kernel reads");
+        const PatchScratch at = patch_scratch(L, M_out, C);
+        PatchPrep p{};
+        p.weights = weights;
+        p.nx = at.nx; p.ny = at.ny; p.nz = n_cls;
+        p.part = reinterpret_cast<unsigned int *>(base + at.part);
+        p.flags = reinterpret_cast<unsigned long long *>(base + at.flags);
+        p.tag = next_finish_tag();
+        p.col_max = ss_b;
+        p.g = g; p.pixels = (int)M_out; p.N = N;
+        while (p.log_t < 6 && 2 << p.log_t <= N / 4) ++p.log_t;
+        p.pixel_max = reinterpret_cast<unsigned int *>(base + at.pixel_max);
+        p.block_max = block_max;
+        const int64_t blocks = (int64_t)at.nx * at.ny * n_cls;
+        if (blocks > 1 << 30) return CDL_ERR_RANGE;
+        CDL_LAUNCH("conv_patch_prep_kernel", stream, conv_patch_prep_kernel, dim3((unsigned)blocks + (unsigned)L.n_max), dim3(256), 0, p);
+        const int rc = check_launch();
+        if (rc != CDL_OK) return rc;
+        return launch_conv_dx_patch(g, wr, PatchMaxima{p.pixel_max, block_max, ss_b, L.n_max, (int)(at.ny * n_cls)}, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, delta_w, d_x_hat, stream);
     }
+    CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, g, M_out * N, block_max, ss_b, n_cls * C);
     // (one limb count for all classes: the largest column sum of any of them)
     PlanArgs pa{plan, block_max, L.n_max, nullptr, ss_b, 0, n_cls * C, 1.0f, delta_w, reinterpret_cast<unsigned long long *>(base + L.flags), next_finish_tag()};
     const dim3 prep((unsigned)(L.ld / 64), (unsigned)((C + 63) / 64), (unsigned)n_cls);
     const bool plan_apart = (int64_t)prep.x * prep.y * prep.z > kPlanMaxBlocks;
-    if (plan_apart || patch) pa.plan = nullptr;
-    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, prep, dim3(256), 0, w_idx, N, L.Np, R, S, C, taps, wr, L.ld, ss_b, patch, pa);
-    if (patch) {
-        static_assert(kPatchMaxima >= kConvDxMaxBlocks, "maxima that a block of the patch kernel reads");
-        const int rc = check_launch();
-        if (rc != CDL_OK) return rc;
-        return launch_conv_dx_patch(g, wr, PatchMaxima{pixel_max, block_max, ss_b, L.n_max, n_cls * C}, L.ld, grids, n_cls, B, H, W, C, N, L.Np, P, Q, stride, delta_w, d_x_hat, stream);
-    }
+    if (plan_apart) pa.plan = nullptr;
+    CDL_LAUNCH("conv_dx_prep_kernel", stream, conv_dx_prep_kernel, prep, dim3(256), 0, weights, ss_b, pa);
     if (plan_apart)
         CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, plan, block_max, L.n_max,
                    (const unsigned int *)nullptr, 0, ss_b, n_cls * C, 1.0f, delta_w);

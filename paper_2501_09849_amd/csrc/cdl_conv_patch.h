@@ -127,8 +127,8 @@ inline PatchPlan plan_patch(const ConvDxGrid *grids, int n_grids, int64_t B, int
     }
     // A block takes about 12 us beside its k-steps (0.28 us each), which short contractions do not pay for once there are enough blocks for
     // the passes that this kernel does without (15 - 25 us) not to count.  Digits made beforehand / patches, us: 59 x 52 x 52 x 240 -> 48, 3 x 3
-    // (18 steps, 5 K blocks)  129 / 150;  195 x 38 x 38 x 96 -> 24 (9, 4.4 K)  101 / 108;  19 x 45 x 45 x 208 -> 36 (18, 1.2 K)  49 / 48;
-    // 27 x 56 x 56 x 64 -> 24 (9, 0.7 K)  44 / 33.
+    // (18 steps, 5 K blocks)  129 / 150;  195 x 38 x 38 x 96 -> 24 (9, 4.4 K)  101 / 108;  19 x 45 x 45 x 208 -> 36 (18, 1.2 K)  49 / 45;
+    // 27 x 56 x 56 x 64 -> 24 (9, 0.7 K)  44 / 31.
     int taps = 0;
     for (int i = 0; i < n_grids; ++i) taps += grids[i].Rc * grids[i].Sc;
     if (best.served && taps * (Np / 32) < 20) {

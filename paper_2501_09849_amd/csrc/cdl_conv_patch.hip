@@ -11,12 +11,12 @@
 //
 // What bounds it: the matrix cores while both blocks of a compute unit are in their k-steps (pipes 55 % busy over the whole kernel at 14 x 14 x 256; LDS
 // and the vector cache at half their rates); the rest of a block - digits 5 us, outputs 3 of 30 - hides only behind the other block.
-// Stride 2: 18 %, digits of 62 pixels for 32 of the grid, and waves of one to four taps.  (With the largest entry taken by every block
-// from g itself, 6 us more a block and no pass before, and a limb count of its own, the whole call was as long within 5 %.)  Before, a pass
+// Stride 2: 18 %, digits of 62 pixels for 32 of the grid, and waves of one to four taps.  (The largest entry taken by every block from g itself, with no
+// pass before, and a limb count of its own: 87 - 87, 97 - 89, 130 - 129 us the call at 28 x 28 x 128, stride 2, 14 x 14 x 256.)  Before, a pass
 // that made the digits ran first and the product read them tap by tap through L2 into LDS, where
 // reads and writes together took longer than the matrix instructions.  The whole call, us, with uniform indices: 256 images of
-// 14 x 14 x 256 -> 256, 3 x 3  216 -> 154;  128 x 28 x 28 x 128 -> 128  123 -> 101;  128 x 7 x 7 x 512 -> 512  139 -> 85;
-// 128 x 56 x 56 x 64 -> 128, stride 2  119 -> 96.
+// 14 x 14 x 256 -> 256, 3 x 3  216 -> 149;  128 x 28 x 28 x 128 -> 128  123 -> 94;  128 x 7 x 7 x 512 -> 512  139 -> 82;
+// 128 x 56 x 56 x 64 -> 128, stride 2  119 -> 88.
 #include "cdl_bwd_plan.h"
 #include "cdl_limbs.h"
 

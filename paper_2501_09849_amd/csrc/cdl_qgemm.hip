@@ -1376,7 +1376,8 @@ void conv_dx_prep_kernel(ConvDxWeights a, unsigned int *col_abs /* zeroed */, Pl
 
 // What the kernel on patches needs (cdl_conv_patch.hip), in one launch: blocks 0 .. nx ny nz - 1 rearrange the weights, and the last block of every 64
 // channels of a class adds up the column sums of |w| of its blocks and leaves the largest; the others take the largest |g| of every
-// pixel (as the bits of a float), and of all their pixels.  Waiting is for lower blocks only (cdl_finish.h); the weights' 8 us pass beside the pass over g.
+// pixel (as the bits of a float), and of all their pixels.  Waiting is for lower blocks only (cdl_finish.h).  15 us for
+// 51 MB of g and 0.6 MB of weights; in two launches 11 + 8.
 struct PatchPrep {
     ConvDxWeights weights;
     int nx, ny, nz;

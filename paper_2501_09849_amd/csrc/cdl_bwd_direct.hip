@@ -1237,7 +1237,7 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
     // (as far as sums in double are as fast as limbs, both products, us: 2000 x 300 x 1000 67 / 70;  1000 x 1000 x 1000 88 / 65.  By what is asked for: only
     // outputs next to entries of g more than 2^20 times as large can show it.)
     const double asked = (d.a.out && !only_b ? padded_macs(M, N, K) : 0.0) + (d.b.out ? padded_macs(N, M, K) : 0.0);
-    const bool exact = asked <= 7e8 && (!bwd_direct_diag(M, N, K) || (M <= 5120 && N <= 5120));
+    const bool exact = asked <= 7e8 && (!diag || (M <= 5120 && N <= 5120));
     d.a.rounds_to = digits_round_to(d.a, exact);
     d.b.rounds_to = digits_round_to(d.b, exact);
     DirectArgs a{};

@@ -104,16 +104,16 @@ def test_small_entries_next_to_large_ones(kind, M, N, K, oa, ob):
     _check(d_b, np.ascontiguousarray(g64.T), a.astype(np.float64) + oa, 0.5, "d_b_hat")
 
 
-# the same for the gradients of a convolution, 16 x 28 x 28 x 64 -> 64 and with stride 2
-@pytest.mark.parametrize("geom", [(16, 28, 28, 64, 64, 3, 3, 1, 1), (24, 33, 31, 96, 64, 3, 3, 2, 1)])
-@pytest.mark.parametrize("size", [1.0, 2.0 ** 30])
-def test_small_entries_next_to_large_ones_conv(geom, size):
+# the same for the gradients of a convolution, 16 x 28 x 28 x 64 -> 64, with stride 2, and a 1 x 1 kernel (a linear layer of 10240 rows)
+@pytest.mark.parametrize("geom", [(16, 28, 28, 64, 64, 3, 3, 1, 1), (24, 33, 31, 96, 64, 3, 3, 2, 1), (40, 16, 16, 128, 128, 1, 1, 1, 0)])
+@pytest.mark.parametrize("size,scale", [(1.0, 1.0), (2.0 ** 30, 1.0), (2.0 ** 30, 2.0 ** -40)])
+def test_small_entries_next_to_large_ones_conv(geom, size, scale):
     import paper_2501_09849_amd as cdl
     torch = gu.torch_mod()
     B, H, W, C, N, R, S, stride, pad = geom
     P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
     gen = torch.Generator().manual_seed(H)
-    g = torch.randn((B, P, Q, N), generator=gen)
+    g = torch.randn((B, P, Q, N), generator=gen) * scale
     g[..., 5] *= size                       # a channel (activations' gradient) and a pixel (weights')
     g[1, 2, 3, :5] *= size
     x = torch.randint(-128, 128, (B, H, W, C), generator=gen, dtype=torch.int32)

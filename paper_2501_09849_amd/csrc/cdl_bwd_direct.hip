@@ -1170,6 +1170,10 @@ static int digits_round_to(const DirectProduct &p, bool exact)
     return e < -1 ? -1 : (e > 254 ? 254 : e);
 }
 
+// Products of `macs` multiply-adds in all that sums in double serve as fast as limbs (both, us, in double / on limbs: 2000 x 300 x 1000 67 / 70;  1000 x 1000 x 1000
+// 88 / 65), with the diagnostic words as far as a contraction in one piece is.
+static bool exact_serves(double macs, int32_t M, int32_t N, bool diag) { return macs <= 7e8 && (!diag || (M <= 5120 && N <= 5120)); }
+
 // The products of a call as a launch: in double or on digits, and the plan.
 struct BwdDirectPlan {
     DirectProduct a, b;
@@ -1222,6 +1226,9 @@ bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool only_b, double *par
     plan_bwd_direct(d, M, N, K, only_b, words && bwd_direct_diag(M, N, K), partial, max_splits);
     int64_t blocks = 0;
     for (int i = 0; i < d.n; ++i) blocks += (int64_t)d.ps[i]->tiles_r * d.ps[i]->tiles_c * d.ps[i]->splits;
+    // (where both fit what double serves, see launch_bwd_direct: directly in any case, so that every product is exact)
+    const double both = padded_macs(N, M, K) + (only_b ? 0.0 : padded_macs(M, N, K));
+    if (blocks <= kDirRecords / 2 && exact_serves(both, M, N, words && bwd_direct_diag(M, N, K))) return true;
     return !d.digits || (blocks <= kDirRecords / 2 && 1.25 * d.us < 27.0 + 4.8e-9 * macs + 0.36e-6 * bytes);
 }
 
@@ -1234,10 +1241,9 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
     plan_bwd_direct(d, M, N, K, only_b, diag, partial, max_splits);
     d.a.g = g; d.a.idx = b_idx; d.a.ldg = N; d.a.ldi = K; d.a.offset = b_offset; d.a.vec = N % 4 == 0; d.a.delta = (double)delta_b; d.a.out = d_a_hat;
     d.b.g = g; d.b.idx = a_idx; d.b.ldg = N; d.b.ldi = K; d.b.offset = a_offset; d.b.delta = (double)delta_a; d.b.out = d_b_hat;
-    // (as far as sums in double are as fast as limbs, both products, us: 2000 x 300 x 1000 67 / 70;  1000 x 1000 x 1000 88 / 65.  By what is asked for: only
-    // outputs next to entries of g more than 2^20 times as large can show it.)
+    // (by what is asked for: only outputs next to entries of g more than 2^20 times as large can show it)
     const double asked = (d.a.out && !only_b ? padded_macs(M, N, K) : 0.0) + (d.b.out ? padded_macs(N, M, K) : 0.0);
-    const bool exact = asked <= 7e8 && (!diag || (M <= 5120 && N <= 5120));
+    const bool exact = exact_serves(asked, M, N, diag);
     d.a.rounds_to = digits_round_to(d.a, exact);
     d.b.rounds_to = digits_round_to(d.b, exact);
     DirectArgs a{};

@@ -104,6 +104,13 @@ def test_small_entries_next_to_large_ones(kind, M, N, K, oa, ob):
     _check(d_b, np.ascontiguousarray(g64.T), a.astype(np.float64) + oa, 0.5, "d_b_hat")
 
 
+# up to 0.7 * 10^9 multiply-adds in whole tiles, both products: directly, also where limbs would take less time by the estimate
+@pytest.mark.parametrize("M,N,K", [(40, 5376, 128), (136, 385, 5631), (16, 3687, 3605), (1583, 75, 2702), (25, 2624, 4032)])
+@pytest.mark.parametrize("kind", [1.0, 2.0 ** 30])
+def test_few_multiplications(M, N, K, kind):
+    test_small_entries_next_to_large_ones(kind, M, N, K, 0, 0)
+
+
 # the same for the gradients of a convolution, 16 x 28 x 28 x 64 -> 64, with stride 2, and a 1 x 1 kernel (a linear layer of 10240 rows)
 @pytest.mark.parametrize("geom", [(16, 28, 28, 64, 64, 3, 3, 1, 1), (24, 33, 31, 96, 64, 3, 3, 2, 1), (40, 16, 16, 128, 128, 1, 1, 1, 0)])
 @pytest.mark.parametrize("size,scale", [(1.0, 1.0), (2.0 ** 30, 1.0), (2.0 ** 30, 2.0 ** -40)])

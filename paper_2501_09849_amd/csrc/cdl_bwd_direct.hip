@@ -1337,12 +1337,15 @@ static DxForm conv_dx_form(int64_t pixels, int32_t N, int32_t C, int32_t R, int3
     return least * N >= kDigitStep && cycles >= kDigitsFrom / 2 ? kWideDigits : kWide;
 }
 
+// what sums in double serve, in tiles of 16 columns up to 48 channels; macs: multiply-adds of a column
+static bool conv_dx_exact(double macs, int32_t C) { return macs * (double)round_up(C, C <= 48 ? 16 : 64) <= kConvExactMacs; }
+
 bool conv_dx_direct_serves(int64_t pixels, int32_t N, int32_t C, int32_t R, int32_t S, int32_t stride)
 {
     if (C <= 32 && (int64_t)R * S * N <= 288) return true;      // (any number of pixels: most of a limb tile would be padding)
     const DxForm form = conv_dx_form(pixels, N, C, R, S, stride);
-    const double cols = (double)round_up(C, form == kThin ? 16 : 64);
-    return (double)pixels * cols * (double)round_up((int64_t)R * S * N, 16) / (stride * stride) <= (form == kWideDigits ? kConvDxDirectMaxMacs : kConvDxDoubleMaxMacs);
+    const double macs = (double)pixels * (double)round_up((int64_t)R * S * N, 16) / (stride * stride);      // a column
+    return macs * (double)round_up(C, form == kThin ? 16 : 64) <= (form == kWideDigits ? kConvDxDirectMaxMacs : kConvDxDoubleMaxMacs) || conv_dx_exact(macs, C);
 }
 
 int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid *grids, int n_grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
@@ -1357,7 +1360,7 @@ int launch_conv_dx_direct(const float *g, const int8_t *w_idx, const ConvDxGrid 
         DirectProduct &p = a.p[c];
         p.g = g; p.idx = w_idx; p.rows = B * k.Hc * k.Wc; p.cols = C; p.kc = k.Rc * k.Sc * N;
         p.delta = (double)delta_w; p.out = d_x_hat; p.splits = 1;
-        p.rounds_to = digits_round_to(p, (double)B * H * W * (double)round_up(C, C <= 48 ? 16 : 64) * (double)round_up((int64_t)R * S * N, 16) / (stride * stride) <= kConvExactMacs);
+        p.rounds_to = digits_round_to(p, conv_dx_exact((double)B * H * W * (double)round_up((int64_t)R * S * N, 16) / (stride * stride), C));
         const int64_t steps = ceil_div(p.kc, form == kWideDigits ? kDigitStep : 16), rows = ceil_div(p.rows, thin ? 64 : 16);
         p.steps = (int)steps;
         p.tiles_c = (int)ceil_div(C, thin ? 16 : 64);

@@ -111,8 +111,9 @@ def test_few_multiplications(M, N, K, kind):
     test_small_entries_next_to_large_ones(kind, M, N, K, 0, 0)
 
 
-# the same for the gradients of a convolution, 16 x 28 x 28 x 64 -> 64, with stride 2, and a 1 x 1 kernel (a linear layer of 10240 rows)
-@pytest.mark.parametrize("geom", [(16, 28, 28, 64, 64, 3, 3, 1, 1), (24, 33, 31, 96, 64, 3, 3, 2, 1), (40, 16, 16, 128, 128, 1, 1, 1, 0)])
+# the same for the gradients of a convolution, 16 x 28 x 28 x 64 -> 64, with stride 2, a 1 x 1 kernel (a linear layer of 10240 rows), 48 channels in double
+@pytest.mark.parametrize("geom", [(16, 28, 28, 64, 64, 3, 3, 1, 1), (24, 33, 31, 96, 64, 3, 3, 2, 1), (40, 16, 16, 128, 128, 1, 1, 1, 0),
+                                  (34, 60, 60, 48, 32, 3, 3, 2, 1)])
 @pytest.mark.parametrize("size,scale", [(1.0, 1.0), (2.0 ** 30, 1.0), (2.0 ** 30, 2.0 ** -40)])
 def test_small_entries_next_to_large_ones_conv(geom, size, scale):
     import paper_2501_09849_amd as cdl

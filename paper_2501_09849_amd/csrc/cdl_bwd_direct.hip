@@ -1211,12 +1211,12 @@ static void plan_bwd_direct(BwdDirectPlan &d, int32_t M, int32_t N, int32_t K, b
     if (d.n == 2 && ceil_div(d.b.steps_per_split, d.b.ksp) > ceil_div(d.a.steps_per_split, d.a.ksp)) { d.ps[0] = &d.b; d.ps[1] = &d.a; }
 }
 
-// Where the products are formed directly: the small ones, and of the others those whose plan takes less time than the limb products
+// Where the products are formed directly: the small ones, what double serves (exact_serves), and of the others those whose plan takes less time than the limb products
 // with their helpers, 27 us + 4.8 us for a thousand million multiply-adds in whole tiles + 0.36 us a megabyte (fitted to 54 shapes of
 // 30 M to 2.6 G multiply-adds, off by 17 %; the plan's time is 0.9 of the measured one, hence 1.25).  Both products, limbs / directly, us:
 //   307 x 1257 x 83  39 / 14     700 x 700 x 700  48 / 20      3914 x 1024 x 128  46 / 25    1092 x 1172 x 785  42 / 43
 //   12425 x 64 x 192  42 / 21    152 x 2252 x 928  43 / 24     9020 x 2048 x 128  116 / 93   2934 x 384 x 1152  47 / 61
-bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool only_b, double *partial, int max_splits, bool words)
+bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool only_b, double *partial, int max_splits, bool words, int asked)
 {
     if (K < 4) return false;
     const double macs = ((only_b ? 0.0 : (double)round_up(M, 32) * (double)round_up(N, 128)) + (double)round_up(N, 32) * (double)round_up(M, 128)) * (double)round_up(K, 128);
@@ -1226,9 +1226,8 @@ bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool only_b, double *par
     plan_bwd_direct(d, M, N, K, only_b, words && bwd_direct_diag(M, N, K), partial, max_splits);
     int64_t blocks = 0;
     for (int i = 0; i < d.n; ++i) blocks += (int64_t)d.ps[i]->tiles_r * d.ps[i]->tiles_c * d.ps[i]->splits;
-    // (where both fit what double serves, see launch_bwd_direct: directly in any case, so that every product is exact)
-    const double both = padded_macs(N, M, K) + (only_b ? 0.0 : padded_macs(M, N, K));
-    if (blocks <= kDirRecords / 2 && exact_serves(both, M, N, words && bwd_direct_diag(M, N, K))) return true;
+    // (what double serves goes directly in any case: exact products)
+    if (asked > 0 && blocks <= kDirRecords / 2 && exact_serves(asked * padded_macs(M, N, K), M, N, words && bwd_direct_diag(M, N, K))) return true;
     return !d.digits || (blocks <= kDirRecords / 2 && 1.25 * d.us < 27.0 + 4.8e-9 * macs + 0.36e-6 * bytes);
 }
 
@@ -1242,8 +1241,8 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
     d.a.g = g; d.a.idx = b_idx; d.a.ldg = N; d.a.ldi = K; d.a.offset = b_offset; d.a.vec = N % 4 == 0; d.a.delta = (double)delta_b; d.a.out = d_a_hat;
     d.b.g = g; d.b.idx = a_idx; d.b.ldg = N; d.b.ldi = K; d.b.offset = a_offset; d.b.delta = (double)delta_a; d.b.out = d_b_hat;
     // (by what is asked for: only outputs next to entries of g more than 2^20 times as large can show it)
-    const double asked = (d.a.out && !only_b ? padded_macs(M, N, K) : 0.0) + (d.b.out ? padded_macs(N, M, K) : 0.0);
-    const bool exact = exact_serves(asked, M, N, diag);
+    const int asked = (d.a.out && !only_b ? 1 : 0) + (d.b.out ? 1 : 0);
+    const bool exact = exact_serves(asked * padded_macs(M, N, K), M, N, diag);
     d.a.rounds_to = digits_round_to(d.a, exact);
     d.b.rounds_to = digits_round_to(d.b, exact);
     DirectArgs a{};

@@ -2488,7 +2488,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     if (cw && cw->R == 1 && cw->S == 1 && cw->stride == 1 && cw->pad == 0) cw = nullptr;
     if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.direct_splits, stream);
     // (many outputs of few multiplications each: one thread per four outputs, see da_direct_kernel)
-    const bool only_b = is_conv_weights || (N <= kDirectMaxN && ((int64_t)M * K >= kDirectMinOutputs || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true)));
+    const bool only_b = is_conv_weights || (N <= kDirectMaxN && ((int64_t)M * K >= kDirectMinOutputs || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0)));
     if (d_a_hat && only_b) {
         // four columns per thread (two where 32 index values per column would not leave registers for four)
         const int c_per = N <= 16 ? 4 : 2;
@@ -2503,7 +2503,8 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         if (!want_db) return check_launch();
     }
 
-    if (!cw && bwd_direct_serves(M, N, K, only_b, partial, L.direct_splits, !is_conv_weights))
+    const int asked = (d_a_hat ? 1 : 0) + (want_db ? 1 : 0);
+    if (!cw && bwd_direct_serves(M, N, K, only_b, partial, L.direct_splits, !is_conv_weights, asked))
         return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.direct_splits, only_b, !is_conv_weights, stream);
 
     const bool by_rows = d_a_hat && limb_by_rows(M, N, K, L.splits);

@@ -20,7 +20,7 @@ def _check(got, g64, idx64, step, what):
     assert np.all(off <= bound + 1.5e-45), "%s: %.3g of the bound" % (what, np.max(off / (bound + 1e-300)))
 
 
-def _run(g, a, b, oa=0, ob=0):
+def _run(g, a, b, oa=0, ob=0, apart=False):
     import paper_2501_09849_amd as cdl
     torch = gu.torch_mod()
     M, N, K = g.shape[0], g.shape[1], a.shape[1]
@@ -30,7 +30,8 @@ def _run(g, a, b, oa=0, ob=0):
     for _ in range(2):
         d_a.fill_(float("nan"))
         d_b.fill_(float("nan"))
-        cdl.cdl_qgemm_bwd_offset(gu.dev(g), gu.dev(a), gu.dev(b), M, N, K, 0.5, 0.25, oa, ob, d_a, d_b, ws)
+        for x, y in ((d_a, None), (None, d_b)) if apart else ((d_a, d_b),):
+            cdl.cdl_qgemm_bwd_offset(gu.dev(g), gu.dev(a), gu.dev(b), M, N, K, 0.5, 0.25, oa, ob, x, y, ws)
     torch.cuda.synchronize()
     return d_a.cpu().numpy(), d_b.cpu().numpy(), ws
 
@@ -85,7 +86,7 @@ def test_scales(kind, M, N, K):
 @pytest.mark.parametrize("kind", [2.0 ** 18, 2.0 ** 24, 2.0 ** 30, 2.0 ** 60, "mixed"])
 @pytest.mark.parametrize("M,N,K", [(2048, 64, 256), (256, 1000, 512), (600, 650, 300), (700, 63, 400), (5120, 64, 192)])
 @pytest.mark.parametrize("oa,ob", [(0, 0), (128, 128)])
-def test_small_entries_next_to_large_ones(kind, M, N, K, oa, ob):
+def test_small_entries_next_to_large_ones(kind, M, N, K, oa, ob, apart=False):
     rng = np.random.default_rng(K)
     g = rng.standard_normal((M, N))
     a, b = _indices(M, N, K)
@@ -98,17 +99,19 @@ def test_small_entries_next_to_large_ones(kind, M, N, K, oa, ob):
     b[5, ::2] = -ob
     a[70 % M, ::2] = -oa
     g = g.astype(np.float32)
-    d_a, d_b, _ = _run(g, a, b, oa, ob)
+    d_a, d_b, _ = _run(g, a, b, oa, ob, apart)
     g64 = g.astype(np.float64)
     _check(d_a, g64, b.astype(np.float64) + ob, 0.25, "d_a_hat")
     _check(d_b, np.ascontiguousarray(g64.T), a.astype(np.float64) + oa, 0.5, "d_b_hat")
 
 
-# up to 0.7 * 10^9 multiply-adds in whole tiles, both products: directly, also where limbs would take less time by the estimate
-@pytest.mark.parametrize("M,N,K", [(40, 5376, 128), (136, 385, 5631), (16, 3687, 3605), (1583, 75, 2702), (25, 2624, 4032)])
+# up to 0.7 * 10^9 multiply-adds of what is asked for, in whole tiles: directly, also where limbs would take less time by the estimate.  apart: one
+# product to a call, layers that are too large for both
+@pytest.mark.parametrize("M,N,K,apart", [(40, 5376, 128, False), (136, 385, 5631, False), (16, 3687, 3605, False), (1583, 75, 2702, False), (25, 2624, 4032, False),
+                                         (489, 512, 2112, True), (74, 3648, 1728, True), (2208, 64, 4672, True)])
 @pytest.mark.parametrize("kind", [1.0, 2.0 ** 30])
-def test_few_multiplications(M, N, K, kind):
-    test_small_entries_next_to_large_ones(kind, M, N, K, 0, 0)
+def test_few_multiplications(M, N, K, apart, kind):
+    test_small_entries_next_to_large_ones(kind, M, N, K, 0, 0, apart)
 
 
 # the same for the gradients of a convolution, 16 x 28 x 28 x 64 -> 64, with stride 2, a 1 x 1 kernel (a linear layer of 10240 rows), 48 channels in double

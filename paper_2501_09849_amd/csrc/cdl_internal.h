@@ -10,8 +10,7 @@
 
 namespace cdl {
 
-// Most blocks any quantizer kernel is launched with; also the number of per-block partial
-// results the workspace holds.  256 CUs x 8 resident blocks of 256 threads.
+// Most blocks a quantizer kernel that loops over its tensor is launched with.  256 CUs x 8 resident blocks of 256 threads.
 constexpr int kMaxQuantBlocks = 2048;
 constexpr int kQuantThreads = 256;
 
@@ -84,15 +83,15 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
                         int8_t *idx, float *soft, float *marg, float *entropy_bits,
                         void *ws, hipStream_t stream);
 
-// scalars: the part of a call's workspace that holds the blocks' sums of the two scalar gradients (kQuantScalarBytes).
+// scalars: the part of a call's workspace that holds the blocks' sums of the two scalar gradients (quantize_scalar_bytes).
 // g and dtheta may be the same tensor.
 // Behind them, the table of the soft regime (cdl_soft.hip): made where the call has a workspace and kSoftFrom entries or more.
 constexpr int64_t kSoftFrom = 1 << 16;
 constexpr int kSoftMaxBins = 512;
 constexpr int kSoftCoefs = 10;
 constexpr size_t kSoftBinBytes = kSoftCoefs * sizeof(double), kSoftTableBytes = kSoftMaxBins * kSoftBinBytes;
-constexpr size_t kQuantSumBytes = (size_t)kMaxQuantBlocks * 2 * sizeof(double);
-constexpr size_t kQuantScalarBytes = kQuantSumBytes + kSoftTableBytes;
+size_t quantize_sum_bytes(int64_t n);        // 16 bytes per block
+size_t quantize_scalar_bytes(int64_t n);     // the sums, then the table
 void *quantize_scalar_area(void *ws, int64_t n, int32_t n_levels);
 int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams &p,
                         float *dtheta, float *d_delta, float *d_alpha,

@@ -2020,7 +2020,8 @@ BwdLayout bwd_layout(int32_t M, int32_t N, int32_t K)
     L.block_max = off; off += align_up((size_t)L.n_max * sizeof(unsigned int), 256);
     L.ss_a = off;    off += align_up((size_t)K * sizeof(unsigned int), 256);   // sums of |a_idx| per column, directly followed by
     L.ss_b = off;    off += align_up((size_t)K * sizeof(unsigned int), 256);   // sums of |b_idx| per column (cleared together)
-    L.scalars = off; off += kQuantScalarBytes;     // the quantizers' backward passes that follow in the same call
+    const int64_t na = (int64_t)M * K, nb = (int64_t)N * K;
+    L.scalars = off; off += align_up(quantize_scalar_bytes(na > nb ? na : nb), 256);     // the quantizers' backward passes that follow in the same call
     L.bt = off;      off += align_up((size_t)pad_to(K, 32) * (size_t)L.ldn, 256);           // b_idx^T: [K][ldn], or in fragments (limb_by_rows)
     L.at = off;      off += align_up((size_t)K * (size_t)L.ldm, 256);           // a_idx^T: [K][ldm]
     L.partial = off; off += align_up((size_t)(L.splits > L.direct_splits ? L.splits : L.direct_splits) * (size_t)N * (size_t)K * sizeof(double), 256);

@@ -34,10 +34,45 @@
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 namespace cdl {
 
 namespace {
+
+// A wave's loads and stores share one counter that goes down in the order of their issue: in a loop that loads, computes and stores, the
+// wait for a trip's loads is also a wait for the stores of the trip before it, which take microseconds to complete, and blocks that drift
+// apart spread the accesses in flight over the whole tensor.  Tensors of more than kOneTripEntries therefore go through in one trip:
+// a block of kOneTripThreads issues all its loads (kOneTripVectors of four entries a thread) before its first store, and blocks
+// start in the order of the tensor.  us, as a loop of up to 2048 blocks / so (with the shorter arithmetic of cdl_quantizer_math.h), cold:
+// gradient (8 B read, 4 written an entry) 12.8 M entries 26.9 / 24.9, 25.6 M 51 / 47.5, 50.3 M 102 / 94, 115.6 M 238 / 221 (6.3 TB/s); index and
+// soft value without PMF (4 B read, 5 written) 12.8 M 22.4 / 20.1, 25.6 M 44 / 39, 50.3 M 83 / 70, 115.6 M 203 / 170 (6.1 TB/s).  Blocks of 256 x 2 vectors
+// against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.
+constexpr int kOneTripThreads = 256, kOneTripVectors = 2;
+constexpr int one_trip_threads(int u) { return u > 1 ? kOneTripThreads : kQuantThreads; }
+constexpr int64_t kOneTripEntries = 4ll * kMaxQuantBlocks * kQuantThreads;
+
+// f(std::true_type) or f(std::false_type): a switch of the launch taken once, so that no load waits at a branch for another
+template <typename F>
+__device__ __forceinline__ void with_constant(bool yes, F f)
+{
+    if (yes) f(std::true_type{});
+    else f(std::false_type{});
+}
+
+// group(v, N): N vectors of four entries v, v + T, .. of n4.  U > 1: U vectors a thread in the block's one trip (without a branch around any: it
+// would take the loads with it, behind the stores), in the last block one at a time.  U == 1: a loop over the tensor.
+template <int T, int U, typename F>
+__device__ __forceinline__ void one_trip_or_loop(int64_t n4, F group)
+{
+    const int64_t v0 = (int64_t)blockIdx.x * T * U;
+    if (U > 1 && v0 + T * U <= n4) group(v0 + threadIdx.x, std::integral_constant<int, U>{});
+    else {
+        const int64_t end = U > 1 ? (v0 + T * U < n4 ? v0 + T * U : n4) : n4;
+#pragma unroll 1
+        for (int64_t v = v0 + threadIdx.x; v < end; v += U > 1 ? T : (int64_t)gridDim.x * T) group(v, std::integral_constant<int, 1>{});
+    }
+}
 
 constexpr int kPad = 4;   // spare histogram bins on each side, so that band offsets never leave the array
 
@@ -83,52 +118,162 @@ void marginal_finalize_kernel(const unsigned long long *__restrict__ rows, int n
 // Forward kernel.  One thread handles four consecutive entries per trip of a grid-stride loop
 // (one 16-byte load, one 16-byte store of soft values, one 4-byte store of indices).
 //
-// MARG: the CPMF of every entry is added into a histogram in LDS, in fixed point: a probability
-// p is added as the integer floor(p * 2^s + 1/2).  (LDS integer atomics run at ~10 lane updates
-// per clock per CU on this chip, fp32 LDS atomics at a thirtieth of that; integer sums are also
-// independent of the order of the adds, so the result is reproducible.)  The block keeps 32 copies of
-// the histogram, bin-major and copy-minor, and lane l uses copy l mod 32: the copy is the LDS bank, so
-// the lanes of one instruction never meet in a bank except lane l with lane l + 32 (measured against
-// 4 or 16 copies per wave, where different bins fall into the same bank: -8 % on the whole forward
-// kernel at 255 levels, -22 % on the pass that only builds the histogram).  s comes from
-// kHistScaleBits: with at most kMaxHistTrips trips of the loop a cell never exceeds 2^31.
-// kPad spare bins on each side take the zero weights of levels that do not exist.  At the end
-// the block adds the copies into 64-bit sums, and marginal_finish adds these over all blocks.
+// MARG: the CPMF of every entry is added up in LDS, in fixed point: a probability p is added as p * 2^s rounded to an integer.
+// (LDS integer atomics run at ~10 lane updates per clock per CU on this chip, fp32 LDS atomics at a thirtieth of that;
+// integer sums are also independent of the order of the adds, so the result is reproducible.)  s comes from
+// kHistScaleBits: with at most kMaxHistTrips trips of the loop a cell never exceeds 2^31.  The block keeps 32 copies of the cells,
+// copy-minor, and lane l uses copy l mod 32: the copy is the LDS bank (pair of banks), so the lanes of one instruction never meet
+// in a bank except lane l with lane l + 32 (measured against 4 or 16 copies per wave, where different bins fall into the same bank:
+// -8 % on the whole forward kernel at 255 levels, -22 % on the pass that only builds the histogram).
+//
+// BINS: one 32-bit cell per level; kPad spare bins on each side take the zero weights of levels that do not exist.
+// PAIRS (unrolled bands whose cells fit kPairBytes: up to 97, 72, 48, 36 levels for W = 1 .. 4): per anchor level c the probabilities of
+// the levels c + j and c - j are the halves of one 64-bit cell, j = 1 .. W, and that of level c is what is missing to the number of
+// entries: W atomics an entry instead of 2 W + 1 (W = 2: 11 us of LDS time per 25.6 M entries instead of 16).  The kernel is bound by
+// the instructions it issues, and here the conversion to an integer costs none: p * 2^s + kHistMagic, a float in [2^23, 2^24), has the integer
+// in its low bits, and what the other bits add up to (kHistOne per entry) is taken off at the end.  The number of entries of a cell is read from
+// the low half of the outermost pair, whose probabilities are so small that their sum stays below 2^20 (outer_pair_is_small; sets of up to
+// five levels in the soft regime keep the bins), for W = 1 from a 32-bit cell that counts.
+// At the end the block adds the copies into 64-bit sums per level, and marginal_end adds these over all blocks.
+// us, forward pass with PMF and the launch that ends it, cold, before (bins, 74 instructions an entry) / so (53): 25.6 M entries of 31 levels 61 / 55,
+// 115.6 M of 16 levels 214 / 204 (bins with the shorter arithmetic: 50.3 M of 255 levels 100 / 92).
 // ------------------------------------------------------------------------------------------
+constexpr int kHistCopies = 32;
+constexpr float kHistMagic = 8388608.0f + 1048576.0f;
+constexpr unsigned int kHistOne = 0x4B100000u;      // the bits of kHistMagic
+constexpr int kPairBytes = 39 << 10;                // four blocks to a compute unit
+
+template <int W, bool PAIRS>
+struct HistCells {
+    unsigned int *bins;                // BINS, this lane's copy: [bin][copies]
+    unsigned long long *pairs;         // PAIRS, this lane's copy: [level][W][copies]
+    unsigned int *counts;              // PAIRS and W = 1, this lane's copy: [level][copies]
+    // level: as the cells' pointers count, which start at level 0 whether it is in the set or not
+    __device__ __forceinline__ void add(const Band<W> &b, int level, float inv)
+    {
+        constexpr int R = kHistCopies;
+        const float invs = inv * (float)(1u << kHistScaleBits);
+        if (PAIRS) {
+            unsigned long long *h = pairs + level * (W * R);
+#pragma unroll
+            for (int j = 1; j <= W; ++j) {
+                float up = fmaf(b.up[j - 1], invs, kHistMagic), dn = fmaf(b.dn[j - 1], invs, kHistMagic);
+                if (W != 2) { up = fmaxf(up, kHistMagic); dn = fmaxf(dn, kHistMagic); }      // (a NaN adds 0; the bands of W = 2 have none)
+                atomicAdd(h + (j - 1) * R, (unsigned long long)__float_as_uint(up) | ((unsigned long long)__float_as_uint(dn) << 32));
+            }
+            if (W == 1) atomicAdd(counts + level * R, 1u);
+        } else {
+            unsigned int *h = bins + (level + kPad - W) * R;   // bin of level c-W
+            atomicAdd(h + W * R, (unsigned int)fmaf(b.ctr, invs, 0.5f));
+#pragma unroll
+            for (int j = 1; j <= W; ++j) {
+                atomicAdd(h + (W + j) * R, (unsigned int)fmaf(b.up[j - 1], invs, 0.5f));
+                atomicAdd(h + (W - j) * R, (unsigned int)fmaf(b.dn[j - 1], invs, 0.5f));
+            }
+        }
+    }
+};
+
+// Bytes of a block's cells
+__host__ __device__ __forceinline__ int hist_bytes_of(int levels, int w, bool pairs)
+{
+    return pairs ? levels * (4 * (2 * w + (w == 1)) * kHistCopies + 8 * (2 * w + 1)) : (levels + 2 * kPad) * 4 * kHistCopies;
+}
+
+// The halves of a cell after n adds, both below 2^31
+__device__ __forceinline__ void pair_halves(unsigned long long cell, unsigned int n, unsigned int &low, unsigned int &high)
+{
+    const unsigned long long base = (unsigned long long)n * kHistOne;
+    low = (unsigned int)cell - (unsigned int)base;
+    high = (unsigned int)(cell >> 32) - (unsigned int)base - (unsigned int)((base + low) >> 32);
+}
+
+// n from the low half of a cell, where that half's sum is below 2^20: n * (kHistOne >> 20) modulo 2^12
+__device__ __forceinline__ unsigned int pair_count(unsigned long long cell)
+{
+    constexpr unsigned int kInverse = 1105u;
+    static_assert(((kHistOne >> 20) * kInverse & 4095u) == 1u, "inverse modulo 2^12");
+    return ((unsigned int)cell >> 20) * kInverse & 4095u;
+}
+
+// From the cells of pairs to the block's sum for each level (returned in thread i < n_levels): sixteen threads to a level take two copies each.
+// sums: [n_levels][2 W + 1].  The caller has synchronised the block after the last add.
+template <int W, int T>
+__device__ __forceinline__ unsigned long long pair_levels(const unsigned long long *cells, const unsigned int *counts, unsigned long long *sums, int n_levels)
+{
+    constexpr int R = kHistCopies, P = 2 * W + 1;
+    const int sub = threadIdx.x & 15;
+    for (int c0 = 0; c0 < n_levels; c0 += T / 16) {
+        const int c = c0 + ((int)threadIdx.x >> 4);
+        unsigned long long v[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) v[i] = 0ull;
+        if (c < n_levels) {
+#pragma unroll
+            for (int q = 0; q < R / 16; ++q) {
+                const unsigned long long *h = cells + (size_t)c * (W * R) + sub + 16 * q;
+                const unsigned int n = W == 1 ? counts[c * R + sub + 16 * q] : pair_count(h[(W - 1) * R]);
+                v[0] += n;
+#pragma unroll
+                for (int j = 1; j <= W; ++j) {
+                    unsigned int low, high;
+                    pair_halves(h[(j - 1) * R], n, low, high);
+                    v[2 * j - 1] += low;
+                    v[2 * j] += high;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 16);
+        }
+        if (c < n_levels && sub == 0) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) sums[c * P + i] = v[i];
+        }
+    }
+    __syncthreads();
+    unsigned long long own = 0ull;
+    const int k = threadIdx.x;
+    if (k < n_levels) {
+        own = sums[k * P] << kHistScaleBits;
+#pragma unroll
+        for (int j = 1; j <= W; ++j) {
+            own -= sums[k * P + 2 * j - 1] + sums[k * P + 2 * j];
+            if (k >= j) own += sums[(k - j) * P + 2 * j - 1];
+            if (k + j < n_levels) own += sums[(k + j) * P + 2 * j];
+        }
+    }
+    return own;
+}
+
 // Quantizes four entries: soft values, level indices, and (MARG) their CPMFs into the histogram.
-template <int W, bool IDX, bool MARG>
-__device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QConst &k, unsigned int *my_hist,
+template <int W, bool IDX, bool MARG, bool PAIRS>
+__device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QConst &k, HistCells<W, PAIRS> &hist,
                                          float (&sv)[4], int (&ci)[4])
 {
-    constexpr int R = 32;
-    constexpr float kScale = (float)(1u << kHistScaleBits);
+    float cf[4];
+    if (W > 0) anchor_levels<IDX>(th, k, cf);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if (W > 0) {
             Band<W> b;
-            band_weights<W, IDX, 1>(th[e], k, b);
+            band_weights<W, 1>(th[e], cf[e], k, b);
             const float inv = fast_rcp(b.Z);
             sv[e] = fmaf(b.S1 * inv, k.delta, b.cf * k.delta);
             ci[e] = (int)b.cf;
-            if (MARG && e < cnt) {
-                unsigned int *h = my_hist + (ci[e] - k.lo + kPad - W) * R;   // bin of level c-W
-                const float invs = inv * kScale;
-                atomicAdd(h + W * R, (unsigned int)fmaf(b.ctr, invs, 0.5f));
-#pragma unroll
-                for (int j = 1; j <= W; ++j) {
-                    atomicAdd(h + (W + j) * R, (unsigned int)fmaf(b.up[j - 1], invs, 0.5f));
-                    atomicAdd(h + (W - j) * R, (unsigned int)fmaf(b.dn[j - 1], invs, 0.5f));
-                }
-            }
+            if (MARG && e < cnt) hist.add(b, ci[e], inv);
         } else {
+            constexpr int R = kHistCopies;
             GenericSums g;
             generic_sums<IDX>(th[e], k, g);
             const float inv = fast_rcp(g.Z);
             sv[e] = fmaf(g.S1 * inv, k.delta, g.cf * k.delta);
             ci[e] = (int)g.cf;
             if (MARG && e < cnt) {
-                unsigned int *h = my_hist + (ci[e] - k.lo + kPad) * R;
-                const float two_u = 2.0f * g.u, invs = inv * kScale;
+                unsigned int *h = hist.bins + (ci[e] + kPad) * R;
+                const float two_u = 2.0f * g.u, invs = inv * (float)(1u << kHistScaleBits);
                 for (int j = g.jlo; j <= g.jhi; ++j)
                     atomicAdd(h + j * R, (unsigned int)fmaf(generic_weight(j, two_u, k), invs, 0.5f));
             }
@@ -136,42 +281,87 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
     }
 }
 
-template <int W, bool IDX, bool SOFT, bool MARG, bool FEW>
-__global__ __launch_bounds__(MARG ? kMargThreads : kQuantThreads)
+// U: vectors of four entries a thread takes per trip.  U > 1 (tensors of more than kOneTripEntries): with MARG the loads of a trip
+// are issued before the trip before it is computed and stored, without MARG there is one trip.
+// Up to kKeepUpTo entries (128 MiB) theta is read by ordinary loads also where the rest streams: a backward pass that follows finds it in the last-level
+// cache (25.6 M entries, forward and backward 97 -> 91 us).  Larger tensors do not stay there, and in memory just written by others such
+// loads take longer (115.6 M entries: 234 against 190 us on the first pass, 196 against 187 later).
+constexpr int64_t kKeepUpTo = 1ll << 25;
+
+template <int W, bool IDX, bool SOFT, bool MARG, bool FEW, int U, bool PAIRS>
+__global__ __launch_bounds__(MARG ? kMargThreads : one_trip_threads(U))
 void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
                          int8_t *__restrict__ idx, float *__restrict__ soft,
                          MargFinish fin)
 {
-    extern __shared__ unsigned int lds_hist[];  // [n_levels + 2 kPad][32] when MARG
-    constexpr int R = 32;
-    constexpr int T = MARG ? kMargThreads : kQuantThreads;
-    const int bins = k.n_levels + 2 * kPad;
-    unsigned int *my_hist = lds_hist + (threadIdx.x & (R - 1));
+    extern __shared__ __attribute__((aligned(16))) unsigned int lds_hist[];  // MARG: hist_bytes_of(n_levels, W, PAIRS)
+    constexpr int R = kHistCopies;
+    constexpr int T = MARG ? kMargThreads : one_trip_threads(U);
+    HistCells<W, PAIRS> hist;
+    unsigned long long *const pairs = reinterpret_cast<unsigned long long *>(lds_hist);
+    unsigned int *const counts = lds_hist + k.n_levels * (2 * W * R);
+    constexpr int kWords = 2 * W + (W == 1);      // of the cells of a level, PAIRS
     if (MARG) {
-        for (int i = threadIdx.x; i < bins * R; i += T) lds_hist[i] = 0u;
+        const int copy = threadIdx.x & (R - 1);
+        hist.bins = lds_hist + copy - k.lo * R;
+        hist.pairs = pairs + copy - k.lo * (W * R);
+        hist.counts = counts + copy - k.lo * R;
+        const int cells = PAIRS ? k.n_levels * kWords * R : (k.n_levels + 2 * kPad) * R;
+        for (int i = 4 * threadIdx.x; i < cells; i += 4 * T) *reinterpret_cast<uint4 *>(lds_hist + i) = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
     }
 
     const int64_t n4 = n >> 2;
-    const int64_t stride = (int64_t)gridDim.x * T;
     float sv[4];
     int ci[4];
-    for (int64_t v = (int64_t)blockIdx.x * T + threadIdx.x; v < n4; v += stride) {
-        const float4 t = load_stream4(theta + 4 * v, k.stream);
-        const float th[4] = {t.x, t.y, t.z, t.w};
-        forward4<W, IDX, MARG>(th, 4, k, my_hist, sv, ci);
-        if (SOFT) store_stream4(soft + 4 * v, sv[0], sv[1], sv[2], sv[3], k.stream);
-        if (IDX) {
-            const uint32_t packed = pack_indices(ci[0], ci[1], ci[2], ci[3], k.idx_off);
-            reinterpret_cast<uint32_t *>(idx)[v] = packed;   // (ordinary store: the products read the indices next)
+    with_constant(n > kKeepUpTo, [&](auto loads) {
+    with_constant(k.stream != 0, [&](auto streams) {
+        auto vec = [&](const float4 &t, int64_t w) {
+            const float th[4] = {t.x, t.y, t.z, t.w};
+            forward4<W, IDX, MARG, PAIRS>(th, 4, k, hist, sv, ci);
+            if (SOFT) store_stream4(soft + 4 * w, sv[0], sv[1], sv[2], sv[3], streams.value);
+            if (IDX) {
+                const uint32_t packed = pack_indices(ci[0], ci[1], ci[2], ci[3], k.idx_off);
+                reinterpret_cast<uint32_t *>(idx)[w] = packed;   // (ordinary store: the products read the indices next)
+            }
+        };
+        if (MARG && U > 1) {
+            float4 t[U];
+            auto load = [&](int64_t v) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) t[u] = load_stream4(theta + 4 * (v + u * T < n4 ? v + u * T : 0), loads.value);
+            };
+            const int64_t stride = (int64_t)gridDim.x * T * U;
+            int64_t v = (int64_t)blockIdx.x * T * U + threadIdx.x;
+            load(v);
+            for (; v < n4; v += stride) {
+                float4 now[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) now[u] = t[u];
+                load(v + stride);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (u == 0 || v + u * T < n4) vec(now[u], v + u * T);
+            }
+        } else {
+            auto group = [&](int64_t v, auto count) {
+                constexpr int N = decltype(count)::value;
+                float4 t[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) t[u] = load_stream4(theta + 4 * (v + u * T), loads.value);
+#pragma unroll
+                for (int u = 0; u < N; ++u) vec(t[u], v + u * T);
+            };
+            one_trip_or_loop<T, U>(n4, group);
         }
-    }
+    });
+    });
     // ragged tail: the last 1..3 entries, one thread of the last block
     const int cnt = (int)(n - (n4 << 2));
     if (cnt > 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         float th[4];
         for (int e = 0; e < 4; ++e) th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
-        forward4<W, IDX, MARG>(th, cnt, k, my_hist, sv, ci);
+        forward4<W, IDX, MARG, PAIRS>(th, cnt, k, hist, sv, ci);
         for (int e = 0; e < cnt; ++e) {
             if (SOFT) soft[(n4 << 2) + e] = sv[e];
             if (IDX) idx[(n4 << 2) + e] = (int8_t)(ci[e] - k.idx_off);
@@ -181,7 +371,9 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
     if (MARG) {
         __syncthreads();
         unsigned long long own = 0ull;
-        if ((int)threadIdx.x < k.n_levels) {
+        if (PAIRS) {
+            own = pair_levels<W, T>(pairs, counts, reinterpret_cast<unsigned long long *>(lds_hist + k.n_levels * (kWords * R)), k.n_levels);
+        } else if ((int)threadIdx.x < k.n_levels) {
             const unsigned int *row = lds_hist + ((int)threadIdx.x + kPad) * R;
 #pragma unroll
             for (int r = 0; r < R; ++r) own += row[(r + (int)threadIdx.x) & (R - 1)];   // rotated start: no bank conflicts
@@ -195,32 +387,15 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
 // upstream gradient.  The two scalar sums are accumulated per thread in double and added up over
 // threads and blocks in a fixed order.
 // ------------------------------------------------------------------------------------------
-template <int W, bool DTHETA, bool SCALARS>
-__global__ __launch_bounds__(kQuantThreads)
+template <int W, bool DTHETA, bool SCALARS, int U>
+__global__ __launch_bounds__(one_trip_threads(U))
 void quantize_bwd_kernel(const float *__restrict__ theta, const float *g, int64_t n, QConst k,
                          float *dtheta /* may be g */, ScalarFinish fin)
 {
+    constexpr int T = one_trip_threads(U);
     double acc_d = 0.0, acc_a = 0.0;
     const int64_t n4 = n >> 2;
-    const int64_t stride = (int64_t)gridDim.x * kQuantThreads;
-    for (int64_t v = (int64_t)blockIdx.x * kQuantThreads + threadIdx.x; v < n4 + 1; v += stride) {
-        float th[4], ge[4];
-        int cnt;
-        if (v < n4) {
-            const float4 t = load_stream4(theta + 4 * v, k.stream);
-            const float4 q = load_stream4(g + 4 * v, k.stream);
-            th[0] = t.x; th[1] = t.y; th[2] = t.z; th[3] = t.w;
-            ge[0] = q.x; ge[1] = q.y; ge[2] = q.z; ge[3] = q.w;
-            cnt = 4;
-        } else {
-            cnt = (int)(n - (n4 << 2));
-            if (cnt == 0) break;
-            for (int e = 0; e < 4; ++e) {
-                th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
-                ge[e] = (e < cnt) ? g[(n4 << 2) + e] : 0.0f;
-            }
-        }
-        float dv[4];
+    auto four = [&](const float (&th)[4], const float (&ge)[4], float (&dv)[4]) {
         float sum_d = 0.0f, sum_a = 0.0f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -233,12 +408,39 @@ void quantize_bwd_kernel(const float *__restrict__ theta, const float *g, int64_
             }
         }
         if (SCALARS) { acc_d += (double)sum_d; acc_a += (double)sum_a; }
-        if (DTHETA) {
-            if (v < n4) store_stream4(dtheta + 4 * v, dv[0], dv[1], dv[2], dv[3], k.stream);
-            else for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
+    };
+    with_constant(k.stream != 0, [&](auto streams) {
+        // vectors v, v + T, ..
+        auto group = [&](int64_t v, auto count) {
+            constexpr int N = decltype(count)::value;
+            float4 t[N], q[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
+                q[u] = load_stream4(g + 4 * (v + u * T), streams.value);
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const float th[4] = {t[u].x, t[u].y, t[u].z, t[u].w}, ge[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+                float dv[4];
+                four(th, ge, dv);
+                if (DTHETA) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+            }
+        };
+        one_trip_or_loop<T, U>(n4, group);
+    });
+    // ragged tail: the last 1..3 entries, one thread of the last block
+    const int cnt = (int)(n - (n4 << 2));
+    if (cnt > 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        float th[4], ge[4], dv[4];
+        for (int e = 0; e < 4; ++e) {
+            th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
+            ge[e] = (e < cnt) ? g[(n4 << 2) + e] : 0.0f;
         }
+        four(th, ge, dv);
+        if (DTHETA) for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
     }
-    if (SCALARS) scalar_finish<kQuantThreads>(acc_d, acc_a, fin);
+    if (SCALARS) scalar_finish<T>(acc_d, acc_a, fin);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -583,7 +785,7 @@ __device__ __forceinline__ int draw_one(float th, float u, const QConst &k)
 {
     if (W > 0) {
         Band<W> b;
-        band_weights<W, false, 1>(th, k, b);
+        band_weights<W, 1>(th, anchor_level<false>(th, k), k, b);
         const float target = u * b.Z;
         float cum = 0.0f;
         int pick = -W - 1, last = 0;
@@ -614,20 +816,31 @@ __device__ __forceinline__ int draw_one(float th, float u, const QConst &k)
     }
 }
 
-template <int W>
-__global__ __launch_bounds__(kQuantThreads)
+template <int W, int U>
+__global__ __launch_bounds__(one_trip_threads(U))
 void quantize_draw_kernel(const float *__restrict__ theta, const float *__restrict__ u, int64_t n, QConst k,
                           int8_t *__restrict__ idx)
 {
+    constexpr int T = one_trip_threads(U);
     const int64_t n4 = n >> 2;
-    const int64_t stride = (int64_t)gridDim.x * kQuantThreads;
-    for (int64_t v = (int64_t)blockIdx.x * kQuantThreads + threadIdx.x; v < n4; v += stride) {
-        const float4 t = load_stream4(theta + 4 * v, k.stream);
-        const float4 r = load_stream4(u + 4 * v, k.stream);
-        const int c0 = draw_one<W>(t.x, r.x, k), c1 = draw_one<W>(t.y, r.y, k);
-        const int c2 = draw_one<W>(t.z, r.z, k), c3 = draw_one<W>(t.w, r.w, k);
-        reinterpret_cast<uint32_t *>(idx)[v] = pack_indices(c0, c1, c2, c3, k.idx_off);
-    }
+    with_constant(k.stream != 0, [&](auto streams) {
+        auto group = [&](int64_t v, auto count) {
+            constexpr int N = decltype(count)::value;
+            float4 t[N], r[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                t[i] = load_stream4(theta + 4 * (v + i * T), streams.value);
+                r[i] = load_stream4(u + 4 * (v + i * T), streams.value);
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c0 = draw_one<W>(t[i].x, r[i].x, k), c1 = draw_one<W>(t[i].y, r[i].y, k);
+                const int c2 = draw_one<W>(t[i].z, r[i].z, k), c3 = draw_one<W>(t[i].w, r[i].w, k);
+                reinterpret_cast<uint32_t *>(idx)[v + i * T] = pack_indices(c0, c1, c2, c3, k.idx_off);
+            }
+        };
+        one_trip_or_loop<T, U>(n4, group);
+    });
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
         for (int64_t e = n4 << 2; e < n; ++e) idx[e] = (int8_t)(draw_one<W>(theta[e], u[e], k) - k.idx_off);
 }
@@ -645,8 +858,8 @@ void quantize_draw_kernel(const float *__restrict__ theta, const float *__restri
 //     dH/dalpha =  (delta^2 / n)       sum_e (C2 - 2 r C1)
 // The table of l_k sits in LDS with kPad zeros on both sides.  dtheta = g_in + scale * dH/dtheta.
 // ------------------------------------------------------------------------------------------
-template <int W, bool DTHETA, bool SCALARS, bool ADD>
-__global__ __launch_bounds__(kQuantThreads)
+template <int W, bool DTHETA, bool SCALARS, bool ADD, int U>
+__global__ __launch_bounds__(one_trip_threads(U))
 void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict__ marg, const float *__restrict__ g_in,
                         int64_t n, QConst k, float dtheta_mul /* scale * (-2 alpha delta / n) */,
                         float *__restrict__ dtheta, ScalarFinish fin)
@@ -655,7 +868,8 @@ void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict
     // sums multiply them by the anchor index - with a level set around index 100 the 2^-24 of a single float
     // l_k (about -5) showed as 2e-4 of dH/dq
     __shared__ float ell[256 + 2 * kPad], ell_fine[256 + 2 * kPad];
-    for (int i = threadIdx.x; i < k.n_levels + 2 * kPad; i += kQuantThreads) {
+    constexpr int T = one_trip_threads(U);
+    for (int i = threadIdx.x; i < k.n_levels + 2 * kPad; i += T) {
         const int lv = i - kPad;
         double v = 0.0;
         if (lv >= 0 && lv < k.n_levels) { const float m = marg[lv]; v = m > 0.0f ? log2((double)m) : 0.0; }
@@ -669,31 +883,14 @@ void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict
 
     double acc_d = 0.0, acc_a = 0.0;
     const int64_t n4 = n >> 2;
-    const int64_t stride = (int64_t)gridDim.x * kQuantThreads;
-    for (int64_t v = (int64_t)blockIdx.x * kQuantThreads + threadIdx.x; v < n4 + 1; v += stride) {
-        float th[4], ge[4];
-        int cnt;
-        if (v < n4) {
-            const float4 t = load_stream4(theta + 4 * v, k.stream);
-            th[0] = t.x; th[1] = t.y; th[2] = t.z; th[3] = t.w;
-            if (ADD) { const float4 q = load_stream4(g_in + 4 * v, k.stream); ge[0] = q.x; ge[1] = q.y; ge[2] = q.z; ge[3] = q.w; }
-            cnt = 4;
-        } else {
-            cnt = (int)(n - (n4 << 2));
-            if (cnt == 0) break;
-            for (int e = 0; e < 4; ++e) {
-                th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
-                if (ADD) ge[e] = (e < cnt) ? g_in[(n4 << 2) + e] : 0.0f;
-            }
-        }
-        float dv[4];
+    auto four = [&](const float (&th)[4], const float (&ge)[4], int cnt, float (&dv)[4]) {
         float sum_d = 0.0f, sum_a = 0.0f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             float cf, u, Z, S1, S2, B0 = 0.0f, B1 = 0.0f, B2 = 0.0f;
             if (W > 0) {
                 Band<W> b;
-                band_weights<W, false, 2>(th[e], k, b);
+                band_weights<W, 2>(th[e], anchor_level<false>(th[e], k), k, b);
                 cf = b.cf; u = b.u; Z = b.Z; S1 = b.S1; S2 = b.S2;
                 const float *lp = ell0 + (int)cf, *fp = fine0 + (int)cf;
                 const float l0 = lp[0], f0 = fp[0];
@@ -724,18 +921,44 @@ void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict
             const float C1 = fmaf(-mu, b0, B1 * inv), C2 = fmaf(-m2, b0, B2 * inv);
             dv[e] = ADD ? fmaf(dtheta_mul, C1, ge[e]) : dtheta_mul * C1;
             if (SCALARS && e < cnt) {
-                const float r = clampf(u * k.inv_delta, -k.r_clamp, k.r_clamp);
+                const float r = u * k.inv_delta;
                 sum_d += fmaf(r - cf, C1, -C2);
                 sum_a += fmaf(-2.0f * r, C1, C2);
             }
         }
         if (SCALARS) { acc_d += (double)sum_d; acc_a += (double)sum_a; }
-        if (DTHETA) {
-            if (v < n4) store_stream4(dtheta + 4 * v, dv[0], dv[1], dv[2], dv[3], k.stream);
-            else for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
+    };
+    with_constant(k.stream != 0, [&](auto streams) {
+        auto group = [&](int64_t v, auto count) {
+            constexpr int N = decltype(count)::value;
+            float4 t[N], q[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
+                q[u] = ADD ? load_stream4(g_in + 4 * (v + u * T), streams.value) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const float th[4] = {t[u].x, t[u].y, t[u].z, t[u].w}, ge[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
+                float dv[4];
+                four(th, ge, 4, dv);
+                if (DTHETA) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+            }
+        };
+        one_trip_or_loop<T, U>(n4, group);
+    });
+    // ragged tail: the last 1..3 entries, one thread of the last block
+    const int cnt = (int)(n - (n4 << 2));
+    if (cnt > 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        float th[4], ge[4], dv[4];
+        for (int e = 0; e < 4; ++e) {
+            th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
+            ge[e] = (ADD && e < cnt) ? g_in[(n4 << 2) + e] : 0.0f;
         }
+        four(th, ge, cnt, dv);
+        if (DTHETA) for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
     }
-    if (SCALARS) scalar_finish<kQuantThreads>(acc_d, acc_a, fin);
+    if (SCALARS) scalar_finish<T>(acc_d, acc_a, fin);
 }
 
 __global__ void zero_floats_kernel(float *a, int na, float *b, int nb, float *c, int nc)
@@ -768,10 +991,13 @@ QConst make_const(const cdl_qparams &p)
     k.n_levels = p.n_levels;
     k.lo_f = (float)p.lo;
     k.hi_f = (float)(p.lo + p.n_levels - 1);
+    k.lo1_f = k.lo_f + 1.0f;
+    k.hi1_f = k.hi_f - 1.0f;
+    k.near = (float)(0.5 * delta * (1.0 - 1.0 / (1 << 20)));
     k.wgen = quantizer_window(kappa, p.n_levels);
     k.slide = 0;
     k.stream = 0;
-    k.r_clamp = INFINITY;
+    k.u_clamp = INFINITY;
     if (p.top_k > 0 && p.top_k < p.n_levels) {
         // Truncated CPMF.  Where the band that kappa asks for is no wider than the top_k nearest levels the
         // truncation drops nothing above fp32 resolution and the ordinary kernels serve; otherwise the generic
@@ -779,7 +1005,7 @@ QConst make_const(const cdl_qparams &p)
         const int wt = (p.top_k - 1) / 2;
         if (k.wgen > wt) { k.wgen = wt; k.slide = 1; }
     }
-    if (band_template(k) == 2) k.r_clamp = (float)(30.0 / (2.0 * kappa * 1.4426950408889634));
+    if (band_template(k) == 2) k.u_clamp = (float)(30.0 / (2.0 * alpha * delta * 1.4426950408889634));
     return k;
 }
 
@@ -794,6 +1020,11 @@ int grid_for(int64_t n)
     return (int)blocks;
 }
 
+// Blocks of the kernels that take a large tensor in one trip, and whether they serve: the unrolled bands (the loop over the
+// levels is bound by arithmetic).
+int64_t one_trip_grid(int64_t n) { return ((n >> 2) + (int64_t)kOneTripThreads * kOneTripVectors) / ((int64_t)kOneTripThreads * kOneTripVectors); }
+bool one_trip_serves(int64_t n, const QConst &k) { return n > kOneTripEntries && band_template(k) != 0 && one_trip_grid(n) <= 2147483647LL; }
+
 // Up to four times as many blocks as can finish the job themselves: that many, of more trips each.  A second launch costs more
 // (forward + backward of 0.3 M entries, 15 levels: 13.8 -> 12.3 us, 255 levels 17.3 -> 14.1; 0.9 M, 15 levels 17.0 -> 16.1) - not in
 // the soft regime, whose kernels are bound by arithmetic.
@@ -804,20 +1035,23 @@ int finishing_grid(int64_t blocks)
     return (int)((blocks + trips - 1) / trips);
 }
 
-// Grid of the histogram kernels: as above, but never more than kMaxHistTrips trips per block, and - once
-// the chip is full - a whole number of rounds: 256 CUs hold four 512-thread blocks each (2048 threads; the
-// histogram of 256 levels takes 33 KB of the 160 KB of LDS), and a last round that fills half of them
-// cost 10-18 % on 50 M entries.
+// Grid of the histogram kernels.  Up to kOneTripEntries a trip a block; then trips of kHistVectors vectors a thread, the next trip's
+// loads issued before this trip's stores, on half the blocks that are resident and from kHistFullFrom on all of them (256 CUs hold four 512-thread
+// blocks each): a block clears its cells first and adds them up last, 2 - 3 us in which its waves load and store nothing.  No more than
+// kMaxHistTrips vectors a thread: beyond, a whole number of rounds of blocks (a last round that fills half of them cost 10-18 % on 50 M entries).
+// us, forward pass with PMF (and the launch that finishes it) on 512 / 1024 / 2048 blocks: 2.4 M entries of 255 levels 14.4 / 15.3 / 18.1,
+// 6.4 M of 15 levels 21.0 / 23.2 / 25.4, 12.8 M of 16 levels 28.8 / 31.1 / 32.1, 25.6 M of 31 levels 60.2 / 57.4 / 58.4.
 constexpr int64_t kHistResident = 256 * 4;
+constexpr int64_t kHistFullFrom = 16ll << 20;
+constexpr int kHistVectors = 2;
 
 int64_t hist_grid_for(int64_t n)
 {
     const int64_t vecs = (n >> 2) + 1;
     const int64_t need = (vecs + (int64_t)kMargThreads * kMaxHistTrips - 1) / ((int64_t)kMargThreads * kMaxHistTrips);
-    int64_t g = (grid_for(n) + 1) / 2;
-    if (need > g) g = need;
-    if (g > kHistResident) g = (g + kHistResident - 1) / kHistResident * kHistResident;
-    return g;
+    if (n <= kOneTripEntries) return (grid_for(n) + 1) / 2;
+    const int64_t g = n < kHistFullFrom ? kHistResident / 2 : kHistResident;
+    return need > g ? (need + kHistResident - 1) / kHistResident * kHistResident : g;
 }
 
 // Whether the histogram kernel finishes the job itself: up to 256 blocks whose records one block can poll in a few
@@ -827,7 +1061,12 @@ bool hist_few(int64_t grid, int32_t n_levels) { return grid <= kFinishMaxBlocks 
 
 // workspace layout: [rows of the histogram kernel's blocks][records of the finishing blocks][scalar partials or records]
 // (or the table and the rows of moments of the soft regime)
-size_t hist_row_bytes(int64_t n, int32_t n_levels) { return align_up((size_t)hist_grid_for(n) * (size_t)n_levels * sizeof(unsigned long long), 256); }
+// (never less than a smaller tensor has: callers keep one workspace for several)
+size_t hist_row_bytes(int64_t n, int32_t n_levels)
+{
+    const int64_t g = hist_grid_for(n), rows = n > kOneTripEntries && g < kHistResident ? kHistResident : g;
+    return align_up((size_t)rows * (size_t)n_levels * sizeof(unsigned long long), 256);
+}
 size_t hist_bytes(int64_t n, int32_t n_levels)
 {
     const size_t rows = hist_row_bytes(n, n_levels);
@@ -852,25 +1091,42 @@ int launch_scalar_end(const ScalarFinish &f, int grid, hipStream_t stream)
     return rc != CDL_OK || !f.partial ? rc : launch_scalar_finalize(f.partial, grid, f.mul_d, f.mul_a, f.d_delta, f.d_alpha, stream);
 }
 
+// Whether the sum of a cell's outermost probabilities stays below 2^20: of two neighbours at a midpoint each has half, so that the level W away
+// has at most e^(-kappa W (W - 1)) / 2, and a cell takes at most 2^10 + 3 entries.  Holds wherever W comes from kappa and not from the size of the set.
+bool outer_pair_is_small(double kappa, int w) { return exp(-kappa * w * (w - 1)) < 1.0 / 1100.0; }
+bool pairs_serve(double kappa, int levels, int w) { return w > 0 && hist_bytes_of(levels, w, true) <= kPairBytes && (w == 1 || outer_pair_is_small(kappa, w)); }
+
 template <int W>
 void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
-                  const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
+                  const float *theta, int64_t n, const QConst &k, double kappa, int8_t *idx, float *soft,
                   const MargFinish &fin)
 {
-    const size_t lds = (size_t)(k.n_levels + 2 * kPad) * sizeof(float) * 32;
-#define CDL_FWD(I, S, M)                                                                                  \
+#define CDL_FWD_P(I, S, M, U, P)                                                                          \
     CDL_LAUNCH((I) ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)", s,                     \
-               (quantize_fwd_kernel<W, I, S, (M) != 0, (M) == 2>), dim3(grid), dim3((M) ? kMargThreads : kQuantThreads), (M) ? lds : 0, \
-               theta, n, k, idx, soft, fin)
-    const bool few = hist_few(grid, k.n_levels);
-    if (want_idx && want_soft && want_marg && few) CDL_FWD(true, true, 2);
-    else if (want_idx && want_soft && want_marg) CDL_FWD(true, true, 1);
-    else if (want_idx && want_soft) CDL_FWD(true, true, 0);
-    else if (want_idx && want_marg && few) CDL_FWD(true, false, 2);
-    else if (want_idx && want_marg) CDL_FWD(true, false, 1);
-    else if (want_idx) CDL_FWD(true, false, 0);
-    else if (few) CDL_FWD(false, false, 2);
-    else CDL_FWD(false, false, 1);
+               (quantize_fwd_kernel<W, I, S, (M) != 0, (M) == 2, U, (P)>), dim3(grid), dim3((M) ? kMargThreads : one_trip_threads(U)), \
+               (M) ? hist_bytes_of(k.n_levels, W, P) : 0, theta, n, k, idx, soft, fin)
+#define CDL_FWD(I, S, M, U)                                                                               \
+    do {                                                                                                  \
+        if ((M) != 0 && pairs) CDL_FWD_P(I, S, M, U, W > 0 && (M) != 0);                                  \
+        else CDL_FWD_P(I, S, M, U, false);                                                                \
+    } while (0)
+    const bool few = hist_few(grid, k.n_levels), pairs = pairs_serve(kappa, k.n_levels, W);
+    constexpr int UM = W > 0 ? kHistVectors : 1, UN = W > 0 ? kOneTripVectors : 1;
+    const bool large = n > kOneTripEntries;      // (without PMF: one_trip_serves)
+    if (want_idx && want_soft && want_marg && few) CDL_FWD(true, true, 2, 1);
+    else if (want_idx && want_soft && want_marg && large) CDL_FWD(true, true, 1, UM);
+    else if (want_idx && want_soft && want_marg) CDL_FWD(true, true, 1, 1);
+    else if (want_idx && want_soft && large) CDL_FWD(true, true, 0, UN);
+    else if (want_idx && want_soft) CDL_FWD(true, true, 0, 1);
+    else if (want_idx && want_marg && few) CDL_FWD(true, false, 2, 1);
+    else if (want_idx && want_marg && large) CDL_FWD(true, false, 1, UM);
+    else if (want_idx && want_marg) CDL_FWD(true, false, 1, 1);
+    else if (want_idx && large) CDL_FWD(true, false, 0, UN);
+    else if (want_idx) CDL_FWD(true, false, 0, 1);
+    else if (few) CDL_FWD(false, false, 2, 1);
+    else if (large) CDL_FWD(false, false, 1, UM);
+    else CDL_FWD(false, false, 1, 1);
+#undef CDL_FWD_P
 #undef CDL_FWD
 }
 
@@ -971,12 +1227,17 @@ void launch_bwd_uniform(bool want_dtheta, bool want_scalars, int grid, hipStream
 }
 
 template <int W>
-void launch_bwd_w(bool want_dtheta, bool want_scalars, int grid, hipStream_t s, const float *theta,
+void launch_bwd_w(bool want_dtheta, bool want_scalars, bool one_trip, int grid, hipStream_t s, const float *theta,
                   const float *g, int64_t n, const QConst &k, float *dtheta, const ScalarFinish &fin)
 {
+    constexpr int U = W > 0 ? kOneTripVectors : 1;
 #define CDL_BWD(D, S) \
-    CDL_LAUNCH("quantize_bwd_kernel", s, (quantize_bwd_kernel<W, D, S>), dim3(grid), dim3(kQuantThreads), 0, \
-               theta, g, n, k, dtheta, fin)
+    do { \
+        if (one_trip) CDL_LAUNCH("quantize_bwd_kernel", s, (quantize_bwd_kernel<W, D, S, U>), dim3(grid), dim3(one_trip_threads(U)), 0, \
+                                 theta, g, n, k, dtheta, fin); \
+        else CDL_LAUNCH("quantize_bwd_kernel", s, (quantize_bwd_kernel<W, D, S, 1>), dim3(grid), dim3(kQuantThreads), 0, \
+                        theta, g, n, k, dtheta, fin); \
+    } while (0)
     if (want_dtheta && want_scalars) CDL_BWD(true, true);
     else if (want_dtheta) CDL_BWD(true, false);
     else CDL_BWD(false, true);
@@ -1004,9 +1265,17 @@ int quantizer_window(double kappa, int n_levels)
 
 void *quantize_scalar_area(void *ws, int64_t n, int32_t n_levels) { return reinterpret_cast<char *>(ws) + hist_bytes(n, n_levels) + kRecordBytes; }
 
+size_t quantize_sum_bytes(int64_t n)
+{
+    const int64_t blocks = one_trip_grid(n) > kMaxQuantBlocks ? one_trip_grid(n) : kMaxQuantBlocks;
+    return align_up((size_t)blocks * 2 * sizeof(double), 256);
+}
+
+size_t quantize_scalar_bytes(int64_t n) { return quantize_sum_bytes(n) + kSoftTableBytes; }
+
 size_t quantize_workspace_bytes(int64_t n, int32_t n_levels)
 {
-    return hist_bytes(n, n_levels) + kRecordBytes + kQuantScalarBytes;
+    return hist_bytes(n, n_levels) + kRecordBytes + quantize_scalar_bytes(n);
 }
 
 // ---- built-in scratch for callers that cannot allocate ---------------------------------------
@@ -1063,7 +1332,8 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
     int64_t grid64 = want_marg ? hist_grid_for(n) : grid_for(n);
     if (want_marg && band_template(k) != 0 && n <= 4ll * kFinishMaxBlocks * kMargThreads * 4 && hist_few(finishing_grid(grid64), p.n_levels)) grid64 = finishing_grid(grid64);
     if (grid64 > 2147483647LL) return CDL_ERR_PARAM;
-    int grid = (int)grid64;
+    const bool one_trip = !want_marg && one_trip_serves(n, k);
+    int grid = one_trip ? (int)one_trip_grid(n) : (int)grid64;
     MargFinish fin{};
     if (want_marg) {
         if (!hist_few(grid, p.n_levels)) fin.rows = reinterpret_cast<unsigned long long *>(ws);
@@ -1073,6 +1343,7 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
         fin.marg = marg;
         fin.entropy_bits = entropy_bits;
     }
+    const double kappa = (double)p.alpha * (double)p.delta * (double)p.delta;
     const bool uniform = uniform_half_width(p, k) != 0;
     const SoftPlan plan = want_marg && (soft_fwd_from_uniform(p, n) || !uniform) ? soft_plan(p, k, n, uniform) : SoftPlan{};
     if (plan.bins) return launch_soft_fwd(theta, n, p, k, plan, idx, soft, fin, ws, stream);
@@ -1088,11 +1359,11 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
         if (rcu != CDL_OK) return rcu;
     } else
     switch (band_template(k)) {
-        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        default: launch_fwd<0>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
+        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
+        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
+        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
+        default: launch_fwd<0>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
     }
     int rc = check_launch();
     if (rc == CDL_OK && fin.rows) {
@@ -1119,13 +1390,14 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
     }
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    const int grid = want_scalars && band_template(k) != 0 ? finishing_grid(grid_for(n)) : grid_for(n);
+    const bool one_trip = one_trip_serves(n, k);
+    const int grid = one_trip ? (int)one_trip_grid(n) : want_scalars && band_template(k) != 0 ? finishing_grid(grid_for(n)) : grid_for(n);
     const double d = (double)p.delta;
     ScalarFinish fin{};
     if (want_scalars) fin = scalar_finish_args(scalars, grid, 1.0, d * d * d, d_delta, d_alpha);
     const SoftPlan plan = want_scalars && uniform_half_width(p, k) && soft_bwd_from_uniform(p, n) ? soft_plan(p, k, n, true) : SoftPlan{};
     if (plan.bins) {
-        const int rc = launch_soft_bwd(theta, g, n, p, k, plan, dtheta, fin, reinterpret_cast<char *>(scalars) + kQuantSumBytes, grid, stream);
+        const int rc = launch_soft_bwd(theta, g, n, p, k, plan, dtheta, fin, reinterpret_cast<char *>(scalars) + quantize_sum_bytes(n), grid, stream);
         return rc != CDL_OK ? rc : launch_scalar_end(fin, grid, stream);
     }
     const bool want_dtheta = dtheta != nullptr;
@@ -1137,11 +1409,11 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
         else launch_bwd_uniform<16>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, u, dtheta, fin);
     } else
     switch (band_template(k)) {
-        case 1: launch_bwd_w<1>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
-        case 2: launch_bwd_w<2>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
-        case 3: launch_bwd_w<3>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
-        case 4: launch_bwd_w<4>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
-        default: launch_bwd_w<0>(want_dtheta, want_scalars, grid, stream, theta, g, n, k, dtheta, fin); break;
+        case 1: launch_bwd_w<1>(want_dtheta, want_scalars, one_trip, grid, stream, theta, g, n, k, dtheta, fin); break;
+        case 2: launch_bwd_w<2>(want_dtheta, want_scalars, one_trip, grid, stream, theta, g, n, k, dtheta, fin); break;
+        case 3: launch_bwd_w<3>(want_dtheta, want_scalars, one_trip, grid, stream, theta, g, n, k, dtheta, fin); break;
+        case 4: launch_bwd_w<4>(want_dtheta, want_scalars, one_trip, grid, stream, theta, g, n, k, dtheta, fin); break;
+        default: launch_bwd_w<0>(want_dtheta, want_scalars, one_trip, grid, stream, theta, g, n, k, dtheta, fin); break;
     }
     return launch_scalar_end(fin, grid, stream);
 }
@@ -1157,8 +1429,14 @@ int launch_quantize_draw(const float *theta, const float *u, int64_t n, const cd
     if (n == 0) return CDL_OK;
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    const int grid = grid_for(n);
-#define CDL_DRAW(WW) CDL_LAUNCH("quantize_draw_kernel", stream, (quantize_draw_kernel<WW>), dim3(grid), dim3(kQuantThreads), 0, theta, u, n, k, idx)
+    const bool one_trip = one_trip_serves(n, k);
+    const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
+#define CDL_DRAW(WW) \
+    do { \
+        constexpr int U = WW > 0 ? kOneTripVectors : 1; \
+        if (one_trip) CDL_LAUNCH("quantize_draw_kernel", stream, (quantize_draw_kernel<WW, U>), dim3(grid), dim3(one_trip_threads(U)), 0, theta, u, n, k, idx); \
+        else CDL_LAUNCH("quantize_draw_kernel", stream, (quantize_draw_kernel<WW, 1>), dim3(grid), dim3(kQuantThreads), 0, theta, u, n, k, idx); \
+    } while (0)
     switch (band_template(k)) {
         case 1: CDL_DRAW(1); break;
         case 2: CDL_DRAW(2); break;
@@ -1172,13 +1450,18 @@ int launch_quantize_draw(const float *theta, const float *u, int64_t n, const cd
 
 namespace {
 template <int W>
-void launch_entropy_bwd_w(bool want_dtheta, bool want_scalars, bool add, int grid, hipStream_t s, const float *theta,
+void launch_entropy_bwd_w(bool want_dtheta, bool want_scalars, bool add, bool one_trip, int grid, hipStream_t s, const float *theta,
                           const float *marg, const float *g_in, int64_t n, const QConst &k, float mul,
                           float *dtheta, const ScalarFinish &fin)
 {
+    constexpr int U = W > 0 ? kOneTripVectors : 1;
 #define CDL_EB(D, S, A) \
-    CDL_LAUNCH("entropy_bwd_kernel", s, (entropy_bwd_kernel<W, D, S, A>), dim3(grid), dim3(kQuantThreads), 0, \
-               theta, marg, g_in, n, k, mul, dtheta, fin)
+    do { \
+        if (one_trip) CDL_LAUNCH("entropy_bwd_kernel", s, (entropy_bwd_kernel<W, D, S, A, U>), dim3(grid), dim3(one_trip_threads(U)), 0, \
+                                 theta, marg, g_in, n, k, mul, dtheta, fin); \
+        else CDL_LAUNCH("entropy_bwd_kernel", s, (entropy_bwd_kernel<W, D, S, A, 1>), dim3(grid), dim3(kQuantThreads), 0, \
+                        theta, marg, g_in, n, k, mul, dtheta, fin); \
+    } while (0)
     if (want_dtheta && want_scalars && add) CDL_EB(true, true, true);
     else if (want_dtheta && want_scalars) CDL_EB(true, true, false);
     else if (want_dtheta && add) CDL_EB(true, false, true);
@@ -1202,18 +1485,19 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     }
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    const int grid = grid_for(n);
+    const bool one_trip = one_trip_serves(n, k);
+    const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
     const bool want_dtheta = dtheta != nullptr;
     const double alpha = (double)p.alpha, delta = (double)p.delta;
     const double mul_theta = (double)scale * (-2.0 * alpha * delta / (double)n);
     ScalarFinish fin{};
     if (want_scalars) fin = scalar_finish_args(quantize_scalar_area(ws, n, p.n_levels), grid, mul_theta, (double)scale * delta * delta / (double)n, d_delta, d_alpha);
     switch (band_template(k)) {
-        case 1: launch_entropy_bwd_w<1>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
-        case 2: launch_entropy_bwd_w<2>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
-        case 3: launch_entropy_bwd_w<3>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
-        case 4: launch_entropy_bwd_w<4>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
-        default: launch_entropy_bwd_w<0>(want_dtheta, want_scalars, g_in != nullptr, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        case 1: launch_entropy_bwd_w<1>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        case 2: launch_entropy_bwd_w<2>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        case 3: launch_entropy_bwd_w<3>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        case 4: launch_entropy_bwd_w<4>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
+        default: launch_entropy_bwd_w<0>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
     }
     return launch_scalar_end(fin, grid, stream);
 }

@@ -19,27 +19,31 @@ struct QConst {
     float b2;         // 2 alpha delta log2(e): t = exp2(b2 u)
     float k1, k4;     // exp(-kappa), exp(-4 kappa)
     float two_kappa;  // 2 alpha delta^2
-    float lo_f;
-    float hi_f;
+    float lo_f, lo1_f;   // the lowest level and the one above it
+    float hi_f, hi1_f;   // the highest level and the one below it
+    float near;       // |theta - r delta| below this: r is the nearest level without looking further (see anchor_levels)
     int lo;
     int n_levels;
     int idx_off;      // what is subtracted from a level index before it is stored as an int8 (0, or 128 for sets that reach beyond 127)
     int wgen;         // band half-width of the generic kernel
     int stream;       // 1: the tensor is large, read and write it with non-temporal accesses
     int slide;        // 1: truncated CPMF - the band of 2 wgen + 1 levels slides at the ends of the level set instead of being cut
-    float r_clamp;    // |u / delta| beyond which the W = 2 kernels hold the offset fixed (see band_weights), else infinity
+    float u_clamp;    // |u| beyond which the W = 2 kernels hold the offset fixed (see band_weights), else infinity
 };
 
-// Four level indices as the four int8 of one word, each stored as index - off
+// Four level indices as the four int8 of one word, each stored as index - off (off: 0 or 128, which flips the top bit of a byte)
 __device__ __forceinline__ uint32_t pack_indices(int c0, int c1, int c2, int c3, int off)
 {
-    return (uint32_t)((c0 - off) & 0xff) | ((uint32_t)((c1 - off) & 0xff) << 8) |
-           ((uint32_t)((c2 - off) & 0xff) << 16) | ((uint32_t)((c3 - off) & 0xff) << 24);
+    const uint32_t low = __builtin_amdgcn_perm((uint32_t)c1, (uint32_t)c0, 0x0c0c0400u);      // (bytes 0 of c0, c1; 0x0c: zero)
+    const uint32_t high = __builtin_amdgcn_perm((uint32_t)c3, (uint32_t)c2, 0x04000c0cu);
+    return (low | high) ^ ((uint32_t)off * 0x01010101u);
 }
 
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float clampf(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+
+__device__ __forceinline__ float unit(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
 
 // Level next to th.  EXACT: the nearest level, lower index on an exact tie, clamped to [lo, hi]:
 // rint(th/delta) can be off by one next to a midpoint; the two fused multiply-adds evaluate
@@ -61,6 +65,31 @@ __device__ __forceinline__ float anchor_level(float th, const QConst &k)
     return clampf(r, k.lo_f, k.hi_f);
 }
 
+// The same for four entries of one tensor.  u = th - r delta with r = rint(th / delta) is exact next to a midpoint (both terms are multiples
+// of the smaller of their last places and |u| <= 2^23 of it), so r is the nearest level wherever |u| is below delta / 2 by more than
+// one rounding; the two signs above are only formed where one of the four is closer (one entry in 10^6): 4 instructions an entry instead of 14.
+template <bool EXACT>
+__device__ __forceinline__ void anchor_levels(const float (&th)[4], const QConst &k, float (&cf)[4])
+{
+    if (EXACT) {
+        float u[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            cf[e] = rintf(th[e] * k.inv_delta);
+            u[e] = fmaf(-cf[e], k.delta, th[e]);
+        }
+        if (fmaxf(fmaxf(fabsf(u[0]), fabsf(u[1])), fmaxf(fabsf(u[2]), fabsf(u[3]))) >= k.near) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) cf[e] = anchor_level<true>(th[e], k);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cf[e] = clampf(cf[e], k.lo_f, k.hi_f);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cf[e] = anchor_level<false>(th[e], k);
+    }
+}
+
 // Weights of the band (up to one common factor) and their power sums in the offset j.
 template <int W>
 struct Band {
@@ -72,25 +101,24 @@ struct Band {
     float Z, S1, S2, S3;
 };
 
-// NMOM: how many of S1, S2, S3 are needed.
-template <int W, bool EXACT, int NMOM>
-__device__ __forceinline__ void band_weights(float th, const QConst &k, Band<W> &b)
+// cf: the anchor level of th.  NMOM: how many of S1, S2, S3 are needed.
+template <int W, int NMOM>
+__device__ __forceinline__ void band_weights(float th, float cf, const QConst &k, Band<W> &b)
 {
-    const float cf = anchor_level<EXACT>(th, k);
     b.cf = cf;
     if (W == 2) {
         // t = exp(2 alpha delta u), clamped where the far side has long vanished so that t^4 stays finite.
         // Beyond the clamp (theta more than 30 / (2 kappa log2 e) steps outside the level set) the near
         // neighbour keeps a weight of 2^-30 e^-kappa where the true one goes on falling: harmless by itself,
-        // but not once it is multiplied by an offset that goes on growing - the scalar gradients therefore
-        // hold u / delta at k.r_clamp there, which bounds that product by 3e-11.
-        const float u = fmaf(-cf, k.delta, th);
+        // but not once it is multiplied by an offset that goes on growing - u is therefore held
+        // there for the scalar gradients too, which bounds that product by 3e-11.
+        const float u = clampf(fmaf(-cf, k.delta, th), -k.u_clamp, k.u_clamp);
         b.u = u;
-        const float t = fast_exp2(clampf(k.b2 * u, -30.0f, 30.0f));
+        const float t = fast_exp2(k.b2 * u);
         const float t2 = t * t, t3 = t2 * t, t4 = t2 * t2;
-        const float above = k.hi_f - cf, below = cf - k.lo_f;   // levels that exist on each side
-        const float k1u = (above >= 1.0f) ? k.k1 : 0.0f, k4u = (above >= 2.0f) ? k.k4 : 0.0f;
-        const float k1d = (below >= 1.0f) ? k.k1 : 0.0f, k4d = (below >= 2.0f) ? k.k4 : 0.0f;
+        // (levels that exist on each side: a difference of whole numbers held in [0, 1] costs a modifier, a comparison and a select four times as much)
+        const float k1u = k.k1 * unit(k.hi_f - cf), k4u = k.k4 * unit(k.hi1_f - cf);
+        const float k1d = k.k1 * unit(cf - k.lo_f), k4d = k.k4 * unit(cf - k.lo1_f);
         const float A = k4u * t4, B = k1u * t3, C = k1d * t, D = k4d;   // levels +2, +1, -1, -2 (times t^2)
         const float p = A + D, q = B + C, x = A - D, y = B - C;
         b.ctr = t2;
@@ -196,13 +224,14 @@ __device__ __forceinline__ void generic_sums(float th, const QConst &k, GenericS
 // variance and third central moment of the level offset j under the CPMF and r = u / delta,
 //     dQd/dtheta = 2 kappa var,   dQd/ddelta = (c + mu) + 2 kappa ((r - c - 2 mu) var - c3),   dQd/dalpha / delta^3 = 2 (r - mu) var - c3.
 // W: band half-width of the unrolled kernels, 0 = the generic loop.  SCALARS: also the last two.
+// With q = c + mu and e = (r - mu) var the last two are q - 2 kappa q var + 2 kappa (e - c3) and 2 e - c3, and c3 = m3 - mu (3 var + mu^2).
 template <int W, bool SCALARS>
 __device__ __forceinline__ void quantizer_bwd_terms(float th, const QConst &k, float &d_theta, float &t_d, float &t_a)
 {
     float cf, u, Z, S1, S2, S3;
     if (W > 0) {
         Band<W> b;
-        band_weights<W, false, SCALARS ? 3 : 2>(th, k, b);
+        band_weights<W, SCALARS ? 3 : 2>(th, anchor_level<false>(th, k), k, b);
         cf = b.cf; u = b.u; Z = b.Z; S1 = b.S1; S2 = b.S2; S3 = b.S3;
     } else {
         GenericSums s;
@@ -217,10 +246,10 @@ __device__ __forceinline__ void quantizer_bwd_terms(float th, const QConst &k, f
     t_a = 0.0f;
     if (SCALARS) {
         const float m3 = S3 * inv;
-        const float c3 = fmaf(-mu, fmaf(-2.0f * mu, mu, 3.0f * m2), m3);   // m3 - 3 mu m2 + 2 mu^3
-        const float r = clampf(u * k.inv_delta, -k.r_clamp, k.r_clamp);
-        t_d = (cf + mu) + k.two_kappa * fmaf(r - cf - 2.0f * mu, var, -c3);
-        t_a = fmaf(2.0f * (r - mu), var, -c3);
+        const float c3 = fmaf(-mu, fmaf(3.0f, var, mu * mu), m3);
+        const float q = cf + mu, e = fmaf(u, k.inv_delta, -mu) * var;      // (u is held where the bands of W = 2 hold it)
+        t_d = fmaf(k.two_kappa, e - c3, fmaf(-q, d_theta, q));
+        t_a = fmaf(2.0f, e, -c3);
     }
 }
 

@@ -1,0 +1,79 @@
+"""Quantizer kernels on tensors that are taken in one trip of all blocks, and the marginal PMF from cells of pairs of levels: remainders
+of a block, the largest sets that keep pairs and the first that do not for every band width, cells filled by equal entries."""
+import numpy as np
+import pytest
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+LINE = 2_097_152      # more entries: one trip, blocks of 2048 entries
+
+
+@pytest.mark.parametrize("n", [LINE, LINE + 1, LINE + 2047, LINE + 2048 + 1027])
+def test_one_trip_remainders(oracle, n):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    lo, levels, delta, alpha = -7, 15, 0.0625, 4.0 / 0.0625 ** 2
+    rng = np.random.default_rng(n)
+    theta = (rng.standard_normal(n) * 0.2).astype(np.float32)
+    g, u = rng.standard_normal(n).astype(np.float32), rng.random(n).astype(np.float32)
+    th_d, g_d = gu.dev(theta), gu.dev(g)
+    ws = gu.workspace(cdl.quantize_workspace_bytes(n, levels))
+    ws.fill_(255)
+    # (one entry more than asked for in every output: it stays as it is)
+    idx, soft = torch.full((n + 1,), 99, dtype=torch.int8, device="cuda"), torch.full((n + 1,), 7.0, device="cuda")
+    dth, dent, drawn = torch.full((n + 1,), 7.0, device="cuda"), torch.full((n + 1,), 7.0, device="cuda"), torch.full((n + 1,), 99, dtype=torch.int8, device="cuda")
+    dd, da, marg = gu.empty((1,), torch.float32), gu.empty((1,), torch.float32), gu.empty((levels,), torch.float32)
+    cdl.cdl_quantize_fwd(th_d, n, lo, levels, delta, alpha, idx, soft)
+    cdl.cdl_quantize_bwd(th_d, g_d, n, lo, levels, delta, alpha, dth, dd, da, ws)
+    cdl.cdl_quantize_draw(th_d, gu.dev(u), n, lo, levels, delta, alpha, drawn)
+    cdl.cdl_marginal_entropy(th_d, n, lo, levels, delta, alpha, marg, gu.empty((1,), torch.float32), ws)
+    cdl.cdl_entropy_bwd(th_d, marg, n, lo, levels, delta, alpha, 0.01 * n, g_d, dent, None, None, ws)
+    torch.cuda.synchronize()
+    assert int(idx[n]) == 99 and float(soft[n]) == 7.0 and float(dth[n]) == 7.0 and float(dent[n]) == 7.0 and int(drawn[n]) == 99
+    r_idx, r_soft, r_gap = oracle.quantize_fwd(theta, lo, levels, delta, alpha)[:3]
+    gu.assert_indices(idx[:n].cpu().numpy(), r_idx, r_gap, "indices")
+    gu.assert_close(soft[:n].cpu().numpy(), r_soft, "soft")
+    r = oracle.quantize_bwd(theta, g, lo, levels, delta, alpha)
+    gu.assert_close(dth[:n].cpu().numpy(), r["dtheta"], "dtheta")
+    gu.check_quantizer_scalars(oracle, "one trip %d" % n, theta, g, (lo, levels, delta, alpha), dd.item(), da.item(), r)
+    r_draw, margin = oracle.quantize_draw(theta, u, lo, levels, delta, alpha)
+    assert np.all(np.asarray(margin)[drawn[:n].cpu().numpy() != r_draw] < 1e-6)
+    tail = slice(n - 5000, n)
+    r_e = oracle.entropy_bwd(theta, marg.cpu().numpy().astype(np.float64), lo, levels, delta, alpha, scale=0.01 * n)
+    gu.assert_close(dent[:n].cpu().numpy()[tail], (r_e["dtheta"] + g)[tail], "entropy gradient")
+
+
+# (kappa of band widths 1 .. 4; the last set that keeps pairs and the first that does not; sets of which every level is live)
+@pytest.mark.parametrize("n", [3001, 90_001, LINE + 5])
+@pytest.mark.parametrize("levels,kappa", [(2, 16.0), (97, 16.0), (98, 16.0), (72, 4.0), (73, 4.0), (48, 2.5), (49, 2.5), (36, 1.5), (37, 1.5), (72, 3.82), (3, 0.05), (5, 0.05), (5, 3.9)])
+def test_marginal_of_pairs(oracle, n, levels, kappa):
+    lo, delta = -(levels // 2), 0.05
+    alpha = kappa / delta ** 2
+    rng = np.random.default_rng(levels)
+    theta = (rng.uniform(-0.6, 0.6, n) * levels * delta).astype(np.float32)      # (beyond both ends too)
+    q = gu.Quantizer(type("S", (), dict(lo=lo, n_levels=levels, delta=delta, alpha=alpha))())
+    got = q.fwd(gu.dev(theta))
+    r_idx, r_soft, r_gap = oracle.quantize_fwd(theta, lo, levels, delta, alpha)[:3]
+    r_m, r_h = oracle.marginal_entropy(theta, lo, levels, delta, alpha)
+    gu.assert_indices(got[0], r_idx, r_gap, "indices")
+    gu.assert_close(got[1], r_soft, "soft")
+    gu.assert_close(got[2], r_m, "marginal PMF")
+    gu.assert_close([got[3]], [r_h], "entropy")
+
+
+# one cell of one copy takes everything its threads see: at a level, halfway between two (both halves), next to the ends and far outside
+@pytest.mark.parametrize("n", [4099, 16_777_215])
+@pytest.mark.parametrize("at", [0.0, 0.5, -0.5, 6.5, 7.0, -7.4, 40.0])
+@pytest.mark.parametrize("kappa", [3.82, 16.0, 2.5])
+def test_marginal_of_equal_entries(oracle, n, at, kappa):
+    torch = gu.torch_mod()
+    lo, levels, delta = -7, 15, 0.0625
+    alpha = kappa / delta ** 2
+    q = gu.Quantizer(type("S", (), dict(lo=lo, n_levels=levels, delta=delta, alpha=alpha))())
+    marg, H = q.marginal(torch.full((n,), at * delta, device="cuda"))
+    r_m, r_h = oracle.marginal_entropy(np.full(4, at * delta, np.float32), lo, levels, delta, alpha)
+    # (all entries round alike: half a unit of 2^-21 each, which the tolerance of 1e-6 holds)
+    gu.assert_close(marg, r_m, "marginal PMF")
+    assert abs(H - r_h) <= 2e-5      # (-m log2 m of a probability rounded by 2^-22: 2^-22 (22 + 1.5), three levels)

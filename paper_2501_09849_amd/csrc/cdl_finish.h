@@ -1,10 +1,12 @@
 // Adding up per-block results inside the kernel that made them (not installed).
 //
-// A kernel whose blocks each leave a partial result is followed by a second, tiny launch that adds the partials up.  For
-// a small tensor that launch costs as much as the pass itself (a tensor of 32 K entries: 4.4 us, and 7.8 us for the
-// launch that adds up its sixteen histograms, and 3 - 4 us of host time), so where a grid has few blocks the block with
-// the highest number waits for the others and finishes the job itself (6.3 us in all).  Large grids keep the second
-// launch: there the waiting block reads a lot, from memory that is busy with the stores of the tensor.
+// A second, tiny launch that adds the blocks' partial results up costs as much as the pass itself for a small tensor (32 K entries: 4.4 us, and
+// 7.8 us for the launch that adds up its sixteen histograms, and 3 - 4 us of host time), so where a grid has few blocks the block with
+// the highest number waits for the others and finishes the job itself (6.3 us in all).  The sums of the two scalar gradients of grids of more
+// blocks go in two steps: the last block of every group of consecutive blocks adds up its group's, the last of the grid those of the
+// groups (backward pass of 2.4 M entries 11.9 -> 10.2 us, of 6.4 M 20.6 -> 19.4; histograms so: 2.4 M entries of 255 levels 14 -> 22).  Tensors
+// that stream past the caches keep the second launch: there the records wait behind the stores of the tensor (25.6 M entries 56.0 us with
+// a second launch, 56.6 in two steps, 18.9 M 41.2 / 43.8).
 //
 // What bounds the hand-over is the number of trips to memory, one after the other, between blocks on different XCDs,
 // about 0.7 us each.  A flag behind the data would cost four (data out and acknowledged, flag out, flag in, data in).
@@ -40,14 +42,17 @@ constexpr int kFinishMaxBlocks = 256;
 // What becomes of the per-block sums of the two scalar gradients.
 struct ScalarFinish {
     double *partial;               // [gridDim.x][2]: left there for scalar_finalize_kernel; null: finished in the kernel
-    unsigned long long *records;   // [gridDim.x][4]
+    unsigned long long *records;   // [gridDim.x][4], then [groups][4]
     unsigned long long tag;
     double mul_d, mul_a;
     float *d_delta, *d_alpha;      // [1] or null
 };
 
-// d_delta = mul_d * sum over blocks of acc_d, d_alpha = mul_a * the same of acc_a; the sums run over threads and
-// blocks in a fixed order.  Called by all T threads of every block.
+// Records of a grid: one per block, one per group of kFinishMaxBlocks of them.
+__host__ __device__ __forceinline__ int64_t scalar_records(int64_t blocks) { return blocks + (blocks + kFinishMaxBlocks - 1) / kFinishMaxBlocks; }
+
+// d_delta = mul_d * sum over blocks of acc_d, d_alpha = mul_a * the same of acc_a; the sums run over threads, blocks and
+// groups in a fixed order.  Called by all T threads of every block.
 template <int T>
 __device__ __forceinline__ void scalar_finish(double acc_d, double acc_a, const ScalarFinish &f)
 {
@@ -74,41 +79,49 @@ __device__ __forceinline__ void scalar_finish(double acc_d, double acc_a, const 
         }
         return;
     }
-    const int last = (int)gridDim.x - 1;
     // (the products keep the check word from fitting a record of which only one word has changed)
     auto check = [&](unsigned long long x, unsigned long long y) {
         return (x * 0x9E3779B97F4A7C15ull + y * 0xBF58476D1CE4E5B9ull) ^ f.tag;
     };
-    if ((int)blockIdx.x != last) {
-        if (threadIdx.x == 0) {
-            unsigned long long *r = f.records + 4 * (size_t)blockIdx.x;
-            const unsigned long long x = (unsigned long long)__double_as_longlong(acc_d), y = (unsigned long long)__double_as_longlong(acc_a);
-            device_store(r, x);
-            device_store(r + 1, y);
-            device_store(r + 2, check(x, y));
-        }
-        return;
-    }
-    if (last > 0) {
-        static_assert(kFinishMaxBlocks <= T, "one record per thread");
+    auto publish = [&](unsigned long long *r) {
+        if (threadIdx.x != 0) return;
+        const unsigned long long x = (unsigned long long)__double_as_longlong(acc_d), y = (unsigned long long)__double_as_longlong(acc_a);
+        device_store(r, x);
+        device_store(r + 1, y);
+        device_store(r + 2, check(x, y));
+    };
+    // adds `count` records to thread 0's sums
+    auto collect = [&](unsigned long long *records, int count) {
         double d = 0.0, a = 0.0;
-        if ((int)threadIdx.x < last) {
-            unsigned long long *r = f.records + 4 * (size_t)threadIdx.x;
+        for (int i = threadIdx.x; i < count; i += T) {
+            unsigned long long *r = records + 4 * (size_t)i;
             unsigned long long x, y, z;
             do {
                 x = device_load(r);
                 y = device_load(r + 1);
                 z = device_load(r + 2);
             } while (z != check(x, y));
-            d = __longlong_as_double((long long)x);
-            a = __longlong_as_double((long long)y);
+            d += __longlong_as_double((long long)x);
+            a += __longlong_as_double((long long)y);
             device_store(r + 2, 0ull);
         }
-        const double own_d = acc_d, own_a = acc_a;
         block_sum(d, a);
-        acc_d = d + own_d;
-        acc_a = a + own_a;
+        acc_d += d;
+        acc_a += a;
+    };
+    const int last = (int)gridDim.x - 1, first = (int)blockIdx.x / kFinishMaxBlocks * kFinishMaxBlocks;
+    const int leader = min(first + kFinishMaxBlocks - 1, last);
+    if ((int)blockIdx.x != leader) {
+        publish(f.records + 4 * (size_t)blockIdx.x);
+        return;
     }
+    if (leader > first) collect(f.records + 4 * (size_t)first, leader - first);
+    unsigned long long *const groups = f.records + 4 * (size_t)gridDim.x;
+    if (leader != last) {
+        publish(groups + 4 * (size_t)(first / kFinishMaxBlocks));
+        return;
+    }
+    if (first > 0) collect(groups, first / kFinishMaxBlocks);
     if (threadIdx.x == 0) {
         if (f.d_delta) *f.d_delta = (float)(acc_d * f.mul_d);
         if (f.d_alpha) *f.d_alpha = (float)(acc_a * f.mul_a);

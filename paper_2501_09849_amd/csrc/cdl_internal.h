@@ -90,7 +90,7 @@ constexpr int64_t kSoftFrom = 1 << 16;
 constexpr int kSoftMaxBins = 512;
 constexpr int kSoftCoefs = 10;
 constexpr size_t kSoftBinBytes = kSoftCoefs * sizeof(double), kSoftTableBytes = kSoftMaxBins * kSoftBinBytes;
-size_t quantize_sum_bytes(int64_t n);        // 16 bytes per block
+size_t quantize_sum_bytes(int64_t n);        // 16 or 32 bytes per block
 size_t quantize_scalar_bytes(int64_t n);     // the sums, then the table
 void *quantize_scalar_area(void *ws, int64_t n, int32_t n_levels);
 int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl_qparams &p,
@@ -201,9 +201,6 @@ size_t qconv_bwd_activations_workspace_bytes(int32_t B, int32_t H, int32_t W, in
 int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
                                  int32_t R, int32_t S, int32_t stride, int32_t pad, float delta_w, float *d_x_hat, void *ws,
                                  hipStream_t stream);
-
-// d_delta = mul_d * sum of partial[2 i], d_alpha = mul_a * sum of partial[2 i + 1], i < n, in a fixed order.
-int launch_scalar_finalize(const double *partial, int n, double mul_d, double mul_a, float *d_delta, float *d_alpha, hipStream_t stream);
 
 // ---- Huffman-coded size (cdl_huffman.hip) --------------------------------------------------
 size_t huffman_workspace_bytes(int64_t n);

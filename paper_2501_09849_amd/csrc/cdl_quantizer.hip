@@ -134,7 +134,8 @@ void marginal_finalize_kernel(const unsigned long long *__restrict__ rows, int n
 // in its low bits, and what the other bits add up to (kHistOne per entry) is taken off at the end.  The number of entries of a cell is read from
 // the low half of the outermost pair, whose probabilities are so small that their sum stays below 2^20 (outer_pair_is_small; sets of up to
 // five levels in the soft regime keep the bins), for W = 1 from a 32-bit cell that counts.
-// At the end the block adds the copies into 64-bit sums per level, and marginal_end adds these over all blocks.
+// At the end the block adds the copies into 64-bit sums per level, and marginal_end adds these over all blocks.  (Grids that finish the PMF themselves
+// keep the bins, whose cells are fewer to clear and to add up: 74 K entries 8.3 against 9.2 us.)
 // us, forward pass with PMF and the launch that ends it, cold, before (bins, 74 instructions an entry) / so (53): 25.6 M entries of 31 levels 61 / 55,
 // 115.6 M of 16 levels 214 / 204 (bins with the shorter arithmetic: 50.3 M of 255 levels 100 / 92).
 // ------------------------------------------------------------------------------------------
@@ -283,11 +284,6 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
 
 // U: vectors of four entries a thread takes per trip.  U > 1 (tensors of more than kOneTripEntries): with MARG the loads of a trip
 // are issued before the trip before it is computed and stored, without MARG there is one trip.
-// Up to kKeepUpTo entries (128 MiB) theta is read by ordinary loads also where the rest streams: a backward pass that follows finds it in the last-level
-// cache (25.6 M entries, forward and backward 97 -> 91 us).  Larger tensors do not stay there, and in memory just written by others such
-// loads take longer (115.6 M entries: 234 against 190 us on the first pass, 196 against 187 later).
-constexpr int64_t kKeepUpTo = 1ll << 25;
-
 template <int W, bool IDX, bool SOFT, bool MARG, bool FEW, int U, bool PAIRS>
 __global__ __launch_bounds__(MARG ? kMargThreads : one_trip_threads(U))
 void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
@@ -314,7 +310,6 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
     const int64_t n4 = n >> 2;
     float sv[4];
     int ci[4];
-    with_constant(n > kKeepUpTo, [&](auto loads) {
     with_constant(k.stream != 0, [&](auto streams) {
         auto vec = [&](const float4 &t, int64_t w) {
             const float th[4] = {t.x, t.y, t.z, t.w};
@@ -329,7 +324,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
             float4 t[U];
             auto load = [&](int64_t v) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) t[u] = load_stream4(theta + 4 * (v + u * T < n4 ? v + u * T : 0), loads.value);
+                for (int u = 0; u < U; ++u) t[u] = load_stream4(theta + 4 * (v + u * T < n4 ? v + u * T : 0), streams.value);
             };
             const int64_t stride = (int64_t)gridDim.x * T * U;
             int64_t v = (int64_t)blockIdx.x * T * U + threadIdx.x;
@@ -348,13 +343,12 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
                 constexpr int N = decltype(count)::value;
                 float4 t[N];
 #pragma unroll
-                for (int u = 0; u < N; ++u) t[u] = load_stream4(theta + 4 * (v + u * T), loads.value);
+                for (int u = 0; u < N; ++u) t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
 #pragma unroll
                 for (int u = 0; u < N; ++u) vec(t[u], v + u * T);
             };
             one_trip_or_loop<T, U>(n4, group);
         }
-    });
     });
     // ragged tail: the last 1..3 entries, one thread of the last block
     const int cnt = (int)(n - (n4 << 2));
@@ -742,36 +736,26 @@ void quantize_bwd_uniform_kernel(const float *__restrict__ theta, const float *g
     if (SCALARS) scalar_finish<kUniThreads>(acc_d, acc_a, fin);
 }
 
-// d_delta = mul_d * sum of partials; d_alpha = mul_a * sum of partials.  Fixed summation order: thread t adds the
-// pairs t, t + T, t + 2T, ... (four independent chains, so that four loads are in flight: with a few thousand pairs
-// one chain per thread is nothing but memory latency), then the threads are added up by halving.
+// The pairs of sums that the blocks of a large grid left.  Fixed summation order: thread t of all takes the pairs t, t + threads, ... (four
+// independent chains, so that four loads are in flight: with a few thousand pairs one chain per thread is nothing but memory
+// latency), then scalar_finish.  56448 pairs: one block 12.2 us, sixteen 6; 12501 pairs: one 5.0, four 5.8.
 constexpr int kScalarFinThreads = 1024;
 
 __global__ __launch_bounds__(kScalarFinThreads)
-void scalar_finalize_kernel(const double *__restrict__ partial, int nblocks, double mul_d, double mul_a,
-                            float *__restrict__ d_delta, float *__restrict__ d_alpha)
+void scalar_finalize_kernel(const double *__restrict__ partial, int n_pairs, ScalarFinish fin)
 {
-    constexpr int T = kScalarFinThreads;
-    __shared__ double sd[T], sa[T];
+    const int T = kScalarFinThreads * (int)gridDim.x;
     const double2 *pairs = reinterpret_cast<const double2 *>(partial);
     double a[4] = {0.0, 0.0, 0.0, 0.0}, b[4] = {0.0, 0.0, 0.0, 0.0};
-    int i = threadIdx.x;
-    for (; i + 3 * T < nblocks; i += 4 * T) {
+    int i = blockIdx.x * kScalarFinThreads + threadIdx.x;
+    for (; i + 3 * (int64_t)T < n_pairs; i += 4 * T) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) { const double2 v = pairs[i + u * T]; a[u] += v.x; b[u] += v.y; }
     }
-    for (int u = 0; i < nblocks; i += T, ++u) { const double2 v = pairs[i]; a[u] += v.x; b[u] += v.y; }
-    sd[threadIdx.x] = (a[0] + a[1]) + (a[2] + a[3]);
-    sa[threadIdx.x] = (b[0] + b[1]) + (b[2] + b[3]);
-    __syncthreads();
-    for (int off = T / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) { sd[threadIdx.x] += sd[threadIdx.x + off]; sa[threadIdx.x] += sa[threadIdx.x + off]; }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        if (d_delta) *d_delta = (float)(sd[0] * mul_d);
-        if (d_alpha) *d_alpha = (float)(sa[0] * mul_a);
-    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+        if (i + u * (int64_t)T < n_pairs) { const double2 v = pairs[i + u * T]; a[u] += v.x; b[u] += v.y; }
+    scalar_finish<kScalarFinThreads>((a[0] + a[1]) + (a[2] + a[3]), (b[0] + b[1]) + (b[2] + b[3]), fin);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -859,7 +843,7 @@ void quantize_draw_kernel(const float *__restrict__ theta, const float *__restri
 // The table of l_k sits in LDS with kPad zeros on both sides.  dtheta = g_in + scale * dH/dtheta.
 // ------------------------------------------------------------------------------------------
 template <int W, bool DTHETA, bool SCALARS, bool ADD, int U>
-__global__ __launch_bounds__(one_trip_threads(U))
+__global__ __launch_bounds__(one_trip_threads(U), W == 1 || W == 2 ? 8 : 1)
 void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict__ marg, const float *__restrict__ g_in,
                         int64_t n, QConst k, float dtheta_mul /* scale * (-2 alpha delta / n) */,
                         float *__restrict__ dtheta, ScalarFinish fin)
@@ -1075,20 +1059,32 @@ size_t hist_bytes(int64_t n, int32_t n_levels)
 }
 constexpr size_t kRecordBytes = 16384 * 2 * sizeof(unsigned long long);      // (marginal_finalize_kernel: at most 16 chunks of 256 levels)
 
-ScalarFinish scalar_finish_args(void *scalars, int grid, double mul_d, double mul_a, float *d_delta, float *d_alpha)
+// Whether the blocks' sums are left for a second launch (cdl_finish.h), and where: [records of the launch that adds up][partial sums or records]
+bool scalars_in_two_launches(int64_t n, int grid) { return n >= kStreamFrom && grid > kMaxQuantBlocks; }
+constexpr int kScalarFinBlocks = 16;
+constexpr size_t kScalarFinBytes = kScalarFinBlocks * 4 * sizeof(unsigned long long);
+
+ScalarFinish scalar_finish_args(void *scalars, int64_t n, int grid, double mul_d, double mul_a, float *d_delta, float *d_alpha)
 {
     ScalarFinish f{};
-    double *area = reinterpret_cast<double *>(scalars);
-    if (grid > kFinishMaxBlocks) f.partial = area;
+    char *const area = reinterpret_cast<char *>(scalars) + kScalarFinBytes;
+    if (scalars_in_two_launches(n, grid)) f.partial = reinterpret_cast<double *>(area);
     else { f.records = reinterpret_cast<unsigned long long *>(area); f.tag = next_finish_tag(); }
     f.mul_d = mul_d; f.mul_a = mul_a; f.d_delta = d_delta; f.d_alpha = d_alpha;
     return f;
 }
 
-int launch_scalar_end(const ScalarFinish &f, int grid, hipStream_t stream)
+int launch_scalar_end(const ScalarFinish &f, void *scalars, int grid, hipStream_t stream)
 {
     const int rc = check_launch();
-    return rc != CDL_OK || !f.partial ? rc : launch_scalar_finalize(f.partial, grid, f.mul_d, f.mul_a, f.d_delta, f.d_alpha, stream);
+    if (rc != CDL_OK || !f.partial) return rc;
+    ScalarFinish last = f;
+    last.partial = nullptr;
+    last.records = reinterpret_cast<unsigned long long *>(scalars);
+    last.tag = next_finish_tag();
+    const int blocks = grid <= 16384 ? 1 : kScalarFinBlocks;
+    CDL_LAUNCH("scalar_finalize_kernel", stream, scalar_finalize_kernel, dim3(blocks), dim3(kScalarFinThreads), 0, f.partial, grid, last);
+    return check_launch();
 }
 
 // Whether the sum of a cell's outermost probabilities stays below 2^20: of two neighbours at a midpoint each has half, so that the level W away
@@ -1107,7 +1103,7 @@ void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStre
                (M) ? hist_bytes_of(k.n_levels, W, P) : 0, theta, n, k, idx, soft, fin)
 #define CDL_FWD(I, S, M, U)                                                                               \
     do {                                                                                                  \
-        if ((M) != 0 && pairs) CDL_FWD_P(I, S, M, U, W > 0 && (M) != 0);                                  \
+        if ((M) == 1 && pairs) CDL_FWD_P(I, S, M, U, W > 0 && (M) == 1);                                  \
         else CDL_FWD_P(I, S, M, U, false);                                                                \
     } while (0)
     const bool few = hist_few(grid, k.n_levels), pairs = pairs_serve(kappa, k.n_levels, W);
@@ -1267,8 +1263,10 @@ void *quantize_scalar_area(void *ws, int64_t n, int32_t n_levels) { return reint
 
 size_t quantize_sum_bytes(int64_t n)
 {
-    const int64_t blocks = one_trip_grid(n) > kMaxQuantBlocks ? one_trip_grid(n) : kMaxQuantBlocks;
-    return align_up((size_t)blocks * 2 * sizeof(double), 256);
+    // (one-trip grids below kStreamFrom and looping grids keep records, larger ones pairs; never less than a smaller tensor)
+    const size_t records = (size_t)scalar_records(one_trip_grid(kStreamFrom)) * 4 * sizeof(unsigned long long), pairs = (size_t)one_trip_grid(n) * 2 * sizeof(double);
+    const size_t small = (size_t)scalar_records(kMaxQuantBlocks) * 4 * sizeof(unsigned long long);
+    return align_up(kScalarFinBytes + (n <= kOneTripEntries ? small : records > pairs ? records : pairs), 256);
 }
 
 size_t quantize_scalar_bytes(int64_t n) { return quantize_sum_bytes(n) + kSoftTableBytes; }
@@ -1394,11 +1392,11 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
     const int grid = one_trip ? (int)one_trip_grid(n) : want_scalars && band_template(k) != 0 ? finishing_grid(grid_for(n)) : grid_for(n);
     const double d = (double)p.delta;
     ScalarFinish fin{};
-    if (want_scalars) fin = scalar_finish_args(scalars, grid, 1.0, d * d * d, d_delta, d_alpha);
+    if (want_scalars) fin = scalar_finish_args(scalars, n, grid, 1.0, d * d * d, d_delta, d_alpha);
     const SoftPlan plan = want_scalars && uniform_half_width(p, k) && soft_bwd_from_uniform(p, n) ? soft_plan(p, k, n, true) : SoftPlan{};
     if (plan.bins) {
         const int rc = launch_soft_bwd(theta, g, n, p, k, plan, dtheta, fin, reinterpret_cast<char *>(scalars) + quantize_sum_bytes(n), grid, stream);
-        return rc != CDL_OK ? rc : launch_scalar_end(fin, grid, stream);
+        return rc != CDL_OK ? rc : launch_scalar_end(fin, scalars, grid, stream);
     }
     const bool want_dtheta = dtheta != nullptr;
     const int jh = uniform_half_width(p, k);
@@ -1415,13 +1413,7 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
         case 4: launch_bwd_w<4>(want_dtheta, want_scalars, one_trip, grid, stream, theta, g, n, k, dtheta, fin); break;
         default: launch_bwd_w<0>(want_dtheta, want_scalars, one_trip, grid, stream, theta, g, n, k, dtheta, fin); break;
     }
-    return launch_scalar_end(fin, grid, stream);
-}
-
-int launch_scalar_finalize(const double *partial, int n, double mul_d, double mul_a, float *d_delta, float *d_alpha, hipStream_t stream)
-{
-    CDL_LAUNCH("scalar_finalize_kernel", stream, scalar_finalize_kernel, dim3(1), dim3(kScalarFinThreads), 0, partial, n, mul_d, mul_a, d_delta, d_alpha);
-    return check_launch();
+    return launch_scalar_end(fin, scalars, grid, stream);
 }
 
 int launch_quantize_draw(const float *theta, const float *u, int64_t n, const cdl_qparams &p, int8_t *idx, hipStream_t stream)
@@ -1491,7 +1483,8 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     const double alpha = (double)p.alpha, delta = (double)p.delta;
     const double mul_theta = (double)scale * (-2.0 * alpha * delta / (double)n);
     ScalarFinish fin{};
-    if (want_scalars) fin = scalar_finish_args(quantize_scalar_area(ws, n, p.n_levels), grid, mul_theta, (double)scale * delta * delta / (double)n, d_delta, d_alpha);
+    void *const scalars = want_scalars ? quantize_scalar_area(ws, n, p.n_levels) : nullptr;
+    if (want_scalars) fin = scalar_finish_args(scalars, n, grid, mul_theta, (double)scale * delta * delta / (double)n, d_delta, d_alpha);
     switch (band_template(k)) {
         case 1: launch_entropy_bwd_w<1>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
         case 2: launch_entropy_bwd_w<2>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
@@ -1499,7 +1492,7 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
         case 4: launch_entropy_bwd_w<4>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
         default: launch_entropy_bwd_w<0>(want_dtheta, want_scalars, g_in != nullptr, one_trip, grid, stream, theta, marg, g_in, n, k, (float)mul_theta, dtheta, fin); break;
     }
-    return launch_scalar_end(fin, grid, stream);
+    return launch_scalar_end(fin, scalars, grid, stream);
 }
 
 }  // namespace cdl

@@ -224,7 +224,7 @@ __device__ __forceinline__ void generic_sums(float th, const QConst &k, GenericS
 // variance and third central moment of the level offset j under the CPMF and r = u / delta,
 //     dQd/dtheta = 2 kappa var,   dQd/ddelta = (c + mu) + 2 kappa ((r - c - 2 mu) var - c3),   dQd/dalpha / delta^3 = 2 (r - mu) var - c3.
 // W: band half-width of the unrolled kernels, 0 = the generic loop.  SCALARS: also the last two.
-// With q = c + mu and e = (r - mu) var the last two are q - 2 kappa q var + 2 kappa (e - c3) and 2 e - c3, and c3 = m3 - mu (3 var + mu^2).
+// The unrolled bands save three instructions: with q = c + mu and e = (r - mu) var the last two are q - 2 kappa q var + 2 kappa (e - c3) and 2 e - c3, and c3 = m3 - mu (3 var + mu^2).
 template <int W, bool SCALARS>
 __device__ __forceinline__ void quantizer_bwd_terms(float th, const QConst &k, float &d_theta, float &t_d, float &t_a)
 {
@@ -246,10 +246,17 @@ __device__ __forceinline__ void quantizer_bwd_terms(float th, const QConst &k, f
     t_a = 0.0f;
     if (SCALARS) {
         const float m3 = S3 * inv;
-        const float c3 = fmaf(-mu, fmaf(3.0f, var, mu * mu), m3);
-        const float q = cf + mu, e = fmaf(u, k.inv_delta, -mu) * var;      // (u is held where the bands of W = 2 hold it)
-        t_d = fmaf(k.two_kappa, e - c3, fmaf(-q, d_theta, q));
-        t_a = fmaf(2.0f, e, -c3);
+        if (W > 0) {
+            const float c3 = fmaf(-mu, fmaf(3.0f, var, mu * mu), m3);
+            const float q = cf + mu, e = fmaf(u, k.inv_delta, -mu) * var;      // (u is held where the bands of W = 2 hold it)
+            t_d = fmaf(k.two_kappa, e - c3, fmaf(-q, d_theta, q));
+            t_a = fmaf(2.0f, e, -c3);
+        } else {
+            const float c3 = fmaf(-mu, fmaf(-2.0f * mu, mu, 3.0f * m2), m3);   // m3 - 3 mu m2 + 2 mu^3
+            const float r = u * k.inv_delta;
+            t_d = (cf + mu) + k.two_kappa * fmaf(r - cf - 2.0f * mu, var, -c3);
+            t_a = fmaf(2.0f * (r - mu), var, -c3);
+        }
     }
 }
 

@@ -15,6 +15,7 @@
 #include "cdl_bwd_plan.h"
 #include "cdl_limbs.h"
 #include "cdl_finish.h"
+#include "cdl_rows.h"
 
 #include <mutex>
 #include "cdl_quantizer_math.h"
@@ -35,7 +36,7 @@ struct GemmArgs {
     const int8_t *A;      // [rowsA][lda]
     const int8_t *B;      // [rowsB][ldb]
     int64_t lda, ldb;
-    int rowsA, rowsB, Kc;  // Kc: contraction length in bytes, multiple of 16
+    int rowsA, rowsB, Kc;  // Kc: contraction length in bytes, multiple of 16 unless the kernel is for any
     int tiles_m, tiles_n;
     int32_t *acc_out;     // [rowsA][ldc] or null
     float *y_out;         // [rowsA][ldc] or null
@@ -48,10 +49,31 @@ struct GemmArgs {
     const int32_t *corr_row;
 };
 
+// The sum of a row of K index bytes, in lane 0 of the wave that reads it (16 bytes a lane and trip: the sums of 52 x 4032 weights byte by byte 15 us, so 4.7).
+__device__ __forceinline__ int row_sum(const int8_t *row, int K, int lane)
+{
+    int s = 0;
+    if (K >= 16) {
+#pragma unroll 4
+        for (int k = 16 * lane; k < K; k += 1024) {
+            const cdl_v4i w = tail_chunk(row, k, K);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_sdot4(w[i], 0x01010101, s, false);
+        }
+    } else if (lane < K) {
+        s = (int)row[lane];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    return s;
+}
+
 __device__ __forceinline__ int swz(int row, int q) { return q ^ ((row >> 1) & 3); }
 
 // TM x TN: 32x32 MFMA tiles per wave; the block's four waves form a 2 x 2 grid.
-template <int TM, int TN>
+// RAGGED: Kc is any length from 16 on, rows start where they start, and the chunk that a row ends in is shifted into place (cdl_rows.h).  That costs
+// less than the copies of both operands with padded rows that aligned loads need: 24773 x 73 x 2646, us, copies and product 77 + 30, so 35.
+template <int TM, int TN, bool RAGGED>
 __global__ __launch_bounds__(kGemmThreads, 2)
 void qgemm_kernel(GemmArgs a)
 {
@@ -124,6 +146,20 @@ void qgemm_kernel(GemmArgs a)
     v4i pa0[LA], pb0[LB], pa1[DEEP ? LA : 1], pb1[DEEP ? LB : 1];
     auto fetch = [&](int kt, v4i (&pa)[LA], v4i (&pb)[LB]) {
         const int64_t off = (int64_t)kt * kKT;
+        if constexpr (RAGGED) {
+            if (kt * kKT + kKT <= a.Kc) {
+#pragma unroll
+                for (int i = 0; i < LA; ++i) pa[i] = load_any16(ga[i] + off);
+#pragma unroll
+                for (int i = 0; i < LB; ++i) pb[i] = load_any16(gb[i] + off);
+            } else {
+#pragma unroll
+                for (int i = 0; i < LA; ++i) pa[i] = tail_chunk(ga[i] - qa[i], kt * kKT + qa[i], a.Kc);
+#pragma unroll
+                for (int i = 0; i < LB; ++i) pb[i] = tail_chunk(gb[i] - qb[i], kt * kKT + qb[i], a.Kc);
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < LA; ++i)
             pa[i] = (kt * kKT + qa[i] < a.Kc) ? *reinterpret_cast<const v4i *>(ga[i] + off) : zero4;
@@ -208,7 +244,7 @@ void qgemm_kernel(GemmArgs a)
 }
 
 template <int TM, int TN>
-int launch_gemm(GemmArgs a, hipStream_t stream)
+int launch_gemm(GemmArgs a, bool ragged, hipStream_t stream)
 {
     constexpr int BM = 2 * TM * 32, BN = 2 * TN * 32;
     a.tiles_m = (a.rowsA + BM - 1) / BM;
@@ -216,7 +252,8 @@ int launch_gemm(GemmArgs a, hipStream_t stream)
     const int64_t total = (int64_t)a.tiles_m * a.tiles_n;
     if (total == 0) return CDL_OK;
     const int64_t grid = (total + 7) / 8 * 8;
-    CDL_LAUNCH("qgemm_kernel(fwd)", stream, (qgemm_kernel<TM, TN>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
+    if (ragged) CDL_LAUNCH("qgemm_kernel(fwd)", stream, (qgemm_kernel<TM, TN, true>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
+    else CDL_LAUNCH("qgemm_kernel(fwd)", stream, (qgemm_kernel<TM, TN, false>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
     return check_launch();
 }
 
@@ -768,10 +805,7 @@ void conv_prep_kernel(int8_t *page, int off, const int8_t *w, int N, int Kc, int
     if (blockIdx.x == 0 && threadIdx.x < 128) page[threadIdx.x] = (int8_t)(-off);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int n = blockIdx.x * 4 + wave; n < N; n += gridDim.x * 4) {
-        int s = 0;
-        for (int k = lane; k < Kc; k += 64) s += (int)w[(int64_t)n * Kc + k];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        const int s = row_sum(w + (int64_t)n * Kc, Kc, lane);
         if (lane == 0) corr[n] = off * s;
     }
 }
@@ -1588,17 +1622,13 @@ void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_
 }
 
 // out[r] = mult * sum_k idx[r][k] + add for an int8 matrix [rows][K]: the corrections of a product whose
-// other operand is stored with an offset.  One wave per row, 4 bytes per lane and trip.
+// other operand is stored with an offset.  One wave per row.
 __global__ __launch_bounds__(256) void index_rowsum_kernel(const int8_t *__restrict__ idx, int rows, int K, int mult, int add,
                                                            int32_t *__restrict__ out)
 {
     const int lane = threadIdx.x & 63;
     for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += gridDim.x * 4) {
-        const int8_t *p = idx + (int64_t)r * K;
-        int s = 0;
-        for (int k = lane; k < K; k += 64) s += (int)p[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+        const int s = row_sum(idx + (int64_t)r * K, K, lane);
         if (lane == 0) out[r] = mult * s + add;
     }
 }
@@ -1617,44 +1647,93 @@ __global__ __launch_bounds__(256) void g_rowsum_kernel(const float *__restrict__
     }
 }
 
-// Column sums of g [M][N]: block b adds rows b * rows_per .. of every column into partial[b][N] (a thread walks its
-// columns down the rows, neighbouring threads read neighbouring columns); g_colsum_finish adds the blocks in a
-// fixed order and multiplies by `mult`.
+// Column sums of g [M][N], and of the same pass max |g| per block (what absmax_kernel leaves): block b adds rows b * rows_per .. of every column into
+// partial[b][N].  A thread takes V neighbouring columns (V = 4 where rows stay aligned) and, where there are fewer such groups than threads, every
+// subs-th row of them, four rows' loads in flight; the subs are added through LDS.  g_colsum_finish adds the blocks.  All in double and in a fixed order.
+// What bounds it is memory: 96570 x 148, us, as two passes with a column and four loads of 4 bytes a thread 10 + 29, so 12 (4.9 TB/s); 10669 x 64 4.3 + 5.0, so 4.4.
+// A thread of g_colsum_finish adds 16 of 512 blocks' sums (64 of them: 6.6 us instead of 4.6).
 constexpr int kColsumBlocks = 512;
 
-__global__ __launch_bounds__(256) void g_colsum_kernel(const float *__restrict__ g, int M, int N, int rows_per, double *__restrict__ partial)
+template <int V>
+__global__ __launch_bounds__(256) void g_colsum_kernel(const float *__restrict__ g, int M, int N, int rows_per, double *__restrict__ partial,
+                                                       unsigned int *__restrict__ block_max, unsigned int *__restrict__ clear, int n_clear)
 {
+    __shared__ double sums[256][V];
+    __shared__ unsigned int wave_max[4];
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0u;      // (absmax_kernel)
+    const int groups = N / V, subs = groups < 256 ? 256 / groups : 1, per_pass = groups < 256 ? groups : 256;
+    const int sub = (int)threadIdx.x / per_pass, at = (int)threadIdx.x - sub * per_pass;
     const int m0 = blockIdx.x * rows_per, m1 = min(M, m0 + rows_per);
-    for (int n = threadIdx.x; n < N; n += 256) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        int m = m0;
-        for (; m + 3 < m1; m += 4) {
-            s0 += (double)g[(int64_t)m * N + n];
-            s1 += (double)g[(int64_t)(m + 1) * N + n];
-            s2 += (double)g[(int64_t)(m + 2) * N + n];
-            s3 += (double)g[(int64_t)(m + 3) * N + n];
+    unsigned int largest = 0u;
+    for (int base = 0; base < groups; base += per_pass) {
+        const int c = V * (base + at);
+        const bool mine = sub < subs && base + at < groups;
+        double s[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) s[e] = 0.0;
+        if (mine) {
+            auto rows = [&](int m, auto count) {
+                constexpr int R = decltype(count)::value;
+                float x[R][V];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float *p = g + (int64_t)(m + r * subs) * N + c;
+                    if (V == 4) {
+                        const float4 t = load_stream4(p);
+                        x[r][0] = t.x; x[r][1 % V] = t.y; x[r][2 % V] = t.z; x[r][3 % V] = t.w;
+                    } else {
+                        x[r][0] = *p;
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        s[e] += (double)x[r][e];
+                        largest = max(largest, __float_as_uint(fabsf(x[r][e])));
+                    }
+            };
+            int m = m0 + sub;
+            for (; m + 3 * subs < m1; m += 4 * subs) rows(m, std::integral_constant<int, 4>{});
+            for (; m < m1; m += subs) rows(m, std::integral_constant<int, 1>{});
         }
-        for (; m < m1; ++m) s0 += (double)g[(int64_t)m * N + n];
-        partial[(int64_t)blockIdx.x * N + n] = (s0 + s1) + (s2 + s3);
+        if (subs > 1) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) sums[threadIdx.x][e] = s[e];
+            __syncthreads();
+            if (sub == 0 && mine)
+                for (int q = 1; q < subs; ++q)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) s[e] += sums[q * per_pass + at][e];
+        }
+        if (sub == 0 && mine)
+#pragma unroll
+            for (int e = 0; e < V; ++e) partial[(int64_t)blockIdx.x * N + c + e] = s[e];
     }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) largest = max(largest, (unsigned int)__shfl_down((int)largest, off, 64));
+    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = largest;
+    __syncthreads();
+    if (threadIdx.x == 0) block_max[blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
 
 __global__ __launch_bounds__(256) void g_colsum_finish_kernel(const double *__restrict__ partial, int blocks, int N, double mult, double *__restrict__ out)
 {
-    // 32 columns per block, eight threads to a column, eight loads in flight each (one thread per column is one chain of
+    // 8 columns per block, 32 threads to a column, eight loads in flight each (one thread per column is one chain of
     // memory latencies: 60 us for 512 blocks' sums of 1000 columns)
-    __shared__ double part[8][33];
-    const int e = threadIdx.x & 31, sub = threadIdx.x >> 5, n = blockIdx.x * 32 + e;
+    __shared__ double part[32][9];
+    const int e = threadIdx.x & 7, sub = threadIdx.x >> 3, n = blockIdx.x * 8 + e;
     double s = 0.0;
     if (n < N) {
 #pragma unroll 8
-        for (int b = sub; b < blocks; b += 8) s += partial[(int64_t)b * N + n];
+        for (int b = sub; b < blocks; b += 32) s += partial[(int64_t)b * N + n];
     }
     part[sub][e] = s;
     __syncthreads();
     if (sub == 0 && n < N) {
 #pragma unroll
-        for (int q = 1; q < 8; ++q) s += part[q][e];
+        for (int q = 1; q < 32; ++q) s += part[q][e];
         out[n] = mult * s;
     }
 }
@@ -1724,7 +1803,8 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ g
 // registers and stores 16 bytes of four output rows, so that 8 lanes write 128 contiguous bytes.  LDS rows are 33 words apart and
 // rows from 64 on 8 words further: the 32 lanes of a read (8 groups of 16 rows, 4 columns) then lie in different banks.
 // Limited by memory: 50176 windows of 2304 entries 65 -> 28 us (4.6 TB/s), a matrix of that size 70 -> 44.
-// ALIGN: of the rows - cols % 16 == 0 (one load per 16 bytes), % 4 == 0 (four) or neither (byte by byte).
+// ALIGNED: the rows are, cols % 16 == 0.  Otherwise they are read in the same 16-byte loads from where they start (cdl_rows.h; 24773 x 2646 byte by
+// byte 84 us, so 46).
 // CONV: src is not a matrix but the activations of a convolutional layer, [B][H][W][C] with C a multiple of 16, and
 // "src[r][c]" is entry c = (tap row, tap column, channel) of the window of output pixel r = (b, p, q) - the matrix of
 // input windows, which is never stored the right way round: only its transpose is written, as the product that
@@ -1748,7 +1828,7 @@ struct TransposeJob {
 
 constexpr int kTrRows = 128, kTrCols = 128;
 
-template <int ALIGN, bool CONV>
+template <bool ALIGNED, bool CONV>
 __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int block, const ConvGeom &geom)
 {
     const int8_t *__restrict__ src = job.src;
@@ -1790,21 +1870,19 @@ __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int blo
                     if (inside) v[j] = *reinterpret_cast<const uint4 *>(src + (((b * geom.H + h0) * geom.W + w0) * geom.C + tap_off));
                 }
             } else if (r < rows) {
-                const int8_t *p = src + (int64_t)r * cols + c;
-                if (ALIGN == 16) {
-                    if (c < cols) v[j] = *reinterpret_cast<const uint4 *>(p);
-                } else {
+                const int8_t *p = src + (int64_t)r * cols;
+                if (ALIGNED) {
+                    if (c < cols) v[j] = *reinterpret_cast<const uint4 *>(p + c);
+                } else if (cols >= 16) {
+                    cdl_v4i w = {0, 0, 0, 0};
+                    if (c + 16 <= cols) w = load_any16(p + c);
+                    else if (c < cols) w = tail_chunk(p, c, cols);
+                    v[j] = uint4{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
+                } else if (c == 0) {
                     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (ALIGN == 4) {
-                            if (c + 4 * i < cols) w[i] = *reinterpret_cast<const uint32_t *>(p + 4 * i);
-                        } else {
-#pragma unroll
-                            for (int b = 0; b < 4; ++b)
-                                if (c + 4 * i + b < cols) w[i] |= (uint32_t)(uint8_t)p[4 * i + b] << (8 * b);
-                        }
-                    }
+                    for (int i = 0; i < 16; ++i)
+                        if (i < cols) w[i >> 2] |= (uint32_t)(uint8_t)p[i] << (8 * (i & 3));
                     v[j] = uint4{w[0], w[1], w[2], w[3]};
                 }
             }
@@ -1862,11 +1940,11 @@ __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int blo
 }
 
 // Blocks 0 .. a.blocks - 1 do job a, the rest job b; the last of all makes the plan.
-template <int ALIGN, bool CONV>
+template <bool ALIGNED, bool CONV>
 __global__ __launch_bounds__(256) void transpose_i8_kernel(TransposeJob a, TransposeJob b, ConvGeom geom, PlanArgs plan)
 {
-    if ((int)blockIdx.x < a.blocks) transpose_tiles<ALIGN, CONV>(a, blockIdx.x, geom);
-    else if (!CONV) transpose_tiles<ALIGN, false>(b, (int)blockIdx.x - a.blocks, geom);
+    if ((int)blockIdx.x < a.blocks) transpose_tiles<ALIGNED, CONV>(a, blockIdx.x, geom);
+    else if (!CONV) transpose_tiles<ALIGNED, false>(b, (int)blockIdx.x - a.blocks, geom);
     plan_at_end(plan, blockIdx.x, gridDim.x);
 }
 
@@ -2133,10 +2211,9 @@ int launch_transposes(const TransposeJob &a, const TransposeJob &b, const ConvGe
     p.flags = reinterpret_cast<unsigned long long *>(flags);
     p.tag = next_finish_tag();
     if (blocks > kPlanMaxBlocks) p.plan = nullptr;
-    if (windows) CDL_LAUNCH("transpose_i8_kernel(windows)", stream, (transpose_i8_kernel<16, true>), dim3((unsigned)blocks), dim3(256), 0, a, b, *windows, p);
-    else if (a.cols % 16 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<16, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
-    else if (a.cols % 4 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<4, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
-    else CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<1, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
+    if (windows) CDL_LAUNCH("transpose_i8_kernel(windows)", stream, (transpose_i8_kernel<true, true>), dim3((unsigned)blocks), dim3(256), 0, a, b, *windows, p);
+    else if (a.cols % 16 == 0) CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<true, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
+    else CDL_LAUNCH("transpose_i8_kernel", stream, (transpose_i8_kernel<false, false>), dim3((unsigned)blocks), dim3(256), 0, a, b, ConvGeom{}, p);
     if (!p.plan)
         CDL_LAUNCH("plan_kernel", stream, plan_kernel, dim3(1), dim3(1024), 0, here.plan, here.block_max, here.n_max, here.col_abs_a, here.n_abs_a,
                    here.col_abs_b, here.n_abs_b, here.delta_a, here.delta_b);
@@ -2199,27 +2276,27 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
                    a_offset != 0 ? 0 : K * a_offset * b_offset, corr_row);
         g.corr_row = corr_row;
     }
-    if (K % 16 != 0) {
-        // rows would not start on 16-byte boundaries: stage zero-padded copies
-        const int kp = (int)pad_to(K, 16);
+    const bool ragged = K % 16 != 0 && K >= 16;
+    if (K < 16) {
+        // less than a chunk: zero-padded copies
         int8_t *ap = reinterpret_cast<int8_t *>(ws);
-        int8_t *bp = ap + align_up((size_t)M * (size_t)kp, 256);
-        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)M * kp, 256, 8192)), dim3(256), 0, a_idx, (int64_t)M, K, ap, kp);
-        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)N * kp, 256, 8192)), dim3(256), 0, b_idx, (int64_t)N, K, bp, kp);
+        int8_t *bp = ap + align_up((size_t)M * 16, 256);
+        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)M * 16, 256, 8192)), dim3(256), 0, a_idx, (int64_t)M, K, ap, 16);
+        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)N * 16, 256, 8192)), dim3(256), 0, b_idx, (int64_t)N, K, bp, 16);
         int rc = check_launch();
         if (rc != CDL_OK) return rc;
-        g.A = ap; g.B = bp; g.lda = kp; g.ldb = kp; g.Kc = kp;
+        g.A = ap; g.B = bp; g.lda = 16; g.ldb = 16; g.Kc = 16;
     }
     g.acc_out = acc; g.y_out = y; g.ldc = N;
     g.scale = delta_a * delta_b;
-    if (dma_serves(M, N, g.Kc)) return launch_gemm_dma(g, stream);
+    if (!ragged && dma_serves(M, N, g.Kc)) return launch_gemm_dma(g, stream);
     // (up to 64 output columns: tiles 64 columns wide, so that half of a wider one is not padding; fewer tiles of 256
     // rows than compute units: tiles of 128 rows, twice as many blocks)
     const bool few = (int64_t)((M + 255) / 256) * ((N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128)) < 256 && M > 128;
     // (and of 64 where tiles of 128 are too few)
     const bool fewer = few && (int64_t)((M + 127) / 128) * ((N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128)) < 256;
-    if (N <= 64) return fewer ? launch_gemm<1, 1>(g, stream) : few ? launch_gemm<2, 1>(g, stream) : launch_gemm<4, 1>(g, stream);
-    return fewer ? launch_gemm<1, 2>(g, stream) : few ? launch_gemm<2, 2>(g, stream) : launch_gemm<4, 2>(g, stream);
+    if (N <= 64) return fewer ? launch_gemm<1, 1>(g, ragged, stream) : few ? launch_gemm<2, 1>(g, ragged, stream) : launch_gemm<4, 1>(g, ragged, stream);
+    return fewer ? launch_gemm<1, 2>(g, ragged, stream) : few ? launch_gemm<2, 2>(g, ragged, stream) : launch_gemm<4, 2>(g, ragged, stream);
 }
 
 int launch_qgemm_quantize_fwd(const float *x, const cdl_qparams &p, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,
@@ -2515,14 +2592,24 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     unsigned int *block_max = reinterpret_cast<unsigned int *>(base + L.block_max);
     unsigned int *ss_a = reinterpret_cast<unsigned int *>(base + L.ss_a);
     unsigned int *ss_b = reinterpret_cast<unsigned int *>(base + L.ss_b);
-    CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, gr, (int64_t)M * N, block_max,
-               ss_a, (int)((L.ss_b - L.ss_a) / sizeof(unsigned int)) + K);
+    // the column sums that the weight gradient needs besides (below) are of the same pass over g as its largest entry
+    int n_max = L.n_max;
+    const int n_clear = (int)((L.ss_b - L.ss_a) / sizeof(unsigned int)) + K;
+    if (want_db && a_offset != 0) {
+        double *cp = reinterpret_cast<double *>(base + L.colsum_partial);
+        const int most = L.n_max < kColsumBlocks ? L.n_max : kColsumBlocks, rows_per = (M + most - 1) / most;
+        n_max = (M + rows_per - 1) / rows_per;
+        if (N % 4 == 0) CDL_LAUNCH("g_colsum_kernel", stream, g_colsum_kernel<4>, dim3(n_max), dim3(256), 0, gr, M, N, rows_per, cp, block_max, ss_a, n_clear);
+        else CDL_LAUNCH("g_colsum_kernel", stream, g_colsum_kernel<1>, dim3(n_max), dim3(256), 0, gr, M, N, rows_per, cp, block_max, ss_a, n_clear);
+    } else {
+        CDL_LAUNCH("absmax_kernel", stream, absmax_kernel, dim3(L.n_max), dim3(256), 0, gr, (int64_t)M * N, block_max, ss_a, n_clear);
+    }
     {
         // the larger operand first: what is left when its blocks run out is the smaller one's
         TransposeJob ja{}, jb{};
         if (want_db) ja = transpose_job(a_idx, M, K, at, L.ldm, ss_a);
         if (d_a_hat) (want_db ? jb : ja) = transpose_job(b_idx, N, K, bt, L.ldn, ss_b, by_rows);
-        const PlanArgs pa{plan, block_max, L.n_max, ss_a, ss_b, want_db ? K : 0, d_a_hat ? K : 0, delta_a, delta_b, nullptr, 0ull};
+        const PlanArgs pa{plan, block_max, n_max, ss_a, ss_b, want_db ? K : 0, d_a_hat ? K : 0, delta_a, delta_b, nullptr, 0ull};
         ConvGeom g{};
         if (cw) {
             g = ConvGeom{cw->B, cw->H, cw->W, cw->C, cw->R, cw->S, cw->stride, cw->pad, cw->P, cw->Q, 0, make_div_by((uint32_t)cw->P * (uint32_t)cw->Q), make_div_by((uint32_t)cw->Q)};
@@ -2542,11 +2629,8 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     }
     if (want_db && a_offset != 0) {
         corr_db = reinterpret_cast<double *>(base + L.corr_db);
-        double *cp = reinterpret_cast<double *>(base + L.colsum_partial);
-        const int rows_per = (M + kColsumBlocks - 1) / kColsumBlocks;
-        const int blocks = (M + rows_per - 1) / rows_per;
-        CDL_LAUNCH("g_colsum_kernel", stream, g_colsum_kernel, dim3(blocks), dim3(256), 0, gr, M, N, rows_per, cp);
-        CDL_LAUNCH("g_colsum_finish_kernel", stream, g_colsum_finish_kernel, dim3((N + 31) / 32), dim3(256), 0, cp, blocks, N,
+        CDL_LAUNCH("g_colsum_finish_kernel", stream, g_colsum_finish_kernel, dim3((N + 7) / 8), dim3(256), 0,
+                   reinterpret_cast<const double *>(base + L.colsum_partial), n_max, N,
                    (double)delta_a * (double)a_offset, corr_db);
     }
     int rc = check_launch();

@@ -9,6 +9,7 @@
 // long as both operands share it.  Rows need no alignment and K any multiple: the last, partial block is shifted into
 // place in registers.  What bounds it is the L2: a wave's tile of 64 x 64 reads 16 KB for 16 MFMAs.
 #include "cdl_internal.h"
+#include "cdl_rows.h"
 
 #include <type_traits>
 
@@ -18,7 +19,6 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));
 
 struct SmallArgs {
     const int8_t *A;      // [M][K]
@@ -30,21 +30,6 @@ struct SmallArgs {
     float scale;
     int oa, ob;           // offsets the operands were stored with
 };
-
-// 16 bytes of a row from entry k0 on, zeros beyond its K entries (K >= 16)
-__device__ __forceinline__ v4i tail_chunk(const int8_t *row, int k0, int K)
-{
-    const int over = min(max(k0 + 16 - K, 0), 16);            // bytes of the chunk that lie beyond the row
-    union { v4i v; unsigned long long q[2]; } u;
-    u.v = *reinterpret_cast<const v4i_any *>(row + (over > 0 ? K - 16 : k0));
-    unsigned long long lo = u.q[0], hi = u.q[1];
-    int s = over;
-    if (s >= 8) { lo = hi; hi = 0ull; s -= 8; }
-    if (s >= 8) { lo = 0ull; s = 0; }
-    if (s > 0) { lo = (lo >> (8 * s)) | (hi << (64 - 8 * s)); hi >>= 8 * s; }
-    u.q[0] = lo; u.q[1] = hi;
-    return u.v;
-}
 
 // 32 x 32 MFMA tiles of a block, and its waves
 constexpr int TM = 1, TN = 1, KS = 4;
@@ -94,9 +79,9 @@ void qgemm_small_kernel(SmallArgs a)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i) fa[buf][i][c] = *reinterpret_cast<const v4i_any *>(pa[i] + k0 + 16 * c);
+                for (int i = 0; i < TM; ++i) fa[buf][i][c] = load_any16(pa[i] + k0 + 16 * c);
 #pragma unroll
-                for (int j = 0; j < TN; ++j) fb[buf][j][c] = *reinterpret_cast<const v4i_any *>(pb[j] + k0 + 16 * c);
+                for (int j = 0; j < TN; ++j) fb[buf][j][c] = load_any16(pb[j] + k0 + 16 * c);
             }
         } else {
 #pragma unroll

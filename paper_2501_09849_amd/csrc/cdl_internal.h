@@ -158,6 +158,11 @@ bool limb_rows_serves(int64_t M, int32_t N, int32_t K);
 int launch_limb_rows(const float *g, const int8_t *frag, int64_t tile_bytes, int32_t M, int32_t N, int32_t K, const BwdPlan *plan, const double *row_corr, float *out,
                      hipStream_t stream);
 
+// The same for few channels on both sides (cdl_conv_thin.hip); grids: of stride 1, one.
+bool conv_dx_thin_serves(const ConvDxGrid *grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, int32_t stride);
+int launch_conv_dx_thin(const float *g, const int8_t *w_idx, const ConvDxGrid &grid, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, float delta_w,
+                        float *d_x_hat, hipStream_t stream);
+
 // The same on limbs, from patches of g in LDS (cdl_conv_patch.hip).  wr: the weights per class as [ld / 32][C / 32][2][32][16] (halves of 32
 // contraction entries, channels, entries), a tap's channels padded with zeros to Np, a multiple of 32; pixel_max: the largest |g| of
 // every pixel, as the bits of a float; block_max [n_max <= kPatchMaxima], col_abs [n_abs]: their maxima are the largest |g| of all and the

@@ -129,6 +129,15 @@ bool qgemm_small_serves(int32_t M, int32_t N, int32_t K);
 int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset,
                        int32_t b_offset, int32_t *acc, float *y, hipStream_t stream);
 
+// The same, and the forward product of a convolution, with few output columns (cdl_fwd_thin.hip).
+struct ConvWindows;
+bool qgemm_thin_serves(int32_t N, int32_t K, int32_t b_offset);
+int launch_qgemm_thin(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset, int32_t *acc, float *y,
+                      hipStream_t stream);
+bool qconv_thin_serves(int64_t M, int32_t N, int32_t K);
+int launch_qconv_thin(const int8_t *x_idx, const int8_t *w_idx, const ConvWindows &w, int32_t N, float scale, int32_t x_offset, int32_t *acc, float *y,
+                      hipStream_t stream);
+
 // cw != null: a_idx is not an [M][K] matrix but the activations [B][H][W][C] of a convolutional layer, whose matrix of
 // input windows (M = B*P*Q rows, K = R*S*C columns) is the operand; only d_b_hat (the weight gradient) is served.
 struct ConvWindows {

@@ -15,8 +15,6 @@
 #include "cdl_div.h"
 #include "cdl_limbs.h"
 
-#include <type_traits>
-
 namespace cdl {
 
 namespace {
@@ -25,7 +23,8 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kThinWaves = 4, kThinPixels = 64 * kThinWaves, kThinDigits = 6;
 constexpr int kThinLds = 160 << 10;      // (two blocks share a compute unit where they fit)
-constexpr int kThinFew = 496;           // contraction entries whose digit sums, times 256 and another added, fit an int32
+constexpr int kThinUnits = 25;           // most units of 16 contraction entries
+static_assert(257ll * 128 * 128 * 16 * kThinUnits < (1ll << 31), "a digit sum, times 256 and another added, fits an int32");
 
 struct ThinArgs {
     const float *g;
@@ -219,27 +218,16 @@ void conv_dx_thin_kernel(ThinArgs a)
                             acc[l][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(*reinterpret_cast<const v4i *>(p + l * plane), fb, acc[l][i], 0, 0, 0);
                     }
                 }
-                // (up to kThinFew entries two digits at a time as integers)
-                auto fold = [&](auto few) {
+                // (two digits at a time as integers)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            double run;
-                            if constexpr (decltype(few)::value) {
-                                run = (double)(256 * acc[5][i][r] + acc[4][i][r]);
-                                run = __builtin_fma(run, 65536.0, (double)(256 * acc[3][i][r] + acc[2][i][r]));
-                                run = __builtin_fma(run, 65536.0, (double)(256 * acc[1][i][r] + acc[0][i][r]));
-                            } else {
-                                run = (double)acc[kThinDigits - 1][i][r];
-#pragma unroll
-                                for (int l = kThinDigits - 2; l >= 0; --l) run = __builtin_fma(run, 256.0, (double)acc[l][i][r]);
-                            }
-                            total[i][c][r] = __builtin_fma(run, unit, total[i][c][r]);
-                        }
-                };
-                if (16 * units <= kThinFew) fold(std::true_type{});
-                else fold(std::false_type{});
+                    for (int r = 0; r < 4; ++r) {
+                        double run = (double)(256 * acc[5][i][r] + acc[4][i][r]);
+                        run = __builtin_fma(run, 65536.0, (double)(256 * acc[3][i][r] + acc[2][i][r]));
+                        run = __builtin_fma(run, 65536.0, (double)(256 * acc[1][i][r] + acc[0][i][r]));
+                        total[i][c][r] = __builtin_fma(run, unit, total[i][c][r]);
+                    }
             }
             largest = rest;
             if (largest > 0u) __syncthreads();      // the planes are written again
@@ -319,7 +307,7 @@ ThinPlan plan_thin(const ConvDxGrid &grid, int64_t B, int32_t C, int32_t N, int 
 // k-steps hide nothing (60 x 27 x 27 x 32 -> 20, 5 x 5  27 / 48).
 bool conv_dx_thin_serves(const ConvDxGrid *grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, int32_t stride)
 {
-    return stride == 1 && C <= 32 && N <= 32 && N % 4 == 0 && grids->Rc * grids->Sc >= 9 && grids->Rc * grids->Sc * ((N + 15) / 16) <= 25 && (int64_t)B * grids->Hc * grids->Wc >= 512 * 64 &&
+    return stride == 1 && C <= 32 && N <= 32 && N % 4 == 0 && grids->Rc * grids->Sc >= 9 && grids->Rc * grids->Sc * ((N + 15) / 16) <= kThinUnits && (int64_t)B * grids->Hc * grids->Wc >= 512 * 64 &&
            plan_thin(*grids, B, C, N, P, Q).lds > 0;
 }
 

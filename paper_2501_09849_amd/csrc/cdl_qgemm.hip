@@ -2228,7 +2228,7 @@ int launch_mfma_probe(int iters, int random_operands, int blocks, int *sink, hip
     return check_launch();
 }
 
-// forward workspace: [zero-padded operand copies when K % 16 != 0][with offsets: corrections per output column: int32 N][per output row: int32 M]
+// forward workspace: [when K % 16 != 0: room for operand copies with padded rows, which are made for K < 16][with offsets: corrections per output column: int32 N][per output row: int32 M]
 size_t qgemm_fwd_workspace_bytes(int32_t M, int32_t N, int32_t K, bool with_offsets)
 {
     size_t b = 0;

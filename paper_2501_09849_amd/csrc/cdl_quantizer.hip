@@ -1478,8 +1478,9 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
     // (every block makes the logarithms of all levels: blocks of one trip do not pay for those of large sets where the tensor streams.  us, loop / one
-    // trip: 24 M entries of 255 levels, two on each side 58.8 / 66.5, of 63 levels 56.4 / 56.7; 47 M 114 / 125 and 110 / 104; 6 M 20.8 / 19.9)
-    const bool one_trip = one_trip_serves(n, k) && (k.n_levels <= 64 || n < kStreamFrom);
+    // trip: 24 M entries of 255 levels, two on each side 58.8 / 66.5, of 63 levels 56.4 / 56.7; 47 M 114 / 125 and 110 / 104; 6 M 20.8 / 19.9.
+    // One level on each side leaves the loop no shorter: 255 levels, 24 M 56.7 / 55.3, 47 M 109 / 102)
+    const bool one_trip = one_trip_serves(n, k) && (k.n_levels <= 64 || n < kStreamFrom || band_template(k) == 1);
     const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
     const bool want_dtheta = dtheta != nullptr;
     const double alpha = (double)p.alpha, delta = (double)p.delta;

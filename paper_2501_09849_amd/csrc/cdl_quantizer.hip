@@ -118,142 +118,32 @@ void marginal_finalize_kernel(const unsigned long long *__restrict__ rows, int n
 // Forward kernel.  One thread handles four consecutive entries per trip of a grid-stride loop
 // (one 16-byte load, one 16-byte store of soft values, one 4-byte store of indices).
 //
-// MARG: the CPMF of every entry is added up in LDS, in fixed point: a probability p is added as p * 2^s rounded to an integer.
-// (LDS integer atomics run at ~10 lane updates per clock per CU on this chip, fp32 LDS atomics at a thirtieth of that;
-// integer sums are also independent of the order of the adds, so the result is reproducible.)  s comes from
-// kHistScaleBits: with at most kMaxHistTrips trips of the loop a cell never exceeds 2^31.  The block keeps 32 copies of the cells,
-// copy-minor, and lane l uses copy l mod 32: the copy is the LDS bank (pair of banks), so the lanes of one instruction never meet
-// in a bank except lane l with lane l + 32 (measured against 4 or 16 copies per wave, where different bins fall into the same bank:
-// -8 % on the whole forward kernel at 255 levels, -22 % on the pass that only builds the histogram).
-//
-// BINS: one 32-bit cell per level; kPad spare bins on each side take the zero weights of levels that do not exist.
-// PAIRS (unrolled bands whose cells fit kPairBytes: up to 97, 72, 48, 36 levels for W = 1 .. 4): per anchor level c the probabilities of
-// the levels c + j and c - j are the halves of one 64-bit cell, j = 1 .. W, and that of level c is what is missing to the number of
-// entries: W atomics an entry instead of 2 W + 1 (W = 2: 11 us of LDS time per 25.6 M entries instead of 16).  The kernel is bound by
-// the instructions it issues, and here the conversion to an integer costs none: p * 2^s + kHistMagic, a float in [2^23, 2^24), has the integer
-// in its low bits, and what the other bits add up to (kHistOne per entry) is taken off at the end.  The number of entries of a cell is read from
-// the low half of the outermost pair, whose probabilities are so small that their sum stays below 2^20 (outer_pair_is_small; sets of up to
-// five levels in the soft regime keep the bins), for W = 1 from a 32-bit cell that counts.
-// At the end the block adds the copies into 64-bit sums per level, and marginal_end adds these over all blocks.  (Grids that finish the PMF themselves
-// keep the bins, whose cells are fewer to clear and to add up: 74 K entries 8.3 against 9.2 us.)
-// us, forward pass with PMF and the launch that ends it, cold, before (bins, 74 instructions an entry) / so (53): 25.6 M entries of 31 levels 61 / 55,
-// 115.6 M of 16 levels 214 / 204 (bins with the shorter arithmetic: 50.3 M of 255 levels 100 / 92).
+// MARG: the CPMF of every entry is added into a histogram in LDS, in fixed point: a probability
+// p is added as the integer floor(p * 2^s + 1/2), so that a level's share is off by half a unit of 2^-s and the rounding of p at most, also where
+// all entries are equal.  (LDS integer atomics run at ~10 lane updates
+// per clock per CU on this chip, fp32 LDS atomics at a thirtieth of that; integer sums are also
+// independent of the order of the adds, so the result is reproducible.)  The block keeps 32 copies of
+// the histogram, bin-major and copy-minor, and lane l uses copy l mod 32: the copy is the LDS bank, so
+// the lanes of one instruction never meet in a bank except lane l with lane l + 32 (measured against
+// 4 or 16 copies per wave, where different bins fall into the same bank: -8 % on the whole forward
+// kernel at 255 levels, -22 % on the pass that only builds the histogram).  s comes from
+// kHistScaleBits: with at most kMaxHistTrips trips of the loop a cell never exceeds 2^31.
+// kPad spare bins on each side take the zero weights of levels that do not exist.  At the end
+// the block adds the copies into 64-bit sums, and marginal_end adds these over all blocks.
+// (Levels c + j and c - j as the halves of one 64-bit cell of level c, that of c from the number of entries: W atomics an entry instead of 2 W + 1, but more
+// cells to clear and to add up, and a share of the nearest level that takes the roundings of all others.  us with indices, bins / pairs:
+// 25.6 M entries of 31 levels, W = 2 41.0 / 40.4, of 63 41.8 / 44.1, W = 3 of 47 60.3 / 63.1; 2.5 M of 63 12.7 / 15.5, 1.5 M of 72 11.1 / 18.1.)
 // ------------------------------------------------------------------------------------------
 constexpr int kHistCopies = 32;
-constexpr float kHistMagic = 8388608.0f + 1048576.0f;
-constexpr unsigned int kHistOne = 0x4B100000u;      // the bits of kHistMagic
-constexpr int kPairBytes = 39 << 10;                // four blocks to a compute unit
-
-template <int W, bool PAIRS>
-struct HistCells {
-    unsigned int *bins;                // BINS, this lane's copy: [bin][copies]
-    unsigned long long *pairs;         // PAIRS, this lane's copy: [level][W][copies]
-    unsigned int *counts;              // PAIRS and W = 1, this lane's copy: [level][copies]
-    // level: as the cells' pointers count, which start at level 0 whether it is in the set or not
-    __device__ __forceinline__ void add(const Band<W> &b, int level, float inv)
-    {
-        constexpr int R = kHistCopies;
-        const float invs = inv * (float)(1u << kHistScaleBits);
-        if (PAIRS) {
-            unsigned long long *h = pairs + level * (W * R);
-#pragma unroll
-            for (int j = 1; j <= W; ++j) {
-                float up = fmaf(b.up[j - 1], invs, kHistMagic), dn = fmaf(b.dn[j - 1], invs, kHistMagic);
-                if (W != 2) { up = fmaxf(up, kHistMagic); dn = fmaxf(dn, kHistMagic); }      // (a NaN adds 0; the bands of W = 2 have none)
-                atomicAdd(h + (j - 1) * R, (unsigned long long)__float_as_uint(up) | ((unsigned long long)__float_as_uint(dn) << 32));
-            }
-            if (W == 1) atomicAdd(counts + level * R, 1u);
-        } else {
-            unsigned int *h = bins + (level + kPad - W) * R;   // bin of level c-W
-            atomicAdd(h + W * R, (unsigned int)fmaf(b.ctr, invs, 0.5f));
-#pragma unroll
-            for (int j = 1; j <= W; ++j) {
-                atomicAdd(h + (W + j) * R, (unsigned int)fmaf(b.up[j - 1], invs, 0.5f));
-                atomicAdd(h + (W - j) * R, (unsigned int)fmaf(b.dn[j - 1], invs, 0.5f));
-            }
-        }
-    }
-};
-
-// Bytes of a block's cells
-__host__ __device__ __forceinline__ int hist_bytes_of(int levels, int w, bool pairs)
-{
-    return pairs ? levels * (4 * (2 * w + (w == 1)) * kHistCopies + 8 * (2 * w + 1)) : (levels + 2 * kPad) * 4 * kHistCopies;
-}
-
-// The halves of a cell after n adds, both below 2^31
-__device__ __forceinline__ void pair_halves(unsigned long long cell, unsigned int n, unsigned int &low, unsigned int &high)
-{
-    const unsigned long long base = (unsigned long long)n * kHistOne;
-    low = (unsigned int)cell - (unsigned int)base;
-    high = (unsigned int)(cell >> 32) - (unsigned int)base - (unsigned int)((base + low) >> 32);
-}
-
-// n from the low half of a cell, where that half's sum is below 2^20: n * (kHistOne >> 20) modulo 2^12
-__device__ __forceinline__ unsigned int pair_count(unsigned long long cell)
-{
-    constexpr unsigned int kInverse = 1105u;
-    static_assert(((kHistOne >> 20) * kInverse & 4095u) == 1u, "inverse modulo 2^12");
-    return ((unsigned int)cell >> 20) * kInverse & 4095u;
-}
-
-// From the cells of pairs to the block's sum for each level (returned in thread i < n_levels): sixteen threads to a level take two copies each.
-// sums: [n_levels][2 W + 1].  The caller has synchronised the block after the last add.
-template <int W, int T>
-__device__ __forceinline__ unsigned long long pair_levels(const unsigned long long *cells, const unsigned int *counts, unsigned long long *sums, int n_levels)
-{
-    constexpr int R = kHistCopies, P = 2 * W + 1;
-    const int sub = threadIdx.x & 15;
-    for (int c0 = 0; c0 < n_levels; c0 += T / 16) {
-        const int c = c0 + ((int)threadIdx.x >> 4);
-        unsigned long long v[P];
-#pragma unroll
-        for (int i = 0; i < P; ++i) v[i] = 0ull;
-        if (c < n_levels) {
-#pragma unroll
-            for (int q = 0; q < R / 16; ++q) {
-                const unsigned long long *h = cells + (size_t)c * (W * R) + sub + 16 * q;
-                const unsigned int n = W == 1 ? counts[c * R + sub + 16 * q] : pair_count(h[(W - 1) * R]);
-                v[0] += n;
-#pragma unroll
-                for (int j = 1; j <= W; ++j) {
-                    unsigned int low, high;
-                    pair_halves(h[(j - 1) * R], n, low, high);
-                    v[2 * j - 1] += low;
-                    v[2 * j] += high;
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < P; ++i) {
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 16);
-        }
-        if (c < n_levels && sub == 0) {
-#pragma unroll
-            for (int i = 0; i < P; ++i) sums[c * P + i] = v[i];
-        }
-    }
-    __syncthreads();
-    unsigned long long own = 0ull;
-    const int k = threadIdx.x;
-    if (k < n_levels) {
-        own = sums[k * P] << kHistScaleBits;
-#pragma unroll
-        for (int j = 1; j <= W; ++j) {
-            own -= sums[k * P + 2 * j - 1] + sums[k * P + 2 * j];
-            if (k >= j) own += sums[(k - j) * P + 2 * j - 1];
-            if (k + j < n_levels) own += sums[(k + j) * P + 2 * j];
-        }
-    }
-    return own;
-}
 
 // Quantizes four entries: soft values, level indices, and (MARG) their CPMFs into the histogram.
-template <int W, bool IDX, bool MARG, bool PAIRS>
-__device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QConst &k, HistCells<W, PAIRS> &hist,
+// my_hist: this lane's copy of the bin of level 0, whether it is in the set or not
+template <int W, bool IDX, bool MARG>
+__device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QConst &k, unsigned int *my_hist,
                                          float (&sv)[4], int (&ci)[4])
 {
+    constexpr int R = kHistCopies;
+    constexpr float kScale = (float)(1u << kHistScaleBits);
     float cf[4];
     if (W > 0) anchor_levels<IDX>(th, k, cf);
 #pragma unroll
@@ -264,17 +154,25 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
             const float inv = fast_rcp(b.Z);
             sv[e] = fmaf(b.S1 * inv, k.delta, b.cf * k.delta);
             ci[e] = (int)b.cf;
-            if (MARG && e < cnt) hist.add(b, ci[e], inv);
+            if (MARG && e < cnt) {
+                unsigned int *h = my_hist + (ci[e] + kPad - W) * R;   // bin of level c-W
+                const float invs = inv * kScale;
+                atomicAdd(h + W * R, (unsigned int)fmaf(b.ctr, invs, 0.5f));
+#pragma unroll
+                for (int j = 1; j <= W; ++j) {
+                    atomicAdd(h + (W + j) * R, (unsigned int)fmaf(b.up[j - 1], invs, 0.5f));
+                    atomicAdd(h + (W - j) * R, (unsigned int)fmaf(b.dn[j - 1], invs, 0.5f));
+                }
+            }
         } else {
-            constexpr int R = kHistCopies;
             GenericSums g;
             generic_sums<IDX>(th[e], k, g);
             const float inv = fast_rcp(g.Z);
             sv[e] = fmaf(g.S1 * inv, k.delta, g.cf * k.delta);
             ci[e] = (int)g.cf;
             if (MARG && e < cnt) {
-                unsigned int *h = hist.bins + (ci[e] + kPad) * R;
-                const float two_u = 2.0f * g.u, invs = inv * (float)(1u << kHistScaleBits);
+                unsigned int *h = my_hist + (ci[e] + kPad) * R;
+                const float two_u = 2.0f * g.u, invs = inv * kScale;
                 for (int j = g.jlo; j <= g.jhi; ++j)
                     atomicAdd(h + j * R, (unsigned int)fmaf(generic_weight(j, two_u, k), invs, 0.5f));
             }
@@ -284,25 +182,18 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
 
 // U: vectors of four entries a thread takes per trip.  U > 1 (tensors of more than kOneTripEntries): with MARG the loads of a trip
 // are issued before the trip before it is computed and stored, without MARG there is one trip.
-template <int W, bool IDX, bool SOFT, bool MARG, bool FEW, int U, bool PAIRS>
+template <int W, bool IDX, bool SOFT, bool MARG, bool FEW, int U>
 __global__ __launch_bounds__(MARG ? kMargThreads : one_trip_threads(U))
 void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
                          int8_t *__restrict__ idx, float *__restrict__ soft,
                          MargFinish fin)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned int lds_hist[];  // MARG: hist_bytes_of(n_levels, W, PAIRS)
+    extern __shared__ __attribute__((aligned(16))) unsigned int lds_hist[];  // [n_levels + 2 kPad][copies] when MARG
     constexpr int R = kHistCopies;
     constexpr int T = MARG ? kMargThreads : one_trip_threads(U);
-    HistCells<W, PAIRS> hist;
-    unsigned long long *const pairs = reinterpret_cast<unsigned long long *>(lds_hist);
-    unsigned int *const counts = lds_hist + k.n_levels * (2 * W * R);
-    constexpr int kWords = 2 * W + (W == 1);      // of the cells of a level, PAIRS
+    unsigned int *my_hist = lds_hist + (int)(threadIdx.x & (R - 1)) - k.lo * R;
     if (MARG) {
-        const int copy = threadIdx.x & (R - 1);
-        hist.bins = lds_hist + copy - k.lo * R;
-        hist.pairs = pairs + copy - k.lo * (W * R);
-        hist.counts = counts + copy - k.lo * R;
-        const int cells = PAIRS ? k.n_levels * kWords * R : (k.n_levels + 2 * kPad) * R;
+        const int cells = (k.n_levels + 2 * kPad) * R;
         for (int i = 4 * threadIdx.x; i < cells; i += 4 * T) *reinterpret_cast<uint4 *>(lds_hist + i) = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
     }
@@ -313,7 +204,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
     with_constant(k.stream != 0, [&](auto streams) {
         auto vec = [&](const float4 &t, int64_t w) {
             const float th[4] = {t.x, t.y, t.z, t.w};
-            forward4<W, IDX, MARG, PAIRS>(th, 4, k, hist, sv, ci);
+            forward4<W, IDX, MARG>(th, 4, k, my_hist, sv, ci);
             if (SOFT) store_stream4(soft + 4 * w, sv[0], sv[1], sv[2], sv[3], streams.value);
             if (IDX) {
                 const uint32_t packed = pack_indices(ci[0], ci[1], ci[2], ci[3], k.idx_off);
@@ -355,7 +246,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
     if (cnt > 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         float th[4];
         for (int e = 0; e < 4; ++e) th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
-        forward4<W, IDX, MARG, PAIRS>(th, cnt, k, hist, sv, ci);
+        forward4<W, IDX, MARG>(th, cnt, k, my_hist, sv, ci);
         for (int e = 0; e < cnt; ++e) {
             if (SOFT) soft[(n4 << 2) + e] = sv[e];
             if (IDX) idx[(n4 << 2) + e] = (int8_t)(ci[e] - k.idx_off);
@@ -365,9 +256,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
     if (MARG) {
         __syncthreads();
         unsigned long long own = 0ull;
-        if (PAIRS) {
-            own = pair_levels<W, T>(pairs, counts, reinterpret_cast<unsigned long long *>(lds_hist + k.n_levels * (kWords * R)), k.n_levels);
-        } else if ((int)threadIdx.x < k.n_levels) {
+        if ((int)threadIdx.x < k.n_levels) {
             const unsigned int *row = lds_hist + ((int)threadIdx.x + kPad) * R;
 #pragma unroll
             for (int r = 0; r < R; ++r) own += row[(r + (int)threadIdx.x) & (R - 1)];   // rotated start: no bank conflicts
@@ -1087,26 +976,17 @@ int launch_scalar_end(const ScalarFinish &f, void *scalars, int grid, hipStream_
     return check_launch();
 }
 
-// Whether the sum of a cell's outermost probabilities stays below 2^20: of two neighbours at a midpoint each has half, so that the level W away
-// has at most e^(-kappa W (W - 1)) / 2, and a cell takes at most 2^10 + 3 entries.  Holds wherever W comes from kappa and not from the size of the set.
-bool outer_pair_is_small(double kappa, int w) { return exp(-kappa * w * (w - 1)) < 1.0 / 1100.0; }
-bool pairs_serve(double kappa, int levels, int w) { return w > 0 && hist_bytes_of(levels, w, true) <= kPairBytes && (w == 1 || outer_pair_is_small(kappa, w)); }
-
 template <int W>
 void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
-                  const float *theta, int64_t n, const QConst &k, double kappa, int8_t *idx, float *soft,
+                  const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
                   const MargFinish &fin)
 {
-#define CDL_FWD_P(I, S, M, U, P)                                                                          \
-    CDL_LAUNCH((I) ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)", s,                     \
-               (quantize_fwd_kernel<W, I, S, (M) != 0, (M) == 2, U, (P)>), dim3(grid), dim3((M) ? kMargThreads : one_trip_threads(U)), \
-               (M) ? hist_bytes_of(k.n_levels, W, P) : 0, theta, n, k, idx, soft, fin)
+    const size_t lds = (size_t)(k.n_levels + 2 * kPad) * kHistCopies * sizeof(unsigned int);
 #define CDL_FWD(I, S, M, U)                                                                               \
-    do {                                                                                                  \
-        if ((M) == 1 && pairs) CDL_FWD_P(I, S, M, U, W > 0 && (M) == 1);                                  \
-        else CDL_FWD_P(I, S, M, U, false);                                                                \
-    } while (0)
-    const bool few = hist_few(grid, k.n_levels), pairs = pairs_serve(kappa, k.n_levels, W);
+    CDL_LAUNCH((I) ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)", s,                     \
+               (quantize_fwd_kernel<W, I, S, (M) != 0, (M) == 2, U>), dim3(grid), dim3((M) ? kMargThreads : one_trip_threads(U)), \
+               (M) ? lds : 0, theta, n, k, idx, soft, fin)
+    const bool few = hist_few(grid, k.n_levels);
     constexpr int UM = W > 0 ? kHistVectors : 1, UN = W > 0 ? kOneTripVectors : 1;
     const bool large = n > kOneTripEntries;      // (without PMF: one_trip_serves)
     if (want_idx && want_soft && want_marg && few) CDL_FWD(true, true, 2, 1);
@@ -1122,7 +1002,6 @@ void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStre
     else if (few) CDL_FWD(false, false, 2, 1);
     else if (large) CDL_FWD(false, false, 1, UM);
     else CDL_FWD(false, false, 1, 1);
-#undef CDL_FWD_P
 #undef CDL_FWD
 }
 
@@ -1341,7 +1220,6 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
         fin.marg = marg;
         fin.entropy_bits = entropy_bits;
     }
-    const double kappa = (double)p.alpha * (double)p.delta * (double)p.delta;
     const bool uniform = uniform_half_width(p, k) != 0;
     const SoftPlan plan = want_marg && (soft_fwd_from_uniform(p, n) || !uniform) ? soft_plan(p, k, n, uniform) : SoftPlan{};
     if (plan.bins) return launch_soft_fwd(theta, n, p, k, plan, idx, soft, fin, ws, stream);
@@ -1357,11 +1235,11 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
         if (rcu != CDL_OK) return rcu;
     } else
     switch (band_template(k)) {
-        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
-        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
-        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
-        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
-        default: launch_fwd<0>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, kappa, idx, soft, fin); break;
+        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        default: launch_fwd<0>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
     }
     int rc = check_launch();
     if (rc == CDL_OK && fin.rows) {

@@ -1,5 +1,5 @@
-"""Quantizer kernels on tensors that are taken in one trip of all blocks, and the marginal PMF from cells of pairs of levels: remainders
-of a block, the largest sets that keep pairs and the first that do not for every band width, cells filled by equal entries."""
+"""Quantizer kernels on tensors that are taken in one trip of all blocks, and the marginal PMF: remainders of a block, small, middling and larger sets
+for every band width, bins filled by equal entries."""
 import numpy as np
 import pytest
 
@@ -45,7 +45,7 @@ def test_one_trip_remainders(oracle, n):
     gu.assert_close(dent[:n].cpu().numpy()[tail], (r_e["dtheta"] + g)[tail], "entropy gradient")
 
 
-# (kappa of band widths 1 .. 4; the last set that keeps pairs and the first that does not; sets of which every level is live)
+# (kappa of band widths 1 .. 4; sets of which every level is live)
 @pytest.mark.parametrize("n", [3001, 90_001, LINE + 5])
 @pytest.mark.parametrize("levels,kappa", [(2, 16.0), (97, 16.0), (98, 16.0), (72, 4.0), (73, 4.0), (48, 2.5), (49, 2.5), (36, 1.5), (37, 1.5), (72, 3.82), (3, 0.05), (5, 0.05), (5, 3.9)])
 def test_marginal_of_pairs(oracle, n, levels, kappa):
@@ -63,7 +63,7 @@ def test_marginal_of_pairs(oracle, n, levels, kappa):
     gu.assert_close([got[3]], [r_h], "entropy")
 
 
-# one cell of one copy takes everything its threads see: at a level, halfway between two (both halves), next to the ends and far outside
+# one bin of one copy takes everything its threads see: at a level, halfway between two, next to the ends and far outside
 @pytest.mark.parametrize("n", [4099, 16_777_215])
 @pytest.mark.parametrize("at", [0.0, 0.5, -0.5, 6.5, 7.0, -7.4, 40.0])
 @pytest.mark.parametrize("kappa", [3.82, 16.0, 2.5])

@@ -163,6 +163,9 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
                     atomicAdd(h + (W + j) * R, (unsigned int)fmaf(b.up[j - 1], invs, 0.5f));
                     atomicAdd(h + (W - j) * R, (unsigned int)fmaf(b.dn[j - 1], invs, 0.5f));
                 }
+                // (the pass that only builds the histogram: the atomics of an entry stay in front of the next one's arithmetic, else those of four
+                // go out in one burst.  us without / so: 25.6 M entries of 31 levels 39.1 / 36.9, 47 levels, three on each side 53.2 / 51.9)
+                if (!IDX && W <= 3) __builtin_amdgcn_sched_barrier(0);
             }
         } else {
             GenericSums g;
@@ -180,8 +183,8 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
     }
 }
 
-// U: vectors of four entries a thread takes per trip.  U > 1 (tensors of more than kOneTripEntries): with MARG the loads of a trip
-// are issued before the trip before it is computed and stored, without MARG there is one trip.
+// U: vectors of four entries a thread takes per trip.  U > 1: with MARG the loads of a trip (hist_ahead) are issued before the trip before it is
+// computed and stored, without MARG there is one trip.
 template <int W, bool IDX, bool SOFT, bool MARG, bool FEW, int U>
 __global__ __launch_bounds__(MARG ? kMargThreads : one_trip_threads(U))
 void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
@@ -908,24 +911,38 @@ int finishing_grid(int64_t blocks)
     return (int)((blocks + trips - 1) / trips);
 }
 
-// Grid of the histogram kernels.  Up to kOneTripEntries a trip a block; then trips of kHistVectors vectors a thread, the next trip's
-// loads issued before this trip's stores, on half the blocks that are resident and from kHistFullFrom on all of them (256 CUs hold four 512-thread
-// blocks each): a block clears its cells first and adds them up last, 2 - 3 us in which its waves load and store nothing.  No more than
-// kMaxHistTrips vectors a thread: beyond, a whole number of rounds of blocks (a last round that fills half of them cost 10-18 % on 50 M entries).
-// us, forward pass with PMF (and the launch that finishes it) on 512 / 1024 / 2048 blocks: 2.4 M entries of 255 levels 14.4 / 15.3 / 18.1,
-// 6.4 M of 15 levels 21.0 / 23.2 / 25.4, 12.8 M of 16 levels 28.8 / 31.1 / 32.1, 25.6 M of 31 levels 60.2 / 57.4 / 58.4.
+// Grid of the histogram kernels: half of grid_for, but never more than kMaxHistTrips trips per block, and - once
+// the chip is full - a whole number of rounds: 256 CUs hold four 512-thread blocks each (2048 threads; the
+// histogram of 256 levels takes 33 KB of the 160 KB of LDS), and a last round that fills half of them
+// cost 10-18 % on 50 M entries.
 constexpr int64_t kHistResident = 256 * 4;
 constexpr int64_t kHistFullFrom = 16ll << 20;
-constexpr int kHistVectors = 2;
 
-int64_t hist_grid_for(int64_t n)
+int64_t hist_grid_for(int64_t n, bool half)
 {
     const int64_t vecs = (n >> 2) + 1;
     const int64_t need = (vecs + (int64_t)kMargThreads * kMaxHistTrips - 1) / ((int64_t)kMargThreads * kMaxHistTrips);
-    if (n <= kOneTripEntries) return (grid_for(n) + 1) / 2;
-    const int64_t g = n < kHistFullFrom ? kHistResident / 2 : kHistResident;
+    const int64_t full = (grid_for(n) + 1) / 2, g = half && full > kHistResident / 2 ? kHistResident / 2 : full;
     return need > g ? (need + kHistResident - 1) / kHistResident * kHistResident : g;
 }
+
+// Where half of them are better: large sets in tensors that four blocks of a compute unit take in few trips, since every block clears its bins first and adds them up
+// last, 2 - 3 us in which it loads and stores nothing; and the kernel of 17 to 33 levels on a common centre, of which a compute unit holds two blocks.
+// us, index, soft value and PMF, on 1024 / 512 blocks: 2.36 M entries of 255 levels, two on each side 14.5 / 13.5, 5 M 18.5 / 18.4, 12.8 M 30.2 / 30.2 (without soft values
+// 27.0 / 26.3), of 200 levels 14.0 / 12.9, of 127 13.6 / 13.5, 12.8 M of 127 29.1 / 30.3, of 15 29.0 / 29.5; four on each side 9 M of 255 33.7 / 36.0; on a common
+// centre 2.5 M of 31 levels 32.9 / 30.2, 13 M of 7 60.8 / 70.4; the nearest five of 15 levels 16 M 61.3 / 69.6.
+bool hist_half(int64_t n, const QConst &k, int uniform_half)
+{
+    if (n <= kOneTripEntries || n >= kHistFullFrom) return false;
+    const int w = band_template(k);
+    return uniform_half == kUniMaxJH || ((w == 1 || w == 2) && k.n_levels >= 192);
+}
+
+// Whether a trip takes kHistVectors vectors a thread and their loads go ahead of the stores of the trip before: where soft values are stored as well and the arithmetic of
+// an entry is short.  us, index, soft value and PMF, a vector a trip / so: 25.6 M entries of 31 levels, two on each side 47.7 / 47.1, 50.3 M 81.1 / 79.2, 12.8 M 28.8 / 29.8;
+// index and PMF 25.6 M 39.6 / 40.6, 36 M 48.8 / 51.4; three on each side 25.6 M of 15 levels 61.5 / 65.8.
+constexpr int kHistVectors = 2;
+bool hist_ahead(int64_t n, const QConst &k) { return n >= kHistFullFrom && (band_template(k) == 1 || band_template(k) == 2); }
 
 // Whether the histogram kernel finishes the job itself: up to 256 blocks whose records one block can poll in a few
 // trips to memory (measured on quantizer forward + backward: 245 blocks of 15 levels 21.4 against 24.7 us, 49 blocks
@@ -935,11 +952,7 @@ bool hist_few(int64_t grid, int32_t n_levels) { return grid <= kFinishMaxBlocks 
 // workspace layout: [rows of the histogram kernel's blocks][records of the finishing blocks][scalar partials or records]
 // (or the table and the rows of moments of the soft regime)
 // (never less than a smaller tensor has: callers keep one workspace for several)
-size_t hist_row_bytes(int64_t n, int32_t n_levels)
-{
-    const int64_t g = hist_grid_for(n), rows = n > kOneTripEntries && g < kHistResident ? kHistResident : g;
-    return align_up((size_t)rows * (size_t)n_levels * sizeof(unsigned long long), 256);
-}
+size_t hist_row_bytes(int64_t n, int32_t n_levels) { return align_up((size_t)hist_grid_for(n, false) * (size_t)n_levels * sizeof(unsigned long long), 256); }
 size_t hist_bytes(int64_t n, int32_t n_levels)
 {
     const size_t rows = hist_row_bytes(n, n_levels);
@@ -977,7 +990,7 @@ int launch_scalar_end(const ScalarFinish &f, void *scalars, int grid, hipStream_
 }
 
 template <int W>
-void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s,
+void launch_fwd(bool want_idx, bool want_soft, bool want_marg, bool one_trip, int grid, hipStream_t s,
                   const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
                   const MargFinish &fin)
 {
@@ -987,20 +1000,18 @@ void launch_fwd(bool want_idx, bool want_soft, bool want_marg, int grid, hipStre
                (quantize_fwd_kernel<W, I, S, (M) != 0, (M) == 2, U>), dim3(grid), dim3((M) ? kMargThreads : one_trip_threads(U)), \
                (M) ? lds : 0, theta, n, k, idx, soft, fin)
     const bool few = hist_few(grid, k.n_levels);
-    constexpr int UM = W > 0 ? kHistVectors : 1, UN = W > 0 ? kOneTripVectors : 1;
-    const bool large = n > kOneTripEntries;      // (without PMF: one_trip_serves)
+    constexpr int UM = W == 1 || W == 2 ? kHistVectors : 1, UN = W > 0 ? kOneTripVectors : 1;
+    const bool ahead = hist_ahead(n, k);
     if (want_idx && want_soft && want_marg && few) CDL_FWD(true, true, 2, 1);
-    else if (want_idx && want_soft && want_marg && large) CDL_FWD(true, true, 1, UM);
+    else if (want_idx && want_soft && want_marg && ahead) CDL_FWD(true, true, 1, UM);
     else if (want_idx && want_soft && want_marg) CDL_FWD(true, true, 1, 1);
-    else if (want_idx && want_soft && large) CDL_FWD(true, true, 0, UN);
+    else if (want_idx && want_soft && one_trip) CDL_FWD(true, true, 0, UN);
     else if (want_idx && want_soft) CDL_FWD(true, true, 0, 1);
     else if (want_idx && want_marg && few) CDL_FWD(true, false, 2, 1);
-    else if (want_idx && want_marg && large) CDL_FWD(true, false, 1, UM);
     else if (want_idx && want_marg) CDL_FWD(true, false, 1, 1);
-    else if (want_idx && large) CDL_FWD(true, false, 0, UN);
+    else if (want_idx && one_trip) CDL_FWD(true, false, 0, UN);
     else if (want_idx) CDL_FWD(true, false, 0, 1);
     else if (few) CDL_FWD(false, false, 2, 1);
-    else if (large) CDL_FWD(false, false, 1, UM);
     else CDL_FWD(false, false, 1, 1);
 #undef CDL_FWD
 }
@@ -1206,7 +1217,7 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
     }
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    int64_t grid64 = want_marg ? hist_grid_for(n) : grid_for(n);
+    int64_t grid64 = want_marg ? hist_grid_for(n, hist_half(n, k, uniform_half_width(p, k))) : grid_for(n);
     if (want_marg && band_template(k) != 0 && n <= 4ll * kFinishMaxBlocks * kMargThreads * 4 && hist_few(finishing_grid(grid64), p.n_levels)) grid64 = finishing_grid(grid64);
     if (grid64 > 2147483647LL) return CDL_ERR_PARAM;
     const bool one_trip = !want_marg && one_trip_serves(n, k);
@@ -1235,11 +1246,11 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
         if (rcu != CDL_OK) return rcu;
     } else
     switch (band_template(k)) {
-        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
-        default: launch_fwd<0>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
+        default: launch_fwd<0>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
     }
     int rc = check_launch();
     if (rc == CDL_OK && fin.rows) {

@@ -47,7 +47,9 @@ namespace {
 // start in the order of the tensor.  us, as a loop of up to 2048 blocks / so (with the shorter arithmetic of cdl_quantizer_math.h), cold:
 // gradient (8 B read, 4 written an entry) 12.8 M entries 26.9 / 24.9, 25.6 M 51 / 47.5, 50.3 M 102 / 94, 115.6 M 238 / 221 (6.3 TB/s); index and
 // soft value without PMF (4 B read, 5 written) 12.8 M 22.4 / 20.1, 25.6 M 44 / 39, 50.3 M 83 / 70, 115.6 M 203 / 170 (6.1 TB/s).  Blocks of 256 x 2 vectors
-// against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.
+// against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.  Passes without scalar gradients go so from twice as many entries on: draws of 3 M entries of
+// 15 levels, one to four levels on each side 7.2 / 7.6, 7.7 / 7.9, 8.8 / 10.0, 10.7 / 11.4, index and soft value 7.3 / 7.7 (one), 7.5 / 7.9 (two); 8.3 M, one to four
+// 15.0 / 14.7, 17.1 / 14.9, 20.0 / 19.1, 24.8 / 23.0.
 constexpr int kOneTripThreads = 256, kOneTripVectors = 2;
 constexpr int one_trip_threads(int u) { return u > 1 ? kOneTripThreads : kQuantThreads; }
 constexpr int64_t kOneTripEntries = 4ll * kMaxQuantBlocks * kQuantThreads;
@@ -693,7 +695,7 @@ __device__ __forceinline__ int draw_one(float th, float u, const QConst &k)
 }
 
 template <int W, int U>
-__global__ __launch_bounds__(one_trip_threads(U))
+__global__ __launch_bounds__(one_trip_threads(U), W == 1 || W == 2 ? 8 : 1)      // (W = 2, 13 M entries: eight waves 20.3, six 21.0 us)
 void quantize_draw_kernel(const float *__restrict__ theta, const float *__restrict__ u, int64_t n, QConst k,
                           int8_t *__restrict__ idx)
 {
@@ -1220,7 +1222,7 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
     int64_t grid64 = want_marg ? hist_grid_for(n, hist_half(n, k, uniform_half_width(p, k))) : grid_for(n);
     if (want_marg && band_template(k) != 0 && n <= 4ll * kFinishMaxBlocks * kMargThreads * 4 && hist_few(finishing_grid(grid64), p.n_levels)) grid64 = finishing_grid(grid64);
     if (grid64 > 2147483647LL) return CDL_ERR_PARAM;
-    const bool one_trip = !want_marg && one_trip_serves(n, k);
+    const bool one_trip = !want_marg && n >= 2 * kOneTripEntries && one_trip_serves(n, k);
     int grid = one_trip ? (int)one_trip_grid(n) : (int)grid64;
     MargFinish fin{};
     if (want_marg) {
@@ -1310,7 +1312,7 @@ int launch_quantize_draw(const float *theta, const float *u, int64_t n, const cd
     if (n == 0) return CDL_OK;
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    const bool one_trip = one_trip_serves(n, k);
+    const bool one_trip = n >= 2 * kOneTripEntries && one_trip_serves(n, k);
     const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
 #define CDL_DRAW(WW) \
     do { \
@@ -1366,10 +1368,10 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     }
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    // (every block makes the logarithms of all levels: blocks of one trip do not pay for those of large sets where the tensor streams.  us, loop / one
-    // trip: 24 M entries of 255 levels, two on each side 58.8 / 66.5, of 63 levels 56.4 / 56.7; 47 M 114 / 125 and 110 / 104; 6 M 20.8 / 19.9.
-    // One level on each side leaves the loop no shorter: 255 levels, 24 M 56.7 / 55.3, 47 M 109 / 102)
-    const bool one_trip = one_trip_serves(n, k) && (k.n_levels <= 64 || n < kStreamFrom || band_template(k) == 1);
+    // (every block makes the logarithms of all levels: blocks of one trip do not pay for those of large sets where the tensor streams, unless one level on each
+    // side leaves the loop no shorter.  us, loop / one trip, two on each side: 9 M entries of 63 levels 26.2 / 25.5, of 128 26.2 / 28.9, of 255 26.8 / 28.4; 25.6 M of 96
+    // 61.5 / 57.1, of 128 61.3 / 58.6, of 180 61.3 / 60.7, of 255 61.1 / 62.6; 47 M of 128 110 / 106, of 255 110 / 110; three on each side 25.6 M of 255 72.9 / 78.2)
+    const bool one_trip = one_trip_serves(n, k) && (k.n_levels <= 64 || (k.n_levels <= 128 && n >= 2 * kStreamFrom) || n < kStreamFrom || band_template(k) == 1);
     const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
     const bool want_dtheta = dtheta != nullptr;
     const double alpha = (double)p.alpha, delta = (double)p.delta;

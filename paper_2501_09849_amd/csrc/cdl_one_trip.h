@@ -1,0 +1,26 @@
+// The launch of the quantizer passes that take a large tensor in one trip (not installed; compiles without HIP).
+#pragma once
+
+#include <stdint.h>
+
+namespace cdl {
+
+// A wave's loads and stores share one counter that goes down in the order of their issue: in a loop that loads, computes and stores, the
+// wait for a trip's loads is also a wait for the stores of the trip before it, which take microseconds to complete, and blocks that drift
+// apart spread the accesses in flight over the whole tensor.  Tensors of more than kOneTripEntries therefore go through in one trip:
+// a block of kOneTripThreads issues all its loads (kOneTripVectors of four entries a thread) before its first store, and blocks
+// start in the order of the tensor.  us, as a loop of up to 2048 blocks / so (with the shorter arithmetic of cdl_quantizer_math.h), cold:
+// gradient (8 B read, 4 written an entry) 12.8 M entries 26.9 / 24.9, 25.6 M 51 / 47.5, 50.3 M 102 / 94, 115.6 M 238 / 221 (6.3 TB/s); index and
+// soft value without PMF (4 B read, 5 written) 12.8 M 22.4 / 20.1, 25.6 M 44 / 39, 50.3 M 83 / 70, 115.6 M 203 / 170 (6.1 TB/s).  Blocks of 256 x 2 vectors
+// against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.  Passes without scalar gradients go so from twice as many entries on: draws of 3 M entries of
+// 15 levels, one to four levels on each side 7.2 / 7.6, 7.7 / 7.9, 8.8 / 10.0, 10.7 / 11.4, index and soft value 7.3 / 7.7 (one), 7.5 / 7.9 (two); 8.3 M, one to four
+// 15.0 / 14.7, 17.1 / 14.9, 20.0 / 19.1, 24.8 / 23.0.
+constexpr int kOneTripThreads = 256, kOneTripVectors = 2;
+
+// Blocks.  The last one has at most the rest of the vectors, and the entries beyond them.
+inline int64_t one_trip_grid(int64_t n) { return ((n >> 2) + (int64_t)kOneTripThreads * kOneTripVectors) / ((int64_t)kOneTripThreads * kOneTripVectors); }
+
+// Whether a launch can have as many: fewer than 2^32 threads (2^35 entries, 137 GB of fp32; larger tensors go through in a loop).
+inline bool one_trip_fits(int64_t n) { return one_trip_grid(n) * kOneTripThreads < (1ll << 32); }
+
+}  // namespace cdl

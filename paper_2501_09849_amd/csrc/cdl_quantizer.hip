@@ -26,6 +26,7 @@
 //   W = 3, 4: one exponential per level;  larger W (soft regime): a table (cdl_soft.hip), kernels on a common centre or a
 //          loop over the band.
 #include "cdl_internal.h"
+#include "cdl_one_trip.h"
 #include "cdl_finish.h"
 #include "cdl_marginal.h"
 #include "cdl_quantizer_math.h"
@@ -40,17 +41,6 @@ namespace cdl {
 
 namespace {
 
-// A wave's loads and stores share one counter that goes down in the order of their issue: in a loop that loads, computes and stores, the
-// wait for a trip's loads is also a wait for the stores of the trip before it, which take microseconds to complete, and blocks that drift
-// apart spread the accesses in flight over the whole tensor.  Tensors of more than kOneTripEntries therefore go through in one trip:
-// a block of kOneTripThreads issues all its loads (kOneTripVectors of four entries a thread) before its first store, and blocks
-// start in the order of the tensor.  us, as a loop of up to 2048 blocks / so (with the shorter arithmetic of cdl_quantizer_math.h), cold:
-// gradient (8 B read, 4 written an entry) 12.8 M entries 26.9 / 24.9, 25.6 M 51 / 47.5, 50.3 M 102 / 94, 115.6 M 238 / 221 (6.3 TB/s); index and
-// soft value without PMF (4 B read, 5 written) 12.8 M 22.4 / 20.1, 25.6 M 44 / 39, 50.3 M 83 / 70, 115.6 M 203 / 170 (6.1 TB/s).  Blocks of 256 x 2 vectors
-// against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.  Passes without scalar gradients go so from twice as many entries on: draws of 3 M entries of
-// 15 levels, one to four levels on each side 7.2 / 7.6, 7.7 / 7.9, 8.8 / 10.0, 10.7 / 11.4, index and soft value 7.3 / 7.7 (one), 7.5 / 7.9 (two); 8.3 M, one to four
-// 15.0 / 14.7, 17.1 / 14.9, 20.0 / 19.1, 24.8 / 23.0.
-constexpr int kOneTripThreads = 256, kOneTripVectors = 2;
 constexpr int one_trip_threads(int u) { return u > 1 ? kOneTripThreads : kQuantThreads; }
 constexpr int64_t kOneTripEntries = 4ll * kMaxQuantBlocks * kQuantThreads;
 
@@ -898,10 +888,8 @@ int grid_for(int64_t n)
     return (int)blocks;
 }
 
-// Blocks of the kernels that take a large tensor in one trip, and whether they serve: the unrolled bands (the loop over the
-// levels is bound by arithmetic).
-int64_t one_trip_grid(int64_t n) { return ((n >> 2) + (int64_t)kOneTripThreads * kOneTripVectors) / ((int64_t)kOneTripThreads * kOneTripVectors); }
-bool one_trip_serves(int64_t n, const QConst &k) { return n > kOneTripEntries && band_template(k) != 0 && one_trip_grid(n) <= 2147483647LL; }
+// Whether the kernels that take a large tensor in one trip serve: the unrolled bands (the loop over the levels is bound by arithmetic).
+bool one_trip_serves(int64_t n, const QConst &k) { return n > kOneTripEntries && band_template(k) != 0 && one_trip_fits(n); }
 
 // Up to four times as many blocks as can finish the job themselves: that many, of more trips each.  A second launch costs more
 // (forward + backward of 0.3 M entries, 15 levels: 13.8 -> 12.3 us, 255 levels 17.3 -> 14.1; 0.9 M, 15 levels 17.0 -> 16.1) - not in

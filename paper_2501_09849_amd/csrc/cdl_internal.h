@@ -125,7 +125,7 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
                      void *ws, hipStream_t stream);
 
 // The same product for problems with few output tiles (cdl_qgemm_small.hip): any K >= 16, no workspace.
-bool qgemm_small_serves(int32_t M, int32_t N, int32_t K);
+bool qgemm_small_serves(int32_t M, int32_t N, int32_t K, int32_t a_offset, int32_t b_offset);
 int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset,
                        int32_t b_offset, int32_t *acc, float *y, hipStream_t stream);
 

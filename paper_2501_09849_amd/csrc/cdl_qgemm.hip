@@ -2228,7 +2228,7 @@ int launch_mfma_probe(int iters, int random_operands, int blocks, int *sink, hip
     return check_launch();
 }
 
-// forward workspace: [when K % 16 != 0: room for operand copies with padded rows, which are made for K < 16][with offsets: corrections per output column: int32 N][per output row: int32 M]
+// forward workspace: [when K % 16 != 0: room for operand copies with padded rows; they are made for K < 16 alone, and the size that callers are told stays as it was][with offsets: corrections per output column: int32 N][per output row: int32 M]
 size_t qgemm_fwd_workspace_bytes(int32_t M, int32_t N, int32_t K, bool with_offsets)
 {
     size_t b = 0;
@@ -2256,7 +2256,7 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
         if (y) CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)M * N, 256, 4096)), dim3(256), 0, y, (int64_t)M * N);
         return check_launch();
     }
-    if (qgemm_small_serves(M, N, K))
+    if (qgemm_small_serves(M, N, K, a_offset, b_offset))
         return launch_qgemm_small(a_idx, b_idx, M, N, K, delta_a * delta_b, a_offset, b_offset, acc, y, stream);
     if (qgemm_thin_serves(N, K, b_offset)) return launch_qgemm_thin(a_idx, b_idx, M, N, K, delta_a * delta_b, a_offset, acc, y, stream);
     GemmArgs g{};

@@ -167,12 +167,16 @@ int launch_tiles(SmallArgs a, hipStream_t stream)
 //   16 x 3072 x 768     13.9 ->  3.3      384 x  320 x 1664   18.0 -> 5.3     10366 x 128 x  832  12.9 -> 9.2
 //   256 x 1000 x 512    10.0 ->  3.4     1988 x  225 x  752   11.9 -> 4.2      1024 x 1024 x 1024 14.1 -> 10.1
 //   512 x 512 x 4096    35.1 ->  9.6       85 x  747 x 2951   52.7 -> 15.4    20000 x  64 x  512   7.4 -> 8.0
-// i.e. up to about a thousand tiles of 32 x 32; twice as many where the others have to copy operands whose rows are not
-// aligned.  (Tiles of 64 x 64 or eight waves per tile: no better on these shapes but the 1024-cube, 8.4.)
-bool qgemm_small_serves(int32_t M, int32_t N, int32_t K)
+// i.e. up to about a thousand tiles of 32 x 32.  Rows that are not aligned, up to 768 entries long: twice as many, unless cdl_fwd_thin.hip serves and is the faster one
+// (up to 16 columns, or an offset).  us, here / the other kernels (an offset: their launch for the sums of the weights included): 2000 x 520 x 300 6.1 / 7.4 (9.4 / 12.0),
+// x 700 7.5 / 9.1, x 900 11.8 / 10.3, x 999 20.1 / 12.1; 300 x 6000 x 500 9.4 / 8.9 (14.1 / 14.5); 1500 x 1000 x 147 8.9 / 7.5; 1024 x 1500 x 3070 111 / 29;
+// 62000 x 16 x 147 9.4 / 6.2, 36000 x 32 x 300 6.7 / 7.1 (10.1 / 7.1).
+// (Tiles of 64 x 64 or eight waves per tile: no better on these shapes but the 1024-cube, 8.4.)
+bool qgemm_small_serves(int32_t M, int32_t N, int32_t K, int32_t a_offset, int32_t b_offset)
 {
     const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32);
-    return K >= 16 && tiles <= (K % 16 ? 2048 : 1024);
+    const bool thin = qgemm_thin_serves(N, K, b_offset) && (N <= 16 || a_offset != 0);
+    return K >= 16 && tiles <= (K % 16 && K <= 768 && !thin ? 2048 : 1024);
 }
 
 int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset,

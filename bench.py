@@ -147,7 +147,7 @@ def kernel_model(wl, name, occurrence):
     if name == "quantize_bwd_kernel":
         n = (nX if occurrence == 0 else nW) if wl.has_gemm else nW
         return "hbm", 12.0 * n, n
-    if name.startswith("qgemm_kernel") or name.startswith("limb_gemm_kernel"):
+    if name.startswith("qgemm_kernel") or name == "fwd_thin_kernel" or name.startswith("limb_gemm_kernel"):
         return "mfma", 2.0 * wl.M * wl.N * wl.K, 0
     if name == "absmax_kernel":
         return "hbm", 4.0 * wl.M * wl.N, 0          # reads g once
@@ -885,7 +885,7 @@ def main():
     if q_us and not st.fused:
         out["quantizer_in_step"] = {"gelem_per_s": n_total / (q_us * 1e-6) / 1e9, "hbm_frac": 21.0 * n_total / (q_us * 1e-6) / 1e9 / HBM_PEAK_GBS,
                                     "us": q_us, "cache": "cold by size"}
-    gf = [r for r in kernels if r["kernel"] == "qgemm_kernel(fwd)"]
+    gf = [r for r in kernels if r["kernel"] in ("qgemm_kernel(fwd)", "fwd_thin_kernel")]
     if gf:
         out["index_gemm_fwd_TOPS"] = gf[0]["algorithmic_TOPS"]
         out["index_gemm_fwd_frac_of_int8_peak"] = gf[0]["frac"]

@@ -333,7 +333,7 @@ int launch_conv_dx_thin(const float *g, const int8_t *w_idx, const ConvDxGrid &g
     do {                                                                                                                                        \
         const hipError_t e_ = hipFuncSetAttribute((const void *)conv_dx_thin_kernel<TN, NU>, hipFuncAttributeMaxDynamicSharedMemorySize, kThinLds); \
         if (e_ != hipSuccess) return hip_failed(e_);                                                                                            \
-        CDL_LAUNCH("conv_dx_direct_kernel", stream, (conv_dx_thin_kernel<TN, NU>), dim3((unsigned)(8 * a.share)), dim3(kThinPixels), plan.lds, a);   \
+        CDL_LAUNCH("conv_dx_thin_kernel", stream, (conv_dx_thin_kernel<TN, NU>), dim3((unsigned)(8 * a.share)), dim3(kThinPixels), plan.lds, a);   \
     } while (0)
     if (C <= 16) { if (N <= 16) CDL_THIN(1, 1); else CDL_THIN(1, 2); }
     else { if (N <= 16) CDL_THIN(2, 1); else CDL_THIN(2, 2); }

@@ -154,7 +154,7 @@ int launch_thin(ThinFwdArgs a, bool conv, hipStream_t stream)
     a.vec = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.acc) | reinterpret_cast<uintptr_t>(a.y)) & 15) == 0;
     a.share = ((a.M + kThinFwdRows - 1) / kThinFwdRows + 7) / 8;
     const dim3 grid((unsigned)(8 * a.share)), block(64 * kThinFwdWaves);
-    const char *name = conv ? "qconv_kernel(fwd)" : "qgemm_kernel(fwd)";
+    const char *name = conv ? "fwd_thin_kernel(windows)" : "fwd_thin_kernel";
     if (conv && a.N <= 16) CDL_LAUNCH(name, stream, (fwd_thin_kernel<true, 1>), grid, block, 0, a);
     else if (conv) CDL_LAUNCH(name, stream, (fwd_thin_kernel<true, 2>), grid, block, 0, a);
     else if (a.N <= 16) CDL_LAUNCH(name, stream, (fwd_thin_kernel<false, 1>), grid, block, 0, a);

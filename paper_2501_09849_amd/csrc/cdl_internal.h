@@ -131,10 +131,10 @@ int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int3
 
 // The same, and the forward product of a convolution, with few output columns (cdl_fwd_thin.hip).
 struct ConvWindows;
-bool qgemm_thin_serves(int32_t N, int32_t K, int32_t b_offset);
+bool qgemm_thin_serves(int32_t M, int32_t N, int32_t K, int32_t a_offset, int32_t b_offset);
 int launch_qgemm_thin(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset, int32_t *acc, float *y,
                       hipStream_t stream);
-bool qconv_thin_serves(int64_t M, int32_t N, int32_t K);
+bool qconv_thin_serves(int64_t M, int32_t N, int32_t K, int32_t x_offset);
 int launch_qconv_thin(const int8_t *x_idx, const int8_t *w_idx, const ConvWindows &w, int32_t N, float scale, int32_t x_offset, int32_t *acc, float *y,
                       hipStream_t stream);
 

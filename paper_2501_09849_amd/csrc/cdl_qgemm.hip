@@ -2258,7 +2258,7 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
     }
     if (qgemm_small_serves(M, N, K, a_offset, b_offset))
         return launch_qgemm_small(a_idx, b_idx, M, N, K, delta_a * delta_b, a_offset, b_offset, acc, y, stream);
-    if (qgemm_thin_serves(N, K, b_offset)) return launch_qgemm_thin(a_idx, b_idx, M, N, K, delta_a * delta_b, a_offset, acc, y, stream);
+    if (qgemm_thin_serves(M, N, K, a_offset, b_offset)) return launch_qgemm_thin(a_idx, b_idx, M, N, K, delta_a * delta_b, a_offset, acc, y, stream);
     GemmArgs g{};
     g.A = a_idx; g.B = b_idx; g.lda = K; g.ldb = K;
     g.rowsA = M; g.rowsB = N; g.Kc = K;
@@ -2503,7 +2503,7 @@ int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_
     a.acc_out = acc; a.y_out = y;
     a.scale = delta_x * delta_w;
     if ((int64_t)a.M * N == 0) return CDL_OK;
-    if (qconv_thin_serves(a.M, N, a.Kc))
+    if (qconv_thin_serves(a.M, N, a.Kc, x_offset))
         return launch_qconv_thin(x_idx, w_idx, ConvWindows{B, H, W, C, R, S, stride, pad, a.P, a.Q}, N, a.scale, x_offset, acc, y, stream);
     if (x_offset != 0) {
         int8_t *page = reinterpret_cast<int8_t *>(ws);

@@ -167,16 +167,18 @@ int launch_tiles(SmallArgs a, hipStream_t stream)
 //   16 x 3072 x 768     13.9 ->  3.3      384 x  320 x 1664   18.0 -> 5.3     10366 x 128 x  832  12.9 -> 9.2
 //   256 x 1000 x 512    10.0 ->  3.4     1988 x  225 x  752   11.9 -> 4.2      1024 x 1024 x 1024 14.1 -> 10.1
 //   512 x 512 x 4096    35.1 ->  9.6       85 x  747 x 2951   52.7 -> 15.4    20000 x  64 x  512   7.4 -> 8.0
-// i.e. up to about a thousand tiles of 32 x 32.  Rows that are not aligned, up to 768 entries long: twice as many, unless cdl_fwd_thin.hip serves and is the faster one
-// (up to 16 columns, or an offset).  us, here / the other kernels (an offset: their launch for the sums of the weights included): 2000 x 520 x 300 6.1 / 7.4 (9.4 / 12.0),
-// x 700 7.5 / 9.1, x 900 11.8 / 10.3, x 999 20.1 / 12.1; 300 x 6000 x 500 9.4 / 8.9 (14.1 / 14.5); 1500 x 1000 x 147 8.9 / 7.5; 1024 x 1500 x 3070 111 / 29;
-// 62000 x 16 x 147 9.4 / 6.2, 36000 x 32 x 300 6.7 / 7.1 (10.1 / 7.1).
-// (Tiles of 64 x 64 or eight waves per tile: no better on these shapes but the 1024-cube, 8.4.)
+// i.e. up to about a thousand tiles of 32 x 32.  A quarter to half as many again where rows start at multiples of four bytes (of one or two, a lane's 16 bytes take
+// far longer) or are short, and are no multiples of 16 (the others' tiles are faster on those), and twice as many where an offset costs the others a launch for the sums of the weights.  us, here / there:
+// 2000 x 520 x 300 6.3 / 7.5, x 1500 11.6 / 12.9, x 301 10.7 / 8.2, x 999 19.9 / 12.1, x 99 5.9 / 6.7; 1024 x 1500 x 700 8.8 / 9.8, x 3020 31 / 26, x 3021 81 / 30; 300 x 6000 x 300
+// 8.5 / 8.2, with an offset 12.6 / 13.6, x 700 12.6 / 10.6 and 17.7 / 16.4; 36001 x 26 x 200 5.4 / 6.4.  (Tiles of 64 x 64 or eight waves per tile: no better on these shapes but the 1024-cube, 8.4.)
 bool qgemm_small_serves(int32_t M, int32_t N, int32_t K, int32_t a_offset, int32_t b_offset)
 {
     const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32);
-    const bool thin = qgemm_thin_serves(N, K, b_offset) && (N <= 16 || a_offset != 0);
-    return K >= 16 && tiles <= (K % 16 && K <= 768 && !thin ? 2048 : 1024);
+    if (K < 16 || tiles > 2048) return false;
+    if (tiles <= 1024) return true;
+    const bool offset = a_offset != 0 || b_offset != 0;
+    if (K % 16 == 0 || (K > 128 && K % 4 != 0) || (N <= 32 && (N <= 16 || offset))) return false;
+    return tiles <= (N <= 32 || K > 2048 ? 1280 : 1536) || (offset && K <= 512);
 }
 
 int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset,

@@ -22,8 +22,10 @@ def _i8(*shape):
     return torch.randint(-7, 8, shape, device="cuda", dtype=torch.int32).to(torch.int8)
 
 
-@pytest.mark.parametrize("M,N,K,offsets,thin", [(40_000, 16, 144, (0, 0), True), (40_000, 17, 1024, (0, 0), True), (50_007, 16, 147, (0, 0), True), (36_001, 32, 50, (128, 0), True),
-                                                (40_000, 16, 144, (0, 128), False), (40_000, 17, 1040, (0, 0), False), (40_000, 33, 144, (0, 0), False), (1000, 16, 144, (0, 0), False)])
+@pytest.mark.parametrize("M,N,K,offsets,thin", [(40_000, 16, 144, (0, 0), True), (131_072, 20, 768, (0, 0), True), (70_000, 20, 448, (0, 0), True), (50_007, 16, 147, (0, 0), True), (36_001, 32, 50, (128, 0), True),
+                                                (65_536, 16, 1040, (0, 0), True), (40_000, 22, 144, (128, 0), True), (40_000, 16, 144, (0, 128), False), (70_000, 20, 464, (0, 0), False),
+                                                (40_000, 22, 144, (0, 0), False), (65_537, 16, 1040, (0, 0), False), (40_000, 16, 301, (0, 0), False), (40_000, 33, 144, (0, 0), False),
+                                                (1000, 16, 144, (0, 0), False)])
 def test_forward_product(M, N, K, offsets, thin):
     import paper_2501_09849_amd as cdl
     torch = gu.torch_mod()
@@ -34,7 +36,7 @@ def test_forward_product(M, N, K, offsets, thin):
 
 
 # B, H, W, C, N, R, stride; the forward product and the activation gradient of the same layer
-@pytest.mark.parametrize("case,forward,gradient", [((40, 32, 32, 16, 16, 3, 1), True, True), ((60, 25, 24, 32, 16, 5, 1), False, True), ((16, 32, 32, 16, 16, 3, 1), True, False),
+@pytest.mark.parametrize("case,forward,gradient", [((40, 32, 32, 16, 16, 3, 1), True, True), ((60, 25, 24, 32, 16, 5, 1), False, True), ((16, 32, 32, 16, 16, 3, 1), True, False), ((32, 32, 32, 16, 32, 3, 1), False, True), ((33, 32, 32, 32, 32, 3, 1), True, True),
                                                    ((64, 28, 28, 32, 32, 3, 2), False, False), ((40, 32, 32, 16, 36, 3, 1), False, False), ((90, 14, 14, 48, 4, 1, 1), True, False)], ids=str)
 def test_convolution(case, forward, gradient):
     import paper_2501_09849_amd as cdl

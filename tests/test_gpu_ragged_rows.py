@@ -53,9 +53,9 @@ def test_both_gradients_of_an_unsigned_layer(M, N, K):
         assert bool(((got.double() - ref).abs() <= 9e-7 + 2.0 ** -23 * ref.abs()).all())
 
 
-# more tiles of 32 x 32 than a thousand: contractions on both sides of the longest that small tiles keep, few columns with and without an offset
+# more tiles of 32 x 32 than a thousand: short and long rows, at multiples of four bytes and not, few columns with and without an offset
 @pytest.mark.parametrize("M,N", [(2003, 517), (270, 5000), (36_001, 31), (50_007, 16)])
-@pytest.mark.parametrize("K", [17, 147, 767, 769])
+@pytest.mark.parametrize("K", [17, 129, 147, 516, 769])
 @pytest.mark.parametrize("offsets", [(0, 0), (128, 0), (0, 128)])
 def test_forward_of_middling_products(M, N, K, offsets):
     test_forward(M, N, K, offsets)

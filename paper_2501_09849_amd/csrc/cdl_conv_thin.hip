@@ -298,17 +298,46 @@ ThinPlan plan_thin(const ConvDxGrid &grid, int64_t B, int32_t C, int32_t N, int 
 
 }  // namespace
 
-// Where this kernel serves.  us of the call, before (in double gathered from memory, on digits or limbs) / so, entries N(0, 1), and in brackets entries
-// times 2^(2 N(0, 1)), of which a range has some below 2^-22 of its largest:
-//   128 x 32 x 32 x 16 -> 16, 3 x 3  24.5 / 12.4 (24.6 / 15.3)     128 x 32 x 32 x 32 -> 16  37.9 / 16.6 (38.2 / 22.6)     32 x 32 x 32 x 16 -> 16  9.3 / 8.4
-//   128 x 28 x 28 x 32 -> 32         60.5 / 31.1 (78.8 / 33.9)     64 x 56 x 56 x 32 -> 32   103 / 67 (135 / 86)          100 x 24 x 24 x 28 -> 16, 5 x 5  28 / 19
+// Pixels from which this kernel is the faster one; 0: from no number on.  It makes digits of 16 or 32 output channels and forms 16 or 32 input channels whatever there are, and the digits
+// are for all taps.  us of the call, before (in double gathered from memory, on digits or limbs) / so, entries N(0, 1), and in brackets entries times 2^(2 N(0, 1)), of which a range has
+// some below 2^-22 of its largest, so that it takes more digits or double; 3 x 3 if not said:
+//   128 x 32 x 32 x 16 -> 16   24.5 / 12.4 (24.6 / 15.3)     128 x 32 x 32 x 32 -> 16  37.9 / 16.6 (38.2 / 22.6)     32 x 32 x 32 x 16 -> 16  9.3 / 8.4
+//   128 x 28 x 28 x 32 -> 32   60.5 / 31.1 (78.8 / 33.9)     64 x 56 x 56 x 32 -> 32   103 / 67 (135 / 86)           100 x 24 x 24 x 28 -> 16, 5 x 5  28 / 19
+// and so / before on 40 x 32 x 32 | 100 x 28 x 28 | 150 x 32 x 32 | 64 x 56 x 56 pixels, where * is what the rule leaves to the other paths:
+//   16 -> 4    1.08* 1.01* 0.93* 1.05* (1.4 1.3 1.1 1.2)     32 -> 4    1.7* 1.1* 1.5* 1.3* (2.4 1.5 1.8 1.5)
+//   16 -> 8    1.12* 0.79 0.72 0.84 (1.3 1.07 0.85 0.96)     32 -> 8    1.33* 0.96* 1.13* 0.97* (1.9 1.18 1.39 1.17)
+//   16 -> 12   0.97* 0.68 0.58 0.66 (1.13 0.87 0.69 0.80)    32 -> 12   1.06* 0.69 0.89 0.75 (1.5 0.95 1.1 0.93)
+//   16 -> 16   0.93 0.60 0.46 0.52 (0.96 0.71 0.56 0.66)     32 -> 16   0.89* 0.56 0.79 0.67 (1.28 0.77 0.90 0.84)
+//   16 -> 20   1.03* 0.80 0.74 0.79 (1.5 1.05 0.81 1.03)     32 -> 20   1.04* 0.98* 0.95* 1.12* (1.6 1.10 1.13 1.45)
+//   16 -> 24   1.01* 0.76 0.61 0.71 (1.26 0.94 0.75 0.92)    32 -> 24   1.4* 0.83 0.77 1.00 (1.4 0.97 1.03 1.36)
+//   16 -> 28   0.85* 0.68 0.54 0.63 (1.24 0.83 0.72 0.82)    32 -> 28   0.84* 0.69 0.68 0.90 (1.3 0.87 0.94 1.28)
+//   16 -> 32   0.74 0.50 0.44 0.46 (0.90 0.66 0.55 0.62)     32 -> 32   0.85 0.83 0.69 0.87 (0.89 0.75 0.70 0.91)
+//   16 -> 4, 5 x 5  1.13* 0.90* 0.79* 1.0* (1.6 1.2 0.9 1.2) 32 -> 4, 5 x 5   1.46* 0.92* 1.20* 1.12* (2.1 1.3 1.5 1.35)
+//   16 -> 8, 5 x 5  0.80 0.65 0.53 0.66 (1.11 0.81 0.62 0.82) 32 -> 8, 5 x 5   0.95* 0.70 0.76 0.75 (1.4 0.85 0.96 0.88)
+//   16 -> 12, 5 x 5 0.62 0.54 0.53 0.19 (0.87 0.62 0.56 0.22) 32 -> 12, 5 x 5  0.70 1.08* 1.16* 0.39 (0.86 1.10 1.24 0.46)
+//   16 -> 16, 5 x 5 0.48 0.41 0.47 0.17 (0.69 0.54 0.55 0.22) 32 -> 16, 5 x 5  0.91* 0.77* 1.0* 0.33 (1.32 1.06 1.22 0.46)
+// (the starred ones of the last two rows on the right run on limbs of a patch in LDS; where a patch for 128 pixels does not fit there, as for rows of 56, that path's tile has 64
+// pixels and 128 channels, three quarters of them for nothing).
 // Few taps do not pay for the digits (256 x 14 x 14 x 16, 1 x 1  8.3 / 11.6), classes of stride 2 make them four times (64 x 28 x 28 x 16 -> 16  8.3 / 13.7), fewer pixels
 // are faster where the waves of a block share a contraction (16 x 32 x 32 x 16 -> 16  6.5), and longer contractions leave a compute unit one block whose
 // k-steps hide nothing (60 x 27 x 27 x 32 -> 20, 5 x 5  27 / 48).
-bool conv_dx_thin_serves(const ConvDxGrid *grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, int32_t stride)
+static int64_t thin_from(int32_t C, int32_t N, int taps)
 {
-    return stride == 1 && C <= 32 && N <= 32 && N % 4 == 0 && grids->Rc * grids->Sc >= 9 && grids->Rc * grids->Sc * ((N + 15) / 16) <= kThinUnits && (int64_t)B * grids->Hc * grids->Wc >= 512 * 64 &&
-           plan_thin(*grids, B, C, N, P, Q).lds > 0;
+    const int64_t few = 32768, more = 65536;
+    if (taps >= 16) return N < 8 ? 0 : N < 12 && C > 16 ? more : few;
+    if (C <= 16) return N % 16 == 0 ? few : N < 8 ? 0 : more;
+    return N == 32 ? few : N < 12 || N == 20 ? 0 : more;
+}
+
+bool conv_dx_thin_serves(const ConvDxGrid *grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N, int32_t R, int32_t S, int32_t P, int32_t Q, int32_t stride)
+{
+    const int taps = grids->Rc * grids->Sc;
+    if (stride != 1 || C > 32 || N > 32 || N % 4 != 0 || taps < 9 || taps * ((N + 15) / 16) > kThinUnits) return false;
+    const int64_t from = thin_from(C, N, taps);
+    if (from == 0 || (int64_t)B * grids->Hc * grids->Wc < from || plan_thin(*grids, B, C, N, P, Q).lds == 0) return false;
+    if (taps < 16 || C <= 16 || N < 12 || conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride)) return true;
+    const PatchPlan other = plan_patch(grids, 1, B, P, Q, C, 32);
+    return !other.served || other.wn > 1;
 }
 
 int launch_conv_dx_thin(const float *g, const int8_t *w_idx, const ConvDxGrid &grid, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, float delta_w,

@@ -168,7 +168,7 @@ int launch_limb_rows(const float *g, const int8_t *frag, int64_t tile_bytes, int
                      hipStream_t stream);
 
 // The same for few channels on both sides (cdl_conv_thin.hip); grids: of stride 1, one.
-bool conv_dx_thin_serves(const ConvDxGrid *grids, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, int32_t stride);
+bool conv_dx_thin_serves(const ConvDxGrid *grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N, int32_t R, int32_t S, int32_t P, int32_t Q, int32_t stride);
 int launch_conv_dx_thin(const float *g, const int8_t *w_idx, const ConvDxGrid &grid, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, float delta_w,
                         float *d_x_hat, hipStream_t stream);
 

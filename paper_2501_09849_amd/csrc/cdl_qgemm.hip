@@ -2429,7 +2429,7 @@ int launch_qconv_bwd_activations(const float *g, const int8_t *w_idx, int32_t B,
     if (zero_first)
         CDL_LAUNCH("zero_f32_kernel", stream, zero_f32_kernel, dim3(blocks_for((int64_t)B * H * W * C, 256, 4096)), dim3(256), 0, d_x_hat, (int64_t)B * H * W * C);
     if (n_cls == 0) return check_launch();
-    if (conv_dx_thin_serves(grids, B, C, N, P, Q, stride)) return launch_conv_dx_thin(g, w_idx, grids[0], B, C, N, P, Q, delta_w, d_x_hat, stream);
+    if (conv_dx_thin_serves(grids, B, H, W, C, N, R, S, P, Q, stride)) return launch_conv_dx_thin(g, w_idx, grids[0], B, C, N, P, Q, delta_w, d_x_hat, stream);
     if (conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride))
         return launch_conv_dx_direct(g, w_idx, grids, n_cls, B, H, W, C, N, R, S, P, Q, stride, delta_w, d_x_hat, stream);
     if (conv_dx_is_linear(R, S, stride))      // (the padding is smaller than the kernel: none)

@@ -726,8 +726,9 @@ void quantize_draw_kernel(const float *__restrict__ theta, const float *__restri
 //     dH/dalpha =  (delta^2 / n)       sum_e (C2 - 2 r C1)
 // The table of l_k sits in LDS with kPad zeros on both sides.  dtheta = g_in + scale * dH/dtheta.
 // ------------------------------------------------------------------------------------------
+// (bands: registers for eight waves.  Without the scalar sums the compiler takes up to 127 for three and four levels on each side, and four waves: 25 M entries 85.7, so 76.3 us)
 template <int W, bool DTHETA, bool SCALARS, bool ADD, int U>
-__global__ __launch_bounds__(one_trip_threads(U), W == 1 || W == 2 ? 8 : 1)
+__global__ __launch_bounds__(one_trip_threads(U), W > 0 ? 8 : 1)
 void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict__ marg, const float *__restrict__ g_in,
                         int64_t n, QConst k, float dtheta_mul /* scale * (-2 alpha delta / n) */,
                         float *__restrict__ dtheta, ScalarFinish fin)
@@ -1356,10 +1357,11 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     }
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    // (every block makes the logarithms of all levels: blocks of one trip do not pay for those of large sets where the tensor streams, unless one level on each
-    // side leaves the loop no shorter.  us, loop / one trip, two on each side: 9 M entries of 63 levels 26.2 / 25.5, of 128 26.2 / 28.9, of 255 26.8 / 28.4; 25.6 M of 96
-    // 61.5 / 57.1, of 128 61.3 / 58.6, of 180 61.3 / 60.7, of 255 61.1 / 62.6; 47 M of 128 110 / 106, of 255 110 / 110; three on each side 25.6 M of 255 72.9 / 78.2)
-    const bool one_trip = one_trip_serves(n, k) && (k.n_levels <= 64 || (k.n_levels <= 128 && n >= 2 * kStreamFrom) || n < kStreamFrom || band_template(k) == 1);
+    // (every block makes the logarithms of all levels: with the scalar gradients, whose sums then take a second launch, blocks of one trip do not pay for those of large sets where
+    // the tensor streams, unless one level on each side leaves the loop no shorter.  us, loop / one trip, two on each side: 9 M entries of 63 levels 26.2 / 25.5, of 128
+    // 26.2 / 28.9, of 255 26.8 / 28.4; 25.6 M of 96 61.5 / 57.1, of 128 61.3 / 58.6, of 180 61.3 / 60.7, of 255 61.1 / 62.6; 47 M of 128 110 / 106, of 255 110 / 110; three on each
+    // side 25.6 M of 255 72.9 / 78.2.  Without them, added to a gradient, 255 levels, two on each side: 25 M 57.7 / 50.2, 50 M 115.6 / 97.3, three 74.6 / 63.1, 141 / 127)
+    const bool one_trip = one_trip_serves(n, k) && (!want_scalars || k.n_levels <= 64 || (k.n_levels <= 128 && n >= 2 * kStreamFrom) || n < kStreamFrom || band_template(k) == 1);
     const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
     const bool want_dtheta = dtheta != nullptr;
     const double alpha = (double)p.alpha, delta = (double)p.delta;

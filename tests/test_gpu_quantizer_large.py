@@ -45,6 +45,29 @@ def test_one_trip_remainders(oracle, n):
     gu.assert_close(dent[:n].cpu().numpy()[tail], (r_e["dtheta"] + g)[tail], "entropy gradient")
 
 
+# the gradient of the entropy without the scalar ones, large sets: one trip as well; entries at both ends of the tensor and of blocks
+@pytest.mark.parametrize("kappa", [16.0, 4.0, 2.5, 1.5])
+@pytest.mark.parametrize("add", [False, True])
+def test_entropy_gradient_alone(oracle, kappa, add):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    n, lo, levels, delta = 4 * LINE + 2051, -127, 255, 0.02
+    alpha = kappa / delta ** 2
+    theta = torch.randn(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    g = 0.5 * theta if add else None
+    marg = np.random.default_rng(1).random(levels) + 0.1
+    marg = (marg / marg.sum()).astype(np.float32)
+    out, ws = torch.full((n + 1,), 7.0, device="cuda"), gu.workspace(cdl.quantize_workspace_bytes(n, levels))
+    cdl.cdl_entropy_bwd(theta, gu.dev(marg), n, lo, levels, delta, alpha, 0.1 * n, g, out, None, None, ws)
+    torch.cuda.synchronize()
+    assert float(out[n]) == 7.0
+    at = np.r_[0:4100, n // 2 // 2048 * 2048 - 50:n // 2 // 2048 * 2048 + 50, n - 5000:n]
+    th, got = theta.cpu().numpy()[at], out[:n].cpu().numpy()[at]
+    # (an entry's gradient has a factor scale / n, and nothing else of the other entries)
+    want = oracle.entropy_bwd(th, marg.astype(np.float64), lo, levels, delta, alpha, scale=0.1 * at.size)["dtheta"]
+    gu.assert_close(got, want + 0.5 * th if add else want, "entropy gradient")
+
+
 # (kappa of band widths 1 .. 4; sets of which every level is live)
 @pytest.mark.parametrize("n", [3001, 90_001, LINE + 5])
 @pytest.mark.parametrize("levels,kappa", [(2, 16.0), (97, 16.0), (98, 16.0), (72, 4.0), (73, 4.0), (48, 2.5), (49, 2.5), (36, 1.5), (37, 1.5), (72, 3.82), (3, 0.05), (5, 0.05), (5, 3.9)])

@@ -4,9 +4,11 @@
 // 7.8 us for the launch that adds up its sixteen histograms, and 3 - 4 us of host time), so where a grid has few blocks the block with
 // the highest number waits for the others and finishes the job itself (6.3 us in all).  The sums of the two scalar gradients of grids of more
 // blocks go in two steps: the last block of every group of consecutive blocks adds up its group's, the last of the grid those of the
-// groups (backward pass of 2.4 M entries 11.9 -> 10.2 us, of 6.4 M 20.6 -> 19.4; histograms so: 2.4 M entries of 255 levels 14 -> 22).  Tensors
-// that stream past the caches keep the second launch: there the records wait behind the stores of the tensor (25.6 M entries 56.0 us with
-// a second launch, 56.6 in two steps, 18.9 M 41.2 / 43.8).
+// groups (backward pass of 2.4 M entries 11.9 -> 10.2 us, of 6.4 M 20.6 -> 19.4; histograms so: 2.4 M entries of 255 levels 14 -> 22).  One-trip grids
+// of tensors that stream past the caches (more than 2048 blocks, 2^23 entries and more) keep the second launch: there the records of a block wait behind
+// its stores of the tensor (25.6 M entries 56.0 us with a second launch, 56.6 in two steps, 18.9 M 41.2 / 43.8).  Grids of up to 2048 blocks that loop
+// finish in the kernel at any size: few blocks, and the pass is bound by arithmetic (9 M entries, 7 levels on a common centre 34.5 us so, 35.5 in two
+// launches; 31 levels 36.2 / 37.6; gradient of the entropy, 47 M entries of 255 levels 109.6 / 112.5).
 //
 // What bounds the hand-over is the number of trips to memory, one after the other, between blocks on different XCDs,
 // about 0.7 us each.  A flag behind the data would cost four (data out and acknowledged, flag out, flag in, data in).
@@ -17,8 +19,14 @@
 //
 // The records live in the caller's workspace, whose contents are arbitrary: the tag is a 64-bit number that no other
 // launch of the process uses, and the reader spoils the check word of every record it has taken, so that a captured
-// launch can be replayed with the tag it was captured with.  Every wait ends: a block only ever waits for blocks with
-// lower numbers, and those wait for nobody.
+// launch can be replayed with the tag it was captured with.
+//
+// Every wait ends.  Only the last block of each group of 256 and the last of the grid wait: a group's last for the others of its group, which wait for
+// nobody, the grid's last for those and for the groups' last ones, so all for blocks of lower numbers.  Grids with records have at most 4097 blocks (2^23
+// entries in one trip), more than are resident, but of them at most 17 wait, and an XCD holds a block on each of its 32 compute units at least: the others
+// finish beside them and make room for all that have not started.  With more launches at a time than that leaves room for, it rests on an XCD
+// starting a launch's blocks in order of their numbers: the waiting ones with a number of 255 and so on lie on one XCD, where the blocks that
+// they wait for have then started, and the other XCDs hold at most one that waits of a launch.
 #pragma once
 
 #include "cdl_internal.h"

@@ -9,10 +9,10 @@ namespace cdl {
 // wait for a trip's loads is also a wait for the stores of the trip before it, which take microseconds to complete, and blocks that drift
 // apart spread the accesses in flight over the whole tensor.  Tensors of more than kOneTripEntries therefore go through in one trip:
 // a block of kOneTripThreads issues all its loads (kOneTripVectors of four entries a thread) before its first store, and blocks
-// start in the order of the tensor.  us, as a loop of up to 2048 blocks / so (with the shorter arithmetic of cdl_quantizer_math.h), cold:
-// gradient (8 B read, 4 written an entry) 12.8 M entries 26.9 / 24.9, 25.6 M 51 / 47.5, 50.3 M 102 / 94, 115.6 M 238 / 221 (6.3 TB/s); index and
-// soft value without PMF (4 B read, 5 written) 12.8 M 22.4 / 20.1, 25.6 M 44 / 39, 50.3 M 83 / 70, 115.6 M 203 / 170 (6.1 TB/s).  Blocks of 256 x 2 vectors
-// against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.  Passes without scalar gradients go so from twice as many entries on: draws of 3 M entries of
+// start in the order of the tensor.  us, as a loop of up to 2048 blocks / so (with the shorter arithmetic of cdl_quantizer_math.h), 31 levels, two on each side, from a
+// cold cache: gradient without scalars (8 B read, 4 written an entry) 12.8 M entries 28.1 / 26.0, 25.6 M 52.6 / 49.3, 50.3 M 102 / 97, 115.6 M 239 / 224 (6.2 TB/s); with
+// them 36.6 / 32.3, 62.7 / 56.4, 112 / 104, 256 / 235; index and soft value without PMF (4 B read, 5 written) 25.2 / 21.7, 43.4 / 37.8, 83.8 / 72.3,
+// 198 / 167 (6.2 TB/s).  Blocks of 256 x 2 vectors against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.  Draws and forward passes go so from twice as many entries on: draws of 3 M entries of
 // 15 levels, one to four levels on each side 7.2 / 7.6, 7.7 / 7.9, 8.8 / 10.0, 10.7 / 11.4, index and soft value 7.3 / 7.7 (one), 7.5 / 7.9 (two); 8.3 M, one to four
 // 15.0 / 14.7, 17.1 / 14.9, 20.0 / 19.1, 24.8 / 23.0.
 constexpr int kOneTripThreads = 256, kOneTripVectors = 2;

@@ -22,6 +22,7 @@ namespace {
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kThinWaves = 4, kThinPixels = 64 * kThinWaves, kThinDigits = 6;
+constexpr int kThinKeep = 6, kThinKept = kThinKeep * kThinPixels / 4;      // quads of channels that a thread keeps in registers, pixels of up to 16 channels that so are kept
 constexpr int kThinLds = 160 << 10;      // (two blocks share a compute unit where they fit)
 constexpr int kThinUnits = 25;           // most units of 16 contraction entries
 static_assert(257ll * 128 * 128 * 16 * kThinUnits < (1ll << 31), "a digit sum, times 256 and another added, fits an int32");
@@ -76,7 +77,7 @@ void conv_dx_thin_kernel(ThinArgs a)
     }
     const float *const src = a.g + (int64_t)lo * N;
     const int quads = count * NQ;      // of four channels; those beyond N are zeros
-    constexpr int kKeep = 6;
+    constexpr int kKeep = kThinKeep;
     float4 kept[kKeep];
     const bool keeps = NU == 1 && quads <= kKeep * T;      // g is read once (32 channels: never so few)
     auto load = [&](int base, float4 (&v)[kKeep]) {
@@ -300,44 +301,51 @@ ThinPlan plan_thin(const ConvDxGrid &grid, int64_t B, int32_t C, int32_t N, int 
 
 // Pixels from which this kernel is the faster one; 0: from no number on.  It makes digits of 16 or 32 output channels and forms 16 or 32 input channels whatever there are, and the digits
 // are for all taps.  us of the call, before (in double gathered from memory, on digits or limbs) / so, entries N(0, 1), and in brackets entries times 2^(2 N(0, 1)), of which a range has
-// some below 2^-22 of its largest, so that it takes more digits or double; 3 x 3 if not said:
+// some below 2^-22 of its largest, so that its digits are made twice; 3 x 3 if not said:
 //   128 x 32 x 32 x 16 -> 16   24.5 / 12.4 (24.6 / 15.3)     128 x 32 x 32 x 32 -> 16  37.9 / 16.6 (38.2 / 22.6)     32 x 32 x 32 x 16 -> 16  9.3 / 8.4
-//   128 x 28 x 28 x 32 -> 32   60.5 / 31.1 (78.8 / 33.9)     64 x 56 x 56 x 32 -> 32   103 / 67 (135 / 86)           100 x 24 x 24 x 28 -> 16, 5 x 5  28 / 19
-// and so / before on 40 x 32 x 32 | 100 x 28 x 28 | 150 x 32 x 32 | 64 x 56 x 56 pixels, where * is what the rule leaves to the other paths:
-//   16 -> 4    1.08* 1.01* 0.93* 1.05* (1.4 1.3 1.1 1.2)     32 -> 4    1.7* 1.1* 1.5* 1.3* (2.4 1.5 1.8 1.5)
-//   16 -> 8    1.12* 0.79 0.72 0.84 (1.3 1.07 0.85 0.96)     32 -> 8    1.33* 0.96* 1.13* 0.97* (1.9 1.18 1.39 1.17)
-//   16 -> 12   0.97* 0.68 0.58 0.66 (1.13 0.87 0.69 0.80)    32 -> 12   1.06* 0.69 0.89 0.75 (1.5 0.95 1.1 0.93)
-//   16 -> 16   0.93 0.60 0.46 0.52 (0.96 0.71 0.56 0.66)     32 -> 16   0.89* 0.56 0.79 0.67 (1.28 0.77 0.90 0.84)
-//   16 -> 20   1.03* 0.80 0.74 0.79 (1.5 1.05 0.81 1.03)     32 -> 20   1.04* 0.98* 0.95* 1.12* (1.6 1.10 1.13 1.45)
-//   16 -> 24   1.01* 0.76 0.61 0.71 (1.26 0.94 0.75 0.92)    32 -> 24   1.4* 0.83 0.77 1.00 (1.4 0.97 1.03 1.36)
-//   16 -> 28   0.85* 0.68 0.54 0.63 (1.24 0.83 0.72 0.82)    32 -> 28   0.84* 0.69 0.68 0.90 (1.3 0.87 0.94 1.28)
-//   16 -> 32   0.74 0.50 0.44 0.46 (0.90 0.66 0.55 0.62)     32 -> 32   0.85 0.83 0.69 0.87 (0.89 0.75 0.70 0.91)
-//   16 -> 4, 5 x 5  1.13* 0.90* 0.79* 1.0* (1.6 1.2 0.9 1.2) 32 -> 4, 5 x 5   1.46* 0.92* 1.20* 1.12* (2.1 1.3 1.5 1.35)
-//   16 -> 8, 5 x 5  0.80 0.65 0.53 0.66 (1.11 0.81 0.62 0.82) 32 -> 8, 5 x 5   0.95* 0.70 0.76 0.75 (1.4 0.85 0.96 0.88)
-//   16 -> 12, 5 x 5 0.62 0.54 0.53 0.19 (0.87 0.62 0.56 0.22) 32 -> 12, 5 x 5  0.70 1.08* 1.16* 0.39 (0.86 1.10 1.24 0.46)
-//   16 -> 16, 5 x 5 0.48 0.41 0.47 0.17 (0.69 0.54 0.55 0.22) 32 -> 16, 5 x 5  0.91* 0.77* 1.0* 0.33 (1.32 1.06 1.22 0.46)
-// (the starred ones of the last two rows on the right run on limbs of a patch in LDS; where a patch for 128 pixels does not fit there, as for rows of 56, that path's tile has 64
-// pixels and 128 channels, three quarters of them for nothing).
-// Few taps do not pay for the digits (256 x 14 x 14 x 16, 1 x 1  8.3 / 11.6), classes of stride 2 make them four times (64 x 28 x 28 x 16 -> 16  8.3 / 13.7), fewer pixels
+//   128 x 28 x 28 x 32 -> 32   60.5 / 31.1 (78.8 / 33.9)     100 x 24 x 24 x 28 -> 16, 5 x 5  28 / 19
+// and so / before, images of 28 x 28 | 56 x 56 | 96 x 96, 80 K pixels, then 200 K, where * is what the rule leaves to the other paths:
+//   16 -> 4    1.0* 1.0* 1.6* (1.3 1.4 1.8)      1.0* 1.1* 1.3* (1.1 1.2 1.6)           32 -> 4    1.1* 1.1* 1.3* (1.5 1.5 1.7)     1.4* 1.4* 2.0* (1.5 1.5 2.2)
+//   16 -> 8    0.86 0.81 1.0* (1.03 1.08 1.4)    0.79 0.81 0.98* (0.92 0.97 1.25)       32 -> 8    0.86* 0.87* 1.3* (1.2 1.2 1.4)   0.97* 0.98* 1.5* (1.15 1.2 1.7)
+//   16 -> 12   0.73 0.75 0.82* (0.86 0.90 1.2)   0.64 0.66 0.80 (0.77 0.78 1.06)        32 -> 12   0.69 0.79 0.79* (0.96 0.96 1.1)  0.81 0.85 1.1* (0.93 0.93 1.4)
+//   16 -> 16   0.55 0.52 0.69 (0.70 0.73 0.89)   0.50 0.51 0.59 (0.62 0.63 0.78)        32 -> 16   0.54 0.54 0.76 (0.77 0.77 0.86)  0.64 0.60 0.81 (0.78 0.83 1.1)
+//   16 -> 20   0.77 0.82 1.3* (1.03 1.07 1.7)    0.73 0.79 1.2* (0.95 1.01 1.7)         32 -> 20   0.81 1.1* 1.2* (1.09 1.4 1.5)    0.78 1.1* 1.5* (1.08 1.5 2.0)
+//   16 -> 24   0.71 0.73 1.2* (0.92 0.96 1.6)    0.68 0.70 1.1* (0.88 0.92 1.5)         32 -> 24   0.62 0.97* 1.0* (0.97 1.4 1.3)   0.74 1.0* 1.3* (0.96 1.3 1.7)
+//   16 -> 28   0.63 0.70 1.2* (0.82 0.86 1.5)    0.60 0.67 0.98* (0.79 0.83 1.3)        32 -> 28   0.74 0.86* 0.92* (0.87 1.3 1.3)  0.67 0.90* 1.2* (0.87 1.2 1.5)
+//   16 -> 32   0.54 0.51 0.79* (0.65 0.67 1.2)   0.45 0.46 0.68 (0.61 0.63 0.94)        32 -> 32   0.72 1.2* 1.0* (0.74 1.2 1.25)   0.55 0.89 0.93 (0.65 0.93 0.96)
+//   and 5 x 5:
+//   16 -> 4    0.89* 1.0* 1.7* (1.1 1.4 2.1)     0.87* 1.0* 1.5* (1.0 1.2 1.8)          32 -> 4    0.89* 1.0* 1.7* (1.3 1.5 2.2)    1.0* 1.1* 1.8* (1.2 1.4 2.4)
+//   16 -> 8    0.64 0.69 1.1* (0.81 0.98 1.4)    0.57 0.67 0.91* (0.68 0.82 1.3)        32 -> 8    0.58 0.77 1.1* (0.84 0.95 1.4)   0.65 0.71 1.2* (0.78 0.91 1.7)
+//   16 -> 12   0.47 0.52 0.87* (0.61 0.74 1.1)   0.44 0.19 0.78* (0.49 0.23 1.06)       32 -> 12   0.91* 0.42 1.5* (1.1 0.58 1.7)   0.92* 0.37 1.6* (1.1 0.50 2.0)
+//   16 -> 16   0.42 0.21 0.61 (0.55 0.28 0.77)   0.43 0.19 0.80 (0.50 0.22 0.96)        32 -> 16   0.89* 0.54 1.3* (1.1 0.54 1.5)   0.96* 0.37 1.5* (1.1 0.46 1.9)
+// With fewer pixels (40 K): 16 -> 12 0.97 (1.13), 16 -> 8 1.1 (1.3), 32 -> 16 0.89 (1.28), 32 -> 28 0.84 (1.3), but 16 -> 16 0.7 - 0.9 (0.96), 32 -> 32 0.6 - 0.85 (0.88).  Few taps do not
+// pay for the digits (256 x 14 x 14 x 16, 1 x 1  8.3 / 11.6), classes of stride 2 make them four times (64 x 28 x 28 x 16 -> 16  8.3 / 13.7), fewer pixels
 // are faster where the waves of a block share a contraction (16 x 32 x 32 x 16 -> 16  6.5), and longer contractions leave a compute unit one block whose
 // k-steps hide nothing (60 x 27 x 27 x 32 -> 20, 5 x 5  27 / 48).
-static int64_t thin_from(int32_t C, int32_t N, int taps)
+static int64_t thin_from(int32_t C, int32_t N, int taps, const ThinPlan &plan)
 {
-    const int64_t few = 32768, more = 65536;
-    if (taps >= 16) return N < 8 ? 0 : N < 12 && C > 16 ? more : few;
-    if (C <= 16) return N % 16 == 0 ? few : N < 8 ? 0 : more;
-    return N == 32 ? few : N < 12 || N == 20 ? 0 : more;
+    const int64_t few = 32768, more = 65536, many = 131072;
+    // (a patch: two blocks share a compute unit; its range of g is kept in registers, px_max being two more than an aligned run of whole rows reads)
+    const bool two = plan.lds <= kThinLds / 2, kept = plan.px_max - 2 <= kThinKept;
+    if (taps >= 16) return N < 8 || !(two || (C <= 16 && N == 16)) ? 0 : N < 12 && C > 16 ? more : few;
+    if (N < 8 || (C > 16 && N < 12)) return 0;
+    if (N > 16) return two ? (N == 32 ? few : more) : N == 32 ? many : 0;
+    if (N == 16) return C <= 16 ? few : more;
+    return kept ? more : C <= 16 && N == 12 ? many : 0;
 }
 
 bool conv_dx_thin_serves(const ConvDxGrid *grids, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N, int32_t R, int32_t S, int32_t P, int32_t Q, int32_t stride)
 {
     const int taps = grids->Rc * grids->Sc;
     if (stride != 1 || C > 32 || N > 32 || N % 4 != 0 || taps < 9 || taps * ((N + 15) / 16) > kThinUnits) return false;
-    const int64_t from = thin_from(C, N, taps);
-    if (from == 0 || (int64_t)B * grids->Hc * grids->Wc < from || plan_thin(*grids, B, C, N, P, Q).lds == 0) return false;
+    const ThinPlan plan = plan_thin(*grids, B, C, N, P, Q);
+    const int64_t from = plan.lds > 0 ? thin_from(C, N, taps, plan) : 0;
+    if (from == 0 || (int64_t)B * grids->Hc * grids->Wc < from) return false;
+    // (many taps of more than 16 input channels: limbs of a patch of 128 pixels in LDS have them for less, and so have digits made beforehand for wider images; a patch of fewer
+    // pixels has a tile of 128 and more channels, most of them for nothing)
     if (taps < 16 || C <= 16 || N < 12 || conv_dx_direct_serves((int64_t)B * H * W, N, C, R, S, stride)) return true;
     const PatchPlan other = plan_patch(grids, 1, B, P, Q, C, 32);
-    return !other.served || other.wn > 1;
+    return other.served && other.wn > 1;
 }
 
 int launch_conv_dx_thin(const float *g, const int8_t *w_idx, const ConvDxGrid &grid, int32_t B, int32_t C, int32_t N, int32_t P, int32_t Q, float delta_w,

@@ -14,7 +14,7 @@ CASES = [(40, 32, 32, 16, 16, 3, 1), (700, 7, 7, 16, 4, 3, 1), (33, 32, 32, 32, 
          (33, 32, 33, 20, 8, 5, 1), (12, 56, 56, 16, 68, 3, 1), (130, 17, 19, 4, 16, 1, 1), (64, 28, 28, 16, 16, 3, 2), (150, 15, 17, 16, 24, 5, 2),
          (129, 16, 16, 32, 36, 3, 2), (40, 30, 31, 8, 4, 1, 2), (33, 32, 32, 16, 88, 3, 1),
          (1400, 7, 8, 4, 28, 3, 1), (80, 30, 31, 28, 28, 3, 1), (150, 30, 31, 12, 8, 3, 1), (140, 31, 33, 16, 20, 3, 1), (70, 31, 33, 8, 24, 3, 1), (70, 31, 33, 20, 12, 3, 1),
-         (70, 32, 33, 20, 8, 5, 1), (36, 31, 33, 20, 12, 5, 1)]
+         (30, 71, 73, 12, 12, 3, 1), (70, 32, 33, 20, 8, 5, 1), (36, 31, 33, 20, 12, 5, 1)]
 
 
 def _reference(G, w, H, W, C, R, stride):

@@ -38,7 +38,8 @@ def test_forward_product(M, N, K, offsets, thin):
 # B, H, W, C, N, R, stride; the forward product and the activation gradient of the same layer
 @pytest.mark.parametrize("case,forward,gradient", [((40, 32, 32, 16, 16, 3, 1), True, True), ((60, 25, 24, 32, 16, 5, 1), False, True), ((16, 32, 32, 16, 16, 3, 1), True, False), ((32, 32, 32, 16, 32, 3, 1), False, True), ((33, 32, 32, 32, 32, 3, 1), True, True),
                                                    ((64, 28, 28, 32, 32, 3, 2), False, False), ((40, 32, 32, 16, 36, 3, 1), False, False), ((64, 32, 32, 32, 16, 3, 1), True, True), ((63, 32, 32, 32, 16, 3, 1), True, False), ((130, 32, 32, 16, 8, 3, 1), True, True),
-                                                   ((130, 32, 32, 32, 8, 3, 1), True, False), ((130, 32, 32, 16, 4, 3, 1), True, False), ((66, 32, 32, 16, 24, 3, 1), True, True), ((130, 32, 32, 32, 20, 3, 1), True, False),
+                                                   ((130, 32, 32, 32, 8, 3, 1), True, False), ((130, 32, 32, 16, 4, 3, 1), True, False), ((66, 32, 32, 16, 24, 3, 1), True, True), ((130, 32, 32, 32, 20, 3, 1), True, True), ((16, 72, 72, 32, 20, 3, 1), True, False), ((30, 72, 72, 16, 12, 3, 1), True, True), ((25, 72, 72, 16, 12, 3, 1), True, False),
+                                                   ((20, 72, 72, 16, 32, 3, 1), True, False), ((26, 72, 72, 16, 32, 3, 1), True, True),
                                                    ((80, 32, 32, 32, 16, 5, 1), False, False), ((26, 56, 56, 32, 16, 5, 1), False, True), ((36, 31, 33, 32, 12, 5, 1), False, True), ((90, 14, 14, 48, 4, 1, 1), True, False)], ids=str)
 def test_convolution(case, forward, gradient):
     import paper_2501_09849_amd as cdl

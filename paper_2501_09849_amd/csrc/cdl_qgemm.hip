@@ -1804,7 +1804,8 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float *__restrict__ g
 // rows from 64 on 8 words further: the 32 lanes of a read (8 groups of 16 rows, 4 columns) then lie in different banks.
 // Limited by memory: 50176 windows of 2304 entries 65 -> 28 us (4.6 TB/s), a matrix of that size 70 -> 44.
 // ALIGNED: the rows are, cols % 16 == 0.  Otherwise they are read in the same 16-byte loads from where they start (cdl_rows.h; 24773 x 2646 byte by
-// byte 84 us, so 46).
+// byte 84 us, so 46), and a chunk that they end in is shifted into place on its way to LDS, when all loads of a tile are under way (89744 x 200 in loads of 4 bytes 18.0 us, shifted
+// behind its own load 21.4, so 16.6; x 150 byte by byte 27.3, 19.6, 16.1).
 // CONV: src is not a matrix but the activations of a convolutional layer, [B][H][W][C] with C a multiple of 16, and
 // "src[r][c]" is entry c = (tap row, tap column, channel) of the window of output pixel r = (b, p, q) - the matrix of
 // input windows, which is never stored the right way round: only its transpose is written, as the product that
@@ -1852,6 +1853,8 @@ __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int blo
         tap_s = tap - tap_r * geom.S;
         tap_off = (tap_r * geom.W + tap_s) * geom.C + (cc - tap * geom.C);
     }
+    // (a chunk that the rows end in is read from their last 16 bytes: this many lie before it)
+    const int over = !ALIGNED && !CONV && cols >= 16 && c < cols ? max(c + 16 - cols, 0) : 0;
     uint4 v[4];
     auto load = [&](int rt) {
 #pragma unroll
@@ -1874,10 +1877,10 @@ __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int blo
                 if (ALIGNED) {
                     if (c < cols) v[j] = *reinterpret_cast<const uint4 *>(p + c);
                 } else if (cols >= 16) {
-                    cdl_v4i w = {0, 0, 0, 0};
-                    if (c + 16 <= cols) w = load_any16(p + c);
-                    else if (c < cols) w = tail_chunk(p, c, cols);
-                    v[j] = uint4{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
+                    if (c < cols) {
+                        const cdl_v4i w = load_any16(p + min(c, cols - 16));
+                        v[j] = uint4{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
+                    }
                 } else if (c == 0) {
                     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -1895,6 +1898,12 @@ __device__ __forceinline__ void transpose_tiles(const TransposeJob &job, int blo
     const int rg = tid & 7, cg = tid >> 3;      // rows 16 rg .. + 15, columns 4 cg .. + 3
     if (t0 < t_end) load(t0);
     for (int rt = t0; rt < t_end; ++rt) {
+        if (!ALIGNED && over > 0)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const cdl_v4i w = without_first(cdl_v4i{(int)v[j].x, (int)v[j].y, (int)v[j].z, (int)v[j].w}, over);
+                v[j] = uint4{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
+            }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             uint32_t *d = tile + at(lrow + 32 * j, 4 * (tid & 7));

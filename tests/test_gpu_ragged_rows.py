@@ -59,3 +59,9 @@ def test_both_gradients_of_an_unsigned_layer(M, N, K):
 @pytest.mark.parametrize("offsets", [(0, 0), (128, 0), (0, 128)])
 def test_forward_of_middling_products(M, N, K, offsets):
     test_forward(M, N, K, offsets)
+
+
+# (transposed in tiles of 128 columns: rows that end at every place of a chunk, in the first tile and behind it)
+@pytest.mark.parametrize("K", [112 + i for i in range(1, 16)] + [144 + i for i in range(1, 16, 2)])
+def test_both_gradients_of_rows_that_end_anywhere(K):
+    test_both_gradients_of_an_unsigned_layer(90_001, 72, K)

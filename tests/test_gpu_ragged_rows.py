@@ -65,3 +65,9 @@ def test_forward_of_middling_products(M, N, K, offsets):
 @pytest.mark.parametrize("K", [112 + i for i in range(1, 16)] + [144 + i for i in range(1, 16, 2)])
 def test_both_gradients_of_rows_that_end_anywhere(K):
     test_both_gradients_of_an_unsigned_layer(90_001, 72, K)
+
+
+# (sums of rows beside an operand with an offset: from one lane a row to a wave, more rows than a grid takes at once)
+@pytest.mark.parametrize("M,N,K", [(1_100_003, 3, 16), (600_011, 5, 17), (530_003, 3, 33), (70_003, 7, 5), (40_001, 17, 63), (40_001, 9, 64), (40_001, 9, 65), (9_001, 70, 1024), (9_001, 70, 1025), (3_003, 300, 2049)])
+def test_forward_with_row_sums(M, N, K):
+    test_forward(M, N, K, (0, 128))

@@ -1635,17 +1635,21 @@ __global__ __launch_bounds__(256) void index_rowsum_kernel(const int8_t *__restr
                                                            int32_t *__restrict__ out)
 {
     const int lanes_log2 = rowsum_lanes_log2(K), lanes = 1 << lanes_log2, lane = threadIdx.x & 63, own = lane & (lanes - 1);
+    if (lanes_log2 == 6) {      // (a wave: its row's address in scalar registers, 82753 x 569 3 us less)
+        for (int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); r < rows; r += (int64_t)gridDim.x * 4) {
+            const int s = row_sum(idx + r * K, K, lane);
+            if (lane == 0) out[r] = mult * s + add;
+        }
+        return;
+    }
     for (int64_t first = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) << (6 - lanes_log2); first < rows; first += (int64_t)gridDim.x * 4 << (6 - lanes_log2)) {
         const int64_t r = first + (lane >> lanes_log2);
         const int8_t *row = idx + (r < rows ? r : rows - 1) * K;
         int s = 0;
         if (K >= 16) {
-#pragma unroll 4
-            for (int k = 16 * own; k < K; k += 1024) {
-                const cdl_v4i w = tail_chunk(row, k, K);
+            const cdl_v4i w = tail_chunk(row, 16 * own, K);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_sdot4(w[i], 0x01010101, s, false);
-            }
+            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_sdot4(w[i], 0x01010101, s, false);
         } else {
             for (int k = 0; k < K; ++k) s += (int)row[k];
         }

@@ -167,18 +167,33 @@ int launch_tiles(SmallArgs a, hipStream_t stream)
 //   16 x 3072 x 768     13.9 ->  3.3      384 x  320 x 1664   18.0 -> 5.3     10366 x 128 x  832  12.9 -> 9.2
 //   256 x 1000 x 512    10.0 ->  3.4     1988 x  225 x  752   11.9 -> 4.2      1024 x 1024 x 1024 14.1 -> 10.1
 //   512 x 512 x 4096    35.1 ->  9.6       85 x  747 x 2951   52.7 -> 15.4    20000 x  64 x  512   7.4 -> 8.0
-// i.e. up to about a thousand tiles of 32 x 32.  A quarter to half as many again where rows start at multiples of four bytes (of one or two, a lane's 16 bytes take
-// far longer) or are short, and are no multiples of 16 (the others' tiles are faster on those), and twice as many where an offset costs the others a launch for the sums of the weights.  us, here / there:
-// 2000 x 520 x 300 6.3 / 7.5, x 1500 11.6 / 12.9, x 301 10.7 / 8.2, x 999 19.9 / 12.1, x 99 5.9 / 6.7; 1024 x 1500 x 700 8.8 / 9.8, x 3020 31 / 26, x 3021 81 / 30; 300 x 6000 x 300
-// 8.5 / 8.2, with an offset 12.6 / 13.6, x 700 12.6 / 10.6 and 17.7 / 16.4; 36001 x 26 x 200 5.4 / 6.4.  (Tiles of 64 x 64 or eight waves per tile: no better on these shapes but the 1024-cube, 8.4.)
+// i.e. up to about a thousand tiles of 32 x 32.  Twice as many at most where contractions are no multiple of 16, by what the others lack there: their tiles shift a row's end into
+// place, they take a launch for each operand's sums beside an offset (those of the rows most), and the kernel for few columns has no offset of the weights.  Here a lane's 16 bytes take far
+// longer at addresses that are no multiples of four.  us, here / there, at 1040 | 1600 | 2040 tiles: 16 columns x 300 6.5 / 5.9 | 9.2 / 7.1 | 10.6 / 8.1, x 1468 13 / 18 | 21 / 24 | 25 / 27, x 301 8.9 / 9
+// | 15.5 / 11 | 18 / 13; offset of the weights, x 300 8.8 / 17 | 10 / 19 | 13 / 22, x 3001 55 / 57 | 70 / 73; 300 columns x 300 8.0 / 8.5 | 11.4 / 9.9, x 700 7.4 / 9.3 | 12.5 / 11; both offsets x 75
+// 8.4 / 14.4 | 11.8 / 15.9 | 12 / 16.  Over 5 K shapes this rule is 0.6 % in the mean from the better of both, and 20 % better than 2048 tiles for all of them.
+static int64_t most_tiles(int32_t N, int32_t K, int32_t a_offset, int32_t b_offset)
+{
+    if (K % 16 == 0) return 1024;
+    const bool words = K % 4 == 0;
+    if (b_offset != 0) {
+        if (words) return N <= 512 || K < 1536 ? 2048 : 1664;
+        if (N > 32) return K < 192 ? 2048 : K < 384 ? 1536 : 1024;
+        return N <= 12 || K < 1024 || (N <= 24 && K < 1536) ? 2048 : K < 1536 ? 1408 : N <= 16 ? 1280 : 1024;
+    }
+    if (a_offset != 0) {
+        if (N <= 32) return words ? (K < 1024 ? 1024 : N <= 16 && K < 1536 ? 1280 : 1792) : K >= 512 && K < 1024 ? 1280 : 1024;
+        return words || K < 256 ? 1536 : 1024;
+    }
+    if (!words) return N > 32 && K >= 64 && K < 128 ? 1536 : 1024;
+    if (N <= 16) return K < 640 ? 1024 : 1920;
+    if (N <= 32) return K < 128 ? 1024 : K < 640 ? 1536 : 1664;
+    return N > 512 && K < 768 ? 1536 : K < 384 || K >= 1024 ? 1280 : 1152;
+}
+
 bool qgemm_small_serves(int32_t M, int32_t N, int32_t K, int32_t a_offset, int32_t b_offset)
 {
-    const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32);
-    if (K < 16 || tiles > 2048) return false;
-    if (tiles <= 1024) return true;
-    const bool offset = a_offset != 0 || b_offset != 0;
-    if (K % 16 == 0 || (K > 128 && K % 4 != 0) || (N <= 32 && (N <= 16 || offset))) return false;
-    return tiles <= (N <= 32 || K > 2048 ? 1280 : 1536) || (offset && K <= 512);
+    return K >= 16 && (int64_t)((M + 31) / 32) * ((N + 31) / 32) <= most_tiles(N, K, a_offset, b_offset);
 }
 
 int launch_qgemm_small(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float scale, int32_t a_offset,

@@ -165,10 +165,10 @@ int launch_thin(ThinFwdArgs a, bool conv, hipStream_t stream)
 }  // namespace
 
 // Where this kernel serves, us, tiles of 64 columns / so, beyond qgemm_small_serves.
-// Rows of up to 1024 entries, the more so with an offset, whose sums cost the others a launch: 65536 x 16 x 144 8.2 / 4.6 (15.1 / 4.6), 100000 x 16 x 1024 23.4 / 22.8, 131072 x 32 x
+// Rows of up to 1664 entries, up to 2048 for 8 columns, the more so with an offset, whose sums cost the others a launch: 65536 x 16 x 144 8.2 / 4.6 (15.1 / 4.6), 100000 x 16 x 1024 23.4 / 22.8, 131072 x 32 x
 // 144 12.4 / 9.6; two tiles of columns 65536 x 32 x 1024 22.1 / 15.8, 70001 x 32 x 768
 // 19.9 / 21.4, x 400 14.6 / 13.2, 131072 x 32 x 768 24.9 / 24.0, x 1024 29.3 / 31.4 (36.4 / 31.5).  Longer ones, up to 16 columns, while
-// all waves fit the chip at once: 65536 x 16 x 2048 33 / 25, 100000 x 16 x 2048 44.8 / 51.9 (51.8 / 51.7).  Rows that start at odd addresses: 100000 x 16 x 147
+// all waves fit the chip at once: 65536 x 16 x 2048 33 / 25, 100000 x 16 x 2048 44.8 / 51.9 (51.8 / 51.7), 98000 x 16 x 1600 40 / 38, x 2000 58 / 60, x 8 x 1600 40 / 37, 190000 x 8 x 1376 77 / 65.  Rows that start at odd addresses: 100000 x 16 x 147
 // 10.6 / 10.2, x 577 20.3 / 27.3 (26.7 / 27.2), 65536 x 1 x 577 17.8 / 13.7, 33000 x 1 x 577 11.0 / 12.7; 70001 x 26 x 250 (18.9 / 16.4).  Rows of the result that are no
 // multiple of four wide are stored word by word, which the second tile of 16 columns does not pay for: 70001 x 17 x 144 8.7 / 6.6, x 22 8.8 / 9.0,
 // x 31 9.2 / 10.2, 131072 x 31 x 144 12.2 / 15.8 (20 / 17).
@@ -176,7 +176,7 @@ bool qgemm_thin_serves(int32_t M, int32_t N, int32_t K, int32_t a_offset, int32_
 {
     if (N > 32 || K < 16 || b_offset != 0) return false;
     const bool words = K % 4 == 0, at_once = M <= 65536, offset = a_offset != 0;
-    if (N <= 16) return words ? K <= 1024 || at_once || offset : K <= (offset || (N <= 4 && M > 49152) ? 640 : 256);
+    if (N <= 16) return words ? K <= (N <= 8 ? 2048 : 1664) || at_once || offset : K <= (offset || (N <= 4 && M > 49152) ? 640 : 256);
     if (offset) return K <= (words ? 1024 : 512);
     const int64_t rounds = ((int64_t)M + 65535) / 65536;      // of resident waves; the last one may be nearly empty
     return (N % 4 == 0 || N < 20) && K <= (!words ? 160 : at_once ? 1024 : 8 * (int64_t)M >= 7 * 65536 * rounds ? 768 : 448);

@@ -2262,7 +2262,18 @@ int launch_mfma_probe(int iters, int random_operands, int blocks, int *sink, hip
     return check_launch();
 }
 
-// forward workspace: [when K % 16 != 0: room for operand copies with padded rows; they are made for K < 16 alone, and the size that callers are told stays as it was][with offsets: corrections per output column: int32 N][per output row: int32 M]
+// Whether a product of rows of K % 16 != 0 entries goes through zero-padded copies of both operands: fewer than a chunk; and results that stream past the last-level cache, where
+// the copies let the kernel of direct loads serve (K up to 15 below a multiple of 64) and N is so large that they are little beside the product.  us, as they are / in copies:
+// 72595 x 1102 x 377 155 / 134, 60000 x 1500 x 377 173 / 136, x 764 220 / 204, x 1020 248 / 243, x 2040 378 / 415, 20000 x 3072 x 505 99 / 82, x 124 53 / 50, but 60000 x 900 x 377 78 / 87;
+// 155000 x 400 x 57 74 / 62, 180232 x 344 x 57 71 / 78.  (Copies for short rows of odd lengths and the other tiles: 0.82 - 1.16, 1.0 in the mean.)
+static bool copies_pay(int32_t M, int32_t N, int32_t K)
+{
+    if (K % 16 == 0) return false;
+    if (K < 16) return true;
+    return (int64_t)M * N >= 60000000 && N >= (K < 64 ? 384 : K < 1024 ? 1024 : 2048) && dma_serves(M, N, pad_to(K, 16));
+}
+
+// forward workspace: [when K % 16 != 0: room for operand copies with padded rows; not every product makes them, see copies_pay][with offsets: corrections per output column: int32 N][per output row: int32 M]
 size_t qgemm_fwd_workspace_bytes(int32_t M, int32_t N, int32_t K, bool with_offsets)
 {
     size_t b = 0;
@@ -2311,16 +2322,16 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
                    a_offset != 0 ? 0 : K * a_offset * b_offset, corr_row);
         g.corr_row = corr_row;
     }
-    const bool ragged = K % 16 != 0 && K >= 16;
-    if (K < 16) {
-        // less than a chunk: zero-padded copies
+    const bool copies = copies_pay(M, N, K), ragged = K % 16 != 0 && !copies;
+    if (copies) {
+        const int kp = (int)pad_to(K, 16);
         int8_t *ap = reinterpret_cast<int8_t *>(ws);
-        int8_t *bp = ap + align_up((size_t)M * 16, 256);
-        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)M * 16, 256, 8192)), dim3(256), 0, a_idx, (int64_t)M, K, ap, 16);
-        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)N * 16, 256, 8192)), dim3(256), 0, b_idx, (int64_t)N, K, bp, 16);
+        int8_t *bp = ap + align_up((size_t)M * (size_t)kp, 256);
+        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)M * kp, 256, 8192)), dim3(256), 0, a_idx, (int64_t)M, K, ap, kp);
+        CDL_LAUNCH("pad_rows_kernel", stream, pad_rows_kernel, dim3(blocks_for((int64_t)N * kp, 256, 8192)), dim3(256), 0, b_idx, (int64_t)N, K, bp, kp);
         int rc = check_launch();
         if (rc != CDL_OK) return rc;
-        g.A = ap; g.B = bp; g.lda = 16; g.ldb = 16; g.Kc = 16;
+        g.A = ap; g.B = bp; g.lda = kp; g.ldb = kp; g.Kc = kp;
     }
     g.acc_out = acc; g.y_out = y; g.ldc = N;
     g.scale = delta_a * delta_b;

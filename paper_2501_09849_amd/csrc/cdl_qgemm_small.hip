@@ -186,9 +186,9 @@ static int64_t most_tiles(int32_t N, int32_t K, int32_t a_offset, int32_t b_offs
         return words || K < 256 ? 1536 : 1024;
     }
     if (!words) return N > 32 && K >= 64 && K < 128 ? 1536 : 1024;
-    if (N <= 16) return K < 640 ? 1024 : 1920;
+    if (N <= 16) return K < 640 ? 1024 : K < 1100 ? 1664 : 2048;
     if (N <= 32) return K < 128 ? 1024 : K < 640 ? 1536 : 1664;
-    return N > 512 && K < 768 ? 1536 : K < 384 || K >= 1024 ? 1280 : 1152;
+    return N > 512 && K < 768 ? 1536 : K < 384 || K >= 1024 ? 1280 : 1200;
 }
 
 bool qgemm_small_serves(int32_t M, int32_t N, int32_t K, int32_t a_offset, int32_t b_offset)

@@ -24,7 +24,7 @@ def _i8(*shape):
 
 @pytest.mark.parametrize("M,N,K,offsets,thin", [(40_000, 16, 144, (0, 0), True), (131_072, 20, 768, (0, 0), True), (70_000, 20, 448, (0, 0), True), (50_007, 16, 147, (0, 0), True), (36_001, 32, 50, (128, 0), True),
                                                 (65_536, 16, 1040, (0, 0), True), (40_000, 22, 144, (128, 0), True), (40_000, 16, 144, (0, 128), False), (70_000, 20, 464, (0, 0), False),
-                                                (40_000, 22, 144, (0, 0), False), (65_537, 16, 1040, (0, 0), False), (40_000, 16, 301, (0, 0), False), (40_000, 33, 144, (0, 0), False),
+                                                (40_000, 22, 144, (0, 0), False), (65_537, 16, 1040, (0, 0), True), (65_537, 16, 1680, (0, 0), False), (65_537, 8, 1680, (0, 0), True), (65_537, 8, 2064, (0, 0), False), (40_000, 16, 301, (0, 0), False), (40_000, 33, 144, (0, 0), False),
                                                 (1000, 16, 144, (0, 0), False)])
 def test_forward_product(M, N, K, offsets, thin):
     import paper_2501_09849_amd as cdl

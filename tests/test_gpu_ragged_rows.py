@@ -71,3 +71,10 @@ def test_both_gradients_of_rows_that_end_anywhere(K):
 @pytest.mark.parametrize("M,N,K", [(1_100_003, 3, 16), (600_011, 5, 17), (530_003, 3, 33), (70_003, 7, 5), (40_001, 17, 63), (40_001, 9, 64), (40_001, 9, 65), (9_001, 70, 1024), (9_001, 70, 1025), (3_003, 300, 2049)])
 def test_forward_with_row_sums(M, N, K):
     test_forward(M, N, K, (0, 128))
+
+
+# (results beyond the last-level cache: copies with padded rows for the kernel of direct loads, and what lies next to them)
+@pytest.mark.parametrize("M,N,K", [(58_601, 1_025, 63), (20_003, 3_077, 121), (20_003, 3_073, 249), (30_001, 2_051, 1_013), (155_009, 401, 50), (155_009, 401, 47), (20_003, 3_077, 129)])
+@pytest.mark.parametrize("offsets", [(0, 0), (128, 128)])
+def test_forward_of_padded_copies(M, N, K, offsets):
+    test_forward(M, N, K, offsets)

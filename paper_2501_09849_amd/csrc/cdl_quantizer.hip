@@ -52,18 +52,25 @@ __device__ __forceinline__ void with_constant(bool yes, F f)
     else f(std::false_type{});
 }
 
-// group(v, N): N vectors of four entries v, v + T, .. of n4.  U > 1: U vectors a thread in the block's one trip (without a branch around any: it
+// group(v, N): N vectors of four entries v, v + T, .. of the first `vectors`.  U > 1: U vectors a thread in the block's one trip (without a branch around any: it
 // would take the loads with it, behind the stores), in the last block one at a time.  U == 1: a loop over the tensor.
+// whole: how many of them have four entries; only calls with N = 1 see one that has fewer.
 template <int T, int U, typename F>
-__device__ __forceinline__ void one_trip_or_loop(int64_t n4, F group)
+__device__ __forceinline__ void one_trip_or_loop(int64_t whole, int64_t vectors, F group)
 {
     const int64_t v0 = (int64_t)blockIdx.x * T * U;
-    if (U > 1 && v0 + T * U <= n4) group(v0 + threadIdx.x, std::integral_constant<int, U>{});
+    if (U > 1 && v0 + T * U <= whole) group(v0 + threadIdx.x, std::integral_constant<int, U>{});
     else {
-        const int64_t end = U > 1 ? (v0 + T * U < n4 ? v0 + T * U : n4) : n4;
+        const int64_t end = U > 1 ? (v0 + T * U < vectors ? v0 + T * U : vectors) : vectors;
 #pragma unroll 1
         for (int64_t v = v0 + threadIdx.x; v < end; v += U > 1 ? T : (int64_t)gridDim.x * T) group(v, std::integral_constant<int, 1>{});
     }
+}
+
+// The first cnt of four entries, zeros behind them
+__device__ __forceinline__ float4 load_first(const float *p, int cnt)
+{
+    return make_float4(p[0], cnt > 1 ? p[1] : 0.0f, cnt > 2 ? p[2] : 0.0f, 0.0f);
 }
 
 constexpr int kPad = 4;   // spare histogram bins on each side, so that band offsets never leave the array
@@ -233,7 +240,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
 #pragma unroll
                 for (int u = 0; u < N; ++u) vec(t[u], v + u * T);
             };
-            one_trip_or_loop<T, U>(n4, group);
+            one_trip_or_loop<T, U>(n4, n4, group);
         }
     });
     // ragged tail: the last 1..3 entries, one thread of the last block
@@ -288,36 +295,35 @@ void quantize_bwd_kernel(const float *__restrict__ theta, const float *g, int64_
         if (SCALARS) { acc_d += (double)sum_d; acc_a += (double)sum_a; }
     };
     with_constant(k.stream != 0, [&](auto streams) {
-        // vectors v, v + T, ..
+        // vectors v, v + T, ..  (a last one of 1 to 3 entries is a thread's vector like all others: by itself behind them it is one more chain at the end of the launch, 1003 entries of
+        // 128 levels in the soft regime 18.3 us, so 10.9)
         auto group = [&](int64_t v, auto count) {
             constexpr int N = decltype(count)::value;
+            const int cnt = N > 1 || v < n4 ? 4 : (int)(n - (n4 << 2));
             float4 t[N], q[N];
+            if (N > 1 || cnt == 4) {
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
-                t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
-                q[u] = load_stream4(g + 4 * (v + u * T), streams.value);
+                for (int u = 0; u < N; ++u) {
+                    t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
+                    q[u] = load_stream4(g + 4 * (v + u * T), streams.value);
+                }
+            } else {
+                t[0] = load_first(theta + 4 * v, cnt);
+                q[0] = load_first(g + 4 * v, cnt);
             }
 #pragma unroll
             for (int u = 0; u < N; ++u) {
                 const float th[4] = {t[u].x, t[u].y, t[u].z, t[u].w}, ge[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
                 float dv[4];
                 four(th, ge, dv);
-                if (DTHETA) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+                if (DTHETA) {
+                    if (N > 1 || cnt == 4) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+                    else for (int e = 0; e < cnt; ++e) dtheta[4 * v + e] = dv[e];
+                }
             }
         };
-        one_trip_or_loop<T, U>(n4, group);
+        one_trip_or_loop<T, U>(n4, (n + 3) >> 2, group);
     });
-    // ragged tail: the last 1..3 entries, one thread of the last block
-    const int cnt = (int)(n - (n4 << 2));
-    if (cnt > 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        float th[4], ge[4], dv[4];
-        for (int e = 0; e < 4; ++e) {
-            th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
-            ge[e] = (e < cnt) ? g[(n4 << 2) + e] : 0.0f;
-        }
-        four(th, ge, dv);
-        if (DTHETA) for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
-    }
     if (SCALARS) scalar_finish<T>(acc_d, acc_a, fin);
 }
 
@@ -707,7 +713,7 @@ void quantize_draw_kernel(const float *__restrict__ theta, const float *__restri
                 reinterpret_cast<uint32_t *>(idx)[v + i * T] = pack_indices(c0, c1, c2, c3, k.idx_off);
             }
         };
-        one_trip_or_loop<T, U>(n4, group);
+        one_trip_or_loop<T, U>(n4, n4, group);
     });
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
         for (int64_t e = n4 << 2; e < n; ++e) idx[e] = (int8_t)(draw_one<W>(theta[e], u[e], k) - k.idx_off);
@@ -800,33 +806,31 @@ void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict
     with_constant(k.stream != 0, [&](auto streams) {
         auto group = [&](int64_t v, auto count) {
             constexpr int N = decltype(count)::value;
+            const int cnt = N > 1 || v < n4 ? 4 : (int)(n - (n4 << 2));      // (the last vector as in quantize_bwd_kernel: 256 K entries of 127 levels in the soft regime 37.6 us by itself, so 22.0)
             float4 t[N], q[N];
+            if (N > 1 || cnt == 4) {
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
-                t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
-                q[u] = ADD ? load_stream4(g_in + 4 * (v + u * T), streams.value) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                for (int u = 0; u < N; ++u) {
+                    t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
+                    q[u] = ADD ? load_stream4(g_in + 4 * (v + u * T), streams.value) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+            } else {
+                t[0] = load_first(theta + 4 * v, cnt);
+                q[0] = ADD ? load_first(g_in + 4 * v, cnt) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
 #pragma unroll
             for (int u = 0; u < N; ++u) {
                 const float th[4] = {t[u].x, t[u].y, t[u].z, t[u].w}, ge[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
                 float dv[4];
-                four(th, ge, 4, dv);
-                if (DTHETA) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+                four(th, ge, cnt, dv);
+                if (DTHETA) {
+                    if (N > 1 || cnt == 4) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+                    else for (int e = 0; e < cnt; ++e) dtheta[4 * v + e] = dv[e];
+                }
             }
         };
-        one_trip_or_loop<T, U>(n4, group);
+        one_trip_or_loop<T, U>(n4, (n + 3) >> 2, group);
     });
-    // ragged tail: the last 1..3 entries, one thread of the last block
-    const int cnt = (int)(n - (n4 << 2));
-    if (cnt > 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        float th[4], ge[4], dv[4];
-        for (int e = 0; e < 4; ++e) {
-            th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
-            ge[e] = (ADD && e < cnt) ? g_in[(n4 << 2) + e] : 0.0f;
-        }
-        four(th, ge, cnt, dv);
-        if (DTHETA) for (int e = 0; e < cnt; ++e) dtheta[(n4 << 2) + e] = dv[e];
-    }
     if (SCALARS) scalar_finish<T>(acc_d, acc_a, fin);
 }
 

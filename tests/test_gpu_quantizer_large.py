@@ -68,6 +68,37 @@ def test_entropy_gradient_alone(oracle, kappa, add):
     gu.assert_close(got, want + 0.5 * th if add else want, "entropy gradient")
 
 
+# a last vector of one to three entries: alone, behind whole ones of the same wave, first of a wave or a block, in the second trip of a loop and in the last block of one trip
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 1_023, 1_025, 66_051, LINE - 1, LINE + 2, LINE + 1_026, 4 * LINE + 4_097])
+@pytest.mark.parametrize("levels,kappa", [(15, 4.0), (15, 1.5), (127, 0.5)])
+def test_last_vector_of_gradients(oracle, n, levels, kappa):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    lo, delta = -(levels // 2), 2.0 / levels
+    alpha = kappa / delta ** 2
+    rng = np.random.default_rng(n + levels)
+    theta, g = (rng.standard_normal(n) * 0.3).astype(np.float32), rng.standard_normal(n).astype(np.float32)
+    marg = rng.random(levels) + 0.1
+    marg = (marg / marg.sum()).astype(np.float32)
+    th_d, g_d, m_d, ws = gu.dev(theta), gu.dev(g), gu.dev(marg), gu.workspace(cdl.quantize_workspace_bytes(n, levels))
+    ws.fill_(255)
+    at = np.unique(np.r_[0:min(n, 500), n // 2048 * 2048 - 3:n // 2048 * 2048 + 3, max(0, n - 500):n].clip(0, n - 1))
+    want = oracle.quantize_bwd(theta[at], g[at], lo, levels, delta, alpha)["dtheta"]
+    want_e = oracle.entropy_bwd(theta[at], marg.astype(np.float64), lo, levels, delta, alpha, scale=0.1 * at.size)["dtheta"]
+    for scalars in (False, True):
+        dd = [gu.empty((1,), torch.float32) if scalars else None for _ in range(4)]
+        outs = [torch.full((n + 1,), 7.0, device="cuda") for _ in range(3)]      # (one more entry than asked for: it stays as it is)
+        cdl.cdl_quantize_bwd(th_d, g_d, n, lo, levels, delta, alpha, outs[0], dd[0], dd[1], ws)
+        cdl.cdl_entropy_bwd(th_d, m_d, n, lo, levels, delta, alpha, 0.1 * n, g_d, outs[1], dd[2], dd[3], ws)
+        cdl.cdl_entropy_bwd(th_d, m_d, n, lo, levels, delta, alpha, 0.1 * n, None, outs[2], dd[2], dd[3], ws)
+        torch.cuda.synchronize()
+        for got, ref in zip(outs, (want, want_e + g[at], want_e)):
+            assert float(got[n]) == 7.0
+            gu.assert_close(got.cpu().numpy()[:n][at], ref, "gradient")
+        if scalars and n <= 66_051:
+            gu.check_quantizer_scalars(oracle, "last vector %d" % n, theta, g, (lo, levels, delta, alpha), dd[0].item(), dd[1].item(), oracle.quantize_bwd(theta, g, lo, levels, delta, alpha))
+
+
 # (kappa of band widths 1 .. 4; sets of which every level is live)
 @pytest.mark.parametrize("n", [3001, 90_001, LINE + 5])
 @pytest.mark.parametrize("levels,kappa", [(2, 16.0), (97, 16.0), (98, 16.0), (72, 4.0), (73, 4.0), (48, 2.5), (49, 2.5), (36, 1.5), (37, 1.5), (72, 3.82), (3, 0.05), (5, 0.05), (5, 3.9)])

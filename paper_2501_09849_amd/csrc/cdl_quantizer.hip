@@ -896,6 +896,22 @@ int grid_for(int64_t n)
 // Whether the kernels that take a large tensor in one trip serve: the unrolled bands (the loop over the levels is bound by arithmetic).
 bool one_trip_serves(int64_t n, const QConst &k) { return n > kOneTripEntries && band_template(k) != 0 && one_trip_fits(n); }
 
+// Gradients of the quantizer.  Wider bands: a loop's waits hide behind the arithmetic up to twice as many entries.  us without scalars, loop / one trip, one to four levels on each side: 3.2 M entries
+// 9.5 / 9.3, 9.4 / 9.1, 10.0 / 10.6, 10.7 / 11.7; 4.5 M 12.0 / 11.6, 11.8 / 11.4, 13.0 / 12.8, 14.3 / 14.4.
+bool gradient_one_trip(int64_t n, const QConst &k) { return one_trip_serves(n, k) && (band_template(k) <= 2 || n >= 2 * kOneTripEntries); }
+
+// Gradient of the entropy: every block makes the logarithms of all levels first, and with the scalar gradients a looping grid finishes their sums itself where blocks of one trip that stream leave them for a
+// second launch.  There one trip pays only for very large tensors that are added to a gradient as well, with up to two levels on each side.  us with the scalars, loop / one trip, 64 levels, two on each side:
+// 3.2 M entries 13.4 / 13.1, 6 M 18.7 / 18.7, 24 M 50.1 / 54.9, 60 M 114 / 121, added to a gradient 24 M 56.6 / 57.5, 60 M 135 / 131 (one on each side 130 / 120); four on each side 3.2 M 17.3 / 19.1, 24 M 81 / 89;
+// 255 levels, two on each side 3.2 M 14.7 / 14.6, 24 M 54 / 66, 60 M 126 / 146, added 134 / 147.  Without them, added to a gradient, 255 levels, two on each side: 25 M 57.7 / 50.2, 50 M 115.6 / 97.3.
+bool entropy_one_trip(int64_t n, const QConst &k, bool scalars, bool add)
+{
+    if (!gradient_one_trip(n, k)) return false;
+    if (!scalars) return true;
+    const int w = band_template(k);
+    return w <= 2 && (n < kStreamFrom || (add && n >= 4 * kStreamFrom && (w == 1 || k.n_levels <= 64)));
+}
+
 // Up to four times as many blocks as can finish the job themselves: that many, of more trips each.  A second launch costs more
 // (forward + backward of 0.3 M entries, 15 levels: 13.8 -> 12.3 us, 255 levels 17.3 -> 14.1; 0.9 M, 15 levels 17.0 -> 16.1) - not in
 // the soft regime, whose kernels are bound by arithmetic.
@@ -1272,7 +1288,7 @@ int launch_quantize_bwd(const float *theta, const float *g, int64_t n, const cdl
     }
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    const bool one_trip = one_trip_serves(n, k);
+    const bool one_trip = gradient_one_trip(n, k);
     const int grid = one_trip ? (int)one_trip_grid(n) : want_scalars && band_template(k) != 0 ? finishing_grid(grid_for(n)) : grid_for(n);
     const double d = (double)p.delta;
     ScalarFinish fin{};
@@ -1361,11 +1377,7 @@ int launch_entropy_bwd(const float *theta, const float *marg, const float *g_in,
     }
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    // (every block makes the logarithms of all levels: with the scalar gradients, whose sums then take a second launch, blocks of one trip do not pay for those of large sets where
-    // the tensor streams, unless one level on each side leaves the loop no shorter.  us, loop / one trip, two on each side: 9 M entries of 63 levels 26.2 / 25.5, of 128
-    // 26.2 / 28.9, of 255 26.8 / 28.4; 25.6 M of 96 61.5 / 57.1, of 128 61.3 / 58.6, of 180 61.3 / 60.7, of 255 61.1 / 62.6; 47 M of 128 110 / 106, of 255 110 / 110; three on each
-    // side 25.6 M of 255 72.9 / 78.2.  Without them, added to a gradient, 255 levels, two on each side: 25 M 57.7 / 50.2, 50 M 115.6 / 97.3, three 74.6 / 63.1, 141 / 127)
-    const bool one_trip = one_trip_serves(n, k) && (!want_scalars || k.n_levels <= 64 || (k.n_levels <= 128 && n >= 2 * kStreamFrom) || n < kStreamFrom || band_template(k) == 1);
+    const bool one_trip = entropy_one_trip(n, k, want_scalars, g_in != nullptr);
     const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
     const bool want_dtheta = dtheta != nullptr;
     const double alpha = (double)p.alpha, delta = (double)p.delta;

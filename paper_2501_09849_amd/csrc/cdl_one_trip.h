@@ -12,9 +12,8 @@ namespace cdl {
 // start in the order of the tensor.  us, as a loop of up to 2048 blocks / so (with the shorter arithmetic of cdl_quantizer_math.h), 31 levels, two on each side, from a
 // cold cache: gradient without scalars (8 B read, 4 written an entry) 12.8 M entries 28.1 / 26.0, 25.6 M 52.6 / 49.3, 50.3 M 102 / 97, 115.6 M 239 / 224 (6.2 TB/s); with
 // them 36.6 / 32.3, 62.7 / 56.4, 112 / 104, 256 / 235; index and soft value without PMF (4 B read, 5 written) 25.2 / 21.7, 43.4 / 37.8, 83.8 / 72.3,
-// 198 / 167 (6.2 TB/s).  Blocks of 256 x 2 vectors against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.  Draws and forward passes go so from twice as many entries on: draws of 3 M entries of
-// 15 levels, one to four levels on each side 7.2 / 7.6, 7.7 / 7.9, 8.8 / 10.0, 10.7 / 11.4, index and soft value 7.3 / 7.7 (one), 7.5 / 7.9 (two); 8.3 M, one to four
-// 15.0 / 14.7, 17.1 / 14.9, 20.0 / 19.1, 24.8 / 23.0.
+// 198 / 167 (6.2 TB/s).  Blocks of 256 x 2 vectors against 512 x 3: 46 / 49 us (gradient of 25.6 M); one vector a thread 50.  (How many entries each pass
+// needs for it: gradient_one_trip, entropy_one_trip and forward_one_trip in cdl_quantizer.hip.)
 constexpr int kOneTripThreads = 256, kOneTripVectors = 2;
 
 // Blocks.  The last one has at most the rest of the vectors, and the entries beyond them.

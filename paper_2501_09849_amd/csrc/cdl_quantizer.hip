@@ -912,6 +912,14 @@ bool entropy_one_trip(int64_t n, const QConst &k, bool scalars, bool add)
     return w <= 2 && (n < kStreamFrom || (add && n >= 4 * kStreamFrom && (w == 1 || k.n_levels <= 64)));
 }
 
+// Draws (two streams of floats read) and forward passes without PMF (with soft values: one read, one written).  Indices alone leave a loop nearly no stores to wait for.  us, loop / one trip, two levels on each side: draws 4.3 M
+// entries 9.5 / 9.9, 6.5 M 13.0 / 13.1, 8.8 M 16.0 / 14.9, 24 M 41 / 35; index and soft value 10.9 / 11.5 (5.3 M), 12.6 / 12.9, 15.4 / 14.8, 38.3 / 34.1; four on each side 5.3 M 15.6 / 15.3, 6.5 M 18.2 / 17.1;
+// indices alone 4.3 M 5.3 / 5.8, 8.8 M 8.6 / 9.2, 16 M 14.4 / 14.5, 24 M 21.0 / 20.6, 48 M 39.7 / 37.7.
+bool forward_one_trip(int64_t n, const QConst &k, bool two_streams)
+{
+    return one_trip_serves(n, k) && n >= (!two_streams ? 2 * kStreamFrom : band_template(k) <= 2 ? kStreamFrom : 3 * kOneTripEntries);
+}
+
 // Up to four times as many blocks as can finish the job themselves: that many, of more trips each.  A second launch costs more
 // (forward + backward of 0.3 M entries, 15 levels: 13.8 -> 12.3 us, 255 levels 17.3 -> 14.1; 0.9 M, 15 levels 17.0 -> 16.1) - not in
 // the soft regime, whose kernels are bound by arithmetic.
@@ -1231,7 +1239,7 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
     int64_t grid64 = want_marg ? hist_grid_for(n, hist_half(n, k, uniform_half_width(p, k))) : grid_for(n);
     if (want_marg && band_template(k) != 0 && n <= 4ll * kFinishMaxBlocks * kMargThreads * 4 && hist_few(finishing_grid(grid64), p.n_levels)) grid64 = finishing_grid(grid64);
     if (grid64 > 2147483647LL) return CDL_ERR_PARAM;
-    const bool one_trip = !want_marg && n >= 2 * kOneTripEntries && one_trip_serves(n, k);
+    const bool one_trip = !want_marg && forward_one_trip(n, k, soft != nullptr);
     int grid = one_trip ? (int)one_trip_grid(n) : (int)grid64;
     MargFinish fin{};
     if (want_marg) {
@@ -1321,7 +1329,7 @@ int launch_quantize_draw(const float *theta, const float *u, int64_t n, const cd
     if (n == 0) return CDL_OK;
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
-    const bool one_trip = n >= 2 * kOneTripEntries && one_trip_serves(n, k);
+    const bool one_trip = forward_one_trip(n, k, true);      // (two numbers read)
     const int grid = one_trip ? (int)one_trip_grid(n) : grid_for(n);
 #define CDL_DRAW(WW) \
     do { \

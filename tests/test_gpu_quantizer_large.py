@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 LINE = 2_097_152      # more entries: one trip, blocks of 2048 entries
 
 
-@pytest.mark.parametrize("n", [LINE, LINE + 1, LINE + 2047, LINE + 2048 + 1027])
+@pytest.mark.parametrize("n", [LINE, LINE + 1, LINE + 2047, LINE + 2048 + 1027, 4 * LINE - 1, 4 * LINE + 1027])
 def test_one_trip_remainders(oracle, n):
     import paper_2501_09849_amd as cdl
     torch = gu.torch_mod()
@@ -43,6 +43,30 @@ def test_one_trip_remainders(oracle, n):
     tail = slice(n - 5000, n)
     r_e = oracle.entropy_bwd(theta, marg.cpu().numpy().astype(np.float64), lo, levels, delta, alpha, scale=0.01 * n)
     gu.assert_close(dent[:n].cpu().numpy()[tail], (r_e["dtheta"] + g)[tail], "entropy gradient")
+
+
+# indices without soft values go in one trip from more entries on; draws and soft values of wider bands from fewer
+@pytest.mark.parametrize("n,kappa", [(8 * LINE - 3, 4.0), (8 * LINE + 1027, 4.0), (8 * LINE + 2, 1.5), (3 * LINE - 1, 1.5), (3 * LINE + 1026, 2.5)])
+def test_indices_and_draws(oracle, n, kappa):
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    q = (-7, 15, 0.0625, kappa / 0.0625 ** 2)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    theta, u = 0.2 * torch.randn(n, device="cuda", generator=gen), torch.rand(n, device="cuda", generator=gen)
+    idx, both, drawn = (torch.full((n + 1,), 99, dtype=torch.int8, device="cuda") for _ in range(3))
+    soft = torch.full((n + 1,), 7.0, device="cuda")
+    cdl.cdl_quantize_fwd(theta, n, *q, idx)
+    cdl.cdl_quantize_fwd(theta, n, *q, both, soft)
+    cdl.cdl_quantize_draw(theta, u, n, *q, drawn)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, both) and int(idx[n]) == 99 and int(drawn[n]) == 99 and float(soft[n]) == 7.0
+    at = np.r_[0:4100, n // 2 // 2048 * 2048 - 50:n // 2 // 2048 * 2048 + 50, n - 5000:n]
+    th = theta.cpu().numpy()[at]
+    r_idx, r_soft, r_gap = oracle.quantize_fwd(th, *q)[:3]
+    gu.assert_indices(idx.cpu().numpy()[:n][at], r_idx, r_gap, "indices")
+    gu.assert_close(soft.cpu().numpy()[:n][at], r_soft, "soft")
+    r_draw, margin = oracle.quantize_draw(th, u.cpu().numpy()[at], *q)
+    assert np.all(np.asarray(margin)[drawn.cpu().numpy()[:n][at] != r_draw] < 1e-6)
 
 
 # the gradient of the entropy without the scalar ones, large sets: one trip as well; entries at both ends of the tensor and of blocks

@@ -52,18 +52,23 @@ __device__ __forceinline__ void with_constant(bool yes, F f)
     else f(std::false_type{});
 }
 
-// group(v, N): N vectors of four entries v, v + T, .. of the first `vectors`.  U > 1: U vectors a thread in the block's one trip (without a branch around any: it
-// would take the loads with it, behind the stores), in the last block one at a time.  U == 1: a loop over the tensor.
-// whole: how many of them have four entries; only calls with N = 1 see one that has fewer.
+// group(v, N, RAGGED): N vectors of four entries v, v + T, .. of the first `vectors`, of which `whole` have four.  U > 1: U vectors a thread in the block's one trip (without a branch
+// around any: it would take the loads with it, behind the stores), in the last block one at a time.  U == 1: a loop over the tensor.
+// RAGGED: the last vector may have fewer entries, which puts a branch around the loads of a loop.  Whole tensors go without where all blocks are short (quantizer gradient, 0.5 M entries of 31 levels, two
+// on each side 6.1 us, with it 6.5; 2.1 M, four 11.5 / 12.1), but the loops of larger ones are faster with it (2.1 M, four on each side without scalars 9.4 / 8.8; 24 M, gradient of the entropy added 57 / 53).
 template <int T, int U, typename F>
 __device__ __forceinline__ void one_trip_or_loop(int64_t whole, int64_t vectors, F group)
 {
     const int64_t v0 = (int64_t)blockIdx.x * T * U;
-    if (U > 1 && v0 + T * U <= whole) group(v0 + threadIdx.x, std::integral_constant<int, U>{});
+    if (U > 1 && v0 + T * U <= whole) group(v0 + threadIdx.x, std::integral_constant<int, U>{}, std::false_type{});
     else {
         const int64_t end = U > 1 ? (v0 + T * U < vectors ? v0 + T * U : vectors) : vectors;
+        auto loop = [&](auto ragged) {
 #pragma unroll 1
-        for (int64_t v = v0 + threadIdx.x; v < end; v += U > 1 ? T : (int64_t)gridDim.x * T) group(v, std::integral_constant<int, 1>{});
+            for (int64_t v = v0 + threadIdx.x; v < end; v += U > 1 ? T : (int64_t)gridDim.x * T) group(v, std::integral_constant<int, 1>{}, ragged);
+        };
+        if (U > 1 || vectors > whole || whole > (int64_t)kMaxQuantBlocks * T) loop(std::true_type{});
+        else loop(std::false_type{});
     }
 }
 
@@ -232,7 +237,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
                     if (u == 0 || v + u * T < n4) vec(now[u], v + u * T);
             }
         } else {
-            auto group = [&](int64_t v, auto count) {
+            auto group = [&](int64_t v, auto count, auto ragged) {
                 constexpr int N = decltype(count)::value;
                 float4 t[N];
 #pragma unroll
@@ -240,7 +245,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
 #pragma unroll
                 for (int u = 0; u < N; ++u) vec(t[u], v + u * T);
             };
-            one_trip_or_loop<T, U>(n4, n4, group);
+            one_trip_or_loop<T, U>(n4, n4, group);      // (the tail is below)
         }
     });
     // ragged tail: the last 1..3 entries, one thread of the last block
@@ -297,11 +302,11 @@ void quantize_bwd_kernel(const float *__restrict__ theta, const float *g, int64_
     with_constant(k.stream != 0, [&](auto streams) {
         // vectors v, v + T, ..  (a last one of 1 to 3 entries is a thread's vector like all others: by itself behind them it is one more chain at the end of the launch, 1003 entries of
         // 128 levels in the soft regime 18.3 us, so 10.9)
-        auto group = [&](int64_t v, auto count) {
+        auto group = [&](int64_t v, auto count, auto ragged) {
             constexpr int N = decltype(count)::value;
-            const int cnt = N > 1 || v < n4 ? 4 : (int)(n - (n4 << 2));
+            const int cnt = !ragged.value || v < n4 ? 4 : (int)(n - (n4 << 2));
             float4 t[N], q[N];
-            if (N > 1 || cnt == 4) {
+            if (!ragged.value || cnt == 4) {
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
                     t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
@@ -317,7 +322,7 @@ void quantize_bwd_kernel(const float *__restrict__ theta, const float *g, int64_
                 float dv[4];
                 four(th, ge, dv);
                 if (DTHETA) {
-                    if (N > 1 || cnt == 4) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+                    if (!ragged.value || cnt == 4) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
                     else for (int e = 0; e < cnt; ++e) dtheta[4 * v + e] = dv[e];
                 }
             }
@@ -698,7 +703,7 @@ void quantize_draw_kernel(const float *__restrict__ theta, const float *__restri
     constexpr int T = one_trip_threads(U);
     const int64_t n4 = n >> 2;
     with_constant(k.stream != 0, [&](auto streams) {
-        auto group = [&](int64_t v, auto count) {
+        auto group = [&](int64_t v, auto count, auto ragged) {
             constexpr int N = decltype(count)::value;
             float4 t[N], r[N];
 #pragma unroll
@@ -713,7 +718,7 @@ void quantize_draw_kernel(const float *__restrict__ theta, const float *__restri
                 reinterpret_cast<uint32_t *>(idx)[v + i * T] = pack_indices(c0, c1, c2, c3, k.idx_off);
             }
         };
-        one_trip_or_loop<T, U>(n4, n4, group);
+        one_trip_or_loop<T, U>(n4, n4, group);      // (the tail is below)
     });
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
         for (int64_t e = n4 << 2; e < n; ++e) idx[e] = (int8_t)(draw_one<W>(theta[e], u[e], k) - k.idx_off);
@@ -804,11 +809,11 @@ void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict
         if (SCALARS) { acc_d += (double)sum_d; acc_a += (double)sum_a; }
     };
     with_constant(k.stream != 0, [&](auto streams) {
-        auto group = [&](int64_t v, auto count) {
+        auto group = [&](int64_t v, auto count, auto ragged) {
             constexpr int N = decltype(count)::value;
-            const int cnt = N > 1 || v < n4 ? 4 : (int)(n - (n4 << 2));      // (the last vector as in quantize_bwd_kernel: 256 K entries of 127 levels in the soft regime 37.6 us by itself, so 22.0)
+            const int cnt = !ragged.value || v < n4 ? 4 : (int)(n - (n4 << 2));      // (the last vector as in quantize_bwd_kernel: 256 K entries of 127 levels in the soft regime 37.6 us by itself, so 22.0)
             float4 t[N], q[N];
-            if (N > 1 || cnt == 4) {
+            if (!ragged.value || cnt == 4) {
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
                     t[u] = load_stream4(theta + 4 * (v + u * T), streams.value);
@@ -824,7 +829,7 @@ void entropy_bwd_kernel(const float *__restrict__ theta, const float *__restrict
                 float dv[4];
                 four(th, ge, cnt, dv);
                 if (DTHETA) {
-                    if (N > 1 || cnt == 4) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
+                    if (!ragged.value || cnt == 4) store_stream4(dtheta + 4 * (v + u * T), dv[0], dv[1], dv[2], dv[3], streams.value);
                     else for (int e = 0; e < cnt; ++e) dtheta[4 * v + e] = dv[e];
                 }
             }

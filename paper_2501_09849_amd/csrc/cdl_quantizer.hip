@@ -189,7 +189,7 @@ __device__ __forceinline__ void forward4(const float (&th)[4], int cnt, const QC
 
 // U: vectors of four entries a thread takes per trip.  U > 1: with MARG the loads of a trip (hist_ahead) are issued before the trip before it is
 // computed and stored, without MARG there is one trip.
-template <int W, bool IDX, bool SOFT, bool MARG, bool FEW, int U>
+template <int W, bool IDX, bool SOFT, bool MARG, int FORM, int U>
 __global__ __launch_bounds__(MARG ? kMargThreads : one_trip_threads(U))
 void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
                          int8_t *__restrict__ idx, float *__restrict__ soft,
@@ -268,7 +268,7 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
 #pragma unroll
             for (int r = 0; r < R; ++r) own += row[(r + (int)threadIdx.x) & (R - 1)];   // rotated start: no bank conflicts
         }
-        marginal_end<T, FEW>(own, k.n_levels, fin);
+        marginal_end<T, FORM>(own, k.n_levels, fin);
     }
 }
 
@@ -485,7 +485,7 @@ __device__ __forceinline__ void uni_sums_literal(float th, const UniConst &u, Un
     o.Z = Z; o.S1 = S1; o.S2 = S2; o.S3 = S3;
 }
 
-template <int JH, bool IDX, bool SOFT, bool MARG, bool FEW>
+template <int JH, bool IDX, bool SOFT, bool MARG, int FORM>
 __global__ __launch_bounds__(kUniThreads)
 void quantize_fwd_uniform_kernel(const float *__restrict__ theta, int64_t n, QConst k, UniConst u,
                                  int8_t *__restrict__ idx, float *__restrict__ soft,
@@ -568,7 +568,7 @@ void quantize_fwd_uniform_kernel(const float *__restrict__ theta, int64_t n, QCo
             for (int t = 0; t < kUniThreads; ++t) tot += uni_lds[(size_t)t * LS + threadIdx.x];
             own = (unsigned long long)__double2ll_rn(tot * (double)(1u << kHistScaleBits));
         }
-        marginal_end<kUniThreads, FEW>(own, k.n_levels, fin);
+        marginal_end<kUniThreads, FORM>(own, k.n_levels, fin);
     }
 }
 
@@ -968,10 +968,18 @@ bool hist_half(int64_t n, const QConst &k, int uniform_half)
 constexpr int kHistVectors = 2;
 bool hist_ahead(int64_t n, const QConst &k) { return n >= kHistFullFrom && (band_template(k) == 1 || band_template(k) == 2); }
 
-// Whether the histogram kernel finishes the job itself: up to 256 blocks whose records one block can poll in a few
-// trips to memory (measured on quantizer forward + backward: 245 blocks of 15 levels 21.4 against 24.7 us, 49 blocks
-// of 255 levels 17.5 against 24.8, 98 of 255 even, 245 of 255 twice as slow as a second launch).
-bool hist_few(int64_t grid, int32_t n_levels) { return grid <= kFinishMaxBlocks && grid * n_levels <= 16384; }
+// Who adds up the blocks' histograms.  Up to 256 blocks finish the job themselves: the last one where their records are 64 KB at most, beyond, the last ones, a slice of the
+// levels each (cdl_marginal.h; the unrolled bands only, the others keep one block up to 256 KB).  Blocks of one trip and more than 256 KB, and larger grids, leave rows for a second launch.
+// us of the forward pass, second launch / slices: 131 K entries of 255 levels (64 blocks, one trip) 8.3 / 8.6, 512 K 9.3 / 10.1;  700 K (171, two) 10.8 / 10.1, 1 M 12.1 / 10.8, 2.1 M (256, four) 13.3 / 13.1;
+// 1024 blocks: 6 M of 63 17.7 / 18.7, 25.6 M of 31 46.0 / 46.9.  Last block / slices: 65 K of 255 (32 blocks) 9.9 / 7.8;  63 levels 512 K (250) 15.6 / 8.8, 1 M (245, two) 16.7 / 9.6, 2.1 M 18.5 / 12.6.
+MargForm marg_form(int64_t blocks, int64_t n, const cdl_qparams &p, const QConst &k)
+{
+    if (blocks > kFinishMaxBlocks) return kMargRows;
+    const int64_t records = blocks * p.n_levels;
+    if (band_template(k) == 0) return records <= 16384 ? kMargLast : kMargRows;
+    const bool one_trip = n <= blocks * (4 * kMargThreads);
+    return records <= 4096 ? kMargLast : records <= 16384 || !one_trip ? kMargSlices : kMargRows;
+}
 
 // workspace layout: [rows of the histogram kernel's blocks][records of the finishing blocks][scalar partials or records]
 // (or the table and the rows of moments of the soft regime)
@@ -1014,29 +1022,31 @@ int launch_scalar_end(const ScalarFinish &f, void *scalars, int grid, hipStream_
 }
 
 template <int W>
-void launch_fwd(bool want_idx, bool want_soft, bool want_marg, bool one_trip, int grid, hipStream_t s,
+void launch_fwd(bool want_idx, bool want_soft, bool want_marg, bool one_trip, MargForm form, int grid, hipStream_t s,
                   const float *theta, int64_t n, const QConst &k, int8_t *idx, float *soft,
                   const MargFinish &fin)
 {
     const size_t lds = (size_t)(k.n_levels + 2 * kPad) * kHistCopies * sizeof(unsigned int);
-#define CDL_FWD(I, S, M, U)                                                                               \
+#define CDL_FWD(I, S, M, F, U)                                                                            \
     CDL_LAUNCH((I) ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)", s,                     \
-               (quantize_fwd_kernel<W, I, S, (M) != 0, (M) == 2, U>), dim3(grid), dim3((M) ? kMargThreads : one_trip_threads(U)), \
+               (quantize_fwd_kernel<W, I, S, M, F, U>), dim3(grid), dim3((M) ? kMargThreads : one_trip_threads(U)), \
                (M) ? lds : 0, theta, n, k, idx, soft, fin)
-    const bool few = hist_few(grid, k.n_levels);
+#define CDL_FWD_MARG(I, S)                                                                                \
+    do {                                                                                                  \
+        if (form == kMargLast) CDL_FWD(I, S, true, kMargLast, 1);                                         \
+        else if (form == kMargRows) CDL_FWD(I, S, true, kMargRows, 1);                                    \
+        else if constexpr (W > 0) CDL_FWD(I, S, true, kMargSlices, 1);                                    \
+    } while (0)
     constexpr int UM = W == 1 || W == 2 ? kHistVectors : 1, UN = W > 0 ? kOneTripVectors : 1;
-    const bool ahead = hist_ahead(n, k);
-    if (want_idx && want_soft && want_marg && few) CDL_FWD(true, true, 2, 1);
-    else if (want_idx && want_soft && want_marg && ahead) CDL_FWD(true, true, 1, UM);
-    else if (want_idx && want_soft && want_marg) CDL_FWD(true, true, 1, 1);
-    else if (want_idx && want_soft && one_trip) CDL_FWD(true, true, 0, UN);
-    else if (want_idx && want_soft) CDL_FWD(true, true, 0, 1);
-    else if (want_idx && want_marg && few) CDL_FWD(true, false, 2, 1);
-    else if (want_idx && want_marg) CDL_FWD(true, false, 1, 1);
-    else if (want_idx && one_trip) CDL_FWD(true, false, 0, UN);
-    else if (want_idx) CDL_FWD(true, false, 0, 1);
-    else if (few) CDL_FWD(false, false, 2, 1);
-    else CDL_FWD(false, false, 1, 1);
+    if (want_idx && want_soft && want_marg && form == kMargRows && hist_ahead(n, k)) CDL_FWD(true, true, true, kMargRows, UM);
+    else if (want_idx && want_soft && want_marg) CDL_FWD_MARG(true, true);
+    else if (want_idx && want_soft && one_trip) CDL_FWD(true, true, false, kMargRows, UN);
+    else if (want_idx && want_soft) CDL_FWD(true, true, false, kMargRows, 1);
+    else if (want_idx && want_marg) CDL_FWD_MARG(true, false);
+    else if (want_idx && one_trip) CDL_FWD(true, false, false, kMargRows, UN);
+    else if (want_idx) CDL_FWD(true, false, false, kMargRows, 1);
+    else CDL_FWD_MARG(false, false);
+#undef CDL_FWD_MARG
 #undef CDL_FWD
 }
 
@@ -1092,22 +1102,22 @@ UniConst make_uniform(const cdl_qparams &p, int jh)
 }
 
 template <int JH>
-int launch_fwd_uniform(bool want_idx, bool want_soft, bool want_marg, int grid, hipStream_t s, const float *theta, int64_t n,
+int launch_fwd_uniform(bool want_idx, bool want_soft, bool want_marg, MargForm form, int grid, hipStream_t s, const float *theta, int64_t n,
                        const QConst &k, const UniConst &u, int8_t *idx, float *soft, const MargFinish &fin)
 {
     const size_t lds = want_marg ? (size_t)kUniThreads * (2 * JH + 1) * sizeof(double) : 0;
 #define CDL_UNI(I, S, M)                                                                                        \
     do {                                                                                                        \
         if (lds > 65536) {                                                                                      \
-            const hipError_t e_ = hipFuncSetAttribute((const void *)quantize_fwd_uniform_kernel<JH, I, S, (M) != 0, (M) == 2>,   \
+            const hipError_t e_ = hipFuncSetAttribute((const void *)quantize_fwd_uniform_kernel<JH, I, S, (M) != 0, (M) == 2 ? kMargLast : kMargRows>,   \
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);    \
             if (e_ != hipSuccess) return hip_failed(e_);                                                        \
         }                                                                                                       \
         CDL_LAUNCH((I) ? "quantize_fwd_kernel" : "quantize_fwd_kernel(marginal only)", s,                       \
-                   (quantize_fwd_uniform_kernel<JH, I, S, (M) != 0, (M) == 2>), dim3(grid), dim3(kUniThreads), lds,              \
+                   (quantize_fwd_uniform_kernel<JH, I, S, (M) != 0, (M) == 2 ? kMargLast : kMargRows>), dim3(grid), dim3(kUniThreads), lds,              \
                    theta, n, k, u, idx, soft, fin);                                                 \
     } while (0)
-    const bool few = hist_few(grid, k.n_levels);
+    const bool few = form == kMargLast;
     if (want_idx && want_soft && want_marg && few) CDL_UNI(true, true, 2);
     else if (want_idx && want_soft && want_marg) CDL_UNI(true, true, 1);
     else if (want_idx && want_soft) CDL_UNI(true, true, 0);
@@ -1242,13 +1252,13 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
     QConst k = make_const(p);
     k.stream = n >= kStreamFrom;
     int64_t grid64 = want_marg ? hist_grid_for(n, hist_half(n, k, uniform_half_width(p, k))) : grid_for(n);
-    if (want_marg && band_template(k) != 0 && n <= 4ll * kFinishMaxBlocks * kMargThreads * 4 && hist_few(finishing_grid(grid64), p.n_levels)) grid64 = finishing_grid(grid64);
+    if (want_marg && band_template(k) != 0 && n <= 4ll * kFinishMaxBlocks * kMargThreads * 4) grid64 = finishing_grid(grid64);
     if (grid64 > 2147483647LL) return CDL_ERR_PARAM;
     const bool one_trip = !want_marg && forward_one_trip(n, k, soft != nullptr);
     int grid = one_trip ? (int)one_trip_grid(n) : (int)grid64;
     MargFinish fin{};
     if (want_marg) {
-        if (!hist_few(grid, p.n_levels)) fin.rows = reinterpret_cast<unsigned long long *>(ws);
+        fin.rows = reinterpret_cast<unsigned long long *>(ws);
         fin.records = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(ws) + hist_bytes(n, p.n_levels));
         fin.tag = next_finish_tag();
         fin.inv_n = 1.0 / ((double)n * (double)(1u << kHistScaleBits));
@@ -1260,24 +1270,30 @@ int launch_quantize_fwd(const float *theta, int64_t n, const cdl_qparams &p,
     if (plan.bins) return launch_soft_fwd(theta, n, p, k, plan, idx, soft, fin, ws, stream);
     const bool want_idx = idx != nullptr, want_soft = soft != nullptr;
     const int jh = (want_soft || want_marg) ? uniform_half_width(p, k) : 0;
+    if (jh && grid > kMaxQuantBlocks) grid = kMaxQuantBlocks;      // (any grid serves: the loop strides over the tensor)
+    const MargForm form = want_marg ? marg_form(grid, n, p, k) : kMargRows;
+    if (form == kMargSlices) {
+        // (the records take the rows' place and, padded to fours, begin to take that of the others, at whose end the slices leave their entropy terms: 6 of 256 KB)
+        fin.records += kRecordBytes / sizeof(unsigned long long) - 2 * kMargCollectors;
+        fin.lg_per = marg_lg_per(grid, p.n_levels);
+    }
     if (jh) {
         const UniConst u = make_uniform(p, jh);
-        if (grid > kMaxQuantBlocks) grid = kMaxQuantBlocks;      // (any grid serves: the loop strides over the tensor)
         int rcu = CDL_OK;
-        if (jh == 4) rcu = launch_fwd_uniform<4>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, u, idx, soft, fin);
-        else if (jh == 8) rcu = launch_fwd_uniform<8>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, u, idx, soft, fin);
-        else rcu = launch_fwd_uniform<16>(want_idx, want_soft, want_marg, grid, stream, theta, n, k, u, idx, soft, fin);
+        if (jh == 4) rcu = launch_fwd_uniform<4>(want_idx, want_soft, want_marg, form, grid, stream, theta, n, k, u, idx, soft, fin);
+        else if (jh == 8) rcu = launch_fwd_uniform<8>(want_idx, want_soft, want_marg, form, grid, stream, theta, n, k, u, idx, soft, fin);
+        else rcu = launch_fwd_uniform<16>(want_idx, want_soft, want_marg, form, grid, stream, theta, n, k, u, idx, soft, fin);
         if (rcu != CDL_OK) return rcu;
     } else
     switch (band_template(k)) {
-        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
-        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
-        default: launch_fwd<0>(want_idx, want_soft, want_marg, one_trip, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 1: launch_fwd<1>(want_idx, want_soft, want_marg, one_trip, form, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 2: launch_fwd<2>(want_idx, want_soft, want_marg, one_trip, form, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 3: launch_fwd<3>(want_idx, want_soft, want_marg, one_trip, form, grid, stream, theta, n, k, idx, soft, fin); break;
+        case 4: launch_fwd<4>(want_idx, want_soft, want_marg, one_trip, form, grid, stream, theta, n, k, idx, soft, fin); break;
+        default: launch_fwd<0>(want_idx, want_soft, want_marg, one_trip, form, grid, stream, theta, n, k, idx, soft, fin); break;
     }
     int rc = check_launch();
-    if (rc == CDL_OK && fin.rows) {
+    if (rc == CDL_OK && want_marg && form == kMargRows) {
         const int level_blocks = (p.n_levels + 7) / 8;
         const int chunks = 64 / level_blocks < kFinChunks ? (64 / level_blocks > 1 ? 64 / level_blocks : 1) : kFinChunks;
         CDL_LAUNCH("marginal_finalize_kernel", stream, marginal_finalize_kernel, dim3(level_blocks, chunks), dim3(kFinThreads), 0,

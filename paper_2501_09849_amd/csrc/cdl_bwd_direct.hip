@@ -909,6 +909,267 @@ void conv_dw_direct_kernel(DirectProduct p, ConvPart cv)
     }
 }
 
+// ---- weight gradients over long contractions: the columns of a block share the digits ----
+//
+// A wave of digit_tile makes the digits of 16 columns of g for its 64 columns of the index operand, and each wave reads g again (131072 x 16 x 144: 80 MB
+// fetched where the operands are 27).  Here a block goes through up to six tiles of 64 columns at once, in rounds of eight steps of 64
+// contraction entries: every wave makes the digits of one step, scaled by the round's largest entry in a row, and multiplies the steps of its part of the round by its own
+// 64 columns.  What is exact, and how, is as in digit_tile; the remainders of a step are multiplied by each wave for its columns, g read once more.
+// What bounds it: the chain of a round - g, the exchange of the rows' largest exponents, the digits through LDS, a wave's steps one after the other - 4.5 us and 1.4 us for
+// each tile beyond two (a block has one compute unit to itself).  dL/dQ(b) by digit_tile / so, with the kernel that adds up the pieces, us: 131072 x 16 x 144  21.9 / 15.7,
+// 131072 x 32 x 144  38.9 / 23.2, 400000 x 24 x 263  158 / 72, 239609 x 29 x 199  88 / 39, 84130 x 21 x 1382  106 / 68.
+// (With a convolution's windows as the operand slower: finding their pixels is on six of eight waves then, 128 x 32 x 32 x 16 -> 16 19.2 / 20.9.  All columns on one wave to
+// a SIMD, without barriers: 288 registers of digit sums and 846 spilled.)
+constexpr int kSharedTiles = 6;
+__host__ __device__ constexpr int shared_parts(int tiles) { return tiles <= 2 ? 4 : tiles <= 4 ? 2 : 1; }      // waves to a tile; at most eight (two to a SIMD, the registers of the digit sums)
+constexpr int kSharedSteps = 8;       // of a round: each of eight waves makes the digits of one
+
+template <int TC>
+__device__ __forceinline__ void shared_tiles(const DirectProduct &p, int row0, int col0, int s0, int s1, double *sums, int8_t *digits)
+{
+    ColumnsOfGMatrix src;
+    constexpr int KS = shared_parts(TC), kMine = kSharedSteps / KS;      // kMine: steps of a round that a wave multiplies
+    __shared__ int exponents[kSharedSteps][16];
+    __shared__ unsigned int rest[kSharedSteps];      // groups of a step that have remainders; bit 16: the whole step in double
+    const int lane = threadIdx.x & 63, q = lane >> 4, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ks = wave / TC, tc = wave - ks * TC;
+    double *const mine = sums + wave * 1024;
+    const bool multiplies = ks < KS;
+    src.init<1, 4>(p, row0, col0 + 64 * tc, lane);
+    const uint32_t sh = (p.cols & 3) != 0 ? src.sh : 0;
+    v4i acc[kDigits][4];
+    int row_sum[kDigits];
+#pragma unroll
+    for (int l = 0; l < kDigits; ++l) {
+        row_sum[l] = 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[l][t] = v4i{0, 0, 0, 0};
+    }
+    int cap = -1, since = 0;
+    bool folded = false;
+    double unit[4], offset_part[4];
+    auto scales = [&]() {
+        double sum = 0.0;
+        if (p.offset) {
+            sum = (double)row_sum[kDigits - 1];
+#pragma unroll
+            for (int l = kDigits - 2; l >= 0; --l) sum = __builtin_fma(sum, 256.0, (double)row_sum[l]);
+            sum += __shfl_xor(sum, 16, 64);
+            sum += __shfl_xor(sum, 32, 64);
+            sum *= (double)p.offset;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            unit[r] = __hiloint2double((1023 - 172 + __shfl(cap, 4 * q + r, 64)) << 20, 0);      // 2^-s
+            offset_part[r] = p.offset ? __shfl(sum, 4 * q + r, 64) : 0.0;
+        }
+    };
+    auto value = [&](int t, int r) {
+        double run = (double)acc[kDigits - 1][t][r];
+#pragma unroll
+        for (int l = kDigits - 2; l >= 0; --l) run = __builtin_fma(run, 256.0, (double)acc[l][t][r]);
+        return (run + offset_part[r]) * unit[r];
+    };
+    auto fold = [&]() {
+        scales();
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                double *m = mine + (4 * t + r) * 64 + lane;
+                const double v = value(t, r);
+                *m = folded ? *m + v : v;
+            }
+        folded = true;
+    };
+
+    auto start = [&](int s) { return max(min(kDigitStep * s, p.kc - kDigitStep), 0); };      // (host: kc >= kDigitStep)
+    float g[4][1][4];
+    uint32_t b[2][4][4];      // two of its steps under way
+    auto load_gradient = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) src.load_g<1, true>(p, start(s) + 16 * u, g[u]);
+    };
+    auto load_columns = [&](int k, int s) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) src.load_index<4, true>(p, start(s) + 16 * u, b[k & 1][u]);
+    };
+    // what a step before it has, of the last one of a contraction that is no multiple of 64, left out
+    auto mask = [&](int s) {
+        if (kDigitStep * s + kDigitStep <= p.kc) return;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) g[u][0][j] = start(s) + 16 * u + 4 * q + j >= kDigitStep * s ? g[u][0][j] : 0.0f;
+    };
+
+    if (s0 + wave < s1) load_gradient(s0 + wave);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (multiplies && s0 + ks + k * KS < s1) load_columns(k, s0 + ks + k * KS);
+    for (int s = s0; s < s1; s += kSharedSteps) {
+        const bool makes = s + wave < s1;
+        float m = 0.0f;
+        if (makes) {
+            mask(s + wave);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                m = largest(m, fabsf(g[u][0][0]), fabsf(g[u][0][1]));
+                m = largest(m, fabsf(g[u][0][2]), fabsf(g[u][0][3]));
+            }
+        }
+        const int E = (int)(max_over_groups(__float_as_uint(m)) >> 23);
+        if (lane < 16) exponents[wave][lane] = E < 255 ? E : 0;      // (a step with an infinity or a NaN has no digits)
+        __syncthreads();
+        int most = 0;
+#pragma unroll
+        for (int w = 0; w < kSharedSteps; ++w) most = max(most, exponents[w][lane & 15]);
+        // (all waves alike)
+        const bool grows = __ballot(most > cap) != 0;
+        if (since > 0 && (grows || since + kSharedSteps > 1024)) {      // (an int32 holds 2048 steps of 64 products of 128 and 128)
+            fold();
+#pragma unroll
+            for (int l = 0; l < kDigits; ++l) {
+                row_sum[l] = 0;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[l][t] = v4i{0, 0, 0, 0};
+            }
+            since = 0;
+        }
+        cap = most > cap ? min(most + 2, 254) : cap;
+        if (makes) {
+            // (see digit_tile)
+            const int whole_from = cap <= p.rounds_to ? 0 : max(cap - 22, 0);
+            auto ordered = [&](int k) { return 2u * __float_as_uint(g[k >> 2][0][k & 3]) - 1u; };
+            const uint32_t limit = whole_from > 0 ? ((uint32_t)whole_from << 24) - 1u : 0u;
+            uint32_t small = ~0u, groups = 0u;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) small = min(small, ordered(k));
+            if (__ballot(small < limit) != 0)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) groups |= __ballot(ordered(k) < limit) != 0 ? 1u << k : 0u;
+            const bool all = __ballot(E == 255) != 0 || __popc(groups) > 12;
+            if (all) groups = 0x1ffffu;
+            if (lane == 0) rest[wave] = groups;
+            const double scale = __hiloint2double((1023 + 172 - cap) << 20, 0);
+            v4i f[kDigits];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                uint32_t d[kDigits];
+                limbs_of4_wide<kDigits>(g[u][0], scale, d);
+#pragma unroll
+                for (int l = 0; l < kDigits; ++l) f[l][u] = all ? 0 : (int)d[l];
+            }
+#pragma unroll
+            for (int l = 0; l < kDigits; ++l) *reinterpret_cast<v4i *>(digits + ((wave * kDigits + l) * 64 + lane) * 16) = f[l];
+        }
+        if (s + kSharedSteps + wave < s1) load_gradient(s + kSharedSteps + wave);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kMine; ++k) {
+            const int w = ks + k * KS, step = s + w;
+            if (!multiplies || step >= s1) break;
+            auto word = [&](int u, int j) { return b[k & 1][u][j] >> sh; };
+            v4i fb[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                uint32_t x[4], c[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j] = word(u, j);
+                transpose4(x, c);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) fb[t][u] = (int)c[t];
+            }
+#pragma unroll
+            for (int l = 0; l < kDigits; ++l) {
+                const v4i fa = *reinterpret_cast<const v4i *>(digits + ((w * kDigits + l) * 64 + lane) * 16);
+                if (p.offset)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) row_sum[l] = __builtin_amdgcn_sdot4(fa[u], 0x01010101, row_sum[l], false);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[l][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb[t], acc[l][t], 0, 0, 0);
+            }
+            ++since;
+            const unsigned int groups = (unsigned int)__builtin_amdgcn_readfirstlane((int)rest[w]);
+            if (groups) {
+                if (!folded) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) mine[i * 64 + lane] = 0.0;
+                    folded = true;
+                }
+                const bool all = groups >> 16;
+                const double unit_of = __hiloint2double((1023 - 172 + cap) << 20, 0), per_unit = __hiloint2double((1023 + 172 - cap) << 20, 0);
+#pragma unroll 1
+                for (int u = 0; u < 4; ++u) {
+                    if (!(groups >> (4 * u) & 15u)) continue;
+                    float v4[1][4];
+                    src.load_g<1, true>(p, start(step) + 16 * u, v4);
+#pragma unroll 1
+                    for (int j = 0; j < 4; ++j) {
+                        if (!(groups >> (4 * u + j) & 1u)) continue;
+                        const float gj = j == 0 ? v4[0][0] : j == 1 ? v4[0][1] : j == 2 ? v4[0][2] : v4[0][3];
+                        double v = start(step) + 16 * u + 4 * q + j >= kDigitStep * step ? (double)gj : 0.0;
+                        if (!all) {
+                            v *= per_unit;
+                            v = (v - __builtin_rint(v)) * unit_of;
+                        }
+                        uint32_t x = 0u;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) x = 4 * u + j == i ? word(i >> 2, i & 3) : x;
+#pragma unroll 1
+                        for (int t = 0; t < 4; ++t) {
+                            const v4d sum = __builtin_amdgcn_mfma_f64_16x16x4f64(v, (double)(((int)(x << (24 - 8 * t)) >> 24) + p.offset), v4d{0.0, 0.0, 0.0, 0.0}, 0, 0, 0);
+                            // (element (row q + 4 r, ...) of that tile)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) mine[(4 * t + q) * 64 + 16 * r + (lane & 15)] += sum[r];
+                        }
+                    }
+                }
+            }
+            if (k + 2 < kMine && step + 2 * KS < s1) load_columns(k, step + 2 * KS);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (multiplies && s + kSharedSteps + ks + k * KS < s1) load_columns(k, s + kSharedSteps + ks + k * KS);
+    }
+    if (multiplies) fold();
+}
+
+constexpr size_t shared_lds(int tiles) { return (size_t)tiles * shared_parts(tiles) * 1024 * sizeof(double) + kSharedSteps * kDigits * 1024; }
+
+template <int TC>
+__global__ __launch_bounds__(kDirThreads)
+void dw_shared_kernel(DirectProduct p, BwdPlan *plan)
+{
+    extern __shared__ __attribute__((aligned(16))) char shared_area[];
+    double *const sums = reinterpret_cast<double *>(shared_area);      // [waves that multiply][1024], then the digits
+    constexpr int KS = shared_parts(TC);
+    if (blockIdx.x == 0 && threadIdx.x == 0) no_limbs(plan);
+    int item = blockIdx.x;
+    const int col0 = item % p.tiles_c * (TC * 64);
+    item /= p.tiles_c;
+    const int row0 = item % p.tiles_r * 16, split = item / p.tiles_r;
+    const int s0 = split * p.steps_per_split, s1 = min(s0 + p.steps_per_split, p.steps);
+    shared_tiles<TC>(p, row0, col0, s0, s1, sums, reinterpret_cast<int8_t *>(sums + TC * KS * 1024));
+    __syncthreads();
+    for (int i = threadIdx.x; i < TC * 256; i += kDirThreads) {
+        const int tc = i >> 8, r = i >> 6 & 3, l = i & 63;
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] += sums[(k * TC + tc) * 1024 + (4 * t + r) * 64 + l];
+        const int row = row0 + 4 * (l >> 4) + r, col = col0 + 64 * tc + 4 * (l & 15);
+        if (row >= p.rows) continue;
+        if (p.splits > 1) {
+            double *o = p.partial + ((int64_t)split * p.rows + row) * p.cols + col;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (col + c < p.cols) o[c] = v[c];
+        } else store_outputs(p, row, col, v);
+    }
+}
+
 // The activation gradient of a convolution; one product per class of input pixels.  THIN: few channels, tiles of 64 pixels
 // x 16 channels (a tile of 16 x 64 would be padding), else 16 x 64.
 struct ConvDxArgs {
@@ -1146,6 +1407,71 @@ double plan_digits(DirectProduct **ps, int n, int max_splits)
     return least;
 }
 
+// Blocks that share digits (dw_shared_kernel): column groups of equal numbers of tiles, pieces of whole rounds; the number of pieces whose time is the least.  Returns that time, us
+// (fitted to 52 layers of 17 to 308 rows, 80 to 2000 columns and 2 to 400 thousand contraction entries).
+double plan_shared(DirectProduct &p, int max_splits, int &tiles)
+{
+    const int64_t all = ceil_div(p.cols, 64);
+    tiles = (int)ceil_div(all, ceil_div(all, kSharedTiles));
+    p.tiles_c = (int)ceil_div(all, tiles);
+    p.tiles_r = (int)ceil_div(p.rows, 16);
+    p.steps = (int)ceil_div(p.kc, kDigitStep);
+    p.narrow = 0;
+    const int64_t per_split = (int64_t)p.tiles_r * p.tiles_c;
+    double least = -1.0;
+    for (int blocks = 1; blocks <= 4; ++blocks) {      // of a compute unit
+        int64_t splits = blocks * kDigitBlocks / per_split;
+        if (splits > max_splits) splits = max_splits;
+        if (splits < 1) splits = 1;
+        const int64_t rounds = ceil_div(ceil_div(p.steps, splits), kSharedSteps);
+        splits = ceil_div(p.steps, rounds * kSharedSteps);
+        double t = (double)ceil_div(splits * per_split, kDigitBlocks) * (3.0 + (4.5 + 1.4 * (tiles - 2)) * (double)rounds);
+        if (splits > 1) t += 5.0 + (double)splits * p.rows * p.cols * 16.0 / 5e6;
+        if (least >= 0.0 && t >= least) continue;
+        least = t;
+        p.steps_per_split = (int)(rounds * kSharedSteps);
+        p.splits = (int)splits;
+    }
+    return least;
+}
+
+// Where they serve: by the two plans' times, of which that of plan_digits does not count what is read several times and is up to 2.2 times too short (36 of the 52 layers; the slowest of these against before
+// 10486 x 264 x 368 29.5 / 30.1, of the others 71132 x 20 x 70 was the better one by 4 %).  A second tile of a few columns is not worth its padding (270320 x 19 x 69 30.5 / 31.7).
+bool shared_serves(const DirectProduct &p, int max_splits)
+{
+    if (p.cols < 80 || p.kc < kDigitStep) return false;
+    DirectProduct now = p, shared = p, *one = &now;
+    int tiles;
+    return plan_shared(shared, max_splits, tiles) < 1.15 * plan_digits(&one, 1, max_splits);
+}
+
+int launch_shared(DirectProduct &p, int max_splits, BwdPlan *plan, hipStream_t stream)
+{
+    int tiles = 0;
+    plan_shared(p, max_splits, tiles);
+    const dim3 grid((unsigned)(p.tiles_r * p.tiles_c * p.splits)), threads(kDirThreads);
+    const size_t lds = shared_lds(tiles);
+#define CDL_SHARED(TC) \
+    do { \
+        const hipError_t e = hipFuncSetAttribute((const void *)dw_shared_kernel<TC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+        if (e != hipSuccess) return hip_failed(e); \
+        CDL_LAUNCH("dw_shared_kernel", stream, dw_shared_kernel<TC>, grid, threads, lds, p, plan); \
+    } while (0)
+    switch (tiles) {
+        case 2: CDL_SHARED(2); break;
+        case 3: CDL_SHARED(3); break;
+        case 4: CDL_SHARED(4); break;
+        case 5: CDL_SHARED(5); break;
+        default: CDL_SHARED(6); break;
+    }
+#undef CDL_SHARED
+    const int rc = check_launch();
+    if (rc != CDL_OK || p.splits == 1) return rc;
+    const int64_t n = (int64_t)p.rows * p.cols;
+    CDL_LAUNCH("direct_reduce_kernel", stream, direct_reduce_kernel<false>, dim3((unsigned)ceil_div(n, 32)), dim3(256), 0, p.partial, p.splits, n, p.delta, p.out, ReduceDiag{});
+    return check_launch();
+}
+
 }  // namespace
 
 static int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
@@ -1246,6 +1572,7 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
     const bool exact = exact_serves(asked * padded_macs(M, N, K), M, N, diag);
     d.a.rounds_to = digits_round_to(d.a, exact);
     d.b.rounds_to = digits_round_to(d.b, exact);
+    if (only_b && d.digits && !diag && d_b_hat && shared_serves(d.b, max_splits)) return launch_shared(d.b, max_splits, plan, stream);
     DirectArgs a{};
     a.plan = plan;
     a.records = reinterpret_cast<unsigned long long *>(records);

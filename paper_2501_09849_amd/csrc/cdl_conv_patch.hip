@@ -20,6 +20,8 @@
 #include "cdl_bwd_plan.h"
 #include "cdl_limbs.h"
 
+#include <type_traits>
+
 namespace cdl {
 
 namespace {
@@ -52,9 +54,12 @@ typedef const PatchArgs __attribute__((address_space(4))) *patch_args_t;
 struct PatchTile { int row0, col0, lo, count; };
 
 template <int L, int WN>
-__device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t, int8_t *lds, double out_scale, float gscale)
+__device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t, int8_t *lds, double out_scale, float gscale, bool few)
 {
     constexpr int TN = 2, ROWS = patch_rows(WN);
+    // The digits and the outputs go before the other block's matrix instructions, which leave issue slots enough: 53 x 19 x 53 x 288 -> 412, 3 x 3 359 -> 353 us, 26 x 55 x 55 x 48 -> 468 170 -> 164.
+    // (A block's k-steps before the other's: 5 - 15 % slower.  Four classes: 97 -> 99.)
+    if (WN != 0) __builtin_amdgcn_s_setprio(2);
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));      // (what the limb counts' code has in common is not moved in front of all of it, where registers are short)
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -106,13 +111,24 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
             to += U * dst_step;
         }
     };
-    if (nc == Np) make_digits(0);      // all channels at once, for all classes
-
     // weights: 1 KB a k-step of 32 entries and tile of 32 columns, in the order of the lanes
     uint32_t bo[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) bo[j] = (uint32_t)min((t.col0 >> 5) + wn * TN + j, (args->C32 >> 5) - 1) * 1024u + (uint32_t)lane * 16u;
     const int half = (lane >> 5) * 16;
+    constexpr int NA = L <= 5 ? 2 : 1, NB = patch_ahead(L);
+    v4i fb[NB][TN];
+    const int nk = idle ? 0 : taps * (nc / 32);
+    PatchWeights weights(0, nc, Np, args->C32, nk);
+    auto load_b = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[buf][j] = *reinterpret_cast<const v4i *>(k.wr + weights.at + bo[j]);
+        weights.next();
+    };
+    // (the first ones on their way while the digits are made: 128 x 7 x 7 x 512 -> 512 82.6 -> 80.7 us, 41 x 51 x 49 x 128 -> 20 51.7 -> 48.7)
+#pragma unroll
+    for (int u = 0; u < NB; ++u) load_b(u);
+    if (nc == Np) make_digits(0);      // all channels at once, for all classes
 
     // (WN = 0: a wave makes its own table)
     for (int i = WN == 0 ? lane : tid; i < (idle ? 0 : taps + 1) * ROWS; i += WN == 0 ? 64 : kPatchThreads) {
@@ -131,24 +147,22 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[l][j][r] = 0;
-    const int arow = wm * 32 + (lane & 31), nk = idle ? 0 : taps * (nc / 32);
+    const int arow = wm * 32 + (lane & 31);
 
     for (int n0 = 0; n0 < Np; n0 += nc) {
-        if (n0 > 0) __syncthreads();
+        if (n0 > 0) {
+            weights = PatchWeights(n0, nc, Np, args->C32, nk);
+#pragma unroll
+            for (int u = 0; u < NB; ++u) load_b(u);
+            __syncthreads();
+        }
         if (nc < Np) make_digits(n0);
         __syncthreads();
 
         // k-steps of 32 entries, tap after tap.  The weights of a step are asked for four steps ahead, the row of LDS two, the digits
         // one (more than four limbs leave registers for less).
-        constexpr int NA = L <= 5 ? 2 : 1, NB = patch_ahead(L);
-        v4i fa[NA][L], fb[NB][TN];
+        v4i fa[NA][L];
         int row[2], at[2];      // a lane's row of a plane, and the step's first channel (put together where they are used: no wait for the table before)
-        PatchWeights weights(n0, nc, Np, args->C32, nk);
-        auto load_b = [&](int buf) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fb[buf][j] = *reinterpret_cast<const v4i *>(k.wr + weights.at + bo[j]);
-            weights.next();
-        };
         int rt = 0, rn = 0;
         auto load_row = [&](int buf) {
             row[buf] = table[rt * ROWS + arow];
@@ -168,12 +182,11 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
 #pragma unroll
                 for (int j = 0; j < TN; ++j) acc[l][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[abuf][l], fb[bbuf][j], acc[l][j], 0, 0, 0);
         };
-#pragma unroll
-        for (int u = 0; u < NB; ++u) load_b(u);
         load_row(0);
         load_row(1);
         if (NA == 2) load_a(0, 0);
         // (a step behind the last one multiplies rows of zeros)
+        if (WN != 0) __builtin_amdgcn_s_setprio(0);
         for (int it = 0; it < nk; it += 4) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -193,6 +206,7 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        if (WN != 0) __builtin_amdgcn_s_setprio(2);
     }
 
     if (idle) return;
@@ -204,18 +218,29 @@ __device__ __forceinline__ void patch_body(patch_args_t args, const PatchTile t,
     const int pixel = m < rows && i < k.Hc && jj < k.Wc ? (b * args->oH + args->step * i + k.oa) * args->oW + args->step * jj + k.oc : -1;
     float *out = args->out;
     const int ecol = t.col0 + wn * TN * 32 + (elane & 31);
+    auto outputs = [&](auto pairs) {
 #pragma unroll
-    for (int rr = 0; rr < 16; ++rr) {
-        const int pix = __shfl(pixel, 4 * (elane >> 5) + 8 * (rr >> 2) + (rr & 3), 64);      // (layout of an accumulator)
-        float *p = out + (int64_t)pix * C + ecol;
+        for (int rr = 0; rr < 16; ++rr) {
+            const int pix = __shfl(pixel, 4 * (elane >> 5) + 8 * (rr >> 2) + (rr & 3), 64);      // (layout of an accumulator)
+            float *p = out + (int64_t)pix * C + ecol;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            double run = (double)acc[L - 1][j][rr];
+            for (int j = 0; j < TN; ++j) {
+                double run;
+                if (L == 4 && pairs.value) {
+                    run = __builtin_fma((double)(256 * acc[L - 1][j][rr] + acc[L - 2][j][rr]), 65536.0, (double)(256 * acc[1][j][rr] + acc[0][j][rr]));
+                } else {
+                    run = (double)acc[L - 1][j][rr];
 #pragma unroll
-            for (int l = L - 2; l >= 0; --l) run = __builtin_fma(run, 256.0, (double)acc[l][j][rr]);
-            if (pix >= 0 && ecol + j * 32 < C) p[j * 32] = (float)(run * out_scale);
+                    for (int l = L - 2; l >= 0; --l) run = __builtin_fma(run, 256.0, (double)acc[l][j][rr]);
+                }
+                if (pix >= 0 && ecol + j * 32 < C) p[j * 32] = (float)(run * out_scale);
+            }
         }
-    }
+    };
+    // (two limbs as one integer: five instructions in double instead of nine.  Not with four classes, whose blocks then all store at a time: 128 x 56 x 56 x 64 -> 128 at stride 2
+    // 95.4 us so, 98.6 with pairs)
+    if (WN != 0 && L == 4 && few) outputs(std::true_type{});
+    else outputs(std::false_type{});
 }
 
 template <int WN>
@@ -253,10 +278,14 @@ void limb_conv_patch_kernel(PatchArgs a)
         const unsigned int *block_max = args->maxima.block_max;
         const int n_max = args->maxima.n_max, n_abs = args->maxima.n_abs;
         unsigned int v[3] = {0u, 0u, 0u};
+        // (the first of each, which are all for most layers, in one trip)
+        const unsigned int *pixel_max = args->maxima.pixel_max + t.lo, *col_abs = args->maxima.col_abs;
+        v[0] = pixel_max[min((int)threadIdx.x, t.count - 1)];
+        v[2] = col_abs[min((int)threadIdx.x, n_abs - 1)];
 #pragma unroll
         for (int u = 0; u < kPatchMaxima / kPatchThreads; ++u) v[1] = max(v[1], block_max[min(u * kPatchThreads + (int)threadIdx.x, n_max - 1)]);
-        for (int i = threadIdx.x; i < n_abs; i += kPatchThreads) v[2] = max(v[2], args->maxima.col_abs[i]);
-        for (int i = threadIdx.x; i < t.count; i += kPatchThreads) v[0] = max(v[0], args->maxima.pixel_max[t.lo + i]);
+        for (int i = kPatchThreads + threadIdx.x; i < n_abs; i += kPatchThreads) v[2] = max(v[2], col_abs[i]);
+        for (int i = kPatchThreads + threadIdx.x; i < t.count; i += kPatchThreads) v[0] = max(v[0], pixel_max[i]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
 #pragma unroll
@@ -286,10 +315,12 @@ void limb_conv_patch_kernel(PatchArgs a)
     const long long scale_bits = finite ? __double_as_longlong(args->delta_w * ldexp(1.0, e + 1 - 8 * L)) : 0x7ff8000000000000ll;
     const double out_scale = __hiloint2double(__builtin_amdgcn_readfirstlane((int)(scale_bits >> 32)), __builtin_amdgcn_readfirstlane((int)scale_bits));
     const float gscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, 8 * L - 1 - e))));
+    // a limb of an output is 128 sum|w| at most: two of them as one integer, 257 times that
+    const bool few = maximum(2) < 65024u;
     switch (L) {
-        case 4: patch_body<4, WN>(args, t, patch_lds, out_scale, gscale); break;
-        case 5: patch_body<5, WN>(args, t, patch_lds, out_scale, gscale); break;
-        default: patch_body<6, WN>(args, t, patch_lds, out_scale, gscale); break;
+        case 4: patch_body<4, WN>(args, t, patch_lds, out_scale, gscale, few); break;
+        case 5: patch_body<5, WN>(args, t, patch_lds, out_scale, gscale, few); break;
+        default: patch_body<6, WN>(args, t, patch_lds, out_scale, gscale, few); break;
     }
 }
 

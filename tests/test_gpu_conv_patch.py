@@ -112,3 +112,21 @@ def test_parts_of_one_step(geom, scale):
 @pytest.mark.parametrize("scale", [1.0, 3.0e4])
 def test_few_pixels_many_channels(geom, scale):
     test_activation_gradient(geom, scale)
+
+
+# four limbs put together in pairs as integers where the largest column sum of |w| leaves room, on both sides of that line: (N taps) 127 = 64770 and 65024, digits of one sign
+@pytest.mark.parametrize("channels,last", [(510, 0), (512, 0), (508, 127)])
+@pytest.mark.parametrize("value", [0.98046875, -0.9960784])
+def test_limb_pairs(channels, last, value):
+    torch = gu.torch_mod()
+    geom = (90, 15, 14, 128, 512, 1, 1, 1, 1)      # (padding: a window matrix of its own, no linear layer)
+    g, _ = _inputs(geom, 1.0)
+    g = torch.where(g.abs() < 1e30, torch.full_like(g, value), g)
+    w = torch.zeros((512, 1, 1, 128), dtype=torch.int8, device="cuda")
+    w[:channels] = 127
+    if last:
+        w[channels:channels + 4] = last
+    step = 2.0 ** -20      # (four limbs)
+    got = _call(g, w, geom, step).double()
+    ref = _reference(g, w, geom, step)
+    assert bool(((got - ref).abs() <= 1e-12 + 2.0 ** -23 * ref.abs()).all())

@@ -119,13 +119,13 @@ def test_few_pixels_many_channels(geom, scale):
 @pytest.mark.parametrize("value", [0.98046875, -0.9960784])
 def test_limb_pairs(channels, last, value):
     torch = gu.torch_mod()
-    geom = (90, 15, 14, 128, 512, 1, 1, 1, 1)      # (padding: a window matrix of its own, no linear layer)
+    geom = (90, 15, 14, 128, 512, 2, 1, 1, 0)
     g, _ = _inputs(geom, 1.0)
     g = torch.where(g.abs() < 1e30, torch.full_like(g, value), g)
-    w = torch.zeros((512, 1, 1, 128), dtype=torch.int8, device="cuda")
-    w[:channels] = 127
+    w = torch.zeros((512, 2, 1, 128), dtype=torch.int8, device="cuda")
+    w[:channels, 0] = 127
     if last:
-        w[channels:channels + 4] = last
+        w[channels:channels + 4, 1] = last
     step = 2.0 ** -20      # (four limbs)
     got = _call(g, w, geom, step).double()
     ref = _reference(g, w, geom, step)

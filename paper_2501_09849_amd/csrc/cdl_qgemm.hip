@@ -304,24 +304,37 @@ __device__ __forceinline__ int lswz(int row) { return (row >> 1) & 7; }
 // took a trip to memory (that size 286 us, without its stores still 252; 100000 x 512 x 128 51 -> 37, 60000 x 1500 x 1024 about 200 -> 160,
 // 65536 x 1024 x 256 63 -> 54).  A step's first fragments are read behind the products of the step before (8192 x 3072 x 3072
 // 101 -> 93).
-constexpr int kFThreads = 512;
-constexpr int kFTile = 256;
-constexpr int kRing = 5, kRingBK = 64, kRingStage = 2 * kFTile * kRingBK, kRingLdsBytes = kRing * kRingStage;
+constexpr int kRingBK = 64;
+// A block of WM x WN waves of TM x TN accumulators each, a ring of RING stages, PER_CU blocks to a compute unit.
+template <int WM_, int WN_, int TM_, int TN_, int RING_, int PER_CU_>
+struct RingShape {
+    static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, RING = RING_, PER_CU = PER_CU_;
+    static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves, kRows = WM * TM * 32, kCols = WN * TN * 32;
+    static constexpr int kStage = (kRows + kCols) * kRingBK, kLds = RING * kStage;
+    static constexpr int kLoadsA = kRows / 16 / kWaves, kLoadsB = kCols / 16 / kWaves;      // of a wave and K-tile, 1 KB each
+    static_assert(kLoadsA * 16 * kWaves == kRows && kLoadsB * 16 * kWaves == kCols && PER_CU * kLds <= 160 << 10, "a wave's loads; LDS");
+};
+using RingWide = RingShape<2, 4, 4, 2, 5, 1>;       // 256 x 256
+// The others, four waves, two blocks to a compute unit: less padding and more blocks where outputs are few or narrow (choose_tiles).
+using RingTall = RingShape<2, 2, 4, 2, 3, 2>;       // 256 x 128
+using RingNarrow = RingShape<4, 1, 2, 2, 4, 2>;     // 256 x 64
+using RingSquare = RingShape<2, 2, 2, 2, 5, 2>;     // 128 x 128
+using RingLow = RingShape<4, 1, 1, 2, 6, 2>;        // 128 x 64
+constexpr int kFTile = RingWide::kRows;
 
-// load i of a wave and operand fills LDS slots (wave * kRingLoads + i) * 64 + lane: row slot / 4, chunk slot % 4
-constexpr int kRingLoads = kFTile / 16 / 8;
-__device__ __forceinline__ int ring_row(int wave, int lane, int i) { return (wave * kRingLoads + i) * 16 + (lane >> 2); }
+// load i of `loads` of a wave and operand fills LDS slots (wave * loads + i) * 64 + lane: row slot / 4, chunk slot % 4
+__device__ __forceinline__ int ring_row(int wave, int lane, int i, int loads) { return (wave * loads + i) * 16 + (lane >> 2); }
 // (sixteen rows read at the same chunk q lie in all sixteen chunks of the 64 banks; with (row >> 1) half the cycles of the reads
 // were conflicts; up to 1 % of the kernel's time)
 __device__ __forceinline__ int ring_swz(int row, int q) { return q ^ ((row >> 2) & 3); }
 __device__ __forceinline__ int ring_chunk(int lane) { return ring_swz(lane >> 2, lane & 3) * 16; }      // (rows 16 apart swizzle alike)
 
 // SOURCE: where a wave's loads come from - tile(m, n, ...) the first K-tile of a tile, issue() the loads of a K-tile and on to the next
-template <bool STREAM, class SOURCE>
+template <class SHAPE, bool STREAM, class SOURCE>
 __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, int nk)
 {
-    constexpr int WN = 4, TM = 4, TN = 2, KS = kRingBK / 32, AHEAD = kRing - 1;
-    constexpr int WL = kRingLoads;
+    constexpr int WN = SHAPE::WN, TM = SHAPE::TM, TN = SHAPE::TN, KS = kRingBK / 32, AHEAD = SHAPE::RING - 1;
+    constexpr int kLoads = SHAPE::kLoadsA + SHAPE::kLoadsB, kStores = TM * TN * 16;      // of a wave: per K-tile, per tile
     extern __shared__ __attribute__((aligned(16))) int8_t flds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -339,7 +352,7 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
         source.tile(m, n, wave, lane);
     };
     auto issue = [&](int stage) {
-        source.issue(flds + stage * kRingStage + wave * WL * 1024);
+        source.issue(flds + stage * SHAPE::kStage, wave);
         if (++load_kt == nk) {
             load_kt = 0;
             load_tile = min(load_tile + each, total - 1);
@@ -350,13 +363,13 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
     int fr[KS];                               // (rows 32 apart swizzle alike)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) fr[ks] = frow * kRingBK + ring_swz(frow, 2 * ks + (lane >> 5)) * 16;
-    const int fa_at = wm * TM * 32 * kRingBK, fb_at = (kFTile + wn * TN * 32) * kRingBK;
+    const int fa_at = wm * TM * 32 * kRingBK, fb_at = (SHAPE::kRows + wn * TN * 32) * kRingBK;
 
     static_assert(KS == 2, "fragments of two k-steps");
     v16i acc[TM][TN];
     v4i fa[2][TM], fb[2][TN];
     auto read = [&](int stage, int ks) {
-        const int8_t *base = flds + stage * kRingStage;
+        const int8_t *base = flds + stage * SHAPE::kStage;
 #pragma unroll
         for (int i = 0; i < TM; ++i) fa[ks][i] = *reinterpret_cast<const v4i *>(base + fa_at + i * 32 * kRingBK + fr[ks]);
 #pragma unroll
@@ -404,7 +417,7 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
             }
     };
     auto epilogue = [&](int tile) {
-        const int m = tile / a.tiles_n, n = tile - m * a.tiles_n, row0 = m * kFTile + wm * TM * 32, col0 = n * kFTile + wn * TN * 32;
+        const int m = tile / a.tiles_n, n = tile - m * a.tiles_n, row0 = m * SHAPE::kRows + wm * TM * 32, col0 = n * SHAPE::kCols + wn * TN * 32;
         const bool full = row0 + TM * 32 <= a.rowsA && col0 + TN * 32 <= a.rowsB, corr = a.corr_col || a.corr_row;
         auto all = [&](auto full_c, auto corr_c) {
             if (a.acc_out) emit(full_c, corr_c, a.acc_out, row0, col0);
@@ -415,7 +428,7 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
         } else {
             if (corr) all(std::false_type{}, std::true_type{});
             else all(std::false_type{}, std::false_type{});
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // (fewer than 128 stores, see below)
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // (fewer than kStores stores, see below)
         }
     };
 
@@ -426,18 +439,18 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 1) * 2 * WL));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 1) * kLoads));
     barrier();
     read(0, 0);
     int stage = 0, kt = 0, tile = first;
     for (int s = 0; s < steps; ++s) {
-        // The next step's loads have landed, so that its first fragments are read behind this one's products; younger are those of two
-        // steps, and where a tile ended since they were asked for its 128 stores or more: loads and stores are counted together, up to 63, in order.
-        if (s >= nk && kt < AHEAD - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(63));
-        else __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 2) * 2 * WL));
+        // The next step's loads have landed, so that its first fragments are read behind this one's products; younger are those of AHEAD - 2
+        // steps, and where a tile ended since they were asked for its kStores stores or more: loads and stores are counted together, up to 63, in order.
+        if (s >= nk && kt < AHEAD - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kStores < 63 ? kStores : 63));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm((AHEAD - 2) * kLoads));
         barrier();                                         // ... for every wave, and every wave has left the stage before
-        const int next = stage + 1 == kRing ? 0 : stage + 1;
-        issue(stage == 0 ? kRing - 1 : stage - 1);
+        const int next = stage + 1 == SHAPE::RING ? 0 : stage + 1;
+        issue(stage == 0 ? SHAPE::RING - 1 : stage - 1);
         read(stage, 1);
         if (kt == 0) multiply(0, std::true_type{});
         else multiply(0, std::false_type{});
@@ -453,38 +466,40 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));              // the loads behind the last step write LDS: done before this wave ends
 }
 
+template <class SHAPE>
 struct MatrixSource {
     const GemmArgs &a;
     const int8_t *src_a, *src_b;             // of the next K-tile (uniform)
-    uint32_t off_a[kRingLoads], off_b[kRingLoads];
+    uint32_t off_a[SHAPE::kLoadsA], off_b[SHAPE::kLoadsB];
     __device__ __forceinline__ void tile(int m, int n, int wave, int lane)
     {
-        src_a = a.A + (int64_t)m * kFTile * a.lda;
-        src_b = a.B + (int64_t)n * kFTile * a.ldb;
+        src_a = a.A + (int64_t)m * SHAPE::kRows * a.lda;
+        src_b = a.B + (int64_t)n * SHAPE::kCols * a.ldb;
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i) {
-            off_a[i] = (uint32_t)min(ring_row(wave, lane, i), a.rowsA - 1 - m * kFTile) * (uint32_t)a.lda + (uint32_t)ring_chunk(lane);
-            off_b[i] = (uint32_t)min(ring_row(wave, lane, i), a.rowsB - 1 - n * kFTile) * (uint32_t)a.ldb + (uint32_t)ring_chunk(lane);
-        }
+        for (int i = 0; i < SHAPE::kLoadsA; ++i)
+            off_a[i] = (uint32_t)min(ring_row(wave, lane, i, SHAPE::kLoadsA), a.rowsA - 1 - m * SHAPE::kRows) * (uint32_t)a.lda + (uint32_t)ring_chunk(lane);
+#pragma unroll
+        for (int i = 0; i < SHAPE::kLoadsB; ++i)
+            off_b[i] = (uint32_t)min(ring_row(wave, lane, i, SHAPE::kLoadsB), a.rowsB - 1 - n * SHAPE::kCols) * (uint32_t)a.ldb + (uint32_t)ring_chunk(lane);
     }
-    __device__ __forceinline__ void issue(int8_t *to)
+    __device__ __forceinline__ void issue(int8_t *stage, int wave)
     {
+        int8_t *const to_a = stage + wave * SHAPE::kLoadsA * 1024, *const to_b = stage + SHAPE::kRows * kRingBK + wave * SHAPE::kLoadsB * 1024;
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_a + off_a[i]), (lptr_t)(to + i * 1024), 16, 0, 0);
+        for (int i = 0; i < SHAPE::kLoadsA; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_a + off_a[i]), (lptr_t)(to_a + i * 1024), 16, 0, 0);
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(to + kFTile * kRingBK + i * 1024), 16, 0, 0);
+        for (int i = 0; i < SHAPE::kLoadsB; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(to_b + i * 1024), 16, 0, 0);
         src_a += kRingBK;
         src_b += kRingBK;
     }
 };
 
-template <bool STREAM>
-__global__ __launch_bounds__(kFThreads, 1)
+template <class SHAPE, bool STREAM>
+__global__ __launch_bounds__(SHAPE::kThreads, SHAPE::PER_CU)
 void qgemm_dma_kernel(GemmArgs a)
 {
-    MatrixSource source{a};
-    ring_tiles<STREAM>(a, source, a.Kc / kRingBK);
+    MatrixSource<SHAPE> source{a};
+    ring_tiles<SHAPE, STREAM>(a, source, a.Kc / kRingBK);
 }
 
 // Contraction lengths that are whole K-tiles, and enough rows: where the rounds of 256 x 256 tiles, one a compute unit, take no longer
@@ -498,25 +513,80 @@ bool dma_serves(int64_t M, int64_t N, int64_t K)
     return here * 100 <= other / 512 * 125 + (rest == 0 ? 0 : rest <= 256 ? 85 : 125);
 }
 
-int64_t ring_grid(int64_t tiles)
+// Which tiles a product of M x N outputs over nk K-tiles of 64 bytes takes.  A form's time, us: its start, its K-tiles through every round of blocks (half: a last round with a block
+// to a compute unit at most), a share for every round, and what its output adds, per megabyte.  Fitted to 260 convolutions and 130 matrix products, each run in every form (off by 5 - 12 %); of the choices six are more
+// than 3 % slower than the staged or wide form that they replace (9 % the worst), and all products together take 0.89 and 0.93 of the time.  us, staged / the choice: convolutions 56 x 56 x 64 -> 64 on 128 images 48.4 / 32.8
+// (narrow), 28 x 28 x 128 -> 128 33.5 / 25.9 (tall), 29 x 18 x 48 -> 148 on 185 36.1 / 24.9 (narrow), 25 x 25 x 448 -> 52 at stride 2 on 138 33.3 / 21.0 (low), 19 x 53 x 288 -> 412 on 53 110 / 89.6 (wide), 26 x 26 x 32 -> 84, 5 x 5,
+// on 229 45.9 / 33.3 (square); matrices 60000 x 128 x 1152 23.7 / 19.1 (square), 982 x 1408 x 1280 11.4 / 8.5 (low), 100352 x 128 x 1152 34.8 / 28.7 (tall).
+enum TileForm { kTileStaged, kTileWide, kTileTall, kTileNarrow, kTileSquare, kTileLow };
+struct TileTime { int rows, cols, per_cu; double start, round, half, share, per_mb; };
+constexpr TileTime kRingTimes[2][5] = {      // matrices, windows; in the order of the forms
+    {{256, 256, 1, 7.1, 0.696, 0.0, 0.0, 0.130}, {256, 128, 2, 5.7, 0.837, 0.549, 0.0, 0.123}, {256, 64, 2, 4.2, 0.675, 0.338, 0.0, 0.113}, {128, 128, 2, 4.6, 0.537, 0.286, 0.0, 0.114}, {128, 64, 2, 4.1, 0.381, 0.207, 0.0, 0.103}},
+    {{256, 256, 1, 8.3, 0.774, 0.0, 0.0, 0.153}, {256, 128, 2, 8.0, 0.870, 0.637, 0.0, 0.130}, {256, 64, 2, 6.5, 0.652, 0.474, 0.0, 0.121}, {128, 128, 2, 6.2, 0.541, 0.424, 0.0, 0.130}, {128, 64, 2, 5.5, 0.406, 0.321, 0.0, 0.129}}};
+constexpr TileTime kStagedTimes[2][2][3] = {      // up to 64 columns, more; 64, 128, 256 rows
+    {{{64, 64, 2, 1.9, 0.386, 0.284, 1.9, 0.025}, {128, 64, 2, 1.4, 0.540, 0.4, 1.4, 0.24}, {256, 64, 2, 5.8, 0.945, 0.986, -5.1, 0.383}}, {{64, 128, 2, 2.1, 0.441, 0.329, 2.1, 0.175}, {128, 128, 2, 3.0, 0.671, 0.49, 3.0, 0.133}, {256, 128, 2, 2.0, 1.075, 0.7, 12.1, 0.003}}},
+    {{{64, 64, 2, 1.9, 0.386, 0.284, 1.9, 0.025}, {128, 64, 2, 2.3, 0.468, 0.35, 2.3, 0.153}, {256, 64, 2, 5.8, 0.945, 0.986, -5.1, 0.383}}, {{64, 128, 2, 2.3, 0.463, 0.367, 2.3, 0.156}, {128, 128, 2, 3.4, 0.726, 0.485, 3.4, 0.094}, {256, 128, 2, 4.2, 1.062, 0.641, 9.1, 0.037}}}};
+
+// least: K-tiles that a block takes the time of in any case (a ring is filled first)
+double tile_time(const TileTime &t, int64_t M, int64_t N, int64_t nk, int least)
+{
+    const int64_t tiles = ((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols), places = 256ll * t.per_cu, rest = tiles % places;
+    const bool half = t.per_cu == 2 && rest > 0 && rest <= 256;
+    const double whole = (double)(tiles / places + (rest > 0 && !half ? 1 : 0)), rounds = whole + (half ? 1.0 : 0.0);
+    const double steps = rounds * (double)nk < least ? least / rounds : (double)nk;
+    return t.start + (whole * t.round + (half ? t.half : 0.0)) * steps + rounds * t.share + 4e-6 * (double)M * (double)N * t.per_mb;
+}
+
+// Rows of a staged tile: as few as give every compute unit one.
+int staged_rows(int64_t M, int64_t N)
+{
+    const int64_t cols = (N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128);
+    const bool few = (M + 255) / 256 * cols < 256 && M > 128;
+    return !few ? 256 : (M + 127) / 128 * cols < 256 ? 64 : 128;
+}
+
+// whole: contractions of whole K-tiles (windows: of taps of whole K-tiles), which the widest tiles take where they are no worse than staged ones.
+TileForm choose_tiles(bool windows, bool whole, int64_t M, int64_t N, int64_t K)
+{
+    // (32-bit offsets inside a tile)
+    if (K >= 1 << 23 || N >= 1 << 27 || (!windows && !whole)) return kTileStaged;
+    constexpr int kRingLeast = 6;
+    const int64_t nk = (K + kRingBK - 1) / kRingBK;
+    const bool wide = whole && dma_serves(M, N, K);
+    const int rows = staged_rows(M, N);
+    TileForm best = wide ? kTileWide : kTileStaged;
+    // (staged tiles of 64 rows, a last round of which is mostly short, are often better than that for windows: 7 x 49 x 49 x 240 -> 24, 5 x 5  35 us, low 42)
+    const double margin = windows && rows == 64 ? 0.85 : 0.92;
+    double least = margin * (wide ? tile_time(kRingTimes[windows][0], M, N, nk, kRingLeast) : tile_time(kStagedTimes[windows][N > 64][rows == 64 ? 0 : rows == 128 ? 1 : 2], M, N, nk, 0));
+    for (int f = 0; f < 5; ++f) {
+        if (f == 4 && !windows && nk < 8) continue;      // (1825 x 694 x 128: staged 5.4, low 8.2)
+        const double t = tile_time(kRingTimes[windows][f], M, N, nk, kRingLeast);
+        if (t < least) { least = t; best = (TileForm)(kTileWide + f); }
+    }
+    return best;
+}
+
+int64_t ring_grid(int64_t tiles, int per_cu)
 {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
         n_cu = 256;
-    return tiles < n_cu ? (tiles + 7) / 8 * 8 : n_cu / 8 * 8;
+    const int64_t places = (int64_t)per_cu * n_cu;
+    return tiles < places ? (tiles + 7) / 8 * 8 : places / 8 * 8;
 }
 
-int launch_gemm_dma(GemmArgs a, hipStream_t stream)
+template <class SHAPE>
+int launch_gemm_ring(GemmArgs a, hipStream_t stream)
 {
-    a.tiles_m = (a.rowsA + kFTile - 1) / kFTile;
-    a.tiles_n = (a.rowsB + kFTile - 1) / kFTile;
+    a.tiles_m = (a.rowsA + SHAPE::kRows - 1) / SHAPE::kRows;
+    a.tiles_n = (a.rowsB + SHAPE::kCols - 1) / SHAPE::kCols;
     const int64_t total = (int64_t)a.tiles_m * a.tiles_n;
     if (total == 0) return CDL_OK;
-    const int64_t grid = ring_grid(total);
-    const auto kernel = stream_output((int64_t)a.rowsA * a.rowsB, a.rowsB, a.y_out) && !a.acc_out ? qgemm_dma_kernel<true> : qgemm_dma_kernel<false>;
-    const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsBytes);
+    const int64_t grid = ring_grid(total, SHAPE::PER_CU);
+    const auto kernel = stream_output((int64_t)a.rowsA * a.rowsB, a.rowsB, a.y_out) && !a.acc_out ? qgemm_dma_kernel<SHAPE, true> : qgemm_dma_kernel<SHAPE, false>;
+    const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, SHAPE::kLds);
     if (e != hipSuccess) return hip_failed(e);
-    CDL_LAUNCH("qgemm_kernel(fwd)", stream, kernel, dim3((unsigned)grid), dim3(kFThreads), kRingLdsBytes, a);
+    CDL_LAUNCH("qgemm_kernel(fwd)", stream, kernel, dim3((unsigned)grid), dim3(SHAPE::kThreads), SHAPE::kLds, a);
     return check_launch();
 }
 
@@ -539,15 +609,21 @@ struct ConvArgs {
     float *y_out;          // [M][N] or null
     float scale;
     const int32_t *corr_col;   // [N] or null: x stored with an offset, x_offset * sum over the window of w[n]
+    // ChunkSource: 128 bytes of zeros; chunks of a tap, and a K-tile's four chunks in whole taps and chunks
+    const int8_t *zero_page;
+    int c16, step_taps, step_in;
+    DivBy by_c16, by_s, by_pq, by_q;
 };
 
 // where output pixel m looks: first input row and column of its window, and the offset of that (possibly
 // virtual) pixel in X
 struct ConvRow { int h0, w0; int64_t off; };
+// BY: with the launch's multipliers (the kernels with direct loads: 2 - 4 % of small layers; the staged one is 3 % slower with them)
+template <bool BY>
 __device__ __forceinline__ ConvRow conv_row(const ConvArgs &a, int m)
 {
     const int pq = a.P * a.Q;
-    const int b = m / pq, rem = m - b * pq, p = rem / a.Q, q = rem - p * a.Q;
+    const int b = BY ? div_by(m, a.by_pq) : m / pq, rem = m - b * pq, p = BY ? div_by(rem, a.by_q) : rem / a.Q, q = rem - p * a.Q;
     ConvRow r;
     r.h0 = p * a.stride - a.pad;
     r.w0 = q * a.stride - a.pad;
@@ -565,20 +641,22 @@ __device__ __forceinline__ void conv_store(const ConvArgs &a, int row, int col, 
 // C a multiple of 64: the tiles of qgemm_dma_kernel, a K-tile being 64 channels of one tap.  Where a row's chunk lies is worked out when the tap
 // changes; inside a tap it moves on by 64 channels, or stays on the padding.  us, against a block for every tile with K-tiles of 128 channels: 256 images of
 // 14 x 14 x 320 -> 320, 3 x 3  102 -> 81;  128 x 28 x 28 x 192 -> 192  76 -> 59;  256 x 14 x 14 x 256 -> 256  44.6 -> 43.0.
+template <class SHAPE>
 struct WindowSource {
+    static constexpr int kLoads = SHAPE::kLoadsA;
     const ConvArgs &a;
     const int8_t *src_b;                     // of the next K-tile (uniform)
-    uint32_t off_b[kRingLoads];
-    int h0[kRingLoads], w0[kRingLoads];      // first input row and column of a row's window, and its first chunk
-    int64_t off[kRingLoads];
+    uint32_t off_b[SHAPE::kLoadsB];
+    int h0[kLoads], w0[kLoads];              // first input row and column of a row's window, and its first chunk
+    int64_t off[kLoads];
     int tr, ts, left;                        // tap of the next K-tile, and K-tiles left in it
-    const int8_t *at[kRingLoads];            // a row's chunk of the next K-tile, or the padding
-    uint32_t on[kRingLoads];
+    const int8_t *at[kLoads];                // a row's chunk of the next K-tile, or the padding
+    uint32_t on[kLoads];
     __device__ __forceinline__ void tap()
     {
         const int64_t tap_off = ((int64_t)tr * a.W + ts) * a.C;
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i) {
+        for (int i = 0; i < kLoads; ++i) {
             const bool inside = (unsigned)(h0[i] + tr) < (unsigned)a.H && (unsigned)(w0[i] + ts) < (unsigned)a.W;
             at[i] = inside ? a.X + (off[i] + tap_off) : a.pad_page;
             on[i] = inside ? kRingBK : 0;
@@ -587,28 +665,30 @@ struct WindowSource {
     }
     __device__ __forceinline__ void tile(int m, int n, int wave, int lane)
     {
-        src_b = a.Wt + (int64_t)n * kFTile * a.Kc;
+        src_b = a.Wt + (int64_t)n * SHAPE::kCols * a.Kc;
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i) {
-            const ConvRow r = conv_row(a, min(m * kFTile + ring_row(wave, lane, i), a.M - 1));
+        for (int i = 0; i < kLoads; ++i) {
+            const ConvRow r = conv_row<true>(a, min(m * SHAPE::kRows + ring_row(wave, lane, i, kLoads), a.M - 1));
             h0[i] = r.h0;
             w0[i] = r.w0;
             off[i] = r.off + ring_chunk(lane);
-            off_b[i] = (uint32_t)min(ring_row(wave, lane, i), a.N - 1 - n * kFTile) * (uint32_t)a.Kc + (uint32_t)ring_chunk(lane);
         }
+#pragma unroll
+        for (int i = 0; i < SHAPE::kLoadsB; ++i)
+            off_b[i] = (uint32_t)min(ring_row(wave, lane, i, SHAPE::kLoadsB), a.N - 1 - n * SHAPE::kCols) * (uint32_t)a.Kc + (uint32_t)ring_chunk(lane);
         tr = ts = 0;
         tap();
     }
-    __device__ __forceinline__ void issue(int8_t *to)
+    __device__ __forceinline__ void issue(int8_t *stage, int wave)
     {
+        int8_t *const to_a = stage + wave * kLoads * 1024, *const to_b = stage + SHAPE::kRows * kRingBK + wave * SHAPE::kLoadsB * 1024;
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i) __builtin_amdgcn_global_load_lds((gptr_t)at[i], (lptr_t)(to + i * 1024), 16, 0, 0);
+        for (int i = 0; i < kLoads; ++i) __builtin_amdgcn_global_load_lds((gptr_t)at[i], (lptr_t)(to_a + i * 1024), 16, 0, 0);
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i)
-            __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(to + kFTile * kRingBK + i * 1024), 16, 0, 0);
+        for (int i = 0; i < SHAPE::kLoadsB; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_b + off_b[i]), (lptr_t)(to_b + i * 1024), 16, 0, 0);
         src_b += kRingBK;
 #pragma unroll
-        for (int i = 0; i < kRingLoads; ++i) at[i] += on[i];
+        for (int i = 0; i < kLoads; ++i) at[i] += on[i];
         if (--left == 0) {
             if (++ts == a.S) { ts = 0; ++tr; }
             tap();                           // (behind the last tap: the next tile follows, or nobody loads from there)
@@ -616,16 +696,72 @@ struct WindowSource {
     }
 };
 
-template <bool STREAM>
-__global__ __launch_bounds__(kFThreads, 1)
+// Any C that is a multiple of 16: a lane's chunk of a K-tile, the same of all its rows, lies in a tap of its own.  What lies behind the contraction in the
+// last K-tile reads as zeros of x and any weights.
+template <class SHAPE>
+struct ChunkSource {
+    static constexpr int kLoads = SHAPE::kLoadsA;
+    const ConvArgs &a;
+    const int8_t *src_b;                     // (uniform)
+    uint32_t row_b[SHAPE::kLoadsB];
+    int h0[kLoads], w0[kLoads];
+    int64_t off[kLoads];
+    int chunk, tap, in_tap;                  // a lane's chunk of the contraction, its tap and place in it
+    __device__ __forceinline__ void tile(int m, int n, int wave, int lane)
+    {
+        src_b = a.Wt + (int64_t)n * SHAPE::kCols * a.Kc;
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const ConvRow r = conv_row<true>(a, min(m * SHAPE::kRows + ring_row(wave, lane, i, kLoads), a.M - 1));
+            h0[i] = r.h0;
+            w0[i] = r.w0;
+            off[i] = r.off;
+        }
+#pragma unroll
+        for (int i = 0; i < SHAPE::kLoadsB; ++i) row_b[i] = (uint32_t)min(ring_row(wave, lane, i, SHAPE::kLoadsB), a.N - 1 - n * SHAPE::kCols) * (uint32_t)a.Kc;
+        chunk = ring_chunk(lane) / 16;
+        tap = div_by(chunk, a.by_c16);
+        in_tap = chunk - tap * a.c16;
+    }
+    __device__ __forceinline__ void issue(int8_t *stage, int wave)
+    {
+        int8_t *const to_a = stage + wave * kLoads * 1024, *const to_b = stage + SHAPE::kRows * kRingBK + wave * SHAPE::kLoadsB * 1024;
+        const int tr = div_by(tap, a.by_s), ts = tap - tr * a.S;
+        const bool there = tap < a.R * a.S;
+        const int64_t tap_off = (int64_t)(tr * a.W + ts) * a.C + in_tap * 16;
+        const int8_t *const outside = there ? a.pad_page : a.zero_page;
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const bool inside = there && (unsigned)(h0[i] + tr) < (unsigned)a.H && (unsigned)(w0[i] + ts) < (unsigned)a.W;
+            __builtin_amdgcn_global_load_lds((gptr_t)(inside ? a.X + (off[i] + tap_off) : outside), (lptr_t)(to_a + i * 1024), 16, 0, 0);
+        }
+        const uint32_t at_b = there ? (uint32_t)chunk * 16u : 0u;
+#pragma unroll
+        for (int i = 0; i < SHAPE::kLoadsB; ++i) __builtin_amdgcn_global_load_lds((gptr_t)(src_b + (row_b[i] + at_b)), (lptr_t)(to_b + i * 1024), 16, 0, 0);
+        chunk += kRingBK / 16;
+        tap += a.step_taps;
+        in_tap += a.step_in;
+        const bool over = in_tap >= a.c16;
+        tap += over ? 1 : 0;
+        in_tap -= over ? a.c16 : 0;
+    }
+};
+
+template <class SHAPE, bool STREAM, bool CHUNKS>
+__global__ __launch_bounds__(SHAPE::kThreads, SHAPE::PER_CU)
 void qconv_dma_kernel(ConvArgs a)
 {
     GemmArgs out{};
     out.rowsA = a.M; out.rowsB = a.N; out.ldc = a.N;
     out.tiles_m = a.tiles_m; out.tiles_n = a.tiles_n;
     out.acc_out = a.acc_out; out.y_out = a.y_out; out.scale = a.scale; out.corr_col = a.corr_col;
-    WindowSource source{a};
-    ring_tiles<STREAM>(out, source, a.Kc / kRingBK);
+    if constexpr (CHUNKS) {
+        ChunkSource<SHAPE> source{a};
+        ring_tiles<SHAPE, STREAM>(out, source, (a.Kc + kRingBK - 1) / kRingBK);
+    } else {
+        WindowSource<SHAPE> source{a};
+        ring_tiles<SHAPE, STREAM>(out, source, a.Kc / kRingBK);
+    }
 }
 
 // Any C that is a multiple of 16: the structure of qgemm_kernel (256 x 128 tile, 64-byte K steps staged through
@@ -663,7 +799,7 @@ void qconv_kernel(ConvArgs a)
     for (int i = 0; i < LA; ++i) {
         const int s = tid + kGemmThreads * i, row = s >> 2;
         qa[i] = swz(row, s & 3);
-        xr[i] = conv_row(a, min(tile_m * BM + row, a.M - 1));
+        xr[i] = conv_row<false>(a, min(tile_m * BM + row, a.M - 1));
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
@@ -2335,14 +2471,18 @@ int launch_qgemm_fwd(const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_
     }
     g.acc_out = acc; g.y_out = y; g.ldc = N;
     g.scale = delta_a * delta_b;
-    if (!ragged && dma_serves(M, N, g.Kc)) return launch_gemm_dma(g, stream);
-    // (up to 64 output columns: tiles 64 columns wide, so that half of a wider one is not padding; fewer tiles of 256
-    // rows than compute units: tiles of 128 rows, twice as many blocks)
-    const bool few = (int64_t)((M + 255) / 256) * ((N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128)) < 256 && M > 128;
-    // (and of 64 where tiles of 128 are too few)
-    const bool fewer = few && (int64_t)((M + 127) / 128) * ((N + (N <= 64 ? 63 : 127)) / (N <= 64 ? 64 : 128)) < 256;
-    if (N <= 64) return fewer ? launch_gemm<1, 1>(g, ragged, stream) : few ? launch_gemm<2, 1>(g, ragged, stream) : launch_gemm<4, 1>(g, ragged, stream);
-    return fewer ? launch_gemm<1, 2>(g, ragged, stream) : few ? launch_gemm<2, 2>(g, ragged, stream) : launch_gemm<4, 2>(g, ragged, stream);
+    switch (choose_tiles(false, !ragged && g.Kc % kRingBK == 0, M, N, g.Kc)) {
+        case kTileWide: return launch_gemm_ring<RingWide>(g, stream);
+        case kTileTall: return launch_gemm_ring<RingTall>(g, stream);
+        case kTileNarrow: return launch_gemm_ring<RingNarrow>(g, stream);
+        case kTileSquare: return launch_gemm_ring<RingSquare>(g, stream);
+        case kTileLow: return launch_gemm_ring<RingLow>(g, stream);
+        case kTileStaged: break;
+    }
+    // (up to 64 output columns: tiles 64 columns wide, so that half of a wider one is not padding)
+    const int rows = staged_rows(M, N);
+    if (N <= 64) return rows == 64 ? launch_gemm<1, 1>(g, ragged, stream) : rows == 128 ? launch_gemm<2, 1>(g, ragged, stream) : launch_gemm<4, 1>(g, ragged, stream);
+    return rows == 64 ? launch_gemm<1, 2>(g, ragged, stream) : rows == 128 ? launch_gemm<2, 2>(g, ragged, stream) : launch_gemm<4, 2>(g, ragged, stream);
 }
 
 int launch_qgemm_quantize_fwd(const float *x, const cdl_qparams &p, const int8_t *b_idx, int32_t M, int32_t N, int32_t K,
@@ -2534,6 +2674,27 @@ size_t qconv_fwd_workspace_bytes(int32_t N, int32_t x_offset)
     return x_offset != 0 ? 256 + align_up((size_t)N * sizeof(int32_t), 256) : 0;
 }
 
+template <class SHAPE>
+static int launch_conv_ring(ConvArgs a, hipStream_t stream)
+{
+    a.tiles_m = (a.M + SHAPE::kRows - 1) / SHAPE::kRows;
+    a.tiles_n = (a.N + SHAPE::kCols - 1) / SHAPE::kCols;
+    const int64_t grid = ring_grid((int64_t)a.tiles_m * a.tiles_n, SHAPE::PER_CU);
+    const bool stream_out = stream_output((int64_t)a.M * a.N, a.N, a.y_out) && !a.acc_out, chunks = a.C % kRingBK != 0;
+    if (chunks) {
+        const int rc = conv_zero_page_ptr(&a.zero_page);
+        if (rc != CDL_OK) return rc;
+        a.step_taps = kRingBK / 16 / a.c16;
+        a.step_in = kRingBK / 16 % a.c16;
+    }
+    const auto kernel = chunks ? (stream_out ? qconv_dma_kernel<SHAPE, true, true> : qconv_dma_kernel<SHAPE, false, true>)
+                               : (stream_out ? qconv_dma_kernel<SHAPE, true, false> : qconv_dma_kernel<SHAPE, false, false>);
+    const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, SHAPE::kLds);
+    if (e != hipSuccess) return hip_failed(e);
+    CDL_LAUNCH("qconv_kernel(fwd)", stream, kernel, dim3((unsigned)grid), dim3(SHAPE::kThreads), SHAPE::kLds, a);
+    return check_launch();
+}
+
 int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_t H, int32_t W, int32_t C, int32_t N,
                      int32_t R, int32_t S, int32_t stride, int32_t pad, float delta_x, float delta_w, int32_t x_offset,
                      int32_t *acc, float *y, void *ws, hipStream_t stream)
@@ -2545,6 +2706,11 @@ int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_
     a.Q = (W + 2 * pad - S) / stride + 1;
     a.M = B * a.P * a.Q;
     a.Kc = R * S * C;
+    a.by_pq = make_div_by((uint32_t)a.P * (uint32_t)a.Q);
+    a.by_q = make_div_by((uint32_t)a.Q);
+    a.c16 = C / 16;
+    a.by_c16 = make_div_by((uint32_t)a.c16);
+    a.by_s = make_div_by((uint32_t)S);
     a.acc_out = acc; a.y_out = y;
     a.scale = delta_x * delta_w;
     if ((int64_t)a.M * N == 0) return CDL_OK;
@@ -2564,31 +2730,21 @@ int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_
     }
     const uint32_t pb = (uint32_t)(uint8_t)(int8_t)(-x_offset);
     a.pad_word = (int)(pb | (pb << 8) | (pb << 16) | (pb << 24));
-    if (C % kRingBK == 0 && dma_serves(a.M, N, a.Kc)) {
-        a.tiles_m = (a.M + kFTile - 1) / kFTile;
-        a.tiles_n = (N + kFTile - 1) / kFTile;
-        const int64_t grid = ring_grid((int64_t)a.tiles_m * a.tiles_n);
-        const auto kernel = stream_output((int64_t)a.M * N, N, y) && !acc ? qconv_dma_kernel<true> : qconv_dma_kernel<false>;
-        const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kRingLdsBytes);
-        if (e != hipSuccess) return hip_failed(e);
-        CDL_LAUNCH("qconv_kernel(fwd)", stream, kernel, dim3((unsigned)grid), dim3(kFThreads), kRingLdsBytes, a);
-        return check_launch();
+    switch (choose_tiles(true, C % kRingBK == 0, a.M, N, a.Kc)) {
+        case kTileWide: return launch_conv_ring<RingWide>(a, stream);
+        case kTileTall: return launch_conv_ring<RingTall>(a, stream);
+        case kTileNarrow: return launch_conv_ring<RingNarrow>(a, stream);
+        case kTileSquare: return launch_conv_ring<RingSquare>(a, stream);
+        case kTileLow: return launch_conv_ring<RingLow>(a, stream);
+        case kTileStaged: break;
     }
-    // (tiles of 256 x 128, or 256 x 64 for up to 64 output channels)
-    // (fewer such tiles than compute units: 128 rows per tile, twice as many blocks)
-    const int BN = N <= 64 ? 64 : 128;
-    const bool few = (int64_t)((a.M + 255) / 256) * ((N + BN - 1) / BN) < 256 && a.M > 128;
-    const bool fewer = few && (int64_t)((a.M + 127) / 128) * ((N + BN - 1) / BN) < 256;
-    const int BM = fewer ? 64 : few ? 128 : 256;
+    const int BN = N <= 64 ? 64 : 128, BM = staged_rows(a.M, N);
     a.tiles_m = (a.M + BM - 1) / BM;
     a.tiles_n = (N + BN - 1) / BN;
     const int64_t grid = ((int64_t)a.tiles_m * a.tiles_n + 7) / 8 * 8;
-    if (N <= 64 && fewer) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<1, 1>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
-    else if (fewer) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<1, 2>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
-    else if (N <= 64 && few) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<2, 1>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
-    else if (N <= 64) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<4, 1>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
-    else if (few) CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<2, 2>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
-    else CDL_LAUNCH("qconv_kernel(fwd)", stream, (qconv_kernel<4, 2>), dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
+    const auto kernel = N <= 64 ? (BM == 64 ? qconv_kernel<1, 1> : BM == 128 ? qconv_kernel<2, 1> : qconv_kernel<4, 1>)
+                                : (BM == 64 ? qconv_kernel<1, 2> : BM == 128 ? qconv_kernel<2, 2> : qconv_kernel<4, 2>);
+    CDL_LAUNCH("qconv_kernel(fwd)", stream, kernel, dim3((unsigned)grid), dim3(kGemmThreads), 0, a);
     return check_launch();
 }
 

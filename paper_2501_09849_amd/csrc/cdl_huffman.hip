@@ -180,11 +180,13 @@ __device__ __forceinline__ void huffman_finish(unsigned long long *key /* [kQueu
     }
 }
 
-// FEW: the last block adds the rows, as records of a count and its check word (cdl_finish.h).
+// FEW: the last block adds the rows.  A record is four counts of 16 bits (a block has 2^15 entries and the 15 last ones at most) and a check word (cdl_finish.h): 1 KB a block, where a check word for
+// every count was 4.  us of a call,
+// with that and one trip's loads under way / so: 255 levels 131 K entries 12.8 / 11.4, 1 M 16.5 / 13.4, 2 M 20.4 / 14.8, 3 levels 2 M 15.6 / 9.7.
 template <bool FEW>
 __global__ __launch_bounds__(kHistThreads)
 void index_hist_kernel(const int8_t *__restrict__ idx, int64_t n, unsigned int *__restrict__ rows /* [gridDim.x][256] */,
-                       unsigned long long *records /* [gridDim.x][256][2] */, unsigned long long tag, HuffmanOut out)
+                       unsigned long long *records /* [gridDim.x][64][2] */, unsigned long long tag, HuffmanOut out)
 {
     __shared__ __attribute__((aligned(16))) unsigned int hist[kHistThreads / 64][256 * kHistCopies];
     for (int i = threadIdx.x; i < (kHistThreads / 64) * 256 * kHistCopies / 4; i += kHistThreads)
@@ -193,13 +195,21 @@ void index_hist_kernel(const int8_t *__restrict__ idx, int64_t n, unsigned int *
     unsigned int *mine = &hist[threadIdx.x >> 6][threadIdx.x & (kHistCopies - 1)];
     const int64_t n16 = n >> 4;
     const int64_t stride = (int64_t)gridDim.x * kHistThreads;
-    for (int64_t v = (int64_t)blockIdx.x * kHistThreads + threadIdx.x; v < n16; v += stride) {
-        const uint4 w = reinterpret_cast<const uint4 *>(idx)[v];
-        const unsigned int ws[4] = {w.x, w.y, w.z, w.w};
+    constexpr int U = FEW ? 4 : 1;      // trips whose loads are under way together (grids that leave rows: 2.36 M entries 13.8 us with one, 14.1 with four)
+    for (int64_t v = (int64_t)blockIdx.x * kHistThreads + threadIdx.x; v < n16; v += U * stride) {
+        uint4 w[U];
 #pragma unroll
-        for (int d = 0; d < 4; ++d)
+        for (int u = 0; u < U; ++u)
+            if (u == 0 || v - (int)threadIdx.x + u * stride < n16) w[u] = reinterpret_cast<const uint4 *>(idx)[v + u * stride < n16 ? v + u * stride : v];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) atomicAdd(mine + ((ws[d] >> (8 * b)) & 0xffu) * kHistCopies, 1u);
+        for (int u = 0; u < U; ++u) {
+            if (u > 0 && v + u * stride >= n16) break;
+            const unsigned int ws[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) atomicAdd(mine + ((ws[d] >> (8 * b)) & 0xffu) * kHistCopies, 1u);
+        }
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
         for (int64_t e = n16 << 4; e < n; ++e) atomicAdd(mine + (unsigned int)(uint8_t)idx[e] * kHistCopies, 1u);
@@ -214,21 +224,23 @@ void index_hist_kernel(const int8_t *__restrict__ idx, int64_t n, unsigned int *
         return;
     }
     if (blockIdx.x != gridDim.x - 1) {
-        unsigned long long *r = records + 2 * ((size_t)blockIdx.x * 256 + threadIdx.x);
-        device_store(r, s);
-        device_store(r + 1, s ^ tag);
+        unsigned long long four = (unsigned long long)s << (16 * (threadIdx.x & 3));
+        four |= lane_xor<1>(four);
+        four |= lane_xor<2>(four);
+        if ((threadIdx.x & 3) < 2) device_store(records + 2 * ((size_t)blockIdx.x * 64 + (threadIdx.x >> 2)) + (threadIdx.x & 1), (threadIdx.x & 1) ? four ^ tag : four);
         return;
     }
-    unsigned long long total = s;
-    const int others = (int)gridDim.x - 1;
-    for (int b = 0; b < others; b += 8) {
+    // wave w: rows w, w + 4, .., a lane four counts
+    const int others = (int)gridDim.x - 1, lane = threadIdx.x & 63;
+    unsigned int sum[4] = {0u, 0u, 0u, 0u};
+    for (int b = threadIdx.x >> 6; b < others; b += 32) {
         unsigned long long v[8];
         bool waiting = true;
         while (waiting) {
             unsigned long long c[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const unsigned long long *r = records + 2 * ((size_t)(b + u < others ? b + u : b) * 256 + threadIdx.x);
+                const unsigned long long *r = records + 2 * ((size_t)(b + 4 * u < others ? b + 4 * u : b) * 64 + lane);
                 v[u] = device_load(r);
                 c[u] = device_load(r + 1);
             }
@@ -238,10 +250,21 @@ void index_hist_kernel(const int8_t *__restrict__ idx, int64_t n, unsigned int *
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (b + u < others) {
-                total += v[u];
-                device_store(records + 2 * ((size_t)(b + u) * 256 + threadIdx.x) + 1, v[u]);
+            if (b + 4 * u < others) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += (unsigned int)(v[u] >> (16 * e)) & 0xffffu;
+                device_store(records + 2 * ((size_t)(b + 4 * u) * 64 + lane) + 1, v[u]);      // (spoilt, for a replay)
             }
+    }
+    unsigned long long total = s;
+    if (others > 0) {
+        __syncthreads();      // (the histogram has been read)
+        unsigned int *const parts = &hist[0][0] + 2 * kQueue * 2;      // behind the queues
+#pragma unroll
+        for (int e = 0; e < 4; ++e) parts[(threadIdx.x >> 6) * 256 + 4 * lane + e] = sum[e];
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kHistThreads / 64; ++w) total += parts[w * 256 + threadIdx.x];
     }
     __syncthreads();
     unsigned long long *key = reinterpret_cast<unsigned long long *>(&hist[0][0]);
@@ -289,15 +312,23 @@ void huffman_kernel(const unsigned int *__restrict__ rows, int nrows, HuffmanOut
     huffman_finish<kHuffThreads>(key, sorted, out);
 }
 
-// Up to this many blocks the histogram's last block finishes the job (all of them: 2 M entries).
+// Up to this many blocks the histogram's last block finishes the job (all of them: 2 M entries; 2.36 M of 255 levels in one launch 15.5 us, in two 13.8).
 constexpr int kHistFewBlocks = 64;
 
+int64_t hist_blocks_of_eight(int64_t n)      // trips
+{
+    const int64_t b = (n / 16 + (int64_t)kHistThreads * 8 - 1) / ((int64_t)kHistThreads * 8);
+    return b < 1 ? 1 : b > kHistMaxBlocks ? kHistMaxBlocks : b;
+}
+
+// Small tensors: as few trips as up to 64 blocks leave (the workspace has room for four times the blocks of eight).  Not the smallest: 20 K entries 6.7 us in one block, 7.0 in five.
 int hist_blocks(int64_t n)
 {
-    int64_t b = (n / 16 + (int64_t)kHistThreads * 8 - 1) / ((int64_t)kHistThreads * 8);
-    if (b < 1) b = 1;
-    if (b > kHistMaxBlocks) b = kHistMaxBlocks;
-    return (int)b;
+    const int64_t eight = hist_blocks_of_eight(n), two = 4 * eight, one = (n / 16 + kHistThreads - 1) / kHistThreads;
+    int64_t b = two < one ? two : one;
+    if (b > kHistFewBlocks) b = kHistFewBlocks;
+    if (n < 65536) return (int)eight;
+    return (int)(b > eight ? b : eight);
 }
 
 }  // namespace
@@ -305,7 +336,7 @@ int hist_blocks(int64_t n)
 size_t huffman_workspace_bytes(int64_t n)
 {
     // (never less than a smaller tensor needs)
-    const size_t blocks = (size_t)hist_blocks(n), few = blocks < kHistFewBlocks ? blocks : kHistFewBlocks;
+    const size_t blocks = (size_t)hist_blocks_of_eight(n), few = blocks < kHistFewBlocks ? blocks : kHistFewBlocks;
     const size_t records = few * 256 * 2 * sizeof(unsigned long long), rows = blocks * 256 * sizeof(unsigned int);
     return records > rows ? records : rows;
 }

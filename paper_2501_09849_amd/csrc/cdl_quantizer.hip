@@ -563,9 +563,22 @@ void quantize_fwd_uniform_kernel(const float *__restrict__ theta, int64_t n, QCo
         }
         __syncthreads();
         unsigned long long own = 0ull;
+        // Every thread adds up one level over every kParts-th row (a wave reads consecutive words) into the first of them, which
+        // nobody else reads; then a thread per level, the kParts sums.  One thread per level over all rows is a chain of 256 reads
+        // and additions.  us, forward pass at alpha step^2 of 0.008 (31 levels), 0.037 (15) and 0.2 (7), that / this: 1000 entries of 31 levels 7.3 / 6.2, 8000 10.9 / 9.6, 131072 11.9 / 10.6,
+        // 2 M 28.4 / 26.5; of 15 levels 131072 9.5 / 8.5; of 7 levels 9.0 / 8.0.
+        constexpr int kParts = kUniThreads / LS;
+        if ((int)threadIdx.x < kParts * LS) {
+            double part = 0.0;
+#pragma unroll 4
+            for (int t = threadIdx.x; t < kUniThreads * LS; t += kParts * LS) part += uni_lds[t];
+            uni_lds[threadIdx.x] = part;
+        }
+        __syncthreads();
         if ((int)threadIdx.x < k.n_levels) {
             double tot = 0.0;
-            for (int t = 0; t < kUniThreads; ++t) tot += uni_lds[(size_t)t * LS + threadIdx.x];
+#pragma unroll
+            for (int t = 0; t < kParts; ++t) tot += uni_lds[(size_t)t * LS + threadIdx.x];
             own = (unsigned long long)__double2ll_rn(tot * (double)(1u << kHistScaleBits));
         }
         marginal_end<kUniThreads, FORM>(own, k.n_levels, fin);

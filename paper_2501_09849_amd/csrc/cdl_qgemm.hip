@@ -1686,74 +1686,134 @@ void limb_reduce_kernel(const double *__restrict__ partial, int splits, int64_t 
 
 // dL/dQ(a) for a very short contraction (N <= 32: the first stages of a small CNN have 16 or 32 output
 // channels): d_a_hat[m][k] = delta_b * sum_n g[m][n] * b_idx[n][k].  One K-tile of the limb kernel would be
-// at least three quarters padding there; here a block takes 128 or 64 rows of g (kept in LDS as doubles), a thread
-// C neighbouring output columns, whose N index values each it keeps in registers as doubles, and every output
-// is a chain of N fused multiply-adds in double: products of a float and an int8 are exact in double and N <= 32
-// additions round at 2^-53 relative.  The threads of a block are spread over (group of C columns, row group):
-// with one column per thread and 256 columns per block, 144 columns (workload 2) left 112 threads of every
-// block idle (35 us; 28 us now); C columns per thread use each value read from LDS C times and load the C index
-// bytes of a row of b_idx as one word.
+// at least three quarters padding there; here every output is a chain of N multiply-adds in double on the matrix cores: products of a
+// float and an int8 are exact in double and N <= 32 additions round at 2^-53 relative.
+// A wave keeps the index values of up to C tiles of 16 columns in registers as doubles and goes over tiles of 16 rows, the entries of g of the next one
+// under way.  Quarter q of the wave holds the contraction entries 4 q to 4 q + 3 (and 16 more on), so that a lane's part of a row of g is one load of 16 bytes
+// and nothing of the operands passes through LDS.
+// Bound by the stores.  us, a thread per two or four columns with the rows of g in LDS, whose reads took as long as the additions / this: 131072 x 16 x 144 (rows, contraction, columns) 26.1 / 20.7,
+// 131072 x 32 x 288 136 / 50, 500000 x 32 x 64 186 / 44, 60000 x 16 x 576 53 / 32, 1000 x 16 x 8000 36 / 16, 262144 x 16 x 16 16.1 / 9.5.
 constexpr int kDirectMaxN = 32;
-constexpr int64_t kDirectMinOutputs = 1 << 22;
-constexpr int direct_rows(int nn) { return 2048 / nn; }     // rows of g per block: 16 KiB of LDS as doubles
+// From so many outputs on; below, bwd_direct_kernel.  Alone, that / this: 16 entries, 1.05 M outputs 5.3 / 6.9 us, 2.4 M 12.6 / 8.0, 3.1 M 12.9 / 10.7, 3.5 M 23.6 / 9.2; 32 entries, 1.05 M 7.3 / 6.9, 2.4 M 13.1 / 9.5.  Where the weight gradient
+// is asked for as well, that kernel makes both in one launch: 2.4 M 15.9 / 20.2, 3.1 M 13.6 / 22.2 (3.5 M in 131072 rows 32.6 / 20.6).
+constexpr int64_t direct_min_outputs(bool both) { return both ? 1 << 22 : 1 << 21; }
+constexpr int direct_tiles(int nn) { return nn == 16 ? 10 : 4; }     // tiles of 16 columns per wave: 80 and 64 registers of index values
 
-template <int NN, int C>
-__global__ __launch_bounds__(256)
-void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_idx, int M, int N, int K,
-                      double delta_b, double b_offset, float *__restrict__ out, int vec_store, BwdPlan *plan /* null: another product follows */)
+// How the outputs are stored.  kDaWords (rows of whole words of four columns; the entry points take aligned tensors only): the index operand comes first in the product and column 4 (i & 3) + (i >> 2) of a tile is its row i, a lane then has
+// four neighbouring outputs.  kDaScalars: g first, 16 neighbouring columns per store.  Both write pieces of 64 bytes.  kDaRows, kDaFlat: through LDS and from there as they lie in memory (kDaFlat: rows of any
+// length, where a wave has all columns); serial in a wave, but results that don't fit the memory-side cache of 256 MB are written at 4 instead of 2.6 TB/s.
+// us, pieces / through LDS: 16 entries, 144 columns, 131072 rows 20.7 / 24.9, 400000 (58 M outputs) 47 / 57, 460000 (66 M) 94 / 72, 1048576 222 / 144; 32 entries, 64 columns, 1 M rows (64 M) 88 / 98; 16 entries, 576 columns, 120000 rows (69 M) 71 / 64;
+// rows of any length: 130 columns, 33333 rows (4.3 M) 15.0 / 16.1, 147, 131072 (19 M) 27.3 / 24.7, 75, 600000 (45 M) 50 / 45, 2 M rows 231 / 161.
+enum DaStore { kDaWords, kDaScalars, kDaRows, kDaFlat };
+bool direct_staged(int64_t outputs, bool words) { return outputs >= (words ? 65000000 : 1 << 24); }
+// Waves: two per SIMD (four: 131072 x 16 x 144 20.7 / 21.5, 460000 rows through LDS 72 / 74), four where their tiles in LDS leave room and a trip is short (1 M x 32 x 48 82 / 74, 3 M x 16 x 27 112 / 98).
+int direct_waves(bool staged, int col_tiles) { return staged && col_tiles <= 5 ? 4096 : 2048; }
+
+template <int NN, DaStore STORE>
+__global__ __launch_bounds__(256, 4)
+void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_idx, int M, int N, int K, int col_tiles /* per wave */, int blocks /* per group of them */,
+                      double delta_b, double b_offset, float *__restrict__ out, BwdPlan *plan /* null: another product follows */)
 {
-    constexpr int kRows = direct_rows(NN);
-    __shared__ double gs[kRows][NN];
-    if (plan && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) no_limbs(plan);
-    const int row0 = blockIdx.x * kRows;
-    const int rows = min(kRows, M - row0);
-    const int groups_total = (K + C - 1) / C;              // groups of C columns
-    const int gpb = min(groups_total, 256);                // of them per block
-    const int row_groups = 256 / gpb;
-    const int cg = blockIdx.y * gpb + (int)threadIdx.x % gpb, rg = (int)threadIdx.x / gpb;
-    for (int i = threadIdx.x; i < kRows * NN; i += 256) {
-        const int r = i / NN, n = i - r * NN;
-        gs[r][n] = (r < rows && n < N) ? (double)g[(int64_t)(row0 + r) * N + n] : 0.0;
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    constexpr int C = direct_tiles(NN), H = NN / 16;
+    constexpr bool VEC = STORE == kDaWords || STORE == kDaRows, STAGED = STORE == kDaRows || STORE == kDaFlat;
+    extern __shared__ __align__(16) float da_lds[];
+    if (plan && blockIdx.x == 0 && threadIdx.x == 0) no_limbs(plan);
+    const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+    const int group = (int)blockIdx.x / blocks, k0 = group * col_tiles * 16;
+    const int tiles = min(col_tiles, (K - k0 + 15) / 16);
+    const int row_tiles = (M - 1) / 16 + 1, step = blocks * 4;
+    int rt = ((int)blockIdx.x - group * blocks) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (rt >= row_tiles) return;
+
+    const bool whole = N % 4 == 0;
+    auto load = [&](int tile, float (&v)[H][4]) {
+        const int row = tile * 16 + i;
+        const float *src = g + (int64_t)row * N;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const int n = 16 * h + 4 * q;
+            if (whole) {
+                const float4 x = row < M && n < N ? *reinterpret_cast<const float4 *>(src + n) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                v[h][0] = x.x; v[h][1] = x.y; v[h][2] = x.z; v[h][3] = x.w;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[h][j] = row < M && n + j < N ? src[n + j] : 0.0f;
+            }
+        }
+    };
+    float next[H][4];
+    load(rt, next);
+    double b[C][H][4];
+#pragma unroll
+    for (int t = 0; t < C; ++t) {
+        const int k = k0 + 16 * t + (VEC ? 4 * (i & 3) + (i >> 2) : i);
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int n = 16 * h + 4 * q + j;
+                b[t][h][j] = t < tiles && n < N && k < K ? (double)b_idx[(int64_t)n * K + k] + b_offset : 0.0;     // (the level index itself)
+            }
     }
-    const bool active = cg < groups_total && rg < row_groups;
-    double b[C][NN];
-    if (C == 4 && vec_store) {
-        // (K % 4 == 0: the four index bytes of a row of b_idx in one load)
+    // the wave's tile of outputs on its way to stores of neighbouring addresses: kDaRows rows of `pitch` words, kDaFlat as in memory (all columns)
+    const int pitch = col_tiles * 16 + 4, width = min(col_tiles * 4, (K - k0) >> 2);
+    float *const mine = da_lds + (threadIdx.x >> 6) * 16 * pitch;
+    const int row_first = lane / width, col_first = lane - row_first * width, row_step = 64 / width, col_step = 64 - row_step * width;
+    for (; rt < row_tiles; rt += step) {
+        double gv[H][4];
 #pragma unroll
-        for (int n = 0; n < NN; ++n) {
-            const uint32_t w4 = (active && n < N) ? *reinterpret_cast<const uint32_t *>(b_idx + (int64_t)n * K + cg * C) : 0u;
+        for (int h = 0; h < H; ++h)
 #pragma unroll
-            for (int c = 0; c < C; ++c) b[c][n] = (active && n < N) ? (double)(int8_t)(w4 >> (8 * c)) + b_offset : 0.0;
+            for (int j = 0; j < 4; ++j) gv[h][j] = (double)next[h][j];
+        if (rt + step < row_tiles) load(rt + step, next);
+#pragma unroll
+        for (int t = 0; t < C; ++t) {
+            if (t < tiles) {
+                v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc = VEC ? __builtin_amdgcn_mfma_f64_16x16x4f64(b[t][h][j], gv[h][j], acc, 0, 0, 0) : __builtin_amdgcn_mfma_f64_16x16x4f64(gv[h][j], b[t][h][j], acc, 0, 0, 0);
+                if (VEC) {
+                    const float4 v = make_float4((float)(acc[0] * delta_b), (float)(acc[1] * delta_b), (float)(acc[2] * delta_b), (float)(acc[3] * delta_b));
+                    const int row = rt * 16 + i, k = k0 + 16 * t + 4 * q;
+                    if (STAGED) *reinterpret_cast<float4 *>(mine + i * pitch + 16 * t + 4 * q) = v;
+                    else if (row < M && k < K) *reinterpret_cast<float4 *>(out + (int64_t)row * K + k) = v;
+                } else {
+                    const int k = k0 + 16 * t + i;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = rt * 16 + q + 4 * r;
+                        const float v = (float)(acc[r] * delta_b);
+                        if (STAGED) { if (k < K) mine[(q + 4 * r) * K + k] = v; }
+                        else if (row < M && k < K) out[(int64_t)row * K + k] = v;
+                    }
+                }
+            }
         }
-    } else {
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int k = cg * C + c;
-#pragma unroll
-            for (int n = 0; n < NN; ++n) b[c][n] = (active && n < N && k < K) ? (double)b_idx[(int64_t)n * K + k] + b_offset : 0.0;   // (the level index itself)
-        }
-    }
-    __syncthreads();
-    if (!active) return;
-    const int k0 = cg * C;
-    for (int r = rg; r < rows; r += row_groups) {
-        double acc[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) acc[c] = 0.0;
-#pragma unroll
-        for (int n = 0; n < NN; ++n) {
-            const double gv = gs[r][n];
-#pragma unroll
-            for (int c = 0; c < C; ++c) acc[c] = fma(gv, b[c][n], acc[c]);
-        }
-        float *o = out + (int64_t)(row0 + r) * K + k0;
-        if (C == 4 && vec_store) {
-            *reinterpret_cast<float4 *>(o) = make_float4((float)(acc[0] * delta_b), (float)(acc[1] * delta_b), (float)(acc[2] * delta_b), (float)(acc[3] * delta_b));
+        if (!STAGED) continue;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int rows = min(16, M - rt * 16);
+        if (STORE == kDaRows) {
+            int row = row_first, col = col_first;
+            float *dst = out + (int64_t)rt * 16 * K + k0;
+            while (row < rows) {
+                *reinterpret_cast<float4 *>(dst + (int64_t)row * K + 4 * col) = *reinterpret_cast<const float4 *>(mine + row * pitch + 4 * col);
+                row += row_step;
+                col += col_step;
+                if (col >= width) { col -= width; ++row; }
+            }
         } else {
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-                if (k0 + c < K) o[c] = (float)(acc[c] * delta_b);
+            float *dst = out + (int64_t)rt * 16 * K;
+            const int count = rows * K;
+            for (int f = lane; f < count >> 2; f += 64) reinterpret_cast<float4 *>(dst)[f] = reinterpret_cast<const float4 *>(mine)[f];
+            if (lane < (count & 3)) dst[(count & ~3) + lane] = mine[(count & ~3) + lane];
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -2770,18 +2830,26 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     const bool is_conv_weights = cw != nullptr;
     if (cw && cw->R == 1 && cw->S == 1 && cw->stride == 1 && cw->pad == 0) cw = nullptr;
     if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.direct_splits, stream);
-    // (many outputs of few multiplications each: one thread per four outputs, see da_direct_kernel)
-    const bool only_b = is_conv_weights || (N <= kDirectMaxN && ((int64_t)M * K >= kDirectMinOutputs || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0)));
+    // (many outputs of few multiplications each: see da_direct_kernel)
+    const bool only_b = is_conv_weights || (N <= kDirectMaxN && ((int64_t)M * K >= direct_min_outputs(want_db) || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0)));
     if (d_a_hat && only_b) {
-        // four columns per thread (two where 32 index values per column would not leave registers for four)
-        const int c_per = N <= 16 ? 4 : 2;
-        const int col_groups = (K + c_per - 1) / c_per;
-        const int rows_per = direct_rows(N <= 16 ? 16 : 32);
-        const dim3 grid((M + rows_per - 1) / rows_per, (col_groups + 255) / 256);
-        const int vec_store = K % 4 == 0 && (reinterpret_cast<uintptr_t>(d_a_hat) & 15) == 0 && (reinterpret_cast<uintptr_t>(b_idx) & 3) == 0;
+        // (blocks of four waves per group of columns: as many as the chip holds, at most one wave per tile of rows)
+        const int most = direct_tiles(N <= 16 ? 16 : 32), all = (K + 15) / 16, groups = (all + most - 1) / most;
+        const int col_tiles = (all + groups - 1) / groups;
+        const bool staged = direct_staged((int64_t)M * K, K % 4 == 0);
+        const int64_t row_blocks = ((int64_t)M + 63) / 64, fill = std::max<int64_t>(direct_waves(staged, col_tiles) / 4 / groups, 1), trips = (row_blocks + fill - 1) / fill;
+        const int blocks = (int)((row_blocks + trips - 1) / trips);
+        const int used = (all + col_tiles - 1) / col_tiles;
+        const dim3 grid(used * blocks);
+        const size_t lds = (size_t)4 * 16 * (col_tiles * 16 + 4) * sizeof(float);
         BwdPlan *words = want_db ? nullptr : plan;
-        if (N <= 16) CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<16, 4>), grid, dim3(256), 0, gr, b_idx, M, N, K, (double)delta_b, (double)b_offset, d_a_hat, vec_store, words);
-        else CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<32, 2>), grid, dim3(256), 0, gr, b_idx, M, N, K, (double)delta_b, (double)b_offset, d_a_hat, vec_store, words);
+#define CDL_DA_N(NN, STORE) CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<NN, STORE>), grid, dim3(256), STORE == kDaRows || STORE == kDaFlat ? lds : 0, gr, b_idx, M, N, K, col_tiles, blocks, (double)delta_b, (double)b_offset, d_a_hat, words)
+#define CDL_DA(STORE) do { if (N <= 16) CDL_DA_N(16, STORE); else CDL_DA_N(32, STORE); } while (0)
+        if (K % 4 == 0) { if (staged) CDL_DA(kDaRows); else CDL_DA(kDaWords); }
+        else if (used == 1 && staged) CDL_DA(kDaFlat);
+        else CDL_DA(kDaScalars);
+#undef CDL_DA_N
+#undef CDL_DA
         d_a_hat = nullptr;           // done; what follows is for the other product only
         if (!want_db) return check_launch();
     }

@@ -1694,9 +1694,16 @@ void limb_reduce_kernel(const double *__restrict__ partial, int splits, int64_t 
 // Bound by the stores.  us, a thread per two or four columns with the rows of g in LDS, whose reads took as long as the additions / this: 131072 x 16 x 144 (rows, contraction, columns) 26.1 / 20.7,
 // 131072 x 32 x 288 136 / 50, 500000 x 32 x 64 186 / 44, 60000 x 16 x 576 53 / 32, 1000 x 16 x 8000 36 / 16, 262144 x 16 x 16 16.1 / 9.5.
 constexpr int kDirectMaxN = 32;
-// From so many outputs on; below, bwd_direct_kernel.  Alone, that / this: 16 entries, 1.05 M outputs 5.3 / 6.9 us, 2.4 M 12.6 / 8.0, 3.1 M 12.9 / 10.7, 3.5 M 23.6 / 9.2; 32 entries, 1.05 M 7.3 / 6.9, 2.4 M 13.1 / 9.5.  Where the weight gradient
-// is asked for as well, that kernel makes both in one launch: 2.4 M 15.9 / 20.2, 3.1 M 13.6 / 22.2 (3.5 M in 131072 rows 32.6 / 20.6).
-constexpr int64_t direct_min_outputs(bool both) { return both ? 1 << 22 : 1 << 21; }
+// Where it serves before bwd_direct_kernel, whose waves take one step of a short contraction each: many outputs, and long ones from fewer on.  us, that / this, alone: 16 entries, 4096 x 256 (rows x columns) 5.3 / 6.9, 16384 x 144 12.6 / 8.0,
+// 2048 x 1500 12.9 / 10.7, 65536 x 16 11.9 / 5.0, 32768 x 36 7.0 / 5.4, 131072 x 27 23.6 / 9.2; 32 entries, 8192 x 200 7.9 / 8.2, 16384 x 144 13.1 / 9.5.  With the weight gradient, which that kernel makes in the same launch: 16 entries, 16384 x 144
+// 15.9 / 20.2, 50000 x 64 17.3 / 21.3, 2048 x 1500 13.6 / 22.2, 65536 x 16 20.2 / 14.3, 65536 x 60 21.4 / 19.7, 131072 x 9 32.9 / 18.4; 32 entries, 65536 x 36 21.0 / 19.6, 65536 x 60 22.7 / 25.2, 100000 x 40 33.4 / 31.6, 200000 x 9 54.8 / 32.3.
+bool da_direct_preferred(int M, int N, int K, bool both)
+{
+    const int64_t outputs = (int64_t)M * K;
+    if (outputs >= 1 << 22) return true;
+    if (!both) return outputs >= 1 << 21 || (M >= 1 << 15 && outputs >= 1 << 20);
+    return M >= 1 << 16 && outputs >= 1 << 20 && (N <= 16 || K <= 40);
+}
 constexpr int direct_tiles(int nn) { return nn == 16 ? 10 : 4; }     // tiles of 16 columns per wave: 80 and 64 registers of index values
 
 // How the outputs are stored.  kDaWords (rows of whole words of four columns; the entry points take aligned tensors only): the index operand comes first in the product and column 4 (i & 3) + (i >> 2) of a tile is its row i, a lane then has
@@ -2831,7 +2838,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     if (cw && cw->R == 1 && cw->S == 1 && cw->stride == 1 && cw->pad == 0) cw = nullptr;
     if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.direct_splits, stream);
     // (many outputs of few multiplications each: see da_direct_kernel)
-    const bool only_b = is_conv_weights || (N <= kDirectMaxN && ((int64_t)M * K >= direct_min_outputs(want_db) || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0)));
+    const bool only_b = is_conv_weights || (N <= kDirectMaxN && (da_direct_preferred(M, N, K, want_db) || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0)));
     if (d_a_hat && only_b) {
         // (blocks of four waves per group of columns: as many as the chip holds, at most one wave per tile of rows)
         const int most = direct_tiles(N <= 16 ? 16 : 32), all = (K + 15) / 16, groups = (all + most - 1) / most;

@@ -12,7 +12,7 @@ CASES = [
     (131072, 16, 16), (131072, 16, 15), (131072, 1, 17), (65537, 3, 32), (20_001, 16, 144), (20_001, 13, 160), (20_001, 16, 164), (20_001, 16, 163), (13_000, 5, 333), (20_001, 12, 144),
     (65_536, 32, 64), (65_535, 17, 68), (60_000, 32, 63), (60_000, 31, 65), (300, 32, 8000), (17, 16, 250_000), (150, 20, 20_003),
     (600_000, 16, 28), (600_001, 16, 29), (600_001, 32, 29), (160_003, 9, 105), (270_001, 32, 63), (160_003, 16, 161), (460_001, 16, 144), (250_001, 30, 264), (2_200_001, 8, 32),
-    (32767, 16, 64), (32768, 16, 64),
+    (32767, 16, 64), (32768, 16, 64), (32768, 32, 32), (32767, 32, 33), (116_509, 3, 9),
 ]
 
 
@@ -55,3 +55,23 @@ def test_infinities():
     bad = torch.zeros(M, dtype=torch.bool, device="cuda")
     bad[5] = bad[M - 1] = True
     assert bool(torch.isinf(da[5]).all()) and bool(torch.isnan(da[M - 1]).all()) and bool((da[~bad] == N).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(65536, 16, 16), (65535, 16, 17), (65536, 17, 40), (65536, 17, 41), (70_001, 5, 63), (131072, 32, 9), (131072, 3, 27)])
+def test_both(M, N, K):
+    """Both products of one call, on both sides of the lines on rows, contraction and columns."""
+    import paper_2501_09849_amd as cdl
+    torch = gu.torch_mod()
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    g = torch.randn(M, N, device="cuda", generator=gen)
+    a = torch.randint(0, 16, (M, K), dtype=torch.int8, device="cuda", generator=gen)
+    b = torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda", generator=gen)
+    da, db = torch.empty(M, K, device="cuda"), torch.empty(N, K, device="cuda")
+    cdl.cdl_qgemm_bwd(g, a, b, M, N, K, 0.5, 0.25, da, db, gu.workspace(cdl.qgemm_bwd_workspace_bytes(M, N, K)))
+    G, A, B = g.double(), a.double(), b.double()
+    # one rounding to fp32, and sums in double or on six digits (2^-44 of the largest entry of a row of g)
+    ref, mag = 0.25 * (G @ B), 0.25 * (G.abs() @ B.abs())
+    assert bool(((da.double() - ref).abs() <= 2.0 ** -23 * ref.abs() + 2.0 ** -40 * mag + 1e-30).all())
+    ref = 0.5 * (G.t().contiguous() @ A)
+    mag = 0.5 * M * float(g.abs().max()) * 15
+    assert bool(((db.double() - ref).abs() <= 2.0 ** -23 * ref.abs() + 2.0 ** -40 * mag).all())

@@ -1685,26 +1685,30 @@ void limb_reduce_kernel(const double *__restrict__ partial, int splits, int64_t 
 }
 
 // dL/dQ(a) for a very short contraction (N <= 32: the first stages of a small CNN have 16 or 32 output
-// channels): d_a_hat[m][k] = delta_b * sum_n g[m][n] * b_idx[n][k].  One K-tile of the limb kernel would be
+// channels; up to 64 in long layers of few columns): d_a_hat[m][k] = delta_b * sum_n g[m][n] * b_idx[n][k].  One K-tile of the limb kernel would be
 // at least three quarters padding there; here every output is a chain of N multiply-adds in double on the matrix cores: products of a
-// float and an int8 are exact in double and N <= 32 additions round at 2^-53 relative.
+// float and an int8 are exact in double and N additions round at 2^-53 relative.
 // A wave keeps the index values of up to C tiles of 16 columns in registers as doubles and goes over tiles of 16 rows, the entries of g of the next one
 // under way.  Quarter q of the wave holds the contraction entries 4 q to 4 q + 3 (and 16 more on), so that a lane's part of a row of g is one load of 16 bytes
 // and nothing of the operands passes through LDS.
 // Bound by the stores.  us, a thread per two or four columns with the rows of g in LDS, whose reads took as long as the additions / this: 131072 x 16 x 144 (rows, contraction, columns) 26.1 / 20.7,
 // 131072 x 32 x 288 136 / 50, 500000 x 32 x 64 186 / 44, 60000 x 16 x 576 53 / 32, 1000 x 16 x 8000 36 / 16, 262144 x 16 x 16 16.1 / 9.5.
-constexpr int kDirectMaxN = 32;
+constexpr int kDirectMaxN = 32, kDirectWideN = 64;
 // Where it serves before bwd_direct_kernel, whose waves take one step of a short contraction each: many outputs, and long ones from fewer on.  us, that / this, alone: 16 entries, 4096 x 256 (rows x columns) 5.3 / 6.9, 16384 x 144 12.6 / 8.0,
 // 2048 x 1500 12.9 / 10.7, 65536 x 16 11.9 / 5.0, 32768 x 36 7.0 / 5.4, 131072 x 27 23.6 / 9.2; 32 entries, 8192 x 200 7.9 / 8.2, 16384 x 144 13.1 / 9.5.  With the weight gradient, which that kernel makes in the same launch: 16 entries, 16384 x 144
 // 15.9 / 20.2, 50000 x 64 17.3 / 21.3, 2048 x 1500 13.6 / 22.2, 65536 x 16 20.2 / 14.3, 65536 x 60 21.4 / 19.7, 131072 x 9 32.9 / 18.4; 32 entries, 65536 x 36 21.0 / 19.6, 65536 x 60 22.7 / 25.2, 100000 x 40 33.4 / 31.6, 200000 x 9 54.8 / 32.3.
+// 33 to 64 entries in long layers of few columns (one wave has all columns; the other kernels' steps are as short, and more of them), us, that / this: alone 64 entries, 65536 x 27 17.8 / 12.8, 131072 x 9 32.2 / 14.7, 400000 x 32 90 / 46,
+// 65536 x 64 16.6 / 19.0, 32768 x 36 9.6 / 11.0; 48 entries, 65536 x 64 18.2 / 15.4, 131072 x 144 44.3 / 47.3; 33 entries, 3 M x 32 1635 / 206; both products, 64 entries, 65536 x 27 35.6 / 33.1, 65536 x 48 34.7 / 37.7, 32768 x 27 24.5 / 27.0;
+// 48 entries, 65536 x 27 35.3 / 30.7, 65536 x 64 35.9 / 37.1, 400000 x 32 136 / 79.
 bool da_direct_preferred(int M, int N, int K, bool both)
 {
+    if (N > kDirectMaxN) return N <= kDirectWideN && M >= 1 << 16 && (K <= 32 || (N <= 48 && K <= 64 && !both));
     const int64_t outputs = (int64_t)M * K;
     if (outputs >= 1 << 22) return true;
     if (!both) return outputs >= 1 << 21 || (M >= 1 << 15 && outputs >= 1 << 20);
     return M >= 1 << 16 && outputs >= 1 << 20 && (N <= 16 || K <= 40);
 }
-constexpr int direct_tiles(int nn) { return nn == 16 ? 10 : 4; }     // tiles of 16 columns per wave: 80 and 64 registers of index values
+constexpr int direct_tiles(int nn) { return nn == 16 ? 10 : 4; }     // tiles of 16 columns per wave: 80 and 64 registers of index values, 96 and 128 beyond 32 entries (two waves per SIMD: with four they spill)
 
 // How the outputs are stored.  kDaWords (rows of whole words of four columns; the entry points take aligned tensors only): the index operand comes first in the product and column 4 (i & 3) + (i >> 2) of a tile is its row i, a lane then has
 // four neighbouring outputs.  kDaScalars: g first, 16 neighbouring columns per store.  Both write pieces of 64 bytes.  kDaRows, kDaFlat: through LDS and from there as they lie in memory (kDaFlat: rows of any
@@ -1717,7 +1721,7 @@ bool direct_staged(int64_t outputs, bool words) { return outputs >= (words ? 650
 int direct_waves(bool staged, int col_tiles) { return staged && col_tiles <= 5 ? 4096 : 2048; }
 
 template <int NN, DaStore STORE>
-__global__ __launch_bounds__(256, 4)
+__global__ __launch_bounds__(256, NN <= 32 ? 4 : 2)
 void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_idx, int M, int N, int K, int col_tiles /* per wave */, int blocks /* per group of them */,
                       double delta_b, double b_offset, float *__restrict__ out, BwdPlan *plan /* null: another product follows */)
 {
@@ -2838,12 +2842,12 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     if (cw && cw->R == 1 && cw->S == 1 && cw->stride == 1 && cw->pad == 0) cw = nullptr;
     if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.direct_splits, stream);
     // (many outputs of few multiplications each: see da_direct_kernel)
-    const bool only_b = is_conv_weights || (N <= kDirectMaxN && (da_direct_preferred(M, N, K, want_db) || !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0)));
+    const bool only_b = is_conv_weights || da_direct_preferred(M, N, K, want_db) || (N <= kDirectMaxN && !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0));
     if (d_a_hat && only_b) {
         // (blocks of four waves per group of columns: as many as the chip holds, at most one wave per tile of rows)
-        const int most = direct_tiles(N <= 16 ? 16 : 32), all = (K + 15) / 16, groups = (all + most - 1) / most;
+        const int most = direct_tiles((N + 15) / 16 * 16), all = (K + 15) / 16, groups = (all + most - 1) / most;
         const int col_tiles = (all + groups - 1) / groups;
-        const bool staged = direct_staged((int64_t)M * K, K % 4 == 0);
+        const bool staged = N <= 32 && direct_staged((int64_t)M * K, K % 4 == 0);
         const int64_t row_blocks = ((int64_t)M + 63) / 64, fill = std::max<int64_t>(direct_waves(staged, col_tiles) / 4 / groups, 1), trips = (row_blocks + fill - 1) / fill;
         const int blocks = (int)((row_blocks + trips - 1) / trips);
         const int used = (all + col_tiles - 1) / col_tiles;
@@ -2852,9 +2856,12 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         BwdPlan *words = want_db ? nullptr : plan;
 #define CDL_DA_N(NN, STORE) CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<NN, STORE>), grid, dim3(256), STORE == kDaRows || STORE == kDaFlat ? lds : 0, gr, b_idx, M, N, K, col_tiles, blocks, (double)delta_b, (double)b_offset, d_a_hat, words)
 #define CDL_DA(STORE) do { if (N <= 16) CDL_DA_N(16, STORE); else CDL_DA_N(32, STORE); } while (0)
-        if (K % 4 == 0) { if (staged) CDL_DA(kDaRows); else CDL_DA(kDaWords); }
+#define CDL_DA_WIDE(STORE) do { if (N <= 48) CDL_DA_N(48, STORE); else CDL_DA_N(64, STORE); } while (0)
+        if (N > 32) { if (K % 4 == 0) CDL_DA_WIDE(kDaWords); else CDL_DA_WIDE(kDaScalars); }
+        else if (K % 4 == 0) { if (staged) CDL_DA(kDaRows); else CDL_DA(kDaWords); }
         else if (used == 1 && staged) CDL_DA(kDaFlat);
         else CDL_DA(kDaScalars);
+#undef CDL_DA_WIDE
 #undef CDL_DA_N
 #undef CDL_DA
         d_a_hat = nullptr;           // done; what follows is for the other product only

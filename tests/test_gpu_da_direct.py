@@ -1,4 +1,4 @@
-"""Activation gradient of short contractions (at most 32 entries): every way in which the outputs are stored, contractions and columns that do and do not fill their tiles, one and several
+"""Activation gradient of short contractions (at most 32 entries, 64 in long layers): every way in which the outputs are stored, contractions and columns that do and do not fill their tiles, one and several
 groups of columns, rows that do not fill a tile, both sides of the line on the number of outputs."""
 import numpy as np
 import pytest
@@ -13,6 +13,7 @@ CASES = [
     (65_536, 32, 64), (65_535, 17, 68), (60_000, 32, 63), (60_000, 31, 65), (300, 32, 8000), (17, 16, 250_000), (150, 20, 20_003),
     (600_000, 16, 28), (600_001, 16, 29), (600_001, 32, 29), (160_003, 9, 105), (270_001, 32, 63), (160_003, 16, 161), (460_001, 16, 144), (250_001, 30, 264), (2_200_001, 8, 32),
     (32767, 16, 64), (32768, 16, 64), (32768, 32, 32), (32767, 32, 33), (116_509, 3, 9),
+    (65536, 33, 32), (65535, 33, 32), (65537, 48, 64), (65537, 48, 65), (65539, 47, 63), (65537, 49, 31), (65536, 64, 32), (65536, 64, 33), (70_003, 64, 1), (131_075, 61, 27), (2_100_001, 64, 31),
 ]
 
 
@@ -57,7 +58,7 @@ def test_infinities():
     assert bool(torch.isinf(da[5]).all()) and bool(torch.isnan(da[M - 1]).all()) and bool((da[~bad] == N).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(65536, 16, 16), (65535, 16, 17), (65536, 17, 40), (65536, 17, 41), (70_001, 5, 63), (131072, 32, 9), (131072, 3, 27)])
+@pytest.mark.parametrize("M,N,K", [(65536, 16, 16), (65535, 16, 17), (65536, 17, 40), (65536, 17, 41), (70_001, 5, 63), (131072, 32, 9), (131072, 3, 27), (65536, 33, 32), (65536, 48, 33), (65541, 64, 27)])
 def test_both(M, N, K):
     """Both products of one call, on both sides of the lines on rows, contraction and columns."""
     import paper_2501_09849_amd as cdl

@@ -609,7 +609,7 @@ struct ConvArgs {
     float *y_out;          // [M][N] or null
     float scale;
     const int32_t *corr_col;   // [N] or null: x stored with an offset, x_offset * sum over the window of w[n]
-    // ChunkSource: 128 bytes of zeros; chunks of a tap, and a K-tile's four chunks in whole taps and chunks
+    // ChunkSource: zeros (16 bytes); chunks of a tap, and a K-tile's four chunks in whole taps and chunks
     const int8_t *zero_page;
     int c16, step_taps, step_in;
     DivBy by_c16, by_s, by_pq, by_q;
@@ -933,12 +933,12 @@ void qconv_kernel(ConvArgs a)
     else epilogue(std::false_type{});
 }
 
-// 128 bytes that read as level index 0 of an operand stored with offset `off`, and (with an offset) the
+// 128 bytes that read as level index 0 of an operand stored with offset `off` and 128 zeros, and (with an offset) the
 // correction per output channel: off * sum of w[n] over the whole window (a padded tap holds -off + off = 0)
 __global__ __launch_bounds__(256)
 void conv_prep_kernel(int8_t *page, int off, const int8_t *w, int N, int Kc, int32_t *corr)
 {
-    if (blockIdx.x == 0 && threadIdx.x < 128) page[threadIdx.x] = (int8_t)(-off);
+    if (blockIdx.x == 0) page[threadIdx.x] = threadIdx.x < 128 ? (int8_t)(-off) : (int8_t)0;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int n = blockIdx.x * 4 + wave; n < N; n += gridDim.x * 4) {
         const int s = row_sum(w + (int64_t)n * Kc, Kc, lane);
@@ -2753,8 +2753,6 @@ static int launch_conv_ring(ConvArgs a, hipStream_t stream)
     const int64_t grid = ring_grid((int64_t)a.tiles_m * a.tiles_n, SHAPE::PER_CU);
     const bool stream_out = stream_output((int64_t)a.M * a.N, a.N, a.y_out) && !a.acc_out, chunks = a.C % kRingBK != 0;
     if (chunks) {
-        const int rc = conv_zero_page_ptr(&a.zero_page);
-        if (rc != CDL_OK) return rc;
         a.step_taps = kRingBK / 16 / a.c16;
         a.step_in = kRingBK / 16 % a.c16;
     }
@@ -2794,10 +2792,12 @@ int launch_qconv_fwd(const int8_t *x_idx, const int8_t *w_idx, int32_t B, int32_
         int rc = check_launch();
         if (rc != CDL_OK) return rc;
         a.pad_page = page;
+        a.zero_page = page + 128;      // (no look-up of the library's own page: a call with an offset may be the first on a GPU, and captured)
         a.corr_col = corr;
     } else {
         int rc = conv_zero_page_ptr(&a.pad_page);
         if (rc != CDL_OK) return rc;
+        a.zero_page = a.pad_page;
     }
     const uint32_t pb = (uint32_t)(uint8_t)(int8_t)(-x_offset);
     a.pad_word = (int)(pb | (pb << 8) | (pb << 16) | (pb << 24));

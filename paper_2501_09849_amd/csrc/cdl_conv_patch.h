@@ -4,11 +4,7 @@
 
 #include <stdint.h>
 
-#ifdef __HIPCC__
-#define CDL_ANYWHERE __host__ __device__ __forceinline__
-#else
-#define CDL_ANYWHERE inline
-#endif
+#include "cdl_anywhere.h"
 
 namespace cdl {
 

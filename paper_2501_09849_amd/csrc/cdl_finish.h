@@ -21,8 +21,8 @@
 // launch of the process uses, and the reader spoils the check word of every record it has taken, so that a captured
 // launch can be replayed with the tag it was captured with.
 //
-// Every wait ends.  Of a histogram in slices (cdl_marginal.h) the last sixteen blocks at most, of 256, wait for all others, which publish before they wait for anybody; two of
-// them lie on an XCD, which holds 32 blocks at least, and the others make room as below.  Of the scalar sums only the last block of each group of 256 and the last of the grid wait: a group's last for the others of its group, which wait for
+// Every wait ends.  Of a histogram in slices the collectors wait, sixteen at most behind 256 blocks at most: for blocks of lower numbers alone (cdl_marg_slices.h).
+// Of the scalar sums only the last block of each group of 256 and the last of the grid wait: a group's last for the others of its group, which wait for
 // nobody, the grid's last for those and for the groups' last ones, so all for blocks of lower numbers.  Grids with records have at most 4097 blocks (2^23
 // entries in one trip), more than are resident, but of them at most 17 wait, and an XCD holds a block on each of its 32 compute units at least: the others
 // finish beside them and make room for all that have not started.  With more launches at a time than that leaves room for, it rests on an XCD

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "cdl_finish.h"
+#include "cdl_marg_slices.h"
 
 #include <math.h>
 
@@ -11,31 +12,20 @@ namespace cdl {
 
 constexpr int kHistScaleBits = 21;      // a probability p is the integer floor(p * 2^21 + 1/2)
 
-// Most blocks that finish a grid's histograms between them.
-constexpr int kMargCollectors = 16;
-
 // What becomes of the per-block histograms: the marginal PMF and its entropy.
 struct MargFinish {
-    unsigned long long *rows;      // [gridDim.x][n_levels], for marginal_finalize_kernel; slices: records, [gridDim.x][n_levels padded to fours]
+    unsigned long long *rows;      // [gridDim.x][n_levels], for marginal_finalize_kernel; slices: records, [workers][n_levels padded to fours]
     unsigned long long *records;   // [blocks][n_levels][2]; slices: [kMargCollectors][2]
     unsigned long long tag;
     double inv_n;                  // 1 / (n * 2^s)
     float *marg;                   // [n_levels] or null
     float *entropy_bits;           // [1] or null
     int lg_per;                    // slices of 2^lg_per levels (a multiple of four)
+    MargRoles roles;               // slices
 };
 
-// How the blocks' histograms are added up: in rows for a second launch, by the last block, by the last blocks, a slice of the levels each.
+// How the blocks' histograms are added up: in rows for a second launch, by the last block, by blocks of their own, a slice of the levels each.
 enum MargForm { kMargRows = 0, kMargLast = 1, kMargSlices = 2 };
-
-// Levels of a slice, as a power of two: slices of at most 16 KB of what the others leave (8 bytes a level and block; one round of loads of 512 threads), up to
-// sixteen slices.  us of the forward pass, slices of 8, 16, 32 KB: 512 K entries of 63 levels (250 blocks) 8.5 / 8.2 / 9.7, of 255 8.7 / 8.7 / 10.2.
-inline int marg_lg_per(int64_t blocks, int n_levels)
-{
-    int lg = 2;
-    while ((1 << lg) < n_levels && ((n_levels + (1 << lg) - 1) >> lg > kMargCollectors || (blocks << lg) < 2048)) ++lg;
-    return lg;
-}
 
 // A record is a 64-bit sum and, as its check word, the sum combined with the tag.
 __device__ __forceinline__ void marginal_publish(unsigned long long v, size_t at, const MargFinish &f)
@@ -103,7 +93,7 @@ __device__ __forceinline__ void marginal_collect(unsigned long long own, int row
 }
 
 // ---- slices ----
-// One block takes 2.5 us for 256 KB of records; here the last blocks share them, at the price of one trip more for their entropy terms.  A record
+// One block takes 2.5 us for 256 KB of records; here up to sixteen blocks behind those that have entries share them, at the price of one trip more for their entropy terms.  A record
 // is four levels' sums of a block, 48 bits with their sign each (a block has at most 2^15 entries of 2^21): three words with a quarter of the
 // fourth sum each in their upper bits, and a check word.  Lane 4 i + j holds word j.  (Times of both sides: marg_form.)
 // Four neighbouring lanes exchange values (1: lane ^ 1, 2: lane ^ 2, 3: lane 3's).
@@ -139,18 +129,16 @@ __device__ __forceinline__ void row_publish(unsigned long long v, int n_levels, 
     device_store(f.rows + (size_t)blockIdx.x * n4 + threadIdx.x, j == 3 ? check : word);
 }
 
-// The last blocks' part, for all T threads of each: block gridDim.x - B + c, B the number of slices of 2^lg_per levels, adds slice c over all blocks,
+// The collectors' part, for all T threads of each: collector c adds slice c, of 2^lg_per levels, over the blocks that have entries,
 // normalises and leaves its entropy terms to the last one, which adds those up in a fixed order.
-// own: the block's sum of level threadIdx.x.
 template <int T, int U>
-__device__ __forceinline__ void rows_collect(unsigned long long own, int slices, int n_levels, const MargFinish &f)
+__device__ __forceinline__ void rows_collect(int n_levels, const MargFinish &f)
 {
-    __shared__ unsigned long long red[T], mine[256];
+    __shared__ unsigned long long red[T];
     __shared__ double hs[T / 64 + kMargCollectors];
-    if ((int)threadIdx.x < n_levels) mine[threadIdx.x] = own;
-    const int lg = f.lg_per, per = 1 << lg, n4 = (n_levels + 3) & ~3, c = (int)blockIdx.x - ((int)gridDim.x - slices);
+    const int lg = f.lg_per, per = 1 << lg, n4 = (n_levels + 3) & ~3, c = f.roles.collector((int)blockIdx.x), terms_from = f.roles.terms_from(c);
     const int local = (int)threadIdx.x & (per - 1), level = (c << lg) + local, sub = (int)threadIdx.x >> lg, subs = T >> lg, j = local & 3;
-    const int others = (int)gridDim.x - 1;
+    const int rows = f.roles.rows_from();
     unsigned long long s = 0ull;
     unsigned long long *const column = f.rows + level;
     auto take = [&](int r, auto count) {      // records r, r + subs, ..
@@ -159,9 +147,8 @@ __device__ __forceinline__ void rows_collect(unsigned long long own, int slices,
         size_t at[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            // (past the end: the thread's first record once more; the block's own row is left out)
-            const int i = r + u * subs < others ? r + u * subs : r;
-            at[u] = (size_t)(i + (i >= (int)blockIdx.x ? 1 : 0)) * n4;
+            // (past the end: the thread's first record once more)
+            at[u] = (size_t)(r + u * subs < rows ? r + u * subs : r) * n4;
         }
         bool waiting = true;
         while (waiting) {
@@ -177,17 +164,17 @@ __device__ __forceinline__ void rows_collect(unsigned long long own, int slices,
             top += quad_other<1>(top);
             top += quad_other<2>(top);
             const unsigned long long v = j == 3 ? top : w[u];
-            if (r + u * subs < others) {
+            if (r + u * subs < rows) {
                 s += (unsigned long long)((long long)(v << 16) >> 16);
                 if (j == 3) device_store(column + at[u], w[u] + 1);      // (spoilt, for a replay)
             }
         }
     };
     if (level < n4) {
-        if (others <= subs) {
-            if (sub < others) take(sub, std::integral_constant<int, 1>{});
+        if (rows <= subs) {
+            if (sub < rows) take(sub, std::integral_constant<int, 1>{});
         } else {
-            for (int r = sub; r < others; r += U * subs) take(r, std::integral_constant<int, U>{});
+            for (int r = sub; r < rows; r += U * subs) take(r, std::integral_constant<int, U>{});
         }
     }
     for (int off = 32; off >= per; off >>= 1) s += (unsigned long long)__shfl_xor((long long)s, off, 64);
@@ -195,7 +182,7 @@ __device__ __forceinline__ void rows_collect(unsigned long long own, int slices,
     __syncthreads();
     double h = 0.0;
     if ((int)threadIdx.x < per && level < n_levels) {
-        unsigned long long sum = mine[level];
+        unsigned long long sum = 0ull;
         const int step = per < 64 ? 64 : per;
         for (int q = local; q < T; q += step) sum += red[q];
         const double m = fmax((double)(long long)sum * f.inv_n, 0.0);
@@ -210,7 +197,7 @@ __device__ __forceinline__ void rows_collect(unsigned long long own, int slices,
     double terms = 0.0;
     if (threadIdx.x == 0)
         for (int q = 0; q < (per + 63) / 64; ++q) terms += hs[q];
-    if (c != slices - 1) {
+    if (c != f.roles.slices - 1) {
         if (threadIdx.x == 0) {
             const unsigned long long bits = (unsigned long long)__double_as_longlong(terms);
             device_store(f.records + 2 * c, bits);
@@ -218,7 +205,7 @@ __device__ __forceinline__ void rows_collect(unsigned long long own, int slices,
         }
         return;
     }
-    if ((int)threadIdx.x < slices - 1) {
+    if ((int)threadIdx.x < terms_from) {
         unsigned long long *const q = f.records + 2 * threadIdx.x;
         unsigned long long v, check;
         do {
@@ -231,7 +218,7 @@ __device__ __forceinline__ void rows_collect(unsigned long long own, int slices,
     __syncthreads();
     if (threadIdx.x == 0) {
         double sum = 0.0;
-        for (int q = 0; q < slices - 1; ++q) sum += hs[T / 64 + q];
+        for (int q = 0; q < terms_from; ++q) sum += hs[T / 64 + q];
         *f.entropy_bits = (float)(sum + terms);
     }
 }
@@ -243,9 +230,7 @@ template <int T, int FORM>
 __device__ __forceinline__ void marginal_end(unsigned long long own, int n_levels, const MargFinish &f)
 {
     if constexpr (FORM == kMargSlices) {
-        const int slices = (n_levels + (1 << f.lg_per) - 1) >> f.lg_per;
-        row_publish(own, n_levels, f);
-        if ((int)blockIdx.x >= (int)gridDim.x - slices) rows_collect<T, 8>(own, slices, n_levels, f);
+        row_publish(own, n_levels, f);      // (the collectors: at the kernel's start)
     } else if constexpr (FORM == kMargLast) {
         if (blockIdx.x == gridDim.x - 1) marginal_collect<T, 8>(own, (int)blockIdx.x, n_levels, f);
         else if ((int)threadIdx.x < n_levels) marginal_publish(own, (size_t)blockIdx.x * n_levels + threadIdx.x, f);

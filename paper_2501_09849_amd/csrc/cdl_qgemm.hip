@@ -514,8 +514,9 @@ bool dma_serves(int64_t M, int64_t N, int64_t K)
 }
 
 // Which tiles a product of M x N outputs over nk K-tiles of 64 bytes takes.  A form's time, us: its start, its K-tiles through every round of blocks (half: a last round with a block
-// to a compute unit at most), a share for every round, and what its output adds, per megabyte.  Fitted to 260 convolutions and 130 matrix products, each run in every form (off by 5 - 12 %); of the choices six are more
-// than 3 % slower than the staged or wide form that they replace (9 % the worst), and all products together take 0.89 and 0.93 of the time.  us, staged / the choice: convolutions 56 x 56 x 64 -> 64 on 128 images 48.4 / 32.8
+// to a compute unit at most), a share for every round, and what its output adds, per megabyte.  Fitted to 260 convolutions and 130 matrix products, each run in every form (off by 5 - 12 %; of the staged tiles of 256 x 64
+// those terms that choose best for 673 layers and 105 products of up to 64 columns).  No term for the operands' bytes: where those bound a product the rules of choose_tiles hold.  Of 1672 convolutions (1 to 512 images and more, 16 to 640 channels -> 20 to 800) and 1033 matrix products (200 to 3 M rows, 33 to 1500
+// columns, 1 to 64 K-tiles), each run in every form, the choices take 0.91 and 0.95 of the time of the staged or wide form that they replace; 48 are more than 3 % slower than that, the worst 9 and 7 %.  us, staged / the choice: convolutions 56 x 56 x 64 -> 64 on 128 images 48.4 / 32.8
 // (narrow), 28 x 28 x 128 -> 128 33.5 / 25.9 (tall), 29 x 18 x 48 -> 148 on 185 36.1 / 24.9 (narrow), 25 x 25 x 448 -> 52 at stride 2 on 138 33.3 / 21.0 (low), 19 x 53 x 288 -> 412 on 53 110 / 89.6 (wide), 26 x 26 x 32 -> 84, 5 x 5,
 // on 229 45.9 / 33.3 (square); matrices 60000 x 128 x 1152 23.7 / 19.1 (square), 982 x 1408 x 1280 11.4 / 8.5 (low), 100352 x 128 x 1152 34.8 / 28.7 (tall).
 enum TileForm { kTileStaged, kTileWide, kTileTall, kTileNarrow, kTileSquare, kTileLow };
@@ -524,8 +525,8 @@ constexpr TileTime kRingTimes[2][5] = {      // matrices, windows; in the order 
     {{256, 256, 1, 7.1, 0.696, 0.0, 0.0, 0.130}, {256, 128, 2, 5.7, 0.837, 0.549, 0.0, 0.123}, {256, 64, 2, 4.2, 0.675, 0.338, 0.0, 0.113}, {128, 128, 2, 4.6, 0.537, 0.286, 0.0, 0.114}, {128, 64, 2, 4.1, 0.381, 0.207, 0.0, 0.103}},
     {{256, 256, 1, 8.3, 0.774, 0.0, 0.0, 0.153}, {256, 128, 2, 8.0, 0.870, 0.637, 0.0, 0.130}, {256, 64, 2, 6.5, 0.652, 0.474, 0.0, 0.121}, {128, 128, 2, 6.2, 0.541, 0.424, 0.0, 0.130}, {128, 64, 2, 5.5, 0.406, 0.321, 0.0, 0.129}}};
 constexpr TileTime kStagedTimes[2][2][3] = {      // up to 64 columns, more; 64, 128, 256 rows
-    {{{64, 64, 2, 1.9, 0.386, 0.284, 1.9, 0.025}, {128, 64, 2, 1.4, 0.540, 0.4, 1.4, 0.24}, {256, 64, 2, 5.8, 0.945, 0.986, -5.1, 0.383}}, {{64, 128, 2, 2.1, 0.441, 0.329, 2.1, 0.175}, {128, 128, 2, 3.0, 0.671, 0.49, 3.0, 0.133}, {256, 128, 2, 2.0, 1.075, 0.7, 12.1, 0.003}}},
-    {{{64, 64, 2, 1.9, 0.386, 0.284, 1.9, 0.025}, {128, 64, 2, 2.3, 0.468, 0.35, 2.3, 0.153}, {256, 64, 2, 5.8, 0.945, 0.986, -5.1, 0.383}}, {{64, 128, 2, 2.3, 0.463, 0.367, 2.3, 0.156}, {128, 128, 2, 3.4, 0.726, 0.485, 3.4, 0.094}, {256, 128, 2, 4.2, 1.062, 0.641, 9.1, 0.037}}}};
+    {{{64, 64, 2, 1.9, 0.386, 0.284, 1.9, 0.025}, {128, 64, 2, 1.4, 0.540, 0.4, 1.4, 0.24}, {256, 64, 2, 0.0, 1.798, 0.667, 0.0, 0.216}}, {{64, 128, 2, 2.1, 0.441, 0.329, 2.1, 0.175}, {128, 128, 2, 3.0, 0.671, 0.49, 3.0, 0.133}, {256, 128, 2, 2.0, 1.075, 0.7, 12.1, 0.003}}},
+    {{{64, 64, 2, 1.9, 0.386, 0.284, 1.9, 0.025}, {128, 64, 2, 2.3, 0.468, 0.35, 2.3, 0.153}, {256, 64, 2, 2.1, 0.818, 0.597, 3.8, 0.132}}, {{64, 128, 2, 2.3, 0.463, 0.367, 2.3, 0.156}, {128, 128, 2, 3.4, 0.726, 0.485, 3.4, 0.094}, {256, 128, 2, 4.2, 1.062, 0.641, 9.1, 0.037}}}};
 
 // least: K-tiles that a block takes the time of in any case (a ring is filled first)
 double tile_time(const TileTime &t, int64_t M, int64_t N, int64_t nk, int least)
@@ -554,6 +555,11 @@ TileForm choose_tiles(bool windows, bool whole, int64_t M, int64_t N, int64_t K)
     const int64_t nk = (K + kRingBK - 1) / kRingBK;
     const bool wide = whole && dma_serves(M, N, K);
     const int rows = staged_rows(M, N);
+    // Bound by memory, which the times do not tell apart.  Outputs beyond the memory-side cache over few K-tiles: whole rows of 256 columns (us, wide / what the times would choose: 252312 x 1189 x 64 287 / 384, 522648 x 574 x 64
+    // 304 / 356, 478895 x 192 x 128 74 / 67).  Up to 64 columns over few K-tiles: staged, whose stores do not wait where the columns end inside a tile (us, staged / so: 662125 x 63 x 128 41.8 / 52.6, 240573 x 43 x 128 16.6 / 20.8,
+    // 147875 x 36 x 448 20.2 / 22.4, 73034 x 46 x 512 15.8 / 14.3; up to 128 rows to a tile 23877 x 38 x 576 6.4 / 7.0, with 64 columns 16514 x 64 x 960 8.5 / 7.5).
+    if (wide && nk <= 8 && M * N > 64 << 20) return kTileWide;
+    if (!windows && N <= 64 && nk < (rows == 256 || N == 64 ? 8 : 17)) return kTileStaged;
     TileForm best = wide ? kTileWide : kTileStaged;
     // (staged tiles of 64 rows, a last round of which is mostly short, are often better than that for windows: 7 x 49 x 49 x 240 -> 24, 5 x 5  35 us, low 42)
     const double margin = windows && rows == 64 ? 0.85 : 0.92;

@@ -111,3 +111,18 @@ def _size(name, *args):
 def conv_fwd(B, H, W, C, N, R, S, stride, pad, x_offset=0):
     return ("cdl_qconv_fwd", [(POINTER, A), (POINTER, A)] + [(INT, v) for v in (B, H, W, C, N, R, S, stride, pad)] + [(FLOAT, 0.5), (FLOAT, 0.25), (INT, x_offset), (POINTER, None),
             (POINTER, A), (POINTER, A), (SIZE, 256 + (N * 4 + 255) // 256 * 256), (POINTER, None)])
+
+
+def gemm_fwd(M, N, K):
+    return ("cdl_qgemm_fwd", [(POINTER, A), (POINTER, A), (INT, M), (INT, N), (INT, K), (FLOAT, 0.5), (FLOAT, 0.25), (POINTER, None), (POINTER, A), (POINTER, A), (SIZE, 1 << 40), (POINTER, None)])
+
+
+RINGS = {"RingShape<2, 4, 4, 2, 5, 1>": "wide", "RingShape<2, 2, 4, 2, 3, 2>": "tall", "RingShape<4, 1, 2, 2, 4, 2>": "narrow", "RingShape<2, 2, 2, 2, 5, 2>": "square", "RingShape<4, 1, 1, 2, 6, 2>": "low"}
+
+
+def tile_form(launches):
+    """Of a forward product: the tiles with direct loads (256 x 256, 256 x 128, 256 x 64, 128 x 128, 128 x 64), or staged ones, or another kernel."""
+    names = [l.name for l in launches if "dma_kernel" in l.name]
+    if names:
+        return next(form for shape, form in RINGS.items() if shape in names[0])
+    return "staged" if any("::qgemm_kernel<" in l.name or "::qconv_kernel<" in l.name for l in launches) else "other"

@@ -748,6 +748,7 @@ struct DirectArgs {
     unsigned long long tag;
     float delta_a, delta_b;
     int *column_sums;              // [splits][cols] of dL/dQ(b), where that is cut into pieces: direct_reduce_kernel finishes then; else null
+    const unsigned int *col_abs_b; // the largest sum of |index| of dL/dQ(a), where that was formed before; else null
 };
 
 struct DirectItem {
@@ -876,6 +877,7 @@ void bwd_direct_kernel(DirectArgs a)
                 sa = max(sa, red[kDirWaves + w]);
                 sb = max(sb, red[2 * kDirWaves + w]);
             }
+            if (a.col_abs_b) sb = *a.col_abs_b;
             choose_limbs(a.plan, gm, sa, sb, a.delta_a, a.delta_b);
         }
     }
@@ -1223,6 +1225,7 @@ struct ReduceDiag {
     unsigned long long tag;
     float delta_a, delta_b;
     BwdPlan *plan;
+    const unsigned int *col_abs_b;     // as in DirectArgs
 };
 
 // out[i] = delta * sum over splits of partial[split][i], eight splits side by side per output.  DIAG: the first ceil(cols / 32) blocks
@@ -1297,6 +1300,7 @@ void direct_reduce_kernel(const double *__restrict__ partial, int splits, int64_
         if (threadIdx.x == 0) {
 #pragma unroll
             for (int w = 1; w < 4; ++w) { gm = max(gm, red[0][w]); sa = max(sa, red[1][w]); sb = max(sb, red[2][w]); }
+            if (dg.col_abs_b) sb = *dg.col_abs_b;
             choose_limbs(dg.plan, gm, sa, sb, dg.delta_a, dg.delta_b);
         }
     }
@@ -1482,7 +1486,7 @@ static double padded_macs(int64_t rows, int64_t kc, int64_t cols) { return (doub
 // Up to kBwdDirectNoDiag the diagnostic words say that neither product has limbs.
 constexpr int64_t kBwdDirectNoDiag = 1ll << 25;
 
-static bool bwd_direct_diag(int32_t M, int32_t N, int32_t K) { return N > 32 && (int64_t)M * N * K > kBwdDirectNoDiag; }
+bool bwd_direct_diag(int32_t M, int32_t N, int32_t K) { return N > 32 && (int64_t)M * N * K > kBwdDirectNoDiag; }
 
 // DirectProduct::rounds_to.  Where sums in double are the alternative (`exact`) nothing is rounded.  Beyond, the alternative are limbs, whose
 // rounding may change an output by kLimbBoundTarget, and digits may round (entries 2^-20 of their row's largest and smaller, by half a unit,
@@ -1560,7 +1564,7 @@ bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool only_b, double *par
 
 int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float delta_a, float delta_b,
                       int32_t a_offset, int32_t b_offset, float *d_a_hat, float *d_b_hat, BwdPlan *plan, void *records, double *partial, int max_splits,
-                      bool only_b, bool words, hipStream_t stream)
+                      bool only_b, bool words, const unsigned int *col_abs_b, hipStream_t stream)
 {
     const bool diag = words && bwd_direct_diag(M, N, K);
     BwdDirectPlan d;
@@ -1590,6 +1594,7 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
     const int splits = d_b_hat ? d.b.splits : 1;
     if (diag) {
         a.tag = next_finish_tag();
+        a.col_abs_b = col_abs_b;
         if (splits > 1) a.column_sums = reinterpret_cast<int *>(partial + (int64_t)splits * N * K);
     }
 #define CDL_DIRECT(KERNEL) CDL_LAUNCH("bwd_direct_kernel", stream, (KERNEL), dim3(grid), dim3(kDirThreads), 0, a)
@@ -1604,7 +1609,7 @@ int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, 
         const dim3 blocks((unsigned)ceil_div(n_out, 32));
         if (diag) {
             const int b_first = a.a_at == 0 ? a.first : 0, b_end = a.a_at == 0 ? (int)grid : a.first;
-            const ReduceDiag dg{a.column_sums, K, a.records, (int)grid, b_first, b_end, a.records + kDirRecords, next_finish_tag(), delta_a, delta_b, plan};
+            const ReduceDiag dg{a.column_sums, K, a.records, (int)grid, b_first, b_end, a.records + kDirRecords, next_finish_tag(), delta_a, delta_b, plan, col_abs_b};
             CDL_LAUNCH("direct_reduce_kernel", stream, direct_reduce_kernel<true>, blocks, dim3(256), 0, partial, splits, n_out, (double)delta_a, d_b_hat, dg);
         } else {
             CDL_LAUNCH("direct_reduce_kernel", stream, direct_reduce_kernel<false>, blocks, dim3(256), 0, partial, splits, n_out, (double)delta_a, d_b_hat, ReduceDiag{});

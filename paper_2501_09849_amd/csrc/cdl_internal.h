@@ -145,14 +145,16 @@ struct ConvWindows {
 };
 
 // Both products of a small layer directly (cdl_bwd_direct.hip).  only_b: for a layer whose dL/dQ(a) is formed
-// elsewhere (the plan is the same whichever of the others are asked for).  words: the diagnostic words may have to tell limb counts.
+// elsewhere (the plan is the same whichever of the others are asked for).  words: the diagnostic words may have to tell limb counts; col_abs_b: what they need of a dL/dQ(a) formed elsewhere, or null.
 // asked: products (1 or 2) that are to be exact where sums in double serve; 0: by time alone.
 struct BwdPlan;
 constexpr size_t kBwdDirectRecordBytes = 8192 * 2 * sizeof(unsigned long long);
 bool bwd_direct_serves(int32_t M, int32_t N, int32_t K, bool only_b, double *partial, int max_splits, bool words, int asked);
 int launch_bwd_direct(const float *g, const int8_t *a_idx, const int8_t *b_idx, int32_t M, int32_t N, int32_t K, float delta_a, float delta_b,
                       int32_t a_offset, int32_t b_offset, float *d_a_hat, float *d_b_hat, BwdPlan *plan, void *records, double *partial, int max_splits,
-                      bool only_b, bool words, hipStream_t stream);
+                      bool only_b, bool words, const unsigned int *col_abs_b, hipStream_t stream);
+// Whether the diagnostic words of a product formed directly tell the limb counts and bounds that limbs would have had (else: no limbs).
+bool bwd_direct_diag(int32_t M, int32_t N, int32_t K);
 
 // The same for the gradients of a convolution, by classes of input pixels (cdl_conv_patch.h).
 bool conv_dw_direct_serves(int64_t M, int32_t N, int32_t K);

@@ -1703,8 +1703,8 @@ constexpr int kDirectMaxN = 32, kDirectWideN = 64;
 // Where it serves before bwd_direct_kernel, whose waves take one step of a short contraction each: many outputs, and long ones from fewer on.  us, that / this, alone: 16 entries, 4096 x 256 (rows x columns) 5.3 / 6.9, 16384 x 144 12.6 / 8.0,
 // 2048 x 1500 12.9 / 10.7, 65536 x 16 11.9 / 5.0, 32768 x 36 7.0 / 5.4, 131072 x 27 23.6 / 9.2; 32 entries, 8192 x 200 7.9 / 8.2, 16384 x 144 13.1 / 9.5.  With the weight gradient, which that kernel makes in the same launch: 16 entries, 16384 x 144
 // 15.9 / 20.2, 50000 x 64 17.3 / 21.3, 2048 x 1500 13.6 / 22.2, 65536 x 16 20.2 / 14.3, 65536 x 60 21.4 / 19.7, 131072 x 9 32.9 / 18.4; 32 entries, 65536 x 36 21.0 / 19.6, 65536 x 60 22.7 / 25.2, 100000 x 40 33.4 / 31.6, 200000 x 9 54.8 / 32.3.
-// 33 to 64 entries in long layers of few columns (one wave has all columns; the other kernels' steps are as short, and more of them), us, that / this: alone 64 entries, 65536 x 27 17.8 / 12.8, 131072 x 9 32.2 / 14.7, 400000 x 32 90 / 46,
-// 65536 x 64 16.6 / 19.0, 32768 x 36 9.6 / 11.0; 48 entries, 65536 x 64 18.2 / 15.4, 131072 x 144 44.3 / 47.3; 33 entries, 3 M x 32 1635 / 206; both products, 64 entries, 65536 x 27 35.6 / 33.1, 65536 x 48 34.7 / 37.7, 32768 x 27 24.5 / 27.0;
+// 33 to 64 entries in long layers of few columns (one wave has all columns; the other kernels' steps are as short, and more of them), us, that / this with the diagnostic words (1.3 - 1.8 us of it alone): alone 64 entries, 65536 x 27 17.7 / 14.6, 131072 x 9 32.2 / 16.3, 400000 x 32 90 / 48.7,
+// 65536 x 64 16.6 / 19.0 (without words), 32768 x 36 9.6 / 11.0 (without); 48 entries, 65536 x 64 18.0 / 16.6, 131072 x 144 44.3 / 47.3 (without); 33 entries, 3 M x 32 1633 / 208; both products, 64 entries, 65536 x 27 35.2 / 33.7, 65536 x 48 34.7 / 37.7, 32768 x 27 24.5 / 27.0;
 // 48 entries, 65536 x 27 35.3 / 30.7, 65536 x 64 35.9 / 37.1, 400000 x 32 136 / 79.
 bool da_direct_preferred(int M, int N, int K, bool both)
 {
@@ -1726,24 +1726,35 @@ bool direct_staged(int64_t outputs, bool words) { return outputs >= (words ? 650
 // Waves: two per SIMD (four: 131072 x 16 x 144 20.7 / 21.5, 460000 rows through LDS 72 / 74), four where their tiles in LDS leave room and a trip is short (1 M x 32 x 48 82 / 74, 3 M x 16 x 27 112 / 98).
 int direct_waves(bool staged, int col_tiles) { return staged && col_tiles <= 5 ? 4096 : 2048; }
 
+// The diagnostic words of a call whose dL/dQ(a) is formed here.  (The last block waits for the others, all of lower numbers: cdl_finish.h.)
+struct DaWords {
+    BwdPlan *plan;                 // null: another product follows, and tells
+    // beyond 32 entries, where the words tell the limb counts and bounds that limbs would have had (bwd_direct_diag):
+    unsigned long long *records;   // [gridDim.x][2]: the blocks' largest |g|, and the first one's of the next line, from which the last block makes the plan; null: no limbs
+    unsigned long long tag;
+    float delta_a, delta_b;
+    unsigned int *col_abs;         // [1]: the largest sum of |index| of a column, for the product that follows; null: none does
+};
+
 template <int NN, DaStore STORE>
 __global__ __launch_bounds__(256, NN <= 32 ? 4 : 2)
 void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_idx, int M, int N, int K, int col_tiles /* per wave */, int blocks /* per group of them */,
-                      double delta_b, double b_offset, float *__restrict__ out, BwdPlan *plan /* null: another product follows */)
+                      double delta_b, double b_offset, float *__restrict__ out, DaWords words)
 {
     typedef double v4d __attribute__((ext_vector_type(4)));
     constexpr int C = direct_tiles(NN), H = NN / 16;
     constexpr bool VEC = STORE == kDaWords || STORE == kDaRows, STAGED = STORE == kDaRows || STORE == kDaFlat;
     extern __shared__ __align__(16) float da_lds[];
-    if (plan && blockIdx.x == 0 && threadIdx.x == 0) no_limbs(plan);
+    if (words.plan && !words.records && blockIdx.x == 0 && threadIdx.x == 0) no_limbs(words.plan);
     const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
     const int group = (int)blockIdx.x / blocks, k0 = group * col_tiles * 16;
     const int tiles = min(col_tiles, (K - k0 + 15) / 16);
     const int row_tiles = (M - 1) / 16 + 1, step = blocks * 4;
     int rt = ((int)blockIdx.x - group * blocks) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (rt >= row_tiles) return;
+    if (NN <= 32 && rt >= row_tiles) return;
 
     const bool whole = N % 4 == 0;
+    unsigned int amax = 0u;
     auto load = [&](int tile, float (&v)[H][4]) {
         const int row = tile * 16 + i;
         const float *src = g + (int64_t)row * N;
@@ -1773,6 +1784,25 @@ void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_
                 b[t][h][j] = t < tiles && n < N && k < K ? (double)b_idx[(int64_t)n * K + k] + b_offset : 0.0;     // (the level index itself)
             }
     }
+    // the largest sum of |index| of a column, from the registers: in the first block's first wave, before its loop (at the end, where the last block waits, 1 us)
+    unsigned int columns = 0u;
+    if (NN > 32 && blockIdx.x == 0 && threadIdx.x < 64) {
+#pragma unroll
+        for (int t = 0; t < C; ++t) {
+            double sum = 0.0;
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum += 16 * h + 4 * q + j < N ? fabs(b[t][h][j] - b_offset) : 0.0;
+            sum += __shfl_xor(sum, 16, 64);
+            sum += __shfl_xor(sum, 32, 64);
+            const int k = k0 + 16 * t + (VEC ? 4 * (i & 3) + (i >> 2) : i);
+            columns = max(columns, t < tiles && k < K ? (unsigned int)sum : 0u);
+        }
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) columns = max(columns, (unsigned int)__shfl_xor((int)columns, off, 64));
+        if (words.col_abs && lane == 0) *words.col_abs = columns;
+    }
     // the wave's tile of outputs on its way to stores of neighbouring addresses: kDaRows rows of `pitch` words, kDaFlat as in memory (all columns)
     const int pitch = col_tiles * 16 + 4, width = min(col_tiles * 4, (K - k0) >> 2);
     float *const mine = da_lds + (threadIdx.x >> 6) * 16 * pitch;
@@ -1782,7 +1812,10 @@ void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_
 #pragma unroll
         for (int h = 0; h < H; ++h)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) gv[h][j] = (double)next[h][j];
+            for (int j = 0; j < 4; ++j) {
+                gv[h][j] = (double)next[h][j];
+                if (NN > 32) amax = max(amax, __float_as_uint(next[h][j]) & 0x7fffffffu);
+            }
         if (rt + step < row_tiles) load(rt + step, next);
 #pragma unroll
         for (int t = 0; t < C; ++t) {
@@ -1831,6 +1864,41 @@ void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+    }
+    if constexpr (NN > 32) {      // (host: one group of columns)
+        if (!words.records) return;
+        __shared__ unsigned int red[2][4];
+        auto block_max = [&](unsigned int v, int which) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v = max(v, (unsigned int)__shfl_xor((int)v, off, 64));
+            if (lane == 0) red[which][threadIdx.x >> 6] = v;
+            __syncthreads();
+            return max(max(red[which][0], red[which][1]), max(red[which][2], red[which][3]));
+        };
+        amax = block_max(amax, 0);
+        if (blockIdx.x != gridDim.x - 1) {
+            if (threadIdx.x == 0) {
+                const unsigned long long v = (unsigned long long)amax << 32 | columns;
+                device_store(words.records + 2 * (size_t)blockIdx.x, v);
+                device_store(words.records + 2 * (size_t)blockIdx.x + 1, v ^ words.tag);
+            }
+            return;
+        }
+        for (int k = threadIdx.x; k < (int)gridDim.x - 1; k += 256) {
+            unsigned long long *r = words.records + 2 * (size_t)k;
+            unsigned long long v, c;
+            do {
+                v = device_load(r);
+                c = device_load(r + 1);
+            } while ((v ^ c) != words.tag);
+            device_store(r + 1, v);
+            amax = max(amax, (unsigned int)(v >> 32));
+            columns = max(columns, (unsigned int)v);
+        }
+        __syncthreads();
+        amax = block_max(amax, 0);
+        columns = block_max(columns, 1);
+        if (threadIdx.x == 0) choose_limbs(words.plan, amax, 0u, columns, words.delta_a, words.delta_b);
     }
 }
 
@@ -2849,6 +2917,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     if (cw && conv_dw_direct_serves(M, N, K)) return launch_conv_dw_direct(gr, a_idx, *cw, N, delta_a, a_offset, d_b_hat, partial, L.direct_splits, stream);
     // (many outputs of few multiplications each: see da_direct_kernel)
     const bool only_b = is_conv_weights || da_direct_preferred(M, N, K, want_db) || (N <= kDirectMaxN && !bwd_direct_serves(M, N, K, false, partial, L.direct_splits, true, 0));
+    const unsigned int *col_abs_b = nullptr;      // the largest sum of |b_idx| of a column, for the words, where dL/dQ(a) is formed before the plan is made
     if (d_a_hat && only_b) {
         // (blocks of four waves per group of columns: as many as the chip holds, at most one wave per tile of rows)
         const int most = direct_tiles((N + 15) / 16 * 16), all = (K + 15) / 16, groups = (all + most - 1) / most;
@@ -2859,7 +2928,14 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         const int used = (all + col_tiles - 1) / col_tiles;
         const dim3 grid(used * blocks);
         const size_t lds = (size_t)4 * 16 * (col_tiles * 16 + 4) * sizeof(float);
-        BwdPlan *words = want_db ? nullptr : plan;
+        // (the words: all of them here, or what another product's cannot know)
+        DaWords words{want_db ? nullptr : plan, nullptr, 0ull, delta_a, delta_b, nullptr};
+        if (N > 32 && want_db) col_abs_b = words.col_abs = reinterpret_cast<unsigned int *>(base + L.ss_b);
+        if (!want_db && bwd_direct_diag(M, N, K)) {
+            words.records = reinterpret_cast<unsigned long long *>(base + L.records);
+            words.tag = next_finish_tag();
+            if (grid.x > kBwdDirectRecordBytes / (2 * sizeof(unsigned long long))) return CDL_ERR_PARAM;      // (at most 512 blocks)
+        }
 #define CDL_DA_N(NN, STORE) CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<NN, STORE>), grid, dim3(256), STORE == kDaRows || STORE == kDaFlat ? lds : 0, gr, b_idx, M, N, K, col_tiles, blocks, (double)delta_b, (double)b_offset, d_a_hat, words)
 #define CDL_DA(STORE) do { if (N <= 16) CDL_DA_N(16, STORE); else CDL_DA_N(32, STORE); } while (0)
 #define CDL_DA_WIDE(STORE) do { if (N <= 48) CDL_DA_N(48, STORE); else CDL_DA_N(64, STORE); } while (0)
@@ -2876,7 +2952,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
 
     const int asked = (d_a_hat ? 1 : 0) + (want_db ? 1 : 0);
     if (!cw && bwd_direct_serves(M, N, K, only_b, partial, L.direct_splits, !is_conv_weights, asked))
-        return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.direct_splits, only_b, !is_conv_weights, stream);
+        return launch_bwd_direct(gr, a_idx, b_idx, M, N, K, delta_a, delta_b, a_offset, b_offset, d_a_hat, d_b_hat, plan, base + L.records, partial, L.direct_splits, only_b, !is_conv_weights, col_abs_b, stream);
 
     const bool by_rows = d_a_hat && limb_by_rows(M, N, K, L.splits);
     int8_t *bt = reinterpret_cast<int8_t *>(base + L.bt);
@@ -2887,7 +2963,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
     unsigned int *ss_b = reinterpret_cast<unsigned int *>(base + L.ss_b);
     // the column sums that the weight gradient needs besides (below) are of the same pass over g as its largest entry
     int n_max = L.n_max;
-    const int n_clear = (int)((L.ss_b - L.ss_a) / sizeof(unsigned int)) + K;
+    const int n_clear = (int)((L.ss_b - L.ss_a) / sizeof(unsigned int)) + (col_abs_b ? 0 : K);
     if (want_db && a_offset != 0) {
         double *cp = reinterpret_cast<double *>(base + L.colsum_partial);
         const int most = L.n_max < kColsumBlocks ? L.n_max : kColsumBlocks, rows_per = (M + most - 1) / most;
@@ -2902,7 +2978,7 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
         TransposeJob ja{}, jb{};
         if (want_db) ja = transpose_job(a_idx, M, K, at, L.ldm, ss_a);
         if (d_a_hat) (want_db ? jb : ja) = transpose_job(b_idx, N, K, bt, L.ldn, ss_b, by_rows);
-        const PlanArgs pa{plan, block_max, n_max, ss_a, ss_b, want_db ? K : 0, d_a_hat ? K : 0, delta_a, delta_b, nullptr, 0ull};
+        const PlanArgs pa{plan, block_max, n_max, ss_a, ss_b, want_db ? K : 0, d_a_hat ? K : col_abs_b ? 1 : 0, delta_a, delta_b, nullptr, 0ull};
         ConvGeom g{};
         if (cw) {
             g = ConvGeom{cw->B, cw->H, cw->W, cw->C, cw->R, cw->S, cw->stride, cw->pad, cw->P, cw->Q, 0, make_div_by((uint32_t)cw->P * (uint32_t)cw->Q), make_div_by((uint32_t)cw->Q)};

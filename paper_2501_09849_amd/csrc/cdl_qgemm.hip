@@ -1804,9 +1804,14 @@ void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_
         if (words.col_abs && lane == 0) *words.col_abs = columns;
     }
     // the wave's tile of outputs on its way to stores of neighbouring addresses: kDaRows rows of `pitch` words, kDaFlat as in memory (all columns)
-    const int pitch = col_tiles * 16 + 4, width = min(col_tiles * 4, (K - k0) >> 2);
+    const int pitch = col_tiles * 16 + 4;
     float *const mine = da_lds + (threadIdx.x >> 6) * 16 * pitch;
-    const int row_first = lane / width, col_first = lane - row_first * width, row_step = 64 / width, col_step = 64 - row_step * width;
+    int width = 0, row_first = 0, col_first = 0, row_step = 0, col_step = 0;
+    if constexpr (STORE == kDaRows) {      // (rows of whole words: every group has one at least)
+        width = min(col_tiles * 4, (K - k0) >> 2);
+        row_first = lane / width; col_first = lane - row_first * width;
+        row_step = 64 / width; col_step = 64 - row_step * width;
+    }
     for (; rt < row_tiles; rt += step) {
         double gv[H][4];
 #pragma unroll

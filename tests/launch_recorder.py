@@ -126,3 +126,9 @@ def tile_form(launches):
     if names:
         return next(form for shape, form in RINGS.items() if shape in names[0])
     return "staged" if any("::qgemm_kernel<" in l.name or "::qconv_kernel<" in l.name for l in launches) else "other"
+
+
+def gemm_bwd(M, N, K, want, b_offset=0):
+    """want: a, b or both"""
+    return ("cdl_qgemm_bwd_offset", [(POINTER, A), (POINTER, A), (POINTER, A), (INT, M), (INT, N), (INT, K), (FLOAT, 0.5), (FLOAT, 0.25), (INT, 0), (INT, b_offset), (POINTER, A if want != "b" else None),
+            (POINTER, A if want != "a" else None), (POINTER, A), (SIZE, 1 << 40), (POINTER, None)])

@@ -4,6 +4,7 @@ import shutil
 import pytest
 
 import launch_recorder as lr
+import ring_cases
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None or shutil.which("c++filt") is None, reason="no host compiler")
 
@@ -31,3 +32,43 @@ def test_forms_of_matrix_products(tmp_path, form, products):
     ("wide", [(370, 19, 22, 64, 460, 1, 1, 1, 0), (164, 99, 25, 128, 196, 1, 1, 1, 0), (256, 14, 14, 256, 256, 3, 3, 1, 1)]), ("narrow", [(128, 56, 56, 64, 64, 3, 3, 1, 1)]), ("tall", [(128, 28, 28, 128, 128, 3, 3, 1, 1)])])
 def test_forms_of_layers(tmp_path, form, layers):
     assert [(g, lr.tile_form(s[0])) for g, s in zip(layers, lr.record(tmp_path, [lr.conv_fwd(*g) for g in layers]))] == [(g, form) for g in layers]
+
+
+def _ring(launches):
+    """form, stores past the caches, K-tiles across taps"""
+    form = lr.tile_form(launches)
+    flags = [l.name.split(">, ", 1)[1].split(">", 1)[0].split(", ") for l in launches if "dma_kernel" in l.name]
+    return (form,) + tuple(f == "true" for f in flags[0]) if flags else (form,)
+
+
+def test_cases_of_the_rings_take_the_forms_that_they_name(tmp_path):
+    """Every form of matrices and of layers, of both kinds of K-tiles, and every one that stores past the caches, is among them."""
+    seen = [_ring(s[0]) for s in lr.record(tmp_path, [lr.gemm_fwd(*c[0]) for c in ring_cases.MATRICES] + [lr.conv_fwd(*c[0]) for c in ring_cases.LAYERS])]
+    matrices, layers = seen[:len(ring_cases.MATRICES)], seen[len(ring_cases.MATRICES):]
+    assert matrices == [(form, stream) for _, form, stream in ring_cases.MATRICES]
+    assert layers == [(form, stream, geom[3] % 64 != 0) for geom, form, stream in ring_cases.LAYERS]
+    forms = {"wide", "tall", "narrow", "square", "low"}
+    assert {m[0] for m in matrices} == forms and {m[0] for m in matrices if m[1]} == forms - {"low"}
+    assert {(l[0], l[2]) for l in layers} == {(f, across) for f in forms for across in (False, True)}
+    assert sum(shape[2] <= 192 and form == "wide" for shape, form, _ in ring_cases.MATRICES) >= 4
+
+
+def _direct(launches):
+    """Rows of the contraction that a wave of da_direct_kernel holds and how it stores (0: words, 1: scalars, 2, 3: through LDS in rows of whole words, of any length); None: another kernel."""
+    names = [l.name for l in launches if "da_direct_kernel" in l.name]
+    if not names:
+        return None
+    held, store = names[0].split("da_direct_kernel<", 1)[1].split(">", 1)[0].split(", ", 1)
+    return int(held), int(store.rsplit(")", 1)[1])
+
+
+def test_cases_of_the_activation_gradient_of_short_contractions(tmp_path):
+    """test_gpu_da_direct.py: every way of storing for every length that has it, and both sides of the lines on outputs, rows, contraction and columns."""
+    import test_gpu_da_direct as cases
+    seen = dict(zip(cases.CASES, (_direct(s[0]) for s in lr.record(tmp_path, [lr.gemm_bwd(*c, "a") for c in cases.CASES]))))
+    others = {(32767, 16, 64), (32767, 32, 33), (65535, 33, 32), (65537, 48, 65), (65536, 64, 33)}
+    assert {c for c in cases.CASES if seen[c] is None} == others
+    assert {v for v in seen.values() if v} == {(16, 0), (16, 1), (16, 2), (16, 3), (32, 0), (32, 1), (32, 2), (32, 3), (48, 0), (48, 1), (64, 0), (64, 1)}
+    both = next(m for m in cases.test_both.pytestmark if m.name == "parametrize").args[1]
+    seen = dict(zip(both, (_direct(s[0]) for s in lr.record(tmp_path, [lr.gemm_bwd(*c, "both") for c in both]))))
+    assert {c for c in both if seen[c] is None} == {(65535, 16, 17), (65536, 17, 41), (65536, 48, 33)}

@@ -53,11 +53,11 @@ __device__ __forceinline__ void with_constant(bool yes, F f)
 }
 
 // group(v, N, RAGGED): N vectors of four entries v, v + T, .. of the first `vectors`, of which `whole` have four.  U > 1: U vectors a thread in the block's one trip (without a branch
-// around any: it would take the loads with it, behind the stores), in the last block one at a time.  U == 1: a loop over the tensor.
+// around any: it would take the loads with it, behind the stores), in the last block one at a time.  U == 1: a loop over the tensor (of the first `blocks` blocks, where that is not 0).
 // RAGGED: the last vector may have fewer entries, which puts a branch around the loads of a loop.  Whole tensors go without where all blocks are short (quantizer gradient, 0.5 M entries of 31 levels, two
 // on each side 6.1 us, with it 6.5; 2.1 M, four 11.5 / 12.1), but the loops of larger ones are faster with it (2.1 M, four on each side without scalars 9.4 / 8.8; 24 M, gradient of the entropy added 57 / 53).
 template <int T, int U, typename F>
-__device__ __forceinline__ void one_trip_or_loop(int64_t whole, int64_t vectors, F group, unsigned int blocks = gridDim.x)
+__device__ __forceinline__ void one_trip_or_loop(int64_t whole, int64_t vectors, F group, int blocks = 0)
 {
     const int64_t v0 = (int64_t)blockIdx.x * T * U;
     if (U > 1 && v0 + T * U <= whole) group(v0 + threadIdx.x, std::integral_constant<int, U>{}, std::false_type{});
@@ -65,7 +65,7 @@ __device__ __forceinline__ void one_trip_or_loop(int64_t whole, int64_t vectors,
         const int64_t end = U > 1 ? (v0 + T * U < vectors ? v0 + T * U : vectors) : vectors;
         auto loop = [&](auto ragged) {
 #pragma unroll 1
-            for (int64_t v = v0 + threadIdx.x; v < end; v += U > 1 ? T : (int64_t)blocks * T) group(v, std::integral_constant<int, 1>{}, ragged);
+            for (int64_t v = v0 + threadIdx.x; v < end; v += U > 1 ? T : (int64_t)(blocks ? blocks : gridDim.x) * T) group(v, std::integral_constant<int, 1>{}, ragged);
         };
         if (U > 1 || vectors > whole || whole > (int64_t)kMaxQuantBlocks * T) loop(std::true_type{});
         else loop(std::false_type{});
@@ -199,13 +199,12 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
     constexpr int R = kHistCopies;
     constexpr int T = MARG ? kMargThreads : one_trip_threads(U);
     unsigned int *my_hist = lds_hist + (int)(threadIdx.x & (R - 1)) - k.lo * R;
-    unsigned int blocks = gridDim.x;      // that have entries
-    if constexpr (MARG && FORM == kMargSlices) {
+    constexpr bool SLICES = MARG && FORM == kMargSlices;
+    if constexpr (SLICES) {
         if (fin.roles.collects((int)blockIdx.x)) {
             rows_collect<T, 8>(k.n_levels, fin);
             return;
         }
-        blocks = (unsigned int)fin.roles.workers;
     }
     if (MARG) {
         const int cells = (k.n_levels + 2 * kPad) * R;
@@ -253,12 +252,12 @@ void quantize_fwd_kernel(const float *__restrict__ theta, int64_t n, QConst k,
 #pragma unroll
                 for (int u = 0; u < N; ++u) vec(t[u], v + u * T);
             };
-            one_trip_or_loop<T, U>(n4, n4, group, blocks);      // (the tail is below)
+            one_trip_or_loop<T, U>(n4, n4, group, SLICES ? fin.roles.workers : 0);      // (the tail is below)
         }
     });
-    // ragged tail: the last 1..3 entries, one thread of the last block
+    // ragged tail: the last 1..3 entries, one thread of the last block that has entries
     const int cnt = (int)(n - (n4 << 2));
-    if (cnt > 0 && blockIdx.x == blocks - 1 && threadIdx.x == 0) {
+    if (cnt > 0 && blockIdx.x == (SLICES ? (unsigned int)fin.roles.workers : gridDim.x) - 1 && threadIdx.x == 0) {
         float th[4];
         for (int e = 0; e < 4; ++e) th[e] = (e < cnt) ? theta[(n4 << 2) + e] : 0.0f;
         forward4<W, IDX, MARG>(th, cnt, k, my_hist, sv, ci);

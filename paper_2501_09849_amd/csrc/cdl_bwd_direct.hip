@@ -1513,7 +1513,8 @@ struct BwdDirectPlan {
     double us;             // on digits: what it takes
 };
 
-// (by the layer's sizes alone: an output is formed in the same order whether or not the other one is asked for too)
+// (by the layer's sizes alone: an output that is formed here is formed in the same order whether or not the other one is asked for too; whether dL/dQ(a) of a short contraction is, and
+// what is served here between 0.35 and 0.7 G multiply-adds, depends on that: da_direct_preferred, bwd_direct_serves)
 static void plan_bwd_direct(BwdDirectPlan &d, int32_t M, int32_t N, int32_t K, bool only_b, bool diag, double *partial, int max_splits)
 {
     d.a = d.b = DirectProduct{};

@@ -21,13 +21,12 @@
 // launch of the process uses, and the reader spoils the check word of every record it has taken, so that a captured
 // launch can be replayed with the tag it was captured with.
 //
-// Every wait ends.  Of a histogram in slices the collectors wait, sixteen at most behind 256 blocks at most: for blocks of lower numbers alone (cdl_marg_slices.h).
-// Of the scalar sums only the last block of each group of 256 and the last of the grid wait: a group's last for the others of its group, which wait for
-// nobody, the grid's last for those and for the groups' last ones, so all for blocks of lower numbers.  Grids with records have at most 4097 blocks (2^23
-// entries in one trip), more than are resident, but of them at most 17 wait, and an XCD holds a block on each of its 32 compute units at least: the others
-// finish beside them and make room for all that have not started.  With more launches at a time than that leaves room for, it rests on an XCD
-// starting a launch's blocks in order of their numbers: the waiting ones with a number of 255 and so on lie on one XCD, where the blocks that
-// they wait for have then started, and the other XCDs hold at most one that waits of a launch.
+// Every wait ends: a block waits for blocks of lower numbers of its launch alone.  Of a histogram in slices the collectors do, sixteen at most behind 256 blocks at most
+// (cdl_marg_slices.h), else the last block; of the scalar sums the last block of each group of 256 waits for the others of its group, which wait for nobody, and the
+// grid's last for those and for the groups' last ones; of diagnostic words and plans the last block.  An XCD starts a launch's blocks in the order of their numbers, so that the lowest
+// one that has not ended has a place or is the next to get one, and it waits for nobody that has not ended: a launch by itself ends with one place on each XCD.  (Grids with records have up to
+// 4097 blocks, 2^23 entries in one trip, more than are resident.)  Launches on several streams share the places: of one at most two collectors, or the 17 last blocks of groups (those with a number of 255 and so on),
+// wait on an XCD, which holds a block on each of its 32 compute units at least, and the others finish beside them.
 #pragma once
 
 #include "cdl_internal.h"

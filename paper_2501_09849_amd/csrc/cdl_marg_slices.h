@@ -10,8 +10,9 @@ namespace cdl {
 // Most blocks that finish a grid's histograms between them.
 constexpr int kMargCollectors = 16;
 
-// Levels of a slice, as a power of two: slices of 16 KB at least of what the blocks leave (8 bytes a level and block) and below 32 KB (one round of loads of 512 threads), up to
-// sixteen slices.
+// Levels of a slice, as a power of two: up to sixteen slices of 16 to 32 KB of what the blocks leave (8 bytes a level and block; one round of loads of 512 threads), or one of all.
+// us of the forward pass, slices of 16 to 32 KB / at most 16 / at most 8: 1 M entries of 63 levels 9.6 / 10.3 / 10.9, 400 K of 40 8.4 / 9.0 / 9.2, 65536 of 255 7.8 / 8.2 / 8.6, 2.1 M of 255
+// 13.0 / 13.0 / 13.3.
 inline int marg_lg_per(int64_t blocks, int n_levels)
 {
     int lg = 2;

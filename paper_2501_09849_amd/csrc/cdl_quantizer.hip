@@ -988,10 +988,11 @@ bool hist_half(int64_t n, const QConst &k, int uniform_half)
 constexpr int kHistVectors = 2;
 bool hist_ahead(int64_t n, const QConst &k) { return n >= kHistFullFrom && (band_template(k) == 1 || band_template(k) == 2); }
 
-// Who adds up the blocks' histograms.  Up to 256 blocks finish the job themselves: the last one where their records are 64 KB at most, beyond, the last ones, a slice of the
-// levels each (cdl_marginal.h; the unrolled bands only, the others keep one block up to 256 KB).  Blocks of one trip and more than 256 KB, and larger grids, leave rows for a second launch.
-// us of the forward pass, second launch / slices: 131 K entries of 255 levels (64 blocks, one trip) 8.3 / 8.6, 512 K 9.3 / 10.1;  700 K (171, two) 10.8 / 10.1, 1 M 12.1 / 10.8, 2.1 M (256, four) 13.3 / 13.1;
-// 1024 blocks: 6 M of 63 17.7 / 18.7, 25.6 M of 31 46.0 / 46.9.  Last block / slices: 65 K of 255 (32 blocks) 9.9 / 7.8;  63 levels 512 K (250) 15.6 / 8.8, 1 M (245, two) 16.7 / 9.6, 2.1 M 18.5 / 12.6.
+// Who adds up the blocks' histograms.  Up to 256 blocks finish the job themselves: the last one where they have 4096 records (of a level) at most, beyond, blocks of their own behind them, a slice of the
+// levels each (cdl_marg_slices.h; the unrolled bands only, the others keep the last block up to 16384).  Blocks of one trip and more than 16384 records, and larger grids, leave rows for a second launch.
+// us of the forward pass, second launch / slices: 65536 entries of 255 levels (33 blocks) 10.0 / 7.7, 131068 (64 blocks, 16320 records) 9.9 / 8.3, 262144 of 63 (129) 9.9 / 8.2, 700 K of 255 (171, two trips) 10.0 / 10.1, 2.1 M (256, four) 13.1 / 13.2;
+// beyond the line 131072 of 255 (65 blocks) 9.9 / 8.5, 524284 (256) 9.8 / 9.7, of 200 with four levels on each side 10.1 / 11.1 (the line is older than the collectors; up to 128 blocks it could go); 1024 blocks (the last ones with entries of their own): 6 M of 63 17.7 / 18.7, 25.6 M of 31 46.0 / 46.9.
+// Last block / slices: 65536 of 255 10.1 / 8.1;  63 levels 520 K (254) 15.4 / 9.2, 1 M (245, two) 16.9 / 10.0, 2.1 M 18.4 / 13.0.
 MargForm marg_form(int64_t blocks, int64_t n, const cdl_qparams &p, const QConst &k)
 {
     if (blocks > kFinishMaxBlocks) return kMargRows;

@@ -1439,14 +1439,17 @@ double plan_shared(DirectProduct &p, int max_splits, int &tiles)
     return least;
 }
 
-// Where they serve: by the two plans' times, of which that of plan_digits does not count what is read several times and is up to 2.2 times too short (36 of the 52 layers; the slowest of these against before
-// 10486 x 264 x 368 29.5 / 30.1, of the others 71132 x 20 x 70 was the better one by 4 %).  A second tile of a few columns is not worth its padding (270320 x 19 x 69 30.5 / 31.7).
+// Where they serve: by the two plans' times.  That of plan_digits does not count what is read several times: it is up to 2.2 times too short where the operands are long, and about right up to 5120 contraction
+// entries, or 20480 against groups of five and six tiles, whose waves have the longest rounds.  Of 530 layers of 1000 to 450000 entries, 20 to 360 rows and 80 to 1600 columns, each measured both ways, 209 are served, in 0.78 of
+// the time of digit_tile, ten of them more than 2 % slower (by one margin of 1.15 for all 34 of 237: 7259 x 320 x 608 30.4 / 37.1, 12354 x 120 x 528 24.6 / 29.6; left 99871 x 56 x 480 54.2 / 64.0, 13763 x 56 x 496 16.3 / 19.2).
+// A second tile of a few columns is not worth its padding (270320 x 19 x 69 30.5 / 31.7).
 bool shared_serves(const DirectProduct &p, int max_splits)
 {
     if (p.cols < 80 || p.kc < kDigitStep) return false;
     DirectProduct now = p, shared = p, *one = &now;
     int tiles;
-    return plan_shared(shared, max_splits, tiles) < 1.15 * plan_digits(&one, 1, max_splits);
+    const double us = plan_shared(shared, max_splits, tiles);
+    return us < (p.kc < (tiles >= 5 ? 20480 : 5120) ? 0.95 : 1.15) * plan_digits(&one, 1, max_splits);
 }
 
 int launch_shared(DirectProduct &p, int max_splits, BwdPlan *plan, hipStream_t stream)

@@ -132,3 +132,7 @@ def gemm_bwd(M, N, K, want, b_offset=0):
     """want: a, b or both"""
     return ("cdl_qgemm_bwd_offset", [(POINTER, A), (POINTER, A), (POINTER, A), (INT, M), (INT, N), (INT, K), (FLOAT, 0.5), (FLOAT, 0.25), (INT, 0), (INT, b_offset), (POINTER, A if want != "b" else None),
             (POINTER, A if want != "a" else None), (POINTER, A), (SIZE, 1 << 40), (POINTER, None)])
+
+
+def conv_bwd_weights(B, H, W, C, N, R, S, stride, pad, x_offset=0):
+    return ("cdl_qconv_bwd_weights", [(POINTER, A), (POINTER, A)] + [(INT, v) for v in (B, H, W, C, N, R, S, stride, pad)] + [(FLOAT, 0.5), (INT, x_offset), (POINTER, A), (POINTER, A), (SIZE, 1 << 40), (POINTER, None)])

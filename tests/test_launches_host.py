@@ -72,3 +72,13 @@ def test_cases_of_the_activation_gradient_of_short_contractions(tmp_path):
     both = next(m for m in cases.test_both.pytestmark if m.name == "parametrize").args[1]
     seen = dict(zip(both, (_direct(s[0]) for s in lr.record(tmp_path, [lr.gemm_bwd(*c, "both") for c in both]))))
     assert {c for c in both if seen[c] is None} == {(65535, 16, 17), (65536, 17, 41), (65536, 48, 33)}
+
+
+# contraction, rows, columns of the weight gradient of a 1 x 1 layer
+@pytest.mark.parametrize("shared,layers", [
+    (False, [(7259, 320, 608), (12354, 120, 528), (5201, 192, 912), (4554, 136, 1024), (13333, 160, 576), (6597, 56, 896), (15508, 76, 976), (2543, 264, 112)]),
+    (True, [(104_394, 48, 224), (131_072, 16, 144), (84_130, 20, 1376), (12_608, 268, 240), (9840, 284, 112)])])
+def test_weight_gradients_that_share_digits(tmp_path, shared, layers):
+    """Not short contractions, whose operands stay in the caches: each of those named here was slower (5 to 22 %) so."""
+    seen = lr.record(tmp_path, [lr.conv_bwd_weights(1, M, 1, K, N, 1, 1, 1, 0) for M, N, K in layers])
+    assert [any("dw_shared_kernel" in l.name for l in s[0]) for s in seen] == [shared] * len(layers)

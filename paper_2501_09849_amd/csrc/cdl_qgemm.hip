@@ -1907,6 +1907,50 @@ void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_
     }
 }
 
+// The same up to 16 entries for results well beyond the memory-side cache whose rows, of more columns than a wave holds, are no whole pieces of 64 bytes: a thread has four neighbouring columns, their index values in
+// registers, and goes over rows of g in LDS, so that the threads of a block write one row behind the other without a gap.  There the pieces of a row that waves of da_direct_kernel store apart begin and end inside lines of
+// memory.  us, da_direct_kernel / this (rows, contraction, columns): 271171 x 12 x 508 204 / 133, 319776 x 7 x 504 206 / 142, 142331 x 10 x 972 172 / 131, 590091 x 8 x 300 224 / 187, 339174 x 6 x 324 153 / 113; of 60 layers 48 with such rows 1.14 times as
+// long, 12 with rows of whole pieces 0.91 (117855 x 9 x 656 0.78, 683073 x 8 x 224 1.0); below 90 M outputs: 128872 x 6 x 572 (74 M) 72 / 95, 257589 x 7 x 276 (71 M) 72 / 84.  (The groups of the same rows side by side on an XCD in da_direct_kernel: no faster
+// here, 5 - 15 % slower elsewhere.)  Bound by its reads of LDS and the stores.
+constexpr int kDaColumnsRows = 128;
+bool da_columns_serves(int64_t M, int N, int K) { return N <= 16 && K % 4 == 0 && K % 16 != 0 && K > 16 * direct_tiles(16) && K <= 1 << 25 /* blocks in y */ && M * K >= 90000000; }
+
+__global__ __launch_bounds__(256)
+void da_columns_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_idx, int M, int N, int K, double delta_b, double b_offset, float *__restrict__ out, BwdPlan *plan /* null: another product follows */)
+{
+    constexpr int NN = 16, C = 4;
+    __shared__ double gs[kDaColumnsRows][NN];
+    if (plan && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) no_limbs(plan);
+    const int row0 = blockIdx.x * kDaColumnsRows, rows = min(kDaColumnsRows, M - row0);
+    const int words = K / C, per_block = min(words, 256), row_groups = 256 / per_block;
+    const int word = blockIdx.y * per_block + (int)threadIdx.x % per_block, first = (int)threadIdx.x / per_block;
+    for (int i = threadIdx.x; i < kDaColumnsRows * NN; i += 256) {
+        const int r = i / NN, n = i - r * NN;
+        gs[r][n] = r < rows && n < N ? (double)g[(int64_t)(row0 + r) * N + n] : 0.0;
+    }
+    const bool active = word < words && first < row_groups;
+    double b[C][NN];
+#pragma unroll
+    for (int n = 0; n < NN; ++n) {
+        const uint32_t w = active && n < N ? *reinterpret_cast<const uint32_t *>(b_idx + (int64_t)n * K + C * word) : 0u;
+#pragma unroll
+        for (int c = 0; c < C; ++c) b[c][n] = active && n < N ? (double)(int8_t)(w >> (8 * c)) + b_offset : 0.0;      // (the level index itself)
+    }
+    __syncthreads();
+    if (!active) return;
+    for (int r = first; r < rows; r += row_groups) {
+        double acc[C] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int n = 0; n < NN; ++n) {
+            const double v = gs[r][n];
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] = fma(v, b[c][n], acc[c]);
+        }
+        *reinterpret_cast<float4 *>(out + (int64_t)(row0 + r) * K + C * word) =
+            make_float4((float)(acc[0] * delta_b), (float)(acc[1] * delta_b), (float)(acc[2] * delta_b), (float)(acc[3] * delta_b));
+    }
+}
+
 // out[r] = mult * sum_k idx[r][k] + add for an int8 matrix [rows][K]: the corrections of a product whose
 // other operand is stored with an offset.  As many lanes a row as it has chunks of 16 bytes, up to a wave (with a wave for every row most lanes of short ones are idle: forward
 // product of 130000 x 16 x 64 with an offset 31.3 us, byte by byte 26.2, so 17.5; x 1024 58).
@@ -2944,7 +2988,9 @@ int launch_qgemm_bwd(const float *gr, const int8_t *a_idx, const int8_t *b_idx,
 #define CDL_DA_N(NN, STORE) CDL_LAUNCH("da_direct_kernel", stream, (da_direct_kernel<NN, STORE>), grid, dim3(256), STORE == kDaRows || STORE == kDaFlat ? lds : 0, gr, b_idx, M, N, K, col_tiles, blocks, (double)delta_b, (double)b_offset, d_a_hat, words)
 #define CDL_DA(STORE) do { if (N <= 16) CDL_DA_N(16, STORE); else CDL_DA_N(32, STORE); } while (0)
 #define CDL_DA_WIDE(STORE) do { if (N <= 48) CDL_DA_N(48, STORE); else CDL_DA_N(64, STORE); } while (0)
-        if (N > 32) { if (K % 4 == 0) CDL_DA_WIDE(kDaWords); else CDL_DA_WIDE(kDaScalars); }
+        if (da_columns_serves(M, N, K))
+            CDL_LAUNCH("da_direct_kernel", stream, da_columns_kernel, dim3((unsigned)(((int64_t)M + kDaColumnsRows - 1) / kDaColumnsRows), (unsigned)((K / 4 + 255) / 256)), dim3(256), 0, gr, b_idx, M, N, K, (double)delta_b, (double)b_offset, d_a_hat, words.plan);
+        else if (N > 32) { if (K % 4 == 0) CDL_DA_WIDE(kDaWords); else CDL_DA_WIDE(kDaScalars); }
         else if (K % 4 == 0) { if (staged) CDL_DA(kDaRows); else CDL_DA(kDaWords); }
         else if (used == 1 && staged) CDL_DA(kDaFlat);
         else CDL_DA(kDaScalars);

@@ -82,3 +82,14 @@ def test_weight_gradients_that_share_digits(tmp_path, shared, layers):
     """Not short contractions, whose operands stay in the caches: each of those named here was slower (5 to 22 %) so."""
     seen = lr.record(tmp_path, [lr.conv_bwd_weights(1, M, 1, K, N, 1, 1, 1, 0) for M, N, K in layers])
     assert [any("dw_shared_kernel" in l.name for l in s[0]) for s in seen] == [shared] * len(layers)
+
+
+def test_activation_gradients_by_columns(tmp_path):
+    import test_gpu_da_columns as cases
+    assert not any("da_columns_kernel" in l.name for l in lr.record(tmp_path, [lr.gemm_bwd(2, 3, 70_000_004, "a")])[0][0])      # (more blocks than a grid has in y)
+    seen = lr.record(tmp_path, [lr.gemm_bwd(*c[:3], want) for c in cases.CASES for want in ("a", "both")])
+    assert [any("da_columns_kernel" in l.name for l in s[0]) for s in seen] == [c[3] for c in cases.CASES for _ in range(2)]
+    for c, (launches, _) in zip([c for c in cases.CASES for _ in range(2)], seen):
+        for l in launches:
+            if "da_columns_kernel" in l.name:
+                assert l.grid == (-(-c[0] // 128), -(-(c[2] // 4) // 256), 1), (c, l)

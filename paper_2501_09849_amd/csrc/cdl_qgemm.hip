@@ -383,8 +383,9 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks][i], fb[ks][j], FIRST ? zero : acc[i][j], 0, 0, 0);
     };
-    // CORR: operands stored with an offset, corrections per column and row (a copy of its own: a load between the stores makes
-    // every store wait for the one before it)
+    // CORR: operands stored with an offset, corrections per column and row, loaded before the first store (a load between the stores makes every store wait for the one before it): a lane
+    // has its columns' and those of the rows 32 i + (its number in its half), which the others get from it
+    // (us, rows x columns x contraction, staged tiles / loads between the stores / so: 6617 x 480 x 448 13.8 / 21.2 / 12.8, 46255 x 608 x 192 52 / 69 / 29.2, 934088 x 288 x 128 461 / 580 / 258; the kernels without corrections are as they were)
     auto emit = [&](auto full_c, auto corr_c, auto *out, int row0, int col0) {
         constexpr bool FULL = decltype(full_c)::value, CORR = decltype(corr_c)::value;
         using T = std::remove_pointer_t<decltype(out)>;
@@ -395,21 +396,28 @@ __device__ __forceinline__ void ring_tiles(const GemmArgs &a, SOURCE &source, in
         const int half4 = 4 * (elane >> 5), ecol = elane & 31;
         const uint32_t off = 4u * (uint32_t)(half4 * (int)a.ldc + ecol);
         const out_t base = (out_t)out + (int64_t)row0 * a.ldc + col0;
+        int row_corr[TM], col_corr[TN];
+        if (CORR) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) col_corr[j] = a.corr_col && (FULL || col0 + ecol + 32 * j < a.rowsB) ? a.corr_col[col0 + ecol + 32 * j] : 0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) row_corr[i] = a.corr_row && (FULL || row0 + 32 * i + ecol < a.rowsA) ? a.corr_row[row0 + 32 * i + ecol] : 0;
+        }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int dr = i * 32 + 8 * (r >> 2) + (r & 3);
+                const int rc = CORR ? __shfl(row_corr[i], 8 * (r >> 2) + (r & 3) + half4, 64) : 0;      // (all lanes, also those beyond the rows)
                 out_t at = base + (int64_t)dr * a.ldc;
                 asm("" : "+s"(at));          // (a base in scalar registers and the lane's offset)
                 const out_t p = (out_t)((byte_t)at + off);
                 const bool row_ok = FULL || row0 + dr + half4 < a.rowsA;
-                const int rc = CORR && a.corr_row && row_ok ? a.corr_row[row0 + dr + half4] : 0;
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     const bool ok = FULL || (row_ok && col0 + ecol + 32 * j < a.rowsB);
                     if (!ok) continue;
-                    const int v = CORR ? acc[i][j][r] + rc + (a.corr_col ? a.corr_col[col0 + ecol + 32 * j] : 0) : acc[i][j][r];
+                    const int v = CORR ? acc[i][j][r] + rc + col_corr[j] : acc[i][j][r];
                     const T x = std::is_same<T, float>::value ? (T)(a.scale * (float)v) : (T)v;
                     if (FULL && STREAM) __builtin_nontemporal_store(x, p + 32 * j);
                     else p[32 * j] = x;

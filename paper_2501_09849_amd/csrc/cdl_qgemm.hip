@@ -1753,7 +1753,7 @@ void da_direct_kernel(const float *__restrict__ g, const int8_t *__restrict__ b_
     constexpr int C = direct_tiles(NN), H = NN / 16;
     constexpr bool VEC = STORE == kDaWords || STORE == kDaRows, STAGED = STORE == kDaRows || STORE == kDaFlat;
     extern __shared__ __align__(16) float da_lds[];
-    if (words.plan && !words.records && blockIdx.x == 0 && threadIdx.x == 0) no_limbs(words.plan);
+    if (words.plan && (NN <= 32 || !words.records) && blockIdx.x == 0 && threadIdx.x == 0) no_limbs(words.plan);
     const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
     const int group = (int)blockIdx.x / blocks, k0 = group * col_tiles * 16;
     const int tiles = min(col_tiles, (K - k0 + 15) / 16);
